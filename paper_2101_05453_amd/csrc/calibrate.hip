@@ -11,7 +11,9 @@
 // batch row for layer norm, activations and the cell update (wavefront
 // reductions for the row statistics), and the projection GEMM.  Parameters
 // stay float32 in memory (they are float32) and are widened on load; all
-// arithmetic and all activations are double.
+// arithmetic and all activations are double.  The products run on the f64
+// MFMA; while a layer computes, the next layer's parameters are uploaded on a
+// second stream.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -75,15 +77,20 @@ __device__ double block_reduce(double v, double *red) {
   return OP == 0 ? (a + b) + (c + d) : OP == 1 ? fmax(fmax(a, b), fmax(c, d)) : fmin(fmin(a, b), fmin(c, d));
 }
 
-// x float -> double, and its range
-__global__ __launch_bounds__(256) void widen_kernel(const float *x, double *out, int64_t n, double *stats) {
+// x float [rows][cols] -> double [rows][ld] (columns beyond cols zero), and its range
+__global__ __launch_bounds__(256) void widen_kernel(const float *x, double *out, int64_t rows, int cols, int ld, double *stats) {
   __shared__ double red[4];
   double lo = INFINITY, hi = -INFINITY;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-    const double v = x[i];
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < rows * ld; i += (int64_t)gridDim.x * 256) {
+    const int64_t row = i / ld;
+    const int col = (int)(i - row * ld);
+    double v = 0.0;
+    if (col < cols) {
+      v = x[row * cols + col];
+      lo = fmin(lo, v);
+      hi = fmax(hi, v);
+    }
     out[i] = v;
-    lo = fmin(lo, v);
-    hi = fmax(hi, v);
   }
   lo = block_reduce<2>(lo, red);
   hi = block_reduce<1>(hi, red);
@@ -93,11 +100,13 @@ __global__ __launch_bounds__(256) void widen_kernel(const float *x, double *out,
   }
 }
 
-// range of a double buffer into two statistics slots
-__global__ __launch_bounds__(256) void range_kernel(const double *v, int64_t n, double *lo_slot, double *hi_slot) {
+// range of a double buffer [rows][ld], columns below cols, into two statistics slots
+__global__ __launch_bounds__(256) void range_kernel(const double *v, int64_t rows, int cols, int ld, double *lo_slot,
+                                                    double *hi_slot) {
   __shared__ double red[4];
   double lo = INFINITY, hi = -INFINITY;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < rows * ld; i += (int64_t)gridDim.x * 256) {
+    if (i % ld >= cols) continue;
     lo = fmin(lo, v[i]);
     hi = fmax(hi, v[i]);
   }
@@ -109,54 +118,152 @@ __global__ __launch_bounds__(256) void range_kernel(const double *v, int64_t n, 
   }
 }
 
-// C[m][n] = (Cin ? Cin[m][n] : 0) + (bias ? bias[n] : 0) + sum_k A[m][k] * W[n][k]
-// A double [M][lda], W float [Nout][K], C double [M][ldc], Cin double [M][ldcin].
-// Workgroup = 16 rows x 64 columns, thread = 1 row x 4 columns, k in tiles of 32
-// through LDS; the sum over k runs in ascending k within a thread.
-__global__ __launch_bounds__(256) void gemm_kernel(const double *A, int lda, const float *W, double *C, int ldc,
-                                                   const double *Cin, int ldcin, const float *bias, int M, int Nout,
-                                                   int K) {
-  __shared__ double As[16][33];
-  __shared__ double Ws[64][33];
-  const int tid = threadIdx.x, tm = tid >> 4, tn = (tid & 15) << 2;
-  const int m0 = blockIdx.x * 16, n0 = blockIdx.y * 64;
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int k0 = 0; k0 < K; k0 += 32) {
-    for (int i = tid; i < 16 * 32; i += 256) {
-      const int r = i >> 5, k = i & 31;
-      As[r][k] = (m0 + r < M && k0 + k < K) ? A[(size_t)(m0 + r) * lda + k0 + k] : 0.0;
-    }
-    for (int i = tid; i < 64 * 32; i += 256) {
-      const int r = i >> 5, k = i & 31;
-      Ws[r][k] = (n0 + r < Nout && k0 + k < K) ? (double)W[(size_t)(n0 + r) * K + k0 + k] : 0.0;
-    }
-    __syncthreads();
-#pragma unroll 8
-    for (int k = 0; k < 32; ++k) {
-      const double a = As[tm][k];
+typedef double v4d __attribute__((ext_vector_type(4)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+inline int64_t up16(int64_t v) { return (v + 15) / 16 * 16; }
+
+// Weights [rows][K] (dense, as the caller has them) -> MFMA order [rows / 16][K / 16][64 lanes][4], zero beyond the
+// real extents: lane (r, q) = r + 16 q of chunk c holds W[16 tile + r][16 c + 4 q + 0..3].  A wave's load of one chunk
+// is then one contiguous KB, and the product kernels need no edge tests on the weights.  Done once per layer: 21 MB
+// in and out at 8192 x 640, about 10 us against 64 steps that read the result.
+__global__ __launch_bounds__(256) void repack_kernel(const float *W, float *op, int rows, int K, int64_t vecs) {
+  const int chunks = (K + 15) >> 4;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < vecs; i += (int64_t)gridDim.x * 256) {
+    const int lane = (int)(i & 63);
+    const int64_t tc = i >> 6;
+    const int64_t row = tc / chunks * 16 + (lane & 15);
+    const int k = (int)(tc % chunks) * 16 + 4 * (lane >> 4);
+    v4f v = {0.f, 0.f, 0.f, 0.f};
+    if (row < rows) {
+      const float *src = W + row * K + k;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[j] = fma(a, Ws[tn + j][k], acc[j]);
+      for (int j = 0; j < 4; ++j)
+        if (k + j < K) v[j] = src[j];
     }
-    __syncthreads();
+    reinterpret_cast<v4f *>(op)[i] = v;
   }
-  const int m = m0 + tm;
-  if (m >= M) return;
+}
+
+// C[m][n] = (Cin ? Cin[m][n] : 0) + (bias ? bias[n] : 0) + sum_k A[m][k] * W[n][k] on v_mfma_f64_16x16x4: A double
+// [M][lda] with lda a multiple of 16 and zero columns beyond K, W in the order of repack_kernel, C double [M][ldc].
+// A wave computes MT x NT tiles of 16 x 16; the k chunks of 16 are split over WK waves whose sums meet in LDS.  The
+// four MFMAs of a chunk take k = 4 q + j, j = 0..3, from lane group q (any assignment of k to the instructions' slots
+// gives the same sum), so that a lane's operands are 16 contiguous bytes of W and 32 of A.  U chunks are loaded
+// together, with PIPE ahead of the U being multiplied.  Result value i of lane (c, q) is row 4 i + q, column c.
+// Bound: 2 M Nout K / 70 TFLOP/s (measured for the library's f64 product on this chip) for the hoisted product, the
+// latency of one weight read for a step's (its 21 MB come from the Infinity Cache at every step).
+template <int MT, int NT, int WM, int WN, int WK, int U, bool PIPE>
+__global__ __launch_bounds__(64 * WM * WN * WK) void gemm_kernel(const double *A, int lda, const float *W, int chunks,
+                                                                 double *C, int64_t ldc, const double *Cin,
+                                                                 int64_t ldcin, const float *bias, int M, int Nout) {
+  extern __shared__ double part[];  // WK > 1: [WM * WN][WK][MT * NT * 4][64]
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r = lane & 15, q = lane >> 4;
+  const int wk = wave % WK, wn = wave / WK % WN, wm = wave / (WK * WN);
+  const int m0 = (blockIdx.y * WM + wm) * MT * 16, t0 = (blockIdx.x * WN + wn) * NT;
+  const int tiles = (Nout + 15) >> 4;
+  const double *ap[MT];
+  const v4f *wp[NT];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int n = n0 + tn + j;
-    if (n >= Nout) continue;
-    double v = acc[j];
-    if (Cin) v += Cin[(size_t)m * ldcin + n];
+  for (int i = 0; i < MT; ++i) {
+    const int m = m0 + 16 * i + r;
+    ap[i] = A + (size_t)(m < M ? m : M - 1) * lda + 4 * q;  // rows beyond M repeat the last one and are not stored
+  }
+#pragma unroll
+  for (int i = 0; i < NT; ++i) {
+    const int t = t0 + i < tiles ? t0 + i : tiles - 1;
+    wp[i] = reinterpret_cast<const v4f *>(W) + (size_t)t * chunks * 64 + lane;
+  }
+  v4d acc[MT][NT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
+  const int per = (chunks + WK - 1) / WK;
+  const int c0 = wk * per, c1 = c0 + per < chunks ? c0 + per : chunks;
+  v4d a[U][MT];
+  v4f w[U][NT];
+  auto load = [&](int c, v4d (&av)[U][MT], v4f (&wv)[U][NT]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int cc = c + u < c1 ? c + u : c1 - 1;
+#pragma unroll
+      for (int i = 0; i < NT; ++i) wv[u][i] = wp[i][(size_t)cc * 64];
+#pragma unroll
+      for (int i = 0; i < MT; ++i) av[u][i] = *reinterpret_cast<const v4d *>(ap[i] + (size_t)cc * 16);
+    }
+  };
+  if (c0 < c1) {
+    load(c0, a, w);
+    for (int c = c0; c < c1; c += U) {
+      v4d an[U][MT];
+      v4f wn_[U][NT];
+      if (PIPE && c + U < c1) load(c + U, an, wn_);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const bool live = c + u < c1;  // uniform over the wave
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int n = 0; n < NT; ++n) {
+            const double wd = live ? (double)w[u][n][j] : 0.0;
+#pragma unroll
+            for (int m = 0; m < MT; ++m) acc[m][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][m][j], wd, acc[m][n], 0, 0, 0);
+          }
+      }
+      if constexpr (PIPE) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+          for (int i = 0; i < MT; ++i) a[u][i] = an[u][i];
+#pragma unroll
+          for (int i = 0; i < NT; ++i) w[u][i] = wn_[u][i];
+        }
+      } else if (c + U < c1) {
+        load(c + U, a, w);
+      }
+    }
+  }
+  auto store = [&](int mt, int nt, int i, double v) {
+    const int m = m0 + 16 * mt + 4 * i + q, n = (t0 + nt) * 16 + r;
+    if (m >= M || n >= Nout) return;
+    if (Cin) v += Cin[m * ldcin + n];
     if (bias) v += (double)bias[n];
-    C[(size_t)m * ldc + n] = v;
+    C[m * ldc + n] = v;
+  };
+  if constexpr (WK == 1) {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) store(mt, nt, i, acc[mt][nt][i]);
+  } else {
+    constexpr int V = MT * NT * 4;
+    double *mine = part + ((size_t)(wm * WN + wn) * WK) * V * 64 + lane;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) mine[(wk * V + (mt * NT + nt) * 4 + i) * 64] = acc[mt][nt][i];
+    __syncthreads();
+    for (int v = wk; v < V; v += WK) {  // the WK waves share the tile's values
+      double sum = 0.0;
+#pragma unroll
+      for (int k = 0; k < WK; ++k) sum += mine[(k * V + v) * 64];
+      store(v / (4 * NT), v / 4 % NT, v & 3, sum);
+    }
   }
 }
 
 struct CellArgs {
   double *pre;    // [B][4*N] gate sums W x + R h of this step, slot per gate; overwritten
   double *c;      // [B][N] cell state, in/out
-  double *m;      // [B][N] hidden state out
-  double *h;      // [B][N] also receives m when there is no projection, else NULL
+  double *m;      // [B][ld_m] hidden state out (the layer output itself when there is no projection)
+  int64_t ld_m;
   const float *b[4], *P[3], *Lw[4];
   int N, flags;
   double *stats;
@@ -164,8 +271,147 @@ struct CellArgs {
 
 __device__ double sigmoid_f64(double v) { return 1.0 / (1.0 + exp(-v)); }
 
-// One workgroup per batch row: eqs. (1)-(6) of Sec. 2 after the matrix
-// products.  Gates f, z, i from c^{t-1}; the cell update; gate o from c^t; m.
+// K sums over a workgroup of 8 waves; every thread gets them.  red: K * 8 doubles that nobody still reads.
+template <int K>
+__device__ void block_sum8(double (&v)[K], double *red) {
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    const double s = wave_sum(v[i]);
+    if ((threadIdx.x & 63) == 0) red[i * 8 + (threadIdx.x >> 6)] = s;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) s += red[i * 8 + w];
+    v[i] = s;
+  }
+}
+
+// Eqs. (1)-(6) of Sec. 2 after the matrix products, for rows of up to 512 E cells.  gridDim.y workgroups share a batch
+// row: each takes the layer norm's mean and deviation over the whole row (its values in registers, the gates that do
+// not wait for the new cell state in one pair of reductions) and then a slice of the cells -- five double exp / tanh
+// per cell are the bulk of the work, and one workgroup per row would leave all but 16 compute units idle at the
+// default calibration batch.  With peephole and layer norm the o gate's statistics need the whole new cell state, so
+// gridDim.y is 1 there (and without a peephole nobody reads the c of another slice).
+template <int E>
+__global__ __launch_bounds__(512) void cell_row_kernel(CellArgs a) {
+  __shared__ double red[4][4 * 8], top[7 * 8], act[4][128];
+  const int b = blockIdx.x, tid = threadIdx.x, N = a.N, wave = tid >> 6;
+  const bool cifg = a.flags & kCifg, ph = a.flags & kPeephole, ln = a.flags & kLayerNorm;
+  const double *pre = a.pre + (size_t)b * 4 * N;
+  double *crow = a.c + (size_t)b * N;
+  const int g0 = cifg ? 1 : 0;
+  double amax[4] = {0.0, 0.0, 0.0, 0.0}, mean[4], sd[4];
+  // gate sum of cell n before the norm; cell: c^{t-1}, or c^t for the o gate
+  auto gate_sum = [&](int g, int n, double cell) {
+    double v = pre[(size_t)g * N + n];
+    if (ph && g != 2) v += (double)a.P[g == 3 ? 2 : g][n] * cell;
+    return v;
+  };
+  // layer-norm statistics of the gates of `mask`: mean, sd (0 where the row is constant)
+  auto statistics = [&](int mask, double *r0, double *r1) {
+    double v[4][E], s[4] = {0.0, 0.0, 0.0, 0.0}, sq[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int n = tid + 512 * e;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) v[g][e] = (mask >> g & 1) && n < N ? gate_sum(g, n, ph ? crow[n] : 0.0) : 0.0;
+    }
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        s[g] += v[g][e];
+        amax[g] = fmax(amax[g], fabs(v[g][e]));
+      }
+    block_sum8(s, r0);
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      if (mask >> g & 1) {
+        mean[g] = s[g] / N;
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+          if (tid + 512 * e < N) sq[g] += (v[g][e] - mean[g]) * (v[g][e] - mean[g]);
+      }
+    block_sum8(sq, r1);
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      if (mask >> g & 1) sd[g] = sqrt(sq[g] / N);
+  };
+  auto norm = [&](int g, int n, double v) {
+    if (ln) v = sd[g] > 0.0 ? (v - mean[g]) / sd[g] * (double)a.Lw[g][n] : 0.0;
+    return v + (double)a.b[g][n];
+  };
+  if (ln) statistics((cifg ? 0 : 1) | 2 | 4 | (ph ? 0 : 8), red[0], red[1]);
+  // 128 cells at a time, one gate per wave pair: the activations are long chains of dependent double instructions, so
+  // the gates of a cell run side by side and meet in LDS
+  const int gate = tid >> 7, cell = tid & 127;
+  const bool late_o = ph && ln;  // gridDim.y == 1
+  const int blocks = (N + 127) >> 7;
+  double cmax = 0.0, lo = INFINITY, hi = -INFINITY;
+  for (int blk = blockIdx.y; blk < blocks; blk += gridDim.y) {
+    const int n = blk * 128 + cell;
+    const bool live = n < N;
+    const double c0 = live ? crow[n] : 0.0;
+    if (live && gate >= g0 && gate != 3) {
+      const double v = norm(gate, n, gate_sum(gate, n, c0));
+      act[gate][cell] = gate == 2 ? tanh(v) : sigmoid_f64(v);
+    } else if (live && gate == 3 && !ph) {
+      act[3][cell] = sigmoid_f64(norm(3, n, gate_sum(3, n, 0.0)));
+    }
+    __syncthreads();
+    if (live && gate == 0) {
+      const double f = act[1][cell], i = cifg ? 1.0 - f : act[0][cell];
+      const double c = i * act[2][cell] + f * c0;
+      crow[n] = c;
+      cmax = fmax(cmax, fabs(c));
+      if (!late_o) {
+        const double o = ph ? sigmoid_f64(norm(3, n, gate_sum(3, n, c))) : act[3][cell];
+        const double mv = o * tanh(c);
+        a.m[b * a.ld_m + n] = mv;
+        lo = fmin(lo, mv);
+        hi = fmax(hi, mv);
+      }
+    }
+    __syncthreads();
+  }
+  if (late_o) {  // every c of the row is there
+    statistics(8, red[2], red[3]);
+    for (int n = tid; n < N; n += 512) {
+      const double c = crow[n];
+      const double mv = sigmoid_f64(norm(3, n, gate_sum(3, n, c))) * tanh(c);
+      a.m[b * a.ld_m + n] = mv;
+      lo = fmin(lo, mv);
+      hi = fmax(hi, mv);
+    }
+  }
+  // ranges: one value per wave into LDS, the last step by seven threads
+  const double t[7] = {amax[0], amax[1], amax[2], amax[3], cmax, hi, -lo};
+#pragma unroll
+  for (int i = 0; i < 7; ++i) {
+    const double w = wave_max(t[i]);
+    if ((tid & 63) == 0) top[i * 8 + wave] = w;
+  }
+  __syncthreads();
+  if (tid < 7) {
+    double w = top[tid * 8];
+    for (int i = 1; i < 8; ++i) w = fmax(w, top[tid * 8 + i]);
+    if (tid < 4) {
+      if (ln && tid >= g0) atomic_max_f64(a.stats + S_GABS + tid, w);
+    } else if (tid == 4) {
+      atomic_max_f64(a.stats + S_CABS, w);
+    } else if (tid == 5) {
+      atomic_max_f64(a.stats + S_MMAX, w);
+    } else {
+      atomic_min_f64(a.stats + S_MMIN, -w);
+    }
+  }
+}
+
+// The same for rows too wide for registers: gate by gate through memory.
+// Gates f, z, i from c^{t-1}; the cell update; gate o from c^t; m.
 __global__ __launch_bounds__(256) void cell_kernel(CellArgs a) {
   __shared__ double red[4];
   const int b = blockIdx.x, tid = threadIdx.x, N = a.N;
@@ -218,8 +464,7 @@ __global__ __launch_bounds__(256) void cell_kernel(CellArgs a) {
   double lo = INFINITY, hi = -INFINITY;
   for (int n = tid; n < N; n += 256) {
     const double mv = pre[3 * (size_t)N + n] * tanh(c[n]);
-    a.m[(size_t)b * N + n] = mv;
-    if (a.h) a.h[(size_t)b * N + n] = mv;
+    a.m[b * a.ld_m + n] = mv;
     lo = fmin(lo, mv);
     hi = fmax(hi, mv);
   }
@@ -232,30 +477,59 @@ __global__ __launch_bounds__(256) void cell_kernel(CellArgs a) {
   }
 }
 
-struct DevBuf {
-  void *p = nullptr;
-  DevBuf() = default;
-  DevBuf(const DevBuf &) = delete;
-  DevBuf &operator=(const DevBuf &) = delete;
-  ~DevBuf() {
-    if (p) (void)hipFree(p);
-  }
-  void swap(DevBuf &o) {
-    void *t = p;
-    p = o.p;
-    o.p = t;
-  }
-  hipError_t alloc(size_t bytes) { return hipMalloc(&p, bytes ? bytes : 256); }
-  template <class T>
-  T *as() const {
-    return static_cast<T *>(p);
+// What a call holds on the device and in the runtime; gone when the call ends, in whatever way (nothing may still
+// be running on the memory then).
+struct Held {
+  hipStream_t s = nullptr, copy = nullptr;
+  hipEvent_t uploaded = nullptr, repacked = nullptr;
+  uint8_t *arena = nullptr;
+  ~Held() {
+    if (copy) (void)hipStreamSynchronize(copy);
+    if (arena) (void)hipStreamSynchronize(s);
+    if (uploaded) (void)hipEventDestroy(uploaded);
+    if (repacked) (void)hipEventDestroy(repacked);
+    if (copy) (void)hipStreamDestroy(copy);
+    if (arena) (void)hipFree(arena);
   }
 };
 
-void launch_gemm(hipStream_t s, const double *A, int lda, const float *W, double *C, int ldc, const double *Cin,
-                 int ldcin, const float *bias, int M, int Nout, int K) {
-  dim3 grid((M + 15) / 16, (Nout + 63) / 64);
-  hipLaunchKernelGGL(gemm_kernel, grid, dim3(256), 0, s, A, lda, W, C, ldc, Cin, ldcin, bias, M, Nout, K);
+// One product.  M rows against Nout rows of weights in repack_kernel's order (K = the real depth).
+//   * Enough 128 x 128 blocks to fill half of the chip: four waves of 64 x 64, the rate of the matrix cores bounds it.
+//   * else 16 or 32 rows x 32 columns per workgroup, k split over its four waves: a step's product at N = 2048 is
+//     256 workgroups, each one weight read deep.
+//   * Few columns and a long k (the projection of a step): 16 x 16 per workgroup, k split over 16 waves.
+void launch_gemm(hipStream_t s, const double *A, int lda, const float *W, double *C, int64_t ldc, const double *Cin,
+                 int64_t ldcin, const float *bias, int M, int Nout, int K) {
+  const int chunks = (K + 15) / 16;
+  auto go = [&](auto kernel, int mb, int nb, int waves, size_t lds) {
+    hipLaunchKernelGGL(kernel, dim3((Nout + nb - 1) / nb, (M + mb - 1) / mb), dim3(64 * waves), lds, s, A, lda, W, chunks, C,
+                       ldc, Cin, ldcin, bias, M, Nout);
+  };
+  if ((int64_t)((M + 127) / 128) * ((Nout + 127) / 128) >= 128)
+    go(gemm_kernel<4, 4, 2, 2, 1, 1, true>, 128, 128, 4, 0);
+  else if (M > 16)
+    go(gemm_kernel<2, 2, 1, 1, 4, 3, true>, 32, 32, 4, 4 * 16 * 64 * 8);
+  else if (Nout <= 2048 && K >= 512)
+    go(gemm_kernel<1, 1, 1, 1, 16, 8, false>, 16, 16, 16, 16 * 4 * 64 * 8);
+  else
+    go(gemm_kernel<1, 2, 1, 1, 4, 5, true>, 16, 32, 4, 4 * 8 * 64 * 8);
+}
+
+void launch_cell(hipStream_t s, const CellArgs &a, int B) {
+  // slices: up to the 256 compute units, at least 128 cells each
+  const bool whole_row = (a.flags & kPeephole) && (a.flags & kLayerNorm);
+  const int slices = whole_row ? 1 : std::max(1, std::min(256 / B, (a.N + 127) / 128));
+  const dim3 grid(B, slices), block(512);
+  if (a.N <= 512)
+    hipLaunchKernelGGL(cell_row_kernel<1>, grid, block, 0, s, a);
+  else if (a.N <= 1024)
+    hipLaunchKernelGGL(cell_row_kernel<2>, grid, block, 0, s, a);
+  else if (a.N <= 2048)
+    hipLaunchKernelGGL(cell_row_kernel<4>, grid, block, 0, s, a);
+  else if (a.N <= 4096)
+    hipLaunchKernelGGL(cell_row_kernel<8>, grid, block, 0, s, a);
+  else
+    hipLaunchKernelGGL(cell_kernel, dim3(B), dim3(256), 0, s, a);
 }
 
 }  // namespace
@@ -283,77 +557,120 @@ extern "C" int lstm_int_calibrate(const lstm_int_layer_params *layers, int32_t n
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   const int64_t TB = (int64_t)T * B;
 
-  DevBuf in, stats;
-  if (in.alloc(sizeof(double) * TB * layers[0].input_size) != hipSuccess) return LSTM_INT_E_OUT_OF_MEMORY;
-  if (stats.alloc(sizeof(double) * S_COUNT * num_layers) != hipSuccess) return LSTM_INT_E_OUT_OF_MEMORY;
-  {
-    std::vector<double> init((size_t)S_COUNT * num_layers, 0.0);
-    for (int l = 0; l < num_layers; ++l) {
-      double *st = init.data() + (size_t)l * S_COUNT;
-      st[S_XMIN] = st[S_HMIN] = st[S_MMIN] = INFINITY;
-      st[S_XMAX] = st[S_HMAX] = st[S_MMAX] = -INFINITY;
-    }
-    if (hipMemcpyAsync(stats.p, init.data(), init.size() * sizeof(double), hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-      return LSTM_INT_E_DEVICE;
-  }
-  const int64_t n_in0 = TB * layers[0].input_size;
-  hipLaunchKernelGGL(widen_kernel, dim3((unsigned)std::min<int64_t>((n_in0 + 255) / 256, 1024)), dim3(256), 0, s, x,
-                     in.as<double>(), n_in0, stats.as<double>());
 
-  DevBuf prev_out;  // the output of the layer before: the input of the layer at work
-  double *cur_in = in.as<double>();
+  // One allocation for the whole call (each one costs about 0.1 ms to make and 0.3 ms to give back): the extents of
+  // every region are the largest over the layers.  Activation rows have a multiple of 16 doubles, zero beyond the
+  // real columns.
+  size_t total = 0;
+  auto take = [&](size_t bytes) {
+    const size_t o = total;
+    total += (bytes + 255) & ~(size_t)255;
+    return o;
+  };
+  size_t raw_f = 0, wop_f = 0, rop_f = 0, pop_f = 0, vec_f = 0, wx_d = 0, act_d = 0, m_d = 0, c_d = 0, pre_d = 0, h_d = 0;
+  for (int l = 0; l < num_layers; ++l) {
+    const size_t I = layers[l].input_size, N = layers[l].num_cells, H = layers[l].output_size;
+    const bool proj = layers[l].flags & kProjection;
+    raw_f = std::max(raw_f, 4 * N * (I + H) + (proj ? H * N : 0));
+    wop_f = std::max<size_t>(wop_f, up16(4 * N) * up16(I));
+    rop_f = std::max<size_t>(rop_f, up16(4 * N) * up16(H));
+    if (proj) pop_f = std::max<size_t>(pop_f, up16(H) * up16(N));
+    vec_f = std::max(vec_f, 11 * N + H);
+    wx_d = std::max(wx_d, (size_t)TB * 4 * N);
+    act_d = std::max<size_t>(act_d, TB * std::max(up16(I), up16(H)));
+    m_d = std::max<size_t>(m_d, B * up16(N));
+    h_d = std::max<size_t>(h_d, B * up16(H));
+    c_d = std::max<size_t>(c_d, (size_t)B * N);
+    pre_d = std::max<size_t>(pre_d, (size_t)B * 4 * N);
+  }
+  const size_t o_stats = take(sizeof(double) * S_COUNT * num_layers), o_raw = take(4 * raw_f), o_wop = take(4 * wop_f),
+               o_rop = take(4 * rop_f), o_pop = take(4 * pop_f), o_vec0 = take(4 * vec_f), o_vec1 = take(4 * vec_f),
+               o_wx = take(8 * wx_d), o_act0 = take(8 * act_d), o_act1 = take(8 * act_d), o_m = take(8 * m_d),
+               o_h0 = take(8 * h_d), o_c = take(8 * c_d), o_pre = take(8 * pre_d);
+  std::vector<std::vector<float>> vectors(num_layers);  // outlives the copies: declared ahead of what waits for them
+  std::vector<double> init((size_t)S_COUNT * num_layers, 0.0);
+  Held held;
+  held.s = s;
+  if (hipMalloc(reinterpret_cast<void **>(&held.arena), total) != hipSuccess) {
+    held.arena = nullptr;
+    return LSTM_INT_E_OUT_OF_MEMORY;
+  }
+  if (hipStreamCreateWithFlags(&held.copy, hipStreamNonBlocking) != hipSuccess ||
+      hipEventCreateWithFlags(&held.uploaded, hipEventDisableTiming) != hipSuccess ||
+      hipEventCreateWithFlags(&held.repacked, hipEventDisableTiming) != hipSuccess)
+    return LSTM_INT_E_DEVICE;
+  auto dbl = [&](size_t o) { return reinterpret_cast<double *>(held.arena + o); };
+  auto flt = [&](size_t o) { return reinterpret_cast<float *>(held.arena + o); };
+  double *const stats = dbl(o_stats);
+  for (int l = 0; l < num_layers; ++l) {
+    double *st = init.data() + (size_t)l * S_COUNT;
+    st[S_XMIN] = st[S_HMIN] = st[S_MMIN] = INFINITY;
+    st[S_XMAX] = st[S_HMAX] = st[S_MMAX] = -INFINITY;
+  }
+  if (hipMemcpyAsync(stats, init.data(), init.size() * sizeof(double), hipMemcpyHostToDevice, s) != hipSuccess)
+    return LSTM_INT_E_DEVICE;
+  const int blocks = 256;  // of the range kernels: each ends with two compare-and-swap loops on the same words
+  double *cur = dbl(o_act0), *next = dbl(o_act1);
+  hipLaunchKernelGGL(widen_kernel, dim3(blocks), dim3(256), 0, s, x, cur, TB, layers[0].input_size,
+                     (int)up16(layers[0].input_size), stats);
+
+  // Parameters of layer l into the raw buffer, on the copy stream: gates first..3 of W, then of R, then W_proj.  The
+  // copies from pageable memory hold the host (13 ms for the 377 MB of an 8-layer encoder), during which the layer
+  // before computes.
+  auto upload = [&](int l) {
+    const lstm_int_layer_params &p = layers[l];
+    const size_t I = p.input_size, N = p.num_cells, H = p.output_size, first = (p.flags & kCifg) ? 1 : 0;
+    bool ok = l == 0 || hipStreamWaitEvent(held.copy, held.repacked, 0) == hipSuccess;  // the raw buffer is free again
+    auto up = [&](void *dst, const void *src, size_t bytes) {
+      ok = ok && hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, held.copy) == hipSuccess;
+    };
+    float *raw = flt(o_raw);
+    for (size_t g = first; g < 4; ++g, raw += N * I) up(raw, p.W[g], sizeof(float) * N * I);
+    for (size_t g = first; g < 4; ++g, raw += N * H) up(raw, p.R[g], sizeof(float) * N * H);
+    if (p.flags & kProjection) up(raw, p.Wproj, sizeof(float) * H * N);
+    std::vector<float> &hv = vectors[l];  // b[4], P[3], Lw[4], bproj
+    hv.assign(11 * N + H, 0.0f);
+    for (size_t g = first; g < 4; ++g) {
+      std::copy(p.b[g], p.b[g] + N, hv.begin() + g * N);
+      if (p.flags & kLayerNorm) std::copy(p.Lw[g], p.Lw[g] + N, hv.begin() + (7 + g) * N);
+      if ((p.flags & kPeephole) && g < 3) std::copy(p.P[g], p.P[g] + N, hv.begin() + (4 + g) * N);
+    }
+    if ((p.flags & kProjection) && p.bproj) std::copy(p.bproj, p.bproj + H, hv.begin() + 11 * N);
+    up(flt(l & 1 ? o_vec1 : o_vec0), hv.data(), sizeof(float) * hv.size());
+    return ok && hipEventRecord(held.uploaded, held.copy) == hipSuccess;
+  };
+  auto repack = [&](const float *src, float *op, int rows, int K) {
+    const int64_t vecs = (int64_t)up16(rows) * up16(K) / 4;
+    hipLaunchKernelGGL(repack_kernel, dim3((unsigned)std::min<int64_t>((vecs + 255) / 256, 4096)), dim3(256), 0, s, src, op,
+                       rows, K, vecs);
+  };
+
+  if (!upload(0)) return LSTM_INT_E_DEVICE;
   for (int l = 0; l < num_layers; ++l) {
     const lstm_int_layer_params &p = layers[l];
-    const int I = p.input_size, N = p.num_cells, H = p.output_size, first = (p.flags & kCifg) ? 1 : 0;
-    const bool ph = p.flags & kPeephole, ln = p.flags & kLayerNorm, proj = p.flags & kProjection;
-    double *st = stats.as<double>() + (size_t)l * S_COUNT;
-
-    // parameters -> device; gate matrices concatenated [4][N][.] (slot 0 unused under CIFG)
-    DevBuf Wd, Rd, vec, Wpd, wx, pre, c, m, h0;
-    DevBuf out;
-    const size_t nvec = (size_t)(4 + 3 + 4) * N + H;  // b[4], P[3], Lw[4], bproj
-    if (Wd.alloc(sizeof(float) * 4 * N * I) != hipSuccess || Rd.alloc(sizeof(float) * 4 * (size_t)N * H) != hipSuccess ||
-        vec.alloc(sizeof(float) * nvec) != hipSuccess || wx.alloc(sizeof(double) * TB * 4 * N) != hipSuccess ||
-        pre.alloc(sizeof(double) * B * 4 * (size_t)N) != hipSuccess || c.alloc(sizeof(double) * (size_t)B * N) != hipSuccess ||
-        m.alloc(sizeof(double) * (size_t)B * N) != hipSuccess || h0.alloc(sizeof(double) * (size_t)B * H) != hipSuccess ||
-        out.alloc(sizeof(double) * TB * H) != hipSuccess || (proj && Wpd.alloc(sizeof(float) * (size_t)H * N) != hipSuccess))
-      return LSTM_INT_E_OUT_OF_MEMORY;
-    std::vector<float> hv(nvec, 0.0f);
-    bool ok = true;
-    auto up = [&](void *dst, const void *src, size_t bytes) {
-      ok = ok && hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s) == hipSuccess;
-    };
-    for (int g = first; g < 4; ++g) {
-      up(Wd.as<float>() + (size_t)g * N * I, p.W[g], sizeof(float) * N * I);
-      up(Rd.as<float>() + (size_t)g * N * H, p.R[g], sizeof(float) * (size_t)N * H);
-      for (int n = 0; n < N; ++n) hv[(size_t)g * N + n] = p.b[g][n];
-      if (ln)
-        for (int n = 0; n < N; ++n) hv[(size_t)(7 + g) * N + n] = p.Lw[g][n];
-    }
-    if (ph)
-      for (int j = first; j < 3; ++j)
-        for (int n = 0; n < N; ++n) hv[(size_t)(4 + j) * N + n] = p.P[j][n];
-    if (proj) {
-      up(Wpd.p, p.Wproj, sizeof(float) * (size_t)H * N);
-      if (p.bproj)
-        for (int j = 0; j < H; ++j) hv[(size_t)11 * N + j] = p.bproj[j];
-    }
-    up(vec.p, hv.data(), sizeof(float) * nvec);
-    ok = ok && hipMemsetAsync(c.p, 0, sizeof(double) * (size_t)B * N, s) == hipSuccess;
-    ok = ok && hipMemsetAsync(h0.p, 0, sizeof(double) * (size_t)B * H, s) == hipSuccess;
-    // the host vectors and the caller's arrays must outlive the copies
-    ok = ok && hipStreamSynchronize(s) == hipSuccess;
+    const int I = p.input_size, N = p.num_cells, H = p.output_size, first = (p.flags & kCifg) ? 1 : 0, G = 4 - first;
+    const bool proj = p.flags & kProjection;
+    const int Ip = (int)up16(I), Np = (int)up16(N), Hp = (int)up16(H);
+    double *st = stats + (size_t)l * S_COUNT;
+    bool ok = hipStreamWaitEvent(s, held.uploaded, 0) == hipSuccess;
+    const float *raw = flt(o_raw);
+    repack(raw, flt(o_wop), G * N, I);
+    repack(raw + (size_t)G * N * I, flt(o_rop), G * N, H);
+    if (proj) repack(raw + (size_t)G * N * (I + H), flt(o_pop), H, N);
+    ok = ok && hipEventRecord(held.repacked, s) == hipSuccess;
+    ok = ok && hipMemsetAsync(dbl(o_c), 0, sizeof(double) * (size_t)B * N, s) == hipSuccess;
+    ok = ok && hipMemsetAsync(dbl(o_h0), 0, sizeof(double) * (size_t)B * Hp, s) == hipSuccess;
+    if (proj && Np != N) ok = ok && hipMemsetAsync(dbl(o_m), 0, sizeof(double) * (size_t)B * Np, s) == hipSuccess;
+    if (Hp != H) ok = ok && hipMemsetAsync(next, 0, sizeof(double) * TB * Hp, s) == hipSuccess;
     if (!ok) return LSTM_INT_E_DEVICE;
 
-    const float *vb = vec.as<float>();
+    const float *vb = flt(l & 1 ? o_vec1 : o_vec0);
+    double *wx = dbl(o_wx), *pre = dbl(o_pre);
     // W x for all steps (eqs. 1-4, first term), gates first..3 in one product
-    launch_gemm(s, cur_in, I, Wd.as<float>() + (size_t)first * N * I, wx.as<double>() + (size_t)first * N, 4 * N,
-                nullptr, 0, nullptr, (int)TB, (4 - first) * N, I);
+    launch_gemm(s, cur, Ip, flt(o_wop), wx, G * (int64_t)N, nullptr, 0, nullptr, (int)TB, G * N, I);
     CellArgs ca;
-    ca.pre = pre.as<double>();
-    ca.c = c.as<double>();
-    ca.m = m.as<double>();
+    ca.pre = pre;
+    ca.c = dbl(o_c);
     for (int g = 0; g < 4; ++g) {
       ca.b[g] = vb + (size_t)g * N;
       ca.Lw[g] = vb + (size_t)(7 + g) * N;
@@ -363,30 +680,31 @@ extern "C" int lstm_int_calibrate(const lstm_int_layer_params *layers, int32_t n
     ca.flags = (int)p.flags;
     ca.stats = st;
     for (int t = 0; t < T; ++t) {
-      const double *hp = t == 0 ? h0.as<double>() : out.as<double>() + (size_t)(t - 1) * B * H;
-      double *ho = out.as<double>() + (size_t)t * B * H;
+      const double *hp = t == 0 ? dbl(o_h0) : next + (size_t)(t - 1) * B * Hp;
+      double *ho = next + (size_t)t * B * Hp;
       // + R h^{t-1}
-      launch_gemm(s, hp, H, Rd.as<float>() + (size_t)first * N * H, pre.as<double>() + (size_t)first * N, 4 * N,
-                  wx.as<double>() + (size_t)t * B * 4 * N + (size_t)first * N, 4 * N, nullptr, B, (4 - first) * N, H);
-      ca.h = proj ? nullptr : ho;
-      hipLaunchKernelGGL(cell_kernel, dim3(B), dim3(256), 0, s, ca);
+      launch_gemm(s, hp, Hp, flt(o_rop), pre + (size_t)first * N, 4 * (int64_t)N, wx + (size_t)t * B * G * N, G * (int64_t)N,
+                  nullptr, B, G * N, H);
+      ca.m = proj ? dbl(o_m) : ho;
+      ca.ld_m = Np;  // without a projection N = H
+      launch_cell(s, ca, B);
       if (proj)  // eq. (7)
-        launch_gemm(s, m.as<double>(), N, Wpd.as<float>(), ho, H, nullptr, 0, vb + (size_t)11 * N, B, H, N);
+        launch_gemm(s, dbl(o_m), Np, flt(o_pop), ho, Hp, nullptr, 0, vb + (size_t)11 * N, B, H, N);
     }
-    const int64_t n_out = TB * H;
-    hipLaunchKernelGGL(range_kernel, dim3((unsigned)std::min<int64_t>((n_out + 255) / 256, 1024)), dim3(256), 0, s,
-                       out.as<double>(), n_out, st + S_HMIN, st + S_HMAX);
-    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) return LSTM_INT_E_DEVICE;
-    if (l == num_layers - 1 && y_float &&
-        hipMemcpy(y_float, out.p, sizeof(double) * n_out, hipMemcpyDeviceToDevice) != hipSuccess)
+    hipLaunchKernelGGL(range_kernel, dim3(blocks), dim3(256), 0, s, next, TB, H, Hp, st + S_HMIN, st + S_HMAX);
+    if (hipGetLastError() != hipSuccess) return LSTM_INT_E_DEVICE;
+    if (l + 1 < num_layers) {
+      if (!upload(l + 1)) return LSTM_INT_E_DEVICE;
+    } else if (y_float && hipMemcpy2DAsync(y_float, sizeof(double) * H, next, sizeof(double) * Hp, sizeof(double) * H, TB,
+                                           hipMemcpyDeviceToDevice, s) != hipSuccess) {
       return LSTM_INT_E_DEVICE;
-    // this layer's output is the next layer's input (the one before it is freed with `out`)
-    prev_out.swap(out);
-    cur_in = prev_out.as<double>();
+    }
+    std::swap(cur, next);  // this layer's output is the next layer's input
   }
+  if (hipStreamSynchronize(s) != hipSuccess) return LSTM_INT_E_DEVICE;
 
   std::vector<double> hs((size_t)S_COUNT * num_layers);
-  if (hipMemcpy(hs.data(), stats.p, hs.size() * sizeof(double), hipMemcpyDeviceToHost) != hipSuccess)
+  if (hipMemcpy(hs.data(), stats, hs.size() * sizeof(double), hipMemcpyDeviceToHost) != hipSuccess)
     return LSTM_INT_E_DEVICE;
   for (int l = 0; l < num_layers; ++l) {
     const double *st = hs.data() + (size_t)l * S_COUNT;

@@ -53,6 +53,19 @@ def test_single_row_single_step(orc):
     _compare(orc, layers, x)
 
 
+@pytest.mark.parametrize("I,N,H,flags,B,T", [
+    (17, 130, 130, wl.LAYER_NORM, 17, 3),  # one row beyond a tile of 16
+    (33, 1030, 20, wl.LAYER_NORM | wl.PEEPHOLE | wl.PROJECTION, 40, 2),  # o gate's statistics after the new cell state
+    (8, 2050, 16, wl.LAYER_NORM | wl.PROJECTION, 3, 2),  # rows one past a register form of the cell
+    (8, 4100, 24, wl.CIFG | wl.LAYER_NORM | wl.PEEPHOLE | wl.PROJECTION, 2, 2),  # rows too wide for registers
+    (16, 512, 512, wl.PEEPHOLE, 3, 3),  # few columns, long k: split over 16 waves
+    (20, 520, 520, wl.CIFG, 260, 4),  # 128 x 128 blocks with ragged edges on both sides
+])
+def test_edges_of_the_products_and_of_the_cell(orc, I, N, H, flags, B, T):
+    layers, x = wl.make_custom([I], N, H, flags, B, T, seed=N + B)
+    _compare(orc, layers, x)
+
+
 def test_c2_statistics_give_the_same_integer_model(orc):
     """At C2's shape the GPU statistics lead prepare to the very model the
     oracle's statistics lead to: every scale, multiplier and quantized tensor."""
