@@ -262,7 +262,7 @@ int lstm_int_forward_bidirectional(const lstm_int_model *fwd, const lstm_int_mod
  *           c_state then enter at t = T - 1 and leave after t = 0.  Default 0.
  * The others are tuning knobs; results never depend on them.
  *   "path": 0 = choose per layer (default): the persistent recurrent kernel
- *               where the layer shape allows it (N % 8 == 0, N <= 2048,
+ *               where the layer shape allows it (N <= 2048,
  *               H <= 1024, no trace of that layer; larger batches and
  *               sequences beyond 2^14 steps run in several launches),
  *               otherwise one launch per operation and step;

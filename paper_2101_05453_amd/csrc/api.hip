@@ -926,7 +926,7 @@ int lstm_int_forward(const lstm_int_model *cm, const int8_t *x, int32_t T, int32
       ra.Wp2 = d.Wp3; ra.bp2 = d.bp3; ra.ptiles = d.ptiles3; ra.prow = d.prow; ra.npadp = d.npadp;
       ra.Mp = h.Mp; ra.rp = 31 - h.ep; ra.zp_h = h.zp_h;
       ra.tx2 = reinterpret_cast<const int4 *>(tx);
-      ra.h0 = h0; ra.out = out; ra.y = (last && !rev) ? y : nullptr;
+      ra.h0 = h0; ra.out = out;
       ra.mbuf = reinterpret_cast<int8_t *>(wsb + ws.m2);
       ra.c_in = c_state ? c_state + c_off : nullptr;
       ra.c_out = c_state ? c_state + c_off : nullptr;
@@ -1020,6 +1020,8 @@ int lstm_int_forward(const lstm_int_model *cm, const int8_t *x, int32_t T, int32
       // statistics words of its groups (they follow the counters)
       auto sync_bytes = [](int groups) { return (int64_t)256 * 64 * 4 + (int64_t)groups * (int64_t)kStatGroupBytes; };
       const int launch_rows = p2_groups * ra.rows_pg;
+      // the kernels write y in words of four cells; rows that are no multiple of four are copied afterwards
+      const bool y_after = last && !rev && !proj && (h.N & 3);
       {
         InGemmArgs ga;
         memset(&ga, 0, sizeof(ga));
@@ -1070,7 +1072,7 @@ int lstm_int_forward(const lstm_int_model *cm, const int8_t *x, int32_t T, int32
         ra.tx2 = tx2_all + (size_t)t0 * (ra.Bp / 32) * (d.GS * 8) * 2 * 64;
         ra.h0 = t0 == 0 ? h0 : out + (size_t)(t0 - 1) * step_out;
         ra.out = out + (size_t)t0 * step_out;
-        ra.y = (last && !rev) ? y + (size_t)t0 * B * h.H : nullptr;
+        ra.y = (last && !rev && !y_after) ? y + (size_t)t0 * B * h.H : nullptr;
         ra.c_in = t0 == 0 ? (c_state ? c_state + c_off : nullptr) : c_carry;
         ra.c_out = (c_state || t0 + tc < T) ? c_carry : nullptr;
         for (int b0 = 0; b0 < B; b0 += launch_rows) {
@@ -1094,7 +1096,10 @@ int lstm_int_forward(const lstm_int_model *cm, const int8_t *x, int32_t T, int32
           pend.dst = h_state + h_off;
           pend.cols = h.H;
         }
-        if (last && rev) launch_flip_rows_i8(s, out, d.Hpad, y, h.H, T, B, h.H, 0);
+        if (last && rev)
+          launch_flip_rows_i8(s, out, d.Hpad, y, h.H, T, B, h.H, 0);
+        else if (y_after)
+          launch_copy_rows_i8(s, out, d.Hpad, y, h.H, TB, h.H, 0);
       }
       h_off += (size_t)B * h.H;
       c_off += (size_t)B * h.N;

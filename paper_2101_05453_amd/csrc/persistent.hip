@@ -191,7 +191,7 @@ void launch_in_gemm(hipStream_t s, const InGemmArgs &a) {
 static const int kKS[] = {8, 20, 32};
 
 bool rec_supported(int N, int H, int flags, int B, int *ks, int *rt, int *groups) {
-  if (N % 8 != 0 || N > 2048 || B < 1) return false;
+  if (N > 2048 || B < 1) return false;
   if (!(flags & 8) && H != N) return false;
   const int GS = (N + 63) / 64;
   const int need = (((H + 127) / 128) * 128) / 32;  // Hpad / 32

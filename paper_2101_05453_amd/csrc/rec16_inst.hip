@@ -19,7 +19,7 @@ static rec_fn pick16(int ks16, int fl) {
 }
 
 bool rec16_supported(int N, int H, int flags, int B, int *ks16, int *groups) {
-  if (N % 8 != 0 || N > 2048 || B < 1) return false;
+  if (N > 2048 || B < 1) return false;
   if (!(flags & 8) && H != N) return false;
   const int GS = (N + 63) / 64;
   const int need = (((H + 127) / 128) * 128 + 63) / 64;

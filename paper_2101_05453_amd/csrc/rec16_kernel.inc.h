@@ -683,7 +683,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   placement_check();
   if (a.c_out && row < a.B && n0 < a.N) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) a.c_out[(size_t)row * a.N + n0 + c] = (int16_t)creg[c];
+    for (int c = 0; c < 4; ++c)
+      if (n0 + c < a.N) a.c_out[(size_t)row * a.N + n0 + c] = (int16_t)creg[c];
   }
 }
 

@@ -848,12 +848,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
           const int32_t mq = sat8(rescale_sat16_pre<0>(om, pm) + zp_m);
           pk |= (uint32_t)(mq & 0xFF) << (8 * c);
         }
-        if (row < a.B && n0 < a.N) {  // N % 8 == 0: the four cells are valid together
+        if (row < a.B && n0 < a.N) {  // cells past N fill padding of the row (and only ever meet zero weights)
           const size_t off = proj ? ((((size_t)(row >> 5) * (a.npadp >> 5) + (n0 >> 5)) * 32 + (row & 31)) * 32 + (n0 & 31))
                                   : (size_t)row * a.Hpad + n0;
           *reinterpret_cast<uint32_t *>(mdst + off) = pk;
           if (!proj && a.y) {
-            int8_t *yd = a.y + ((size_t)t * a.B + row) * a.H + n0;  // H = N, a multiple of 4
+            int8_t *yd = a.y + ((size_t)t * a.B + row) * a.H + n0;  // H = N, a multiple of 4 (y is NULL otherwise)
             __builtin_nontemporal_store(pk, reinterpret_cast<uint32_t *>(yd));  // not read again here
           }
         }
@@ -977,7 +977,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         const int n0 = member * 64 + cell_w + tl * 8;
         if (row < a.B && n0 < a.N)
 #pragma unroll
-          for (int c = 0; c < 4; ++c) a.c_out[(size_t)row * a.N + n0 + c] = (int16_t)creg[rt][tl][c];
+          for (int c = 0; c < 4; ++c)
+            if (n0 + c < a.N) a.c_out[(size_t)row * a.N + n0 + c] = (int16_t)creg[rt][tl][c];
       }
   }
 }

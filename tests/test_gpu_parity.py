@@ -529,3 +529,42 @@ def test_large_input_product_on_the_per_step_path(orc):
     (a ragged last row block) by 4 * 320 = 1280 columns, every traced tensor against the oracle."""
     layers, x = wl.make_custom([100], 320, 320, wl.PEEPHOLE, 70, 30, seed=77, weight_param=0.05)
     run_and_compare(orc, layers, x, "tile256", trace=True, options={"path": 1})
+
+
+@pytest.mark.parametrize("N,H,flags,B,options", [
+    (203, None, wl.PEEPHOLE, 21, {}),  # three cells in the last word of a row
+    (203, None, wl.LAYER_NORM, 37, {"rows16": 0}),
+    (130, 57, wl.LAYER_NORM | wl.PEEPHOLE | wl.PROJECTION, 33, {}),  # two cells in the last workgroup
+    (321, 130, wl.CIFG | wl.LAYER_NORM | wl.PROJECTION, 40, {"rows16": 0}),
+    (65, None, wl.CIFG, 5, {}),  # one
+    (1, None, wl.LAYER_NORM, 3, {}),
+    (2, None, 0, 600, {"rows16": 0}),
+])
+@pytest.mark.parametrize("stack", [0, 2])
+def test_any_number_of_cells_on_the_persistent_kernels(orc, N, H, flags, B, options, stack):
+    """Cells that fill no word, tile or workgroup of the recurrent kernels: two calls with carried state, y, h and c of
+    both layers against the oracle, and no per-step launch."""
+    import torch
+
+    H = H or N
+    T = 5
+    layers, x = wl.make_custom([11, H], N, H, flags, B, T, seed=N + B, weight_param=0.1)
+    lib_model, orc_model, xq = prepare_both(orc, layers, x)
+    for k, v in dict(options, stack=stack).items():
+        lib_model.set_option(k, v)
+    traces = [orc.forward(orc_model, xq, trace_layer=l)[1] for l in range(2)]
+    want_y = orc.forward(orc_model, xq)
+    hs = torch.cat([torch.full((B * H,), lib_model.get_quant(l)["zp_h"], dtype=torch.int8) for l in range(2)]).cuda()
+    cs = torch.zeros(2 * B * N, dtype=torch.int16).cuda()
+    xd = torch.from_numpy(xq).cuda()
+    lib_model.profile_begin()
+    for t0, t1 in ((0, 3), (3, T)):
+        y = lib_model.forward(xd[t0:t1].contiguous(), h_state=hs, c_state=cs)
+        torch.cuda.synchronize()
+        assert_equal(f"y[{t0}:{t1}]", y.cpu().numpy(), want_y[t0:t1])
+        for l in range(2):
+            assert_equal(f"h[{t1 - 1}] layer {l}", hs.cpu().numpy().reshape(2, B, H)[l], traces[l]["h"][t1 - 1])
+            assert_equal(f"c[{t1 - 1}] layer {l}", cs.cpu().numpy().reshape(2, B, N)[l], traces[l]["c"][t1 - 1])
+    assert_equal("y without state", lib_model.forward(xd).cpu().numpy(), want_y)
+    assert lib_model.profile_end()["cell"]["launches"] == 0
+    assert lib_model.device_status() == 0
