@@ -828,6 +828,152 @@ int forward_stack(lstm_int_model *m, const int8_t *x, int32_t T, int32_t B, int8
   return hipGetLastError() == hipSuccess ? LSTM_INT_OK : LSTM_INT_E_DEVICE;
 }
 
+// How a layer runs on the persistent path for batches of B rows: which kernel, its launch constants, tables and LDS
+// budget.  ok = false: it runs one launch per operation and step.  What points into a call's buffers is left to the
+// caller.
+struct RecPlan {
+  RecArgs ra;
+  int groups = 0;      // most groups in one launch
+  bool ok = false, use16 = false;
+};
+
+RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B) {
+  const LayerHost &h = m->host[l];
+  const LayerDev &d = m->dev[l];
+  const bool proj = h.projection();
+  RecPlan p;
+  RecArgs &ra = p.ra;
+  memset(&ra, 0, sizeof(ra));
+  int p2_ks = 0, p2_rt = 0, p2_groups = 0;
+  if (!d.p2 || !rec_supported(h.N, h.H, (int)h.flags, B, &p2_ks, &p2_rt, &p2_groups)) return p;
+  ra.T = T; ra.B = B; ra.N = h.N; ra.H = h.H; ra.Hpad = d.Hpad; ra.flags = (int)h.flags; ra.m_c = h.m_c;
+  ra.GS = d.GS; ra.groups = p2_groups; ra.rows_pg = 32 * p2_rt; ra.ks = d.ks; ra.Ncp = d.Ncp;
+  ra.Bp = round_up(B, 32);
+  ra.R2 = d.R2; ra.bh4 = d.bh4; ra.Lq4 = d.Lq4; ra.qb4 = d.qb4; ra.Pq3 = d.Pq3;
+  ra.pre_h = 0;
+  for (int g = 0; g < 4; ++g) {
+    const int sg = g < 4 - h.G ? 4 - h.G : g;  // an absent gate borrows valid numbers; its rows are zero
+    ra.Mh[g] = h.Mh[sg]; ra.rh[g] = 31 - h.eh[sg];
+    ra.pre_h = std::max(ra.pre_h, preshift_mode(ra.rh[g], d.amax_h[sg]));
+    ra.Mln[g] = h.Mln[sg]; ra.rln[g] = 31 - h.eln[sg];
+  }
+  for (int j = 0; j < 3; ++j) { ra.Mc[j] = h.Mc[j]; ra.rc[j] = 31 - h.ec[j]; }
+  ra.Mm = h.Mm; ra.rm = 31 - h.em; ra.zp_m = h.zp_m;
+  // the 32-row kernel's tiling of W_proj (the 16-row kernel gets the 32-row tiles back below)
+  ra.Wp2 = d.Wp3; ra.bp2 = d.bp3; ra.ptiles = d.ptiles3; ra.prow = d.prow; ra.npadp = d.npadp;
+  ra.Mp = h.Mp; ra.rp = 31 - h.ep; ra.zp_h = h.zp_h;
+  ra.status = m->status;
+  ra.spin_limit = m->spin_limit;
+  ra.poll_sleep = m->poll_sleep;
+  ra.stats_sleep = m->stats_sleep;
+  ra.idle_sleep = m->idle_sleep;
+  ra.stats_first_sleep = m->stats_first_sleep;
+  // the last arrival lands about 0.45 us after a workgroup's own in a group of 32, sooner in small groups
+  ra.sync_sleep = m->sync_sleep >= 0 ? m->sync_sleep : (d.GS >= 16 ? 16 : 4);
+  ra.idle_poll_sleep = m->idle_poll_sleep;
+  ra.ticks = m->phase_timing ? reinterpret_cast<long long *>(m->status + 16) : nullptr;
+  ra.extra_arrivals = m->extra_arrivals;
+  // the kernel's one-product form of rescale needs shifts in [3, 62]; its tables must compress (lut_ok below)
+  auto shift_ok = [](int r) { return r >= 3 && r <= 62; };
+  bool ok = shift_ok(ra.rm) && (!proj || shift_ok(ra.rp));
+  for (int g = 4 - h.G; g < 4; ++g)
+    if (!shift_ok(ra.rh[g]) || (h.layer_norm() && !shift_ok(ra.rln[g]))) ok = false;
+  for (int j = 4 - h.G; j < 3; ++j)
+    if (h.peephole() && !shift_ok(ra.rc[j])) ok = false;
+  // rec_kernel's tables: the shortest prefixes first (the budget test below uses them)
+  auto set_lut = [&](int i, const WideTable &w) {
+    int dom = 0, tail = 0;
+    w.shortest(&dom, &tail);
+    ra.lut[i].blob = w.blob; ra.lut[i].sh = w.sh; ra.lut[i].dom = dom; ra.lut[i].tail = tail;
+    return dom > 0;
+  };
+  const bool lut0 = set_lut(0, m->wsig3), lut1 = set_lut(1, m->wtanh3), lut2 = set_lut(2, d.wtanhc);
+  const bool lut_ok = lut0 && lut1 && lut2;
+  if (ok && ra.rows_pg == 64 && lut_ok && rec_lds_bytes(ra) > 160 * 1024) {
+    // two row tiles per group do not fit the LDS: one tile per group, more launches over the batch
+    ra.rows_pg = 32;
+    p2_groups = std::min(8 * (32 / d.GS), (B + 31) / 32);
+    ra.groups = p2_groups;
+  }
+  if (!ok || !lut_ok || rec_lds_bytes(ra) > 160 * 1024) return p;
+  // small batches: groups of 16 rows fill more compute units and halve a step's arithmetic
+  int k16 = 0, g16 = 0;
+  if (m->rows16 && d.p16 && rec16_supported(h.N, h.H, (int)h.flags, B, &k16, &g16)) {
+    RecArgs r16 = ra;
+    r16.R2h = d.R2h; r16.ks16 = d.ks16; r16.rows_pg = 16; r16.groups = g16;
+    r16.Wp2 = d.Wp2; r16.bp2 = d.bp2; r16.ptiles = d.ptiles; r16.prow = 32;
+    if (rec16_lds_bytes(r16) <= 160 * 1024) {
+      ra = r16;
+      p2_groups = g16;
+      p.use16 = true;
+    }
+  }
+  // 2:4 recurrent weights: the 32-row kernel with one row tile per group has a sparse-MFMA form
+  if (!p.use16 && m->sparse && d.R2s && ra.rows_pg == 32) {
+    ra.R2 = d.R2s;
+    ra.sparse = 1;
+  }
+  auto lds_need = [&]() { return p.use16 ? rec16_lds_bytes(ra) : rec_lds_bytes(ra); };
+  // What LDS is left goes to longer prefixes of the two gate tables, 1 KB at a time in turn: a value
+  // beyond the prefix costs the whole group a detour (rec_kernel.inc.h, lookup), and with 24576 entries
+  // (|x| < 6 in Q3.12) there is about one per million layer-norm outputs instead of one per thousand.
+  // A prefix that reaches the table's flat end needs no tail part any more.
+  bool grew = true;
+  while (grew) {
+    grew = false;
+    for (int i = 0; i < 2; ++i) {
+      const WideTable &w = i == 0 ? m->wsig3 : m->wtanh3;
+      LutWide keep = ra.lut[i];
+      if (keep.dom >= 32768 || (!keep.tail && keep.dom - 1 >= w.flat_from)) continue;  // nothing left to gain
+      ra.lut[i].dom = keep.dom + 1024;
+      ra.lut[i].tail = (ra.lut[i].dom - 1 < w.flat_from) ? 1 : 0;
+      if (ra.lut[i].tail && !w.has_tail) { ra.lut[i] = keep; continue; }
+      if (i == 1 && ra.lut[2].blob == keep.blob) ra.lut[2] = ra.lut[1];  // one copy serves the cell tanh too
+      if (lds_need() > 160 * 1024) {
+        ra.lut[i] = keep;
+        if (i == 1 && ra.lut[2].blob == keep.blob) ra.lut[2] = keep;
+      } else {
+        grew = true;
+      }
+    }
+  }
+  p.groups = p2_groups;
+  p.ok = true;
+  return p;
+}
+
+// Synchronization scratch of a launch (plan_workspace's `sync`): barrier counters and placement words, statistics words.
+// The placement words share the zeroed counter region: bytes 8..15 of the blocks of groups 0..7 (bytes 0..3 are the
+// barrier counter).
+void set_sync(RecArgs &ra, const lstm_int_model *m, uint8_t *sync) {
+  ra.counters = reinterpret_cast<unsigned *>(sync);
+  ra.tickets = m->cooperative ? nullptr : reinterpret_cast<unsigned long long *>(ra.counters + 2);
+  ra.acc = reinterpret_cast<unsigned long long *>(sync + 256 * 64 * 4);
+}
+
+// Bytes of that scratch a launch over `groups` groups uses, all of them to be cleared before it: all counters, and the
+// statistics words of its groups (they follow the counters).
+int64_t sync_bytes(int groups) { return (int64_t)256 * 64 * 4 + (int64_t)groups * (int64_t)kStatGroupBytes; }
+
+// The hoisted W x of layer l (its output goes to ga.tx2, in the tile order of the recurrent kernels).
+InGemmArgs plan_in_gemm(const lstm_int_model *m, int l, int T, int B) {
+  const LayerHost &h = m->host[l];
+  const LayerDev &d = m->dev[l];
+  InGemmArgs ga;
+  memset(&ga, 0, sizeof(ga));
+  ga.T = T; ga.B = B; ga.Bp = round_up(B, 32);
+  ga.W2 = d.W2; ga.W2f = d.W2f; ga.kpad = d.Ipad; ga.tiles = d.GS * 8; ga.bx2 = d.bx2;
+  ga.all_hi = 1;
+  ga.pre = 0;
+  for (int g = 0; g < 4; ++g) {
+    const int sg = g < 4 - h.G ? 4 - h.G : g;
+    ga.M[g] = h.Mx[sg]; ga.r[g] = 31 - h.ex[sg];
+    if (ga.r[g] < 32) ga.all_hi = 0;
+    ga.pre = std::max(ga.pre, preshift_mode(ga.r[g], d.amax_x[sg]));
+  }
+  return ga;
+}
+
 }  // namespace
 
 extern "C" {
@@ -901,141 +1047,30 @@ int lstm_int_forward(const lstm_int_model *cm, const int8_t *x, int32_t T, int32
     int8_t *out = reinterpret_cast<int8_t *>(wsb + ws.out[l & 1]);
     const size_t step_out = (size_t)B * d.Hpad;
 
-    // persistent path: eligible shape, no dump requested for this layer, batch fits one launch
-    int p2_ks = 0, p2_rt = 0, p2_groups = 0;
-    bool use_p2 = m->path != 1 && !tr && d.p2 && (reinterpret_cast<uintptr_t>(y) & 3) == 0 &&
-                  rec_supported(h.N, h.H, (int)h.flags, B, &p2_ks, &p2_rt, &p2_groups);
-    RecArgs ra;
-    bool use16 = false;
+    // persistent path: eligible shape, no dump requested for this layer
+    RecPlan plan;
+    if (m->path != 1 && !tr && (reinterpret_cast<uintptr_t>(y) & 3) == 0) plan = plan_rec(m, l, T, B);
+    const bool use_p2 = plan.ok, use16 = plan.use16;
+    const int p2_groups = plan.groups;
+    RecArgs &ra = plan.ra;
+    // option "sparse" = 2: a layer with 2:4 recurrent weights must run in the sparse form, or the call fails
+    if (m->sparse == 2 && d.R2s && !(use_p2 && ra.sparse)) return LSTM_INT_E_UNSUPPORTED;
     if (use_p2) {
-      memset(&ra, 0, sizeof(ra));
-      ra.T = T; ra.B = B; ra.N = h.N; ra.H = h.H; ra.Hpad = d.Hpad; ra.flags = (int)h.flags; ra.m_c = h.m_c;
-      ra.GS = d.GS; ra.groups = p2_groups; ra.rows_pg = 32 * p2_rt; ra.ks = d.ks; ra.Ncp = d.Ncp;
-      ra.Bp = round_up(B, 32);
-      ra.R2 = d.R2; ra.bh4 = d.bh4; ra.Lq4 = d.Lq4; ra.qb4 = d.qb4; ra.Pq3 = d.Pq3;
-      ra.pre_h = 0;
-      for (int g = 0; g < 4; ++g) {
-        const int sg = g < 4 - h.G ? 4 - h.G : g;  // an absent gate borrows valid numbers; its rows are zero
-        ra.Mh[g] = h.Mh[sg]; ra.rh[g] = 31 - h.eh[sg];
-        ra.pre_h = std::max(ra.pre_h, preshift_mode(ra.rh[g], d.amax_h[sg]));
-        ra.Mln[g] = h.Mln[sg]; ra.rln[g] = 31 - h.eln[sg];
-      }
-      for (int j = 0; j < 3; ++j) { ra.Mc[j] = h.Mc[j]; ra.rc[j] = 31 - h.ec[j]; }
-      ra.Mm = h.Mm; ra.rm = 31 - h.em; ra.zp_m = h.zp_m;
-      // the 32-row kernel's tiling of W_proj (the 16-row kernel gets the 32-row tiles back below)
-      ra.Wp2 = d.Wp3; ra.bp2 = d.bp3; ra.ptiles = d.ptiles3; ra.prow = d.prow; ra.npadp = d.npadp;
-      ra.Mp = h.Mp; ra.rp = 31 - h.ep; ra.zp_h = h.zp_h;
       ra.tx2 = reinterpret_cast<const int4 *>(tx);
       ra.h0 = h0; ra.out = out;
       ra.mbuf = reinterpret_cast<int8_t *>(wsb + ws.m2);
       ra.c_in = c_state ? c_state + c_off : nullptr;
       ra.c_out = c_state ? c_state + c_off : nullptr;
-      ra.counters = reinterpret_cast<unsigned *>(wsb + ws.sync);
-      // the words share the zeroed counter region: bytes 8..15 of the blocks of groups 0..7 (bytes 0..3
-      // are the barrier counter)
-      ra.tickets = m->cooperative ? nullptr : reinterpret_cast<unsigned long long *>(ra.counters + 2);
-      ra.acc = reinterpret_cast<unsigned long long *>(wsb + ws.sync + 256 * 64 * 4);
-      ra.status = m->status;
-      ra.spin_limit = m->spin_limit;
-      ra.poll_sleep = m->poll_sleep;
-      ra.stats_sleep = m->stats_sleep;
-      ra.idle_sleep = m->idle_sleep;
-      ra.stats_first_sleep = m->stats_first_sleep;
-      // the last arrival lands about 0.45 us after a workgroup's own in a group of 32, sooner in small groups
-      ra.sync_sleep = m->sync_sleep >= 0 ? m->sync_sleep : (d.GS >= 16 ? 16 : 4);
-      ra.idle_poll_sleep = m->idle_poll_sleep;
-      ra.ticks = m->phase_timing ? reinterpret_cast<long long *>(m->status + 16) : nullptr;
-      ra.extra_arrivals = m->extra_arrivals;
-      // the kernel's one-product form of rescale needs shifts in [3, 62]; its tables must compress (lut_ok below)
-      auto shift_ok = [](int r) { return r >= 3 && r <= 62; };
-      bool ok = shift_ok(ra.rm) && (!proj || shift_ok(ra.rp));
-      for (int g = 4 - h.G; g < 4; ++g)
-        if (!shift_ok(ra.rh[g]) || (h.layer_norm() && !shift_ok(ra.rln[g]))) ok = false;
-      for (int j = 4 - h.G; j < 3; ++j)
-        if (h.peephole() && !shift_ok(ra.rc[j])) ok = false;
-      // rec_kernel's tables: the shortest prefixes first (the budget test below uses them)
-      auto set_lut = [&](int i, const WideTable &w) {
-        int dom = 0, tail = 0;
-        w.shortest(&dom, &tail);
-        ra.lut[i].blob = w.blob; ra.lut[i].sh = w.sh; ra.lut[i].dom = dom; ra.lut[i].tail = tail;
-        return dom > 0;
-      };
-      const bool lut_ok = set_lut(0, m->wsig3) & set_lut(1, m->wtanh3) & set_lut(2, d.wtanhc);
-      if (ok && ra.rows_pg == 64 && lut_ok && rec_lds_bytes(ra) > 160 * 1024) {
-        // two row tiles per group do not fit the LDS: one tile per group, more launches over the batch
-        p2_rt = 1;
-        ra.rows_pg = 32;
-        p2_groups = std::min(8 * (32 / d.GS), (B + 31) / 32);
-        ra.groups = p2_groups;
-      }
-      if (!ok || !lut_ok || rec_lds_bytes(ra) > 160 * 1024) use_p2 = false;
-      // small batches: groups of 16 rows fill more compute units and halve a step's arithmetic
-      int k16 = 0, g16 = 0;
-      if (use_p2 && m->rows16 && d.p16 && rec16_supported(h.N, h.H, (int)h.flags, B, &k16, &g16)) {
-        RecArgs r16 = ra;
-        r16.R2h = d.R2h; r16.ks16 = d.ks16; r16.rows_pg = 16; r16.groups = g16;
-        r16.Wp2 = d.Wp2; r16.bp2 = d.bp2; r16.ptiles = d.ptiles; r16.prow = 32;
-        if (rec16_lds_bytes(r16) <= 160 * 1024) {
-          ra = r16;
-          p2_groups = g16;
-          use16 = true;
-        }
-      }
-      // 2:4 recurrent weights: the 32-row kernel with one row tile per group has a sparse-MFMA form
-      if (use_p2 && !use16 && m->sparse && d.R2s && ra.rows_pg == 32) {
-        ra.R2 = d.R2s;
-        ra.sparse = 1;
-      }
-    }
-    // option "sparse" = 2: a layer with 2:4 recurrent weights must run in the sparse form, or the call fails
-    if (m->sparse == 2 && d.R2s && !(use_p2 && ra.sparse)) return LSTM_INT_E_UNSUPPORTED;
-    if (use_p2) {
-      auto lds_need = [&]() { return use16 ? rec16_lds_bytes(ra) : rec_lds_bytes(ra); };
-      // What LDS is left goes to longer prefixes of the two gate tables, 1 KB at a time in turn: a value
-      // beyond the prefix costs the whole group a detour (rec_kernel.inc.h, lookup), and with 24576 entries
-      // (|x| < 6 in Q3.12) there is about one per million layer-norm outputs instead of one per thousand.
-      // A prefix that reaches the table's flat end needs no tail part any more.
-      bool grew = true;
-      while (grew) {
-        grew = false;
-        for (int i = 0; i < 2; ++i) {
-          const WideTable &w = i == 0 ? m->wsig3 : m->wtanh3;
-          LutWide keep = ra.lut[i];
-          if (keep.dom >= 32768 || (!keep.tail && keep.dom - 1 >= w.flat_from)) continue;  // nothing left to gain
-          ra.lut[i].dom = keep.dom + 1024;
-          ra.lut[i].tail = (ra.lut[i].dom - 1 < w.flat_from) ? 1 : 0;
-          if (ra.lut[i].tail && !w.has_tail) { ra.lut[i] = keep; continue; }
-          if (i == 1 && ra.lut[2].blob == keep.blob) ra.lut[2] = ra.lut[1];  // one copy serves the cell tanh too
-          if (lds_need() > 160 * 1024) {
-            ra.lut[i] = keep;
-            if (i == 1 && ra.lut[2].blob == keep.blob) ra.lut[2] = keep;
-          } else {
-            grew = true;
-          }
-        }
-      }
+      set_sync(ra, m, wsb + ws.sync);
     }
     if (use_p2) {
-      // bytes of the synchronization region a launch over `groups` groups uses: all counters, and the
-      // statistics words of its groups (they follow the counters)
-      auto sync_bytes = [](int groups) { return (int64_t)256 * 64 * 4 + (int64_t)groups * (int64_t)kStatGroupBytes; };
       const int launch_rows = p2_groups * ra.rows_pg;
       // the kernels write y in words of four cells; rows that are no multiple of four are copied afterwards
       const bool y_after = last && !rev && !proj && (h.N & 3);
       {
-        InGemmArgs ga;
-        memset(&ga, 0, sizeof(ga));
-        ga.A = in; ga.lda = ld_in; ga.T = T; ga.B = B; ga.Bp = ra.Bp;
+        InGemmArgs ga = plan_in_gemm(m, l, T, B);
+        ga.A = in; ga.lda = ld_in;
         ga.a_slack = in != x;  // the workspace buffers have the slack, the caller's x need not
-        ga.W2 = d.W2; ga.W2f = d.W2f; ga.kpad = d.Ipad; ga.tiles = d.GS * 8; ga.bx2 = d.bx2;
-        ga.all_hi = 1;
-        ga.pre = 0;
-        for (int g = 0; g < 4; ++g) {
-          const int sg = g < 4 - h.G ? 4 - h.G : g;
-          ga.M[g] = h.Mx[sg]; ga.r[g] = 31 - h.ex[sg];
-          if (ga.r[g] < 32) ga.all_hi = 0;
-          ga.pre = std::max(ga.pre, preshift_mode(ga.r[g], d.amax_x[sg]));
-        }
         ga.tx2 = reinterpret_cast<int4 *>(tx);
         // initial h (given, or real 0 = zp_h), the cleared words of the first launch and the previous layer's
         // final h on its way to the state buffer: done by the input GEMM's workgroups ahead of their own
@@ -1207,17 +1242,140 @@ int lstm_int_forward_static(const lstm_int_model *m, const int8_t *x, int32_t T,
   return lstm_int_forward(m, x, T, B, y, h_state, c_state, ws, LSTM_INT_STATIC_WORKSPACE_BYTES, hip_stream, nullptr);
 }
 
-// Workspace of a bidirectional call: the larger of the two directions' own workspaces, then one dense
-// [T, B, max(H_fwd, H_bwd)] staging buffer from which each direction's output is placed into its columns of y.
+// ---------------------------------------------------------------------------
+// Bidirectional layers
+// ---------------------------------------------------------------------------
+// Side by side: where each layer of the two stacks has the same shape and both directions' groups of 16 rows fit one
+// launch of the 16-row kernel, a layer of both runs in one launch, and the backward kernel walks time downward by
+// itself -- no flipped copies of x and y.  A direction alone would leave at least half of the compute units idle there,
+// and a step costs the same whether its neighbours work or not.  Otherwise the two directions run one after the other.
+// (One layer of 512 cells, 64 rows, 100 steps: 1.00 ms one after the other, 0.52 ms side by side.)
+static bool pair_chosen(const lstm_int_model *f, const lstm_int_model *b, int32_t T, int32_t B) {
+  const size_t L = f->host.size();
+  if (b->host.size() != L || f->device < 0 || b->device != f->device || T < 1 || B < 1 || T > 1 << 14 || f->path == 1 ||
+      b->path == 1 || f->cooperative != b->cooperative)
+    return false;
+  for (size_t l = 0; l < L; ++l) {
+    const LayerHost &hf = f->host[l], &hb = b->host[l];
+    if (hf.N != hb.N || hf.H != hb.H || hf.flags != hb.flags || hf.I != hb.I) return false;
+    if ((f->sparse == 2 && f->dev[l].R2s) || (b->sparse == 2 && b->dev[l].R2s)) return false;
+    const RecPlan pf = plan_rec(f, (int)l, T, B), pb = plan_rec(b, (int)l, T, B);
+    if (!pf.ok || !pb.ok || !pf.use16 || !pb.use16 || pf.groups + pb.groups > 8 * (32 / pf.ra.GS)) return false;
+  }
+  return true;
+}
+
+static int forward_pair(lstm_int_model *const (&m)[2], const int8_t *x, int32_t T, int32_t B, int8_t *y,
+                        int8_t *const (&h_state)[2], int16_t *const (&c_state)[2], uint8_t *wsb, hipStream_t s) {
+  const int L = (int)m[0]->host.size();
+  const Workspace ws[2] = {plan_workspace(m[0], T, B), plan_workspace(m[1], T, B)};
+  uint8_t *base[2] = {wsb, wsb + ws[0].total};
+  const int Hl[2] = {m[0]->host.back().H, m[1]->host.back().H};
+  // y is written by the kernels where its words of four columns are aligned in both halves
+  const bool y_direct = ((Hl[0] | Hl[1]) & 3) == 0 && (reinterpret_cast<uintptr_t>(y) & 3) == 0;
+  const int I0 = m[0]->host[0].I, Ip0 = m[0]->dev[0].Ipad;
+  const int8_t *in[2] = {x, x};
+  int ld_in[2] = {I0, I0};
+  if ((I0 & 63) || (reinterpret_cast<uintptr_t>(x) & 15) || (B & 31)) {  // as in lstm_int_forward; one copy serves both
+    Timed t(m[0]->prof, s, LSTM_INT_K_OTHER);
+    int8_t *xp = reinterpret_cast<int8_t *>(base[0] + ws[0].xpad);
+    launch_copy_rows_i8(s, x, I0, xp, Ip0, T * B, I0, 0);
+    in[0] = in[1] = xp;
+    ld_in[0] = ld_in[1] = Ip0;
+  }
+  struct {
+    const int8_t *src = nullptr;
+    int ld = 0, cols = 0;
+    int8_t *dst = nullptr;
+  } pend[2];  // a layer's final h on its way to the caller's state buffer
+  size_t h_off[2] = {0, 0}, c_off[2] = {0, 0};
+  for (int l = 0; l < L; ++l) {
+    RecArgs2 pair;
+    RecPlan plan[2] = {plan_rec(m[0], l, T, B), plan_rec(m[1], l, T, B)};
+    const int groups = plan[0].groups + plan[1].groups;
+    for (int i = 0; i < 2; ++i) {
+      const LayerHost &h = m[i]->host[l];
+      const LayerDev &d = m[i]->dev[l];
+      int8_t *out = reinterpret_cast<int8_t *>(base[i] + ws[i].out[l & 1]);
+      int8_t *h0 = reinterpret_cast<int8_t *>(base[i] + ws[i].h0);
+      const int8_t *h_src = h_state[i] ? h_state[i] + h_off[i] : nullptr;
+      InGemmArgs ga = plan_in_gemm(m[i], l, T, B);
+      ga.A = in[i]; ga.lda = ld_in[i];
+      ga.a_slack = in[i] != x;
+      ga.tx2 = reinterpret_cast<int4 *>(base[i] + ws[i].tx);
+      uint8_t *sync = base[0] + ws[0].sync;
+      const int64_t clear = i == 0 ? sync_bytes(groups) : 0;
+      if (in_gemm_ws_supported(ga)) {
+        ga.has_init = 1;
+        ga.init.h_src = h_src; ga.init.ld_src = h.H;
+        ga.init.h0 = h0; ga.init.ld_h0 = d.Hpad; ga.init.rows = B; ga.init.cols = h.H; ga.init.zp = h.zp_h;
+        ga.init.sync = reinterpret_cast<int4 *>(sync); ga.init.sync_vec = clear / 16;
+        ga.init.c_src = pend[i].src; ga.init.c_ld_src = pend[i].ld; ga.init.c_dst = pend[i].dst; ga.init.c_cols = pend[i].cols;
+        Timed t(m[i]->prof, s, LSTM_INT_K_INPUT_GEMM);
+        launch_in_gemm_ws(s, ga, m[i]->num_cus);
+      } else {
+        {
+          Timed t(m[i]->prof, s, LSTM_INT_K_OTHER);
+          launch_init_layer(s, h_src, h.H, h0, d.Hpad, B, h.H, h.zp_h, sync, clear, pend[i].src, pend[i].ld, pend[i].dst,
+                            pend[i].cols);
+        }
+        Timed t(m[i]->prof, s, LSTM_INT_K_INPUT_GEMM);
+        launch_in_gemm(s, ga);
+      }
+      RecArgs &ra = pair.d[i];
+      ra = plan[i].ra;
+      ra.tx2 = ga.tx2;
+      ra.h0 = h0; ra.out = out;
+      ra.mbuf = reinterpret_cast<int8_t *>(base[i] + ws[i].m2);
+      ra.c_in = ra.c_out = c_state[i] ? c_state[i] + c_off[i] : nullptr;
+      ra.rev = i;
+      ra.ldy = Hl[0] + Hl[1];
+      ra.y = l == L - 1 && y_direct ? y + (i ? Hl[0] : 0) : nullptr;
+      set_sync(ra, m[0], sync);
+      if (!rec_extents_ok(ra, ws[i], T, 0, h.projection())) return LSTM_INT_E_WORKSPACE;
+      pend[i].dst = nullptr;
+      if (h_state[i]) {
+        pend[i].src = i ? out : out + (size_t)(T - 1) * B * d.Hpad;
+        pend[i].ld = d.Hpad;
+        pend[i].dst = h_state[i] + h_off[i];
+        pend[i].cols = h.H;
+      }
+      h_off[i] += (size_t)B * h.H;
+      c_off[i] += (size_t)B * h.N;
+      in[i] = out;
+      ld_in[i] = d.Hpad;
+    }
+    if ((size_t)groups * kStatGroupBytes > (size_t)256 * kStatGroupBytes) return LSTM_INT_E_WORKSPACE;
+    Timed t0(m[0]->prof, s, LSTM_INT_K_RECURRENT), t1(m[1]->prof, s, LSTM_INT_K_RECURRENT);
+    if (launch_rec16_pair(s, pair, m[0]->cooperative != 0) != hipSuccess) return LSTM_INT_E_DEVICE;
+  }
+  for (int i = 0; i < 2; ++i) {
+    Timed t(m[i]->prof, s, LSTM_INT_K_OTHER);
+    if (pend[i].dst) launch_copy_rows_i8(s, pend[i].src, pend[i].ld, pend[i].dst, pend[i].cols, B, pend[i].cols, 0);
+    if (!y_direct) launch_place_cols_i8(s, in[i], ld_in[i], y + (i ? Hl[0] : 0), Hl[0] + Hl[1], (int64_t)T * B, Hl[i]);
+  }
+  return hipGetLastError() == hipSuccess ? LSTM_INT_OK : LSTM_INT_E_DEVICE;
+}
+
+// Workspace of a bidirectional call: one after the other, the larger of the two directions' own workspaces, then one
+// dense [T, B, max(H_fwd, H_bwd)] staging buffer from which each direction's output is placed into its columns of y;
+// side by side, the workspaces of both.
 static size_t bidi_stage_offset(const lstm_int_model *f, const lstm_int_model *b, int32_t T, int32_t B) {
   const size_t wf = lstm_int_workspace_bytes(f, T, B), wb = lstm_int_workspace_bytes(b, T, B);
   return ((wf > wb ? wf : wb) + 255) & ~(size_t)255;
 }
+static size_t bidi_sequential_bytes(const lstm_int_model *f, const lstm_int_model *b, int32_t T, int32_t B) {
+  const int Hm = std::max(f->host.back().H, b->host.back().H);
+  return bidi_stage_offset(f, b, T, B) + (((size_t)T * B * Hm + 255) & ~(size_t)255);
+}
+static size_t bidi_pair_bytes(const lstm_int_model *f, const lstm_int_model *b, int32_t T, int32_t B) {
+  return plan_workspace(f, T, B).total + plan_workspace(b, T, B).total;
+}
 
 size_t lstm_int_bidirectional_workspace_bytes(const lstm_int_model *f, const lstm_int_model *b, int32_t T, int32_t B) {
   if (!f || !b || T < 0 || B < 0 || f->host.empty() || b->host.empty()) return 0;
-  const int Hm = std::max(f->host.back().H, b->host.back().H);
-  return bidi_stage_offset(f, b, T, B) + (((size_t)T * B * Hm + 255) & ~(size_t)255);
+  const size_t seq = bidi_sequential_bytes(f, b, T, B);
+  return pair_chosen(f, b, T, B) ? std::max(seq, bidi_pair_bytes(f, b, T, B)) : seq;
 }
 
 int lstm_int_forward_bidirectional(const lstm_int_model *f, const lstm_int_model *b, const int8_t *x, int32_t T,
@@ -1232,19 +1390,25 @@ int lstm_int_forward_bidirectional(const lstm_int_model *f, const lstm_int_model
   if (f->device < 0 || f->device != b->device) return LSTM_INT_E_DEVICE;
   if (T == 0 || B == 0) return LSTM_INT_OK;
   if (!x || !y) return LSTM_INT_E_INVALID_ARG;
-  if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) ||
-      workspace_bytes < lstm_int_bidirectional_workspace_bytes(f, b, T, B))
+  if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) || workspace_bytes < bidi_sequential_bytes(f, b, T, B))
     return LSTM_INT_E_WORKSPACE;
   const int Hf = f->host.back().H, Hb = b->host.back().H;
+  hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
+  if ((int64_t)T * B <= (int64_t)1 << 30 && pair_chosen(f, b, T, B) && workspace_bytes >= bidi_pair_bytes(f, b, T, B)) {
+    if (hipSetDevice(f->device) != hipSuccess) return LSTM_INT_E_DEVICE;
+    lstm_int_model *const m[2] = {const_cast<lstm_int_model *>(f), const_cast<lstm_int_model *>(b)};  // profiling counters only
+    int8_t *const hs[2] = {h_state_fwd, h_state_bwd};
+    int16_t *const cs[2] = {c_state_fwd, c_state_bwd};
+    return forward_pair(m, x, T, B, y, hs, cs, static_cast<uint8_t *>(workspace), s);
+  }
   const size_t so = bidi_stage_offset(f, b, T, B);
   int8_t *stage = reinterpret_cast<int8_t *>(workspace) + so;
-  hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
   int rc = lstm_int_forward(f, x, T, B, stage, h_state_fwd, c_state_fwd, workspace, so, hip_stream, nullptr);
   if (rc != LSTM_INT_OK) return rc;
-  launch_place_cols_i8(s, stage, y, Hf + Hb, (int64_t)T * B, Hf);
+  launch_place_cols_i8(s, stage, Hf, y, Hf + Hb, (int64_t)T * B, Hf);
   rc = lstm_int_forward(b, x, T, B, stage, h_state_bwd, c_state_bwd, workspace, so, hip_stream, nullptr);
   if (rc != LSTM_INT_OK) return rc;
-  launch_place_cols_i8(s, stage, y + Hf, Hf + Hb, (int64_t)T * B, Hb);
+  launch_place_cols_i8(s, stage, Hb, y + Hf, Hf + Hb, (int64_t)T * B, Hb);
   return hipGetLastError() == hipSuccess ? LSTM_INT_OK : LSTM_INT_E_DEVICE;
 }
 

@@ -156,6 +156,14 @@ struct RecArgs {
   int extra_arrivals;  // 0; tests set 1: every group barrier then waits for an arrival that never comes, so that
                        // the bounded waits give up (and every workgroup leaves the kernel) on demand
   int sparse;  // rec_kernel, 32 rows per group: R2 holds the recurrent weights in the 2:4 compressed form below
+  int ldy, rev;  // pair launches only (RecArgs2): row stride of y; 1 = step t works at time T - 1 - t
+};
+
+// Two layers of one shape in one launch of the 16-row kernel (the two directions of a bidirectional layer): groups
+// [0, groups) of the launch run d[0], the next d[1].groups run d[1].  Both name the same synchronization scratch, which
+// holds words for all of them.
+struct RecArgs2 {
+  RecArgs d[2];
 };
 
 // Recurrent weights with at most two nonzeros in every aligned group of four along k (the pruned models of
@@ -186,6 +194,8 @@ hipError_t rec_init();
 bool rec16_supported(int N, int H, int flags, int B, int *ks16, int *groups);
 size_t rec16_lds_bytes(const RecArgs &a);
 hipError_t launch_rec16(hipStream_t s, const RecArgs &a, bool cooperative);
+// both fit one launch: d[0].groups + d[1].groups <= 8 (32 / GS)
+hipError_t launch_rec16_pair(hipStream_t s, const RecArgs2 &a, bool cooperative);
 hipError_t rec16_init();
 
 // ---------------------------------------------------------------------------

@@ -18,6 +18,17 @@ static rec_fn pick16(int ks16, int fl) {
   return nullptr;
 }
 
+typedef void (*rec16_pair_fn)(RecArgs2);
+rec16_pair_fn rec16_pick_pair_4(int fl);
+rec16_pair_fn rec16_pick_pair_10(int fl);
+rec16_pair_fn rec16_pick_pair_16(int fl);
+static rec16_pair_fn pick16_pair(int ks16, int fl) {
+  if (ks16 == 4) return rec16_pick_pair_4(fl);
+  if (ks16 == 10) return rec16_pick_pair_10(fl);
+  if (ks16 == 16) return rec16_pick_pair_16(fl);
+  return nullptr;
+}
+
 bool rec16_supported(int N, int H, int flags, int B, int *ks16, int *groups) {
   if (N > 2048 || B < 1) return false;
   if (!(flags & 8) && H != N) return false;
@@ -57,6 +68,9 @@ hipError_t rec16_init() {
       hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(pick16(ks, fl)),
                                          hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
       if (e != hipSuccess) return e;
+      e = hipFuncSetAttribute(reinterpret_cast<const void *>(pick16_pair(ks, fl)), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              160 * 1024);
+      if (e != hipSuccess) return e;
     }
   return hipSuccess;
 }
@@ -72,6 +86,20 @@ hipError_t launch_rec16(hipStream_t s, const RecArgs &a, bool cooperative) {
                                       (unsigned)rec16_lds_bytes(a), s);
   return hipLaunchKernel(reinterpret_cast<const void *>(fn), dim3(8 * slots), dim3(256), params,
                          (unsigned)rec16_lds_bytes(a), s);
+}
+
+hipError_t launch_rec16_pair(hipStream_t s, const RecArgs2 &a, bool cooperative) {
+  const RecArgs &f = a.d[0], &b = a.d[1];
+  rec16_pair_fn fn = pick16_pair(f.ks16, f.flags & 7);
+  if (!fn || !f.R2h || !b.R2h || f.GS != b.GS || f.ks16 != b.ks16 || f.flags != b.flags || f.groups + b.groups > 8 * (32 / f.GS))
+    return hipErrorInvalidValue;
+  const int slots = f.GS * ((f.groups + b.groups + 7) / 8);
+  const size_t lf = rec16_lds_bytes(f), lb = rec16_lds_bytes(b);
+  RecArgs2 args = a;
+  void *params[] = {&args};
+  const auto launch = cooperative ? [](const void *k, dim3 g, dim3 t, void **p, size_t l, hipStream_t st) { return hipLaunchCooperativeKernel(k, g, t, p, (unsigned)l, st); }
+                                  : [](const void *k, dim3 g, dim3 t, void **p, size_t l, hipStream_t st) { return hipLaunchKernel(k, g, t, p, l, st); };
+  return launch(reinterpret_cast<const void *>(fn), dim3(8 * slots), dim3(256), params, lf > lb ? lf : lb, s);
 }
 
 }  // namespace lstm_int

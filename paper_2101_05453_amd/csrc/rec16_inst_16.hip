@@ -3,4 +3,5 @@
 
 namespace lstm_int {
 rec_fn rec16_pick_16(int fl) { return rec16_pick_ks<16>(fl); }
+rec16_pair_fn rec16_pick_pair_16(int fl) { return rec16_pick_ks<16, true, rec16_pair_fn>(fl); }
 }  // namespace lstm_int

@@ -3,4 +3,5 @@
 
 namespace lstm_int {
 rec_fn rec16_pick_4(int fl) { return rec16_pick_ks<4>(fl); }
+rec16_pair_fn rec16_pick_pair_4(int fl) { return rec16_pick_ks<4, true, rec16_pair_fn>(fl); }
 }  // namespace lstm_int

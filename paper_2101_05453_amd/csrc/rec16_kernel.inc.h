@@ -28,45 +28,57 @@ namespace lstm_int {
     }                                                                                     \
   } while (0)
 
-template <int KS16, int FL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void rec16_kernel(RecArgs a) {
+__device__ __forceinline__ const RecArgs &rec16_args(const RecArgs &a, int) { return a; }
+__device__ __forceinline__ const RecArgs &rec16_args(const RecArgs2 &a, int i) { return a.d[i]; }
+
+// PAIR: the launch runs two layers of one shape side by side, each possibly backward in time (RecArgs2).
+template <int KS16, int FL, bool PAIR = false>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void rec16_kernel(
+    std::conditional_t<PAIR, RecArgs2, RecArgs> args) {
   constexpr bool cifg = FL & 1, ph = FL & 2, ln = FL & 4;
   const long long t_start = (long long)wall_clock64();
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 15, q = lane >> 4;
-  const bool proj = a.flags & 8;
   constexpr int g_first = cifg ? 1 : 0;
-  const int GS = a.GS;
+  const RecArgs &a0 = rec16_args(args, 0);
+  const int GS = a0.GS;
 
   // placement, as in rec_kernel
   const int wg = blockIdx.x;
   const int xcc = (int)(__builtin_amdgcn_s_getreg(20 | (0 << 6) | (3 << 11)) & 7);
   const int slot = wg >> 3;
   int xcd = wg & 7;
-  if (a.tickets) {
+  if (a0.tickets) {
     xcd = xcc;
   } else if (xcc != xcd && GS > 1 && tid == 0) {
-    __hip_atomic_store(a.status, 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(a0.status, 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   auto placement_check = [&]() {
-    if (a.tickets && tid == 0) {
+    if (a0.tickets && tid == 0) {
       const int xcc_now = (int)(__builtin_amdgcn_s_getreg(20 | (0 << 6) | (3 << 11)) & 7);
       const unsigned places = gridDim.x >> 3;  // at most 32
       const u64 mine = ((u64)1 << 32) + ((u64)1 << (wg >> 3));
       const u64 now =
-          __hip_atomic_fetch_add(&a.tickets[xcc_now * 32], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + mine;
+          __hip_atomic_fetch_add(&a0.tickets[xcc_now * 32], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + mine;
       const unsigned count = (unsigned)(now >> 32);
       const unsigned all = places >= 32 ? 0xFFFFFFFFu : (1u << places) - 1;
       if (count > places || (count == places && (unsigned)now != all))
-        __hip_atomic_store(a.status, 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(a0.status, 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   };
-  const int group = xcd + 8 * (slot / GS), member = slot % GS;
-  if (group >= a.groups) {
+  const int gl = xcd + 8 * (slot / GS), member = slot % GS;  // group of the launch
+  if (gl >= a0.groups + (PAIR ? rec16_args(args, 1).groups : 0)) {
     placement_check();
     return;
   }
+  const int which = PAIR && gl >= a0.groups ? 1 : 0;
+  const RecArgs &a = rec16_args(args, which);
+  const int group = gl - (which ? a0.groups : 0);
+  const bool proj = a.flags & 8;
+  const int ldy = PAIR ? a.ldy : a.H;
+  // time of step t
+  auto time_of = [&](int t) { return PAIR && a.rev ? a.T - 1 - t : t; };
   constexpr int items = 64;                    // (gate, row) layer-norm rows of the group
   const int row0 = a.batch0 + group * 16;      // first batch row of the group
   const int cellw = wave * 16 + 4 * q;         // + c, within the workgroup's 64 cells
@@ -231,9 +243,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   __syncthreads();
 
   unsigned epoch = 0;
-  unsigned *counter = a.counters + group * 64;
+  unsigned *counter = a.counters + gl * 64;
   // one set of words: two sets (as in rec_kernel) made this kernel 2-3 % slower, at 8 and at 32 workgroups per group
-  u64 *accS = a.acc + (size_t)group * kStatGroupWords;  // [round][S1|S2][item], item < 64
+  u64 *accS = a.acc + (size_t)gl * kStatGroupWords;  // [round][S1|S2][item], item < 64
   int64_t prevS[2][2] = {{0, 0}, {0, 0}};       // this thread's item, per round: S1, S2
   const double inv_n = 1.0 / (double)a.N;
   const bool pre_ln = a.rln[0] < 33 || a.rln[1] < 33 || a.rln[2] < 33 || a.rln[3] < 33;
@@ -253,6 +265,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   // cell tile of 8 = 2 wave + q / 2, lane there = row % 32 + 32 * (q % 2)
   v4i txn0, txn1;
   auto tx_request = [&](int t) {
+    if (PAIR) t = time_of(t < a.T ? t : a.T - 1);
     size_t rb = ((size_t)t * a.Bp + row0) >> 5;
     const size_t rbmax = ((size_t)a.T * a.Bp) >> 5;
     rb = rb < rbmax ? rb : rbmax - 1;
@@ -267,7 +280,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   for (int t = 0; t < a.T; ++t) {
     // ---- h^{t-1} rows of the group -> LDS
     {
-      const int8_t *hp = t == 0 ? a.h0 : a.out + (size_t)(t - 1) * a.B * a.Hpad;
+      const int8_t *hp = t == 0 ? a.h0 : a.out + (size_t)time_of(t - 1) * a.B * a.Hpad;
 #pragma unroll
       for (int j = 0; j < NCH; ++j)
         __builtin_amdgcn_global_load_lds(
@@ -587,8 +600,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                          ((((size_t)(row >> 4) * (a.npadp >> 6) + member) * 16 + (row & 15)) << 6) + cellw;
           *reinterpret_cast<uint32_t *>(mdst) = pk;
         } else {
-          *reinterpret_cast<uint32_t *>(a.out + ((size_t)t * a.B + row) * a.Hpad + n0) = pk;
-          if (a.y) __builtin_nontemporal_store(pk, reinterpret_cast<uint32_t *>(a.y + ((size_t)t * a.B + row) * a.H + n0));
+          const size_t orow = (size_t)time_of(t) * a.B + row;
+          *reinterpret_cast<uint32_t *>(a.out + orow * a.Hpad + n0) = pk;
+          if (a.y) __builtin_nontemporal_store(pk, reinterpret_cast<uint32_t *>(a.y + orow * ldy + n0));
         }
       }
     }
@@ -647,14 +661,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             pk |= (uint32_t)(hq & 0xFF) << (8 * v);
           }
           if (row < a.B && p0 < a.H) {
-            int8_t *od = a.out + ((size_t)t * a.B + row) * a.Hpad + p0;
+            const size_t orow = (size_t)time_of(t) * a.B + row;
+            int8_t *od = a.out + orow * a.Hpad + p0;
             if (p0 + 3 < a.H) {
               *reinterpret_cast<uint32_t *>(od) = pk;
             } else {
               for (int c = 0; c < 4 && p0 + c < a.H; ++c) od[c] = (int8_t)(pk >> (8 * c));
             }
             if (a.y) {
-              int8_t *yd = a.y + ((size_t)t * a.B + row) * a.H + p0;
+              int8_t *yd = a.y + orow * ldy + p0;
               for (int c = 0; c < 4 && p0 + c < a.H; ++c) yd[c] = (int8_t)(pk >> (8 * c));
             }
           }
@@ -690,18 +705,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 
 #undef TICK
 
+typedef void (*rec16_pair_fn)(RecArgs2);
+
 // kernel for (flags & 7) at k depth KS16
-template <int KS16>
-rec_fn rec16_pick_ks(int fl) {
+template <int KS16, bool PAIR = false, class Fn = rec_fn>
+Fn rec16_pick_ks(int fl) {
   switch (fl & 7) {
-    case 0: return rec16_kernel<KS16, 0>;
-    case 1: return rec16_kernel<KS16, 1>;
-    case 2: return rec16_kernel<KS16, 2>;
-    case 3: return rec16_kernel<KS16, 3>;
-    case 4: return rec16_kernel<KS16, 4>;
-    case 5: return rec16_kernel<KS16, 5>;
-    case 6: return rec16_kernel<KS16, 6>;
-    default: return rec16_kernel<KS16, 7>;
+    case 0: return rec16_kernel<KS16, 0, PAIR>;
+    case 1: return rec16_kernel<KS16, 1, PAIR>;
+    case 2: return rec16_kernel<KS16, 2, PAIR>;
+    case 3: return rec16_kernel<KS16, 3, PAIR>;
+    case 4: return rec16_kernel<KS16, 4, PAIR>;
+    case 5: return rec16_kernel<KS16, 5, PAIR>;
+    case 6: return rec16_kernel<KS16, 6, PAIR>;
+    default: return rec16_kernel<KS16, 7, PAIR>;
   }
 }
 

@@ -54,6 +54,17 @@ def test_bidirectional_outputs_side_by_side(orc, case):
     assert_equal("bidi.y0", y2.cpu().numpy(), np.concatenate([orc.forward(of, xh), orc.forward(ob, xh, reverse=True)], axis=2))
 
 
+@pytest.mark.parametrize("case", [
+    (wl.PEEPHOLE, [30, 41], 41, 41, 3, 5),  # output rows that are no words of four
+    (wl.LAYER_NORM | wl.PROJECTION, [64, 130], 320, 130, 70, 4),  # five groups per direction over the XCDs
+    (wl.CIFG, [200], 512, 512, 33, 1),  # one step
+    (wl.LAYER_NORM, [24], 1024, 1024, 128, 3),  # both directions fill the chip together
+    (wl.LAYER_NORM, [24], 1024, 1024, 130, 2),  # one row more than fits: one after the other
+])
+def test_both_directions_in_one_launch(orc, case):
+    test_bidirectional_outputs_side_by_side(orc, case)
+
+
 def test_bidirectional_argument_checks(orc):
     import torch
     from paper_2101_05453_amd import binding
