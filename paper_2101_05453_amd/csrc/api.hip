@@ -135,7 +135,7 @@ struct lstm_int_model {
   int path = 0;
   int reverse = 0;  // 1: the recursion runs from time T - 1 down to 0
   int cooperative = 0;  // 1: the persistent kernel is launched cooperatively
-  int rows16 = 1;       // 1: batches that fit one launch of the 16-row kernel take it
+  int rows16 = 1;       // 1, 2: batches that fit one launch of the 16-row kernel take it; 1: layers of up to 256 cells its one-workgroup form
   int sparse = 1;       // 1: layers whose recurrent weights are 2:4 run R h on the sparse MFMA (32-row kernel)
   int stack = 1;        // stacked launch (one layer per XCD): 0 never, 1 where it is expected to be faster, 2 wherever it can run
   int flag_sleep = 2;   // stacked launch: pause between two polls of the layer below's flag, x 64 clocks
@@ -272,8 +272,9 @@ Requant make_requant(const int32_t *M, const int32_t *e, int first, int count, i
 // on the device can take the whole GPU down).  T_all = steps of the whole call, t0 = first step of this launch.
 bool rec_extents_ok(const RecArgs &ra, const Workspace &ws, int T_all, int t0, bool has_proj) {
   const size_t Bp = (size_t)ra.Bp;
+  const bool solo = ra.tickets == nullptr && ra.counters == nullptr;  // the one-workgroup kernel has no scratch
   if (ra.Bp % 32 || ra.Bp < ra.B || ra.B < 1 || ra.T < 1 || t0 < 0 || t0 + ra.T > T_all) return false;
-  if (ra.groups < 1 || ra.groups > 256 || ra.batch0 < 0 || ra.batch0 >= ra.B) return false;
+  if (ra.groups < 1 || (ra.groups > 256 && !solo) || ra.batch0 < 0 || ra.batch0 >= ra.B) return false;
   // the first row of every group is a real row: later row tiles of a group are skipped or clamped by the kernels
   if ((int64_t)ra.batch0 + (int64_t)(ra.groups - 1) * ra.rows_pg >= ra.B) return false;
   // W x terms: [T_all * Bp / 32][GS * 8 tiles][2][64 lanes] 16-byte pieces
@@ -283,6 +284,7 @@ bool rec_extents_ok(const RecArgs &ra, const Workspace &ws, int T_all, int t0, b
   // m exchange buffer [T][Bp][npadp] in tiles
   if (has_proj && (size_t)ra.T * Bp * ra.npadp > ws.m2_bytes) return false;
   // counters [groups][64] words and statistics accumulators [groups][4][256] 64-bit words
+  if (solo) return true;
   if ((size_t)ra.groups * 64 * 4 > (size_t)256 * 64 * 4 || (size_t)ra.groups * kStatGroupBytes > (size_t)256 * kStatGroupBytes)
     return false;
   return true;
@@ -611,7 +613,7 @@ int upload(lstm_int_model *m) {
   m->tanh3 = reinterpret_cast<const uint16_t *>(dbase + tab_off[3]);
   m->wsig3 = wide_sig;
   m->wtanh3 = wide_tab[3];
-  if (rec_init() != hipSuccess || rec16_init() != hipSuccess || in_gemm_init() != hipSuccess || gemm_init() != hipSuccess || stack_init() != hipSuccess)
+  if (rec_init() != hipSuccess || rec16_init() != hipSuccess || solo_init() != hipSuccess || in_gemm_init() != hipSuccess || gemm_init() != hipSuccess || stack_init() != hipSuccess)
     return LSTM_INT_E_DEVICE;
   // The stacked kernel runs models whose layers are all alike (same cells, width and variant; every layer
   // above the first reads the layer below), up to 8 of them, within the shift and table limits of the
@@ -834,7 +836,7 @@ int forward_stack(lstm_int_model *m, const int8_t *x, int32_t T, int32_t B, int8
 struct RecPlan {
   RecArgs ra;
   int groups = 0;      // most groups in one launch
-  bool ok = false, use16 = false;
+  bool ok = false, use16 = false, solo = false;  // solo: the one-workgroup form of the 16-row kernel
 };
 
 RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B) {
@@ -896,9 +898,20 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B) {
     ra.groups = p2_groups;
   }
   if (!ok || !lut_ok || rec_lds_bytes(ra) > 160 * 1024) return p;
+  // layers of up to 256 cells: one workgroup per 4 rows, nothing to exchange
+  if (m->rows16 == 1 && d.p16 && solo_supported(h.N, h.H, (int)h.flags, B)) {
+    RecArgs r1 = ra;
+    r1.R2h = d.R2h; r1.ks16 = d.ks16; r1.rows_pg = 4; r1.groups = (B + 3) / 4; r1.ldy = h.H;
+    r1.Wp2 = d.Wp2; r1.bp2 = d.bp2; r1.ptiles = d.ptiles; r1.prow = 32;
+    if (solo_lds_bytes(r1) <= 160 * 1024) {
+      ra = r1;
+      p2_groups = r1.groups;
+      p.solo = p.use16 = true;
+    }
+  }
   // small batches: groups of 16 rows fill more compute units and halve a step's arithmetic
   int k16 = 0, g16 = 0;
-  if (m->rows16 && d.p16 && rec16_supported(h.N, h.H, (int)h.flags, B, &k16, &g16)) {
+  if (!p.solo && m->rows16 && d.p16 && rec16_supported(h.N, h.H, (int)h.flags, B, &k16, &g16)) {
     RecArgs r16 = ra;
     r16.R2h = d.R2h; r16.ks16 = d.ks16; r16.rows_pg = 16; r16.groups = g16;
     r16.Wp2 = d.Wp2; r16.bp2 = d.bp2; r16.ptiles = d.ptiles; r16.prow = 32;
@@ -913,7 +926,7 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B) {
     ra.R2 = d.R2s;
     ra.sparse = 1;
   }
-  auto lds_need = [&]() { return p.use16 ? rec16_lds_bytes(ra) : rec_lds_bytes(ra); };
+  auto lds_need = [&]() { return p.solo ? solo_lds_bytes(ra) : p.use16 ? rec16_lds_bytes(ra) : rec_lds_bytes(ra); };
   // What LDS is left goes to longer prefixes of the two gate tables, 1 KB at a time in turn: a value
   // beyond the prefix costs the whole group a detour (rec_kernel.inc.h, lookup), and with 24576 entries
   // (|x| < 6 in Q3.12) there is about one per million layer-norm outputs instead of one per thousand.
@@ -1061,7 +1074,7 @@ int lstm_int_forward(const lstm_int_model *cm, const int8_t *x, int32_t T, int32
       ra.mbuf = reinterpret_cast<int8_t *>(wsb + ws.m2);
       ra.c_in = c_state ? c_state + c_off : nullptr;
       ra.c_out = c_state ? c_state + c_off : nullptr;
-      set_sync(ra, m, wsb + ws.sync);
+      if (!plan.solo) set_sync(ra, m, wsb + ws.sync);
     }
     if (use_p2) {
       const int launch_rows = p2_groups * ra.rows_pg;
@@ -1076,17 +1089,18 @@ int lstm_int_forward(const lstm_int_model *cm, const int8_t *x, int32_t T, int32
         // final h on its way to the state buffer: done by the input GEMM's workgroups ahead of their own
         // work, or by a kernel of their own where the general input GEMM runs
         const int g0 = std::min(p2_groups, (B + ra.rows_pg - 1) / ra.rows_pg);
+        const int64_t clear = plan.solo ? 0 : sync_bytes(g0);
         const bool ws_gemm = in_gemm_ws_supported(ga);
         if (ws_gemm) {
           ga.has_init = 1;
           ga.init.h_src = h_state ? h_state + h_off : nullptr; ga.init.ld_src = h.H;
           ga.init.h0 = h0; ga.init.ld_h0 = d.Hpad; ga.init.rows = B; ga.init.cols = h.H; ga.init.zp = h.zp_h;
-          ga.init.sync = reinterpret_cast<int4 *>(wsb + ws.sync); ga.init.sync_vec = sync_bytes(g0) / 16;
+          ga.init.sync = reinterpret_cast<int4 *>(wsb + ws.sync); ga.init.sync_vec = clear / 16;
           ga.init.c_src = pend.src; ga.init.c_ld_src = pend.ld; ga.init.c_dst = pend.dst; ga.init.c_cols = pend.cols;
         } else {
           Timed t(m->prof, s, LSTM_INT_K_OTHER);
           launch_init_layer(s, h_state ? h_state + h_off : nullptr, h.H, h0, d.Hpad, B, h.H, h.zp_h, wsb + ws.sync,
-                            sync_bytes(g0), pend.src, pend.ld, pend.dst, pend.cols);
+                            clear, pend.src, pend.ld, pend.dst, pend.cols);
         }
         pend.dst = nullptr;
         Timed t(m->prof, s, LSTM_INT_K_INPUT_GEMM);
@@ -1113,14 +1127,18 @@ int lstm_int_forward(const lstm_int_model *cm, const int8_t *x, int32_t T, int32
         for (int b0 = 0; b0 < B; b0 += launch_rows) {
           ra.batch0 = b0;
           ra.groups = std::min(p2_groups, (B - b0 + ra.rows_pg - 1) / ra.rows_pg);
-          if (b0 > 0 || t0 > 0) {
+          if (!plan.solo && (b0 > 0 || t0 > 0)) {
             Timed t(m->prof, s, LSTM_INT_K_OTHER);
             launch_fill_i16(s, reinterpret_cast<int16_t *>(wsb + ws.sync), sync_bytes(ra.groups) / 2, 0);
           }
           if (!rec_extents_ok(ra, ws, T, t0, proj)) return LSTM_INT_E_WORKSPACE;
           Timed t(m->prof, s, LSTM_INT_K_RECURRENT);
           const bool coop = m->cooperative != 0;
-          if ((use16 ? launch_rec16(s, ra, coop) : launch_rec(s, ra, coop)) != hipSuccess) return LSTM_INT_E_DEVICE;
+          RecArgs2 one;
+          memset(&one, 0, sizeof(one));
+          if (plan.solo) one.d[0] = ra;
+          if ((plan.solo ? launch_solo(s, one) : use16 ? launch_rec16(s, ra, coop) : launch_rec(s, ra, coop)) != hipSuccess)
+            return LSTM_INT_E_DEVICE;
         }
       }
       {
@@ -1260,7 +1278,8 @@ static bool pair_chosen(const lstm_int_model *f, const lstm_int_model *b, int32_
     if (hf.N != hb.N || hf.H != hb.H || hf.flags != hb.flags || hf.I != hb.I) return false;
     if ((f->sparse == 2 && f->dev[l].R2s) || (b->sparse == 2 && b->dev[l].R2s)) return false;
     const RecPlan pf = plan_rec(f, (int)l, T, B), pb = plan_rec(b, (int)l, T, B);
-    if (!pf.ok || !pb.ok || !pf.use16 || !pb.use16 || pf.groups + pb.groups > 8 * (32 / pf.ra.GS)) return false;
+    if (!pf.ok || !pb.ok || !pf.use16 || !pb.use16 || pf.solo != pb.solo) return false;
+    if (!pf.solo && pf.groups + pb.groups > 8 * (32 / pf.ra.GS)) return false;
   }
   return true;
 }
@@ -1304,7 +1323,7 @@ static int forward_pair(lstm_int_model *const (&m)[2], const int8_t *x, int32_t 
       ga.a_slack = in[i] != x;
       ga.tx2 = reinterpret_cast<int4 *>(base[i] + ws[i].tx);
       uint8_t *sync = base[0] + ws[0].sync;
-      const int64_t clear = i == 0 ? sync_bytes(groups) : 0;
+      const int64_t clear = i == 0 && !plan[0].solo ? sync_bytes(groups) : 0;
       if (in_gemm_ws_supported(ga)) {
         ga.has_init = 1;
         ga.init.h_src = h_src; ga.init.ld_src = h.H;
@@ -1331,7 +1350,7 @@ static int forward_pair(lstm_int_model *const (&m)[2], const int8_t *x, int32_t 
       ra.rev = i;
       ra.ldy = Hl[0] + Hl[1];
       ra.y = l == L - 1 && y_direct ? y + (i ? Hl[0] : 0) : nullptr;
-      set_sync(ra, m[0], sync);
+      if (!plan[0].solo) set_sync(ra, m[0], sync);
       if (!rec_extents_ok(ra, ws[i], T, 0, h.projection())) return LSTM_INT_E_WORKSPACE;
       pend[i].dst = nullptr;
       if (h_state[i]) {
@@ -1345,9 +1364,9 @@ static int forward_pair(lstm_int_model *const (&m)[2], const int8_t *x, int32_t 
       in[i] = out;
       ld_in[i] = d.Hpad;
     }
-    if ((size_t)groups * kStatGroupBytes > (size_t)256 * kStatGroupBytes) return LSTM_INT_E_WORKSPACE;
     Timed t0(m[0]->prof, s, LSTM_INT_K_RECURRENT), t1(m[1]->prof, s, LSTM_INT_K_RECURRENT);
-    if (launch_rec16_pair(s, pair, m[0]->cooperative != 0) != hipSuccess) return LSTM_INT_E_DEVICE;
+    if ((plan[0].solo ? launch_solo(s, pair) : launch_rec16_pair(s, pair, m[0]->cooperative != 0)) != hipSuccess)
+      return LSTM_INT_E_DEVICE;
   }
   for (int i = 0; i < 2; ++i) {
     Timed t(m[i]->prof, s, LSTM_INT_K_OTHER);
@@ -1430,7 +1449,7 @@ int lstm_int_set_option(lstm_int_model *m, const char *key, int64_t value) {
     return LSTM_INT_OK;
   }
   if (!strcmp(key, "rows16")) {
-    if (value < 0 || value > 1) return LSTM_INT_E_INVALID_ARG;
+    if (value < 0 || value > 2) return LSTM_INT_E_INVALID_ARG;
     m->rows16 = (int)value;
     return LSTM_INT_OK;
   }

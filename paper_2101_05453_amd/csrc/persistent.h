@@ -156,7 +156,7 @@ struct RecArgs {
   int extra_arrivals;  // 0; tests set 1: every group barrier then waits for an arrival that never comes, so that
                        // the bounded waits give up (and every workgroup leaves the kernel) on demand
   int sparse;  // rec_kernel, 32 rows per group: R2 holds the recurrent weights in the 2:4 compressed form below
-  int ldy, rev;  // pair launches only (RecArgs2): row stride of y; 1 = step t works at time T - 1 - t
+  int ldy, rev;  // RecArgs2 launches only: row stride of y; 1 = step t works at time T - 1 - t
 };
 
 // Two layers of one shape in one launch of the 16-row kernel (the two directions of a bidirectional layer): groups
@@ -197,6 +197,14 @@ hipError_t launch_rec16(hipStream_t s, const RecArgs &a, bool cooperative);
 // both fit one launch: d[0].groups + d[1].groups <= 8 (32 / GS)
 hipError_t launch_rec16_pair(hipStream_t s, const RecArgs2 &a, bool cooperative);
 hipError_t rec16_init();
+
+// The same step for layers of up to 256 cells and outputs, one workgroup per 4 batch rows (solo_kernel.inc.h): no
+// exchange between workgroups, hence no synchronization scratch, and any number of steps in one launch.
+// Takes RecArgs2 always (d[1].groups = 0: one layer); rows_pg = 4, groups = ceil(B / 4), ldy set.
+bool solo_supported(int N, int H, int flags, int B);
+size_t solo_lds_bytes(const RecArgs &a);
+hipError_t launch_solo(hipStream_t s, const RecArgs2 &a);
+hipError_t solo_init();
 
 // ---------------------------------------------------------------------------
 // Stacked layers in one launch (stack_kernel.inc.h): layer l of a stack of up to 8 equal layers runs on

@@ -539,6 +539,13 @@ def test_large_input_product_on_the_per_step_path(orc):
     (65, None, wl.CIFG, 5, {}),  # one
     (1, None, wl.LAYER_NORM, 3, {}),
     (2, None, 0, 600, {"rows16": 0}),
+    (203, None, wl.LAYER_NORM | wl.PEEPHOLE, 21, {"rows16": 2}),  # groups of 16 rows, several workgroups each
+    (130, 57, wl.CIFG | wl.LAYER_NORM | wl.PROJECTION, 33, {"rows16": 2}),
+    (256, 255, wl.LAYER_NORM | wl.PEEPHOLE | wl.PROJECTION, 7, {}),  # the widest row of one workgroup
+    (250, None, wl.CIFG | wl.LAYER_NORM, 5, {}),
+    (128, 64, wl.PROJECTION | wl.PEEPHOLE, 9, {}),
+    (100, None, wl.LAYER_NORM, 1030, {}),  # two rounds of workgroups
+    (64, 64, wl.LAYER_NORM | wl.PROJECTION, 4, {}),
 ])
 @pytest.mark.parametrize("stack", [0, 2])
 def test_any_number_of_cells_on_the_persistent_kernels(orc, N, H, flags, B, options, stack):
