@@ -697,9 +697,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 
   placement_check();
   if (a.c_out && row < a.B && n0 < a.N) {
+    int n1 = n0;
+    asm volatile("" : "+v"(n1));  // computed here: shared with the prologue it would hold registers through the loop
 #pragma unroll
     for (int c = 0; c < 4; ++c)
-      if (n0 + c < a.N) a.c_out[(size_t)row * a.N + n0 + c] = (int16_t)creg[c];
+      if (n1 + c < a.N) a.c_out[(size_t)row * a.N + n1 + c] = (int16_t)creg[c];
   }
 }
 

@@ -974,7 +974,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
       for (int tl = 0; tl < 2; ++tl) {
         const int row = row0 + rt * 32 + col;
-        const int n0 = member * 64 + cell_w + tl * 8;
+        int n0 = member * 64 + cell_w + tl * 8;
+        asm volatile("" : "+v"(n0));  // computed here: shared with the prologue it would hold six registers through the loop
         if (row < a.B && n0 < a.N)
 #pragma unroll
           for (int c = 0; c < 4; ++c)
