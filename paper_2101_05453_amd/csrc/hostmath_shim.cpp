@@ -32,7 +32,7 @@ void hm_layernorm2(const int16_t *q, int32_t n, const int16_t *qL, const int32_t
     s1 += q[i];
     s2 += (int64_t)q[i] * q[i];
   }
-  const LnRow2 row = ln_row2(ln_row(s1, s2, n, 1.0 / (double)n));
+  const LnRow2 row = ln_row2(s1, s2, n, 1.0 / (double)n);
   const RescaleHi p = rescale_hi_prepare(M, r);
   for (int i = 0; i < n; ++i)
     out[i] = ln_row_is_narrow(row)
@@ -46,7 +46,7 @@ int hm_ln_row_is_narrow(const int16_t *q, int32_t n) {
     s1 += q[i];
     s2 += (int64_t)q[i] * q[i];
   }
-  return ln_row_is_narrow(ln_row2(ln_row(s1, s2, n, 1.0 / (double)n))) ? 1 : 0;
+  return ln_row_is_narrow(ln_row2(s1, s2, n, 1.0 / (double)n)) ? 1 : 0;
 }
 int32_t hm_rescale_sat16_pre(int32_t a, int32_t M, int32_t r) {
   return rescale_sat16_pre(a, rescale_hi_prepare(M, r));

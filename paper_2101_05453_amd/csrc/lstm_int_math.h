@@ -184,11 +184,51 @@ LSTM_HD int32_t ln_apply(int32_t q, const LnRow &row, int32_t qL, int32_t qb, in
 struct LnRow2 {
   double a, b;
 };
-LSTM_HD LnRow2 ln_row2(const LnRow &r) {
+// From the sums, in double all the way (the integers are those of ln_row): a row's (mean, sigma) is a chain of
+// dependent operations that every step of a recurrent kernel waits for, and conversions between 64-bit integers and
+// double, a correctly rounded square root and a correctly rounded division were more than half of it (0.2 to 0.3 us of
+// a round of statistics).
+//   quotients: floor(num / n) with |num| < 2^52 from the rounded reciprocal of n, corrected by the exact remainder as in
+//     floor_div_recip (all integers here are exact in double; S2 2^20 is not, hence the split of ln_row for every n);
+//   sigma = floor(sqrt(var)), var < 2^50: an estimate good to 2^-40 misses the root by less than one, and the exact
+//     remainder settles it as in isqrt_u52;
+//   1 / sigma: any reciprocal good to 2^-45 leaves the quotient estimate of ln_second_stage inside its margin (2^37 2^-45
+//     = 2^-8 against 1/2, in units of 1 / sigma).
+// On the device the square root and the reciprocal start from the hardware's estimates (2^-23), with one and two steps of
+// Newton's iteration (2^-45, 2^-53).
+LSTM_HD double floor_div_f64(double num, double d, double inv_d) {
+  const double q = floor(num * inv_d);
+  const double rem = fma(-q, d, num);
+  return rem < 0.0 ? q - 1.0 : (rem >= d ? q + 1.0 : q);
+}
+LSTM_HD LnRow2 ln_row2(int64_t S1, int64_t S2, int32_t n, double inv_n) {
+  const double dn = (double)n, half = (double)(n >> 1), s2 = (double)S2;
+  const double mean = floor_div_f64((double)S1 * 1024.0 + half, dn, inv_n);
+  const double q = floor_div_f64(s2, dn, inv_n);
+  const double low = floor_div_f64(fma(fma(-q, dn, s2), 1048576.0, half), dn, inv_n);
+  double var = fma(q, 1048576.0, low) - mean * mean;  // every term an integer of at most 2^50
+  var = var > 0.0 ? var : 0.0;
+#if defined(__HIP_DEVICE_COMPILE__)
+  const double y = __builtin_amdgcn_rsq(var > 0.0 ? var : 1.0);
+  double r = var * y;
+  r = floor(fma(0.5 * y, fma(-r, r, var), r));
+#else
+  double r = floor(sqrt(var));
+#endif
+  const double rem = fma(-r, r, var);
+  r = rem < 0.0 ? r - 1.0 : (rem >= 2.0 * r + 1.0 ? r + 1.0 : r);
+#if defined(__HIP_DEVICE_COMPILE__)
+  const double d = r > 0.0 ? r : 1.0;
+  double inv = __builtin_amdgcn_rcp(d);
+  inv = fma(inv, fma(-d, inv, 1.0), inv);
+  inv = fma(inv, fma(-d, inv, 1.0), inv);
+  inv = r > 0.0 ? inv : 0.0;
+#else
+  const double inv = r > 0.0 ? 1.0 / r : 0.0;
+#endif
   LnRow2 o;
-  const double inv = r.sigma ? r.inv_sigma : 0.0;
   o.a = 1048576.0 * inv;
-  o.b = ((double)(-(int64_t)r.mean * 1024 + (r.sigma >> 1)) + 0.5) * inv;
+  o.b = (fma(mean, -1024.0, floor(r * 0.5)) + 0.5) * inv;
   return o;
 }
 LSTM_HD double ln_weight_scaled(int32_t qL) { return (double)qL * (1.0 / 1024.0); }

@@ -401,7 +401,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
           const int64_t S2 = (int64_t)((c2 - (u64)prevS[round][1]) & kValMask);
           prevS[round][0] = (int64_t)c1;
           prevS[round][1] = (int64_t)c2;
-          lnrow[tid] = ln_row2(ln_row(S1, S2, a.N, inv_n));
+          lnrow[tid] = ln_row2(S1, S2, a.N, inv_n);
         }
       }
       __syncthreads();

@@ -219,7 +219,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
       const bool here = lane < 16 && (item >> 2) >= g_lo && (item >> 2) <= g_hi;
       const int64_t pk = (int64_t)red[item];
       const int64_t S1 = ((pk + (1 << 23)) & 0xFFFFFF) - (1 << 23);  // 256 values of at most 32767: below 2^23
-      const LnRow2 lr = ln_row2(ln_row(S1, (pk - S1) >> 24, N, inv_n));
+      const LnRow2 lr = ln_row2(S1, (pk - S1) >> 24, N, inv_n);
       const bool narrow = __builtin_amdgcn_ballot_w64(here && !ln_row_is_narrow(lr)) == 0;
       if (here) {
         red[item] = 0;  // the next adds come after the barrier below

@@ -590,7 +590,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             prevS[round][ss][0] = (int64_t)c1[ss];
             prevS[round][ss][1] = (int64_t)c2[ss];
           }
-          lnrow[tid] = ln_row2(ln_row(S1, S2, a.N, inv_n));
+          lnrow[tid] = ln_row2(S1, S2, a.N, inv_n);
         }
       }
       __syncthreads();
