@@ -284,9 +284,9 @@ int lstm_int_forward_bidirectional(const lstm_int_model *fwd, const lstm_int_mod
  *   "rows16": 1 (default) = batches of up to 16 * 8 * (32 / ceil(N / 64)) rows
  *           run in a variant of the persistent kernel that works on groups of
  *           16 rows (more compute units busy, half the arithmetic per
- *           workgroup and step), layers of up to 256 cells at any batch with one
- *           workgroup per 16 rows; 2 = without the latter; 0 = always groups of
- *           32 or 64 rows.
+ *           workgroup and step), of 4 rows where that still fits one launch, or, for
+ *           layers of up to 256 cells, one workgroup per 4 rows; 2 = groups of
+ *           16 rows only; 0 = always groups of 32 or 64 rows.
  *   "cooperative_launch": the persistent kernel needs all its workgroups (one
  *           per compute unit, up to all of them) on the device at once.
  *           0 (default) = plain launch: that holds when nothing else occupies

@@ -135,7 +135,7 @@ struct lstm_int_model {
   int path = 0;
   int reverse = 0;  // 1: the recursion runs from time T - 1 down to 0
   int cooperative = 0;  // 1: the persistent kernel is launched cooperatively
-  int rows16 = 1;       // 1, 2: batches that fit one launch of the 16-row kernel take it; 1: layers of up to 256 cells its one-workgroup form
+  int rows16 = 1;       // 1, 2: batches that fit one launch of the 16-row kernel take it; 1: also the one-workgroup and the four-row kernel
   int sparse = 1;       // 1: layers whose recurrent weights are 2:4 run R h on the sparse MFMA (32-row kernel)
   int stack = 1;        // stacked launch (one layer per XCD): 0 never, 1 where it is expected to be faster, 2 wherever it can run
   int flag_sleep = 2;   // stacked launch: pause between two polls of the layer below's flag, x 64 clocks
@@ -162,6 +162,8 @@ struct Workspace {
   size_t tx_bytes, out_bytes, m2_bytes;  // extents of the regions the persistent kernels index
 };
 constexpr size_t kStatGroupBytes = (size_t)kStatGroupWords * 8;  // statistics words of one group of workgroups
+constexpr size_t kQuadWgBytes = 2 * kQuadWgWords * 8;  // exchange words of one workgroup of the four-row kernel
+static_assert(kQuadWgBytes <= kStatGroupBytes, "they lie where the statistics words of 256 groups are");
 constexpr size_t kSyncBytes = 256 * 64 * 4 + 256 * kStatGroupBytes;  // counters + statistics accumulators
 constexpr size_t kStackFlagsOff = 256 * 64 * 4 + 8 * kStatGroupBytes;  // stacked launch: flags behind the counters and the statistics words of its 8 layers
 
@@ -613,7 +615,7 @@ int upload(lstm_int_model *m) {
   m->tanh3 = reinterpret_cast<const uint16_t *>(dbase + tab_off[3]);
   m->wsig3 = wide_sig;
   m->wtanh3 = wide_tab[3];
-  if (rec_init() != hipSuccess || rec16_init() != hipSuccess || solo_init() != hipSuccess || in_gemm_init() != hipSuccess || gemm_init() != hipSuccess || stack_init() != hipSuccess)
+  if (rec_init() != hipSuccess || rec16_init() != hipSuccess || solo_init() != hipSuccess || quad_init() != hipSuccess || in_gemm_init() != hipSuccess || gemm_init() != hipSuccess || stack_init() != hipSuccess)
     return LSTM_INT_E_DEVICE;
   // The stacked kernel runs models whose layers are all alike (same cells, width and variant; every layer
   // above the first reads the layer below), up to 8 of them, within the shift and table limits of the
@@ -836,10 +838,12 @@ int forward_stack(lstm_int_model *m, const int8_t *x, int32_t T, int32_t B, int8
 struct RecPlan {
   RecArgs ra;
   int groups = 0;      // most groups in one launch
-  bool ok = false, use16 = false, solo = false;  // solo: the one-workgroup form of the 16-row kernel
+  bool ok = false, use16 = false;
+  bool solo = false, quad = false;  // with use16: the one-workgroup kernel / the four-row kernel instead of the 16-row one
 };
 
-RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B) {
+// share: launches' worth of groups that are to fit one launch (2: both directions of a bidirectional layer)
+RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1) {
   const LayerHost &h = m->host[l];
   const LayerDev &d = m->dev[l];
   const bool proj = h.projection();
@@ -909,9 +913,21 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B) {
       p.solo = p.use16 = true;
     }
   }
+  // larger layers, batches small enough for it: groups of four rows
+  int g4 = 0;
+  if (!p.solo && m->rows16 == 1 && d.p16 && quad_supported(h.N, h.H, (int)h.flags, B, share, &g4)) {
+    RecArgs r4 = ra;
+    r4.R2h = d.R2h; r4.ks16 = d.ks16; r4.rows_pg = 4; r4.groups = g4; r4.ldy = h.H;
+    r4.Wp2 = d.Wp2; r4.bp2 = d.bp2; r4.ptiles = d.ptiles; r4.prow = 32;
+    if (quad_lds_bytes(r4) <= 160 * 1024) {
+      ra = r4;
+      p2_groups = g4;
+      p.quad = p.use16 = true;
+    }
+  }
   // small batches: groups of 16 rows fill more compute units and halve a step's arithmetic
   int k16 = 0, g16 = 0;
-  if (!p.solo && m->rows16 && d.p16 && rec16_supported(h.N, h.H, (int)h.flags, B, &k16, &g16)) {
+  if (!p.use16 && m->rows16 && d.p16 && rec16_supported(h.N, h.H, (int)h.flags, B, &k16, &g16)) {
     RecArgs r16 = ra;
     r16.R2h = d.R2h; r16.ks16 = d.ks16; r16.rows_pg = 16; r16.groups = g16;
     r16.Wp2 = d.Wp2; r16.bp2 = d.bp2; r16.ptiles = d.ptiles; r16.prow = 32;
@@ -926,7 +942,7 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B) {
     ra.R2 = d.R2s;
     ra.sparse = 1;
   }
-  auto lds_need = [&]() { return p.solo ? solo_lds_bytes(ra) : p.use16 ? rec16_lds_bytes(ra) : rec_lds_bytes(ra); };
+  auto lds_need = [&]() { return p.quad ? quad_lds_bytes(ra) : p.solo ? solo_lds_bytes(ra) : p.use16 ? rec16_lds_bytes(ra) : rec_lds_bytes(ra); };
   // What LDS is left goes to longer prefixes of the two gate tables, 1 KB at a time in turn: a value
   // beyond the prefix costs the whole group a detour (rec_kernel.inc.h, lookup), and with 24576 entries
   // (|x| < 6 in Q3.12) there is about one per million layer-norm outputs instead of one per thousand.
@@ -967,6 +983,10 @@ void set_sync(RecArgs &ra, const lstm_int_model *m, uint8_t *sync) {
 // Bytes of that scratch a launch over `groups` groups uses, all of them to be cleared before it: all counters, and the
 // statistics words of its groups (they follow the counters).
 int64_t sync_bytes(int groups) { return (int64_t)256 * 64 * 4 + (int64_t)groups * (int64_t)kStatGroupBytes; }
+// ... as the plan's kernel uses it (the four-row kernel's exchange words lie where the statistics words are)
+int64_t sync_bytes(const RecPlan &p, int groups) {
+  return p.solo ? 0 : p.quad ? (int64_t)256 * 64 * 4 + (int64_t)groups * p.ra.GS * kQuadWgBytes : sync_bytes(groups);
+}
 
 // The hoisted W x of layer l (its output goes to ga.tx2, in the tile order of the recurrent kernels).
 InGemmArgs plan_in_gemm(const lstm_int_model *m, int l, int T, int B) {
@@ -1089,7 +1109,7 @@ int lstm_int_forward(const lstm_int_model *cm, const int8_t *x, int32_t T, int32
         // final h on its way to the state buffer: done by the input GEMM's workgroups ahead of their own
         // work, or by a kernel of their own where the general input GEMM runs
         const int g0 = std::min(p2_groups, (B + ra.rows_pg - 1) / ra.rows_pg);
-        const int64_t clear = plan.solo ? 0 : sync_bytes(g0);
+        const int64_t clear = sync_bytes(plan, g0);
         const bool ws_gemm = in_gemm_ws_supported(ga);
         if (ws_gemm) {
           ga.has_init = 1;
@@ -1129,15 +1149,15 @@ int lstm_int_forward(const lstm_int_model *cm, const int8_t *x, int32_t T, int32
           ra.groups = std::min(p2_groups, (B - b0 + ra.rows_pg - 1) / ra.rows_pg);
           if (!plan.solo && (b0 > 0 || t0 > 0)) {
             Timed t(m->prof, s, LSTM_INT_K_OTHER);
-            launch_fill_i16(s, reinterpret_cast<int16_t *>(wsb + ws.sync), sync_bytes(ra.groups) / 2, 0);
+            launch_fill_i16(s, reinterpret_cast<int16_t *>(wsb + ws.sync), sync_bytes(plan, ra.groups) / 2, 0);
           }
           if (!rec_extents_ok(ra, ws, T, t0, proj)) return LSTM_INT_E_WORKSPACE;
           Timed t(m->prof, s, LSTM_INT_K_RECURRENT);
           const bool coop = m->cooperative != 0;
           RecArgs2 one;
           memset(&one, 0, sizeof(one));
-          if (plan.solo) one.d[0] = ra;
-          if ((plan.solo ? launch_solo(s, one) : use16 ? launch_rec16(s, ra, coop) : launch_rec(s, ra, coop)) != hipSuccess)
+          if (plan.solo || plan.quad) one.d[0] = ra;
+          if ((plan.solo ? launch_solo(s, one) : plan.quad ? launch_quad(s, one, coop) : use16 ? launch_rec16(s, ra, coop) : launch_rec(s, ra, coop)) != hipSuccess)
             return LSTM_INT_E_DEVICE;
         }
       }
@@ -1277,8 +1297,8 @@ static bool pair_chosen(const lstm_int_model *f, const lstm_int_model *b, int32_
     const LayerHost &hf = f->host[l], &hb = b->host[l];
     if (hf.N != hb.N || hf.H != hb.H || hf.flags != hb.flags || hf.I != hb.I) return false;
     if ((f->sparse == 2 && f->dev[l].R2s) || (b->sparse == 2 && b->dev[l].R2s)) return false;
-    const RecPlan pf = plan_rec(f, (int)l, T, B), pb = plan_rec(b, (int)l, T, B);
-    if (!pf.ok || !pb.ok || !pf.use16 || !pb.use16 || pf.solo != pb.solo) return false;
+    const RecPlan pf = plan_rec(f, (int)l, T, B, 2), pb = plan_rec(b, (int)l, T, B, 2);
+    if (!pf.ok || !pb.ok || !pf.use16 || !pb.use16 || pf.solo != pb.solo || pf.quad != pb.quad) return false;
     if (!pf.solo && pf.groups + pb.groups > 8 * (32 / pf.ra.GS)) return false;
   }
   return true;
@@ -1310,7 +1330,7 @@ static int forward_pair(lstm_int_model *const (&m)[2], const int8_t *x, int32_t 
   size_t h_off[2] = {0, 0}, c_off[2] = {0, 0};
   for (int l = 0; l < L; ++l) {
     RecArgs2 pair;
-    RecPlan plan[2] = {plan_rec(m[0], l, T, B), plan_rec(m[1], l, T, B)};
+    RecPlan plan[2] = {plan_rec(m[0], l, T, B, 2), plan_rec(m[1], l, T, B, 2)};
     const int groups = plan[0].groups + plan[1].groups;
     for (int i = 0; i < 2; ++i) {
       const LayerHost &h = m[i]->host[l];
@@ -1323,7 +1343,7 @@ static int forward_pair(lstm_int_model *const (&m)[2], const int8_t *x, int32_t 
       ga.a_slack = in[i] != x;
       ga.tx2 = reinterpret_cast<int4 *>(base[i] + ws[i].tx);
       uint8_t *sync = base[0] + ws[0].sync;
-      const int64_t clear = i == 0 && !plan[0].solo ? sync_bytes(groups) : 0;
+      const int64_t clear = i == 0 ? sync_bytes(plan[0], groups) : 0;
       if (in_gemm_ws_supported(ga)) {
         ga.has_init = 1;
         ga.init.h_src = h_src; ga.init.ld_src = h.H;
@@ -1365,7 +1385,8 @@ static int forward_pair(lstm_int_model *const (&m)[2], const int8_t *x, int32_t 
       ld_in[i] = d.Hpad;
     }
     Timed t0(m[0]->prof, s, LSTM_INT_K_RECURRENT), t1(m[1]->prof, s, LSTM_INT_K_RECURRENT);
-    if ((plan[0].solo ? launch_solo(s, pair) : launch_rec16_pair(s, pair, m[0]->cooperative != 0)) != hipSuccess)
+    const bool coop = m[0]->cooperative != 0;
+    if ((plan[0].solo ? launch_solo(s, pair) : plan[0].quad ? launch_quad(s, pair, coop) : launch_rec16_pair(s, pair, coop)) != hipSuccess)
       return LSTM_INT_E_DEVICE;
   }
   for (int i = 0; i < 2; ++i) {

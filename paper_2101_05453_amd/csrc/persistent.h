@@ -206,6 +206,14 @@ size_t solo_lds_bytes(const RecArgs &a);
 hipError_t launch_solo(hipStream_t s, const RecArgs2 &a);
 hipError_t solo_init();
 
+constexpr int kQuadWgWords = 64 + 64 + 2 * 16;  // exchange words of a workgroup per slot: h, m, two rounds of statistics
+// The same step on groups of four batch rows for larger layers and small batches (quad_kernel.inc.h).  Takes RecArgs2
+// always; rows_pg = 4, groups = ceil(B / 4), ldy set; `share` launches' worth of groups must fit one (2 for a pair).
+bool quad_supported(int N, int H, int flags, int B, int share, int *groups);
+size_t quad_lds_bytes(const RecArgs &a);
+hipError_t launch_quad(hipStream_t s, const RecArgs2 &a, bool cooperative);
+hipError_t quad_init();
+
 // ---------------------------------------------------------------------------
 // Stacked layers in one launch (stack_kernel.inc.h): layer l of a stack of up to 8 equal layers runs on
 // XCD l, all at once, each on its own step -- while layer l works on step t, layer l + 1 works on step
