@@ -455,7 +455,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         for (int g = 0; g < 4; ++g) {
           if (g < g_first) continue;
           int32_t v = tx[g] + rescale_sat16_pre<decltype(pre_tag)::value>(acc[g][0], ps[g]);
-          if (ph && g < 2) v += rescale_sat16_pre(Pq[g < 3 ? g : 0] * creg, pc[g < 3 ? g : 0]);
+          if (ph && g < 2) v += rescale_sat16_pre(mul_i24(Pq[g < 3 ? g : 0], creg), pc[g < 3 ? g : 0]);
           if (!(ph && g == 3)) v = clamp_i32(v, glo, 32767);
           gs[g] = v;
         }
@@ -490,7 +490,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       creg = cell_update32(ig, mirror_tanh(x[1], tv[1]), fg, creg, m_c);
     }
     if (ph) {  // finish the o gate sum with P_o . c^t (eq. 5)
-      gs[3] = clamp_i32(gs[3] + rescale_sat16_pre(Pq[2] * creg, pc[2]), glo, 32767);
+      gs[3] = clamp_i32(gs[3] + rescale_sat16_pre(mul_i24(Pq[2], creg), pc[2]), glo, 32767);
       if (ln) {
         add_stats(3, gs[3]);
         if (!collect_stats(1, 3, 3, t)) return;
@@ -503,7 +503,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       if (ph && ln) normalize(std::integral_constant<int, 1>{}, gates, x + 1);
       lookup(std::integral_constant<int, ph ? 2 : 1>{}, x, tb, tv);
       const int32_t o = ph ? mirror_sigmoid(x[1], tv[1]) : xo;
-      int32_t om = o * mirror_tanh(x[0], tv[0]);
+      int32_t om = mul_i24(o, mirror_tanh(x[0], tv[0]));
       if (pre_m) om = rescale_preshift(om, pm);
       const int32_t mq = sat8(rescale_sat16_pre<0>(om, pm) + zp_m);
       publish((proj ? xm : xh) + (size_t)(t & 1) * slot_words + q * m_row_words + member * 16 + wave * 4 + (c16 >> 2), mq, tag);

@@ -336,7 +336,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
           const int32_t w = txw[idx >> 1];
           const int32_t tx = (idx & 1) ? (w >> 16) : (int32_t)(int16_t)(w & 0xFFFF);
           int32_t v = tx + th;
-          if (ph && g < 2) v += rescale_sat16_pre((int32_t)PqL[g * 64 + cellw + c] * creg[c], prm->c[g]);
+          if (ph && g < 2) v += rescale_sat16_pre(mul_i24(PqL[g * 64 + cellw + c], creg[c]), prm->c[g]);
           if (!(ph && g == 3)) v = clamp_i32(v, glo, 32767);
           gs[g][c] = v;
           s1 += v;
@@ -547,7 +547,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         creg[c] = cell_update32(ig, zg, fg, creg[c], m_c);
         cx[0][c] = creg[c];
         if (ph) {  // finish the o gate sum with P_o . c^t (eq. 5)
-          int32_t v = gs[3][c] + rescale_sat16_pre((int32_t)PqL[2 * 64 + cellw + c] * creg[c], prm->c[2]);
+          int32_t v = gs[3][c] + rescale_sat16_pre(mul_i24(PqL[2 * 64 + cellw + c], creg[c]), prm->c[2]);
           v = clamp_i32(v, glo, 32767);
           gs[3][c] = v;
           s1 += v;
@@ -587,7 +587,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       uint32_t pk = 0;
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        int32_t om = xo[c] * mirror_tanh(cx[0][c], tcv[0][c]);
+        int32_t om = mul_i24(xo[c], mirror_tanh(cx[0][c], tcv[0][c]));
         if (pre_m) om = rescale_preshift(om, pm);
         const int32_t mq = sat8(rescale_sat16_pre<0>(om, pm) + zp_m);
         pk |= (uint32_t)(mq & 0xFF) << (8 * c);

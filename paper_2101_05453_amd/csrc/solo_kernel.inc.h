@@ -308,7 +308,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
           for (int g = 0; g < 4; ++g) {
             if (g < g_first) continue;
             int32_t v = txq[0][u][g] + rescale_sat16_pre<decltype(pre_tag)::value>(acc[g][0], ps[g]);
-            if (ph && g < 2) v += rescale_sat16_pre(Pq[u][g < 3 ? g : 0] * creg[u], pc[g < 3 ? g : 0]);
+            if (ph && g < 2) v += rescale_sat16_pre(mul_i24(Pq[u][g < 3 ? g : 0], creg[u]), pc[g < 3 ? g : 0]);
             if (!(ph && g == 3)) v = clamp_i32(v, glo, 32767);
             gs[u][g] = v;
           }
@@ -356,7 +356,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
       xo[u] = ph ? 0 : mirror_sigmoid(x[2], tv[2]);
       creg[u] = cell_update32(ig, mirror_tanh(x[1], tv[1]), fg, creg[u], m_c);
       if (ph) {  // finish the o gate sum with P_o . c^t (eq. 5)
-        gs[u][3] = clamp_i32(gs[u][3] + rescale_sat16_pre(Pq[u][2] * creg[u], pc[2]), glo, 32767);
+        gs[u][3] = clamp_i32(gs[u][3] + rescale_sat16_pre(mul_i24(Pq[u][2], creg[u]), pc[2]), glo, 32767);
         if (ln) add_stats(3, gs[u][3]);
       }
     }
@@ -371,7 +371,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
       if (ph && ln) normalize(std::integral_constant<int, 1>{}, u, gates, x + 1);
       lookup(std::integral_constant<int, ph ? 2 : 1>{}, x, tb, tv);
       const int32_t o = ph ? mirror_sigmoid(x[1], tv[1]) : xo[u];
-      int32_t om = o * mirror_tanh(x[0], tv[0]);
+      int32_t om = mul_i24(o, mirror_tanh(x[0], tv[0]));
       if (pre_m) om = rescale_preshift(om, pm);
       const int8_t mq = (int8_t)sat8(rescale_sat16_pre<0>(om, pm) + zp_m);
       if (proj) {

@@ -509,7 +509,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             int32_t v = tx + th;
             if (ph && g < 2) {
               const int cl = cell_w + tl * 8 + c;
-              v += rescale_sat16_pre((int32_t)PqL[g * 64 + cl] * creg[tl][c], prm->c[g]);
+              v += rescale_sat16_pre(mul_i24(PqL[g * 64 + cl], creg[tl][c]), prm->c[g]);
             }
             if (!(ph && g == 3)) v = clamp_i32(v, glo, 32767);
             acc[tl][idx] = v;
@@ -757,7 +757,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
           creg[tl][c] = cnew;
           if (ph) {  // finish the o gate sum with P_o . c^t (eq. 5)
             const int cl = cell_w + tl * 8 + c;
-            int32_t v = acc[tl][12 + c] + rescale_sat16_pre((int32_t)PqL[2 * 64 + cl] * cnew, prm->c[2]);
+            int32_t v = acc[tl][12 + c] + rescale_sat16_pre(mul_i24(PqL[2 * 64 + cl], cnew), prm->c[2]);
             v = clamp_i32(v, glo, 32767);
             acc[tl][12 + c] = v;
             s1 += v;
@@ -824,7 +824,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       uint32_t pk = 0;
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        int32_t om = xo[tl][c] * tc[tl][c];
+        int32_t om = mul_i24(xo[tl][c], tc[tl][c]);
         if (pre_m) om = rescale_preshift(om, pm);
         const int32_t mq = sat8(rescale_sat16_pre<0>(om, pm) + zp_m);
         pk |= (uint32_t)(mq & 0xFF) << (8 * c);
