@@ -117,11 +117,12 @@ size_t gru_int_workspace_bytes(const gru_int_model *model, int32_t T, int32_t B)
  *   trace    NULL, or dumps of one layer
  * Per layer: W x + bx over all T*B rows as one int8 MFMA matmul, then R h8 + bh
  * of the three gates fused with the whole elementwise cell -- as ONE persistent
- * launch for all T steps where the layer fits (N <= 1024, batches of up to
- * 256 * (32 / ceil(N / 32)) rows, no trace of that layer: the recurrent weights
- * stay in registers and the workgroups that share 32 batch rows meet at one
- * barrier per step inside one XCD), else as one launch per step.  Allocates
- * nothing, never synchronizes the host, launches kernels only.
+ * launch for all T steps where the layer fits (N <= 2048, no trace of that
+ * layer: the recurrent weights stay in registers, and the workgroups that share
+ * 4, 16 or 32 batch rows exchange the int8 state once per step inside one XCD;
+ * batches of more than 256 * (32 / ceil(N / 64)) rows take several launches),
+ * else as one launch per step.  Allocates nothing, never synchronizes the host,
+ * launches kernels only.
  * The persistent launch needs all its workgroups on the device at once (one
  * per compute unit): nothing else may occupy the device for long while it
  * runs; if that does not hold its bounded waits give up, the call's outputs
@@ -135,8 +136,8 @@ int gru_int_forward(const gru_int_model *model, const int8_t *x, int32_t T, int3
 /*
  * Options: "persistent" 1 (default) / 0 = never the one-launch form;
  * "spin_limit" = polls after which a wait inside the persistent kernel gives
- * up; "sync_sleep" = pause before the first poll of a barrier, in units of 64
- * clocks; "barrier_never_completes" 1 = test hook: every barrier waits for an
+ * up; "sync_sleep" = pause before the first poll of the flags (groups of 16 and
+ * 32 rows), in units of 64 clocks; "barrier_never_completes" 1 = test hook: every barrier waits for an
  * arrival that never comes (keep spin_limit small); "reset_status" clears the
  * status word (synchronizes the device).  Results never depend on the tuning
  * options.  Unknown keys or values give LSTM_INT_E_INVALID_ARG.

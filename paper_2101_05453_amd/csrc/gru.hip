@@ -15,11 +15,11 @@
 //      (rescale, sigma/tanh tables, reset product, coupled update, the int8
 //      form of the new state) follows in the same kernel with one LDS
 //      reduction and no exchange between workgroups.
-//   3. where the layer fits (up to 1024 cells), steps 2 of all T steps as ONE
-//      persistent launch, gru_seq_kernel: weights in registers, one barrier
-//      per step among the workgroups of an XCD that share 32 batch rows; the
-//      input term then comes from the LSTM path's register-resident input GEMM
-//      (in_gemm.hip) in its tile order.
+//   3. where the layer fits (up to 2048 cells), steps 2 of all T steps as ONE
+//      persistent launch instead (gru_seq.hip): weights in registers, one
+//      exchange per step inside an XCD; the input term then comes from the LSTM
+//      path's register-resident input GEMM (in_gemm.hip) in its tile order
+//      where its depth allows.
 // The state is read and written in place (each (row, cell) belongs to one
 // thread); its int8 form is written three times: in operand order for the
 // next step, row-major for the next layer's matmul, dense for the caller.
@@ -32,6 +32,7 @@
 #include <vector>
 
 #include "../../include/gru_int.h"
+#include "gru_seq.h"
 #include "kernels.h"
 #include "lstm_int_math.h"
 #include "model.h"
@@ -55,19 +56,23 @@ struct GruLayerHost {
 
 // padded extents of one layer on the device
 struct GruDims {
-  int Ip, Kp, Ncp, cols_pad;  // input depth / state depth (multiples of 64), cells (multiple of 32), 3N to 128
+  int Ip, Kp, Ncp;   // input depth / state depth (multiples of 64), cells (multiple of 32)
+  int Nt, cols_pad;  // columns of a gate in the row-major input terms (multiple of 8: 16-byte pieces), 3 Nt to 128
 };
 GruDims gru_dims(int I, int N) {
-  return GruDims{(I + 63) / 64 * 64, (N + 63) / 64 * 64, (N + 31) / 32 * 32, (3 * N + 127) / 128 * 128};
+  const int Nt = (N + 7) / 8 * 8;
+  return GruDims{(I + 63) / 64 * 64, (N + 63) / 64 * 64, (N + 31) / 32 * 32, Nt, (3 * Nt + 127) / 128 * 128};
 }
 // bytes of the operand-ordered copy of the int8 state for B rows: whole blocks of 32 rows, an even number of them
 size_t hop_bytes(int B, int Kp) { return (size_t)((B + 63) / 64 * 2) * (Kp / 32) * 1024; }
 
 struct GruLayerDev {
-  const int8_t *W = nullptr;      // [cols_pad][Ip] gate-major rows, zero beyond the real extents
+  const int8_t *W = nullptr;      // [cols_pad][Ip] gate-major rows, Nt per gate, zero beyond the real extents
   const int32_t *bx = nullptr;    // [cols_pad] folded input bias
   const int8_t *Rop = nullptr;    // [Ncp/32][3][Kp/32][64 lanes][16 B]: operand order of the 32x32x32 MFMA
   const int32_t *bh = nullptr;    // [3][Ncp]
+  const int8_t *R16 = nullptr;    // up to 2048 cells: R for the persistent kernels (GruSeqArgs)
+  const int32_t *bh64 = nullptr;  // [3][cells to 64]
   // input depth up to 1024: W once more as the register-resident input GEMM reads it (in_gemm.hip): tiles of 8 cells
   // x 4 gate slots (slot 0 empty, slots 1-3 = r, u, n), row 8 slot + cell % 8, [tile][Ip/32][64 lanes][16 B]
   const int8_t *W2f = nullptr;
@@ -175,11 +180,9 @@ __host__ __device__ __forceinline__ size_t hop_offset(int row, int k, int KS32) 
 }
 
 // Start of a layer: the working state (caller's h_state slice or zeros) is used in place; its int8 form
-// goes to the operand-ordered buffer hop0 (columns N..Kp-1 zero); sync_vec 16-byte words at sync are cleared.
-__global__ void gru_init_kernel(int16_t *h16, int B, int N, int Kp, int8_t *hop0, int zero_state, int4 *sync,
-                                int sync_vec) {
+// goes to the operand-ordered buffer hop0 (columns N..Kp-1 zero).
+__global__ void gru_init_kernel(int16_t *h16, int B, int N, int Kp, int8_t *hop0, int zero_state) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < sync_vec) sync[i] = int4{0, 0, 0, 0};  // counters and placement words of the persistent kernel
   if (i >= (int64_t)B * Kp) return;
   const int b = (int)(i / Kp), k = (int)(i - (int64_t)b * Kp);
   int32_t v = 0;
@@ -198,7 +201,8 @@ struct GruStepArgs {
   const int8_t *hop_prev;     // state before the step, operand order
   const int8_t *Rop;          // [ctiles][3][KS32][64 lanes][16 B]
   const int32_t *bh;          // [3][32 ctiles]
-  const int16_t *tx;          // [B][3N] of this step, or NULL:
+  const int16_t *tx;          // [B][3 Nt] of this step, or NULL:
+  int32_t Nt;
   const int4 *tx2;            // this step's input terms in the input GEMM's tile order [row block][tile of 8 cells][half][lane][8]
   int32_t tiles;              // tiles of 8 cells per row block of tx2
   int16_t *h16;               // [B][N] in/out
@@ -222,7 +226,6 @@ struct GruStepArgs {
 // of R at every step of a sequence and keeps it in its L2 (N = 2048: 1.5 MB of 4 MB).  The mapping only places
 // the work; results do not depend on where a workgroup runs.
 constexpr int kPartTile = 32 * 33;  // one 32 x 32 tile of partial sums in LDS, row stride 33
-constexpr int kSeqSigBytes = 65552;  // the sigma table of the persistent kernel in LDS: 32769 entries, to 16 bytes
 
 template <int RB>
 __global__ __launch_bounds__(256) void gru_step_kernel(GruStepArgs a) {
@@ -240,7 +243,7 @@ __global__ __launch_bounds__(256) void gru_step_kernel(GruStepArgs a) {
   const int rsub = threadIdx.x >> 3, cg = threadIdx.x & 7;
   const int N = a.N;
   const int n0 = ct * 32 + 4 * cg;
-  const bool vec = (N & 3) == 0;  // runs of four cells are aligned 8-byte pieces of tx and h16
+  const bool vec = (N & 3) == 0;  // runs of four cells are aligned 8-byte pieces of h16
   int rowe[RB];
   int32_t txe[RB][3][4], h16e[RB][4];
 #pragma unroll
@@ -266,18 +269,11 @@ __global__ __launch_bounds__(256) void gru_step_kernel(GruStepArgs a) {
         txe[rb][g][0] = t4.x; txe[rb][g][1] = t4.y; txe[rb][g][2] = t4.z; txe[rb][g][3] = t4.w;
       }
     } else {
-      const int16_t *txp = a.tx + (size_t)row * 3 * N + n0;
-      if (vec && n0 < N) {
+      const int16_t *txp = a.tx + (size_t)row * 3 * a.Nt + n0;
 #pragma unroll
-        for (int g = 0; g < 3; ++g) {
-          const short4 t4 = *reinterpret_cast<const short4 *>(txp + (size_t)g * N);
-          txe[rb][g][0] = t4.x; txe[rb][g][1] = t4.y; txe[rb][g][2] = t4.z; txe[rb][g][3] = t4.w;
-        }
-      } else {
-#pragma unroll
-        for (int g = 0; g < 3; ++g)
-#pragma unroll
-          for (int c = 0; c < 4; ++c) txe[rb][g][c] = n0 + c < N ? txp[(size_t)g * N + c] : 0;
+      for (int g = 0; g < 3; ++g) {
+        const short4 t4 = n0 < a.Nt ? *reinterpret_cast<const short4 *>(txp + (size_t)g * a.Nt) : short4{0, 0, 0, 0};
+        txe[rb][g][0] = t4.x; txe[rb][g][1] = t4.y; txe[rb][g][2] = t4.z; txe[rb][g][3] = t4.w;
       }
     }
   }
@@ -356,7 +352,7 @@ __global__ __launch_bounds__(256) void gru_step_kernel(GruStepArgs a) {
       }
       const int32_t r = sigmoid_from_table(a.sig_tab, sat16(txe[rb][0][c] + th[0]));  // Sec. 3.2.1
       const int32_t u = sigmoid_from_table(a.sig_tab, sat16(txe[rb][1][c] + th[1]));
-      const int32_t rn = (r * th[2] + 16384) >> 15;  // Q0.15 x Q3.12 -> Q3.12; |r th| < 2^30
+      const int32_t rn = (mul_i24(r, th[2]) + 16384) >> 15;  // Q0.15 x Q3.12 -> Q3.12; |r th| < 2^30
       const int32_t cand = tanh_from_table(a.tanh_tab, sat16(txe[rb][2][c] + rn));
       const int32_t ubar = cifg_input_gate(u);  // 1 - u, Sec. 3.2.9
       const int32_t hn = cell_update32(ubar, cand, u, h16e[rb][c], 0);  // Sec. 3.2.7, both products Q0.30 -> Q0.15
@@ -402,237 +398,6 @@ __global__ __launch_bounds__(256) void gru_step_kernel(GruStepArgs a) {
   }
 }
 
-// ---------------------------------------------------------------------------
-// Persistent form of the step kernel: one launch runs all T steps of a layer.
-// ---------------------------------------------------------------------------
-// Wait of one workgroup for the other members of its group (the workgroups that share 32 batch rows), at the end of
-// every step: every wave first waits for its own stores, thread 0 adds one to the group's counter and polls it
-// (relaxed agent-scope atomics; the members of a group run on one XCD and meet in its L2).  Gives up after
-// spin_limit polls or when another workgroup has: the status word becomes 1 and every workgroup leaves the kernel.
-__device__ __forceinline__ bool gru_group_sync(unsigned *counter, unsigned &epoch, int GS, int *status, int spin_limit,
-                                               int first_sleep, int *lds_flag) {
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  if (GS == 1) return true;
-  epoch += (unsigned)GS;
-  if (threadIdx.x == 0) {
-    __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    for (int i = 0; i < first_sleep; ++i) __builtin_amdgcn_s_sleep(1);  // a poll before the arrivals have landed only delays them
-    int budget = spin_limit;
-    for (;;) {
-      const unsigned c = __hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if ((int)(c - epoch) >= 0) break;
-      --budget;
-      if ((budget & 15) == 0 &&
-          (budget <= 0 || __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
-        __hip_atomic_store(status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        lds_flag[0] = 0;
-        break;
-      }
-    }
-  }
-  __syncthreads();
-  return lds_flag[0] != 0;
-}
-
-struct GruSeqArgs {
-  int32_t B, N, Kp, KS32, T;
-  int32_t GS, groups;         // workgroups per group (= tiles of 32 cells); groups of 32 batch rows
-  const int8_t *hop0;         // state before step 0, operand order
-  int8_t *hop_seq;            // [T][row blocks][KS32][64 lanes][16 B]: the state after every step, operand order; the
-                              // exchange buffer of the launch, every line written once and never read before that
-  size_t hop_step;            // bytes of one step of hop_seq
-  const int8_t *Rop;          // [GS][3][KS32][64 lanes][16 B]
-  const int32_t *bh;          // [3][32 GS]
-  const int16_t *tx;          // [T][B][3N], or NULL:
-  const int4 *tx2;            // the input term in the input GEMM's tile order [(t Bp + b) / 32][tile of 8 cells][half][lane][8]
-  int32_t tiles, bp_blocks;   // of tx2: tiles of 8 cells per row block; row blocks per step (Bp / 32)
-  int16_t *h16;               // [B][N]: read before step 0, written after step T - 1
-  int8_t *h8_seq;             // [T][B][Kp] row-major
-  int8_t *y;                  // [T][B][N] or NULL
-  int32_t Mh[3], rh[3];
-  const uint16_t *sig_tab, *tanh_tab;
-  unsigned *counters;         // [groups][64], zero at launch
-  unsigned long long *tickets;  // [8][32], zero at launch: placement check
-  int *status;
-  int32_t spin_limit, sync_sleep;
-  int32_t extra_arrivals;     // test hook: every barrier waits for this many arrivals more than will come
-};
-
-constexpr int kSeqMaxPer = 8;  // k steps per wave: depth up to 4 x 8 x 32 = 1024
-
-// The step kernel's work with the weights kept in registers over the whole sequence: the workgroups that share 32
-// batch rows -- one per tile of 32 cells -- form a group on ONE XCD; each keeps its 96 x Kp bytes of R as MFMA
-// operands (wave w the k steps of its quarter of the depth: at most 96 registers), its threads' share of the state in
-// registers, and per step loads only the int8 state of the group (operand order, one KB per k step, the KB of k step j
-// written by member j), runs the matmul and the cell as gru_step_kernel does, publishes its 32 cells of the new state
-// and meets the group at one barrier.  A GRU step needs this one exchange (the LSTM with layer norm and projection
-// needs three).  Placement: the XCD is read from the XCC_ID register and the place there is w / 8 (the hardware deals
-// consecutive workgroups out to the XCDs in turn); every workgroup records its place when it is done and a place taken
-// twice or not at all raises the status word (2), as in the LSTM's recurrent kernel.  All workgroups must be resident
-// at once (one per compute unit, launched on an otherwise idle stream); if they are not, the bounded waits end the
-// kernel with status 1.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gru_seq_kernel(GruSeqArgs a) {
-  __shared__ __attribute__((aligned(16))) int32_t part[4 * 3 * kPartTile];
-  __shared__ int flag[4];
-  // the sigma table (Q3.12, all 32769 entries) in LDS: the reset gate's lookup is the first of two dependent ones on
-  // the chain from the matmul to the new state, and from LDS it no longer costs a round trip to the L2
-  extern __shared__ __attribute__((aligned(16))) uint16_t sig_lds[];  // kSeqSigBytes, set at launch
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int col = lane & 31, b2 = lane >> 5;
-  const int wg = blockIdx.x;
-  const int xcc = (int)(__builtin_amdgcn_s_getreg(20 | (0 << 6) | (3 << 11)) & 7);  // XCC_ID, bits 3:0
-  const int slot = wg >> 3, GS = a.GS;
-  auto placement_check = [&]() {
-    if (tid == 0) {
-      const unsigned places = gridDim.x >> 3;  // at most 32
-      const unsigned long long mine = (1ull << 32) + (1ull << (wg >> 3));
-      const unsigned long long now =
-          __hip_atomic_fetch_add(&a.tickets[xcc * 32], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + mine;
-      const unsigned count = (unsigned)(now >> 32);
-      const unsigned all = places >= 32 ? 0xFFFFFFFFu : (1u << places) - 1;
-      if (count > places || (count == places && (unsigned)now != all))
-        __hip_atomic_store(a.status, 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-  };
-  const int group = xcc + 8 * (slot / GS), ct = slot % GS;
-  if (group >= a.groups) {  // no rows for this workgroup
-    placement_check();
-    return;
-  }
-  const int KS = a.KS32;
-  const int per = (KS + 3) >> 2;
-  const int k0 = wave * per, k1 = k0 + per < KS ? k0 + per : KS;
-
-  // ---- once: the wave's share of the weights -> registers (k steps past its share hold zeros)
-  v4i Wr[3][kSeqMaxPer];
-  {
-    const v4i *wp = reinterpret_cast<const v4i *>(a.Rop) + (size_t)ct * 3 * KS * 64 + lane;
-#pragma unroll
-    for (int g = 0; g < 3; ++g)
-#pragma unroll
-      for (int u = 0; u < kSeqMaxPer; ++u) {
-        Wr[g][u] = k0 + u < k1 ? wp[((size_t)g * KS + k0 + u) * 64] : v4i{0, 0, 0, 0};
-      }
-  }
-  // this thread's share of the cell: row rsub of the group, cells 4 cg .. 4 cg + 3 of the tile
-  const int rsub = tid >> 3, cg = tid & 7;
-  const int N = a.N;
-  const int n0 = ct * 32 + 4 * cg;
-  const int row = group * 32 + rsub;
-  const bool row_ok = row < a.B;
-  const int rowc = row_ok ? row : a.B - 1;
-  const bool vec = (N & 3) == 0;
-  int32_t bhe[3][4], h16r[4];
-#pragma unroll
-  for (int g = 0; g < 3; ++g) {
-    const int4 b4 = *reinterpret_cast<const int4 *>(a.bh + g * 32 * GS + n0);
-    bhe[g][0] = b4.x; bhe[g][1] = b4.y; bhe[g][2] = b4.z; bhe[g][3] = b4.w;
-  }
-#pragma unroll
-  for (int c = 0; c < 4; ++c) h16r[c] = n0 + c < N ? a.h16[(size_t)rowc * N + n0 + c] : 0;
-  {
-    const int4 *src = reinterpret_cast<const int4 *>(a.sig_tab);  // readable to a multiple of 16 bytes: the arena goes on
-    int4 *dst = reinterpret_cast<int4 *>(sig_lds);
-    for (int i = tid; i < kSeqSigBytes / 16; i += 256) dst[i] = src[i];
-  }
-  if (tid == 0) flag[0] = 1;
-  __syncthreads();
-
-  unsigned epoch = 0;
-  unsigned *counter = a.counters + group * 64;
-  const size_t hop_blk = (size_t)group * KS * 64;  // this group's row block, in 16-byte units
-  for (int t = 0; t < a.T; ++t) {
-    // W x terms of this thread's cells: from memory, not needed before the matmul is done
-    int32_t txe[3][4];
-    if (a.tx2) {
-      // tile order: lane (row % 32, half b2) of tile n / 8 holds value 4 slot + c for cell 8 (n / 8) + 4 b2 + c, values
-      // 0-7 in the first 16 bytes of the lane, 8-15 in the second
-      const int4 *tp = a.tx2 + (((size_t)t * a.bp_blocks + group) * a.tiles + (ct * 4 + (cg >> 1))) * 128 + ((cg & 1) << 5) + rsub;
-#pragma unroll
-      for (int g = 0; g < 3; ++g) {
-        const int slot = g + 1;
-        const short4 t4 = *reinterpret_cast<const short4 *>(reinterpret_cast<const int16_t *>(tp + (slot >> 1) * 64) + (slot & 1) * 4);
-        txe[g][0] = t4.x; txe[g][1] = t4.y; txe[g][2] = t4.z; txe[g][3] = t4.w;
-      }
-    } else {
-      const int16_t *txp = a.tx + ((size_t)t * a.B + rowc) * 3 * N + n0;
-      if (vec && n0 < N) {
-#pragma unroll
-        for (int g = 0; g < 3; ++g) {
-          const short4 t4 = *reinterpret_cast<const short4 *>(txp + (size_t)g * N);
-          txe[g][0] = t4.x; txe[g][1] = t4.y; txe[g][2] = t4.z; txe[g][3] = t4.w;
-        }
-      } else {
-#pragma unroll
-        for (int g = 0; g < 3; ++g)
-#pragma unroll
-          for (int c = 0; c < 4; ++c) txe[g][c] = n0 + c < N ? txp[(size_t)g * N + c] : 0;
-      }
-    }
-    // ---- R h8: the group's int8 state, the wave's k steps
-    const v4i *hp = reinterpret_cast<const v4i *>(t == 0 ? a.hop0 : a.hop_seq + (size_t)(t - 1) * a.hop_step) + hop_blk + lane;
-    v4i hf[kSeqMaxPer];
-#pragma unroll
-    for (int u = 0; u < kSeqMaxPer; ++u)  // k steps past the wave's share meet zero weights: re-read a step that exists
-      hf[u] = hp[(size_t)(k0 + u < k1 ? k0 + u : (k0 < KS ? k0 : 0)) * 64];
-    v16i acc[3];
-#pragma unroll
-    for (int g = 0; g < 3; ++g)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[g][v] = 0;
-#pragma unroll
-    for (int u = 0; u < kSeqMaxPer; ++u)
-#pragma unroll
-      for (int g = 0; g < 3; ++g) acc[g] = __builtin_amdgcn_mfma_i32_32x32x32_i8(Wr[g][u], hf[u], acc[g], 0, 0, 0);
-#pragma unroll
-    for (int g = 0; g < 3; ++g)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) part[(wave * 3 + g) * kPartTile + (2 * v + b2) * 33 + col] = acc[g][v];
-    __syncthreads();
-
-    // ---- the cell (as in gru_step_kernel), state in registers
-    int32_t h84[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      int32_t th[3];
-#pragma unroll
-      for (int g = 0; g < 3; ++g) {
-        const int o = g * kPartTile + (2 * (4 * (cg >> 1) + c) + (cg & 1)) * 33 + rsub;
-        const int32_t sum = part[o] + part[o + 3 * kPartTile] + part[o + 6 * kPartTile] + part[o + 9 * kPartTile];
-        th[g] = sat16(rescale(sum + bhe[g][c], a.Mh[g], a.rh[g]));
-      }
-      const int32_t r = sigmoid_from_table(sig_lds, sat16(txe[0][c] + th[0]));
-      const int32_t u = sigmoid_from_table(sig_lds, sat16(txe[1][c] + th[1]));
-      const int32_t rn = (r * th[2] + 16384) >> 15;
-      const int32_t cand = tanh_from_table(a.tanh_tab, sat16(txe[2][c] + rn));
-      const int32_t hn = cell_update32(cifg_input_gate(u), cand, u, h16r[c], 0);
-      h16r[c] = n0 + c < N ? hn : 0;
-      h84[c] = n0 + c < N ? state_i8(hn) : 0;
-    }
-    if (row_ok && n0 < N) {
-      const uint32_t pk = (uint32_t)(h84[0] & 0xFF) | ((uint32_t)(h84[1] & 0xFF) << 8) | ((uint32_t)(h84[2] & 0xFF) << 16) |
-                          ((uint32_t)(h84[3] & 0xFF) << 24);
-      *reinterpret_cast<uint32_t *>(a.hop_seq + (size_t)t * a.hop_step + hop_offset(row, n0, KS)) = pk;
-      *reinterpret_cast<uint32_t *>(a.h8_seq + ((size_t)t * a.B + row) * a.Kp + n0) = pk;
-      if (a.y) {
-        int8_t *yd = a.y + ((size_t)t * a.B + row) * N + n0;
-        if (vec && !(reinterpret_cast<uintptr_t>(a.y) & 3))
-          *reinterpret_cast<uint32_t *>(yd) = pk;
-        else
-          for (int c = 0; c < 4 && n0 + c < N; ++c) yd[c] = (int8_t)h84[c];
-      }
-    }
-    // rows of the block past the batch are never written: their (garbage) state only ever feeds their own results
-    if (!gru_group_sync(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, a.sync_sleep, flag)) return;
-  }
-  if (row_ok)
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-      if (n0 + c < N) a.h16[(size_t)row * N + n0 + c] = (int16_t)h16r[c];
-  placement_check();
-}
-
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 }  // namespace
@@ -650,22 +415,21 @@ struct gru_int_model {
   int device = -1;
   bool profiling = false;
   std::vector<GruTimed> timed;
-  int persistent = 1;   // layers that fit run all their steps in one launch of gru_seq_kernel
-  int spin_limit = 1 << 21, sync_sleep = 12;
+  int persistent = 1;   // layers that fit run all their steps in one launch (gru_seq.hip)
+  int spin_limit = 1 << 21, sync_sleep = 8;
   int extra_arrivals = 0;  // test hook (option "barrier_never_completes")
-  int *status = nullptr;  // device word: nonzero once a wait inside gru_seq_kernel gave up (1) or placement failed (2)
+  int *status = nullptr;  // device word: nonzero once a wait inside a persistent kernel gave up (1) or placement failed (2)
   int num_cus = 0;
   std::vector<GruLayerHost> host;
   std::vector<GruLayerDev> dev;
   uint8_t *arena = nullptr;
   const uint16_t *sig_tab = nullptr, *tanh_tab = nullptr;
+  LutWide lut[2] = {};     // the same two as the persistent kernels keep them (dom = 0: they do not compress, and none runs)
 };
 
 namespace {
 
 // carve-up of the workspace for (T, B)
-constexpr size_t kGruSyncBytes = 256 * 64 * 4;  // group counters [256][64 words]; the placement words lie inside
-
 struct GruWs {
   size_t xpad, tx, out[2], hop[2], h16, sync, hop_seq, total;
 };
@@ -674,7 +438,7 @@ GruWs gru_workspace(const gru_int_model *m, int64_t T, int64_t B) {
   size_t off = 0, max_tx = 0, max_out = 0, max_hop = 0, sum_h16 = 0;
   for (const GruLayerHost &q : m->host) {
     const GruDims d = gru_dims(q.I, q.N);
-    max_tx = std::max(max_tx, (size_t)T * B * 3 * q.N * 2);
+    max_tx = std::max(max_tx, (size_t)T * B * 3 * d.Nt * 2);
     // the same terms in the register-resident input GEMM's tile order: rows padded to 32 per step, cells to 64, 4 gate slots
     max_tx = std::max(max_tx, (size_t)T * ((B + 31) / 32 * 32) * ((q.N + 63) / 64 * 64) * 4 * 2);
     max_out = std::max(max_out, ((size_t)T * B + 32) * d.Kp);  // 32 rows of slack: that GEMM reads whole blocks of 32 rows
@@ -690,7 +454,7 @@ GruWs gru_workspace(const gru_int_model *m, int64_t T, int64_t B) {
   w.hop[1] = off; off += align256(max_hop);
   w.h16 = off; off += align256(sum_h16);
   w.sync = off; off += kGruSyncBytes;
-  w.hop_seq = off; off += align256(max_hop * (size_t)T);  // the persistent kernel's exchange buffer: one copy per step
+  w.hop_seq = off; off += align256(max_hop * (size_t)T);  // the persistent kernels' exchange buffer: one copy per step
   w.total = off;
   return w;
 }
@@ -731,9 +495,20 @@ int gru_int_prepare(const gru_int_layer_params *layers, int32_t num_layers, int3
       return off;
     };
     const size_t o_sig = reserve(kTab * 2), o_tanh = reserve(kTab * 2), o_status = reserve(256);
+    const size_t o_wide[2] = {reserve(kLutWideBytes), reserve(kLutWideBytes)};
     fill_sigmoid_table(3, reinterpret_cast<uint16_t *>(img.data() + o_sig));
     fill_tanh_table(3, reinterpret_cast<uint16_t *>(img.data() + o_tanh));
-    struct Off { size_t W, bx, R, bh, W2f, bx2; int tiles; };
+    LutWide lut[2] = {};
+    for (int i = 0; i < 2; ++i) {
+      int has_tail = 0, flat_from = 0;
+      const int sh = compress_table_wide(reinterpret_cast<const uint16_t *>(img.data() + (i ? o_tanh : o_sig)),
+                                         img.data() + o_wide[i], &has_tail, &flat_from);
+      if (sh < 0 || (!has_tail && flat_from + 1 > 32768)) continue;
+      lut[i].sh = sh;
+      lut[i].tail = has_tail;
+      lut[i].dom = has_tail ? 16384 : (flat_from + 1 + 1023) / 1024 * 1024;
+    }
+    struct Off { size_t W, bx, R, bh, W2f, bx2, R16, bh64; int tiles; };
     std::vector<Off> offs(num_layers);
     for (int l = 0; l < num_layers; ++l) {
       const GruLayerHost &q = m->host[l];
@@ -760,8 +535,11 @@ int gru_int_prepare(const gru_int_layer_params *layers, int32_t num_layers, int3
             reinterpret_cast<int32_t *>(img.data() + o.bx2)[tile * 32 + rho] = q.bx_fold[g * N + n];
           }
       }
-      for (int r = 0; r < 3 * N; ++r) std::memcpy(img.data() + o.W + (size_t)r * d.Ip, q.Wq.data() + (size_t)r * I, I);
-      std::memcpy(img.data() + o.bx, q.bx_fold.data(), (size_t)3 * N * 4);
+      for (int g = 0; g < 3; ++g) {
+        for (int n = 0; n < N; ++n)
+          std::memcpy(img.data() + o.W + ((size_t)g * d.Nt + n) * d.Ip, q.Wq.data() + ((size_t)g * N + n) * I, I);
+        std::memcpy(img.data() + o.bx + (size_t)g * d.Nt * 4, q.bx_fold.data() + (size_t)g * N, (size_t)N * 4);
+      }
       // first operand of the 32x32x32 MFMA: lane (row = lane % 32, half = lane / 32) holds, for k step ks, bytes
       // 32 ks + 16 half .. + 15 of weight row 32 ct + row of gate g (zero beyond N in either direction)
       for (int ct = 0; ct < d.Ncp / 32; ++ct)
@@ -775,11 +553,25 @@ int gru_int_prepare(const gru_int_layer_params *layers, int32_t num_layers, int3
             }
       for (int g = 0; g < 3; ++g)
         std::memcpy(img.data() + o.bh + (size_t)g * d.Ncp * 4, q.bhq.data() + (size_t)g * N, (size_t)N * 4);
+      o.R16 = o.bh64 = 0;
+      if (int cap = 0; gru_seq_rows(N, 1, &cap)) {
+        const int K64 = d.Kp / 64;  // = tiles of 64 cells
+        o.R16 = reserve((size_t)3 * d.Kp * d.Kp);
+        o.bh64 = reserve((size_t)3 * d.Kp * 4);
+        uint8_t *dst = img.data() + o.R16;
+        for (int n16 = 0; n16 < K64 * 4; ++n16)
+          for (int g = 0; g < 3; ++g)
+            for (int ks = 0; ks < K64; ++ks)
+              for (int lane = 0; lane < 64; ++lane, dst += 16) {
+                const int n = n16 * 16 + (lane & 15), k0 = ks * 64 + (lane >> 4) * 16;
+                if (n < N && k0 < N) std::memcpy(dst, q.Rq.data() + ((size_t)g * N + n) * N + k0, std::min(16, N - k0));
+              }
+        for (int g = 0; g < 3; ++g)
+          std::memcpy(img.data() + o.bh64 + (size_t)g * d.Kp * 4, q.bhq.data() + (size_t)g * N, (size_t)N * 4);
+      }
       offs[l] = o;
     }
-    if (hipSetDevice(device) != hipSuccess || in_gemm_init() != hipSuccess || gemm_init() != hipSuccess ||
-        hipFuncSetAttribute(reinterpret_cast<const void *>(&gru_seq_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            kSeqSigBytes) != hipSuccess ||
+    if (hipSetDevice(device) != hipSuccess || in_gemm_init() != hipSuccess || gemm_init() != hipSuccess || gru_seq_init() != hipSuccess ||
         hipMalloc(reinterpret_cast<void **>(&m->arena), img.size()) != hipSuccess) {
       m->arena = nullptr;
       delete m;
@@ -797,12 +589,20 @@ int gru_int_prepare(const gru_int_layer_params *layers, int32_t num_layers, int3
     }
     m->sig_tab = reinterpret_cast<const uint16_t *>(m->arena + o_sig);
     m->tanh_tab = reinterpret_cast<const uint16_t *>(m->arena + o_tanh);
+    for (int i = 0; i < 2; ++i) {
+      m->lut[i] = lut[i];
+      m->lut[i].blob = m->arena + o_wide[i];
+    }
     m->dev.resize(num_layers);
     for (int l = 0; l < num_layers; ++l) {
       m->dev[l].W = reinterpret_cast<const int8_t *>(m->arena + offs[l].W);
       m->dev[l].bx = reinterpret_cast<const int32_t *>(m->arena + offs[l].bx);
       m->dev[l].Rop = reinterpret_cast<const int8_t *>(m->arena + offs[l].R);
       m->dev[l].bh = reinterpret_cast<const int32_t *>(m->arena + offs[l].bh);
+      if (offs[l].R16) {
+        m->dev[l].R16 = reinterpret_cast<const int8_t *>(m->arena + offs[l].R16);
+        m->dev[l].bh64 = reinterpret_cast<const int32_t *>(m->arena + offs[l].bh64);
+      }
       if (offs[l].tiles) {
         m->dev[l].W2f = reinterpret_cast<const int8_t *>(m->arena + offs[l].W2f);
         m->dev[l].bx2 = reinterpret_cast<const int32_t *>(m->arena + offs[l].bx2);
@@ -888,7 +688,7 @@ int gru_int_forward(const gru_int_model *m, const int8_t *x, int32_t T, int32_t 
     }
     rq.M[3] = rq.M[2];
     rq.r[3] = rq.r[2];
-    rq.cols_per_gate = N;
+    rq.cols_per_gate = d.Nt;
     rq.zp = 0;
     gru_int_model *mm = const_cast<gru_int_model *>(m);  // the profile is bookkeeping beside the model
     auto timed_begin = [&](int cls, int launches) {
@@ -901,12 +701,13 @@ int gru_int_forward(const gru_int_model *m, const int8_t *x, int32_t T, int32_t 
     auto timed_end = [&]() {
       if (m->profiling && !mm->timed.empty()) (void)hipEventRecord(mm->timed.back().stop, s);
     };
-    // One launch for all steps (gru_seq_kernel) where the layer fits: depth up to 1024 in registers, one workgroup
-    // per tile of 32 cells and group of 32 rows, a group inside one XCD of 32 compute units, all groups resident.
-    const int ctiles = d.Ncp / 32;
-    const int groups = (B + 31) / 32;
-    const bool seq = m->persistent && !tr && m->num_cus == 256 && d.Kp <= 128 * kSeqMaxPer && ctiles <= 32 &&
-                     groups <= 8 * (32 / ctiles) && T < (1 << 20);
+    // One launch for all steps where the layer fits (gru_seq.hip), several for batches that do not fit one
+    int rows_pg = 0, max_groups = 0;
+    if (m->persistent && !tr && m->num_cus == 256 && dv.R16 && m->lut[0].dom && m->lut[1].dom && T < (1 << 20))
+      rows_pg = gru_seq_rows(N, B, &max_groups);
+    for (int g = 0; g < 3; ++g)
+      if (31 - q.eh[g] < 3 || 31 - q.eh[g] > 62) rows_pg = 0;
+    const bool seq = rows_pg != 0;
     // The input term: from the LSTM path's input GEMM where the input depth allows (weights resident in registers, depth
     // up to 1024, output in its tile order, which both recurrent kernels read); else, and with a trace, from the
     // general matmul, row-major.
@@ -922,45 +723,60 @@ int gru_int_forward(const gru_int_model *m, const int8_t *x, int32_t T, int32_t 
     // (on the launch-per-step path only where the matmul is large: the tile-ordered terms cost the step kernel
     // 0.5 us per step, measured, which 8192 rows and more of a faster matmul pay for)
     const bool ws_gemm = !tr && dv.W2f && m->num_cus == 256 && (seq || TB >= 8192) && in_gemm_ws_supported(ga);
-    timed_begin(GRU_INT_K_INPUT_GEMM, 1);
-    if (ws_gemm)
-      launch_in_gemm_ws(s, ga, m->num_cus);
-    else
-      launch_gemm_i16(s, in, ld_in, (int)TB, dv.W, d.Ip, 3 * N, dv.bx, rq, tx, 3 * N);
-    timed_end();
-    {
-      const int64_t n = (int64_t)B * d.Kp;  // the state before step 0 goes where step "-1" would have put it
-      const int sync_vec = seq ? (int)(kGruSyncBytes / 16) : 0;
-      const int64_t work = std::max<int64_t>(n, sync_vec);
-      hipLaunchKernelGGL(gru_init_kernel, dim3((unsigned)((work + 255) / 256)), dim3(256), 0, s, h16, B, N, d.Kp, hop[1],
-                         h_state ? 0 : 1, reinterpret_cast<int4 *>(ws + w.sync), sync_vec);
-    }
+    GruSeqArgs sa{};
     if (seq) {
-      GruSeqArgs q2{};
-      q2.B = B; q2.N = N; q2.Kp = d.Kp; q2.KS32 = d.Kp / 32; q2.T = T;
-      q2.GS = ctiles; q2.groups = groups;
-      q2.hop0 = hop[1];
-      q2.hop_seq = reinterpret_cast<int8_t *>(ws + w.hop_seq);
-      q2.hop_step = hop_bytes(B, d.Kp);
-      q2.Rop = dv.Rop; q2.bh = dv.bh; q2.h16 = h16; q2.h8_seq = out;
-      q2.tx = ws_gemm ? nullptr : tx;
-      q2.tx2 = ws_gemm ? ga.tx2 : nullptr;
-      q2.tiles = dv.tiles; q2.bp_blocks = ga.Bp / 32;
-      q2.y = l == L - 1 ? y : nullptr;
+      sa.B = B; sa.N = N; sa.T = T; sa.Kp = d.Kp;
+      sa.GS = d.Kp / 64; sa.rows_pg = rows_pg;
+      sa.groups = std::min((B + rows_pg - 1) / rows_pg, max_groups);
+      sa.R16 = dv.R16; sa.bh = dv.bh64;
+      sa.tx2 = ws_gemm ? ga.tx2 : nullptr;
+      sa.tiles = dv.tiles; sa.Bp = ga.Bp;
+      sa.tx = ws_gemm ? nullptr : tx;
+      sa.Nt = d.Nt;
+      sa.h16 = h_state ? h16 : nullptr; sa.zero_state = h_state ? 0 : 1;
+      sa.h8 = l == L - 1 ? nullptr : out;
+      sa.y = l == L - 1 ? y : nullptr;
+      sa.hx = reinterpret_cast<int8_t *>(ws + w.hop_seq);
+      sa.hx_step = hop_bytes(B, d.Kp);
       for (int g = 0; g < 3; ++g) {
-        q2.Mh[g] = q.Mh[g];
-        q2.rh[g] = 31 - q.eh[g];
+        sa.Mh[g] = q.Mh[g];
+        sa.rh[g] = 31 - q.eh[g];
       }
-      q2.sig_tab = m->sig_tab; q2.tanh_tab = m->tanh_tab;
-      q2.counters = reinterpret_cast<unsigned *>(ws + w.sync);
-      q2.tickets = reinterpret_cast<unsigned long long *>(q2.counters + 2);
-      q2.status = m->status;
-      q2.spin_limit = m->spin_limit; q2.sync_sleep = m->sync_sleep;
-      q2.extra_arrivals = m->extra_arrivals;
+      sa.lut[0] = m->lut[0]; sa.lut[1] = m->lut[1];
+      sa.sync = ws + w.sync;
+      sa.status = m->status;
+      sa.spin_limit = m->spin_limit; sa.sync_sleep = m->sync_sleep;
+      sa.never = m->extra_arrivals;
+      if (ws_gemm) {  // the input GEMM clears the scratch on the way
+        ga.has_init = 1;
+        ga.init.sync = reinterpret_cast<int4 *>(sa.sync);
+        ga.init.sync_vec = (long long)(gru_seq_sync_bytes(sa) / 16);
+      }
+    }
+    timed_begin(GRU_INT_K_INPUT_GEMM, 1);
+    if (ws_gemm) {
+      launch_in_gemm_ws(s, ga, m->num_cus);
+    } else {
+      // the matmul's row arithmetic is 32-bit (padded columns may exceed what the call was checked for): in runs of rows
+      const int64_t most = (((int64_t)1 << 31) - 1) / std::max(3 * d.Nt, d.Ip);
+      for (int64_t r0 = 0; r0 < TB; r0 += most)
+        launch_gemm_i16(s, in + r0 * ld_in, ld_in, (int)std::min(most, TB - r0), dv.W, d.Ip, 3 * d.Nt, dv.bx, rq, tx + r0 * 3 * d.Nt, 3 * d.Nt);
+    }
+    timed_end();
+    if (seq) {
       timed_begin(GRU_INT_K_STEP, T);
-      hipLaunchKernelGGL(gru_seq_kernel, dim3((unsigned)(8 * ctiles * ((groups + 7) / 8))), dim3(256), kSeqSigBytes, s, q2);
+      for (int b0 = 0; b0 < B; b0 += max_groups * rows_pg) {
+        sa.batch0 = b0;
+        sa.groups = std::min((B - b0 + rows_pg - 1) / rows_pg, max_groups);
+        if (!ws_gemm || b0 > 0) launch_fill_i16(s, reinterpret_cast<int16_t *>(sa.sync), (int64_t)gru_seq_sync_bytes(sa) / 2, 0);
+        if (launch_gru_seq(s, sa) != hipSuccess) return LSTM_INT_E_DEVICE;
+      }
       timed_end();
     } else {
+    {
+      const int64_t n = (int64_t)B * d.Kp;  // the state before step 0 goes where step "-1" would have put it
+      hipLaunchKernelGGL(gru_init_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, h16, B, N, d.Kp, hop[1], h_state ? 0 : 1);
+    }
     GruStepArgs a{};
     a.B = B; a.N = N; a.Kp = d.Kp; a.KS32 = d.Kp / 32;
     a.ctiles = d.Ncp / 32;
@@ -981,7 +797,8 @@ int gru_int_forward(const gru_int_model *m, const int8_t *x, int32_t T, int32_t 
       const size_t tb = (size_t)t * B;
       a.hop_prev = hop[(t + 1) & 1];
       a.hop_out = hop[t & 1];
-      a.tx = ws_gemm ? nullptr : tx + tb * 3 * N;
+      a.tx = ws_gemm ? nullptr : tx + tb * 3 * d.Nt;
+      a.Nt = d.Nt;
       a.tx2 = ws_gemm ? ga.tx2 + (size_t)t * (ga.Bp / 32) * dv.tiles * 128 : nullptr;
       a.tiles = dv.tiles;
       a.h8_out = out + tb * d.Kp;
