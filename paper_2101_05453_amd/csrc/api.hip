@@ -192,7 +192,7 @@ Workspace plan_workspace(const lstm_int_model *m, int64_t T, int64_t B) {
   w.out_bytes = ((size_t)T * B + 32) * maxHpad;
   w.m2_bytes = (size_t)T * round_up(B, 32) * maxNpadp;
   w.tx = take(w.tx_bytes);
-  // 32 rows of slack behind the activation buffers: the input GEMM reads whole blocks of 32 rows
+  // 32 rows of slack behind the activation buffers
   w.out[0] = take(((size_t)T * B + 32) * maxHpad);
   w.out[1] = take(((size_t)T * B + 32) * maxHpad);
   w.xpad = take(((size_t)T * B + 32) * round_up(m->host[0].I, 64));
@@ -323,15 +323,6 @@ struct Timed {
     }
   }
 };
-
-// How the one-product rescale must treat an operand bounded by amax in magnitude
-// when the shift is r: 0 = as it is (r >= 33), 1 = shifted left by 33 - r (the
-// shifted bound still fits 32 bits), 2 = clamped first.
-int preshift_mode(int r, int64_t amax) {
-  if (r >= 33) return 0;
-  const int k = 33 - r;
-  return (k < 31 && (amax << k) <= 0x7FFFFFFFll) ? 1 : 2;
-}
 
 int upload(lstm_int_model *m) {
   if (hipSetDevice(m->device) != hipSuccess) return LSTM_INT_E_DEVICE;
@@ -1041,15 +1032,25 @@ int lstm_int_forward(const lstm_int_model *cm, const int8_t *x, int32_t T, int32
   int8_t *h0 = reinterpret_cast<int8_t *>(wsb + ws.h0);
   const int TB = T * B;
 
-  // layer 0 reads x in place when its rows are already 64-byte multiples and the batch fills whole
-  // blocks of 32 rows (the input GEMM reads whole blocks, up to 31 rows beyond the last real one)
   const int8_t *in = x;
   int ld_in = m->host[0].I;
   // A reverse run is the forward run on the time-flipped sequence: x is flipped on the way in, every
   // buffer between the layers is then indexed by step (step k works at time T - 1 - k), and y (and the
   // traces) are flipped back on the way out.  The kernels know nothing of it.
   const bool rev = m->reverse != 0;
-  if ((m->host[0].I & 63) || (reinterpret_cast<uintptr_t>(x) & 15) || (B & 31) || rev) {
+  // Layer 0 reads x in place where the input GEMM with resident weights runs it, which takes rows of 16-byte pieces and any
+  // batch, or where x already has the shape that the other kernels read (rows of 64-byte multiples, blocks of 32 rows).  A
+  // copy first costs a launch and 3 to 5 us, a tenth of a small call.
+  const bool y_aligned = (reinterpret_cast<uintptr_t>(y) & 3) == 0;
+  RecPlan plan0;
+  bool x_in_place = false;
+  if (m->path != 1 && !(trace && trace->layer == 0) && y_aligned) {
+    plan0 = plan_rec(m, 0, T, B);
+    InGemmArgs g0 = plan_in_gemm(m, 0, T, B);
+    g0.A = x; g0.lda = m->host[0].I;
+    x_in_place = plan0.ok && !rev && in_gemm_ws_supported(g0);
+  }
+  if (!(x_in_place || (!(m->host[0].I & 63) && !(reinterpret_cast<uintptr_t>(x) & 15) && !(B & 31) && !rev))) {
     Timed t(m->prof, s, LSTM_INT_K_OTHER);
     int8_t *xp = reinterpret_cast<int8_t *>(wsb + ws.xpad);
     if (rev)
@@ -1082,7 +1083,7 @@ int lstm_int_forward(const lstm_int_model *cm, const int8_t *x, int32_t T, int32
 
     // persistent path: eligible shape, no dump requested for this layer
     RecPlan plan;
-    if (m->path != 1 && !tr && (reinterpret_cast<uintptr_t>(y) & 3) == 0) plan = plan_rec(m, l, T, B);
+    if (m->path != 1 && !tr && y_aligned) plan = l == 0 ? plan0 : plan_rec(m, l, T, B);
     const bool use_p2 = plan.ok, use16 = plan.use16;
     const int p2_groups = plan.groups;
     RecArgs &ra = plan.ra;
@@ -1103,7 +1104,7 @@ int lstm_int_forward(const lstm_int_model *cm, const int8_t *x, int32_t T, int32
       {
         InGemmArgs ga = plan_in_gemm(m, l, T, B);
         ga.A = in; ga.lda = ld_in;
-        ga.a_slack = in != x;  // the workspace buffers have the slack, the caller's x need not
+        ga.cols = in == x ? h.I : 0;
         ga.tx2 = reinterpret_cast<int4 *>(tx);
         // initial h (given, or real 0 = zp_h), the cleared words of the first launch and the previous layer's
         // final h on its way to the state buffer: done by the input GEMM's workgroups ahead of their own
@@ -1315,7 +1316,14 @@ static int forward_pair(lstm_int_model *const (&m)[2], const int8_t *x, int32_t 
   const int I0 = m[0]->host[0].I, Ip0 = m[0]->dev[0].Ipad;
   const int8_t *in[2] = {x, x};
   int ld_in[2] = {I0, I0};
-  if ((I0 & 63) || (reinterpret_cast<uintptr_t>(x) & 15) || (B & 31)) {  // as in lstm_int_forward; one copy serves both
+  bool x_in_place = !(I0 & 63) && !(reinterpret_cast<uintptr_t>(x) & 15) && !(B & 31);  // as in lstm_int_forward
+  if (!x_in_place) {
+    InGemmArgs g0[2] = {plan_in_gemm(m[0], 0, T, B), plan_in_gemm(m[1], 0, T, B)};
+    g0[0].A = g0[1].A = x;
+    g0[0].lda = g0[1].lda = I0;
+    x_in_place = in_gemm_ws_supported(g0[0]) && in_gemm_ws_supported(g0[1]);
+  }
+  if (!x_in_place) {  // one copy serves both
     Timed t(m[0]->prof, s, LSTM_INT_K_OTHER);
     int8_t *xp = reinterpret_cast<int8_t *>(base[0] + ws[0].xpad);
     launch_copy_rows_i8(s, x, I0, xp, Ip0, T * B, I0, 0);
@@ -1340,7 +1348,7 @@ static int forward_pair(lstm_int_model *const (&m)[2], const int8_t *x, int32_t 
       const int8_t *h_src = h_state[i] ? h_state[i] + h_off[i] : nullptr;
       InGemmArgs ga = plan_in_gemm(m[i], l, T, B);
       ga.A = in[i]; ga.lda = ld_in[i];
-      ga.a_slack = in[i] != x;
+      ga.cols = in[i] == x ? h.I : 0;
       ga.tx2 = reinterpret_cast<int4 *>(base[i] + ws[i].tx);
       uint8_t *sync = base[0] + ws[0].sync;
       const int64_t clear = i == 0 ? sync_bytes(plan[0], groups) : 0;

@@ -52,6 +52,7 @@ struct GruLayerHost {
   int32_t Mx[3] = {0, 0, 0}, ex[3] = {0, 0, 0}, Mh[3] = {0, 0, 0}, eh[3] = {0, 0, 0};
   std::vector<int8_t> Wq, Rq;
   std::vector<int32_t> bxq, bhq, bx_fold;
+  int64_t amax_x[3] = {0, 0, 0};  // bounds of the input accumulators
 };
 
 // padded extents of one layer on the device
@@ -154,6 +155,7 @@ int prepare_gru_layer(const gru_int_layer_params &p, bool has_prev, GruLayerHost
       const int64_t f = (int64_t)q.bxq[g * N + n] - (int64_t)q.zp_x * sum;
       if (std::llabs(f) + 128 * sum_abs > 2147483647LL) return LSTM_INT_E_UNSUPPORTED;
       q.bx_fold[g * N + n] = (int32_t)f;
+      q.amax_x[g] = std::max<int64_t>(q.amax_x[g], std::llabs(f) + 128 * sum_abs);
       const int8_t *r = q.Rq.data() + ((size_t)g * N + n) * N;
       int64_t rabs = 0;
       for (int k = 0; k < N; ++k) rabs += std::abs((int)r[k]);
@@ -441,7 +443,7 @@ GruWs gru_workspace(const gru_int_model *m, int64_t T, int64_t B) {
     max_tx = std::max(max_tx, (size_t)T * B * 3 * d.Nt * 2);
     // the same terms in the register-resident input GEMM's tile order: rows padded to 32 per step, cells to 64, 4 gate slots
     max_tx = std::max(max_tx, (size_t)T * ((B + 31) / 32 * 32) * ((q.N + 63) / 64 * 64) * 4 * 2);
-    max_out = std::max(max_out, ((size_t)T * B + 32) * d.Kp);  // 32 rows of slack: that GEMM reads whole blocks of 32 rows
+    max_out = std::max(max_out, ((size_t)T * B + 32) * d.Kp);
     max_hop = std::max(max_hop, hop_bytes((int)B, d.Kp));
     sum_h16 = std::max(sum_h16, (size_t)B * q.N * 2);
   }
@@ -655,18 +657,6 @@ int gru_int_forward(const gru_int_model *m, const int8_t *x, int32_t T, int32_t 
 
   const int8_t *in = x;
   int ld_in = m->host[0].I;
-  {
-    // the matmul reads rows of Ip bytes in 16-byte pieces: a padded copy unless x already has that shape
-    const GruDims d0 = gru_dims(m->host[0].I, m->host[0].N);
-    // (or, for the input GEMM that reads whole blocks of 32 rows, unless the batch is a multiple of 32: the copy has
-    // 32 rows of slack behind it)
-    if (d0.Ip != m->host[0].I || (reinterpret_cast<uintptr_t>(x) & 15) || (B & 31)) {
-      int8_t *xp = reinterpret_cast<int8_t *>(ws + w.xpad);
-      launch_copy_rows_i8(s, x, m->host[0].I, xp, d0.Ip, (int)TB, m->host[0].I, 0);
-      in = xp;
-      ld_in = d0.Ip;
-    }
-  }
   size_t h_off = 0;
   for (int l = 0; l < L; ++l) {
     const GruLayerHost &q = m->host[l];
@@ -712,17 +702,26 @@ int gru_int_forward(const gru_int_model *m, const int8_t *x, int32_t T, int32_t 
     // up to 1024, output in its tile order, which both recurrent kernels read); else, and with a trace, from the
     // general matmul, row-major.
     InGemmArgs ga{};
-    ga.A = in; ga.a_slack = 1; ga.lda = ld_in; ga.T = T; ga.B = B; ga.Bp = (B + 31) / 32 * 32;
+    ga.A = in; ga.lda = ld_in; ga.cols = in == x ? q.I : 0; ga.T = T; ga.B = B; ga.Bp = (B + 31) / 32 * 32;
     ga.W2f = dv.W2f; ga.kpad = d.Ip; ga.tiles = dv.tiles; ga.bx2 = dv.bx2;
     ga.M[0] = 1 << 30; ga.r[0] = 33;  // the empty gate slot
     for (int g = 0; g < 3; ++g) {
       ga.M[g + 1] = q.Mx[g];
       ga.r[g + 1] = 31 - q.ex[g];
+      ga.pre = std::max(ga.pre, preshift_mode(ga.r[g + 1], q.amax_x[g]));
     }
     ga.tx2 = reinterpret_cast<int4 *>(ws + w.tx);
     // (on the launch-per-step path only where the matmul is large: the tile-ordered terms cost the step kernel
     // 0.5 us per step, measured, which 8192 rows and more of a faster matmul pay for)
     const bool ws_gemm = !tr && dv.W2f && m->num_cus == 256 && (seq || TB >= 8192) && in_gemm_ws_supported(ga);
+    // The register-resident GEMM reads x in place in any batch (rows of 16-byte pieces); the general one takes rows of Ip
+    // bytes, a padded copy unless x already has that shape.
+    if (l == 0 && !ws_gemm && (d.Ip != q.I || (reinterpret_cast<uintptr_t>(x) & 15) || (B & 31))) {
+      int8_t *xp = reinterpret_cast<int8_t *>(ws + w.xpad);
+      launch_copy_rows_i8(s, x, q.I, xp, d.Ip, (int)TB, q.I, 0);
+      in = xp;
+      ld_in = d.Ip;
+    }
     GruSeqArgs sa{};
     if (seq) {
       sa.B = B; sa.N = N; sa.T = T; sa.Kp = d.Kp;

@@ -32,6 +32,21 @@ typedef short v2s __attribute__((ext_vector_type(2)));
 
 namespace {
 
+// Loads through a buffer descriptor are bounded: what lies at or beyond base + bytes reads as zero.
+#if defined(__HIP_DEVICE_COMPILE__)
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+__device__ __forceinline__ rsrc_t make_rsrc(const int8_t *base, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t *>(base), 0, bytes, 0x00020000);  // raw, stride 0
+}
+__device__ __forceinline__ void rsrc_load_lds16(rsrc_t r, uint8_t *dst, unsigned offset) {  // lane l: 16 bytes to dst + 16 l
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)dst, 16, (int)offset, 0, 0, 0);
+}
+#else
+typedef int rsrc_t;
+__device__ rsrc_t make_rsrc(const int8_t *, int) { return 0; }
+__device__ void rsrc_load_lds16(rsrc_t, uint8_t *, unsigned) {}
+#endif
+
 // sat16(rescale(s, M, r)) of two values, packed; PRE = operand treatment (InGemmArgs::pre)
 template <int PRE>
 __device__ __forceinline__ int32_t requant2(int32_t s0, int32_t s1, const RescaleHi &p0, const RescaleHi &p1) {
@@ -95,15 +110,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   // The address of a load is a scalar base (the block's first row; rows of
   // consecutive t follow each other in memory) plus a per-lane offset that is
   // the same for every block.  The padded rows of a ragged batch (Bp > B) read
-  // the rows that follow in memory -- the first rows of the next t, or, in the
-  // last row block, the 31 rows of slack the caller provides behind the buffer;
-  // their results are never read back.
+  // the rows that follow in memory -- the first rows of the next t, or, behind
+  // the last row, nothing: the loads are bounded by the bytes left (the buffer
+  // descriptor's size); their results are never read back.
   unsigned voff[NCH];
 #pragma unroll
   for (int j = 0; j < NCH; ++j) {
     const int o = (wave + 4 * j) * 1024 + lane * 16;
     const int r = o / LS, c = o - r * LS;
-    const bool in = r < 32 && c < a.kpad;  // padding reads (row 0, byte 0) of the block
+    const bool in = r < 32 && c < a.cols;  // padding reads (row 0, byte 0) of the block
     voff[j] = in ? (unsigned)(r * a.lda + c) : 0u;  // below 32 * lda + kpad < 2^31
   }
   // the block to be loaded next: its row block, first b, and first row t * B + b
@@ -113,11 +128,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     st_b = (rb0 << 5) - t * a.Bp;
     st_row = t * a.B + st_b;
   }
-  const int8_t *st_base = a.A + (size_t)st_row * a.lda;
+  const long long bytes_total = (long long)(a.T * a.B - 1) * a.lda + a.cols;
+  auto block_rsrc = [&]() {
+    const long long at = (long long)st_row * a.lda, left = bytes_total - at;
+    return make_rsrc(a.A + at, (int)(left < 0x7FFFFFFF ? left : 0x7FFFFFFF));
+  };
+  auto st_rsrc = block_rsrc();
   auto stage_one = [&](int slot, int j) {
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(st_base + voff[j]),
-                                     (__attribute__((address_space(3))) void *)(lds + slot * BUF + (wave + 4 * j) * 1024),
-                                     16, 0, 0);
+    rsrc_load_lds16(st_rsrc, lds + slot * BUF + (wave + 4 * j) * 1024, voff[j]);
   };
   auto stage_advance = [&]() {
     if (st_rb + 1 >= rb1) return;  // past the end: the last block again, into a stage nobody reads
@@ -128,7 +146,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       st_row += a.B - st_b;  // = (t + 1) * B
       st_b = 0;
     }
-    st_base = a.A + (size_t)st_row * a.lda;
+    st_rsrc = block_rsrc();
   };
 
   // requantize and store the pieces [p_lo, p_hi) of a finished block: piece
@@ -330,7 +348,7 @@ hipError_t in_gemm_init() {
 
 bool in_gemm_ws_supported(const InGemmArgs &a) {
   if (a.kpad > 1024 || a.kpad % 64 != 0 || a.tiles % 8 != 0 || !a.W2f) return false;
-  if (a.Bp != a.B && !a.a_slack) return false;  // the last row block would read beyond the buffer
+  if (a.lda % 16 != 0 || (reinterpret_cast<uintptr_t>(a.A) & 15)) return false;  // 16-byte loads
   if (32ll * a.lda + a.kpad >= (1ll << 31)) return false;  // 32-bit offsets within a row block
   for (int g = 0; g < 4; ++g)
     if (a.r[g] < 3 || a.r[g] > 62) return false;
@@ -340,6 +358,7 @@ bool in_gemm_ws_supported(const InGemmArgs &a) {
 void launch_in_gemm_ws(hipStream_t s, const InGemmArgs &a0, int num_cus) {
   if (a0.T <= 0 || a0.B <= 0) return;
   InGemmArgs a = a0;
+  if (a.cols == 0) a.cols = a.kpad;
   for (int g = 0; g < 4; ++g) {
     a.rs[g] = rescale_hi_prepare(a.M[g], a.r[g]);
     if (a.rs[g].k != 0 && a.pre == 0) a.pre = 2;  // a caller that proved no bound

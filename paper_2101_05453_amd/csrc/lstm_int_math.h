@@ -282,6 +282,13 @@ LSTM_HD int32_t rescale_sat16_pre(int32_t a, const RescaleHi &p) {
 #endif
   return sat16((hi + p.add) >> p.sh);
 }
+// PRE for an operand bounded by amax in magnitude and a shift r: 0 = as it is (r >= 33), 1 = shifted left by 33 - r (the
+// shifted bound still fits 32 bits), 2 = clamped first
+LSTM_HD int preshift_mode(int r, int64_t amax) {
+  if (r >= 33) return 0;
+  const int k = 33 - r;
+  return (k < 31 && (amax << k) <= 0x7FFFFFFFll) ? 1 : 2;
+}
 LSTM_HD int32_t f64_low_word(double w) {
 #if defined(__HIP_DEVICE_COMPILE__)
   return __double2loint(w);

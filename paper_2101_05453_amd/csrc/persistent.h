@@ -54,9 +54,8 @@ __device__ __forceinline__ void layer_init_device(const LayerInit &w, long long 
 
 struct InGemmArgs {
   const int8_t *A;  // activations [T*B, lda]
-  int a_slack;       // the buffer is readable for 31 more rows behind row T*B - 1 (launch_in_gemm_ws needs it
-                     // when B is no multiple of 32: the padded rows of the last row block read them)
   int lda, T, B, Bp;
+  int cols;          // launch_in_gemm_ws: bytes of a row that may be read, a multiple of 16; 0 = kpad
   const int8_t *W2;  // [tiles][32][kpad] tile-ordered weight rows
   const int8_t *W2f; // the same as MFMA operands [tiles][kpad / 32][64 lanes][16]: lane = row + 32 * (k / 16 % 2)
                      // holds bytes k % 16 of k step k / 32 (launch_in_gemm_ws reads this one)

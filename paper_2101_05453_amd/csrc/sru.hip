@@ -45,6 +45,7 @@ struct SruLayerHost {
   std::vector<int8_t> Wq;
   std::vector<int16_t> vq;
   std::vector<int32_t> bq, b_fold;
+  int64_t amax_x[4] = {0, 0, 0, 0};  // bounds of the accumulators
 };
 
 // padded extents of one layer on the device
@@ -153,6 +154,7 @@ int prepare_sru_layer(const sru_int_layer_params &p, const SruLayerHost *prev, S
       const int64_t f = (int64_t)q.bq[g * N + n] - (int64_t)q.zp_x * sum;
       if (std::llabs(f) + 128 * sum_abs > 2147483647LL) return LSTM_INT_E_UNSUPPORTED;
       q.b_fold[g * N + n] = (int32_t)f;
+      q.amax_x[g] = std::max<int64_t>(q.amax_x[g], std::llabs(f) + 128 * sum_abs);
     }
   }
   for (int j = 0; j < 2; ++j) {  // 16-bit recurrent vectors (Sec. 3.2.3); v c goes to Q3.12
@@ -433,7 +435,7 @@ SruWs sru_workspace(const sru_int_model *m, int64_t T, int64_t B) {
     max_tx = std::max(max_tx, (size_t)T * B * q.G * q.N * 2);
     // the same terms in the register-resident input GEMM's tile order: rows padded to 32 per step, cells to 64, 4 slots
     max_tx = std::max(max_tx, (size_t)T * ((B + 31) / 32 * 32) * ((q.N + 63) / 64 * 64) * 4 * 2);
-    max_out = std::max(max_out, ((size_t)T * B + 32) * d.Kp);  // 32 rows of slack: that GEMM reads whole blocks of 32 rows
+    max_out = std::max(max_out, ((size_t)T * B + 32) * d.Kp);
     max_c = std::max(max_c, (size_t)B * q.N * 2);
   }
   const SruDims d0 = sru_dims(m->host[0].I, m->host[0].N, m->host[0].G);
@@ -592,17 +594,6 @@ int sru_int_forward(const sru_int_model *m, const int8_t *x, int32_t T, int32_t 
 
   const int8_t *in = x;
   int ld_in = m->host[0].I;
-  {
-    // the matmuls read rows of Ip bytes in 16-byte pieces, the register-resident one whole blocks of 32 rows: a
-    // padded copy (with 32 rows of slack behind it) unless x already has that shape
-    const SruDims d0 = sru_dims(m->host[0].I, m->host[0].N, m->host[0].G);
-    if (d0.Ip != m->host[0].I || (reinterpret_cast<uintptr_t>(x) & 15) || (B & 31)) {
-      int8_t *xp = reinterpret_cast<int8_t *>(ws + w.xpad);
-      launch_copy_rows_i8(s, x, m->host[0].I, xp, d0.Ip, (int)TB, m->host[0].I, 0);
-      in = xp;
-      ld_in = d0.Ip;
-    }
-  }
   sru_int_model *mm = const_cast<sru_int_model *>(m);  // the profile is bookkeeping beside the model
   auto timed_begin = [&](int cls) {
     if (!m->profiling) return;
@@ -625,14 +616,23 @@ int sru_int_forward(const sru_int_model *m, const int8_t *x, int32_t T, int32_t 
     const sru_int_trace *tr = (trace && trace->layer == l) ? trace : nullptr;
 
     InGemmArgs ga{};
-    ga.A = in; ga.a_slack = 1; ga.lda = ld_in; ga.T = T; ga.B = B; ga.Bp = (B + 31) / 32 * 32;
+    ga.A = in; ga.lda = ld_in; ga.cols = in == x ? q.I : 0; ga.T = T; ga.B = B; ga.Bp = (B + 31) / 32 * 32;
     ga.W2f = dv.W2f; ga.kpad = d.Ip; ga.tiles = dv.tiles; ga.bx2 = dv.b2;
     for (int g = 0; g < 4; ++g) {
       ga.M[g] = g < G ? q.Mx[g] : 1 << 30;  // an empty slot 3 multiplies zeros
       ga.r[g] = g < G ? 31 - q.ex[g] : 33;
+      ga.pre = std::max(ga.pre, preshift_mode(ga.r[g], q.amax_x[g]));
     }
     ga.tx2 = reinterpret_cast<int4 *>(ws + w.tx);
     const bool ws_gemm = m->register_gemm && !tr && dv.W2f && m->num_cus == 256 && in_gemm_ws_supported(ga);
+    // The register-resident GEMM reads x in place in any batch (rows of 16-byte pieces); the general one takes rows of Ip
+    // bytes, a padded copy unless x already has that shape.
+    if (l == 0 && !ws_gemm && (d.Ip != q.I || (reinterpret_cast<uintptr_t>(x) & 15) || (B & 31))) {
+      int8_t *xp = reinterpret_cast<int8_t *>(ws + w.xpad);
+      launch_copy_rows_i8(s, x, q.I, xp, d.Ip, (int)TB, q.I, 0);
+      in = xp;
+      ld_in = d.Ip;
+    }
     timed_begin(SRU_INT_K_INPUT_GEMM);
     if (ws_gemm) {
       launch_in_gemm_ws(s, ga, m->num_cus);
