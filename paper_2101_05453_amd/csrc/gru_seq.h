@@ -34,8 +34,8 @@ struct GruSeqArgs {
   int32_t never;              // test hook: every wait is for something that never comes
 };
 
-// scratch: placement words [8][32 words of 8 B], flags [256 workgroups][64 B], exchange words [256 workgroups][2][64 words]
-constexpr size_t kGruFlagsOff = 2048, kGruWordsOff = kGruFlagsOff + 256 * 64, kGruSyncBytes = kGruWordsOff + 256 * 1024;
+// scratch: placement words [8][32 words of 8 B], flags [256 workgroups][2 row tiles][64 B], exchange words [256 workgroups][2][64 words]
+constexpr size_t kGruFlagsOff = 2048, kGruWordsOff = kGruFlagsOff + 256 * 128, kGruSyncBytes = kGruWordsOff + 256 * 1024;
 inline size_t gru_seq_sync_bytes(const GruSeqArgs &a) {
   return a.rows_pg == 4 ? kGruWordsOff + (size_t)a.groups * a.GS * 1024 : kGruWordsOff;
 }

@@ -9,7 +9,8 @@
 //    tag) byte pairs, four cells to a 64-bit word, the tag being the step: a reader polls the words it needs.
 //  * gru_rows_kernel, groups of 16 or 32 rows: a lane has four cells of a row.  A workgroup stores its piece of the state
 //    in operand order, waits for the acknowledgement and raises its flag, a word in a line of its own; one wave polls the
-//    flags of all members, then every wave fetches a quarter of the tile, global -> LDS without a register in between.
+////    flags of all members, then every wave fetches a quarter of the tile, global -> LDS without a register in between.
+//    Groups of 32 rows are two tiles of 16 by turns, the exchange of one under the product and the cell of the other.
 //    (A flag per wave, polled by the waves that need it, saves both barriers but four times the polling delays the very
 //    stores it waits for: 0.3 to 1.3 us per step slower.  Flags packed into lines: another 1 to 3 us.)
 //
@@ -17,7 +18,8 @@
 // exchange (1 us among 2 to 32 workgroups), not the product: 0.65 us of 3.7 at 2048 cells and 64 rows.  Time per step (us),
 // one launch per step, which re-reads the weights from L2 (before; up to 1024 cells 3.6 in one launch) -> these kernels:
 //    512 cells, 16 rows   3.6 -> 1.5     1024 cells, 128 rows  3.7 -> 2.9     2048 cells, 16 rows   8.4 -> 3.3
-//    512 cells, 256 rows  3.7 -> 2.7     1024 cells, 512 rows  10.5 -> 4.6    2048 cells, 256 rows  13.4 -> 6.1
+//    512 cells, 256 rows  3.7 -> 2.7     1024 cells, 512 rows  10.5 -> 4.6    2048 cells, 256 rows  13.4 -> 5.7
+// (both tiles of 32 rows in one turn: 6.1; without any exchange it would take 4.9)
 //
 // Placement and the waits that end are those of the LSTM's recurrent kernels (rec_kernel.inc.h).
 #include "gru_seq.h"
@@ -369,18 +371,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   constexpr int TX = R * 512;  // bytes of a step's W x terms
   uint8_t *txL = lds + RT * KS * 1024;
   int32_t *bhL = reinterpret_cast<int32_t *>(txL + 2 * TX);  // [3][64]
-  int *flag = reinterpret_cast<int *>(bhL + 192);
-  int off = (RT * KS * 1024 + 2 * TX + 768 + 16 + 1023) & ~1023;
+  v4i *stage = reinterpret_cast<v4i *>(bhL + 192);           // [row tile][64 lanes]: this workgroup's piece of the new state
+  int *flag = reinterpret_cast<int *>(stage + RT * 64);
+  int off = (RT * KS * 1024 + 2 * TX + 768 + RT * 1024 + 16 + 1023) & ~1023;
   const GruLut ls = gru_lut_place(a.lut[0], off), lt = gru_lut_place(a.lut[1], off);
   gru_lut_load(a.lut[0], ls, lds, wave, lane);
   gru_lut_load(a.lut[1], lt, lds, wave, lane);
   if (tid < 192) bhL[tid] = a.bh[(tid >> 6) * 64 * GS + member * 64 + (tid & 63)];
 
-  // W x terms of a step -> LDS, 2 RT KB per wave.  Tile order: piece ((tile 2 + half) 2 + quad) R + row; row-major: piece
-  // (row 3 + gate) 8 + j
+  // W x terms of a step -> LDS, by waves 1 to 3: the poll of wave 0 would wait behind them.
+  // Tile order: piece ((tile 2 + half) 2 + quad) R + row; row-major: piece (row 3 + gate) 8 + j
   const int8_t *tx_src;  // of the first step; a piece's offset from it is the same in every step
   size_t tx_step;
-  unsigned tx_off[2 * RT];
+  constexpr int NTX = (8 * RT + 2) / 3;
+  unsigned tx_off[NTX];
   unsigned tx_has = 0;
   if (a.tx2) {
     tx_src = reinterpret_cast<const int8_t *>(a.tx2 + ((size_t)(row0 >> 5) * a.tiles + member * 8) * 128);
@@ -390,8 +394,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     tx_step = (size_t)a.B * 3 * a.Nt * 2;
   }
 #pragma unroll
-  for (int i = 0; i < 2 * RT; ++i) {
-    const int pc = (wave * 2 * RT + i) * 64 + lane;
+  for (int i = 0; i < NTX; ++i) {
+    const int pc = (wave - 1 + 3 * i) * 64 + lane;
+    if (wave == 0 || pc >= 8 * RT * 64) continue;
     if (a.tx2) {
       const int rr = pc & (R - 1), quad = (pc / R) & 1, half = (pc / (2 * R)) & 1, tile = pc / (4 * R);
       tx_off[i] = (unsigned)(tile * 128 + half * 64 + 32 * quad + (row0 & 31) + rr) * 16;
@@ -405,8 +410,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   auto tx_request = [&](int t) {
     const int8_t *src = tx_src + (size_t)t * tx_step;
 #pragma unroll
-    for (int i = 0; i < 2 * RT; ++i)
-      if (tx_has >> i & 1) dma16(src + tx_off[i], txL + (t & 1) * TX + (wave * 2 * RT + i) * 1024);
+    for (int i = 0; i < NTX; ++i)
+      if (tx_has >> i & 1) dma16(src + tx_off[i], txL + (t & 1) * TX + (wave - 1 + 3 * i) * 1024);
   };
   // byte offset of a lane's four terms of a gate, row tile 0; row tile rt: tx_row rt further
   int tx_at[3];
@@ -463,151 +468,187 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   if (tid == 0) flag[0] = 1;
   const bool y_vec = (N & 15) == 0 && (reinterpret_cast<uintptr_t>(a.y) & 15) == 0;
   const bool y_words = (N & 3) == 0 && (reinterpret_cast<uintptr_t>(a.y) & 3) == 0;
-  unsigned *const flags = reinterpret_cast<unsigned *>(a.sync + kGruFlagsOff) + pl.group * GS * 16;
+  unsigned *const flags = reinterpret_cast<unsigned *>(a.sync + kGruFlagsOff) + pl.group * RT * GS * 16;  // [row tile][member], a line each
   const int per = (GS + 3) >> 2, m0 = wave * per < GS ? wave * per : GS, m1 = m0 + per < GS ? m0 + per : GS;  // members whose pieces this wave fetches
   // group's part of a step of the exchange buffer, in rows of 16: tiles of ks_n KB
   int8_t *const hx0 = a.hx + (size_t)(a.batch0 / 16 + pl.group * RT) * ks_n * 1024;
   wait_vmem();
   __syncthreads();
 
-  for (int t = 0; t < T; ++t) {
-    // The terms of this step.  (Read in an asm: behind an ordinary read of memory that transfers fill, the compiler waits for
-    // every operation on global memory before it, here the stores of the output of the step before.)
-    short4 tx4[RT][3];
+  // The terms of a step.  (Read in an asm: behind an ordinary read of memory that transfers fill, the compiler waits for
+  // every operation on global memory before it, here the stores of the output of the step before.)
+  auto read_tx = [&](int t, int rt, short4 (&tx4)[3]) {
+    const unsigned at = (unsigned)(RT * KS * 1024 + (t & 1) * TX + rt * tx_row);
+    asm volatile("ds_read_b64 %0, %3\n ds_read_b64 %1, %4\n ds_read_b64 %2, %5\n s_waitcnt lgkmcnt(0)"
+                 : "=&v"(tx4[0]), "=&v"(tx4[1]), "=&v"(tx4[2])
+                 : "v"(at + tx_at[0]), "v"(at + tx_at[1]), "v"(at + tx_at[2])
+                 : "memory");
+  };
+  auto product = [&](int rt, v4i (&acc)[3]) {
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-      const unsigned at = (unsigned)(RT * KS * 1024 + (t & 1) * TX + rt * tx_row);
-      asm volatile("ds_read_b64 %0, %3\n ds_read_b64 %1, %4\n ds_read_b64 %2, %5\n s_waitcnt lgkmcnt(0)"
-                   : "=&v"(tx4[rt][0]), "=&v"(tx4[rt][1]), "=&v"(tx4[rt][2])
-                   : "v"(at + tx_at[0]), "v"(at + tx_at[1]), "v"(at + tx_at[2])
-                   : "memory");
+    for (int g = 0; g < 3; ++g) acc[g] = *reinterpret_cast<const v4i *>(bhL + g * 64 + wave * 16 + 4 * q);
+    constexpr int DEPTH = 4;  // k steps of operands ahead
+    v4i hf[DEPTH];
+#pragma unroll
+    for (int ks = 0; ks < DEPTH; ++ks) hf[ks] = hT[(rt * KS + ks) * 64 + lane];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+#pragma unroll
+      for (int g = 0; g < 3; ++g) acc[g] = __builtin_amdgcn_mfma_i32_16x16x64_i8(Wf[g][ks], hf[ks % DEPTH], acc[g], 0, 0, 0);
+      if (ks + DEPTH < KS) hf[ks % DEPTH] = hT[(rt * KS + ks + DEPTH) * 64 + lane];
+      __builtin_amdgcn_sched_barrier(0);
     }
-    if (t + 1 < T) tx_request(t + 1);
-    v4i acc[3][RT];
+  };
+  // the cell of a row tile: new state into h, its int8 form packed
+  auto cell = [&](const v4i (&acc)[3], const short4 (&tx4)[3], int32_t (&h)[4]) {
+    int32_t th[3][4], tx[3][4];
 #pragma unroll
     for (int g = 0; g < 3; ++g) {
-      const v4i b = *reinterpret_cast<const v4i *>(bhL + g * 64 + wave * 16 + 4 * q);
-#pragma unroll
-      for (int rt = 0; rt < RT; ++rt) acc[g][rt] = b;
+      tx[g][0] = tx4[g].x; tx[g][1] = tx4[g].y; tx[g][2] = tx4[g].z; tx[g][3] = tx4[g].w;
     }
-    {
-      constexpr int DEPTH = 4;  // k steps of operands ahead
-      v4i hf[DEPTH][RT];
+    if (pre) {
 #pragma unroll
-      for (int ks = 0; ks < DEPTH; ++ks)
+      for (int g = 0; g < 3; ++g)
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) hf[ks][rt] = hT[(rt * KS + ks) * 64 + lane];
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-          for (int g = 0; g < 3; ++g) acc[g][rt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(Wf[g][ks], hf[ks % DEPTH][rt], acc[g][rt], 0, 0, 0);
-        if (ks + DEPTH < KS)
-#pragma unroll
-          for (int rt = 0; rt < RT; ++rt) hf[ks % DEPTH][rt] = hT[(rt * KS + ks + DEPTH) * 64 + lane];
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-    // every wave is done with the tile before any wave fetches the next state into it
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    uint32_t pk[RT];
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-      int32_t th[3][4], tx[3][4];
-#pragma unroll
-      for (int g = 0; g < 3; ++g) {
-        const short4 t4 = tx4[rt][g];
-        tx[g][0] = t4.x; tx[g][1] = t4.y; tx[g][2] = t4.z; tx[g][3] = t4.w;
-      }
-      if (pre) {
-#pragma unroll
-        for (int g = 0; g < 3; ++g)
-#pragma unroll
-          for (int c = 0; c < 4; ++c) th[g][c] = rescale_sat16_pre<2>(acc[g][rt][c], ps[g]);
-      } else {
-#pragma unroll
-        for (int g = 0; g < 3; ++g)
-#pragma unroll
-          for (int c = 0; c < 4; ++c) th[g][c] = rescale_sat16_pre<0>(acc[g][rt][c], ps[g]);
-      }
-      int32_t x[8], v[8], xn[4], vn[4];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        x[c] = sat16(tx[0][c] + th[0][c]);
-        x[4 + c] = sat16(tx[1][c] + th[1][c]);
-      }
-      gru_lookup<8>(lds, ls, x, v);
-#pragma unroll
-      for (int c = 0; c < 4; ++c) xn[c] = sat16(tx[2][c] + ((mul_i24(mirror_sigmoid(x[c], v[c]), th[2][c]) + 16384) >> 15));
-      gru_lookup<4>(lds, lt, xn, vn);
-      pk[rt] = 0;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const int32_t u = mirror_sigmoid(x[4 + c], v[4 + c]);
-        hreg[rt][c] = cell_update32(cifg_input_gate(u), mirror_tanh(xn[c], vn[c]), u, hreg[rt][c], 0);
-        pk[rt] |= (uint32_t)(state_i8(hreg[rt][c]) & 0xFF) << (8 * c);
-      }
-    }
-    // byte 4 q of lane (c16, wave) of k step `member`
-    if (GS == 1 || (t == T - 1 && T > 1)) {  // nobody else reads this state (see gru_quad_kernel)
-#pragma unroll
-      for (int rt = 0; rt < RT; ++rt) *reinterpret_cast<uint32_t *>(lds + ((rt * KS + member) * 64 + wave * 16 + c16) * 16 + 4 * q) = pk[rt];
-      wait_vmem();
-      __syncthreads();
+        for (int c = 0; c < 4; ++c) th[g][c] = rescale_sat16_pre<2>(acc[g][c], ps[g]);
     } else {
-      int8_t *const hx = hx0 + (size_t)t * a.hx_step;
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) *reinterpret_cast<uint32_t *>(hx + ((size_t)(rt * ks_n + member) * 64 + wave * 16 + c16) * 16 + 4 * q) = pk[rt];
-      wait_vmem();
-      __syncthreads();
-      if (wave == 0) {
-        const unsigned step = (unsigned)(t + 1);
-        if (lane == 0) __hip_atomic_store(flags + member * 16, step, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        for (int i = 0; i < a.sync_sleep; ++i) __builtin_amdgcn_s_sleep(1);
-        int budget = a.spin_limit;
-        for (;;) {
-          const unsigned f = __hip_atomic_load(flags + (lane < GS ? lane : 0) * 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          if (__builtin_amdgcn_ballot_w64((int)(f - step) < 0 || a.never) == 0) break;
-          if (gru_spent(a, budget)) {
-            __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            flag[0] = 0;
-            break;
-          }
-        }
+      for (int g = 0; g < 3; ++g)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) th[g][c] = rescale_sat16_pre<0>(acc[g][c], ps[g]);
+    }
+    int32_t x[8], v[8], xn[4], vn[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      x[c] = sat16(tx[0][c] + th[0][c]);
+      x[4 + c] = sat16(tx[1][c] + th[1][c]);
+    }
+    gru_lookup<8>(lds, ls, x, v);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) xn[c] = sat16(tx[2][c] + ((mul_i24(mirror_sigmoid(x[c], v[c]), th[2][c]) + 16384) >> 15));
+    gru_lookup<4>(lds, lt, xn, vn);
+    uint32_t pk = 0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int32_t u = mirror_sigmoid(x[4 + c], v[4 + c]);
+      h[c] = cell_update32(cifg_input_gate(u), mirror_tanh(xn[c], vn[c]), u, h[c], 0);
+      pk |= (uint32_t)(state_i8(h[c]) & 0xFF) << (8 * c);
+    }
+    return pk;
+  };
+  // byte 4 q of lane (c16, wave) of a piece: this lane's four cells
+  const int mine = (wave * 16 + c16) * 16 + 4 * q;
+  auto store_piece = [&](int t, int rt, uint32_t pk) {
+    *reinterpret_cast<uint32_t *>(hx0 + (size_t)t * a.hx_step + (size_t)(rt * ks_n + member) * 1024 + mine) = pk;
+  };
+  auto fetch = [&](int t, int rt) {  // a quarter of the tile per wave
+    const int8_t *src = hx0 + (size_t)t * a.hx_step + (size_t)rt * ks_n * 1024 + lane * 16;
+    for (int m = m0; m < m1; ++m) dma16(src + (size_t)m * 1024, hT + (rt * KS + m) * 64);
+  };
+  auto raise = [&](int rt, int step) {
+    if (tid == 0) __hip_atomic_store(flags + (rt * GS + member) * 16, (unsigned)step, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  auto poll = [&](int rt, int step) {  // wave 0: all members have finished `step` steps of the row tile
+    int budget = a.spin_limit;
+    for (;;) {
+      const unsigned f = __hip_atomic_load(flags + (rt * GS + (lane < GS ? lane : 0)) * 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (__builtin_amdgcn_ballot_w64((int)(f - (unsigned)step) < 0 || a.never) == 0) break;
+      if (gru_spent(a, budget)) {
+        __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        flag[0] = 0;
+        break;
       }
-      __syncthreads();
-      asm volatile("" ::: "memory");
-      for (int m = m0; m < m1; ++m)
+    }
+  };
+  auto output = [&](int t, int rt) {  // this workgroup's 64 columns: 16 cells of a row per lane of one wave
+    const int row = row0 + rt * 16 + c16, n = member * 64 + 16 * q;
+    if (row >= a.B) return;
+    const size_t orow = (size_t)t * a.B + row;
+    const v4i w = stage[rt * 64 + lane];
+    if (a.h8) *reinterpret_cast<v4i *>(a.h8 + orow * a.Kp + n) = w;
+    if (!a.y) return;
+    int8_t *yd = a.y + orow * N + n;
+    if (y_vec) {
+      if (n < N) *reinterpret_cast<v4i *>(yd) = w;
+    } else if (y_words) {
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) dma16(hx + ((size_t)(rt * ks_n + m) * 64 + lane) * 16, hT + (rt * KS + m) * 64);
-      wait_vmem();
+      for (int j = 0; j < 4; ++j)
+        if (n + 4 * j < N) reinterpret_cast<int32_t *>(yd)[j] = w[j];
+    } else {
+#pragma unroll
+      for (int j = 0; j < 16; ++j)
+        if (n + j < N) yd[j] = (int8_t)(w[j >> 2] >> (8 * (j & 3)));
+    }
+  };
+  auto keep_piece = [&](int rt, uint32_t pk) {  // in LDS: for the output, and, where the group is this workgroup, as the state
+    *reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(stage + rt * 64) + mine) = pk;
+    if (GS == 1) *reinterpret_cast<uint32_t *>(lds + rt * KS * 1024 + mine) = pk;
+  };
+
+  if constexpr (RT == 1) {
+    for (int t = 0; t < T; ++t) {
+      short4 tx4[3];
+      v4i acc[3];
+      read_tx(t, 0, tx4);
+      if (t + 1 < T) tx_request(t + 1);
+      product(0, acc);
+      // every wave is done with the tile before any wave fetches the next state into it
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      const uint32_t pk = cell(acc, tx4, hreg[0]);
+      keep_piece(0, pk);
+      if (GS == 1 || (t == T - 1 && T > 1)) {  // nobody else reads this state (see gru_quad_kernel)
+        wait_vmem();
+        __syncthreads();
+      } else {
+        store_piece(t, 0, pk);
+        wait_vmem();
+        __syncthreads();
+        if (wave == 0) {
+          raise(0, t + 1);
+          for (int i = 0; i < a.sync_sleep; ++i) __builtin_amdgcn_s_sleep(1);
+          poll(0, t + 1);
+        }
+        __syncthreads();
+        asm volatile("" ::: "memory");
+        fetch(t, 0);
+        wait_vmem();
+        __syncthreads();
+        if (flag[0] == 0) return;
+      }
+      if (wave == 1) output(t, 0);
+    }
+  } else {
+    // Two row tiles by turns: while the members exchange the state of one, they work on the other.  The flags of the other
+    // tile were raised half a step ago when they are polled, its pieces arrive under the cell of this one.
+    for (int t = 0; t < T; ++t) {
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt) {
+        short4 tx4[3];
+        v4i acc[3];
+        read_tx(t, rt, tx4);
+        if (rt == 0 && t + 1 < T) tx_request(t + 1);
+        product(rt, acc);
+        const int other_step = t - (rt == 0);  // the step whose state of the other tile comes in now
+        const bool comes = GS > 1 && other_step >= 0 && other_step + 1 < T;
+        if (comes && wave == 0) poll(1 - rt, other_step + 1);
+        // (not __syncthreads: nothing waits for the stores of the output)
+        asm volatile("s_waitcnt lgkmcnt(0)\n s_barrier" ::: "memory");
+        if (comes) fetch(other_step, 1 - rt);
+        const uint32_t pk = cell(acc, tx4, hreg[rt]);
+        keep_piece(rt, pk);
+        if (GS > 1 && t + 1 < T) store_piece(t, rt, pk);
+        wait_vmem();
+        __syncthreads();
+        if (flag[0] == 0) return;
+        if (GS > 1) raise(rt, t + 1);
+        if (wave == 1) output(t, rt);
+      }
+    }
+    if (GS > 1 && T == 1) {  // h16 is read by every member and written by each
+      if (wave == 0) poll(1, 1);
       __syncthreads();
       if (flag[0] == 0) return;
-    }
-    // this workgroup's 64 columns of the output, a row tile per wave
-    if (wave < RT) {
-      const int row = row0 + wave * 16 + c16, n = member * 64 + 16 * q;
-      if (row < a.B) {
-        const size_t orow = (size_t)t * a.B + row;
-        const v4i w = hT[(wave * KS + member) * 64 + lane];
-        if (a.h8) *reinterpret_cast<v4i *>(a.h8 + orow * a.Kp + n) = w;
-        if (a.y) {
-          int8_t *yd = a.y + orow * N + n;
-          if (y_vec) {
-            if (n < N) *reinterpret_cast<v4i *>(yd) = w;
-          } else if (y_words) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-              if (n + 4 * j < N) reinterpret_cast<int32_t *>(yd)[j] = w[j];
-          } else {
-#pragma unroll
-            for (int j = 0; j < 16; ++j)
-              if (n + j < N) yd[j] = (int8_t)(w[j >> 2] >> (8 * (j & 3)));
-          }
-        }
-      }
     }
   }
   gru_placement_check(a);
@@ -646,7 +687,7 @@ gru_fn gru_pick(int ks, int rows) {
   }
 }
 size_t gru_lds_bytes(int ks, int rows, const LutWide (&lut)[2]) {
-  size_t n = rows == 4 ? 8 * (size_t)(ks * 64 + 16) + 4096 + 16 : (size_t)(rows / 16) * ks * 1024 + 2 * rows * 512 + 768 + 16;
+  size_t n = rows == 4 ? 8 * (size_t)(ks * 64 + 16) + 4096 + 16 : (size_t)(rows / 16) * (ks + 1) * 1024 + 2 * rows * 512 + 768 + 16;
   n = (n + 1023) & ~(size_t)1023;
   for (const LutWide &l : lut) n += (size_t)lut_wide_lds_bytes(l.dom, l.sh, l.tail != 0);
   return n;
