@@ -9,7 +9,7 @@
 //    tag) byte pairs, four cells to a 64-bit word, the tag being the step: a reader polls the words it needs.
 //  * gru_rows_kernel, groups of 16 or 32 rows: a lane has four cells of a row.  A workgroup stores its piece of the state
 //    in operand order, waits for the acknowledgement and raises its flag, a word in a line of its own; one wave polls the
-////    flags of all members, then every wave fetches a quarter of the tile, global -> LDS without a register in between.
+//    flags of all members, then every wave fetches a quarter of the tile, global -> LDS without a register in between.
 //    Groups of 32 rows are two tiles of 16 by turns, the exchange of one under the product and the cell of the other.
 //    (A flag per wave, polled by the waves that need it, saves both barriers but four times the polling delays the very
 //    stores it waits for: 0.3 to 1.3 us per step slower.  Flags packed into lines: another 1 to 3 us.)

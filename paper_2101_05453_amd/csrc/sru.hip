@@ -172,7 +172,9 @@ int prepare_sru_layer(const sru_int_layer_params &p, const SruLayerHost *prev, S
 
 constexpr int kDepth = 4;  // steps whose terms are in flight ahead of the one being computed
 constexpr int kSigEntries = 32776;  // the table's 32769 entries, to a multiple of 8
+constexpr int kSigFull = 65536;      // its values for every x, index x + 32768
 constexpr int kScanBlock = 256;    // threads per workgroup of the scan (each workgroup holds a table: two per compute unit)
+constexpr int kScanBlockFull = 512;  // with the table of all values (128 KB): one workgroup per compute unit
 
 struct SruScanArgs {
   int32_t T, B, N, G;
@@ -193,7 +195,8 @@ struct SruScanArgs {
   int8_t *out;         // [T*B][ld_out] for the next layer's matmul, or NULL
   int32_t ld_out;
   int8_t *y;           // dense [T*B][N], or NULL
-  const uint16_t *sig_tab;  // Q3.12
+  const uint16_t *sig_tab;  // Q3.12, by magnitude
+  const uint16_t *sig_full; // by value
   int16_t *tr_tx, *tr_tv, *tr_act, *tr_c, *tr_h16;  // dumps (row-major form only), each may be NULL
   int8_t *tr_y;
 };
@@ -205,17 +208,22 @@ struct SruScanArgs {
 // here and every instruction of that wave, scalar branches included, is time on the chain from step to step --
 // N is a multiple of 4 and y is 4-byte aligned (whole aligned pieces everywhere), no dumps, and the operands of the
 // elementwise rescales cannot overflow their left shift (their clamp is dropped).
-template <bool TILE, bool FAST>
-__global__ __launch_bounds__(kScanBlock) void sru_scan_kernel(SruScanArgs a) {
+// FULL: sigma from a table of all 65536 values, 128 KB of LDS: a lookup is one add and one read instead of the magnitude
+// before and the mirroring after it (five instructions of about 38 per gate).  2048 cells, 256 rows, 64 steps, 267 MB:
+// 78 us per layer -> 70, 3.8 TB/s (98 -> 92 from tile-ordered terms, 300 MB).
+template <bool TILE, bool FAST, bool FULL>
+__global__ __launch_bounds__(FULL ? kScanBlockFull : kScanBlock) void sru_scan_kernel(SruScanArgs a) {
+  constexpr int BLOCK = FULL ? kScanBlockFull : kScanBlock;
   constexpr int CPT = 4;             // cells per thread
   constexpr int PRE = FAST ? 1 : 2;  // operand treatment of rescale_sat16_pre
   // the Q3.12 sigma table in LDS: the lookup sits in the chain from one step's state to the next, where a gather
   // from memory costs its full latency every step (measured at 1024 cells, B = 256, T = 64: 117 -> 68 us per layer)
-  __shared__ __attribute__((aligned(16))) uint16_t sig_lds[kSigEntries];
+  extern __shared__ __attribute__((aligned(16))) uint16_t sig_lds[];
   {
-    const int4 *src = reinterpret_cast<const int4 *>(a.sig_tab);  // the table's buffer is readable to a multiple of 16 bytes
+    const int4 *src = reinterpret_cast<const int4 *>(FULL ? a.sig_full : a.sig_tab);  // readable to a multiple of 16 bytes
     int4 *dst = reinterpret_cast<int4 *>(sig_lds);
-    for (int i = threadIdx.x; i < kSigEntries / 8; i += kScanBlock) dst[i] = src[i];
+#pragma unroll 4
+    for (int i = threadIdx.x; i < (FULL ? kSigFull : kSigEntries) / 8; i += BLOCK) dst[i] = src[i];
     __syncthreads();  // before any thread leaves: every thread of the workgroup gets here
   }
   const int N = a.N;
@@ -225,7 +233,7 @@ __global__ __launch_bounds__(kScanBlock) void sru_scan_kernel(SruScanArgs a) {
   if (TILE) {
     const int lane = threadIdx.x & 63;
     const int tiles_used = (N + 7) >> 3;
-    const int w = blockIdx.x * (kScanBlock / 64) + (threadIdx.x >> 6);
+    const int w = blockIdx.x * (BLOCK / 64) + (threadIdx.x >> 6);
     const int rbk = w / tiles_used, tile = w - rbk * tiles_used;
     if (rbk >= a.bp_blocks) return;
     row = rbk * 32 + (lane & 31);
@@ -234,7 +242,7 @@ __global__ __launch_bounds__(kScanBlock) void sru_scan_kernel(SruScanArgs a) {
     tp_step = (size_t)a.bp_blocks * a.tiles * 128;
   } else {
     const int N4 = (N + 3) >> 2;
-    const int64_t idx = (int64_t)blockIdx.x * kScanBlock + threadIdx.x;
+    const int64_t idx = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
     if (idx >= (int64_t)a.B * N4) return;
     row = (int)(idx / N4);
     n0 = 4 * (int)(idx - (int64_t)row * N4);
@@ -251,6 +259,10 @@ __global__ __launch_bounds__(kScanBlock) void sru_scan_kernel(SruScanArgs a) {
     cst[c] = (n < N && !a.zero_state) ? a.c_state[(size_t)rowc * N + n] : 0;
     vf[c] = n < N ? a.vq[n] : 0;
     vr[c] = n < N ? a.vq[N + n] : 0;
+    if (FAST) {  // the operand's left shift of the rescale, by at most one, on the factor that stays
+      vf[c] = (int32_t)((uint32_t)vf[c] << a.pv[0].k);
+      vr[c] = (int32_t)((uint32_t)vr[c] << a.pv[1].k);
+    }
   }
 
   // the terms of a step as they come from memory
@@ -259,16 +271,20 @@ __global__ __launch_bounds__(kScanBlock) void sru_scan_kernel(SruScanArgs a) {
     int32_t x4;   // the thread's input bytes (identity highway)
   };
   const size_t GN = (size_t)a.G * N;
+  // this thread's addresses: what is of the thread once, what is of the step in scalar arithmetic
+  const int16_t *const tx0 = a.tx + (size_t)rowc * GN + n0;
+  const int8_t *const x0 = a.xin + (size_t)rowc * a.ld_x + n0;
+  int8_t *const out0 = a.out ? a.out + (size_t)row * a.ld_out + n0 : nullptr, *const y0 = a.y ? a.y + (size_t)row * N + n0 : nullptr;
+  const size_t tx_step = (size_t)a.B * GN, x_step = (size_t)a.B * a.ld_x, out_step = (size_t)a.B * a.ld_out, y_step = (size_t)a.B * N;
   auto request = [&](int t) {
     Raw r;
     r.p0 = r.p1 = int4{0, 0, 0, 0};
     r.x4 = 0;
-    const size_t tb = (size_t)t * a.B + rowc;
     if (TILE) {
       r.p0 = tp[(size_t)t * tp_step];
       r.p1 = tp[(size_t)t * tp_step + 64];
     } else {
-      const int16_t *q = a.tx + tb * GN + n0;
+      const int16_t *q = tx0 + (size_t)t * tx_step;
       if (vec) {
         const int2 s0 = *reinterpret_cast<const int2 *>(q), s1 = *reinterpret_cast<const int2 *>(q + N);
         const int2 s2 = *reinterpret_cast<const int2 *>(q + 2 * (size_t)N);
@@ -288,7 +304,7 @@ __global__ __launch_bounds__(kScanBlock) void sru_scan_kernel(SruScanArgs a) {
       }
     }
     if (identity) {
-      const int8_t *xp = a.xin + tb * a.ld_x + n0;
+      const int8_t *xp = x0 + (size_t)t * x_step;
       if (vec) {
         r.x4 = *reinterpret_cast<const int32_t *>(xp);
       } else {
@@ -317,12 +333,19 @@ __global__ __launch_bounds__(kScanBlock) void sru_scan_kernel(SruScanArgs a) {
     for (int c = 0; c < CPT; ++c) {
       // both gates read the state before the step (Secs. 3.2.3, 3.2.1)
       // (all products here are of 16-bit values: the 24-bit multiply is exact and runs at full rate)
-      tvf[c] = rescale_sat16_pre<PRE>(__mul24(vf[c], cst[c]), a.pv[0]);
-      tvr[c] = rescale_sat16_pre<PRE>(__mul24(vr[c], cst[c]), a.pv[1]);
-      const int32_t f = sigmoid_from_table(sig_lds, sat16(tx[1][c] + tvf[c]));
-      const int32_t g = sigmoid_from_table(sig_lds, sat16(tx[2][c] + tvr[c]));
-      const int32_t fbar = 32768 - f < 32767 ? 32768 - f : 32767;  // Sec. 3.2.9
-      const int32_t gbar = 32768 - g < 32767 ? 32768 - g : 32767;
+      tvf[c] = rescale_sat16_pre<FAST ? 0 : 2>(__mul24(vf[c], cst[c]), a.pv[0]);
+      tvr[c] = rescale_sat16_pre<FAST ? 0 : 2>(__mul24(vr[c], cst[c]), a.pv[1]);
+      // FAST: the Q3.12 table stays within 1..32767 (the host has checked), no clamp of a gate or its complement acts
+      auto sigmoid = [&](int32_t x) -> int32_t {
+        if (FULL) return sig_lds[x + 32768];
+        if (!FAST) return sigmoid_from_table(sig_lds, x);
+        const int32_t v = sig_lds[x < 0 ? -x : x];
+        return x < 0 ? 32768 - v : v;
+      };
+      auto complement = [&](int32_t v) { return FAST ? 32768 - v : cifg_input_gate(v); };  // Sec. 3.2.9
+      const int32_t f = sigmoid(sat16(tx[1][c] + tvf[c]));
+      const int32_t g = sigmoid(sat16(tx[2][c] + tvr[c]));
+      const int32_t fbar = complement(f), gbar = complement(g);
       // Sec. 3.2.7: products of a Q0.15 gate and a value in the state's format, each rounded back, saturating sum
       const int32_t cn = sat16(((__mul24(f, cst[c]) + 16384) >> 15) + ((__mul24(fbar, tx[0][c]) + 16384) >> 15));
       const int32_t hn = sat16(((__mul24(g, cn) + 16384) >> 15) + ((__mul24(gbar, tx[3][c]) + 16384) >> 15));
@@ -338,8 +361,8 @@ __global__ __launch_bounds__(kScanBlock) void sru_scan_kernel(SruScanArgs a) {
     for (int c = 0; c < CPT; ++c) packed |= (int32_t)((uint32_t)(yv[c] & 0xFF) << (8 * c));
     if (FAST) {
       if (row_ok && n0 < N) {  // the only lane-dependent branch of a step
-        if (a.out) *reinterpret_cast<int32_t *>(a.out + tb * a.ld_out + n0) = packed;
-        if (a.y) *reinterpret_cast<int32_t *>(a.y + tb * N + n0) = packed;
+        if (a.out) *reinterpret_cast<int32_t *>(out0 + (size_t)t * out_step) = packed;
+        if (a.y) *reinterpret_cast<int32_t *>(y0 + (size_t)t * y_step) = packed;
       }
       return;
     }
@@ -353,8 +376,8 @@ __global__ __launch_bounds__(kScanBlock) void sru_scan_kernel(SruScanArgs a) {
           if (n0 + c < N) o[c] = (int8_t)yv[c];
       }
     };
-    if (a.out) put(a.out + tb * a.ld_out + n0, true);
-    if (a.y) put(a.y + tb * N + n0, (reinterpret_cast<uintptr_t>(a.y) & 3) == 0);
+    if (a.out) put(out0 + (size_t)t * out_step, true);
+    if (a.y) put(y0 + (size_t)t * y_step, (reinterpret_cast<uintptr_t>(a.y) & 3) == 0);
     if (!TILE) {
 #pragma unroll
       for (int c = 0; c < CPT; ++c) {
@@ -399,6 +422,20 @@ __global__ __launch_bounds__(kScanBlock) void sru_scan_kernel(SruScanArgs a) {
   }
 }
 
+typedef void (*scan_fn)(SruScanArgs);
+scan_fn pick_scan(bool tile, bool fast, bool full) {
+  if (tile) return full ? sru_scan_kernel<true, true, true> : fast ? sru_scan_kernel<true, true, false> : sru_scan_kernel<true, false, false>;
+  return full ? sru_scan_kernel<false, true, true> : fast ? sru_scan_kernel<false, true, false> : sru_scan_kernel<false, false, false>;
+}
+hipError_t scan_init() {
+  for (int v = 0; v < 6; ++v) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(pick_scan(v & 1, v >> 1 > 0, v >> 1 > 1)),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 struct SruTimed {
   hipEvent_t start, stop;
   int cls, launches;
@@ -419,7 +456,8 @@ struct sru_int_model {
   std::vector<SruLayerHost> host;
   std::vector<SruLayerDev> dev;
   uint8_t *arena = nullptr;
-  const uint16_t *sig_tab = nullptr;
+  const uint16_t *sig_tab = nullptr, *sig_full = nullptr;
+  bool sig_inner = false;  // no value of sigma's table is 0 or beyond 32767, mirrored ones included
 };
 
 namespace {
@@ -484,6 +522,13 @@ int sru_int_prepare(const sru_int_layer_params *layers, int32_t num_layers, int3
     };
     const size_t o_sig = reserve((size_t)kSigEntries * 2);
     fill_sigmoid_table(3, reinterpret_cast<uint16_t *>(img.data() + o_sig));
+    const size_t o_full = reserve((size_t)kSigFull * 2);
+    {
+      const uint16_t *tab = reinterpret_cast<const uint16_t *>(img.data() + o_sig);
+      uint16_t *full = reinterpret_cast<uint16_t *>(img.data() + o_full);
+      for (int x = -32768; x < 32768; ++x) full[x + 32768] = (uint16_t)sigmoid_from_table(tab, x);
+      m->sig_inner = *std::max_element(tab, tab + 32769) <= 32767 && *std::min_element(full, full + kSigFull) >= 1;
+    }
     struct Off { size_t W, bias, vq, W2f, b2; int tiles; };
     std::vector<Off> offs(num_layers);
     for (int l = 0; l < num_layers; ++l) {
@@ -513,6 +558,7 @@ int sru_int_prepare(const sru_int_layer_params *layers, int32_t num_layers, int3
       offs[l] = o;
     }
     if (hipSetDevice(device) != hipSuccess || in_gemm_init() != hipSuccess || gemm_init() != hipSuccess ||
+        scan_init() != hipSuccess ||
         hipMalloc(reinterpret_cast<void **>(&m->arena), img.size()) != hipSuccess) {
       m->arena = nullptr;
       delete m;
@@ -528,6 +574,7 @@ int sru_int_prepare(const sru_int_layer_params *layers, int32_t num_layers, int3
       m->num_cus = hipGetDeviceProperties(&prop, device) == hipSuccess ? prop.multiProcessorCount : 0;
     }
     m->sig_tab = reinterpret_cast<const uint16_t *>(m->arena + o_sig);
+    m->sig_full = reinterpret_cast<const uint16_t *>(m->arena + o_full);
     m->dev.resize(num_layers);
     for (int l = 0; l < num_layers; ++l) {
       m->dev[l].W = reinterpret_cast<const int8_t *>(m->arena + offs[l].W);
@@ -666,27 +713,20 @@ int sru_int_forward(const sru_int_model *m, const int8_t *x, int32_t T, int32_t 
     a.ld_out = d.Kp;
     a.y = l == L - 1 ? y : nullptr;
     a.sig_tab = m->sig_tab;
+    a.sig_full = m->sig_full;
     if (tr) {
       a.tr_tx = tr->tx; a.tr_tv = tr->tv; a.tr_act = tr->act; a.tr_c = tr->c; a.tr_h16 = tr->h16; a.tr_y = tr->y;
     }
     timed_begin(SRU_INT_K_SCAN);
-    constexpr int kWpb = kScanBlock / 64;
     // the specialization that drops the checks the host can make once (see sru_scan_kernel)
     const bool fast = !tr && (N & 3) == 0 && (reinterpret_cast<uintptr_t>(y) & 3) == 0 && 31 - q.ev[0] >= 32 &&
-                      31 - q.ev[1] >= 32 && 31 - q.eh >= 18 && (G == 4 || 31 - q.es >= 11);
-    if (ws_gemm) {
-      const dim3 grid((unsigned)(((int64_t)a.bp_blocks * ((N + 7) / 8) + kWpb - 1) / kWpb));
-      if (fast)
-        hipLaunchKernelGGL((sru_scan_kernel<true, true>), grid, dim3(kScanBlock), 0, s, a);
-      else
-        hipLaunchKernelGGL((sru_scan_kernel<true, false>), grid, dim3(kScanBlock), 0, s, a);
-    } else {
-      const dim3 grid((unsigned)(((int64_t)B * ((N + 3) / 4) + kScanBlock - 1) / kScanBlock));
-      if (fast)
-        hipLaunchKernelGGL((sru_scan_kernel<false, true>), grid, dim3(kScanBlock), 0, s, a);
-      else
-        hipLaunchKernelGGL((sru_scan_kernel<false, false>), grid, dim3(kScanBlock), 0, s, a);
-    }
+                      31 - q.ev[1] >= 32 && 31 - q.eh >= 18 && (G == 4 || 31 - q.es >= 11) && m->sig_inner;
+    // the large table where the workgroups fill the chip and the steps pay for loading it (1 us; a step gains 0.1 to 0.3)
+    const bool full = fast && (int64_t)B * N >= (int64_t)256 * kScanBlockFull * 2 && T >= 8;
+    const int block = full ? kScanBlockFull : kScanBlock;
+    const size_t lds = (size_t)(full ? kSigFull : kSigEntries) * 2;
+    const int64_t threads = ws_gemm ? (int64_t)a.bp_blocks * ((N + 7) / 8) * 64 : (int64_t)B * ((N + 3) / 4);
+    hipLaunchKernelGGL(pick_scan(ws_gemm, fast, full), dim3((unsigned)((threads + block - 1) / block)), dim3(block), lds, s, a);
     timed_end();
     in = out;
     ld_in = d.Kp;
