@@ -48,6 +48,35 @@ int hm_ln_row_is_narrow(const int16_t *q, int32_t n) {
   }
   return ln_row_is_narrow(ln_row2(s1, s2, n, 1.0 / (double)n)) ? 1 : 0;
 }
+// the pieces of ln_row2 from estimates that are off by the given relative errors
+int64_t hm_ln_sigma(int64_t var, double rsq_error) {
+  LnEstimates est;
+  est.rsq_error = rsq_error;
+  return (int64_t)ln_sigma_f64((double)var, est);
+}
+double hm_ln_reciprocal(int64_t r, double rcp_error) {
+  LnEstimates est;
+  est.rcp_error = rcp_error;
+  return ln_reciprocal_f64((double)r, est);
+}
+// hm_layernorm2 from such estimates
+void hm_layernorm2_estimates(const int16_t *q, int32_t n, const int16_t *qL, const int32_t *qb, int32_t M, int32_t r,
+                             double rsq_error, double rcp_error, int16_t *out) {
+  int64_t s1 = 0, s2 = 0;
+  for (int i = 0; i < n; ++i) {
+    s1 += q[i];
+    s2 += (int64_t)q[i] * q[i];
+  }
+  LnEstimates est;
+  est.rsq_error = rsq_error;
+  est.rcp_error = rcp_error;
+  const LnRow2 row = ln_row2(s1, s2, n, 1.0 / (double)n, est);
+  const RescaleHi p = rescale_hi_prepare(M, r);
+  for (int i = 0; i < n; ++i)
+    out[i] = ln_row_is_narrow(row)
+                 ? (int16_t)rescale_sat16_pre(ln_second_stage_narrow(q[i], row, ln_weight_scaled(qL[i]), ln_bias_scaled(qb[i])), p)
+                 : (int16_t)ln_apply2(q[i], row, ln_weight_scaled(qL[i]), ln_bias_scaled(qb[i]), p);
+}
 int32_t hm_rescale_sat16_pre(int32_t a, int32_t M, int32_t r) {
   return rescale_sat16_pre(a, rescale_hi_prepare(M, r));
 }

@@ -203,38 +203,48 @@ struct LnRow2 {
 //     remainder settles it as in isqrt_u52;
 //   1 / sigma: any reciprocal good to 2^-45 leaves the quotient estimate of ln_second_stage inside its margin (2^37 2^-45
 //     = 2^-8 against 1/2, in units of 1 / sigma).
-// On the device the square root and the reciprocal start from the hardware's estimates (2^-23), with one and two steps of
-// Newton's iteration (2^-45, 2^-53).
+// The square root and the reciprocal start from estimates -- the hardware's, whose relative error is below 2^-23 -- and take
+// one and two steps of Newton's iteration (2^-45, 2^-53).  The host has no such instruction: it rounds a result and spoils it
+// by as much as the hardware may, so that the same steps run in both builds (tests/test_hostmath.py spoils it by twice that).
+struct LnEstimates {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __device__ __forceinline__ double rsq(double v) const { return __builtin_amdgcn_rsq(v); }
+  __device__ __forceinline__ double rcp(double v) const { return __builtin_amdgcn_rcp(v); }
+#else
+  double rsq_error = 1.0 / 8388608, rcp_error = -1.0 / 8388608;
+  double rsq(double v) const { return (1.0 / sqrt(v)) * (1.0 + rsq_error); }
+  double rcp(double v) const { return (1.0 / v) * (1.0 + rcp_error); }
+#endif
+};
 LSTM_HD double floor_div_f64(double num, double d, double inv_d) {
   const double q = floor(num * inv_d);
   const double rem = fma(-q, d, num);
   return rem < 0.0 ? q - 1.0 : (rem >= d ? q + 1.0 : q);
 }
-LSTM_HD LnRow2 ln_row2(int64_t S1, int64_t S2, int32_t n, double inv_n) {
+// floor(sqrt(var)) of an integer 0 <= var < 2^50
+LSTM_HD double ln_sigma_f64(double var, const LnEstimates &est) {
+  const double y = est.rsq(var > 0.0 ? var : 1.0);
+  double r = var * y;
+  r = floor(fma(0.5 * y, fma(-r, r, var), r));
+  const double rem = fma(-r, r, var);
+  return rem < 0.0 ? r - 1.0 : (rem >= 2.0 * r + 1.0 ? r + 1.0 : r);
+}
+// 1 / r, 0 for r = 0
+LSTM_HD double ln_reciprocal_f64(double r, const LnEstimates &est) {
+  const double d = r > 0.0 ? r : 1.0;
+  double inv = est.rcp(d);
+  inv = fma(inv, fma(-d, inv, 1.0), inv);
+  inv = fma(inv, fma(-d, inv, 1.0), inv);
+  return r > 0.0 ? inv : 0.0;
+}
+LSTM_HD LnRow2 ln_row2(int64_t S1, int64_t S2, int32_t n, double inv_n, const LnEstimates &est = LnEstimates()) {
   const double dn = (double)n, half = (double)(n >> 1), s2 = (double)S2;
   const double mean = floor_div_f64((double)S1 * 1024.0 + half, dn, inv_n);
   const double q = floor_div_f64(s2, dn, inv_n);
   const double low = floor_div_f64(fma(fma(-q, dn, s2), 1048576.0, half), dn, inv_n);
   double var = fma(q, 1048576.0, low) - mean * mean;  // every term an integer of at most 2^50
   var = var > 0.0 ? var : 0.0;
-#if defined(__HIP_DEVICE_COMPILE__)
-  const double y = __builtin_amdgcn_rsq(var > 0.0 ? var : 1.0);
-  double r = var * y;
-  r = floor(fma(0.5 * y, fma(-r, r, var), r));
-#else
-  double r = floor(sqrt(var));
-#endif
-  const double rem = fma(-r, r, var);
-  r = rem < 0.0 ? r - 1.0 : (rem >= 2.0 * r + 1.0 ? r + 1.0 : r);
-#if defined(__HIP_DEVICE_COMPILE__)
-  const double d = r > 0.0 ? r : 1.0;
-  double inv = __builtin_amdgcn_rcp(d);
-  inv = fma(inv, fma(-d, inv, 1.0), inv);
-  inv = fma(inv, fma(-d, inv, 1.0), inv);
-  inv = r > 0.0 ? inv : 0.0;
-#else
-  const double inv = r > 0.0 ? 1.0 / r : 0.0;
-#endif
+  const double r = ln_sigma_f64(var, est), inv = ln_reciprocal_f64(r, est);
   LnRow2 o;
   o.a = 1048576.0 * inv;
   o.b = (fma(mean, -1024.0, floor(r * 0.5)) + 0.5) * inv;

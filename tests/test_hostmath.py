@@ -3,6 +3,7 @@ tables of prepare.cpp), compiled for the host, against the oracle: the same
 integers on exhaustive or adversarial ranges.  (The device build of the same
 header is covered by the GPU parity tests.)"""
 import ctypes as C
+import math
 import os
 import random
 
@@ -162,6 +163,44 @@ def test_layernorm_matches_oracle(orc, hm):
             hm.hm_layernorm2(q.ctypes.data, n, qL.ctypes.data, qb.ctypes.data, M, 31 - e, got2.ctypes.data)
             assert (got2 == want).all(), (trial, n, kind)
     assert forms[0] > 100 and forms[1] > 100, forms
+
+
+# What the hardware's estimates of 1 / sqrt and 1 / x may be off by is 2^-23 (relative); the tests allow twice that.
+ESTIMATE_ERRORS = (0.0, 2.0**-23, -(2.0**-23), 2.0**-22, -(2.0**-22))
+
+
+def test_row_statistics_from_rough_estimates(hm):
+    """sigma and 1 / sigma of a row as the device computes them, from estimates and Newton steps: sigma exact around
+    every kind of square up to 2^50, the reciprocal good to 2^-50 (the layer norm needs 2^-45)."""
+    hm.hm_ln_sigma.restype, hm.hm_ln_sigma.argtypes = C.c_int64, [C.c_int64, C.c_double]
+    hm.hm_ln_reciprocal.restype, hm.hm_ln_reciprocal.argtypes = C.c_double, [C.c_int64, C.c_double]
+    rnd = random.Random(12)
+    roots = list(range(1, 300)) + [2**k + d for k in range(9, 25) for d in (-1, 0, 1)] + [2**25 - 1]
+    roots += [rnd.randrange(1, 2**rnd.randrange(1, 26)) for _ in range(4000)]
+    for e in ESTIMATE_ERRORS:
+        assert hm.hm_ln_sigma(0, e) == 0 and hm.hm_ln_reciprocal(0, e) == 0.0
+        for k in roots:
+            for var in (k * k - 1, k * k, k * k + 1, k * k + 2 * k):
+                if var < 2**50:
+                    assert hm.hm_ln_sigma(var, e) == math.isqrt(var), (var, e)
+            assert abs(hm.hm_ln_reciprocal(k, e) * k - 1.0) <= 2.0**-50, (k, e)
+    # and these errors are what the steps can take, not far less: at 2^-10 the root comes out wrong
+    assert any(hm.hm_ln_sigma(k * k, 2.0**-10) != k for k in roots)
+
+
+@pytest.mark.parametrize("rsq_error", ESTIMATE_ERRORS)
+@pytest.mark.parametrize("rcp_error", ESTIMATE_ERRORS)
+def test_layernorm_from_rough_estimates_matches_oracle(orc, hm, rsq_error, rcp_error):
+    hm.hm_layernorm2_estimates.argtypes = [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_int32, C.c_int32, C.c_double,
+                                           C.c_double, C.c_void_p]
+    rng = np.random.default_rng(6)
+    for trial in range(60):
+        n = int(rng.choice([1, 2, 3, 17, 64, 512, 1000, 2048, 4096]))
+        q, qL, qb = _ln_case(rng, n, ["normal", "extreme", "spike", "near_constant", "constant", "threshold"][trial % 6])
+        M, e = int(rng.integers(2**30, 2**31)), int(rng.integers(-24, 4))
+        got = np.zeros(n, np.int16)
+        hm.hm_layernorm2_estimates(q.ctypes.data, n, qL.ctypes.data, qb.ctypes.data, M, 31 - e, rsq_error, rcp_error, got.ctypes.data)
+        assert (got == orc.int_layernorm(q, qL, qb, M, e)).all(), (trial, n)
 
 
 def test_rescale_sat16_from_high_word(orc, hm):
