@@ -721,11 +721,16 @@ int sru_int_forward(const sru_int_model *m, const int8_t *x, int32_t T, int32_t 
     // the specialization that drops the checks the host can make once (see sru_scan_kernel)
     const bool fast = !tr && (N & 3) == 0 && (reinterpret_cast<uintptr_t>(y) & 3) == 0 && 31 - q.ev[0] >= 32 &&
                       31 - q.ev[1] >= 32 && 31 - q.eh >= 18 && (G == 4 || 31 - q.es >= 11) && m->sig_inner;
-    // the large table where the workgroups fill the chip and the steps pay for loading it (1 us; a step gains 0.1 to 0.3)
-    const bool full = fast && (int64_t)B * N >= (int64_t)256 * kScanBlockFull * 2 && T >= 8;
+    const int64_t threads = ws_gemm ? (int64_t)a.bp_blocks * ((N + 7) / 8) * 64 : (int64_t)B * ((N + 3) / 4);
+    // The table of all values makes a step's instructions fewer, but a workgroup twice as large: as long as the other form's
+    // workgroups have a compute unit each, half of the chip would idle.  Two layers, 64 steps, the other form -> this one,
+    // us:   256 of the other form's workgroups (1024 cells x 256 rows) 203 -> 293,  (2048 x 128) 274 -> 313
+    //       288 (1024 x 288) 303 -> 307,  (2048 x 144) 356 -> 354         320 (1024 x 320) 321 -> 322,  (2048 x 160) 372 -> 365
+    //       384 (2048 x 192) 438 -> 425   512 (2048 x 256) 524 -> 517
+    // From 320 on, then, and where the steps pay for loading it: 8 steps of 2048 x 256 32.4 -> 31.4.
+    const bool full = fast && threads >= (int64_t)320 * kScanBlock && T >= 8;
     const int block = full ? kScanBlockFull : kScanBlock;
     const size_t lds = (size_t)(full ? kSigFull : kSigEntries) * 2;
-    const int64_t threads = ws_gemm ? (int64_t)a.bp_blocks * ((N + 7) / 8) * 64 : (int64_t)B * ((N + 3) / 4);
     hipLaunchKernelGGL(pick_scan(ws_gemm, fast, full), dim3((unsigned)((threads + block - 1) / block)), dim3(block), lds, s, a);
     timed_end();
     in = out;

@@ -1,5 +1,5 @@
 """The SRU scan with the table of all sigma values (large batches, eight steps and more): the smallest call that takes it,
-the largest that does not, and a ragged one."""
+the largest ones that do not, and a ragged one."""
 import pytest
 
 import lstm_workloads as wl
@@ -9,6 +9,10 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("inputs,N,B,T", [
+    ([64], 1024, 320, 8),  # 320 workgroups of the other form
+    ([64], 1024, 320, 7),  # too few steps
+    ([64], 1024, 288, 8),  # too few workgroups
+    ([64, 1028], 1028, 330, 9),  # tile order, then row-major
     ([64], 1024, 256, 8),
     ([64], 1024, 256, 7),
     ([64, 1028], 1028, 257, 9),
