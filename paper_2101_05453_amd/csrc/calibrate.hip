@@ -22,8 +22,11 @@
 #include <vector>
 
 #include "../../include/lstm_int.h"
+#include "calibrate_plan.h"
 
 namespace {
+
+using namespace lstm_int;
 
 constexpr int kCifg = LSTM_INT_CIFG, kPeephole = LSTM_INT_PEEPHOLE, kLayerNorm = LSTM_INT_LAYER_NORM,
               kProjection = LSTM_INT_PROJECTION;
@@ -502,8 +505,11 @@ void launch_gemm(hipStream_t s, const double *A, int lda, const float *W, double
                  int64_t ldcin, const float *bias, int M, int Nout, int K) {
   const int chunks = (K + 15) / 16;
   auto go = [&](auto kernel, int mb, int nb, int waves, size_t lds) {
-    hipLaunchKernelGGL(kernel, dim3((Nout + nb - 1) / nb, (M + mb - 1) / mb), dim3(64 * waves), lds, s, A, lda, W, chunks, C,
-                       ldc, Cin, ldcin, bias, M, Nout);
+    const int64_t per = calibrate_rows_per_launch(mb);
+    for (int64_t m = 0; m < M; m += per)
+      hipLaunchKernelGGL(kernel, dim3((Nout + nb - 1) / nb, (unsigned)((std::min<int64_t>(per, M - m) + mb - 1) / mb)),
+                         dim3(64 * waves), lds, s, A + m * lda, lda, W, chunks, C + m * ldc, ldc, Cin ? Cin + m * ldcin : nullptr,
+                         ldcin, bias, (int)std::min<int64_t>(per, M - m), Nout);
   };
   if ((int64_t)((M + 127) / 128) * ((Nout + 127) / 128) >= 128)
     go(gemm_kernel<4, 4, 2, 2, 1, 1, true>, 128, 128, 4, 0);
@@ -515,7 +521,7 @@ void launch_gemm(hipStream_t s, const double *A, int lda, const float *W, double
     go(gemm_kernel<1, 2, 1, 1, 4, 5, true>, 16, 32, 4, 4 * 8 * 64 * 8);
 }
 
-void launch_cell(hipStream_t s, const CellArgs &a, int B) {
+void launch_cell_rows(hipStream_t s, const CellArgs &a, int B) {
   // slices: up to the 256 compute units, at least 128 cells each
   const bool whole_row = (a.flags & kPeephole) && (a.flags & kLayerNorm);
   const int slices = whole_row ? 1 : std::max(1, std::min(256 / B, (a.N + 127) / 128));
@@ -530,6 +536,16 @@ void launch_cell(hipStream_t s, const CellArgs &a, int B) {
     hipLaunchKernelGGL(cell_row_kernel<8>, grid, block, 0, s, a);
   else
     hipLaunchKernelGGL(cell_kernel, dim3(B), dim3(256), 0, s, a);
+}
+void launch_cell(hipStream_t s, const CellArgs &a, int B) {
+  CellArgs part = a;
+  for (int b = 0; b < B; b += kCalibrateCellRows) {
+    const int rows = std::min(B - b, kCalibrateCellRows);
+    launch_cell_rows(s, part, rows);
+    part.pre += (size_t)rows * 4 * a.N;
+    part.c += (size_t)rows * a.N;
+    part.m += (size_t)rows * a.ld_m;
+  }
 }
 
 }  // namespace

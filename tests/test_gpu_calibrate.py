@@ -103,3 +103,28 @@ def test_argument_errors():
     layers[0].W[1] = None  # a missing gate matrix
     with pytest.raises(binding.LstmIntError):
         binding.calibrate(layers, xd)
+
+
+def test_more_rows_than_one_launch_takes():
+    """2 steps of 4194305 batch rows: one row more than a launch of the cell kernel takes, and T B = 8388610 rows of the
+    hoisted product, which are more than 65535 blocks of 128.  One cell, so that the reference is elementwise."""
+    import torch
+    from paper_2101_05453_amd import binding
+
+    T, B = 2, (1 << 22) + 1
+    layers, _ = wl.make_custom([1], 1, 1, 0, 1, 1, seed=4, weight_param=0.5)
+    p = layers[0]
+    x = torch.randn((T, B, 1), generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
+    st, y = binding.calibrate(layers, x, want_output=True, apply=False)
+    h = c = torch.zeros(B, dtype=torch.float64, device="cuda")
+    want, cabs = [], 0.0
+    for t in range(T):
+        i, f, z, o = (float(p.W[g][0, 0]) * x[t, :, 0].double() + float(p.R[g][0, 0]) * h + float(p.b[g][0]) for g in range(4))
+        c = torch.sigmoid(i) * torch.tanh(z) + torch.sigmoid(f) * c
+        h = torch.sigmoid(o) * torch.tanh(c)
+        want.append(h)
+        cabs = max(cabs, float(c.abs().max()))
+    want = torch.stack(want)
+    assert float((y[:, :, 0] - want).abs().max()) <= RTOL
+    _close([st[0][k] for k in ("x_min", "x_max", "h_min", "h_max", "c_absmax")],
+           [float(x.min()), float(x.max()), float(want.min()), float(want.max()), cabs])
