@@ -19,6 +19,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <new>
 #include <vector>
 
 #include "../../include/lstm_int.h"
@@ -124,7 +125,7 @@ __global__ __launch_bounds__(256) void range_kernel(const double *v, int64_t row
 typedef double v4d __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-inline int64_t up16(int64_t v) { return (v + 15) / 16 * 16; }
+inline int64_t up16(int64_t v) { return calibrate_up16(v); }
 
 // Weights [rows][K] (dense, as the caller has them) -> MFMA order [rows / 16][K / 16][64 lanes][4], zero beyond the
 // real extents: lane (r, q) = r + 16 q of chunk c holds W[16 tile + r][16 c + 4 q + 0..3].  A wave's load of one chunk
@@ -548,11 +549,8 @@ void launch_cell(hipStream_t s, const CellArgs &a, int B) {
   }
 }
 
-}  // namespace
-
-extern "C" int lstm_int_calibrate(const lstm_int_layer_params *layers, int32_t num_layers, int32_t device,
-                                  const float *x, int32_t T, int32_t B, void *hip_stream,
-                                  lstm_int_layer_stats *stats_out, double *y_float) {
+int calibrate(const lstm_int_layer_params *layers, int32_t num_layers, int32_t device, const float *x, int32_t T, int32_t B,
+              void *hip_stream, lstm_int_layer_stats *stats_out, double *y_float) {
   if (!layers || num_layers < 1 || device < 0 || !x || T < 1 || B < 1 || !stats_out) return LSTM_INT_E_INVALID_ARG;
   for (int l = 0; l < num_layers; ++l) {
     const lstm_int_layer_params &p = layers[l];
@@ -573,41 +571,13 @@ extern "C" int lstm_int_calibrate(const lstm_int_layer_params *layers, int32_t n
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   const int64_t TB = (int64_t)T * B;
 
-
-  // One allocation for the whole call (each one costs about 0.1 ms to make and 0.3 ms to give back): the extents of
-  // every region are the largest over the layers.  Activation rows have a multiple of 16 doubles, zero beyond the
-  // real columns.
-  size_t total = 0;
-  auto take = [&](size_t bytes) {
-    const size_t o = total;
-    total += (bytes + 255) & ~(size_t)255;
-    return o;
-  };
-  size_t raw_f = 0, wop_f = 0, rop_f = 0, pop_f = 0, vec_f = 0, wx_d = 0, act_d = 0, m_d = 0, c_d = 0, pre_d = 0, h_d = 0;
-  for (int l = 0; l < num_layers; ++l) {
-    const size_t I = layers[l].input_size, N = layers[l].num_cells, H = layers[l].output_size;
-    const bool proj = layers[l].flags & kProjection;
-    raw_f = std::max(raw_f, 4 * N * (I + H) + (proj ? H * N : 0));
-    wop_f = std::max<size_t>(wop_f, up16(4 * N) * up16(I));
-    rop_f = std::max<size_t>(rop_f, up16(4 * N) * up16(H));
-    if (proj) pop_f = std::max<size_t>(pop_f, up16(H) * up16(N));
-    vec_f = std::max(vec_f, 11 * N + H);
-    wx_d = std::max(wx_d, (size_t)TB * 4 * N);
-    act_d = std::max<size_t>(act_d, TB * std::max(up16(I), up16(H)));
-    m_d = std::max<size_t>(m_d, B * up16(N));
-    h_d = std::max<size_t>(h_d, B * up16(H));
-    c_d = std::max<size_t>(c_d, (size_t)B * N);
-    pre_d = std::max<size_t>(pre_d, (size_t)B * 4 * N);
-  }
-  const size_t o_stats = take(sizeof(double) * S_COUNT * num_layers), o_raw = take(4 * raw_f), o_wop = take(4 * wop_f),
-               o_rop = take(4 * rop_f), o_pop = take(4 * pop_f), o_vec0 = take(4 * vec_f), o_vec1 = take(4 * vec_f),
-               o_wx = take(8 * wx_d), o_act0 = take(8 * act_d), o_act1 = take(8 * act_d), o_m = take(8 * m_d),
-               o_h0 = take(8 * h_d), o_c = take(8 * c_d), o_pre = take(8 * pre_d);
+  // One allocation for the whole call: each one costs about 0.1 ms to make and 0.3 ms to give back.
+  const CalibratePlan plan = calibrate_plan(layers, num_layers, T, B, sizeof(double) * S_COUNT);
   std::vector<std::vector<float>> vectors(num_layers);  // outlives the copies: declared ahead of what waits for them
   std::vector<double> init((size_t)S_COUNT * num_layers, 0.0);
   Held held;
   held.s = s;
-  if (hipMalloc(reinterpret_cast<void **>(&held.arena), total) != hipSuccess) {
+  if (hipMalloc(reinterpret_cast<void **>(&held.arena), plan.total) != hipSuccess) {
     held.arena = nullptr;
     return LSTM_INT_E_OUT_OF_MEMORY;
   }
@@ -615,9 +585,9 @@ extern "C" int lstm_int_calibrate(const lstm_int_layer_params *layers, int32_t n
       hipEventCreateWithFlags(&held.uploaded, hipEventDisableTiming) != hipSuccess ||
       hipEventCreateWithFlags(&held.repacked, hipEventDisableTiming) != hipSuccess)
     return LSTM_INT_E_DEVICE;
-  auto dbl = [&](size_t o) { return reinterpret_cast<double *>(held.arena + o); };
-  auto flt = [&](size_t o) { return reinterpret_cast<float *>(held.arena + o); };
-  double *const stats = dbl(o_stats);
+  auto dbl = [&](const CalibrateRegion &r) { return reinterpret_cast<double *>(held.arena + r.off); };
+  auto flt = [&](const CalibrateRegion &r) { return reinterpret_cast<float *>(held.arena + r.off); };
+  double *const stats = dbl(plan.stats);
   for (int l = 0; l < num_layers; ++l) {
     double *st = init.data() + (size_t)l * S_COUNT;
     st[S_XMIN] = st[S_HMIN] = st[S_MMIN] = INFINITY;
@@ -626,7 +596,7 @@ extern "C" int lstm_int_calibrate(const lstm_int_layer_params *layers, int32_t n
   if (hipMemcpyAsync(stats, init.data(), init.size() * sizeof(double), hipMemcpyHostToDevice, s) != hipSuccess)
     return LSTM_INT_E_DEVICE;
   const int blocks = 256;  // of the range kernels: each ends with two compare-and-swap loops on the same words
-  double *cur = dbl(o_act0), *next = dbl(o_act1);
+  double *cur = dbl(plan.act[0]), *next = dbl(plan.act[1]);
   hipLaunchKernelGGL(widen_kernel, dim3(blocks), dim3(256), 0, s, x, cur, TB, layers[0].input_size,
                      (int)up16(layers[0].input_size), stats);
 
@@ -640,7 +610,7 @@ extern "C" int lstm_int_calibrate(const lstm_int_layer_params *layers, int32_t n
     auto up = [&](void *dst, const void *src, size_t bytes) {
       ok = ok && hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, held.copy) == hipSuccess;
     };
-    float *raw = flt(o_raw);
+    float *raw = flt(plan.raw);
     for (size_t g = first; g < 4; ++g, raw += N * I) up(raw, p.W[g], sizeof(float) * N * I);
     for (size_t g = first; g < 4; ++g, raw += N * H) up(raw, p.R[g], sizeof(float) * N * H);
     if (p.flags & kProjection) up(raw, p.Wproj, sizeof(float) * H * N);
@@ -652,7 +622,7 @@ extern "C" int lstm_int_calibrate(const lstm_int_layer_params *layers, int32_t n
       if ((p.flags & kPeephole) && g < 3) std::copy(p.P[g], p.P[g] + N, hv.begin() + (4 + g) * N);
     }
     if ((p.flags & kProjection) && p.bproj) std::copy(p.bproj, p.bproj + H, hv.begin() + 11 * N);
-    up(flt(l & 1 ? o_vec1 : o_vec0), hv.data(), sizeof(float) * hv.size());
+    up(flt(plan.vec[l & 1]), hv.data(), sizeof(float) * hv.size());
     return ok && hipEventRecord(held.uploaded, held.copy) == hipSuccess;
   };
   auto repack = [&](const float *src, float *op, int rows, int K) {
@@ -664,29 +634,30 @@ extern "C" int lstm_int_calibrate(const lstm_int_layer_params *layers, int32_t n
   if (!upload(0)) return LSTM_INT_E_DEVICE;
   for (int l = 0; l < num_layers; ++l) {
     const lstm_int_layer_params &p = layers[l];
+    const CalibrateLayer &at = plan.layers[l];
     const int I = p.input_size, N = p.num_cells, H = p.output_size, first = (p.flags & kCifg) ? 1 : 0, G = 4 - first;
     const bool proj = p.flags & kProjection;
     const int Ip = (int)up16(I), Np = (int)up16(N), Hp = (int)up16(H);
     double *st = stats + (size_t)l * S_COUNT;
     bool ok = hipStreamWaitEvent(s, held.uploaded, 0) == hipSuccess;
-    const float *raw = flt(o_raw);
-    repack(raw, flt(o_wop), G * N, I);
-    repack(raw + (size_t)G * N * I, flt(o_rop), G * N, H);
-    if (proj) repack(raw + (size_t)G * N * (I + H), flt(o_pop), H, N);
+    const float *raw = flt(plan.raw);
+    repack(raw, flt(at.wop), G * N, I);
+    repack(raw + (size_t)G * N * I, flt(at.rop), G * N, H);
+    if (proj) repack(raw + (size_t)G * N * (I + H), flt(at.pop), H, N);
     ok = ok && hipEventRecord(held.repacked, s) == hipSuccess;
-    ok = ok && hipMemsetAsync(dbl(o_c), 0, sizeof(double) * (size_t)B * N, s) == hipSuccess;
-    ok = ok && hipMemsetAsync(dbl(o_h0), 0, sizeof(double) * (size_t)B * Hp, s) == hipSuccess;
-    if (proj && Np != N) ok = ok && hipMemsetAsync(dbl(o_m), 0, sizeof(double) * (size_t)B * Np, s) == hipSuccess;
+    ok = ok && hipMemsetAsync(dbl(at.c), 0, sizeof(double) * (size_t)B * N, s) == hipSuccess;
+    ok = ok && hipMemsetAsync(dbl(at.h0), 0, sizeof(double) * (size_t)B * Hp, s) == hipSuccess;
+    if (proj && Np != N) ok = ok && hipMemsetAsync(dbl(at.m), 0, sizeof(double) * (size_t)B * Np, s) == hipSuccess;
     if (Hp != H) ok = ok && hipMemsetAsync(next, 0, sizeof(double) * TB * Hp, s) == hipSuccess;
     if (!ok) return LSTM_INT_E_DEVICE;
 
-    const float *vb = flt(l & 1 ? o_vec1 : o_vec0);
-    double *wx = dbl(o_wx), *pre = dbl(o_pre);
+    const float *vb = flt(plan.vec[l & 1]);
+    double *wx = dbl(at.wx), *pre = dbl(at.pre);
     // W x for all steps (eqs. 1-4, first term), gates first..3 in one product
-    launch_gemm(s, cur, Ip, flt(o_wop), wx, G * (int64_t)N, nullptr, 0, nullptr, (int)TB, G * N, I);
+    launch_gemm(s, cur, Ip, flt(at.wop), wx, G * (int64_t)N, nullptr, 0, nullptr, (int)TB, G * N, I);
     CellArgs ca;
     ca.pre = pre;
-    ca.c = dbl(o_c);
+    ca.c = dbl(at.c);
     for (int g = 0; g < 4; ++g) {
       ca.b[g] = vb + (size_t)g * N;
       ca.Lw[g] = vb + (size_t)(7 + g) * N;
@@ -696,16 +667,16 @@ extern "C" int lstm_int_calibrate(const lstm_int_layer_params *layers, int32_t n
     ca.flags = (int)p.flags;
     ca.stats = st;
     for (int t = 0; t < T; ++t) {
-      const double *hp = t == 0 ? dbl(o_h0) : next + (size_t)(t - 1) * B * Hp;
+      const double *hp = t == 0 ? dbl(at.h0) : next + (size_t)(t - 1) * B * Hp;
       double *ho = next + (size_t)t * B * Hp;
       // + R h^{t-1}
-      launch_gemm(s, hp, Hp, flt(o_rop), pre + (size_t)first * N, 4 * (int64_t)N, wx + (size_t)t * B * G * N, G * (int64_t)N,
+      launch_gemm(s, hp, Hp, flt(at.rop), pre + (size_t)first * N, 4 * (int64_t)N, wx + (size_t)t * B * G * N, G * (int64_t)N,
                   nullptr, B, G * N, H);
-      ca.m = proj ? dbl(o_m) : ho;
+      ca.m = proj ? dbl(at.m) : ho;
       ca.ld_m = Np;  // without a projection N = H
       launch_cell(s, ca, B);
       if (proj)  // eq. (7)
-        launch_gemm(s, dbl(o_m), Np, flt(o_pop), ho, Hp, nullptr, 0, vb + (size_t)11 * N, B, H, N);
+        launch_gemm(s, dbl(at.m), Np, flt(at.pop), ho, Hp, nullptr, 0, vb + (size_t)11 * N, B, H, N);
     }
     hipLaunchKernelGGL(range_kernel, dim3(blocks), dim3(256), 0, s, next, TB, H, Hp, st + S_HMIN, st + S_HMAX);
     if (hipGetLastError() != hipSuccess) return LSTM_INT_E_DEVICE;
@@ -736,4 +707,16 @@ extern "C" int lstm_int_calibrate(const lstm_int_layer_params *layers, int32_t n
     for (int g = 0; g < 4; ++g) o.g_absmax[g] = st[S_GABS + g];
   }
   return LSTM_INT_OK;
+}
+
+}  // namespace
+
+extern "C" int lstm_int_calibrate(const lstm_int_layer_params *layers, int32_t num_layers, int32_t device,
+                                  const float *x, int32_t T, int32_t B, void *hip_stream,
+                                  lstm_int_layer_stats *stats_out, double *y_float) {
+  try {
+    return calibrate(layers, num_layers, device, x, T, B, hip_stream, stats_out, y_float);
+  } catch (const std::bad_alloc &) {
+    return LSTM_INT_E_OUT_OF_MEMORY;
+  }
 }

@@ -2,9 +2,75 @@
 // a CPU.
 #pragma once
 
+#include <stddef.h>
 #include <stdint.h>
 
+#include <algorithm>
+#include <vector>
+
+#include "../../include/lstm_int.h"
+
 namespace lstm_int {
+
+// Where a call keeps what, in one allocation.  Kept through the call: the statistics, the raw parameters and the vectors of
+// a layer (the next layer's are uploaded while this one computes), and the layer inputs and outputs, which change places
+// from layer to layer.  The rest belongs to one layer at a time, so the layers share the same bytes, each with a layout of
+// its own (the largest of every buffer over the layers at once would take more than any layer needs when they differ).  A
+// layer's parameters are there twice, as uploaded and in the order of the products.
+struct CalibrateRegion {
+  size_t off = 0, bytes = 0;
+};
+struct CalibrateLayer {
+  CalibrateRegion wop, rop, pop, wx, m, h0, c, pre;
+};
+struct CalibratePlan {
+  CalibrateRegion stats, raw, vec[2], act[2];
+  std::vector<CalibrateLayer> layers;
+  size_t total = 0;
+};
+
+inline int64_t calibrate_up16(int64_t v) { return (v + 15) / 16 * 16; }
+
+inline CalibratePlan calibrate_plan(const lstm_int_layer_params *layers, int num_layers, int64_t T, int64_t B,
+                                    size_t stats_bytes_per_layer) {
+  CalibratePlan p;
+  p.layers.resize(num_layers);
+  size_t off = 0;
+  auto place = [&](CalibrateRegion &r, size_t bytes) {
+    r.off = off;
+    r.bytes = bytes;
+    off += (bytes + 255) & ~(size_t)255;
+  };
+  auto up16 = [](size_t v) { return (size_t)calibrate_up16((int64_t)v); };
+  size_t raw = 0, vec = 0, act[2] = {(size_t)T * B * up16(layers[0].input_size), 0};
+  for (int l = 0; l < num_layers; ++l) {
+    const size_t I = layers[l].input_size, N = layers[l].num_cells, H = layers[l].output_size;
+    raw = std::max(raw, 4 * N * (I + H) + ((layers[l].flags & LSTM_INT_PROJECTION) ? H * N : 0));
+    vec = std::max(vec, 11 * N + H);
+    act[(l + 1) & 1] = std::max(act[(l + 1) & 1], (size_t)T * B * up16(H));  // layer l writes what layer l + 1 reads
+  }
+  place(p.stats, stats_bytes_per_layer * num_layers);
+  place(p.raw, sizeof(float) * raw);
+  for (CalibrateRegion &r : p.vec) place(r, sizeof(float) * vec);
+  for (int i = 0; i < 2; ++i) place(p.act[i], sizeof(double) * act[i]);
+  const size_t shared = off;
+  p.total = off;
+  for (int l = 0; l < num_layers; ++l) {
+    const size_t I = layers[l].input_size, N = layers[l].num_cells, H = layers[l].output_size;
+    CalibrateLayer &r = p.layers[l];
+    off = shared;
+    place(r.wop, sizeof(float) * up16(4 * N) * up16(I));
+    place(r.rop, sizeof(float) * up16(4 * N) * up16(H));
+    if (layers[l].flags & LSTM_INT_PROJECTION) place(r.pop, sizeof(float) * up16(H) * up16(N));
+    place(r.wx, sizeof(double) * T * B * 4 * N);
+    place(r.m, sizeof(double) * B * up16(N));
+    place(r.h0, sizeof(double) * B * up16(H));
+    place(r.c, sizeof(double) * B * N);
+    place(r.pre, sizeof(double) * B * 4 * N);
+    p.total = std::max(p.total, off);
+  }
+  return p;
+}
 
 // Rows that one launch of a product takes when a workgroup takes `block` of them: the row blocks are grid.y, which holds
 // 65535.

@@ -1,6 +1,7 @@
 // Host-only C entry points onto lstm_int_math.h, so that the arithmetic the
 // kernels run can be checked exhaustively on a CPU.  Not part of
 // liblstm_int.so.
+#include "calibrate_plan.h"
 #include "lstm_int_math.h"
 #include "model.h"
 
@@ -105,6 +106,20 @@ int32_t hm_cell_update(int32_t i, int32_t z, int32_t f, int32_t c, int32_t m_c) 
 }
 int32_t hm_hidden(int32_t o, int32_t tc, int32_t M, int32_t r, int32_t zp) {
   return hidden_state(o, tc, M, r, zp);
+}
+
+// The statistics run's buffers: out[0] = bytes of the allocation, then (offset, bytes)
+// of stats, raw, vec[2], act[2] and, per layer, of wop, rop, pop, wx, m, h0, c, pre.
+void hm_calibrate_plan(const lstm_int_layer_params *layers, int32_t num_layers, int32_t T, int32_t B, int64_t *out) {
+  const CalibratePlan p = calibrate_plan(layers, num_layers, T, B, 88);
+  *out++ = (int64_t)p.total;
+  auto put = [&](const CalibrateRegion &r) {
+    *out++ = (int64_t)r.off;
+    *out++ = (int64_t)r.bytes;
+  };
+  for (const CalibrateRegion *r : {&p.stats, &p.raw, &p.vec[0], &p.vec[1], &p.act[0], &p.act[1]}) put(*r);
+  for (const CalibrateLayer &l : p.layers)
+    for (const CalibrateRegion *r : {&l.wop, &l.rop, &l.pop, &l.wx, &l.m, &l.h0, &l.c, &l.pre}) put(*r);
 }
 
 // The library's offline phase on the host (what lstm_int_prepare runs before the upload); *checksum

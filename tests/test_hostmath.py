@@ -245,6 +245,41 @@ def test_cell_update_and_hidden(orc, hm):
         assert hm.hm_cifg(f) == min(32768 - f, 32767)
 
 
+def test_statistics_run_of_unlike_layers_needs_no_more_than_its_layers(hm):
+    """Layers of unlike sizes share the bytes that only one of them uses at a time: a layer with wide input products after
+    one with large weights takes what the larger of the two takes, not the largest of every buffer; and no two buffers in
+    use at once overlap."""
+    from types import SimpleNamespace
+
+    from paper_2101_05453_amd import binding
+
+    def layer(I, N, H, flags):
+        z = lambda *s: np.zeros(s, np.float32)  # noqa: E731
+        return SimpleNamespace(input_size=I, num_cells=N, output_size=H, flags=flags, W=[z(N, I)] * 4, R=[z(N, H)] * 4,
+                               b=[z(N)] * 4, P=[z(N)] * 3, Lw=[z(N)] * 4, Wproj=z(H, N), bproj=z(H), x_min=0.0, x_max=0.0,
+                               h_min=0.0, h_max=0.0, m_min=0.0, m_max=0.0, c_absmax=0.0, g_absmax=[0.0] * 4)
+
+    def plan(layers, T, B):
+        arr, keep = binding.marshal_layers(layers)
+        out = np.zeros(1 + 2 * (6 + 8 * len(layers)), np.int64)
+        hm.hm_calibrate_plan(arr, len(layers), T, B, out.ctypes.data_as(C.c_void_p))
+        del keep
+        r = out[1:].reshape(-1, 2)
+        return int(out[0]), r[:6], r[6:].reshape(len(layers), 8, 2)
+
+    weights, rows = layer(1500, 1500, 40, 8), layer(40, 3000, 24, 8)  # 25 MB of parameters; 196 MB of W x terms
+    T, B = 64, 32
+    total, fixed, per = plan([weights, rows], T, B)
+    own = [int(sum((b + 255) // 256 * 256 for _, b in p)) for p in per]
+    assert total == int(sum((b + 255) // 256 * 256 for _, b in fixed)) + max(own)
+    assert per[0][0][1] == 4 * 6000 * 1504 and per[1][3][1] == 8 * T * B * 12000  # repacked W; W x terms
+    for p in per:
+        spans = sorted((int(o), int(o + b)) for o, b in np.concatenate([fixed, p]) if b)
+        assert all(a[1] <= b[0] for a, b in zip(spans, spans[1:])) and spans[-1][1] <= total
+    # the inputs and outputs of the layers change places: layer 0 reads act[0] and writes act[1]
+    assert fixed[4][1] == 8 * T * B * 1504 and fixed[5][1] == 8 * T * B * 48
+
+
 def test_sparse_operand_packing(hm):
     """The 2:4 compressed form of recurrent weight rows (sparse MFMA operands): unpacking every lane's
     values through its index bits, at the k positions the layout states, gives the row back; and the
