@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
     (wl.LAYER_NORM | wl.PROJECTION, [48, 24], 64, 24, 37, 6),
     (wl.CIFG | wl.LAYER_NORM | wl.PEEPHOLE, [64], 128, 128, 16, 9),
 ])
-def test_bidirectional_outputs_side_by_side(orc, case):
+def test_bidirectional_outputs_side_by_side(orc, case, rows16=1):
     import torch
     from paper_2101_05453_amd import binding
 
@@ -26,6 +26,8 @@ def test_bidirectional_outputs_side_by_side(orc, case):
     # the backward direction's statistics belong to the flipped sequence; the ranges of x are the same either way
     fwd, bwd = binding.prepare(lay_f, device=0), binding.prepare(lay_b, device=0)
     bwd.set_option("reverse", 1)
+    for model in (fwd, bwd):
+        model.set_option("rows16", rows16)
     of, ob = orc.prepare(lay_f), orc.prepare(lay_b)
     xq = fwd.quantize_input(xd)
     dims_f, dims_b = fwd.dims(), bwd.dims()
@@ -63,6 +65,16 @@ def test_bidirectional_outputs_side_by_side(orc, case):
 ])
 def test_both_directions_in_one_launch(orc, case):
     test_bidirectional_outputs_side_by_side(orc, case)
+
+
+@pytest.mark.parametrize("N", [130, 320, 650])  # the three k depths
+@pytest.mark.parametrize("variant", range(8))
+def test_both_directions_in_one_launch_of_the_16_row_kernel(orc, variant, N):
+    """Every instantiation of the 16-row kernel that runs two directions side by side (CIFG, peephole, layer norm), with
+    and without a projection, two groups per direction."""
+    proj = (variant + N) % 20 < 10
+    H = N - 5 if proj else N
+    test_bidirectional_outputs_side_by_side(orc, (variant | (wl.PROJECTION if proj else 0), [24], N, H, 21, 4), rows16=2)
 
 
 def test_bidirectional_argument_checks(orc):

@@ -38,15 +38,21 @@ def test_variants_every_tensor(orc, flags):
     run_and_compare(orc, layers, x, f"variant{flags}")
 
 
+@pytest.mark.parametrize("N,rows16", [
+    (200, 1),  # one workgroup per four rows: launched plainly whatever the option says
+    (200, 2),  # groups of 16 rows: 4 workgroups per group, 5 groups
+    (200, 0),  # groups of 32 rows: 3 groups
+    (320, 1),  # groups of four rows
+])
 @pytest.mark.parametrize("flags", [wl.LAYER_NORM | wl.PROJECTION, wl.CIFG | wl.LAYER_NORM | wl.PEEPHOLE])
-def test_cooperative_launch(orc, flags):
-    """Option "cooperative_launch": the persistent kernel launched through the
-    runtime's cooperative path (the default is a plain launch); 4 workgroups per
-    group, 3 groups, two layers."""
-    H = 136 if flags & wl.PROJECTION else 200
-    print(f"cooperative flags={flags}", flush=True)
-    layers, x = wl.make_custom([72, H], 200, H, flags, 70, 6, seed=flags + 31, weight_param=0.08)
-    run_and_compare(orc, layers, x, f"coop{flags}", trace=False, options={"cooperative_launch": 1})
+def test_cooperative_launch(orc, flags, N, rows16):
+    """Option "cooperative_launch": the persistent kernels launched through the
+    runtime's cooperative path (the default is a plain launch), two layers."""
+    H = 136 if flags & wl.PROJECTION else N
+    print(f"cooperative flags={flags} N={N} rows16={rows16}", flush=True)
+    layers, x = wl.make_custom([72, H], N, H, flags, 70, 6, seed=flags + 31, weight_param=0.08)
+    run_and_compare(orc, layers, x, f"coop{flags}", trace=False,
+                    options={"cooperative_launch": 1, "rows16": rows16, "stack": 0})
 
 
 @pytest.mark.parametrize("flags", [0, wl.LAYER_NORM | wl.PEEPHOLE | wl.PROJECTION, wl.CIFG | wl.LAYER_NORM])
@@ -121,14 +127,15 @@ def test_two_row_tiles_per_group(orc, case):
     assert prof["recurrent"]["launches"] == 1 and prof["cell"]["launches"] == 0, prof  # one launch: 64 rows per group
 
 
-@pytest.mark.parametrize("rows16", [1, 0])
+@pytest.mark.parametrize("rows16", [2, 1, 0])
 @pytest.mark.parametrize("flags", [wl.LAYER_NORM | wl.PROJECTION, wl.CIFG | wl.LAYER_NORM | wl.PEEPHOLE,
                                    wl.PEEPHOLE | wl.PROJECTION])
 def test_persistent_path_every_step_and_layer(orc, flags, rows16):
     """The persistent kernels dump no intermediate tensors, so their state is
     checked step by step instead: the sequence runs as one-step calls with h and c
     carried in the state buffers, and after every call the h and c of EVERY layer
-    are compared with the oracle's traces of that layer at that step."""
+    are compared with the oracle's traces of that layer at that step.  rows16 = 2:
+    groups of 16 rows, 1: one workgroup per four rows, 0: groups of 32 rows."""
     import torch
 
     print(f"every step and layer: flags={flags} rows16={rows16}", flush=True)
@@ -181,13 +188,14 @@ def test_benchmark_configs_take_the_persistent_path(name):
     assert model.device_status() == 0
 
 
-@pytest.mark.parametrize("rows16", [1, 0])
+@pytest.mark.parametrize("rows16", [2, 1, 0])
 def test_wait_gives_up_and_model_recovers(orc, rows16):
     """A barrier that cannot complete (option "barrier_never_completes": it waits for
     one arrival more than will come) and a small spin limit make the waits inside
     the persistent kernel give up: every workgroup leaves the kernel (no hang),
     the status word says so, and after a reset the same model computes the right
-    answer again.  On both kernels of the one-layer path."""
+    answer again.  On the three kernels of the one-layer path that wait: groups of
+    16 rows (rows16 = 2), of 4 (1) and of 32 (0)."""
     import torch
 
     print("bounded waits", flush=True)
@@ -390,17 +398,26 @@ def test_empty_and_error_paths(orc):
 @pytest.mark.parametrize("T,flags,with_state,rows16", [
     (1 << 14, wl.LAYER_NORM, True, 1), ((1 << 14) + 1, wl.LAYER_NORM, True, 1),
     ((1 << 14) + 1, wl.LAYER_NORM | wl.PROJECTION, False, 1),
+    (1 << 14, wl.LAYER_NORM, True, 2), ((1 << 14) + 1, wl.LAYER_NORM, True, 2),
+    ((1 << 14) + 1, wl.LAYER_NORM | wl.PROJECTION, False, 2),
     (1 << 14, wl.LAYER_NORM, True, 0), ((1 << 14) + 1, wl.LAYER_NORM | wl.PROJECTION, False, 0)])
 def test_longest_sequences(orc, T, flags, with_state, rows16):
-    """2^14 steps is the most one launch of the persistent kernel takes (its
-    layer-norm statistics words count up over the launch); one step more and
-    the layer runs in two pieces, h and c carried from one to the next (c through
-    the caller's state buffer, or through the workspace when there is none).  Two
-    workgroups per group, so the words are in use.  On the 16-row kernel and,
-    with option "rows16" off, on the kernel with groups of 32 rows."""
+    """2^14 steps is the most one launch takes (the layer-norm statistics words of
+    the kernels with groups of 16 or 32 rows count up over the launch); one step
+    more and the layer runs in two pieces, h and c carried from one to the next (c
+    through the caller's state buffer, or through the workspace when there is
+    none).  On one workgroup per four rows (rows16 = 1), and on groups of 16 (2)
+    and of 32 rows (0), of two workgroups, so the words are in use."""
     print(f"T {T} rows16 {rows16}", flush=True)
     layers, x = wl.make_custom([16], 128, 64, flags, 3, T, seed=21)
     run_and_compare(orc, layers, x, f"long{T}", trace=False, with_state=with_state, options={"rows16": rows16})
+
+
+@pytest.mark.parametrize("T,with_state", [(1 << 14, True), ((1 << 14) + 1, True), ((1 << 14) + 1, False)])
+def test_longest_sequences_in_groups_of_four_rows(orc, T, with_state):
+    """The same boundary on the kernel with groups of four rows, whose exchange words are cleared anew for each piece."""
+    layers, x = wl.make_custom([16], 257, 64, wl.LAYER_NORM | wl.PROJECTION, 2, T, seed=22)
+    run_and_compare(orc, layers, x, f"long4_{T}", trace=False, with_state=with_state)
 
 
 def test_maximum_sizes(orc):
@@ -412,6 +429,7 @@ def test_maximum_sizes(orc):
     run_and_compare(orc, layers, x, "depth32768", trace=True)
 
 
+@pytest.mark.parametrize("rows16", [2, 1])
 @pytest.mark.parametrize("case", [
     # (inputs, N, H, flags, B, T, rows)
     ([72, 200], 200, 200, wl.LAYER_NORM, 37, 6, None),                      # 4 workgroups x 3 groups, ragged rows
@@ -422,25 +440,26 @@ def test_maximum_sizes(orc):
     ([64], 1024, 1024, wl.LAYER_NORM, 48, 3, [0, 17, 47]),                  # k depth 16
     ([640, 640], 2048, 640, wl.LAYER_NORM | wl.PROJECTION, 120, 4, [0, 17, 50, 119]),  # the C4 layer, 8 groups of 32
 ])
-def test_rows16_kernel(orc, case):
-    """Option "rows16" (on by default): batches of up to 16 * 8 * (32 / workgroups
-    per group) rows take the recurrent kernel that works on groups of 16 rows."""
-    _rows16(orc, case, 1)
+def test_rows16_kernel(orc, case, rows16):
+    """Batches of up to 16 * 8 * (32 / workgroups per group) rows on the recurrent
+    kernel that works on groups of 16 rows (rows16 = 2), and on what the default
+    picks for them: fewer rows per group where those fit one launch."""
+    _rows16(orc, case, rows16)
 
 
-@pytest.mark.parametrize("rows16", [1, 0])
+@pytest.mark.parametrize("rows16", [2, 1, 0])
 @pytest.mark.parametrize("flags", VARIANTS)
 def test_rows16_variants(orc, flags, rows16):
     """Every variant on the persistent path at a small ragged batch, two layers:
-    on the 16-row kernel (default) and, with the option off, on the kernel
-    with groups of 32 rows."""
+    in groups of 16 rows (rows16 = 2), one workgroup per four rows (1) and in
+    groups of 32 rows (0)."""
     H = 136 if flags & wl.PROJECTION else 200
     _rows16(orc, ([72, H], 200, H, flags, 37, 5, None), rows16)
 
 
 def test_rows16_c3_layer(orc):
     """The C3 layer (peephole, layer norm, projection: two statistics rounds per
-    step) at B = 100 on the 16-row kernel."""
+    step) at B = 100 on the 16-row kernel (25 groups of four would not fit one launch)."""
     flags = wl.LAYER_NORM | wl.PEEPHOLE | wl.PROJECTION
     _rows16(orc, ([640], 2048, 640, flags, 100, 4, [0, 15, 16, 63, 99]), 1)
 
@@ -459,8 +478,12 @@ def _rows16(orc, case, rows16):
     assert prof["recurrent"]["launches"] == len(inputs) and prof["cell"]["launches"] == 0, prof
 
 
-@pytest.mark.parametrize("stack", [0, 2])
-def test_forward_captured_in_a_hip_graph(orc, stack):
+@pytest.mark.parametrize("stack,rows16,N", [
+    (0, 1, 200), (2, 1, 200),  # layer after layer on one workgroup per four rows; all layers in one launch
+    (0, 2, 200), (0, 0, 200),  # groups of 16, of 32 rows
+    (0, 1, 320),  # groups of four rows
+])
+def test_forward_captured_in_a_hip_graph(orc, stack, rows16, N):
     """forward allocates nothing, never synchronizes and launches only kernels, so
     a caller can capture it in a HIP graph: one-step calls with carried state,
     replayed with the program's own synchronization between the replays, give
@@ -468,11 +491,12 @@ def test_forward_captured_in_a_hip_graph(orc, stack):
     the whole sequence)."""
     import torch
 
-    print(f"graph capture stack={stack}", flush=True)
+    print(f"graph capture stack={stack} rows16={rows16} N={N}", flush=True)
     flags = wl.LAYER_NORM | wl.PROJECTION
-    layers, x = wl.make_custom([72, 136], 200, 136, flags, 20, 6, seed=77, weight_param=0.08)
+    layers, x = wl.make_custom([72, 136], N, 136, flags, 20, 6, seed=77, weight_param=0.08)
     lib_model, orc_model, xq = prepare_both(orc, layers, x)
-    lib_model.set_option("stack", stack)  # layer after layer, and all layers in one launch
+    lib_model.set_option("stack", stack)
+    lib_model.set_option("rows16", rows16)
     T, B, _ = xq.shape
     dims = lib_model.dims()
     want = orc.forward(orc_model, xq)
