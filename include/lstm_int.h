@@ -303,6 +303,11 @@ int lstm_int_forward_bidirectional(const lstm_int_model *fwd, const lstm_int_mod
  *           among the workgroups of a group waits for one arrival more than
  *           will come, so the waits give up after spin_limit polls (keep it
  *           small) and the outputs of the call are not valid.  Default 0.
+ *   "misplaced_workgroup": 1 = test hook for the placement check: a workgroup
+ *           too many has counted itself on every XCD before a plain launch of a
+ *           persistent kernel whose workgroups meet, so the status word becomes
+ *           nonzero (2, or 1 where a wait that saw the 2 gave up after it).
+ *           Default 0.
  *   "poll_sleep", "stats_sleep": pause between two polls of a group barrier /
  *           of the layer-norm statistics words inside the persistent kernel,
  *           in units of 64 clocks (0..1024; defaults 0 and 0).
@@ -350,6 +355,10 @@ int lstm_int_sparse_layers(const lstm_int_model *model, int32_t *count);
  * kernel so far ran to completion; nonzero = a wait gave up (1) or the
  * workgroups of a group were not placed on one XCD (2), and the outputs of
  * that call are not valid.  The word is sticky.  Synchronizes the device.
+ * Where lstm_int_forward_bidirectional runs both directions in one launch, a
+ * wait that gave up concerns the direction it belongs to, and only that model
+ * says so (rows never interact); a misplaced workgroup concerns both, and both
+ * models say so.
  */
 int lstm_int_device_status(const lstm_int_model *model, int32_t *status);
 

@@ -151,6 +151,7 @@ struct lstm_int_model {
   int sync_sleep = -1;  // pause before the first poll where all arrive together; -1 = by group size
   int phase_timing = 0;
   int extra_arrivals = 0;  // test hook: group barriers wait for one arrival too many (see RecArgs)
+  int misplaced = 0;       // test hook: the placement check of a launch finds a workgroup too many on every XCD
   int num_cus = 256;
   Profile prof;
 };
@@ -707,6 +708,13 @@ size_t lstm_int_workspace_bytes(const lstm_int_model *m, int32_t T, int32_t B) {
 
 namespace {
 
+// Test hook "misplaced_workgroup": on every XCD a workgroup has counted itself already.
+void plant_misplaced(const lstm_int_model *m, hipStream_t s, uint8_t *sync) {
+  if (!m->misplaced) return;
+  for (int xcd = 0; xcd < 8; ++xcd)  // the upper half of the XCD's placement word counts
+    launch_fill_i16(s, reinterpret_cast<int16_t *>(sync + 256 * xcd + 12), 1, 1);
+}
+
 // All layers in one launch (stack_kernel.inc.h).  The caller has checked stack_chosen and the workspace size.
 int forward_stack(lstm_int_model *m, const int8_t *x, int32_t T, int32_t B, int8_t *y, int8_t *h_state,
                   int16_t *c_state, uint8_t *wsb, hipStream_t s) {
@@ -816,6 +824,7 @@ int forward_stack(lstm_int_model *m, const int8_t *x, int32_t T, int32_t B, int8
     si.sync_vec = (long long)((flags_off + (size_t)L * sa.row_tiles * 128 + 15) / 16);
     launch_stack_init(s, si);
   }
+  plant_misplaced(m, s, wsb + sp.sync);
   {
     Timed t(m->prof, s, LSTM_INT_K_RECURRENT);
     if (launch_stack(s, sa, m->cooperative != 0) != hipSuccess) return LSTM_INT_E_DEVICE;
@@ -1153,6 +1162,7 @@ int lstm_int_forward(const lstm_int_model *cm, const int8_t *x, int32_t T, int32
             launch_fill_i16(s, reinterpret_cast<int16_t *>(wsb + ws.sync), sync_bytes(plan, ra.groups) / 2, 0);
           }
           if (!rec_extents_ok(ra, ws, T, t0, proj)) return LSTM_INT_E_WORKSPACE;
+          if (!plan.solo) plant_misplaced(m, s, wsb + ws.sync);
           Timed t(m->prof, s, LSTM_INT_K_RECURRENT);
           const bool coop = m->cooperative != 0;
           RecArgs2 one;
@@ -1395,6 +1405,7 @@ static int forward_pair(lstm_int_model *const (&m)[2], const int8_t *x, int32_t 
       in[i] = out;
       ld_in[i] = d.Hpad;
     }
+    if (!plan[0].solo) plant_misplaced(m[0], s, base[0] + ws[0].sync);
     Timed t0(m[0]->prof, s, LSTM_INT_K_RECURRENT), t1(m[1]->prof, s, LSTM_INT_K_RECURRENT);
     const bool coop = m[0]->cooperative != 0;
     if ((plan[0].solo ? launch_solo(s, pair) : plan[0].quad ? launch_quad(s, pair, coop) : launch_rec16_pair(s, pair, coop)) != hipSuccess)
@@ -1537,6 +1548,11 @@ int lstm_int_set_option(lstm_int_model *m, const char *key, int64_t value) {
   if (!strcmp(key, "barrier_never_completes")) {
     if (value < 0 || value > 1) return LSTM_INT_E_INVALID_ARG;
     m->extra_arrivals = (int)value;
+    return LSTM_INT_OK;
+  }
+  if (!strcmp(key, "misplaced_workgroup")) {
+    if (value < 0 || value > 1) return LSTM_INT_E_INVALID_ARG;
+    m->misplaced = (int)value;
     return LSTM_INT_OK;
   }
   if (!strcmp(key, "spin_limit")) {

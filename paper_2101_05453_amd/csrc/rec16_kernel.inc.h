@@ -52,11 +52,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const int wg = blockIdx.x;
   const int xcc = (int)(__builtin_amdgcn_s_getreg(20 | (0 << 6) | (3 << 11)) & 7);
   const int slot = wg >> 3;
+  // both layers of the launch depend on where its workgroups are
+  auto misplaced = [&]() {
+    __hip_atomic_store(a0.status, 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (PAIR) __hip_atomic_store(other_status<RecArgs2>(), 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
   int xcd = wg & 7;
   if (a0.tickets) {
     xcd = xcc;
   } else if (xcc != xcd && GS > 1 && tid == 0) {
-    __hip_atomic_store(a0.status, 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    misplaced();
   }
   auto placement_check = [&]() {
     if (a0.tickets && tid == 0) {
@@ -67,8 +72,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
           __hip_atomic_fetch_add(&a0.tickets[xcc_now * 32], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + mine;
       const unsigned count = (unsigned)(now >> 32);
       const unsigned all = places >= 32 ? 0xFFFFFFFFu : (1u << places) - 1;
-      if (count > places || (count == places && (unsigned)now != all))
-        __hip_atomic_store(a0.status, 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (count > places || (count == places && (unsigned)now != all)) misplaced();
     }
   };
   const int gl = xcd + 8 * (slot / GS), member = slot % GS;  // group of the launch

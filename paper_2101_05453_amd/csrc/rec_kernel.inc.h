@@ -61,6 +61,18 @@ __device__ __forceinline__ bool group_sync(unsigned *counter, unsigned &epoch, i
   return lds_flag[0] != 0;
 }
 
+// The status word of the second layer of a launch of two (RecArgs2, the kernel's only argument), NULL if there is none.
+// Read from the argument segment where it is needed, at the end of a launch: as a use of the argument it stayed in a pair of
+// scalar registers through the step loop, and the four-row kernel took 3.4 % longer (512 cells, layer norm, 16 rows).
+template <class Args>
+__device__ __forceinline__ int *other_status() {
+  typedef const __attribute__((address_space(4))) uint8_t *arg_ptr;
+  arg_ptr p = (arg_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(int *const __attribute__((address_space(4))) *)(p + offsetof(Args, d) + sizeof(((Args *)0)->d[0]) +
+                                                           offsetof(RecArgs, status));
+}
+
 // Per-layer constants, kept in LDS and read where they are used: as kernel
 // arguments they would all be live in scalar registers across the time loop.
 struct PrmLds {  // 256 bytes (kPrmLdsBytes in persistent.hip)

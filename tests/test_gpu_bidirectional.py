@@ -77,6 +77,44 @@ def test_both_directions_in_one_launch_of_the_16_row_kernel(orc, variant, N):
     test_bidirectional_outputs_side_by_side(orc, (variant | (wl.PROJECTION if proj else 0), [24], N, H, 21, 4), rows16=2)
 
 
+@pytest.mark.parametrize("rows16", [1, 2])  # groups of four rows, of 16
+def test_status_words_of_a_shared_launch(rows16):
+    """Both directions in one launch: a misplaced workgroup (test hook) is reported by both models, a wait that gave up by
+    the model of its direction alone, and the other direction's half of the output is right then."""
+    import torch
+    from paper_2101_05453_amd import binding
+
+    _, x = wl.make_custom([24], 300, 300, wl.LAYER_NORM, 20, 5, seed=31)
+    models = []
+    for seed in (31, 77):
+        layers, _ = wl.make_custom([24], 300, 300, wl.LAYER_NORM, 20, 5, seed=seed)
+        xd = calibrate_on_gpu(layers, x)
+        models.append(binding.prepare(layers, device=0))
+        models[-1].set_option("rows16", rows16)
+    fwd, bwd = models
+    bwd.set_option("reverse", 1)
+    xq = fwd.quantize_input(xd)
+    want = binding.forward_bidirectional(fwd, bwd, xq)
+    assert (fwd.device_status(), bwd.device_status()) == (0, 0)
+    fwd.set_option("misplaced_workgroup", 1)
+    binding.forward_bidirectional(fwd, bwd, xq)
+    # 1: a wait that saw the 2 and gave up
+    assert fwd.device_status() in (1, 2) and bwd.device_status() in (1, 2)
+    fwd.set_option("misplaced_workgroup", 0)
+    for m in models:
+        m.set_option("reset_status", 1)
+    bwd.set_option("spin_limit", 64)
+    bwd.set_option("barrier_never_completes", 1)
+    got = binding.forward_bidirectional(fwd, bwd, xq)
+    assert (fwd.device_status(), bwd.device_status()) == (0, 1)
+    assert torch.equal(got[:, :, :300], want[:, :, :300])
+    bwd.set_option("spin_limit", 1 << 21)
+    bwd.set_option("barrier_never_completes", 0)
+    bwd.set_option("reset_status", 1)
+    assert torch.equal(binding.forward_bidirectional(fwd, bwd, xq), want)
+    assert (fwd.device_status(), bwd.device_status()) == (0, 0)
+
+
 def test_bidirectional_argument_checks(orc):
     import torch
     from paper_2101_05453_amd import binding

@@ -218,6 +218,30 @@ def test_wait_gives_up_and_model_recovers(orc, rows16):
     assert_equal("recovered", y.cpu().numpy(), orc.forward(orc_model, xq))
 
 
+@pytest.mark.parametrize("options", [{"rows16": 0}, {"rows16": 1}, {"rows16": 2}, {"stack": 2}])
+def test_misplaced_workgroup_is_reported(options):
+    """The placement check of every kernel whose workgroups meet, with one workgroup too many counted (test hook)."""
+    import torch
+
+    from paper_2101_05453_amd import binding
+    from parity_util import calibrate_on_gpu
+
+    layers, x = wl.make_custom([40, 300], 300, 300, 0, 20, 3, seed=33)
+    xf = calibrate_on_gpu(layers, x)
+    model = binding.prepare(layers, device=0)
+    for k, v in dict({"stack": 0}, **options).items():
+        model.set_option(k, v)
+    xq = model.quantize_input(xf)
+    want = model.forward(xq)
+    assert model.device_status() == 0
+    model.set_option("misplaced_workgroup", 1)
+    model.forward(xq)
+    assert model.device_status() in (1, 2)  # 1: a wait that saw the 2 and gave up
+    model.set_option("misplaced_workgroup", 0)
+    model.set_option("reset_status", 1)
+    assert torch.equal(model.forward(xq), want) and model.device_status() == 0
+
+
 def test_batch_beyond_one_launch(orc):
     """N = 2048 with a projection: 8 groups of 64 rows per launch (two row tiles per
     group), so B = 600 runs in two launches, the second with a ragged last group
