@@ -905,7 +905,7 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1) {
   // layers of up to 256 cells: one workgroup per 4 rows, nothing to exchange
   if (m->rows16 == 1 && d.p16 && solo_supported(h.N, h.H, (int)h.flags, B)) {
     RecArgs r1 = ra;
-    r1.R2h = d.R2h; r1.ks16 = d.ks16; r1.rows_pg = 4; r1.groups = (B + 3) / 4; r1.ldy = h.H;
+    r1.R2h = d.R2h; r1.ks16 = d.ks16; r1.rows_pg = 4; r1.groups = (B + 3) / 4;
     r1.Wp2 = d.Wp2; r1.bp2 = d.bp2; r1.ptiles = d.ptiles; r1.prow = 32;
     if (solo_lds_bytes(r1) <= 160 * 1024) {
       ra = r1;
@@ -917,7 +917,7 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1) {
   int g4 = 0;
   if (!p.solo && m->rows16 == 1 && d.p16 && quad_supported(h.N, h.H, (int)h.flags, B, share, &g4)) {
     RecArgs r4 = ra;
-    r4.R2h = d.R2h; r4.ks16 = d.ks16; r4.rows_pg = 4; r4.groups = g4; r4.ldy = h.H;
+    r4.R2h = d.R2h; r4.ks16 = d.ks16; r4.rows_pg = 4; r4.groups = g4;
     r4.Wp2 = d.Wp2; r4.bp2 = d.bp2; r4.ptiles = d.ptiles; r4.prow = 32;
     if (quad_lds_bytes(r4) <= 160 * 1024) {
       ra = r4;
@@ -1167,7 +1167,10 @@ int lstm_int_forward(const lstm_int_model *cm, const int8_t *x, int32_t T, int32
           const bool coop = m->cooperative != 0;
           RecArgs2 one;
           memset(&one, 0, sizeof(one));
-          if (plan.solo || plan.quad) one.d[0] = ra;
+          if (plan.solo || plan.quad) {
+            static_cast<RecArgs &>(one.d[0]) = ra;
+            one.d[0].ldy = h.H;
+          }
           if ((plan.solo ? launch_solo(s, one) : plan.quad ? launch_quad(s, one, coop) : use16 ? launch_rec16(s, ra, coop) : launch_rec(s, ra, coop)) != hipSuccess)
             return LSTM_INT_E_DEVICE;
         }
@@ -1379,8 +1382,8 @@ static int forward_pair(lstm_int_model *const (&m)[2], const int8_t *x, int32_t 
         Timed t(m[i]->prof, s, LSTM_INT_K_INPUT_GEMM);
         launch_in_gemm(s, ga);
       }
-      RecArgs &ra = pair.d[i];
-      ra = plan[i].ra;
+      RecDirArgs &ra = pair.d[i];
+      static_cast<RecArgs &>(ra) = plan[i].ra;
       ra.tx2 = ga.tx2;
       ra.h0 = h0; ra.out = out;
       ra.mbuf = reinterpret_cast<int8_t *>(base[i] + ws[i].m2);

@@ -86,7 +86,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     return;
   }
   const int which = gl >= a0.groups ? 1 : 0;
-  const RecArgs &a = args.d[which];
+  const RecDirArgs &a = args.d[which];
   const int row0 = a.batch0 + (gl - (which ? a0.groups : 0)) * RG;
   const bool proj = a.flags & 8;
   const int ldy = a.ldy;

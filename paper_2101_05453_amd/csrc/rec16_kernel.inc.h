@@ -29,7 +29,11 @@ namespace lstm_int {
   } while (0)
 
 __device__ __forceinline__ const RecArgs &rec16_args(const RecArgs &a, int) { return a; }
-__device__ __forceinline__ const RecArgs &rec16_args(const RecArgs2 &a, int i) { return a.d[i]; }
+__device__ __forceinline__ const RecDirArgs &rec16_args(const RecArgs2 &a, int i) { return a.d[i]; }
+__device__ __forceinline__ int rec16_ldy(const RecArgs &a) { return a.H; }
+__device__ __forceinline__ int rec16_ldy(const RecDirArgs &a) { return a.ldy; }
+__device__ __forceinline__ int rec16_rev(const RecArgs &) { return 0; }
+__device__ __forceinline__ int rec16_rev(const RecDirArgs &a) { return a.rev; }
 
 // PAIR: the launch runs two layers of one shape side by side, each possibly backward in time (RecArgs2).
 template <int KS16, int FL, bool PAIR = false>
@@ -41,7 +45,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 15, q = lane >> 4;
   constexpr int g_first = cifg ? 1 : 0;
-  const RecArgs &a0 = rec16_args(args, 0);
+  const auto &a0 = rec16_args(args, 0);
   const int GS = a0.GS;
 
   // placement, as in rec_kernel
@@ -77,12 +81,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     return;
   }
   const int which = PAIR && gl >= a0.groups ? 1 : 0;
-  const RecArgs &a = rec16_args(args, which);
+  const auto &a = rec16_args(args, which);
   const int group = gl - (which ? a0.groups : 0);
   const bool proj = a.flags & 8;
-  const int ldy = PAIR ? a.ldy : a.H;
+  const int ldy = rec16_ldy(a);
   // time of step t
-  auto time_of = [&](int t) { return PAIR && a.rev ? a.T - 1 - t : t; };
+  auto time_of = [&](int t) { return rec16_rev(a) ? a.T - 1 - t : t; };
   constexpr int items = 64;                    // (gate, row) layer-norm rows of the group
   const int row0 = a.batch0 + group * 16;      // first batch row of the group
   const int cellw = wave * 16 + 4 * q;         // + c, within the workgroup's 64 cells

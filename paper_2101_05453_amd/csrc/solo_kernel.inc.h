@@ -38,7 +38,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c16 = lane & 15, q = lane >> 4;
   const int which = (int)blockIdx.x >= args.d[0].groups ? 1 : 0;
-  const RecArgs &a = args.d[which];
+  const RecDirArgs &a = args.d[which];
   const int row0 = ((int)blockIdx.x - (which ? args.d[0].groups : 0)) * RG;
   const bool proj = a.flags & 8;
   const int ldy = a.ldy;
