@@ -334,7 +334,11 @@ int lstm_int_forward_bidirectional(const lstm_int_model *fwd, const lstm_int_mod
  *   "phase_timing": nonzero makes workgroup 0 of the persistent kernel add the
  *           time it spends in each of its phases to 16 device counters
  *           (diagnostics; read them with lstm_int_phase_ticks).  In a stacked
- *           launch the value is 1 + the layer whose workgroup 0 is timed.
+ *           launch the value is 1 + the layer whose workgroup 0 is timed.  The
+ *           kernels for groups of four rows and for layers of up to 256 cells
+ *           have no timers (there they cost up to 7 % of a call even when off):
+ *           calls that run on them leave the counters as they are; "rows16" = 2
+ *           or 0 takes, and times, groups of 16 or 32 rows instead.
  * Unknown keys or values give LSTM_INT_E_INVALID_ARG.
  */
 int lstm_int_set_option(lstm_int_model *model, const char *key, int64_t value);

@@ -244,11 +244,12 @@ bool stack_chosen(const lstm_int_model *m, int64_t T, int64_t B) {
   if (!stack_supported(h.N, h.H, (int)h.flags, m->dev[0].Ipad, L, (int)T, (int)B, &ks) || ks != m->stack_ks) return false;
   if (kStackFlagsOff + (size_t)L * ((B + 31) / 32) * 128 > kSyncBytes) return false;  // flags behind the statistics words
   if (m->stack == 2) return true;
-  // Expected time of the two ways, in microseconds, from the times measured on the 8-layer benchmark stack
-  // (N = 2048, H = 640).  One after the other: about 30 us per layer for the input GEMM launch and the weight
-  // prologue, and 8.1 us per step up to 128 rows, 11 us per 256 rows beyond.  Stacked: every layer walks its
-  // T * tiles items (step, tile of 32 rows) one after the other at about 20.5 us each, one item behind the
-  // layer below.
+  // Expected time of the two ways, in microseconds, from the times measured on a stack of 8 layers of 2048 cells,
+  // 640 outputs, whose layers ran on the kernels for groups of 16 and 32 rows.  (Groups of four rows and the
+  // one-workgroup kernel are faster, so smaller layers at few rows may do better one after the other than this
+  // says.)  One after the other: about 30 us per layer for the input GEMM launch and the weight prologue, and 8.1 us
+  // per step up to 128 rows, 11 us per 256 rows beyond.  Stacked: every layer walks its T * tiles items (step, tile
+  // of 32 rows) one after the other at about 20.5 us each, one item behind the layer below.
   const double tiles = (double)((B + 31) / 32);
   const double seq = L * (30.0 + T * (B <= 128 ? 8.1 : 11.0 * ((B + 255) / 256)));
   const double stk = 25.0 + (T * tiles + L - 1) * m->stack_step_us;

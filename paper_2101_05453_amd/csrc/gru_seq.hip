@@ -6,7 +6,9 @@
 //
 //  * gru_quad_kernel, groups of 4 rows: a lane has one cell of one row (little work per wave: what bounds a small batch is
 //    the number of instructions a wave issues per step and the latency of the exchange).  The state travels as (value,
-//    tag) byte pairs, four cells to a 64-bit word, the tag being the step: a reader polls the words it needs.
+//    tag) byte pairs, four cells to a 64-bit word, the tag being the step: a reader polls the words it needs.  (Stored at
+//    workgroup scope, polled at agent scope; they meet in the L2 of the group's one XCD, see quad_kernel.inc.h.  Stored at
+//    agent scope, through the L2 to memory: 512 cells, 16 rows, 100 steps 152 -> 267 us.)
 //  * gru_rows_kernel, groups of 16 or 32 rows: a lane has four cells of a row.  A workgroup stores its piece of the state
 //    in operand order, waits for the acknowledgement and raises its flag, a word in a line of its own; one wave polls the
 //    flags of all members, then every wave fetches a quarter of the tile, global -> LDS without a register in between.

@@ -19,6 +19,12 @@
 // Words are single-copy atomic at 64 bits, so a tag vouches for its values.  Two
 // slots alternate: a workgroup stores step t + 2 only after it has read step t + 1
 // of all others, who stored that after they had read all of step t.
+// A word is stored at workgroup scope and polled at agent scope.  What makes the
+// two meet is the placement, not the scopes: the L1 writes through, so the store is
+// in the L2 of the group's XCD, and a load of agent scope goes past the L1 to that
+// L2.  A group spread over two XCDs would never see its words (the waits end, and
+// the placement check says why).  An agent-scope store goes on through the L2 to
+// memory: 512 cells, layer norm, 16 rows, 100 steps 304 -> 383 us.
 // A wave's memory operations return in order, so nothing slow may be ahead of a
 // poll: the W x terms (from memory, asked for two steps ahead) go to LDS by waves 2
 // and 3, the layer output is stored by wave 1, each right after the step's last

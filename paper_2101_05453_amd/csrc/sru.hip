@@ -332,7 +332,7 @@ __global__ __launch_bounds__(FULL ? kScanBlockFull : kScanBlock) void sru_scan_k
 #pragma unroll
     for (int c = 0; c < CPT; ++c) {
       // both gates read the state before the step (Secs. 3.2.3, 3.2.1)
-      // (all products here are of 16-bit values: the 24-bit multiply is exact and runs at full rate)
+      // (all products here are of 16-bit values: the 24-bit multiply is exact)
       tvf[c] = rescale_sat16_pre<FAST ? 0 : 2>(__mul24(vf[c], cst[c]), a.pv[0]);
       tvr[c] = rescale_sat16_pre<FAST ? 0 : 2>(__mul24(vr[c], cst[c]), a.pv[1]);
       // FAST: the Q3.12 table stays within 1..32767 (the host has checked), no clamp of a gate or its complement acts
