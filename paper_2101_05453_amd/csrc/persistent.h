@@ -159,9 +159,10 @@ struct RecArgs {
 
 // Two layers of one shape in one launch (the two directions of a bidirectional layer): groups [0, groups) of the launch run
 // d[0], the next d[1].groups run d[1].  Both name the same synchronization scratch, which holds words for all of them.
-// What only these launches need stays out of RecArgs, which StackArgs begins with: eight bytes more there moved the fields
-// behind it across lines of the argument segment, and a one-step call of the stacked launch, which has read no line of it
-// before, took 135.7 us instead of 134.0 (8 layers of 2048 cells, 32 rows; same instructions).
+// What only these launches need stays out of RecArgs, which StackArgs begins with.  A one-step call of the stacked launch (8
+// layers of 2048 cells, 32 rows) takes 133 or 135 us, one of the two throughout a process; with eight bytes more in RecArgs
+// -- the same instructions, every field behind them at another place of the argument segment -- it was the slower one in 16
+// of 25 processes on three machines (all of them on one), without them in 1 of 41.
 struct RecDirArgs : RecArgs {
   int ldy, rev;  // row stride of y; 1 = step t works at time T - 1 - t
 };
