@@ -161,8 +161,8 @@ struct RecArgs {
 // d[0], the next d[1].groups run d[1].  Both name the same synchronization scratch, which holds words for all of them.
 // What only these launches need stays out of RecArgs, which StackArgs begins with.  A one-step call of the stacked launch (8
 // layers of 2048 cells, 32 rows) takes 133 or 135 us, one of the two throughout a process; with eight bytes more in RecArgs
-// -- the same instructions, every field behind them at another place of the argument segment -- it was the slower one in 16
-// of 25 processes on three machines (all of them on one), without them in 1 of 41.
+// -- the same instructions, every field behind them at another place of the argument segment -- it was the slower one in 21
+// of 34 processes on four machines (in all on one of them), without them in 2 of 50.
 struct RecDirArgs : RecArgs {
   int ldy, rev;  // row stride of y; 1 = step t works at time T - 1 - t
 };
