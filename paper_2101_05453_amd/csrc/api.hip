@@ -875,7 +875,8 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1) {
   ra.stats_sleep = m->stats_sleep;
   ra.idle_sleep = m->idle_sleep;
   ra.stats_first_sleep = m->stats_first_sleep;
-  // the last arrival lands about 0.45 us after a workgroup's own in a group of 32, sooner in small groups
+  // the last arrival lands about 0.45 us after a workgroup's own in a group of 32, sooner in small groups; in the 32-row
+  // kernel a pause of 8 is as good as one of 16 at 32 workgroups and 2 % better at 16 (0 and 4: 0.4 % worse at 32)
   ra.sync_sleep = m->sync_sleep >= 0 ? m->sync_sleep : (d.GS >= 16 ? 16 : 4);
   ra.idle_poll_sleep = m->idle_poll_sleep;
   ra.ticks = m->phase_timing ? reinterpret_cast<long long *>(m->status + 16) : nullptr;
@@ -896,6 +897,7 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1) {
   };
   const bool lut0 = set_lut(0, m->wsig3), lut1 = set_lut(1, m->wtanh3), lut2 = set_lut(2, d.wtanhc);
   const bool lut_ok = lut0 && lut1 && lut2;
+  ra.flags |= kFourPredSlots;
   if (ok && ra.rows_pg == 64 && lut_ok && rec_lds_bytes(ra) > 160 * 1024) {
     // two row tiles per group do not fit the LDS: one tile per group, more launches over the batch
     ra.rows_pg = 32;
@@ -966,6 +968,12 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1) {
         grew = true;
       }
     }
+  }
+  // eight partial sums of the projection where they fit beside the tables (one barrier less per step)
+  if (!p.use16) {
+    if (m->sync_sleep < 0 && d.GS >= 16) ra.sync_sleep = 8;
+    ra.flags &= ~kFourPredSlots;
+    if (lds_need() > 160 * 1024) ra.flags |= kFourPredSlots;
   }
   p.groups = p2_groups;
   p.ok = true;

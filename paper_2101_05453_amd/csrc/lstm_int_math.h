@@ -294,6 +294,15 @@ LSTM_HD int32_t rescale_sat16_pre(int32_t a, const RescaleHi &p) {
 #endif
   return sat16((hi + p.add) >> p.sh);
 }
+// rescale(a, M, r) without the saturation, for an operand that needs no treatment (at most 2^30 in magnitude)
+LSTM_HD int32_t rescale_hi_pre(int32_t a, const RescaleHi &p) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const int32_t hi = __mulhi(a, p.M);
+#else
+  const int32_t hi = (int32_t)(((int64_t)a * (int64_t)p.M) >> 32);
+#endif
+  return (hi + p.add) >> p.sh;
+}
 // PRE for an operand bounded by amax in magnitude and a shift r: 0 = as it is (r >= 33), 1 = shifted left by 33 - r (the
 // shifted bound still fits 32 bits), 2 = clamped first
 LSTM_HD int preshift_mode(int r, int64_t amax) {

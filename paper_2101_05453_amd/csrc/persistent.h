@@ -100,8 +100,14 @@ constexpr int kStatSetWords = 2 * 2 * 256;
 constexpr int kStatGroupWords = 2 * kStatSetWords;
 __host__ __device__ inline bool stat_two_sets(int GS) { return GS >= 16; }
 
+// rec_kernel: the eight waves' partial sums of the projection go through four slots of LDS instead of eight, two waves to a
+// slot one after the other (where W_proj and the tables leave no room for eight: 1024 cells with 640 outputs)
+constexpr int kFourPredSlots = 256;
+
 struct RecArgs {
-  int T, B, N, H, Hpad, flags, m_c;
+  int T, B, N, H, Hpad;
+  int flags;      // the layer's; rec_kernel: | kFourPredSlots
+  int m_c;
   int GS;         // workgroups (compute units) per group = cells / 64
   int groups;     // groups in this launch, each owns rows_pg batch rows
   int batch0;     // first batch row of this launch
@@ -109,7 +115,7 @@ struct RecArgs {
   int ks;         // 32-wide k steps held in registers (template KS)
   int Ncp;        // GS * 64
   int Bp;         // B rounded up to 32
-  const int4 *R2;      // [GS][4 waves][2 tiles][ks][64 lanes] 16 bytes each (sparse != 0: see rec_sparse_bytes)
+  const int4 *R2;      // [GS][8 tiles][ks][64 lanes] 16 bytes each (sparse != 0: see rec_sparse_bytes)
   const int4 *R2h;     // 16-row kernel: [GS][4 waves][4 tiles][ks16][64 lanes] 16 bytes each
   int ks16;            // 16-row kernel: 64-wide k steps held in registers
   const int32_t *bh4;  // [4][Ncp]
@@ -173,8 +179,8 @@ struct RecArgs2 {
 // Recurrent weights with at most two nonzeros in every aligned group of four along k (the pruned models of
 // Table 1 in their structured form) as operands of the sparse MFMA v_smfmac_i32_32x32x64_i8, which takes a
 // 64-deep k step in the time the dense 32x32x32 instruction takes a 32-deep one:
-//   values  [GS][4 waves][2 tiles][ks / 2][64 lanes] 16 bytes,
-//   indices [GS][4 waves][2 tiles][ks / 2][64 lanes] 4 bytes, behind all the values.
+//   values  [GS][8 tiles][ks / 2][64 lanes] 16 bytes,
+//   indices [GS][8 tiles][ks / 2][64 lanes] 4 bytes, behind all the values.
 // Lane = rho + 32 * a (rho = the tile row, as in R2) holds, for k step q, the groups of four
 //   k = 64 q + (j < 4 ? 0 : 32) + 16 a + 4 (j % 4) + 0..3,   j = 0..7,
 // as value bytes 2 j and 2 j + 1 (the group's two kept weights; a group with fewer nonzeros is filled with

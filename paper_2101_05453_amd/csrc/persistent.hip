@@ -214,10 +214,11 @@ bool rec_supported(int N, int H, int flags, int B, int *ks, int *rt, int *groups
 size_t rec_lds_bytes(const RecArgs &a) {
   const int items = (a.rows_pg / 32) * 128;
   const bool proj = a.flags & 8;
-  size_t tile = (((size_t)a.rows_pg * (a.ks * 32 + 16) + 1023) / 1024 + 1) * 1024;
-  if (proj && tile < 4 * 16 * 64 * 4) tile = 4 * 16 * 64 * 4;
+  size_t tile = ((size_t)a.rows_pg * (a.ks * 32 + 16) + 1023) / 1024 * 1024;
+  const size_t pred = proj ? (size_t)(a.flags & kFourPredSlots ? 4 : 8) * 4096 : 0;
+  if (tile < pred) tile = pred;
   size_t n = tile + (size_t)items * 8 + (size_t)items * sizeof(LnRow2) + 2 * 4 * 64 * 8 + 4 * 64 * 2 + 4 * 64 * 4 +
-             kPrmLdsBytes + 16 + 16 * 8 + 3 * 32 /* LutLds */;
+             32 * 4 + kPrmLdsBytes + 16 + 16 * 8 + 3 * 32 /* LutLds */;
   for (int i = 0; i < 3; ++i)
     if (i < 2 || a.lut[2].blob != a.lut[1].blob) n += (size_t)lut_wide_lds_bytes(a.lut[i].dom, a.lut[i].sh, a.lut[i].tail != 0);
   if (proj) {
@@ -279,9 +280,9 @@ hipError_t launch_rec(hipStream_t s, const RecArgs &a, bool cooperative) {
   // in-order stream on a device nothing else occupies.  If the workgroups do not all arrive, the bounded
   // waits give up and raise the status word: an error, not a hang.
   if (cooperative)
-    return hipLaunchCooperativeKernel(reinterpret_cast<const void *>(fn), dim3(8 * slots), dim3(256), params,
+    return hipLaunchCooperativeKernel(reinterpret_cast<const void *>(fn), dim3(8 * slots), dim3(512), params,
                                       (unsigned)rec_lds_bytes(a), s);
-  return hipLaunchKernel(reinterpret_cast<const void *>(fn), dim3(8 * slots), dim3(256), params,
+  return hipLaunchKernel(reinterpret_cast<const void *>(fn), dim3(8 * slots), dim3(512), params,
                          (unsigned)rec_lds_bytes(a), s);
 }
 

@@ -10,6 +10,7 @@
 
 namespace lstm_int {
 
+typedef int v2i __attribute__((ext_vector_type(2)));
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef int v16i __attribute__((ext_vector_type(16)));
@@ -27,13 +28,9 @@ typedef unsigned long long u64;
 // added made the barrier slower).  Gives up after spin_limit polls (or when
 // another workgroup gave up), raising the status word so that every workgroup
 // leaves the kernel; lds_flag[0] is then 0 for good.
-// PENDING: vector memory loads the caller issued after its last store and does
-// not need yet (the counter of outstanding operations drains in issue order, so
-// waiting until PENDING are left means every store before them is complete).
-template <int PENDING = 0>
 __device__ __forceinline__ bool group_sync(unsigned *counter, unsigned &epoch, int GS, int *status,
                                            int spin_limit, int first_sleep, int poll_sleep, int *lds_flag) {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PENDING) : "memory");
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (GS == 1) return true;
   epoch += (unsigned)GS;
@@ -79,7 +76,8 @@ struct PrmLds {  // 256 bytes (kPrmLdsBytes in persistent.hip)
   RescaleHi h[4], c[4], ln[4];  // R h terms, peephole terms, layer-norm second stage
   RescaleHi m, p;               // hidden state, projection
   int32_t zp_m, zp_h, m_c, glo;
-  int32_t pad[4];
+  double inv_n;  // 1 / N
+  int32_t pad[2];
 };
 
 static_assert(sizeof(PrmLds) == 256, "rec_lds_bytes assumes 256 bytes");
@@ -99,17 +97,47 @@ __device__ __forceinline__ int32_t mirror_sigmoid(int32_t x, int32_t t) {
 __device__ __forceinline__ int32_t mirror_tanh(int32_t x, int32_t t) {
   return x < 0 ? -t : (t > 32767 ? 32767 : t);
 }
+// The same for a kernel with two or more waves per SIMD, which then issues an add, a shift or a logical operation every 2.2
+// clocks and a comparison, a select, a maximum or a three-operand instruction every 4.3 (one wave alone: every 5 clocks,
+// whatever it is): signs are handled by masks.  (The compiler would make the comparisons of these again if it knew what
+// the mask is.)
+__device__ __forceinline__ int32_t sign_mask(int32_t v) {
+  int32_t s = v >> 31;
+  asm("" : "+v"(s));
+  return s;
+}
+__device__ __forceinline__ int32_t abs_masked(int32_t v) {
+  const int32_t s = sign_mask(v);
+  return (v ^ s) - s;
+}
+// sigma of Q3.12 stays below 32767 (32757 at the largest x): its output clamp never acts
+__device__ __forceinline__ int32_t mirror_sigmoid_masked(int32_t x, int32_t t) {
+  const int32_t s = sign_mask(x);
+  return (t ^ s) + (s & 32769);  // x < 0: ~t + 32769 = 32768 - t
+}
+__device__ __forceinline__ int32_t mirror_tanh_masked(int32_t x, int32_t t) {
+  const int32_t s = sign_mask(x), v = (t ^ s) - s;
+  return v > 32767 ? 32767 : v;
+}
 
+// Eight waves, two per SIMD, each with one weight tile (8 cells, 4 gates, all of k).  The arithmetic of a step is bound by
+// the issue of its instructions, and one wave alone issues one every 5 clocks whatever it is; four waves with two tiles each
+// took 1220 us where this form takes 1063 (two layers of 1024 cells, coupled gates, layer norm, 1024 rows, 32 steps) and 5590
+// where it takes 5380 (eight layers of 2048 cells, 640 outputs, layer norm, 256 rows, 64 steps).  A wave has half of the
+// registers then, and a register spilled to scratch memory is read back behind the W x terms on their way from HBM (the
+// first build of this form, with 32 such registers, took 5900): hence the lane addresses computed anew in every step, the
+// LDS arrays of fixed size at known offsets, and the two machine passes switched off for these files (build.py).
 // FL: bit 0 CIFG, bit 1 peephole, bit 2 layer norm, bit 3 "no projection" (compile
 // time, so that the code carries no tests of them); with bit 3 clear the
 // projection is a runtime flag.  SP: the recurrent weights are in the 2:4
 // compressed form (persistent.h) and R h runs on the sparse MFMA.
 template <int KS, int RT, int FL, bool SP = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void rec_kernel(RecArgs a) {
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void rec_kernel(RecArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   const long long t_start = (long long)wall_clock64();
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 31, b2 = lane >> 5;
+  constexpr int WAVES = 8;  // one weight tile each
   constexpr bool cifg = FL & 1, ph = FL & 2, ln = FL & 4;
   // bit 3: the layer is known to have no projection (measured: dropping the projection code from
   // those kernels gains 1.7 % at C5, while fixing the flag to "on" at compile time loses 5 % at C4)
@@ -161,27 +189,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   constexpr int items = RT * 128;  // (rt, gate, row) layer-norm rows of the group
   const int row0 = a.batch0 + group * rows_pg;  // first batch row of the group
 
-  // ---- LDS carve-up (rec_lds_bytes mirrors it)
+  // ---- LDS carve-up (rec_lds_bytes mirrors it): what has a fixed size first, at offsets known to the compiler
   constexpr int LS = KS * 32 + 16;  // h tile row stride
   uint8_t *p = lds;
-  int8_t *hT = reinterpret_cast<int8_t *>(p);
-  int32_t *pred = reinterpret_cast<int32_t *>(p);  // projection partials reuse the h tile between steps
-  {
-    // whole 1 KB chunks, plus one that takes the loads past the tile (every wave issues the same number)
-    const size_t tile_bytes = (((size_t)rows_pg * LS + 1023) / 1024 + 1) * 1024;
-    const size_t pred_bytes = proj ? 4 * 16 * 64 * 4 : 0;
-    p += tile_bytes > pred_bytes ? tile_bytes : pred_bytes;
-  }
   u64 *red = reinterpret_cast<u64 *>(p);                 p += (size_t)items * 8;
   LnRow2 *lnrow = reinterpret_cast<LnRow2 *>(p);         p += (size_t)items * sizeof(LnRow2);
   double *LdL = reinterpret_cast<double *>(p);           p += 4 * 64 * 8;  // layer-norm weights / 2^10 as doubles
   double *bdL = reinterpret_cast<double *>(p);           p += 4 * 64 * 8;  // layer-norm biases / 2^10 + 2^-11 as doubles
   int16_t *PqL = reinterpret_cast<int16_t *>(p);         p += 4 * 64 * 2;  // 3 used
   int32_t *bhL = reinterpret_cast<int32_t *>(p);         p += 4 * 64 * 4;
+  int32_t *bpL = reinterpret_cast<int32_t *>(p);         p += 32 * 4;
   PrmLds *prm = reinterpret_cast<PrmLds *>(p);           p += sizeof(PrmLds);
   int *flag = reinterpret_cast<int *>(p);                p += 16;
   u64 *tickL = reinterpret_cast<u64 *>(p);               p += 16 * 8;  // phase timers
   LutLds *lutP = reinterpret_cast<LutLds *>(p);          p += 3 * sizeof(LutLds);
+  int8_t *hT = reinterpret_cast<int8_t *>(p);
+  v4i *pred = reinterpret_cast<v4i *>(p);  // projection partials [slot][4][64] reuse the h tile between steps
+  const bool four_slots = a.flags & kFourPredSlots;
+  {
+    const size_t tile_bytes = ((size_t)rows_pg * LS + 1023) / 1024 * 1024;  // whole 1 KB chunks
+    const size_t pred_bytes = proj ? (four_slots ? 4 : 8) * 4096 : 0;
+    p += tile_bytes > pred_bytes ? tile_bytes : pred_bytes;
+  }
   // compressed sigma / tanh tables (wide form, lstm_int_math.h): deltas of the first dom entries, their
   // bases, and the tail part where one is kept; the cell-format tanh shares the gate one if equal
   const bool share_tanh = a.lut[2].blob == a.lut[1].blob;
@@ -207,37 +236,34 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   // parameters, the tables and the W_proj tiles -> LDS
   constexpr int KW = SP ? KS / 2 : KS;  // weight operands per tile: 64-deep k steps in the sparse form
   static_assert(!SP || KS % 2 == 0, "the sparse form takes k in steps of 64");
-  v4i Wf[2][KW];
-  int Wi[2][SP ? KW : 1];  // sparse form: the index word of each operand
+  v4i Wf[KW];
+  int Wi[SP ? KW : 1];  // sparse form: the index word of each operand
   {
-    const int4 *src = a.R2 + ((size_t)(member * 4 + wave) * 2) * KW * 64 + lane;
-    const int *isrc = reinterpret_cast<const int *>(a.R2 + (size_t)GS * 4 * 2 * KW * 64) +
-                      ((size_t)(member * 4 + wave) * 2) * KW * 64 + lane;
-    // all loads of a tile are in flight together before the first is moved to its place
+    const int4 *src = a.R2 + (size_t)(member * WAVES + wave) * KW * 64 + lane;
+    const int *isrc = reinterpret_cast<const int *>(a.R2 + (size_t)GS * WAVES * KW * 64) +
+                      (size_t)(member * WAVES + wave) * KW * 64 + lane;
+    // all loads are in flight together before the first is pinned to its place
+    int4 w[KW];
+    int wi[KW];
 #pragma unroll
-    for (int tl = 0; tl < 2; ++tl) {
-      int4 w[KW];
-      int wi[KW];
-#pragma unroll
-      for (int ks = 0; ks < KW; ++ks) {
-        w[ks] = src[(size_t)(tl * KW + ks) * 64];
-        if (SP) wi[ks] = isrc[(size_t)(tl * KW + ks) * 64];
-      }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int ks = 0; ks < KW; ++ks) {
-        Wf[tl][ks] = v4i{w[ks].x, w[ks].y, w[ks].z, w[ks].w};
-        asm volatile("" : "+a"(Wf[tl][ks]));  // resident in accumulation registers for the whole launch
-        if (SP) {
-          Wi[tl][ks] = wi[ks];
-          asm volatile("" : "+v"(Wi[tl][ks]));  // the index operand is read from an ordinary vector register
-        }
-      }
-      __builtin_amdgcn_sched_barrier(0);
+    for (int ks = 0; ks < KW; ++ks) {
+      w[ks] = src[(size_t)ks * 64];
+      if (SP) wi[ks] = isrc[(size_t)ks * 64];
     }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < KW; ++ks) {
+      Wf[ks] = v4i{w[ks].x, w[ks].y, w[ks].z, w[ks].w};
+      asm volatile("" : "+v"(Wf[ks]));  // resident in registers for the whole launch
+      if (SP) {
+        Wi[ks] = wi[ks];
+        asm volatile("" : "+v"(Wi[ks]));  // the index operand is read from an ordinary vector register
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
   }
-  const int cell_w = wave * 16 + 4 * b2;  // + tile * 8 + c, within the workgroup's 64 cells
-  {
+  const int cell_w = wave * 8 + 4 * b2;  // + c, within the workgroup's 64 cells
+  if (tid < 256) {
     const int g = tid >> 6, n = tid & 63;  // 256 threads = 4 gates x 64 cells
     const size_t idx = (size_t)g * a.Ncp + member * 64 + n;
     LdL[tid] = ln ? ln_weight_scaled(a.Lq4[idx]) : 0.0;
@@ -263,9 +289,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     prm->m = rescale_hi_prepare(a.Mm, a.rm);
     prm->p = rescale_hi_prepare(proj ? a.Mp : 0, proj ? a.rp : 33);
     prm->zp_m = a.zp_m; prm->zp_h = a.zp_h;
+    prm->inv_n = 1.0 / (double)a.N;
     prm->m_c = a.m_c; prm->glo = ln ? -32767 : -32768;
   }
-  for (int i = tid; i < rows_pg * LS / 16; i += 256) reinterpret_cast<int4 *>(hT)[i] = int4{0, 0, 0, 0};
+  for (int i = tid; i < rows_pg * LS / 16; i += 64 * WAVES) reinterpret_cast<int4 *>(hT)[i] = int4{0, 0, 0, 0};
   // tables and W_proj tiles: global -> LDS loads, all in flight together
   {
     auto dma = [&](const void *src, const void *dst) {
@@ -278,7 +305,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       const int nd = a.lut[i].dom >> 10;
       const int nb = (((a.lut[i].dom >> a.lut[i].sh) * 2) + 1023) >> 10;
       const int nt = a.lut[i].tail ? 3 : 0;
-      for (int c = wave; c < nd + nb + nt; c += 4) {
+      for (int c = wave; c < nd + nb + nt; c += WAVES) {
         const int so = c < nd ? c * 1024 : (c < nd + nb ? kLutWideBaseOff + (c - nd) * 1024 : kLutWideTailOff + (c - nd - nb) * 1024);
         dma(a.lut[i].blob + so + lane * 16, lutD[i] + c * 1024);
       }
@@ -289,7 +316,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const int prow = a.prow;
     const int wp_rows = my_ptiles * prow;
     const int wp_chunks = (wp_rows * WLS + 1023) >> 10;
-    for (int c = wave; c < wp_chunks; c += 4) {
+    for (int c = wave; c < wp_chunks; c += WAVES) {
       const int o = c * 1024 + lane * 16;
       const int r = o / WLS, col_b = o - r * WLS;
       const int8_t *src = a.Wp2;
@@ -302,42 +329,35 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   }
 
-  // cell state of this lane's 8 cells x RT row tiles, kept in registers
-  int32_t creg[RT][2][4];
+  // cell state of this lane's 4 cells x RT row tiles, kept in registers
+  int32_t creg[RT][4];
 #pragma unroll
-  for (int rt = 0; rt < RT; ++rt)
+  for (int rt = 0; rt < RT; ++rt) {
+    const int row = row0 + rt * 32 + col;
+    const int n0 = member * 64 + cell_w;
 #pragma unroll
-    for (int tl = 0; tl < 2; ++tl) {
-      const int row = row0 + rt * 32 + col;
-      const int n0 = member * 64 + cell_w + tl * 8;
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-        creg[rt][tl][c] = (a.c_in && row < a.B && n0 + c < a.N) ? a.c_in[(size_t)row * a.N + n0 + c] : 0;
-    }
+    for (int c = 0; c < 4; ++c)
+      creg[rt][c] = (a.c_in && row < a.B && n0 + c < a.N) ? a.c_in[(size_t)row * a.N + n0 + c] : 0;
+  }
 
   // h tile staging by global -> LDS loads (no registers in between): wave
-  // instruction (wave + 4 j) fills bytes [1024 c, 1024 (c + 1)) of the tile,
+  // instruction c = wave + 8 j fills bytes [1024 c, 1024 (c + 1)) of the tile,
   // lane l its 16 bytes at 16 l; the lane's source is wherever that byte range
   // falls in the padded [row][LS] tile (pad bytes and the tail read offset 0
   // and hold garbage that only ever meets zero weights)
   constexpr int TILE_KB = (rows_pg * LS + 1023) / 1024;
-  constexpr int NCH = (TILE_KB + 3) / 4;  // chunks per wave
-  int hsrc[NCH];
+  constexpr int NCH = (TILE_KB + WAVES - 1) / WAVES;  // chunks per wave
+  unsigned hsrc[NCH];
 #pragma unroll
   for (int j = 0; j < NCH; ++j) {
-    const int o = (wave + 4 * j) * 1024 + lane * 16;
+    const int o = (wave + WAVES * j) * 1024 + lane * 16;
     const int r = o / LS, c = o - r * LS;
     int row = row0 + r;
     row = row < a.B ? row : a.B - 1;
-    hsrc[j] = (r < rows_pg && c < a.Hpad) ? row * a.Hpad + c : 0;
+    hsrc[j] = (r < rows_pg && c < a.Hpad) ? (unsigned)(row * a.Hpad + c) : 0u;
   }
 
-  // projection bias of this thread's four outputs of its first tile
-  int32_t bpr[4] = {0, 0, 0, 0};
-  if (my_ptiles > 0) {
-    const int4 b4 = *reinterpret_cast<const int4 *>(a.bp2 + member * 32 + 8 * (tid >> 6) + 4 * ((tid & 63) >> 5));
-    bpr[0] = b4.x; bpr[1] = b4.y; bpr[2] = b4.z; bpr[3] = b4.w;
-  }
+  if (my_ptiles > 0 && tid < 32) bpL[tid] = a.bp2[member * 32 + tid];  // the first tile's projection bias
 
   if (tid < 16) tickL[tid] = 0;
   if (tid < items) red[tid] = 0;
@@ -350,8 +370,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   unsigned epoch = 0;
   unsigned *counter = a.counters + group * 64;
   u64 *accS = a.acc + (size_t)group * kStatGroupWords;  // [set][round][S1|S2][item]
-  int64_t prevS[2][2][2] = {{{0, 0}, {0, 0}}, {{0, 0}, {0, 0}}};  // this thread's item, per round and set: S1, S2
-  const double inv_n = 1.0 / (double)a.N;
+  uint32_t prev1[2] = {0, 0};  // this thread's item, per round: the sums of the statistics words as last read
+  u64 prev2[2] = {0, 0};
   const int g_first = cifg ? 1 : 0;
   // uniform: some shift of the layer norm's second stage / of the hidden state's rescale is below 33
   const bool pre_ln = ln && (a.rln[0] < 33 || a.rln[1] < 33 || a.rln[2] < 33 || a.rln[3] < 33);
@@ -361,80 +381,83 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   // ticks per phase, summed in LDS (an add that returns nothing, so the timer
   // waits for no memory) and written out after the last step
   long long tick_last = 0;
-  const bool timing = a.ticks && wg == 0 && tid == 0;
+  const bool timing = a.ticks && wg == 0 && wave == 0;  // uniform
 #define TICK(i)                                                                           \
   do {                                                                                    \
     if (timing) {                                                                         \
       asm volatile("" ::: "memory");                                                      \
       const long long now = (long long)wall_clock64();                                    \
-      __hip_atomic_fetch_add(&tickL[i], (u64)(now - tick_last), __ATOMIC_RELAXED,         \
-                             __HIP_MEMORY_SCOPE_WORKGROUP);                               \
+      if (lane == 0)                                                                      \
+        __hip_atomic_fetch_add(&tickL[i], (u64)(now - tick_last), __ATOMIC_RELAXED,       \
+                               __HIP_MEMORY_SCOPE_WORKGROUP);                             \
       tick_last = now;                                                                    \
     }                                                                                     \
   } while (0)
   if (timing) {
     tick_last = t_start;
-    __hip_atomic_store(&a.ticks[15], t_start, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane == 0) __hip_atomic_store(&a.ticks[15], t_start, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   TICK(10);  // everything before the first step
 
-  // the two 16-byte W x pieces of (rt, tile) for step t
-  auto tx_ptr = [&](int t, int rt, int tl) -> const int4 * {
+  // the two 16-byte W x pieces of row tile rt for step t
+  auto tx_ptr = [&](int t, int rt) -> const int4 * {
     size_t rb = ((size_t)t * a.Bp + row0 + rt * 32) >> 5;
     const size_t rbmax = ((size_t)a.T * a.Bp) >> 5;
     rb = rb < rbmax ? rb : rbmax - 1;
-    return a.tx2 + ((rb * (size_t)(GS * 8) + member * 8 + wave * 2 + tl) * 2) * 64 + lane;
+    return a.tx2 + ((rb * (size_t)(GS * 8) + member * 8 + wave) * 2) * 64 + lane;
   };
 
-
-  // The W x terms of a step come from memory, not from a cache.  The dense kernel asks for them after the h tile
-  // is in LDS: the MFMA phase covers the latency.  The sparse kernel's MFMA phase is too short for that (measured:
-  // the gate sums, and then the whole group at the statistics, waited for the slowest workgroup's terms), so it
-  // asks for the terms of step t before the last barrier of step t - 1 (those of step 0 ahead of the loop).
-  // That is not free -- the polling wave's loads return in issue order, so its polls wait behind its own W x
-  // loads -- which is why the dense kernel does not do the same (measured: 1.2 % slower with it).
-  constexpr bool TX_AHEAD = SP;
-  int4 txv[RT][2][2];
+  // The W x terms of a step come from memory, not from a cache: those of step t + 1 are asked for when step t has its
+  // row statistics (or its gate sums, without a layer norm), under the cell's arithmetic and ahead of the stores of m.
+  // (Two row tiles have no registers for that: they ask when the h tile is in LDS, and R h of both covers most of it.)
+  int4 txv[RT][2];
   auto load_tx = [&](int t) {
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-      for (int tl = 0; tl < 2; ++tl) {
-        const int4 *src = tx_ptr(t, rt, tl);  // clamped to the last row block: step T reads step T - 1's again
-        // read once: a streaming load keeps the W x terms from displacing the exchange buffers in L2
-        const v4i t0 = __builtin_nontemporal_load(reinterpret_cast<const v4i *>(src));
-        const v4i t1 = __builtin_nontemporal_load(reinterpret_cast<const v4i *>(src + 64));
-        txv[rt][tl][0] = int4{t0.x, t0.y, t0.z, t0.w};
-        txv[rt][tl][1] = int4{t1.x, t1.y, t1.z, t1.w};
-      }
+    for (int rt = 0; rt < RT; ++rt) {
+      const int4 *src = tx_ptr(t, rt);  // clamped to the last row block: step T reads step T - 1's again
+      // read once: a streaming load keeps the W x terms from displacing the exchange buffers in L2
+      const v4i t0 = __builtin_nontemporal_load(reinterpret_cast<const v4i *>(src));
+      const v4i t1 = __builtin_nontemporal_load(reinterpret_cast<const v4i *>(src + 64));
+      txv[rt][0] = int4{t0.x, t0.y, t0.z, t0.w};
+      txv[rt][1] = int4{t1.x, t1.y, t1.z, t1.w};
+    }
   };
-  constexpr int TXLOADS = TX_AHEAD ? RT * 4 : 0;  // vector loads in flight across the step's last barrier
-  if (TX_AHEAD && a.T > 0) load_tx(0);
+  if (RT == 1 && a.T > 0) load_tx(0);
 
+  const int tid0 = tid;
+  const bool tails = a.lut[0].tail | a.lut[1].tail | a.lut[2].tail;  // some table's LDS copy ends before its flat part
+  // this lane's operand row of W_proj; rows beyond a tile's prow outputs re-read row 0: their results are never stored
+  const int wp_lane = (col < a.prow ? col : 0) * WLS + (b2 << 4);
   for (int t = 0; t < a.T; ++t) {
+    // Addresses of a lane are computed anew in every step: kept from before the loop they would cost registers that the
+    // compiler then finds in scratch memory, whose loads return behind the W x terms on their way from HBM.
+    int tid = tid0;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, col = lane & 31, b2 = lane >> 5, cell_w = wave * 8 + 4 * b2;
     // ---- h^{t-1} rows of the group -> LDS
     {
       const int8_t *hp = t == 0 ? a.h0 : a.out + (size_t)(t - 1) * a.B * a.Hpad;
+      asm volatile("" : "+s"(hp));  // one scalar base: not a pointer per lane for each of the two
 #pragma unroll
-      for (int j = 0; j < NCH; ++j)  // chunks past the tile land in the spare chunk behind it
-        __builtin_amdgcn_global_load_lds(
-              (const __attribute__((address_space(1))) void *)(hp + hsrc[j]),
-              (__attribute__((address_space(3))) void *)(lds + (wave + 4 * j < TILE_KB ? wave + 4 * j : TILE_KB) * 1024),
-              16, 0, 0);
+      for (int j = 0; j < NCH; ++j)
+        if (WAVES * (j + 1) <= TILE_KB || wave + WAVES * j < TILE_KB) {
+          unsigned o = hsrc[j];
+          asm volatile("" : "+v"(o));  // widened here, not kept widened
+          __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(hp + o),
+                                           (__attribute__((address_space(3))) void *)(hT + (wave + WAVES * j) * 1024), 16, 0, 0);
+        }
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
     __syncthreads();
-    if (!TX_AHEAD) load_tx(t);
+    if (RT > 1) load_tx(t);
     TICK(0);
 
-    // ---- R h on the MFMA: acc[rt][tile][4*gate + c]
-    v16i acc[RT][2];
+    // ---- R h on the MFMA: acc[rt][4*gate + c]
+    v16i acc[RT];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-      for (int tl = 0; tl < 2; ++tl)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[rt][tl][v] = bhL[(v >> 2) * 64 + cell_w + tl * 8 + (v & 3)];
+      for (int v = 0; v < 16; ++v) acc[rt][v] = bhL[(v >> 2) * 64 + cell_w + (v & 3)];
     if constexpr (SP) {
       constexpr int DEPTH = 2;  // 64-deep h fragments in flight ahead of the MFMAs
       v8i hf[RT][DEPTH];
@@ -453,15 +476,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       for (int kq = 0; kq < KW; ++kq) {
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
-#pragma unroll
-          for (int tl = 0; tl < 2; ++tl)
-            acc[rt][tl] = __builtin_amdgcn_smfmac_i32_32x32x64_i8(Wf[tl][kq], hf[rt][kq % DEPTH], acc[rt][tl], Wi[tl][kq], 0, 0);
+          acc[rt] = __builtin_amdgcn_smfmac_i32_32x32x64_i8(Wf[kq], hf[rt][kq % DEPTH], acc[rt], Wi[kq], 0, 0);
           if (kq + DEPTH < KW) hf[rt][kq % DEPTH] = frag(rt, kq + DEPTH);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
     } else {
-      constexpr int DEPTH = 4;  // h fragments in flight ahead of the MFMAs
+      constexpr int DEPTH = RT == 1 ? 4 : 2;  // h fragments in flight ahead of the MFMAs
       v4i hf[RT][DEPTH];
       const int8_t *hbase = hT + (size_t)col * LS + (b2 << 4);
 #pragma unroll
@@ -474,9 +495,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       for (int ks = 0; ks < KS; ++ks) {
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
-#pragma unroll
-          for (int tl = 0; tl < 2; ++tl)
-            acc[rt][tl] = __builtin_amdgcn_mfma_i32_32x32x32_i8(Wf[tl][ks], hf[rt][ks % DEPTH], acc[rt][tl], 0, 0, 0);  // acc starts from the folded bias
+          acc[rt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(Wf[ks], hf[rt][ks % DEPTH], acc[rt], 0, 0, 0);  // acc starts from the folded bias
           if (ks + DEPTH < KS)
             hf[rt][ks % DEPTH] = *reinterpret_cast<const v4i *>(hbase + (size_t)rt * 32 * LS + (ks + DEPTH) * 32);
         }
@@ -494,38 +513,33 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       constexpr int PRE = decltype(pre_tag)::value;  // operand treatment of the R h rescale (RecArgs::pre_h)
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
+        if (RT > 1) __builtin_amdgcn_sched_barrier(0);  // the row tiles one after the other: both at once do not fit the registers
         int32_t s1[4] = {0, 0, 0, 0};
-        uint32_t s2[4][2] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};  // four squares of 16-bit values fit 32 bits
+        uint32_t s2[4] = {0, 0, 0, 0};  // four squares of 16-bit values fit 32 bits
+        const int32_t txw[8] = {txv[rt][0].x, txv[rt][0].y, txv[rt][0].z, txv[rt][0].w,
+                                txv[rt][1].x, txv[rt][1].y, txv[rt][1].z, txv[rt][1].w};
 #pragma unroll
-        for (int tl = 0; tl < 2; ++tl) {
-          const int32_t txw[8] = {txv[rt][tl][0].x, txv[rt][tl][0].y, txv[rt][tl][0].z, txv[rt][tl][0].w,
-                                  txv[rt][tl][1].x, txv[rt][tl][1].y, txv[rt][tl][1].z, txv[rt][tl][1].w};
+        for (int g = 0; g < 4; ++g) {
+          const RescaleHi pg = prm->h[g];
 #pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const RescaleHi pg = prm->h[g];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-              const int idx = g * 4 + c;
-              const int32_t th = rescale_sat16_pre<PRE>(acc[rt][tl][idx], pg);
-              const int32_t w = txw[idx >> 1];
-              const int32_t tx = (idx & 1) ? (w >> 16) : (int32_t)(int16_t)(w & 0xFFFF);
-              int32_t v = tx + th;
-              if (ph && g < 2) {
-                const int cl = cell_w + tl * 8 + c;
-                v += rescale_sat16_pre(mul_i24(PqL[g * 64 + cl], creg[rt][tl][c]), prm->c[g]);
-              }
-              if (!(ph && g == 3)) v = clamp_i32(v, glo, 32767);
-              acc[rt][tl][idx] = v;
-              s1[g] += v;
-              s2[g][tl] += (uint32_t)v * (uint32_t)v;
-            }
+          for (int c = 0; c < 4; ++c) {
+            const int idx = g * 4 + c;
+            const int32_t th = rescale_sat16_pre<PRE>(acc[rt][idx], pg);
+            const int32_t w = txw[idx >> 1];
+            const int32_t tx = (idx & 1) ? (w >> 16) : (int32_t)(int16_t)(w & 0xFFFF);
+            int32_t v = tx + th;
+            if (ph && g < 2) v += rescale_sat16_pre(mul_i24(PqL[g * 64 + cell_w + c], creg[rt][c]), prm->c[g]);
+            if (!(ph && g == 3)) v = clamp_i32(v, glo, 32767);
+            acc[rt][idx] = v;
+            s1[g] += v;
+            s2[g] += (uint32_t)v * (uint32_t)v;
           }
         }
         if (ln) {
 #pragma unroll
           for (int g = 0; g < (ph ? 3 : 4); ++g) {  // with a peephole the o gate follows after c^t
-            // the 8 lanes of a row (2 per wave) add into one LDS word: no cross-lane traffic, no wait
-            const int64_t pk = ((int64_t)((u64)s2[g][0] + (u64)s2[g][1]) << 24) + s1[g];
+            // the 16 lanes of a row (2 per wave) add into one LDS word: no cross-lane traffic, no wait
+            const int64_t pk = ((int64_t)(u64)s2[g] << 24) + s1[g];
             __hip_atomic_fetch_add(&red[(rt * 4 + g) * 32 + col], (u64)pk, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_WORKGROUP);
           }
@@ -595,17 +609,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             }
             for (int i = 0; i < a.stats_sleep; ++i) __builtin_amdgcn_s_sleep(1);
           }
-          int64_t S1 = -(int64_t)GS * (1 << 22), S2 = 0;
-#pragma unroll
-          for (int ss = 0; ss < 2; ++ss) {
-            c1[ss] &= kValMask;
-            c2[ss] &= kValMask;
-            S1 += (int64_t)((c1[ss] - (u64)prevS[round][ss][0]) & kValMask);
-            S2 += (int64_t)((c2[ss] - (u64)prevS[round][ss][1]) & kValMask);
-            prevS[round][ss][0] = (int64_t)c1[ss];
-            prevS[round][ss][1] = (int64_t)c2[ss];
-          }
-          lnrow[tid] = ln_row2(S1, S2, a.N, inv_n);
+          // the sets' value fields together, less those of the step before; a step adds less than 2^29 and 2^42
+          const uint32_t now1 = (uint32_t)c1[0] + (uint32_t)c1[1];
+          const u64 now2 = (c2[0] + c2[1]) & kValMask;
+          const int64_t S1 = (int64_t)(now1 - prev1[round]) - (int64_t)GS * (1 << 22);
+          const int64_t S2 = (int64_t)((now2 - prev2[round]) & kValMask);
+          prev1[round] = now1;
+          prev2[round] = now2;
+          int n = a.N;
+          asm volatile("" : "+s"(n));  // its conversions to double are made here, not kept
+          lnrow[tid] = ln_row2(S1, S2, n, prm->inv_n);
         }
       }
       __syncthreads();
@@ -618,6 +631,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       if (!collect_stats(0, g_first, ph ? 2 : 3)) return;
       TICK(4);
     }
+    if (RT == 1) load_tx(t + 1);
 
     // ---- layer norm, sigma/tanh, cell update (Secs. 3.2.6, 3.2.1, 3.2.9, 3.2.7),
     // in batches of one weight tile (up to 4 gates x 4 cells of a row).  Every
@@ -625,9 +639,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     // scheduling barriers keep the compiler from sinking each read next to its
     // use, which exposes one LDS round trip per element (measured: more than
     // half of this phase).
-    // gates of `gmask` (bit g) of tile (rt, tl): gate sums -> layer norm -> xv[g][c]
-    constexpr int LNB = KS >= 32 ? 1 : 2;  // the deepest register-resident R leaves room for less
-    auto normalize = [&](int rt, int tl, int gmask, const LnRow2 (&lr)[4], int32_t (&xv)[4][4], bool narrow) {
+    // gates of `gmask` (bit g) of row tile rt: gate sums -> layer norm -> xv[g][c]
+    constexpr int LNB = RT == 1 ? 2 : 1;
+    auto normalize = [&](int rt, int gmask, const LnRow2 (&lr)[4], int32_t (&xv)[4][4], bool narrow, auto sat_tag) {
+      constexpr bool SAT = decltype(sat_tag)::value;  // false: the lookup that follows clamps the magnitude anyway
       if (ln) {
 #pragma unroll
         for (int gp = 0; gp < 4; gp += LNB) {  // LNB gates per batch of reads: 8 LNB doubles in flight
@@ -640,8 +655,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
               pl[g - gp] = prm->ln[g];
 #pragma unroll
               for (int c = 0; c < 4; ++c) {
-                wL[g - gp][c] = LdL[g * 64 + cell_w + tl * 8 + c];
-                wb[g - gp][c] = bdL[g * 64 + cell_w + tl * 8 + c];
+                wL[g - gp][c] = LdL[g * 64 + cell_w + c];
+                wb[g - gp][c] = bdL[g * 64 + cell_w + c];
               }
             }
           __builtin_amdgcn_sched_barrier(0);
@@ -650,8 +665,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             if (gmask >> g & 1)
 #pragma unroll
               for (int c = 0; c < 4; ++c)
-                xv[g][c] = narrow ? ln_second_stage_narrow(acc[rt][tl][g * 4 + c], lr[g], wL[g - gp][c], wb[g - gp][c])
-                                  : ln_second_stage(acc[rt][tl][g * 4 + c], lr[g], wL[g - gp][c], wb[g - gp][c]);
+                xv[g][c] = narrow ? ln_second_stage_narrow(acc[rt][g * 4 + c], lr[g], wL[g - gp][c], wb[g - gp][c])
+                                  : ln_second_stage(acc[rt][g * 4 + c], lr[g], wL[g - gp][c], wb[g - gp][c]);
           if (pre_ln) {  // some second-stage shift is below 33 (uniform; rare)
 #pragma unroll
             for (int g = gp; g < gp + LNB; ++g)
@@ -663,18 +678,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
           for (int g = gp; g < gp + LNB; ++g)
             if (gmask >> g & 1)
 #pragma unroll
-              for (int c = 0; c < 4; ++c) xv[g][c] = rescale_sat16_pre<0>(xv[g][c], pl[g - gp]);
+              for (int c = 0; c < 4; ++c) xv[g][c] = SAT ? rescale_sat16_pre<0>(xv[g][c], pl[g - gp]) : rescale_hi_pre(xv[g][c], pl[g - gp]);
         }
       } else {
 #pragma unroll
         for (int g = 0; g < 4; ++g)
           if (gmask >> g & 1)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) xv[g][c] = acc[rt][tl][g * 4 + c];
+            for (int c = 0; c < 4; ++c) xv[g][c] = acc[rt][g * 4 + c];
       }
     };
     // table values of |xv[g][c]| for the gates of gmask; tb[g] = which table (0 sigma, 1 tanh, 2 cell tanh)
-    auto lookup = [&](int gmask, const int32_t (&xv)[4][4], const int (&tb)[4], int32_t (&tv)[4][4]) {
+    auto lookup = [&](int gmask, const int32_t (&xv)[4][4], const int (&tb)[4], int32_t (&tv)[4][4], auto tails_tag) {
+      constexpr bool TAILS = decltype(tails_tag)::value;
       int32_t mag[4][4];
       uint32_t base[4][4], delta[4][4];
       int32_t top[3] = {0, 0, 0};  // largest |x| looked up in each table
@@ -693,8 +709,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
           const int dom = lp[tb[g]].dom, sh = lp[tb[g]].sh;
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
-            mag[g][c] = abs_i32(xv[g][c]);  // at most 2^15
-            top[tb[g]] = top[tb[g]] > mag[g][c] ? top[tb[g]] : mag[g][c];
+            mag[g][c] = abs_masked(xv[g][c]);  // at most 2^15
+            if (TAILS) top[tb[g]] = top[tb[g]] > mag[g][c] ? top[tb[g]] : mag[g][c];
             const int32_t ai = mag[g][c] < dom ? mag[g][c] : dom - 1;
             base[g][c] = *reinterpret_cast<const uint16_t *>(lds + lp[tb[g]].offB + 2 * (ai >> sh));
             delta[g][c] = lds[lp[tb[g]].offD + ai];
@@ -712,6 +728,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       // thousand, i.e. some lane of most batches -- and the step then waits for the slowest of the group's
       // 128 waves; with 24576 entries it is one in a million.  The tests narrow down from the batch to the
       // gate to the cell.
+      if (!TAILS) return;
       bool over = false;
 #pragma unroll
       for (int i = 0; i < 3; ++i) {
@@ -736,9 +753,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     };
     const int gate_tb[4] = {0, 0, 1, 0};
     constexpr int gates_now = (cifg ? 0 : 1) | 2 | 4 | (ph ? 0 : 8);  // with a peephole the o gate waits for c^t
-    int32_t xi[RT][2][4], xf[RT][2][4], xz[RT][2][4], xo[RT][2][4];
+    const int32_t m_c = prm->m_c;
+    int32_t xo[RT][4];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
+      if (RT > 1) __builtin_amdgcn_sched_barrier(0);
       LnRow2 lr[4];
       bool narrow = false;  // uniform: every row of this wave has sigma >= 2^12, the second stage stays within int32
       if (ln) {
@@ -750,51 +769,37 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         }
         narrow = __builtin_amdgcn_ballot_w64(wide) == 0;
       }
-#pragma unroll
-      for (int tl = 0; tl < 2; ++tl) {
-        int32_t xv[4][4], tv[4][4];
-        if (narrow)
-          normalize(rt, tl, gates_now, lr, xv, true);
-        else
-          normalize(rt, tl, gates_now, lr, xv, false);
-        if (KS >= 32) {  // the deepest register-resident R leaves room for two gates' reads at a time
-          lookup(gates_now & 3, xv, gate_tb, tv);
-          lookup(gates_now & 12, xv, gate_tb, tv);
+      int32_t xv[4][4], tv[4][4];
+      if ((!ln || narrow) && !tails) {
+        normalize(rt, gates_now, lr, xv, true, std::false_type{});
+        lookup(gates_now, xv, gate_tb, tv, std::false_type{});
+      } else {
+        asm volatile("");  // keeps what both forms begin with from being computed ahead of them, for all gates at once
+        if (narrow) {
+          normalize(rt, gates_now, lr, xv, true, std::true_type{});
         } else {
-          lookup(gates_now, xv, gate_tb, tv);
+          asm volatile("");
+          normalize(rt, gates_now, lr, xv, false, std::true_type{});
         }
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          xi[rt][tl][c] = cifg ? 0 : mirror_sigmoid(xv[0][c], tv[0][c]);
-          xf[rt][tl][c] = mirror_sigmoid(xv[1][c], tv[1][c]);
-          xz[rt][tl][c] = mirror_tanh(xv[2][c], tv[2][c]);
-          xo[rt][tl][c] = ph ? 0 : mirror_sigmoid(xv[3][c], tv[3][c]);
-        }
+        lookup(gates_now, xv, gate_tb, tv, std::true_type{});
       }
-    }
-    const int32_t m_c = prm->m_c;
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
       int32_t s1 = 0;
       int64_t s2 = 0;
 #pragma unroll
-      for (int tl = 0; tl < 2; ++tl)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const int32_t f = xf[rt][tl][c];
-          const int32_t i = cifg ? cifg_input_gate(f) : xi[rt][tl][c];
-          const int32_t cnew = cell_update32(i, xz[rt][tl][c], f, creg[rt][tl][c], m_c);
-          creg[rt][tl][c] = cnew;
-          if (ph) {  // finish the o gate sum with P_o . c^t (eq. 5)
-            const int cl = cell_w + tl * 8 + c;
-            int32_t v = acc[rt][tl][12 + c] +
-                        rescale_sat16_pre(mul_i24(PqL[2 * 64 + cl], cnew), prm->c[2]);
-            v = clamp_i32(v, glo, 32767);
-            acc[rt][tl][12 + c] = v;
-            s1 += v;
-            s2 += (int64_t)v * v;
-          }
+      for (int c = 0; c < 4; ++c) {
+        xo[rt][c] = ph ? 0 : mirror_sigmoid_masked(xv[3][c], tv[3][c]);
+        const int32_t f = mirror_sigmoid_masked(xv[1][c], tv[1][c]);
+        const int32_t i = cifg ? cifg_input_gate(f) : mirror_sigmoid_masked(xv[0][c], tv[0][c]);
+        const int32_t cnew = cell_update32(i, mirror_tanh_masked(xv[2][c], tv[2][c]), f, creg[rt][c], m_c);
+        creg[rt][c] = cnew;
+        if (ph) {  // finish the o gate sum with P_o . c^t (eq. 5)
+          int32_t v = acc[rt][12 + c] + rescale_sat16_pre(mul_i24(PqL[2 * 64 + cell_w + c], cnew), prm->c[2]);
+          v = clamp_i32(v, glo, 32767);
+          acc[rt][12 + c] = v;
+          s1 += v;
+          s2 += (int64_t)v * v;
         }
+      }
       if (ph && ln) {
         const int64_t pk = (s2 << 24) + s1;
         __hip_atomic_fetch_add(&red[(rt * 4 + 3) * 32 + col], (u64)pk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -810,33 +815,33 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 
     // ---- hidden state (Sec. 3.2.7); m is int8.  tanh of the new cell state in its
     // own format (Sec. 3.2.2), and with a peephole the layer norm and sigma of the o gate
-    int32_t tc[RT][2][4];
+    int32_t tc[RT][4];
     {
-      const int hid_tb[4] = {2, 2, 0, 0};  // c^t of the two weight tiles, then the o gate sums of the two
+      const int hid_tb[4] = {2, 0, 0, 0};  // c^t, then the o gate sums
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
+        if (RT > 1) __builtin_amdgcn_sched_barrier(0);
         LnRow2 lr[4];
         if (ph && ln) lr[3] = lnrow[(rt * 4 + 3) * 32 + col];
-        // one batch per row tile: c^t of both weight tiles in slots 0 and 1, the o gate sums in 2 and 3
-        int32_t xv[4][4], tv[4][4], ov[2][4][4];
+        int32_t xv[4][4], tv[4][4], ov[4][4];
 #pragma unroll
-        for (int tl = 0; tl < 2; ++tl) {
+        for (int c = 0; c < 4; ++c) xv[0][c] = creg[rt][c];
+        if (ph) {
+          normalize(rt, 8, lr, ov, false, std::true_type{});
 #pragma unroll
-          for (int c = 0; c < 4; ++c) xv[tl][c] = creg[rt][tl][c];
-          if (ph) {
-            normalize(rt, tl, 8, lr, ov[tl], false);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) xv[2 + tl][c] = ov[tl][3][c];
-          }
+          for (int c = 0; c < 4; ++c) xv[1][c] = ov[3][c];
         }
-        lookup(ph ? 15 : 3, xv, hid_tb, tv);
+        if (tails) {
+          asm volatile("");
+          lookup(ph ? 3 : 1, xv, hid_tb, tv, std::true_type{});
+        } else {
+          lookup(ph ? 3 : 1, xv, hid_tb, tv, std::false_type{});
+        }
 #pragma unroll
-        for (int tl = 0; tl < 2; ++tl)
-#pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            tc[rt][tl][c] = mirror_tanh(xv[tl][c], tv[tl][c]);
-            if (ph) xo[rt][tl][c] = mirror_sigmoid(xv[2 + tl][c], tv[2 + tl][c]);
-          }
+        for (int c = 0; c < 4; ++c) {
+          tc[rt][c] = mirror_tanh_masked(xv[0][c], tv[0][c]);
+          if (ph) xo[rt][c] = mirror_sigmoid_masked(xv[1][c], tv[1][c]);
+        }
       }
     }
     // Without a projection m is h and goes to the layer output [T, B, Hpad].  With one it goes to the
@@ -848,26 +853,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
       const int row = row0 + rt * 32 + col;
+      const int n0 = member * 64 + cell_w;
+      uint32_t pk = 0;
 #pragma unroll
-      for (int tl = 0; tl < 2; ++tl) {
-        const int n0 = member * 64 + cell_w + tl * 8;
-        uint32_t pk = 0;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          // sat8 of the sum is unchanged by the 16-bit clamp before it: |zp| <= 128
-          int32_t om = mul_i24(xo[rt][tl][c], tc[rt][tl][c]);  // below 2^30 in magnitude
-          if (pre_m) om = rescale_preshift(om, pm);
-          const int32_t mq = sat8(rescale_sat16_pre<0>(om, pm) + zp_m);
-          pk |= (uint32_t)(mq & 0xFF) << (8 * c);
-        }
-        if (row < a.B && n0 < a.N) {  // cells past N fill padding of the row (and only ever meet zero weights)
-          const size_t off = proj ? ((((size_t)(row >> 5) * (a.npadp >> 5) + (n0 >> 5)) * 32 + (row & 31)) * 32 + (n0 & 31))
-                                  : (size_t)row * a.Hpad + n0;
-          *reinterpret_cast<uint32_t *>(mdst + off) = pk;
-          if (!proj && a.y) {
-            int8_t *yd = a.y + ((size_t)t * a.B + row) * a.H + n0;  // H = N, a multiple of 4 (y is NULL otherwise)
-            __builtin_nontemporal_store(pk, reinterpret_cast<uint32_t *>(yd));  // not read again here
-          }
+      for (int c = 0; c < 4; ++c) {
+        // sat8 of the sum is unchanged by the 16-bit clamp before it: |zp| <= 128
+        int32_t om = mul_i24(xo[rt][c], tc[rt][c]);  // below 2^30 in magnitude
+        if (pre_m) om = rescale_preshift(om, pm);
+        const int32_t mq = sat8(rescale_sat16_pre<0>(om, pm) + zp_m);
+        pk |= (uint32_t)(mq & 0xFF) << (8 * c);
+      }
+      if (row < a.B && n0 < a.N) {  // cells past N fill padding of the row (and only ever meet zero weights)
+        // scalar bases, 32-bit offsets of the lane: pointers of the lane's own would be held through the loop
+        int8_t *mb = mdst + (proj ? ((size_t)((row0 >> 5) + rt) * (a.npadp >> 5) + member * 2 + (wave >> 2)) * 1024
+                                  : (size_t)(row0 + rt * 32) * a.Hpad + member * 64);
+        *reinterpret_cast<uint32_t *>(mb + (unsigned)(proj ? col * 32 + (wave & 3) * 8 + 4 * b2 : col * a.Hpad + cell_w)) = pk;
+        if (!proj && a.y) {
+          int8_t *yb = a.y + ((size_t)t * a.B + row0 + rt * 32) * a.H + member * 64;  // H = N, a multiple of 4 (y is NULL otherwise)
+          __builtin_nontemporal_store(pk, reinterpret_cast<uint32_t *>(yb + (unsigned)(col * a.H + cell_w)));  // not read again here
         }
       }
     }
@@ -875,99 +878,105 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     if (proj) {
       if (!group_sync(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, a.sync_sleep, a.poll_sleep, flag)) return;
     } else {
-      if (TX_AHEAD) load_tx(t + 1);
-      if (!group_sync<TXLOADS>(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, a.sync_sleep, a.poll_sleep, flag)) return;
+      if (!group_sync(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, a.sync_sleep, a.poll_sleep, flag)) return;
     }
     TICK(7);
 
-    // ---- projection (Sec. 3.2.8): tile pt of 32 outputs, K = N split over the four waves
+    // ---- projection (Sec. 3.2.8): tile pt of 32 outputs, K = N split over the eight waves
     if (proj) {
-
-      const int per_wave = a.npadp >> 7;  // 32-wide k steps per wave, at most 16 (N <= 2048)
-      const RescaleHi pp = prm->p;
-      const int32_t zp_h = prm->zp_h;
+      const int ksteps = a.npadp >> 5;     // 32-wide k steps, a multiple of 4, at most 64 (N <= 2048)
+      const int per_wave = (ksteps + 7) >> 3;
+      const int kfirst = wave * per_wave;  // the last waves may have fewer, or none
       for (int pt = 0; pt < my_ptiles; ++pt) {
         const int ptile = member + pt * GS;
+        const int8_t *wrow = WpL + wp_lane + pt * a.prow * WLS + kfirst * 32;
+        const int kmine = ksteps - kfirst < per_wave ? ksteps - kfirst : per_wave;  // uniform
+        v4i mv[8];
+        auto load_m = [&](int rt) {
+          // rows of the tile beyond the batch were never written; their results are not stored either
+          const int8_t *mrow = a.mbuf + (size_t)t * a.Bp * a.npadp + ((size_t)((row0 >> 5) + rt) * ksteps + kfirst) * 1024;
+          const unsigned moff = col * 32 + b2 * 16;
+          if (ksteps == 64) {  // N = 2048: eight steps for every wave
+#pragma unroll
+            for (int k = 0; k < 8; ++k) mv[k] = *reinterpret_cast<const v4i *>(mrow + moff + k * 1024);
+            __builtin_amdgcn_sched_barrier(0);
+          } else {
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+              if (k < kmine) mv[k] = *reinterpret_cast<const v4i *>(mrow + moff + k * 1024);
+          }
+        };
+        // a row tile that starts beyond the batch (second tile of a ragged last group) has no rows in the exchange buffer
+        // at all; the test is uniform over the workgroup, so the barriers below stay matched
+        auto has_rows = [&](int rt) { return rt == 0 || (rt < RT && row0 + rt * 32 < a.B); };
+        load_m(0);
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
-          // a row tile that starts beyond the batch (second tile of a ragged last group) has no rows in the
-          // exchange buffer at all; the test is uniform over the workgroup, so the barriers below stay matched
-          if (rt > 0 && row0 + rt * 32 >= a.B) continue;
-          // rows of the tile beyond the batch were never written; their results are not stored either
-          const int8_t *mrow = a.mbuf + (size_t)t * a.Bp * a.npadp +
-                               ((((size_t)((row0 >> 5) + rt) * (a.npadp >> 5) + wave * per_wave) * 32 + col) << 5) +
-                               (b2 << 4);
-          // operand rows beyond the tile's prow outputs re-read row 0: their results are never stored
-          const int8_t *wrow = WpL + ((size_t)pt * a.prow + (col < a.prow ? col : 0)) * WLS + (b2 << 4) + wave * per_wave * 32;
-          int4 mv[16];
-#pragma unroll
-          for (int k = 0; k < 16; ++k) {
-            const int kk = k < per_wave ? k : per_wave - 1;  // steps past the end re-read the last one
-            mv[k] = *reinterpret_cast<const int4 *>(mrow + kk * 1024);
-          }
+          if (!has_rows(rt)) continue;
           v16i pacc;
 #pragma unroll
           for (int v = 0; v < 16; ++v) pacc[v] = 0;
-          if (per_wave == 16) {  // N = 2048: no padding step, no operand select
+          if (ksteps == 64) {
 #pragma unroll
-            for (int k = 0; k < 16; ++k) {
-              const v4i wf = *reinterpret_cast<const v4i *>(wrow + k * 32);
-              pacc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf, v4i{mv[k].x, mv[k].y, mv[k].z, mv[k].w}, pacc, 0, 0, 0);
-            }
+            for (int k = 0; k < 8; ++k)
+              pacc = __builtin_amdgcn_mfma_i32_32x32x32_i8(*reinterpret_cast<const v4i *>(wrow + k * 32), mv[k], pacc, 0, 0, 0);
           } else {
 #pragma unroll
-            for (int k = 0; k < 16; ++k) {
-              const int kk = k < per_wave ? k : per_wave - 1;
-              v4i wf = *reinterpret_cast<const v4i *>(wrow + kk * 32);
-              if (k >= per_wave) wf = v4i{0, 0, 0, 0};  // ... against zero weights
-              pacc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf, v4i{mv[k].x, mv[k].y, mv[k].z, mv[k].w}, pacc, 0, 0, 0);
-            }
+            for (int k = 0; k < 8; ++k)
+              if (k < kmine)
+                pacc = __builtin_amdgcn_mfma_i32_32x32x32_i8(*reinterpret_cast<const v4i *>(wrow + k * 32), mv[k], pacc, 0, 0, 0);
           }
+          if (has_rows(rt + 1)) load_m(rt + 1);  // on their way while this tile's sums are added up
+          // result v of a lane: output 8 (v / 4) + 4 (lane / 32) + v % 4 of row lane % 32.  Eight partial sums in LDS, or
+          // four where a layer's W_proj leaves no room for them: two waves then share a slot, one after the other
+          const int own = ((wave & (four_slots ? 3 : 7)) << 8) + lane;
+          if (!four_slots || wave >= 4)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) pred[(wave * 16 + v) * 64 + lane] = pacc[v];
+            for (int q = 0; q < 4; ++q) pred[own + q * 64] = v4i{pacc[4 * q], pacc[4 * q + 1], pacc[4 * q + 2], pacc[4 * q + 3]};
           __syncthreads();
-          {
-            // thread (q = tid / 64, lane' = tid % 64): outputs 8q + 4*(lane'/32) + 0..3 of row lane' % 32
-            const int q = tid >> 6, l2 = tid & 63;
-            const int pl = 8 * q + 4 * (l2 >> 5);  // row of the tile; prow is a multiple of 4
+          if (four_slots) {
+            if (wave < 4)
+#pragma unroll
+              for (int q = 0; q < 4; ++q) pred[own + q * 64] += v4i{pacc[4 * q], pacc[4 * q + 1], pacc[4 * q + 2], pacc[4 * q + 3]};
+            __syncthreads();
+          }
+          if (4 * wave < a.prow) {  // a thread finishes the outputs pl, pl + 1 of row `col`; prow is a multiple of 4
+            const int pl = 4 * wave + 2 * b2;
+            const v2i *mine = reinterpret_cast<const v2i *>(pred) + (wave << 6) + 2 * col + b2;
+            v2i sum = (mine[0] + mine[512]) + (mine[1024] + mine[1536]);
+            if (!four_slots) sum += (mine[2048] + mine[2560]) + (mine[3072] + mine[3584]);
+            const RescaleHi pp = prm->p;
+            const int32_t zp_h = prm->zp_h;
             const int p0 = ptile * a.prow + pl;
-            const int orow = row0 + rt * 32 + (l2 & 31);
-            uint32_t pk = 0;
+            uint32_t hq[2];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-              const int v = 4 * q + c;
-              const int32_t s = pred[(0 * 16 + v) * 64 + l2] + pred[(1 * 16 + v) * 64 + l2] +
-                                pred[(2 * 16 + v) * 64 + l2] + pred[(3 * 16 + v) * 64 + l2] +
-                                (pt == 0 ? bpr[c] : a.bp2[ptile * 32 + pl + c]);
-              const int32_t hq = sat8(rescale_sat16_pre(s, pp) + zp_h);
-              pk |= (uint32_t)(hq & 0xFF) << (8 * c);
-            }
-            if (orow < a.B && p0 < a.H && pl < a.prow) {
-              int8_t *od = a.out + ((size_t)t * a.B + orow) * a.Hpad + p0;
-              if (p0 + 3 < a.H) {
-                *reinterpret_cast<uint32_t *>(od) = pk;
-              } else {
-                for (int c = 0; c < 4 && p0 + c < a.H; ++c) od[c] = (int8_t)(pk >> (8 * c));
-              }
+            for (int c = 0; c < 2; ++c)
+              hq[c] = (uint32_t)(sat8(rescale_sat16_pre(sum[c] + (pt == 0 ? bpL[pl + c] : a.bp2[ptile * 32 + pl + c]), pp) + zp_h) & 0xFF);
+            if (row0 + rt * 32 + col < a.B && p0 < a.H) {
+              const size_t orow0 = (size_t)t * a.B + row0 + rt * 32;
+              int8_t *od = a.out + orow0 * a.Hpad + ptile * a.prow + (unsigned)(col * a.Hpad + pl);
+              // outputs past H fall into the padding of the row (and only ever meet zero weights)
+              *reinterpret_cast<uint16_t *>(od) = (uint16_t)(hq[0] | hq[1] << 8);
               if (a.y) {
-                int8_t *yd = a.y + ((size_t)t * a.B + orow) * a.H + p0;
-                for (int c = 0; c < 4 && p0 + c < a.H; ++c) yd[c] = (int8_t)(pk >> (8 * c));
+                int8_t *yd = a.y + orow0 * a.H + ptile * a.prow + (unsigned)(col * a.H + pl);
+                yd[0] = (int8_t)hq[0];
+                if (p0 + 1 < a.H) yd[1] = (int8_t)hq[1];
               }
             }
           }
-          __syncthreads();
+          // the last tile's partial sums are overwritten behind the group barrier only
+          if (pt + 1 < my_ptiles || rt + 1 < RT) __syncthreads();
         }
       }
       TICK(8);
-      if (TX_AHEAD) load_tx(t + 1);
-      if (!group_sync<TXLOADS>(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, my_ptiles == 0 ? a.idle_sleep : 0,
+      if (!group_sync(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, my_ptiles == 0 ? a.idle_sleep : 0,
                       my_ptiles == 0 ? a.idle_poll_sleep : a.poll_sleep, flag))
         return;
       TICK(9);
     }
   }
 #undef TICK
-  if (timing)
+  if (timing && lane == 0)
     for (int i = 0; i < 11; ++i) a.ticks[i] += (long long)tickL[i];
   if (a.ticks && tid == 0) {
     // spread of the workgroups' lifetimes against workgroup 0's start (maxima over all launches)
@@ -982,17 +991,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   placement_check();
   if (a.c_out) {
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
+    for (int rt = 0; rt < RT; ++rt) {
+      const int row = row0 + rt * 32 + col;
+      int n0 = member * 64 + cell_w;
+      asm volatile("" : "+v"(n0));  // computed here: shared with the prologue it would hold six registers through the loop
+      if (row < a.B && n0 < a.N)
 #pragma unroll
-      for (int tl = 0; tl < 2; ++tl) {
-        const int row = row0 + rt * 32 + col;
-        int n0 = member * 64 + cell_w + tl * 8;
-        asm volatile("" : "+v"(n0));  // computed here: shared with the prologue it would hold six registers through the loop
-        if (row < a.B && n0 < a.N)
-#pragma unroll
-          for (int c = 0; c < 4; ++c)
-            if (n0 + c < a.N) a.c_out[(size_t)row * a.N + n0 + c] = (int16_t)creg[rt][tl][c];
-      }
+        for (int c = 0; c < 4; ++c)
+          if (n0 + c < a.N) a.c_out[(size_t)row * a.N + n0 + c] = (int16_t)creg[rt][c];
+    }
   }
 }
 
@@ -1021,7 +1028,7 @@ rec_fn rec_pick_ks(int rt, int fl) {
   LSTM_REC_CASE(1, 4) LSTM_REC_CASE(1, 5) LSTM_REC_CASE(1, 6) LSTM_REC_CASE(1, 7)
   LSTM_REC_CASE(1, 8) LSTM_REC_CASE(1, 9) LSTM_REC_CASE(1, 10) LSTM_REC_CASE(1, 11)
   LSTM_REC_CASE(1, 12) LSTM_REC_CASE(1, 13) LSTM_REC_CASE(1, 14) LSTM_REC_CASE(1, 15)
-  if (KS < 32) {
+  if constexpr (KS < 32) {
     LSTM_REC_CASE(2, 0) LSTM_REC_CASE(2, 1) LSTM_REC_CASE(2, 2) LSTM_REC_CASE(2, 3)
     LSTM_REC_CASE(2, 4) LSTM_REC_CASE(2, 5) LSTM_REC_CASE(2, 6) LSTM_REC_CASE(2, 7)
     LSTM_REC_CASE(2, 8) LSTM_REC_CASE(2, 9) LSTM_REC_CASE(2, 10) LSTM_REC_CASE(2, 11)
