@@ -19,7 +19,8 @@
 //      persistent launch instead (gru_seq.hip): weights in registers, one
 //      exchange per step inside an XCD; the input term then comes from the LSTM
 //      path's register-resident input GEMM (in_gemm.hip) in its tile order
-//      where its depth allows.
+//      where its depth allows.  (Depths from 1025 to 2048: deep_gemm.hip, in
+//      the general matmul's order, on either path.)
 // The state is read and written in place (each (row, cell) belongs to one
 // thread); its int8 form is written three times: in operand order for the
 // next step, row-major for the next layer's matmul, dense for the caller.
@@ -79,6 +80,10 @@ struct GruLayerDev {
   const int8_t *W2f = nullptr;
   const int32_t *bx2 = nullptr;   // [tiles][32]
   int tiles = 0;                  // a multiple of 8 (cells padded to 64)
+  // depths beyond that: the form of deep_gemm.hip
+  DeepWeights deep;
+  const int4 *Wd = nullptr;
+  const int32_t *bd = nullptr;
 };
 
 bool finite_all(const float *a, size_t n) {
@@ -510,7 +515,7 @@ int gru_int_prepare(const gru_int_layer_params *layers, int32_t num_layers, int3
       lut[i].tail = has_tail;
       lut[i].dom = has_tail ? 16384 : (flat_from + 1 + 1023) / 1024 * 1024;
     }
-    struct Off { size_t W, bx, R, bh, W2f, bx2, R16, bh64; int tiles; };
+    struct Off { size_t W, bx, R, bh, W2f, bx2, R16, bh64, Wd, bd; int tiles; DeepWeights deep; };
     std::vector<Off> offs(num_layers);
     for (int l = 0; l < num_layers; ++l) {
       const GruLayerHost &q = m->host[l];
@@ -541,6 +546,13 @@ int gru_int_prepare(const gru_int_layer_params *layers, int32_t num_layers, int3
         for (int n = 0; n < N; ++n)
           std::memcpy(img.data() + o.W + ((size_t)g * d.Nt + n) * d.Ip, q.Wq.data() + ((size_t)g * N + n) * I, I);
         std::memcpy(img.data() + o.bx + (size_t)g * d.Nt * 4, q.bx_fold.data() + (size_t)g * N, (size_t)N * 4);
+      }
+      o.deep = deep_weights(d.Ip, 3, d.Nt);
+      if (o.deep.stages) {
+        o.Wd = reserve(o.deep.bytes());
+        o.bd = reserve((size_t)o.deep.cbs * 128 * 4);
+        deep_pack(o.deep, 3, d.Nt, d.Ip, reinterpret_cast<int8_t *>(img.data() + o.W), reinterpret_cast<int32_t *>(img.data() + o.bx),
+                  reinterpret_cast<int8_t *>(img.data() + o.Wd), reinterpret_cast<int32_t *>(img.data() + o.bd));
       }
       // first operand of the 32x32x32 MFMA: lane (row = lane % 32, half = lane / 32) holds, for k step ks, bytes
       // 32 ks + 16 half .. + 15 of weight row 32 ct + row of gate g (zero beyond N in either direction)
@@ -573,7 +585,7 @@ int gru_int_prepare(const gru_int_layer_params *layers, int32_t num_layers, int3
       }
       offs[l] = o;
     }
-    if (hipSetDevice(device) != hipSuccess || in_gemm_init() != hipSuccess || gemm_init() != hipSuccess || gru_seq_init() != hipSuccess ||
+    if (hipSetDevice(device) != hipSuccess || in_gemm_init() != hipSuccess || deep_gemm_init() != hipSuccess || gemm_init() != hipSuccess || gru_seq_init() != hipSuccess ||
         hipMalloc(reinterpret_cast<void **>(&m->arena), img.size()) != hipSuccess) {
       m->arena = nullptr;
       delete m;
@@ -609,6 +621,11 @@ int gru_int_prepare(const gru_int_layer_params *layers, int32_t num_layers, int3
         m->dev[l].W2f = reinterpret_cast<const int8_t *>(m->arena + offs[l].W2f);
         m->dev[l].bx2 = reinterpret_cast<const int32_t *>(m->arena + offs[l].bx2);
         m->dev[l].tiles = offs[l].tiles;
+      }
+      if (offs[l].deep.stages) {
+        m->dev[l].deep = offs[l].deep;
+        m->dev[l].Wd = reinterpret_cast<const int4 *>(m->arena + offs[l].Wd);
+        m->dev[l].bd = reinterpret_cast<const int32_t *>(m->arena + offs[l].bd);
       }
     }
   } catch (const std::bad_alloc &) {
@@ -714,14 +731,22 @@ int gru_int_forward(const gru_int_model *m, const int8_t *x, int32_t T, int32_t 
     // (on the launch-per-step path only where the matmul is large: the tile-ordered terms cost the step kernel
     // 0.5 us per step, measured, which 8192 rows and more of a faster matmul pay for)
     const bool ws_gemm = !tr && dv.W2f && m->num_cus == 256 && (seq || TB >= 8192) && in_gemm_ws_supported(ga);
-    // The register-resident GEMM reads x in place in any batch (rows of 16-byte pieces); the general one takes rows of Ip
-    // bytes, a padded copy unless x already has that shape.
-    if (l == 0 && !ws_gemm && (d.Ip != q.I || (reinterpret_cast<uintptr_t>(x) & 15) || (B & 31))) {
+    // depths beyond 1024: the weights in registers as well (deep_gemm.hip; figures in sru.hip, whose layers take it too)
+    DeepGemmArgs da{};
+    da.lda = d.Ip; da.M = (int)TB; da.kpad = d.Ip; da.Wd = dv.Wd; da.bias = dv.bd;
+    da.G = 3; da.N = d.Nt; da.out = tx; da.ldc = 3 * d.Nt;
+    for (int g = 0; g < 3; ++g) da.rs[g] = rescale_hi_prepare(q.Mx[g], rq.r[g]);
+    da.pre = ga.pre;
+    const bool deep = !tr && dv.deep.stages && m->num_cus == 256 && !ws_gemm && deep_gemm_supported(da, rq.r);
+    // The register-resident GEMMs read x in place in any batch (rows of 16-byte pieces, the deep one of Ip bytes); the general
+    // one takes rows of Ip bytes in whole blocks of 32, a padded copy unless x already has that shape.
+    if (l == 0 && !ws_gemm && (d.Ip != q.I || (reinterpret_cast<uintptr_t>(x) & 15) || (!deep && (B & 31)))) {
       int8_t *xp = reinterpret_cast<int8_t *>(ws + w.xpad);
       launch_copy_rows_i8(s, x, q.I, xp, d.Ip, (int)TB, q.I, 0);
       in = xp;
       ld_in = d.Ip;
     }
+    da.A = in;  // rows of d.Ip bytes, 16-byte aligned: the caller's, the copy, or the layer below's
     GruSeqArgs sa{};
     if (seq) {
       sa.B = B; sa.N = N; sa.T = T; sa.Kp = d.Kp;
@@ -755,6 +780,8 @@ int gru_int_forward(const gru_int_model *m, const int8_t *x, int32_t T, int32_t 
     timed_begin(GRU_INT_K_INPUT_GEMM, 1);
     if (ws_gemm) {
       launch_in_gemm_ws(s, ga, m->num_cus);
+    } else if (deep) {
+      launch_deep_gemm(s, da, dv.deep, m->num_cus);
     } else {
       // the matmul's row arithmetic is 32-bit (padded columns may exceed what the call was checked for): in runs of rows
       const int64_t most = (((int64_t)1 << 31) - 1) / std::max(3 * d.Nt, d.Ip);

@@ -80,6 +80,35 @@ hipError_t in_gemm_init();
 bool in_gemm_ws_supported(const InGemmArgs &a);
 void launch_in_gemm_ws(hipStream_t s, const InGemmArgs &a, int num_cus);
 
+// Input matmul of depths 1025 to 2048 with the weights in registers (deep_gemm.hip), row-major int16 output as the general
+// matmul writes it.
+struct DeepWeights {
+  int stages = 0;  // 0: not for this shape; else a half of the depth is 8 * stages k steps of 32
+  int Np = 0;      // columns per gate as packed: N rounded up to 16
+  int cbs = 0;     // blocks of 128 packed columns
+  size_t bytes() const { return (size_t)cbs * 128 * 2 * 8 * stages * 32; }
+};
+DeepWeights deep_weights(int kpad, int G, int N);
+// W [G N][kpad], bias [G N] -> Wd (zeroed) [4 cbs tiles][2 halves of the depth][8 stages k steps][64 lanes][16], bd (zeroed)
+// [128 cbs]
+void deep_pack(const DeepWeights &w, int G, int N, int kpad, const int8_t *W, const int32_t *bias, int8_t *Wd, int32_t *bd);
+struct DeepGemmArgs {
+  const int8_t *A;  // [M, lda], rows readable for kpad bytes
+  int lda, M, kpad;
+  const int4 *Wd;
+  const int32_t *bias;  // packed
+  int G, N;             // gates, columns per gate of the output
+  int16_t *out;         // [M, ldc], gate g at column g * N
+  int ldc;
+  RescaleHi rs[4];
+  int pre;              // operand treatment of the rescale: 0 none, 1 left shift, 2 clamp and left shift
+  // filled by launch_deep_gemm
+  int Np, cbs, parts, by_rows;
+};
+hipError_t deep_gemm_init();
+bool deep_gemm_supported(const DeepGemmArgs &a, const int32_t *r);
+void launch_deep_gemm(hipStream_t s, const DeepGemmArgs &a, const DeepWeights &w, int num_cus);
+
 // One activation table as the persistent kernels keep it in LDS: a prefix of `dom` entries of the table's wide form
 // (lstm_int_math.h), and the tail part if lookups at and beyond dom can differ from entry dom - 1.
 struct LutWide {

@@ -7,7 +7,8 @@
 //   1. the matmul slots (candidate, forget, reset, highway) of all T*B rows as
 //      one int8 MFMA matmul, each slot rescaled to its own int16 format: the
 //      register-resident input GEMM of the LSTM path (in_gemm.hip, input depth
-//      up to 1024, tile-ordered output) or the general matmul (kernels.hip,
+//      up to 1024, tile-ordered output), its form for depths up to 2048
+//      (deep_gemm.hip, row-major output) or the general matmul (kernels.hip,
 //      row-major output);
 //   2. sru_scan_kernel: the recurrence has no matmul, every (row, cell) is a
 //      chain of its own through time.  A thread carries four neighbouring cells
@@ -65,6 +66,10 @@ struct SruLayerDev {
   const int8_t *W2f = nullptr;
   const int32_t *b2 = nullptr;   // [tiles][32]
   int tiles = 0;                 // a multiple of 8 (cells padded to 64)
+  // depths beyond that: the form of deep_gemm.hip
+  DeepWeights deep;
+  const int4 *Wd = nullptr;
+  const int32_t *bd = nullptr;
 };
 
 bool finite_all(const float *a, size_t n) {
@@ -529,7 +534,7 @@ int sru_int_prepare(const sru_int_layer_params *layers, int32_t num_layers, int3
       for (int x = -32768; x < 32768; ++x) full[x + 32768] = (uint16_t)sigmoid_from_table(tab, x);
       m->sig_inner = *std::max_element(tab, tab + 32769) <= 32767 && *std::min_element(full, full + kSigFull) >= 1;
     }
-    struct Off { size_t W, bias, vq, W2f, b2; int tiles; };
+    struct Off { size_t W, bias, vq, W2f, b2, Wd, bd; int tiles; DeepWeights deep; };
     std::vector<Off> offs(num_layers);
     for (int l = 0; l < num_layers; ++l) {
       const SruLayerHost &q = m->host[l];
@@ -555,9 +560,16 @@ int sru_int_prepare(const sru_int_layer_params *layers, int32_t num_layers, int3
       for (int r = 0; r < G * N; ++r) std::memcpy(img.data() + o.W + (size_t)r * d.Ip, q.Wq.data() + (size_t)r * I, I);
       std::memcpy(img.data() + o.bias, q.b_fold.data(), (size_t)G * N * 4);
       std::memcpy(img.data() + o.vq, q.vq.data(), (size_t)2 * N * 2);
+      o.deep = deep_weights(d.Ip, G, N);
+      if (o.deep.stages) {
+        o.Wd = reserve(o.deep.bytes());
+        o.bd = reserve((size_t)o.deep.cbs * 128 * 4);
+        deep_pack(o.deep, G, N, d.Ip, reinterpret_cast<int8_t *>(img.data() + o.W), reinterpret_cast<int32_t *>(img.data() + o.bias),
+                  reinterpret_cast<int8_t *>(img.data() + o.Wd), reinterpret_cast<int32_t *>(img.data() + o.bd));
+      }
       offs[l] = o;
     }
-    if (hipSetDevice(device) != hipSuccess || in_gemm_init() != hipSuccess || gemm_init() != hipSuccess ||
+    if (hipSetDevice(device) != hipSuccess || in_gemm_init() != hipSuccess || deep_gemm_init() != hipSuccess || gemm_init() != hipSuccess ||
         scan_init() != hipSuccess ||
         hipMalloc(reinterpret_cast<void **>(&m->arena), img.size()) != hipSuccess) {
       m->arena = nullptr;
@@ -584,6 +596,11 @@ int sru_int_prepare(const sru_int_layer_params *layers, int32_t num_layers, int3
         m->dev[l].W2f = reinterpret_cast<const int8_t *>(m->arena + offs[l].W2f);
         m->dev[l].b2 = reinterpret_cast<const int32_t *>(m->arena + offs[l].b2);
         m->dev[l].tiles = offs[l].tiles;
+      }
+      if (offs[l].deep.stages) {
+        m->dev[l].deep = offs[l].deep;
+        m->dev[l].Wd = reinterpret_cast<const int4 *>(m->arena + offs[l].Wd);
+        m->dev[l].bd = reinterpret_cast<const int32_t *>(m->arena + offs[l].bd);
       }
     }
   } catch (const std::bad_alloc &) {
@@ -672,17 +689,28 @@ int sru_int_forward(const sru_int_model *m, const int8_t *x, int32_t T, int32_t 
     }
     ga.tx2 = reinterpret_cast<int4 *>(ws + w.tx);
     const bool ws_gemm = m->register_gemm && !tr && dv.W2f && m->num_cus == 256 && in_gemm_ws_supported(ga);
-    // The register-resident GEMM reads x in place in any batch (rows of 16-byte pieces); the general one takes rows of Ip
-    // bytes, a padded copy unless x already has that shape.
-    if (l == 0 && !ws_gemm && (d.Ip != q.I || (reinterpret_cast<uintptr_t>(x) & 15) || (B & 31))) {
+    // depths beyond 1024: the weights in registers as well (deep_gemm.hip), in any batch: 16384 rows x 6144 columns x 2048
+    // 238 -> 200 us, 256 rows 15 -> 12; 1280 columns x 1088 and less, 64 to 256 rows: the same as the general matmul
+    DeepGemmArgs da{};
+    da.lda = d.Ip; da.M = (int)TB; da.kpad = d.Ip; da.Wd = dv.Wd; da.bias = dv.bd;
+    da.G = G; da.N = N; da.out = tx; da.ldc = G * N;
+    for (int g = 0; g < G; ++g) da.rs[g] = rescale_hi_prepare(q.Mx[g], ga.r[g]);
+    da.pre = ga.pre;
+    const bool deep = m->register_gemm && !tr && dv.deep.stages && m->num_cus == 256 && deep_gemm_supported(da, ga.r);
+    // The register-resident GEMMs read x in place in any batch (rows of 16-byte pieces, the deep one of Ip bytes); the general
+    // one takes rows of Ip bytes in whole blocks of 32, a padded copy unless x already has that shape.
+    if (l == 0 && !ws_gemm && (d.Ip != q.I || (reinterpret_cast<uintptr_t>(x) & 15) || (!deep && (B & 31)))) {
       int8_t *xp = reinterpret_cast<int8_t *>(ws + w.xpad);
       launch_copy_rows_i8(s, x, q.I, xp, d.Ip, (int)TB, q.I, 0);
       in = xp;
       ld_in = d.Ip;
     }
+    da.A = in;  // rows of d.Ip bytes, 16-byte aligned: the caller's, the copy, or the layer below's
     timed_begin(SRU_INT_K_INPUT_GEMM);
     if (ws_gemm) {
       launch_in_gemm_ws(s, ga, m->num_cus);
+    } else if (deep) {
+      launch_deep_gemm(s, da, dv.deep, m->num_cus);
     } else {
       Requant rq{};
       rq.all_hi = 1;
