@@ -19,7 +19,7 @@ HIP_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contra
 EXTRA_FLAGS = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] for f in ("in_gemm.hip", "deep_gemm.hip", "rec_inst_8.hip", "rec_inst_20.hip", "rec_inst_32.hip", "rec_sparse_inst_8.hip", "rec_sparse_inst_20.hip", "rec_sparse_inst_32.hip", "rec16_inst_4.hip", "rec16_inst_10.hip", "rec16_inst_16.hip", "solo_inst.hip", "quad_inst_8.hip", "quad_inst_10.hip", "quad_inst_16.hip", "stack_inst_8.hip", "stack_inst_20.hip", "stack_inst_32.hip", "gru_seq.hip")}
 # rec_kernel: what these two passes move out of its step loop, or turn into running pointers of it, ends in spilled registers
 # (eight layers of 2048 cells, 256 rows: 5530 -> 5340 us)
-for _f in ("rec_inst_8.hip", "rec_inst_20.hip", "rec_inst_32.hip", "rec_sparse_inst_8.hip", "rec_sparse_inst_20.hip", "rec_sparse_inst_32.hip"):
+for _f in ("rec_inst_8.hip", "rec_inst_20.hip", "rec_inst_32.hip", "rec_sparse_inst_8.hip", "rec_sparse_inst_20.hip", "rec_sparse_inst_32.hip", "stack_inst_8.hip", "stack_inst_20.hip", "stack_inst_32.hip"):
     EXTRA_FLAGS[_f] = EXTRA_FLAGS[_f] + ["-mllvm", "-disable-lsr", "-mllvm", "-disable-machine-licm"]
 
 

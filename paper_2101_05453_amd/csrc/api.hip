@@ -147,7 +147,7 @@ struct lstm_int_model {
   int spin_limit = 1 << 21;
   int poll_sleep = 0, stats_sleep = 0;  // pauses between polls, in units of 64 clocks
   int idle_sleep = 64, idle_poll_sleep = 12;
-  int stats_first_sleep = 8;
+  int stats_first_sleep = -1;  // pause before the first poll of the statistics words; -1 = by kernel
   int sync_sleep = -1;  // pause before the first poll where all arrive together; -1 = by group size
   int phase_timing = 0;
   int extra_arrivals = 0;  // test hook: group barriers wait for one arrival too many (see RecArgs)
@@ -766,7 +766,10 @@ int forward_stack(lstm_int_model *m, const int8_t *x, int32_t T, int32_t B, int8
   ra.status = m->status;
   ra.spin_limit = m->spin_limit;
   ra.poll_sleep = m->poll_sleep; ra.stats_sleep = m->stats_sleep; ra.idle_sleep = m->idle_sleep;
-  ra.stats_first_sleep = m->stats_first_sleep;
+  // Adds that share the L2 with streamed weights take longer to land: where W comes from memory (more than one item per
+  // layer) the first poll waits 16 x 64 clocks (8 layers of 2048 cells, 32 rows, 64 steps: 8 1297 us, 12 1245, 16 1224, 20
+  // 1229, 32 1250; 1024 cells, 8 steps: 269, 261, 258.5, 258.4, 265; 640 cells and a call of one item: no difference)
+  ra.stats_first_sleep = m->stats_first_sleep >= 0 ? m->stats_first_sleep : (d.GS >= 16 && (T > 1 || B > 32) ? 16 : 8);
   ra.sync_sleep = m->sync_sleep >= 0 ? m->sync_sleep : (d.GS >= 16 ? 16 : 4);
   ra.idle_poll_sleep = m->idle_poll_sleep;
   ra.ticks = m->phase_timing ? reinterpret_cast<long long *>(m->status + 16) : nullptr;
@@ -788,9 +791,10 @@ int forward_stack(lstm_int_model *m, const int8_t *x, int32_t T, int32_t B, int8
   {
     // W of a layer is 4 N Ipad bytes, read by the GS workgroups of one XCD through its 4 MB L2: ask ahead for
     // at most stack_prefetch_kb KB of it per XCD (default 2 MB), spread evenly over the waves
-    const int64_t per_wave = (int64_t)m->stack_prefetch_kb * 8 / ((int64_t)d.GS * 4);
-    sa.prefetch_lines = (int)std::min<int64_t>(per_wave, 16 * (int64_t)(m->dev[L - 1].Ipad / 32));
+    const int64_t per_wave = (int64_t)m->stack_prefetch_kb * 8 / ((int64_t)d.GS * 8);
+    sa.prefetch_lines = (int)std::min<int64_t>(per_wave, 8 * (int64_t)(m->dev[L - 1].Ipad / 32));
   }
+  ra.flags |= kFourPredSlots;
   if (stack_lds_bytes(sa) > 160 * 1024) return LSTM_INT_E_UNSUPPORTED;
   {
     // longer prefixes of the gate tables into the LDS that is left, as for the kernels of one layer -- unless a
@@ -813,6 +817,8 @@ int forward_stack(lstm_int_model *m, const int8_t *x, int32_t T, int32_t B, int8
           grew = true;
       }
     }
+    ra.flags &= ~kFourPredSlots;
+    if (stack_lds_bytes(sa) > 160 * 1024) ra.flags |= kFourPredSlots;
   }
   {
     Timed t(m->prof, s, LSTM_INT_K_OTHER);
@@ -874,7 +880,7 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1) {
   ra.poll_sleep = m->poll_sleep;
   ra.stats_sleep = m->stats_sleep;
   ra.idle_sleep = m->idle_sleep;
-  ra.stats_first_sleep = m->stats_first_sleep;
+  ra.stats_first_sleep = m->stats_first_sleep >= 0 ? m->stats_first_sleep : 8;
   // the last arrival lands about 0.45 us after a workgroup's own in a group of 32, sooner in small groups; in the 32-row
   // kernel a pause of 8 is as good as one of 16 at 32 workgroups and 2 % better at 16 (0 and 4: 0.4 % worse at 32)
   ra.sync_sleep = m->sync_sleep >= 0 ? m->sync_sleep : (d.GS >= 16 ? 16 : 4);

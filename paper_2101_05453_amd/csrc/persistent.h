@@ -301,12 +301,13 @@ struct StackArgs {
                              // buffer, or workspace)
   int c_given;               // 0: the cell state starts from zero, 1: from c_base
   int8_t *h_final;           // NULL, or the caller's h state: layer l's last h, [B, H], at + l * B * H
-  unsigned *flags;           // [L][row_tiles] words 128 bytes apart, zeroed: steps finished
+  unsigned *flags;           // [L][row_tiles] lines of 32 words, zeroed: steps finished, in word 0 for the whole layer, or, in
+                             // a launch of one item per layer, in word w for workgroup w of the layer
   int lutc_lds_bytes;        // LDS bytes of the largest cell-format tanh copy among the layers (0: all share the
                              // gate tanh table's copy); host side of the LDS budget
   int flag_sleep;            // pause between two polls of a flag, x 64 clocks
   int tick_layer;            // the layer whose workgroup 0 fills the phase timers (diagnostics)
-  int prefetch_lines;        // 128-byte lines of a wave's slice of W asked for ahead of W x (at most 16 * kx)
+  int prefetch_lines;        // 128-byte lines of a wave's slice of W asked for ahead of W x (at most 8 * kx)
 };
 
 struct StackInit {

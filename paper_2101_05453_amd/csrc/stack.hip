@@ -45,10 +45,11 @@ size_t stack_lds_bytes(const StackArgs &sa) {
   const RecArgs &a = sa.c;
   const int items = 128;
   const bool proj = a.flags & 8;
-  size_t tile = (((size_t)32 * (a.ks * 32 + 16) + 1023) / 1024 + 1) * 1024;
-  if (proj && tile < 4 * 16 * 64 * 4) tile = 4 * 16 * 64 * 4;
+  size_t tile = ((size_t)32 * (a.ks * 32 + 16) + 1023) / 1024 * 1024;
+  const size_t pred = proj ? (size_t)(a.flags & kFourPredSlots ? 4 : 8) * 4096 : 0;
+  if (tile < pred) tile = pred;
   size_t n = tile + (size_t)items * 8 + (size_t)items * sizeof(LnRow2) + 2 * 4 * 64 * 8 + 4 * 64 * 2 + 4 * 64 * 4 +
-             8 * 32 * 4 + 320 /* StkPrm */ + 16 + 12 * 8 + 3 * 32 /* LutLds */;
+             8 * 32 * 4 + 32 * 4 + 320 /* StkPrm */ + 16 + 12 * 8 + 3 * 32 /* LutLds */;
   for (int i = 0; i < 2; ++i) n += (size_t)lut_wide_lds_bytes(a.lut[i].dom, a.lut[i].sh, a.lut[i].tail != 0);
   n += (size_t)sa.lutc_lds_bytes;  // the largest cell-format copy among the layers
   if (proj) {
@@ -100,9 +101,9 @@ hipError_t launch_stack(hipStream_t s, const StackArgs &sa, bool cooperative) {
   // one workgroup per compute unit, GS per XCD: all of them have to be resident at once (see launch_rec)
   const dim3 grid(8 * a.GS);
   if (cooperative)
-    return hipLaunchCooperativeKernel(reinterpret_cast<const void *>(fn), grid, dim3(256), params,
+    return hipLaunchCooperativeKernel(reinterpret_cast<const void *>(fn), grid, dim3(512), params,
                                       (unsigned)stack_lds_bytes(sa), s);
-  return hipLaunchKernel(reinterpret_cast<const void *>(fn), grid, dim3(256), params, (unsigned)stack_lds_bytes(sa), s);
+  return hipLaunchKernel(reinterpret_cast<const void *>(fn), grid, dim3(512), params, (unsigned)stack_lds_bytes(sa), s);
 }
 
 }  // namespace lstm_int

@@ -31,7 +31,8 @@ struct StkPrm {  // per-layer constants in LDS, 320 bytes
   RescaleHi h[4], c[4], ln[4], x[4];
   RescaleHi m, p;
   int32_t zp_m, zp_h, m_c, glo;
-  int32_t pad[4];
+  double inv_n;  // 1 / N
+  int32_t pad[2];
 };
 static_assert(sizeof(StkPrm) == 320, "stack_lds_bytes assumes 320 bytes");
 
@@ -42,14 +43,17 @@ __device__ __forceinline__ int32_t stk_requant2(int32_t s0, int32_t s1, const Re
   return (v0 & 0xFFFF) | (v1 << 16);
 }
 
+// Eight waves with one weight tile each, as in rec_kernel (four with two: 8 layers of 2048 cells, 640 outputs, layer norm, 32
+// rows, one step 133.5 -> 120.6 us; 1024 cells, layer norm and peephole, 8 steps 365 -> 281).
 // FL as in rec_kernel: bit 0 CIFG, bit 1 peephole, bit 2 layer norm, bit 3 "no projection".
 // ONE: the launch has one item per layer (one step, one row tile).
 template <int KS, int FL, bool ONE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void stack_kernel(StackArgs sa) {
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void stack_kernel(StackArgs sa) {
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   const RecArgs &a = sa.c;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 31, b2 = lane >> 5;
+  constexpr int WAVES = 8;  // one weight tile each, as in rec_kernel
   constexpr bool cifg = FL & 1, ph = FL & 2, ln = FL & 4;
   constexpr bool proj = !(FL & 8);
   const int GS = a.GS;
@@ -99,16 +103,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   int8_t *hfin = sa.h_final ? sa.h_final + (size_t)layer * a.B * a.H : nullptr;
   const int kx = sl.kx;
 
-  // ---- LDS carve-up (stack_lds_bytes mirrors it)
+  // ---- LDS carve-up (stack_lds_bytes mirrors it): what has a fixed size first, at offsets known to the compiler
   constexpr int LS = KS * 32 + 16;  // tile row stride (h rows and x rows alike)
   uint8_t *p = lds;
-  int8_t *hT = reinterpret_cast<int8_t *>(p);
-  int32_t *pred = reinterpret_cast<int32_t *>(p);  // projection partials reuse the tile between steps
-  {
-    const size_t tile_bytes = (((size_t)32 * LS + 1023) / 1024 + 1) * 1024;
-    const size_t pred_bytes = proj ? 4 * 16 * 64 * 4 : 0;
-    p += tile_bytes > pred_bytes ? tile_bytes : pred_bytes;
-  }
   u64 *red = reinterpret_cast<u64 *>(p);                 p += (size_t)items * 8;
   LnRow2 *lnrow = reinterpret_cast<LnRow2 *>(p);         p += (size_t)items * sizeof(LnRow2);
   double *LdL = reinterpret_cast<double *>(p);           p += 4 * 64 * 8;
@@ -116,10 +113,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   int16_t *PqL = reinterpret_cast<int16_t *>(p);         p += 4 * 64 * 2;
   int32_t *bhL = reinterpret_cast<int32_t *>(p);         p += 4 * 64 * 4;
   int32_t *bxL = reinterpret_cast<int32_t *>(p);         p += 8 * 32 * 4;  // folded input bias, tile row order
+  int32_t *bpL = reinterpret_cast<int32_t *>(p);         p += 32 * 4;      // projection bias of the first output tile
   StkPrm *prm = reinterpret_cast<StkPrm *>(p);           p += sizeof(StkPrm);
   int *flag = reinterpret_cast<int *>(p);                p += 16;
   u64 *tickL = reinterpret_cast<u64 *>(p);               p += 12 * 8;  // phase timers
   LutLds *lutP = reinterpret_cast<LutLds *>(p);          p += 3 * sizeof(LutLds);
+  int8_t *hT = reinterpret_cast<int8_t *>(p);
+  v4i *pred = reinterpret_cast<v4i *>(p);  // projection partials [slot][4][64] reuse the tile between steps
+  const bool four_slots = a.flags & kFourPredSlots;
+  {
+    const size_t tile_bytes = ((size_t)32 * LS + 1023) / 1024 * 1024;  // whole 1 KB chunks
+    const size_t pred_bytes = proj ? (four_slots ? 4 : 8) * 4096 : 0;
+    p += tile_bytes > pred_bytes ? tile_bytes : pred_bytes;
+  }
   // the activation tables as in rec_kernel: prefixes of the wide form; the two gate tables are common to
   // the layers, the cell-format tanh is the layer's own (or the gate tanh's copy when the formats agree)
   const LutWide lw[3] = {a.lut[0], a.lut[1], sl.lutc};
@@ -143,25 +149,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const int my_ptiles = proj ? (a.ptiles > member ? (a.ptiles - member + GS - 1) / GS : 0) : 0;
 
   // ---- one-time loads: R slice -> registers; per-cell parameters, tables, W_proj tiles -> LDS
-  v4i Wf[2][KS];
-  {
-    const int4 *src = sl.R2 + ((size_t)(member * 4 + wave) * 2) * KS * 64 + lane;
+  v4i Wf[KS];
+  // 1 KB per wave load, all in flight together before the first is pinned to its place
+  auto load_operands = [&](const int4 *src, int n) {
+    int4 w[KS];
 #pragma unroll
-    for (int tl = 0; tl < 2; ++tl) {
-      int4 w[KS];
+    for (int ks = 0; ks < KS; ++ks) w[ks] = src[(size_t)(ks < n ? ks : 0) * 64];
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) w[ks] = src[(size_t)(tl * KS + ks) * 64];
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        Wf[tl][ks] = v4i{w[ks].x, w[ks].y, w[ks].z, w[ks].w};
-        asm volatile("" : "+a"(Wf[tl][ks]));  // resident in accumulation registers for the whole launch
-      }
-      __builtin_amdgcn_sched_barrier(0);
+    for (int ks = 0; ks < KS; ++ks) {
+      Wf[ks] = v4i{w[ks].x, w[ks].y, w[ks].z, w[ks].w};
+      asm volatile("" : "+v"(Wf[ks]));
     }
-  }
-  const int cell_w = wave * 16 + 4 * b2;  // + tile * 8 + c, within the workgroup's 64 cells
-  {
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  load_operands(sl.R2 + (size_t)(member * WAVES + wave) * KS * 64 + lane, KS);
+  const int cell_w = wave * 8 + 4 * b2;  // + c, within the workgroup's 64 cells
+  if (tid < 256) {
     const int g = tid >> 6, n = tid & 63;
     const size_t idx = (size_t)g * a.Ncp + member * 64 + n;
     LdL[tid] = ln ? ln_weight_scaled(sl.Lq4[idx]) : 0.0;
@@ -176,33 +180,38 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     prm->c[tid] = rescale_hi_prepare(tid < 3 && ph ? sl.Mc[tid] : 0, tid < 3 && ph ? sl.rc[tid] : 33);
     prm->ln[tid] = rescale_hi_prepare(sl.Mln[tid], ln ? sl.rln[tid] : 33);
   }
-  if (tid < 3) {
-    LutLds d;
-    const LutWide &w = (tid == 2 && share_tanh) ? lw[1] : lw[tid];  // a shared copy has the gate table's prefix
-    d.dom = w.dom; d.sh = w.sh;
-    d.offD = (int32_t)(lutD[tid] - lds);
-    d.offB = (int32_t)(lutB[tid] - lds);
-    d.offT = lutTl[tid] ? (int32_t)(lutTl[tid] - lds) : 0;
-    d.pad[0] = d.pad[1] = d.pad[2] = 0;
-    lutP[tid] = d;
-  }
+#pragma unroll
+  for (int i = 0; i < 3; ++i)  // (indexed by the thread these arrays would lie in scratch memory)
+    if (tid == i) {
+      LutLds d;
+      d.dom = i == 2 && share_tanh ? lw[1].dom : lw[i].dom;  // a shared copy has the gate table's prefix
+      d.sh = i == 2 && share_tanh ? lw[1].sh : lw[i].sh;
+      d.offD = (int32_t)(lutD[i] - lds);
+      d.offB = (int32_t)(lutB[i] - lds);
+      d.offT = lutTl[i] ? (int32_t)(lutTl[i] - lds) : 0;
+      d.pad[0] = d.pad[1] = d.pad[2] = 0;
+      lutP[i] = d;
+    }
   if (tid == 0) {
     prm->m = rescale_hi_prepare(sl.Mm, sl.rm);
     prm->p = rescale_hi_prepare(proj ? sl.Mp : 0, proj ? sl.rp : 33);
     prm->zp_m = sl.zp_m; prm->zp_h = sl.zp_h;
+    prm->inv_n = 1.0 / (double)a.N;
     prm->m_c = sl.m_c; prm->glo = ln ? -32767 : -32768;
   }
-  for (int i = tid; i < 32 * LS / 16; i += 256) reinterpret_cast<int4 *>(hT)[i] = int4{0, 0, 0, 0};
+  for (int i = tid; i < 32 * LS / 16; i += 64 * WAVES) reinterpret_cast<int4 *>(hT)[i] = int4{0, 0, 0, 0};
   {
     auto dma = [&](const void *src, const void *dst) {
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
                                        (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
     };
-    for (int i = 0; i < (share_tanh ? 2 : 3); ++i) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      if (i == 2 && share_tanh) continue;
       const int nd = lw[i].dom >> 10;
       const int nb = (((lw[i].dom >> lw[i].sh) * 2) + 1023) >> 10;
       const int nt = lw[i].tail ? 3 : 0;
-      for (int c = wave; c < nd + nb + nt; c += 4) {
+      for (int c = wave; c < nd + nb + nt; c += WAVES) {
         const int so = c < nd ? c * 1024 : (c < nd + nb ? kLutWideBaseOff + (c - nd) * 1024 : kLutWideTailOff + (c - nd - nb) * 1024);
         dma(lw[i].blob + so + lane * 16, lutD[i] + c * 1024);
       }
@@ -210,7 +219,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const int prow = a.prow;
     const int wp_rows = my_ptiles * prow;
     const int wp_chunks = (wp_rows * WLS + 1023) >> 10;
-    for (int c = wave; c < wp_chunks; c += 4) {
+    for (int c = wave; c < wp_chunks; c += WAVES) {
       const int o = c * 1024 + lane * 16;
       const int r = o / WLS, col_b = o - r * WLS;
       const int8_t *src = sl.Wp2;
@@ -224,13 +233,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   }
 
   constexpr int TILE_KB = (32 * LS + 1023) / 1024;
-  constexpr int NCH = (TILE_KB + 3) / 4;  // chunks per wave
+  constexpr int NCH = (TILE_KB + WAVES - 1) / WAVES;  // chunks per wave
 
-  int32_t bpr[4] = {0, 0, 0, 0};
-  if (my_ptiles > 0) {
-    const int4 b4 = *reinterpret_cast<const int4 *>(sl.bp2 + member * 32 + 8 * (tid >> 6) + 4 * ((tid & 63) >> 5));
-    bpr[0] = b4.x; bpr[1] = b4.y; bpr[2] = b4.z; bpr[3] = b4.w;
-  }
+  if (my_ptiles > 0 && tid < 32) bpL[tid] = sl.bp2[member * 32 + tid];
   if (tid < items) red[tid] = 0;
   if (tid < 12) tickL[tid] = 0;
   if (tid == 0) {
@@ -241,14 +246,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 
   // optional phase timing (diagnostics): workgroup 0 of one layer, 100 MHz wall clock ticks per phase
   long long tick_last = 0;
-  const bool timing = a.ticks && layer == sa.tick_layer && member == 0 && tid == 0;
+  const bool timing = a.ticks && layer == sa.tick_layer && member == 0 && wave == 0;  // uniform
 #define TICK(i)                                                                           \
   do {                                                                                    \
     if (timing) {                                                                         \
       asm volatile("" ::: "memory");                                                      \
       const long long now = (long long)wall_clock64();                                    \
-      __hip_atomic_fetch_add(&tickL[i], (u64)(now - tick_last), __ATOMIC_RELAXED,         \
-                             __HIP_MEMORY_SCOPE_WORKGROUP);                               \
+      if (lane == 0)                                                                      \
+        __hip_atomic_fetch_add(&tickL[i], (u64)(now - tick_last), __ATOMIC_RELAXED,       \
+                               __HIP_MEMORY_SCOPE_WORKGROUP);                             \
       tick_last = now;                                                                    \
     }                                                                                     \
   } while (0)
@@ -273,8 +279,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     }
   }
   if (tid == 0) __hip_atomic_fetch_add(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  int64_t prevS[2][2][2] = {{{0, 0}, {0, 0}}, {{0, 0}, {0, 0}}};  // this thread's item, per round and set: S1, S2
-  const double inv_n = 1.0 / (double)a.N;
+  uint32_t prev1[2] = {0, 0};  // this thread's item, per round: the sums of the statistics words as last read
+  u64 prev2[2] = {0, 0};
   const int g_first = cifg ? 1 : 0;
   const bool pre_ln = ln && (sl.rln[0] < 33 || sl.rln[1] < 33 || sl.rln[2] < 33 || sl.rln[3] < 33);
   const bool pre_m = sl.rm < 33;
@@ -284,40 +290,46 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   const int pre_h = sl.pre_h, pre_x = sl.pre_x;
 
   // the tile of 32 rows starting at row0 of a [.., ld] buffer -> LDS; bytes of a row beyond `width`, the
-  // row padding and the spare chunk read offset 0 of the buffer (they only ever meet zero weights or are
+  // row padding read offset 0 of the tile (they only ever meet zero weights or are
   // not used); BYPASS = the loads pass the L2 by (rows written by another XCD during this launch)
   auto tile_to_lds = [&](const int8_t *base, int ld, int width, int row0, auto bypass_tag) {
     constexpr int AUX = decltype(bypass_tag)::value ? 16 : 0;  // sc1
+    const int8_t *tile = base + (size_t)row0 * ld;
+    asm volatile("" : "+s"(tile));
+    int l = lane;
+    asm volatile("" : "+v"(l));  // the lane's offsets are computed here, not kept
 #pragma unroll
     for (int j = 0; j < NCH; ++j) {
-      const int o = (wave + 4 * j) * 1024 + lane * 16;
-      const int r = o / LS, c = o - r * LS;
-      int row = row0 + r;
-      row = row < a.B ? row : a.B - 1;
-      const size_t off = (r < 32 && c < width) ? (size_t)row * ld + c : 0;
-      __builtin_amdgcn_global_load_lds(
-          (const __attribute__((address_space(1))) void *)(base + off),
-          (__attribute__((address_space(3))) void *)(lds + (wave + 4 * j < TILE_KB ? wave + 4 * j : TILE_KB) * 1024), 16,
-          0, AUX);
+      if (WAVES * (j + 1) > TILE_KB && wave + WAVES * j >= TILE_KB) continue;  // uniform
+      const int o = (wave + WAVES * j) * 1024 + l * 16;
+      const int r = o / LS, c = o - r * LS, last = a.B - 1 - row0;
+      const unsigned off = (r < 32 && c < width) ? (unsigned)((r < last ? r : last) * ld + c) : 0u;
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(tile + off),
+                                       (__attribute__((address_space(3))) void *)(hT + (wave + WAVES * j) * 1024), 16, 0, AUX);
     }
   };
 
-  int32_t creg[2][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+  const bool tails = lw[0].tail | lw[1].tail | lw[2].tail;  // some table's LDS copy ends before its flat part
+  // this lane's operand row of W_proj; rows beyond a tile's prow outputs re-read row 0: their results are never stored
+  const int wp_lane = (col < a.prow ? col : 0) * WLS + (b2 << 4);
+  int32_t creg[4] = {0, 0, 0, 0};
+  const int tid0 = tid;
   for (int it = 0; it < n_items; ++it) {
+    // addresses of a lane are computed anew for every item (see rec_kernel)
+    int tid = tid0;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, col = lane & 31, b2 = lane >> 5, cell_w = wave * 8 + 4 * b2;
     const int t = it / RTILES, rtile = it - t * RTILES;
     const int row0 = rtile * 32;
     const int row = row0 + col;
 
-    // ---- cell state of this lane's 8 cells: in registers from step to step when the batch is one row
+    // ---- cell state of this lane's 4 cells: in registers from step to step when the batch is one row
     // tile, in memory between the items of a row tile otherwise
     if (t == 0 || RTILES > 1) {
+      const int n0 = member * 64 + cell_w;
 #pragma unroll
-      for (int tl = 0; tl < 2; ++tl) {
-        const int n0 = member * 64 + cell_w + tl * 8;
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-          creg[tl][c] = ((t > 0 || sa.c_given) && row < a.B && n0 + c < a.N) ? cbuf[(size_t)row * a.N + n0 + c] : 0;
-      }
+      for (int c = 0; c < 4; ++c)
+        creg[c] = ((t > 0 || sa.c_given) && row < a.B && n0 + c < a.N) ? cbuf[(size_t)row * a.N + n0 + c] : 0;
     }
 
     // ---- h^{t-1} rows of the tile -> LDS; R h on the MFMA; kept as packed int16 terms
@@ -328,28 +340,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     }
     __syncthreads();
     TICK(0);
-    // The first part of this wave's slice of W (two tiles of kx fragments of 1 KB, contiguous) is asked for
+    // The first part of this wave's slice of W (one tile of kx fragments of 1 KB, contiguous) is asked for
     // ahead of its use, one word per 128-byte line, so that it is on its way into the L2 while R h runs and
     // the input is waited for.  Not all of it: a layer's W can be larger than the XCD's L2, and the last
     // lines would push the first out again before they are used (measured on the 8-layer benchmark stack:
     // about half of W ahead is best, all of it is as slow as none).
-    constexpr int NPF = (KS * 16 + 63) / 64;
+    constexpr int NPF = (KS * 8 + 63) / 64;
     unsigned pf[NPF];
     {
-      const int8_t *w0 = sl.W2f + ((size_t)(member * 8 + wave * 2) * kx) * 1024;
+      const int8_t *w0 = sl.W2f + ((size_t)(member * WAVES + wave) * kx) * 1024;
 #pragma unroll
       for (int i = 0; i < NPF; ++i) {
         const int line = lane + 64 * i;
         pf[i] = (line < sa.prefetch_lines && !ONE) ? *reinterpret_cast<const unsigned *>(w0 + (size_t)line * 128) : 0u;
       }
     }
-    int32_t thp[2][8];  // [tile][(4 gate + c) / 2]: low half = even index
+    int32_t thp[8];  // [(4 gate + c) / 2]: low half = even index
     {
-      v16i acc[2];
+      v16i acc;
 #pragma unroll
-      for (int tl = 0; tl < 2; ++tl)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[tl][v] = bhL[(v >> 2) * 64 + cell_w + tl * 8 + (v & 3)];
+      for (int v = 0; v < 16; ++v) acc[v] = bhL[(v >> 2) * 64 + cell_w + (v & 3)];
       constexpr int DEPTH = 4;
       v4i hf[DEPTH];
       const int8_t *hbase = hT + (size_t)col * LS + (b2 << 4);
@@ -358,19 +368,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
-#pragma unroll
-        for (int tl = 0; tl < 2; ++tl)
-          acc[tl] = __builtin_amdgcn_mfma_i32_32x32x32_i8(Wf[tl][ks], hf[ks % DEPTH], acc[tl], 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(Wf[ks], hf[ks % DEPTH], acc, 0, 0, 0);
         if (ks + DEPTH < KS) hf[ks % DEPTH] = *reinterpret_cast<const v4i *>(hbase + (ks + DEPTH) * 32);
         __builtin_amdgcn_sched_barrier(0);
       }
       auto pack = [&](auto pre_tag) {
         constexpr int PRE = decltype(pre_tag)::value;
 #pragma unroll
-        for (int tl = 0; tl < 2; ++tl)
-#pragma unroll
-          for (int j = 0; j < 8; ++j)
-            thp[tl][j] = stk_requant2<PRE>(acc[tl][2 * j], acc[tl][2 * j + 1], prm->h[(2 * j) >> 2]);
+        for (int j = 0; j < 8; ++j) thp[j] = stk_requant2<PRE>(acc[2 * j], acc[2 * j + 1], prm->h[(2 * j) >> 2]);
       };
       if (pre_h == 0)
         pack(std::integral_constant<int, 0>{});
@@ -383,46 +388,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     // R: W takes its place in the registers while the layers below are still at work, and W x below runs
     // from registers instead of waiting for memory.
     constexpr bool w_resident = ONE;
-    if (w_resident) {
-      const int8_t *wsrc = sl.W2f + ((size_t)(member * 8 + wave * 2) * kx) * 1024 + (lane << 4);
-#pragma unroll
-      for (int tl = 0; tl < 2; ++tl) {
-        int4 w[KS];
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-          w[ks] = *reinterpret_cast<const int4 *>(wsrc + ((size_t)tl * kx + (ks < kx ? ks : 0)) * 1024);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          Wf[tl][ks] = v4i{w[ks].x, w[ks].y, w[ks].z, w[ks].w};
-          asm volatile("" : "+a"(Wf[tl][ks]));
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
+    if (w_resident) load_operands(reinterpret_cast<const int4 *>(sl.W2f + ((size_t)(member * WAVES + wave) * kx) * 1024) + lane, kx);
     TICK(1);
 
-    // ---- W x^t: weights streamed from memory as MFMA operands, DW k steps ahead per tile
+    // ---- W x^t: weights streamed from memory as MFMA operands, DW k steps ahead
     constexpr int DW = 6;
-    v4i wq[2][DW];
-    const int8_t *wbase = sl.W2f + ((size_t)(member * 8 + wave * 2) * kx) * 1024 + (lane << 4);
-    auto wload = [&](int tl, int ks) -> v4i {
-      return *reinterpret_cast<const v4i *>(wbase + ((size_t)tl * kx + ks) * 1024);
-    };
+    v4i wq[DW];
+    const int8_t *wbase = sl.W2f + ((size_t)(member * WAVES + wave) * kx) * 1024 + (lane << 4);
+    auto wload = [&](int ks) -> v4i { return *reinterpret_cast<const v4i *>(wbase + (size_t)ks * 1024); };
 #pragma unroll
     for (int ks = 0; ks < DW && ks < KS; ++ks)
-      if (ks < kx && !w_resident) {
-        wq[0][ks] = wload(0, ks);
-        wq[1][ks] = wload(1, ks);
-      }
-    // the input rows: wait until the layer below has finished step t of this row tile
+      if (ks < kx && !w_resident) wq[ks] = wload(ks);
+    // The input rows: wait until the layer below has finished step t of this row tile.  ONE: each of its workgroups that
+    // store rows says so itself, in a word of the tile's line that a lane of wave 0 polls, so that its last barrier is not
+    // waited for (8 layers of 2048 cells, 32 rows: 120.6 -> 111.7 us); else the first workgroup does, behind that barrier.
     if (layer > 0) {
-      if (tid == 0) {
-        const unsigned *f = sa.flags + ((size_t)(layer - 1) * RTILES + rtile) * 32;
+      const int sayers = !ONE ? 1 : proj ? (a.ptiles < GS ? a.ptiles : GS) : GS;
+      if (wave == 0 && lane < sayers) {
+        const unsigned *f = sa.flags + ((size_t)(layer - 1) * RTILES + rtile) * 32 + lane;
+        const unsigned want = (unsigned)(t + 1 + (ONE ? a.extra_arrivals : 0));
         int budget = a.spin_limit;
         for (;;) {
           const unsigned v = __hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          if ((int)(v - (unsigned)(t + 1)) >= 0) break;
+          if ((int)(v - want) >= 0) break;
           if (--budget <= 0 || __hip_atomic_load(a.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
             __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             flag[0] = 0;
@@ -448,11 +436,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     }
     __syncthreads();
     TICK(3);
-    v16i acc[2];
+    v16i acc;
 #pragma unroll
-    for (int tl = 0; tl < 2; ++tl)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[tl][v] = bxL[(wave * 2 + tl) * 32 + (v >> 2) * 8 + 4 * b2 + (v & 3)];
+    for (int v = 0; v < 16; ++v) acc[v] = bxL[wave * 32 + (v >> 2) * 8 + 4 * b2 + (v & 3)];
     {
       constexpr int DEPTH = 4;
       v4i xf[DEPTH];
@@ -464,9 +450,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
           if (ks < kx) {  // uniform
-#pragma unroll
-            for (int tl = 0; tl < 2; ++tl)
-              acc[tl] = __builtin_amdgcn_mfma_i32_32x32x32_i8(Wf[tl][ks], xf[ks % DEPTH], acc[tl], 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(Wf[ks], xf[ks % DEPTH], acc, 0, 0, 0);
             if (ks + DEPTH < KS) xf[ks % DEPTH] = *reinterpret_cast<const v4i *>(xbase + (ks + DEPTH) * 32);
           }
           __builtin_amdgcn_sched_barrier(0);
@@ -475,13 +459,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
           if (ks < kx) {  // uniform
-#pragma unroll
-            for (int tl = 0; tl < 2; ++tl)
-              acc[tl] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wq[tl][ks % DW], xf[ks % DEPTH], acc[tl], 0, 0, 0);
-            if (ks + DW < KS && ks + DW < kx) {
-              wq[0][ks % DW] = wload(0, ks + DW);
-              wq[1][ks % DW] = wload(1, ks + DW);
-            }
+            acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wq[ks % DW], xf[ks % DEPTH], acc, 0, 0, 0);
+            if (ks + DW < KS && ks + DW < kx) wq[ks % DW] = wload(ks + DW);
             if (ks + DEPTH < KS) xf[ks % DEPTH] = *reinterpret_cast<const v4i *>(xbase + (ks + DEPTH) * 32);
           }
           __builtin_amdgcn_sched_barrier(0);
@@ -494,34 +473,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     auto gate_sums = [&](auto pre_tag) {
       constexpr int PRE = decltype(pre_tag)::value;
       int32_t s1[4] = {0, 0, 0, 0};
-      uint32_t s2[4][2] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};
+      uint32_t s2[4] = {0, 0, 0, 0};  // four squares of 16-bit values fit 32 bits
 #pragma unroll
-      for (int tl = 0; tl < 2; ++tl) {
+      for (int g = 0; g < 4; ++g) {
+        const RescaleHi pg = prm->x[g];
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const RescaleHi pg = prm->x[g];
-#pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            const int idx = g * 4 + c;
-            const int32_t tx = rescale_sat16_pre<PRE>(acc[tl][idx], pg);
-            const int32_t w = thp[tl][idx >> 1];
-            const int32_t th = (idx & 1) ? (w >> 16) : (int32_t)(int16_t)(w & 0xFFFF);
-            int32_t v = tx + th;
-            if (ph && g < 2) {
-              const int cl = cell_w + tl * 8 + c;
-              v += rescale_sat16_pre(mul_i24(PqL[g * 64 + cl], creg[tl][c]), prm->c[g]);
-            }
-            if (!(ph && g == 3)) v = clamp_i32(v, glo, 32767);
-            acc[tl][idx] = v;
-            s1[g] += v;
-            s2[g][tl] += (uint32_t)v * (uint32_t)v;
-          }
+        for (int c = 0; c < 4; ++c) {
+          const int idx = g * 4 + c;
+          const int32_t tx = rescale_sat16_pre<PRE>(acc[idx], pg);
+          const int32_t w = thp[idx >> 1];
+          const int32_t th = (idx & 1) ? (w >> 16) : (int32_t)(int16_t)(w & 0xFFFF);
+          int32_t v = tx + th;
+          if (ph && g < 2) v += rescale_sat16_pre(mul_i24(PqL[g * 64 + cell_w + c], creg[c]), prm->c[g]);
+          if (!(ph && g == 3)) v = clamp_i32(v, glo, 32767);
+          acc[idx] = v;
+          s1[g] += v;
+          s2[g] += (uint32_t)v * (uint32_t)v;
         }
       }
       if (ln) {
 #pragma unroll
         for (int g = 0; g < (ph ? 3 : 4); ++g) {
-          const int64_t pk = ((int64_t)((u64)s2[g][0] + (u64)s2[g][1]) << 24) + s1[g];
+          const int64_t pk = ((int64_t)(u64)s2[g] << 24) + s1[g];
           __hip_atomic_fetch_add(&red[g * 32 + col], (u64)pk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
       }
@@ -580,17 +553,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             }
             for (int i = 0; i < a.stats_sleep; ++i) __builtin_amdgcn_s_sleep(1);
           }
-          int64_t S1 = -(int64_t)GS * (1 << 22), S2 = 0;
-#pragma unroll
-          for (int ss = 0; ss < 2; ++ss) {
-            c1[ss] &= kValMask;
-            c2[ss] &= kValMask;
-            S1 += (int64_t)((c1[ss] - (u64)prevS[round][ss][0]) & kValMask);
-            S2 += (int64_t)((c2[ss] - (u64)prevS[round][ss][1]) & kValMask);
-            prevS[round][ss][0] = (int64_t)c1[ss];
-            prevS[round][ss][1] = (int64_t)c2[ss];
-          }
-          lnrow[tid] = ln_row2(S1, S2, a.N, inv_n);
+          // the sets' value fields together, less those of the step before; a step adds less than 2^29 and 2^42
+          const uint32_t now1 = (uint32_t)c1[0] + (uint32_t)c1[1];
+          const u64 now2 = (c2[0] + c2[1]) & kValMask;
+          const int64_t S1 = (int64_t)(now1 - prev1[round]) - (int64_t)GS * (1 << 22);
+          const int64_t S2 = (int64_t)((now2 - prev2[round]) & kValMask);
+          prev1[round] = now1;
+          prev2[round] = now2;
+          int n = a.N;
+          asm volatile("" : "+s"(n));  // its conversions to double are made here, not kept
+          lnrow[tid] = ln_row2(S1, S2, n, prm->inv_n);
         }
       }
       __syncthreads();
@@ -604,11 +576,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     TICK(6);
 
     // ---- layer norm, sigma/tanh, cell update (Secs. 3.2.6, 3.2.1, 3.2.9, 3.2.7)
-    constexpr int LNB = KS >= 32 ? 1 : 2;
-    auto normalize = [&](int tl, int gmask, const LnRow2 (&lr)[4], int32_t (&xv)[4][4], bool narrow) {
+    constexpr int LNB = ONE ? 2 : 1;  // gates per batch of reads: with the operands of W x on their way there is room for one
+    auto normalize = [&](int gmask, const LnRow2 (&lr)[4], int32_t (&xv)[4][4], bool narrow, auto sat_tag) {
+      constexpr bool SAT = decltype(sat_tag)::value;  // false: the lookup that follows clamps the magnitude anyway
       if (ln) {
 #pragma unroll
-        for (int gp = 0; gp < 4; gp += LNB) {
+        for (int gp = 0; gp < 4; gp += LNB) {  // LNB gates per batch of reads: 8 LNB doubles in flight
           if (!(gmask >> gp & ((1 << LNB) - 1))) continue;
           double wL[LNB][4], wb[LNB][4];
           RescaleHi pl[LNB];
@@ -618,8 +591,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
               pl[g - gp] = prm->ln[g];
 #pragma unroll
               for (int c = 0; c < 4; ++c) {
-                wL[g - gp][c] = LdL[g * 64 + cell_w + tl * 8 + c];
-                wb[g - gp][c] = bdL[g * 64 + cell_w + tl * 8 + c];
+                wL[g - gp][c] = LdL[g * 64 + cell_w + c];
+                wb[g - gp][c] = bdL[g * 64 + cell_w + c];
               }
             }
           __builtin_amdgcn_sched_barrier(0);
@@ -628,9 +601,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             if (gmask >> g & 1)
 #pragma unroll
               for (int c = 0; c < 4; ++c)
-                xv[g][c] = narrow ? ln_second_stage_narrow(acc[tl][g * 4 + c], lr[g], wL[g - gp][c], wb[g - gp][c])
-                                  : ln_second_stage(acc[tl][g * 4 + c], lr[g], wL[g - gp][c], wb[g - gp][c]);
-          if (pre_ln) {
+                xv[g][c] = narrow ? ln_second_stage_narrow(acc[g * 4 + c], lr[g], wL[g - gp][c], wb[g - gp][c])
+                                  : ln_second_stage(acc[g * 4 + c], lr[g], wL[g - gp][c], wb[g - gp][c]);
+          if (pre_ln) {  // some second-stage shift is below 33 (uniform; rare)
 #pragma unroll
             for (int g = gp; g < gp + LNB; ++g)
               if (gmask >> g & 1)
@@ -641,22 +614,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
           for (int g = gp; g < gp + LNB; ++g)
             if (gmask >> g & 1)
 #pragma unroll
-              for (int c = 0; c < 4; ++c) xv[g][c] = rescale_sat16_pre<0>(xv[g][c], pl[g - gp]);
+              for (int c = 0; c < 4; ++c) xv[g][c] = SAT ? rescale_sat16_pre<0>(xv[g][c], pl[g - gp]) : rescale_hi_pre(xv[g][c], pl[g - gp]);
         }
       } else {
 #pragma unroll
         for (int g = 0; g < 4; ++g)
           if (gmask >> g & 1)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) xv[g][c] = acc[tl][g * 4 + c];
+            for (int c = 0; c < 4; ++c) xv[g][c] = acc[g * 4 + c];
       }
     };
-    // table values of |xv[g][c]| for the gates of gmask; tb[g] = which table (0 sigma, 1 tanh, 2 cell tanh);
-    // see rec_kernel's lookup
-    auto lookup = [&](int gmask, const int32_t (&xv)[4][4], const int (&tb)[4], int32_t (&tv)[4][4]) {
+    // table values of |xv[g][c]| for the gates of gmask; tb[g] = which table (0 sigma, 1 tanh, 2 cell tanh)
+    auto lookup = [&](int gmask, const int32_t (&xv)[4][4], const int (&tb)[4], int32_t (&tv)[4][4], auto tails_tag) {
+      constexpr bool TAILS = decltype(tails_tag)::value;
       int32_t mag[4][4];
       uint32_t base[4][4], delta[4][4];
       int32_t top[3] = {0, 0, 0};  // largest |x| looked up in each table
+      // the tables' places and sizes come from LDS (the same words for every lane)
       LutLds lp[3];
 #pragma unroll
       for (int i = 0; i < 3; ++i) {
@@ -671,8 +645,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
           const int dom = lp[tb[g]].dom, sh = lp[tb[g]].sh;
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
-            mag[g][c] = abs_i32(xv[g][c]);
-            top[tb[g]] = top[tb[g]] > mag[g][c] ? top[tb[g]] : mag[g][c];
+            mag[g][c] = abs_masked(xv[g][c]);  // at most 2^15
+            if (TAILS) top[tb[g]] = top[tb[g]] > mag[g][c] ? top[tb[g]] : mag[g][c];
             const int32_t ai = mag[g][c] < dom ? mag[g][c] : dom - 1;
             base[g][c] = *reinterpret_cast<const uint16_t *>(lds + lp[tb[g]].offB + 2 * (ai >> sh));
             delta[g][c] = lds[lp[tb[g]].offD + ai];
@@ -684,6 +658,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         if (gmask >> g & 1)
 #pragma unroll
           for (int c = 0; c < 4; ++c) tv[g][c] = (int32_t)(base[g][c] + delta[g][c]);
+      if (!TAILS) return;
       bool over = false;
 #pragma unroll
       for (int i = 0; i < 3; ++i) {
@@ -708,7 +683,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     };
     const int gate_tb[4] = {0, 0, 1, 0};
     constexpr int gates_now = (cifg ? 0 : 1) | 2 | 4 | (ph ? 0 : 8);
-    int32_t xi[2][4], xf_[2][4], xz[2][4], xo[2][4];
+    int32_t xo[4];
+    const int32_t m_c = prm->m_c;
     {
       LnRow2 lr[4];
       bool narrow = false;  // uniform: every row of this wave has sigma >= 2^12 (see rec_kernel)
@@ -721,49 +697,38 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         }
         narrow = __builtin_amdgcn_ballot_w64(wide) == 0;
       }
-#pragma unroll
-      for (int tl = 0; tl < 2; ++tl) {
-        int32_t xv[4][4], tv[4][4];
-        if (narrow)
-          normalize(tl, gates_now, lr, xv, true);
-        else
-          normalize(tl, gates_now, lr, xv, false);
-        if (KS >= 32) {
-          lookup(gates_now & 3, xv, gate_tb, tv);
-          lookup(gates_now & 12, xv, gate_tb, tv);
+      int32_t xv[4][4], tv[4][4];
+      if ((!ln || narrow) && !tails) {
+        normalize(gates_now, lr, xv, true, std::false_type{});
+        lookup(gates_now, xv, gate_tb, tv, std::false_type{});
+      } else {
+        asm volatile("");  // keeps what both forms begin with from being computed ahead of them, for all gates at once
+        if (narrow) {
+          normalize(gates_now, lr, xv, true, std::true_type{});
         } else {
-          lookup(gates_now, xv, gate_tb, tv);
+          asm volatile("");
+          normalize(gates_now, lr, xv, false, std::true_type{});
         }
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          xi[tl][c] = cifg ? 0 : mirror_sigmoid(xv[0][c], tv[0][c]);
-          xf_[tl][c] = mirror_sigmoid(xv[1][c], tv[1][c]);
-          xz[tl][c] = mirror_tanh(xv[2][c], tv[2][c]);
-          xo[tl][c] = ph ? 0 : mirror_sigmoid(xv[3][c], tv[3][c]);
-        }
+        lookup(gates_now & 3, xv, gate_tb, tv, std::true_type{});  // two gates' reads at a time: the rarer form, and the larger
+        lookup(gates_now & 12, xv, gate_tb, tv, std::true_type{});
       }
-    }
-    const int32_t m_c = prm->m_c;
-    {
       int32_t s1 = 0;
       int64_t s2 = 0;
 #pragma unroll
-      for (int tl = 0; tl < 2; ++tl)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const int32_t f = xf_[tl][c];
-          const int32_t i = cifg ? cifg_input_gate(f) : xi[tl][c];
-          const int32_t cnew = cell_update32(i, xz[tl][c], f, creg[tl][c], m_c);
-          creg[tl][c] = cnew;
-          if (ph) {  // finish the o gate sum with P_o . c^t (eq. 5)
-            const int cl = cell_w + tl * 8 + c;
-            int32_t v = acc[tl][12 + c] + rescale_sat16_pre(mul_i24(PqL[2 * 64 + cl], cnew), prm->c[2]);
-            v = clamp_i32(v, glo, 32767);
-            acc[tl][12 + c] = v;
-            s1 += v;
-            s2 += (int64_t)v * v;
-          }
+      for (int c = 0; c < 4; ++c) {
+        xo[c] = ph ? 0 : mirror_sigmoid_masked(xv[3][c], tv[3][c]);
+        const int32_t f = mirror_sigmoid_masked(xv[1][c], tv[1][c]);
+        const int32_t i = cifg ? cifg_input_gate(f) : mirror_sigmoid_masked(xv[0][c], tv[0][c]);
+        const int32_t cnew = cell_update32(i, mirror_tanh_masked(xv[2][c], tv[2][c]), f, creg[c], m_c);
+        creg[c] = cnew;
+        if (ph) {  // finish the o gate sum with P_o . c^t (eq. 5)
+          int32_t v = acc[12 + c] + rescale_sat16_pre(mul_i24(PqL[2 * 64 + cell_w + c], cnew), prm->c[2]);
+          v = clamp_i32(v, glo, 32767);
+          acc[12 + c] = v;
+          s1 += v;
+          s2 += (int64_t)v * v;
         }
+      }
       if (ph && ln) {
         const int64_t pk = (s2 << 24) + s1;
         __hip_atomic_fetch_add(&red[3 * 32 + col], (u64)pk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -772,13 +737,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     // the new cell state goes back to memory: read again by this thread at the tile's next step, or, after
     // the last step, the state the caller gets back
     if (RTILES > 1 || t == a.T - 1) {
+      const int n0 = member * 64 + cell_w;
+      if (row < a.B && n0 < a.N)
 #pragma unroll
-      for (int tl = 0; tl < 2; ++tl) {
-        const int n0 = member * 64 + cell_w + tl * 8;
-        if (row < a.B && n0 < a.N)
-#pragma unroll
-          for (int c = 0; c < 4; ++c) cbuf[(size_t)row * a.N + n0 + c] = (int16_t)creg[tl][c];
-      }
+        for (int c = 0; c < 4; ++c) cbuf[(size_t)row * a.N + n0 + c] = (int16_t)creg[c];
     }
     TICK(7);
     if (ph && ln) {
@@ -787,30 +749,30 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     }
 
     // ---- hidden state (Sec. 3.2.7)
-    int32_t tc[2][4];
+    int32_t tc[4];
     {
-      const int hid_tb[4] = {2, 2, 0, 0};
+      const int hid_tb[4] = {2, 0, 0, 0};  // c^t, then the o gate sums
       LnRow2 lr[4];
       if (ph && ln) lr[3] = lnrow[3 * 32 + col];
-      int32_t xv[4][4], tv[4][4], ov[2][4][4];
+      int32_t xv[4][4], tv[4][4], ov[4][4];
 #pragma unroll
-      for (int tl = 0; tl < 2; ++tl) {
+      for (int c = 0; c < 4; ++c) xv[0][c] = creg[c];
+      if (ph) {
+        normalize(8, lr, ov, false, std::true_type{});
 #pragma unroll
-        for (int c = 0; c < 4; ++c) xv[tl][c] = creg[tl][c];
-        if (ph) {
-          normalize(tl, 8, lr, ov[tl], false);
-#pragma unroll
-          for (int c = 0; c < 4; ++c) xv[2 + tl][c] = ov[tl][3][c];
-        }
+        for (int c = 0; c < 4; ++c) xv[1][c] = ov[3][c];
       }
-      lookup(ph ? 15 : 3, xv, hid_tb, tv);
+      if (tails) {
+        asm volatile("");
+        lookup(ph ? 3 : 1, xv, hid_tb, tv, std::true_type{});
+      } else {
+        lookup(ph ? 3 : 1, xv, hid_tb, tv, std::false_type{});
+      }
 #pragma unroll
-      for (int tl = 0; tl < 2; ++tl)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          tc[tl][c] = mirror_tanh(xv[tl][c], tv[tl][c]);
-          if (ph) xo[tl][c] = mirror_sigmoid(xv[2 + tl][c], tv[2 + tl][c]);
-        }
+      for (int c = 0; c < 4; ++c) {
+        tc[c] = mirror_tanh_masked(xv[0][c], tv[0][c]);
+        if (ph) xo[c] = mirror_sigmoid_masked(xv[1][c], tv[1][c]);
+      }
     }
     // Without a projection m is the layer output h: it goes to [T, B, Hpad] with stores that write through
     // the L2 (the next layer's XCD reads it).  With one it goes to the exchange buffer of this XCD.
@@ -818,13 +780,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const RescaleHi pm = prm->m;
     const int32_t zp_m = prm->zp_m;
     const bool final_step = t == a.T - 1;
-#pragma unroll
-    for (int tl = 0; tl < 2; ++tl) {
-      const int n0 = member * 64 + cell_w + tl * 8;
+    {
+      const int n0 = member * 64 + cell_w;
       uint32_t pk = 0;
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        int32_t om = mul_i24(xo[tl][c], tc[tl][c]);
+        int32_t om = mul_i24(xo[c], tc[c]);
         if (pre_m) om = rescale_preshift(om, pm);
         const int32_t mq = sat8(rescale_sat16_pre<0>(om, pm) + zp_m);
         pk |= (uint32_t)(mq & 0xFF) << (8 * c);
@@ -843,87 +804,102 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       }
     }
     TICK(8);
-    if (!group_sync(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, a.sync_sleep, a.poll_sleep, flag)) return;
+    if ((proj || !ONE) && !group_sync(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, a.sync_sleep, a.poll_sleep, flag)) return;
     TICK(9);
 
     // ---- projection (Sec. 3.2.8)
     if (proj) {
-      const int per_wave = a.npadp >> 7;
-      const RescaleHi pp = prm->p;
-      const int32_t zp_h = prm->zp_h;
+      const int ksteps = a.npadp >> 5;     // 32-wide k steps, a multiple of 4, at most 64 (N <= 2048)
+      const int per_wave = (ksteps + 7) >> 3;
+      const int kfirst = wave * per_wave;  // the last waves may have fewer, or none
+      const int kmine = ksteps - kfirst < per_wave ? ksteps - kfirst : per_wave;  // uniform
       for (int pt = 0; pt < my_ptiles; ++pt) {
         const int ptile = member + pt * GS;
-        const int8_t *mrow = mbuf + (size_t)t * a.Bp * a.npadp +
-                             ((((size_t)(row0 >> 5) * (a.npadp >> 5) + wave * per_wave) * 32 + col) << 5) + (b2 << 4);
-        const int8_t *wrow = WpL + ((size_t)pt * a.prow + (col < a.prow ? col : 0)) * WLS + (b2 << 4) + wave * per_wave * 32;
-        int4 mv[16];
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-          const int kk = k < per_wave ? k : per_wave - 1;
-          mv[k] = *reinterpret_cast<const int4 *>(mrow + kk * 1024);
-        }
+        const int8_t *wrow = WpL + wp_lane + pt * a.prow * WLS + kfirst * 32;
+        const int8_t *mrow = mbuf + (size_t)t * a.Bp * a.npadp + ((size_t)(row0 >> 5) * ksteps + kfirst) * 1024;
+        const unsigned moff = col * 32 + b2 * 16;
+        v4i mv[8];
         v16i pacc;
 #pragma unroll
         for (int v = 0; v < 16; ++v) pacc[v] = 0;
+        if (ksteps == 64) {  // N = 2048: eight steps for every wave
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-          const int kk = k < per_wave ? k : per_wave - 1;
-          v4i wf = *reinterpret_cast<const v4i *>(wrow + kk * 32);
-          if (k >= per_wave) wf = v4i{0, 0, 0, 0};
-          pacc = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf, v4i{mv[k].x, mv[k].y, mv[k].z, mv[k].w}, pacc, 0, 0, 0);
+          for (int k = 0; k < 8; ++k) mv[k] = *reinterpret_cast<const v4i *>(mrow + moff + k * 1024);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int k = 0; k < 8; ++k)
+            pacc = __builtin_amdgcn_mfma_i32_32x32x32_i8(*reinterpret_cast<const v4i *>(wrow + k * 32), mv[k], pacc, 0, 0, 0);
+        } else {
+#pragma unroll
+          for (int k = 0; k < 8; ++k)
+            if (k < kmine) mv[k] = *reinterpret_cast<const v4i *>(mrow + moff + k * 1024);
+#pragma unroll
+          for (int k = 0; k < 8; ++k)
+            if (k < kmine)
+              pacc = __builtin_amdgcn_mfma_i32_32x32x32_i8(*reinterpret_cast<const v4i *>(wrow + k * 32), mv[k], pacc, 0, 0, 0);
         }
+        // partial sums through LDS and two outputs per thread, as in rec_kernel
+        const int own = ((wave & (four_slots ? 3 : 7)) << 8) + lane;
+        if (!four_slots || wave >= 4)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) pred[(wave * 16 + v) * 64 + lane] = pacc[v];
+          for (int q = 0; q < 4; ++q) pred[own + q * 64] = v4i{pacc[4 * q], pacc[4 * q + 1], pacc[4 * q + 2], pacc[4 * q + 3]};
         __syncthreads();
-        {
-          const int q = tid >> 6, l2 = tid & 63;
-          const int pl = 8 * q + 4 * (l2 >> 5);  // row of the tile; prow is a multiple of 4
-          const int p0 = ptile * a.prow + pl;
-          const int orow = row0 + (l2 & 31);
-          uint32_t pk = 0;
+        if (four_slots) {
+          if (wave < 4)
 #pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            const int v = 4 * q + c;
-            const int32_t s = pred[(0 * 16 + v) * 64 + l2] + pred[(1 * 16 + v) * 64 + l2] +
-                              pred[(2 * 16 + v) * 64 + l2] + pred[(3 * 16 + v) * 64 + l2] +
-                              (pt == 0 ? bpr[c] : sl.bp2[ptile * 32 + pl + c]);
-            const int32_t hq = sat8(rescale_sat16_pre(s, pp) + zp_h);
-            pk |= (uint32_t)(hq & 0xFF) << (8 * c);
-          }
-          if (orow < a.B && p0 < a.H && pl < a.prow) {
-            int8_t *od = out + ((size_t)t * a.B + orow) * a.Hpad + p0;
-            if (p0 + 3 < a.H) {
-              __hip_atomic_store(reinterpret_cast<uint32_t *>(od), pk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            } else {
-              for (int c = 0; c < 4 && p0 + c < a.H; ++c)
-                __hip_atomic_store(od + c, (int8_t)(pk >> (8 * c)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
+            for (int q = 0; q < 4; ++q) pred[own + q * 64] += v4i{pacc[4 * q], pacc[4 * q + 1], pacc[4 * q + 2], pacc[4 * q + 3]};
+          __syncthreads();
+        }
+        if (4 * wave < a.prow) {
+          const int pl = 4 * wave + 2 * b2;
+          const v2i *mine = reinterpret_cast<const v2i *>(pred) + (wave << 6) + 2 * col + b2;
+          v2i sum = (mine[0] + mine[512]) + (mine[1024] + mine[1536]);
+          if (!four_slots) sum += (mine[2048] + mine[2560]) + (mine[3072] + mine[3584]);
+          const RescaleHi pp = prm->p;
+          const int32_t zp_h = prm->zp_h;
+          const int p0 = ptile * a.prow + pl;
+          uint32_t hq[2];
+#pragma unroll
+          for (int c = 0; c < 2; ++c)
+            hq[c] = (uint32_t)(sat8(rescale_sat16_pre(sum[c] + (pt == 0 ? bpL[pl + c] : sl.bp2[ptile * 32 + pl + c]), pp) + zp_h) & 0xFF);
+          if (row < a.B && p0 < a.H) {
+            const size_t orow0 = (size_t)t * a.B + row0;
+            int8_t *od = out + orow0 * a.Hpad + ptile * a.prow + (unsigned)(col * a.Hpad + pl);
+            // an output past H falls into the padding of the row (and only ever meets zero weights)
+            __hip_atomic_store(reinterpret_cast<uint16_t *>(od), (uint16_t)(hq[0] | hq[1] << 8), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (yout) {
-              int8_t *yd = yout + ((size_t)t * a.B + orow) * a.H + p0;
-              for (int c = 0; c < 4 && p0 + c < a.H; ++c) yd[c] = (int8_t)(pk >> (8 * c));
+              int8_t *yd = yout + orow0 * a.H + ptile * a.prow + (unsigned)(col * a.H + pl);
+              yd[0] = (int8_t)hq[0];
+              if (p0 + 1 < a.H) yd[1] = (int8_t)hq[1];
             }
             if (final_step && hfin) {
-              int8_t *hd = hfin + (size_t)orow * a.H + p0;
-              for (int c = 0; c < 4 && p0 + c < a.H; ++c) hd[c] = (int8_t)(pk >> (8 * c));
+              int8_t *hd = hfin + (size_t)row * a.H + p0;
+              hd[0] = (int8_t)hq[0];
+              if (p0 + 1 < a.H) hd[1] = (int8_t)hq[1];
             }
           }
         }
-        __syncthreads();
+        // the last tile's partial sums are overwritten behind the group barrier only
+        if (pt + 1 < my_ptiles) __syncthreads();
       }
       TICK(10);
-      if (!group_sync(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, my_ptiles == 0 ? a.idle_sleep : 0,
-                      my_ptiles == 0 ? a.idle_poll_sleep : a.poll_sleep, flag))
+      if (!ONE && !group_sync(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, my_ptiles == 0 ? a.idle_sleep : 0,
+                              my_ptiles == 0 ? a.idle_poll_sleep : a.poll_sleep, flag))
         return;
       TICK(11);
     }
-    // every workgroup of the layer is past its stores of step t (and they are acknowledged): tell the
-    // layer above
-    if (!last_layer && member == 0 && tid == 0)
-      __hip_atomic_store(sa.flags + ((size_t)layer * RTILES + rtile) * 32, (unsigned)(t + 1), __ATOMIC_RELAXED,
+    // The stores of step t are acknowledged, those of the whole layer (the barrier above), or, ONE, of this workgroup: tell
+    // the layer above
+    if (ONE) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+    }
+    if (!last_layer && (ONE || member == 0) && tid == 0)
+      __hip_atomic_store(sa.flags + ((size_t)layer * RTILES + rtile) * 32 + member, (unsigned)(t + 1), __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_AGENT);
   }
 #undef TICK
-  if (timing)
+  if (timing && lane == 0)
     for (int i = 0; i < 12; ++i) a.ticks[i] += (long long)tickL[i];
   placement_check();
 }

@@ -1,6 +1,7 @@
-"""The 32-row kernel's division of a step over eight waves, at its edges: projections whose k steps do not divide by eight
-(waves with fewer steps, or none), an odd number of outputs, one and two output tiles per workgroup (partial sums through
-eight and through four slots of LDS), a second row tile, and values beyond the part of the tables that LDS holds."""
+"""The division of a step over eight waves, in the 32-row and in the stacked kernel, at its edges: projections whose k steps
+do not divide by eight (waves with fewer steps, or none), an odd number of outputs, one and two output tiles per workgroup
+(partial sums through eight and through four slots of LDS), a second row tile, values beyond the part of the tables that LDS
+holds, and the hand-off between the layers of a one-step stack."""
 import numpy as np
 import pytest
 
@@ -41,3 +42,38 @@ def test_saturated_gates(orc, N, H, flags):
     y = lib_model.forward(torch.from_numpy(xq).cuda()).cpu().numpy()
     assert lib_model.device_status() == 0
     assert_equal("y", y, np.asarray(orc.forward(orc_model, xq)))
+
+
+@pytest.mark.parametrize("I,N,H,flags,B,T", [
+    (64, 72, 9, PROJ, 5, 1),                 # one item per layer: the workgroups' own words; one of two has outputs
+    (64, 300, 131, PROJ | LN, 32, 1),
+    (128, 1024, 640, PROJ | LN, 9, 1),       # two output tiles of some workgroups, four slots
+    (128, 640, 640, LN | PH, 32, 1),         # no projection: every workgroup stores rows
+    (64, 72, 9, PROJ | CIFG, 37, 3),         # two row tiles: the first workgroup's word behind the barrier
+    (64, 1100, 33, PROJ | LN | PH, 33, 2),
+    (128, 1024, 640, PROJ | LN, 40, 2),
+])
+def test_division_over_the_waves_of_a_stack(orc, I, N, H, flags, B, T):
+    layers, x = wl.make_custom([I, H, H], N, H, flags, B, T, seed=N + H + B, weight_param=0.9 / N ** 0.5)
+    run_and_compare(orc, layers, x, f"stack{N}h{H}", trace=False, options={"stack": 2})
+
+
+@pytest.mark.parametrize("flags", [LN, PROJ | LN, 0])
+def test_waits_of_a_one_step_stack_give_up(orc, flags):
+    import torch
+
+    H = 64 if flags & PROJ else 320
+    layers, x = wl.make_custom([64, H, H], 320, H, flags, 7, 1, seed=11, weight_param=0.05)
+    lib_model, orc_model, xq = prepare_both(orc, layers, x)
+    lib_model.set_option("stack", 2)
+    xd = torch.from_numpy(xq).cuda()
+    lib_model.set_option("spin_limit", 64)
+    lib_model.set_option("barrier_never_completes", 1)
+    lib_model.forward(xd)
+    torch.cuda.synchronize()
+    assert lib_model.device_status() == 1
+    lib_model.set_option("spin_limit", 1 << 21)
+    lib_model.set_option("barrier_never_completes", 0)
+    lib_model.set_option("reset_status", 1)
+    assert_equal("recovered", lib_model.forward(xd).cpu().numpy(), np.asarray(orc.forward(orc_model, xq)))
+    assert lib_model.device_status() == 0
