@@ -244,6 +244,10 @@ bool stack_chosen(const lstm_int_model *m, int64_t T, int64_t B) {
   if (!stack_supported(h.N, h.H, (int)h.flags, m->dev[0].Ipad, L, (int)T, (int)B, &ks) || ks != m->stack_ks) return false;
   if (kStackFlagsOff + (size_t)L * ((B + 31) / 32) * 128 > kSyncBytes) return false;  // flags behind the statistics words
   if (m->stack == 2) return true;
+  // no call outgrows the library's own workspace (lstm_int_forward_static) because of this choice
+  if (plan_stack(m, T, B).total > (size_t)LSTM_INT_STATIC_WORKSPACE_BYTES &&
+      plan_workspace(m, T, B).total <= (size_t)LSTM_INT_STATIC_WORKSPACE_BYTES)
+    return false;
   // Expected time of the two ways, in microseconds, from the times measured on a stack of 8 layers of 2048 cells,
   // 640 outputs, whose layers ran on the kernels for groups of 16 and 32 rows.  (Groups of four rows and the
   // one-workgroup kernel are faster, so smaller layers at few rows may do better one after the other than this
@@ -367,6 +371,9 @@ int upload(lstm_int_model *m) {
         fill_tanh_table(mc, reinterpret_cast<uint16_t *>(image.data() + tab_off[mc]));
         wide_tab[mc].sh = compress_table_wide(reinterpret_cast<const uint16_t *>(image.data() + tab_off[mc]),
                                               image.data() + wide_off[mc], &wide_tab[mc].has_tail, &wide_tab[mc].flat_from);
+        if (wide_tab[mc].sh < 0)
+          wide_tab[mc].sh = compress_table_flat(reinterpret_cast<const uint16_t *>(image.data() + tab_off[mc]),
+                                                image.data() + wide_off[mc], wide_tab[mc].flat_from);
         wide_tab[mc].blob = static_cast<const uint8_t *>(m->arena) + wide_off[mc];
       }
     }

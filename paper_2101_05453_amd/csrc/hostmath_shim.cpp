@@ -92,6 +92,9 @@ int32_t hm_tanh(const uint16_t *tab, int32_t x) { return tanh_from_table(tab, x)
 int hm_compress_wide(const uint16_t *tab, uint8_t *blob, int *has_tail, int *flat_from) {
   return compress_table_wide(tab, blob, has_tail, flat_from);
 }
+int hm_compress_flat(const uint16_t *tab, uint8_t *blob, int flat_from) {
+  return compress_table_flat(tab, blob, flat_from);
+}
 int32_t hm_lut_wide_mag(const uint8_t *blob, int sh, int dom, int with_tail, int32_t a) {
   return lut_wide_mag(blob, sh, dom, with_tail != 0, a);
 }

@@ -388,8 +388,9 @@ LSTM_HD int32_t lut_tail_value(const uint16_t *starts, const uint32_t *masks, in
 // Wide form of a compressed table (global memory): the same encoding over ALL 32768 entries, from which a
 // kernel copies into LDS as long a prefix (`dom` entries, a multiple of 1024) as its LDS budget allows --
 // the longer, the rarer a lookup has to go to the tail.  Layout: 32768 deltas; the bases (32768 >> sh
-// uint16, at most 8 KB); 512 tail starts (1 KB) and 512 tail masks (2 KB) for the entries 16384..32767
-// (lut_tail_value's form incl. the step to entry 32768, present if the table rises by at most one per entry there).
+// uint16, at most 8 KB; at a shift below 3 for a prefix only); 512 tail starts (1 KB) and 512 tail masks (2 KB)
+// for the entries 16384..32767 (lut_tail_value's form incl. the step to entry 32768, present if the table rises
+// by at most one per entry there).
 constexpr int kLutWideBaseOff = 32768, kLutWideTailOff = 32768 + 8192, kLutWideBytes = kLutWideTailOff + 3072;
 // bytes of the LDS copy for a prefix of dom entries
 LSTM_HD int32_t lut_wide_lds_bytes(int32_t dom, int32_t sh, bool with_tail) {

@@ -49,6 +49,14 @@ void fill_tanh_table(int m, uint16_t *tab /*[32769]*/);
 // within 8 bits); *has_tail = the tail part is filled (the table rises by at most one per entry from 16384
 // on); *flat_from = first index from which on every entry is equal.
 int compress_table_wide(const uint16_t *tab, uint8_t *blob /*[kLutWideBytes]*/, int *has_tail, int *flat_from);
+// The wide form of a table that is steep at first and flat soon, tanh in Q(m).(15-m) for m >= 6 (2^m per
+// entry at zero, flat from entry 3020, 1510, 755 on): a shift of 0..2 with deltas and bases for the entries up
+// to the flat part only, so that the bases fit the blob's 8 KB, and no tail part.  The one legal prefix is the
+// first multiple of 1024 beyond flat_from.  -1 if the bases would not fit or no shift keeps the deltas in 8
+// bits.  Without it such a layer has no table in LDS and takes one launch per step: two layers of
+// 512 cells, projection to 256, peephole and layer norm with cells in Q6.9, 64 steps: 32 rows 2085 us, 685 with
+// this form; 4 rows 1816, 677.
+int compress_table_flat(const uint16_t *tab, uint8_t *blob /*[kLutWideBytes]*/, int flat_from);
 // 2:4 structure along k of a weight row (the pruned models of Table 1 in structured form): at most two nonzeros in
 // every aligned group of four.
 bool sparse24_row_ok(const int8_t *row, int K);

@@ -337,6 +337,27 @@ int compress_table_wide(const uint16_t *tab, uint8_t *blob, int *has_tail, int *
   return -1;
 }
 
+int compress_table_flat(const uint16_t *tab, uint8_t *blob, int flat_from) {
+  const int dom = (flat_from + 1 + 1023) / 1024 * 1024;
+  for (int sh = 2; sh >= 0; --sh) {
+    if (dom > 4096 << sh) return -1;  // more bases than the 8 KB hold, and a smaller shift has more
+    bool ok = true;
+    for (int a = 0; a < dom && ok; ++a) {
+      const int d = (int)tab[a] - (int)tab[(a >> sh) << sh];
+      ok = d >= 0 && d <= 255;
+    }
+    if (!ok) continue;
+    memset(blob, 0, kLutWideBytes);
+    uint16_t *base = reinterpret_cast<uint16_t *>(blob + kLutWideBaseOff);
+    for (int a = 0; a < dom; ++a) {
+      blob[a] = (uint8_t)(tab[a] - tab[(a >> sh) << sh]);
+      if ((a & ((1 << sh) - 1)) == 0) base[a >> sh] = tab[a];
+    }
+    return sh;
+  }
+  return -1;
+}
+
 void fill_sigmoid_table(int m, uint16_t *tab) {
   for (int64_t a = 0; a <= 32768; ++a) {
     const uint64_t E = (uint64_t)exp_neg_q31(a << m);

@@ -100,6 +100,27 @@ def test_wide_tables_every_prefix(orc, hm, m):
                 assert hm.hm_lut_wide_mag(blob.ctypes.data, sh, dom, with_tail, a) == int(tab[a]), (kind, m, dom, a)
 
 
+@pytest.mark.parametrize("m,shift", [(6, 2), (7, 1), (8, 0)])
+def test_flat_form_of_the_steep_tables(hm, m, shift):
+    """tanh in Q(m).(15-m) with m >= 6 has no wide form; the flat one returns its value for every |x|.  A table that is
+    not flat within the bases' 8 KB has none."""
+    hm.hm_compress_wide.argtypes = [C.c_void_p, C.c_void_p, C.POINTER(C.c_int), C.POINTER(C.c_int)]
+    hm.hm_compress_flat.argtypes = [C.c_void_p, C.c_void_p, C.c_int]
+    hm.hm_lut_wide_mag.argtypes = [C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int32]
+    tab = np.zeros(32769, np.uint16)
+    hm.hm_tanh_table(m, tab.ctypes.data)
+    blob = np.zeros(32768 + 8192 + 3072, np.uint8)
+    has_tail, flat_from = C.c_int(), C.c_int()
+    assert hm.hm_compress_wide(tab.ctypes.data, blob.ctypes.data, C.byref(has_tail), C.byref(flat_from)) == -1
+    assert has_tail.value == 0
+    assert hm.hm_compress_flat(tab.ctypes.data, blob.ctypes.data, flat_from.value) == shift
+    dom = (flat_from.value + 1 + 1023) // 1024 * 1024
+    assert (dom >> shift) * 2 <= 8192 and not blob[32768 + 8192:].any()
+    for a in range(0, 32769):
+        assert hm.hm_lut_wide_mag(blob.ctypes.data, shift, dom, 0, a) == int(tab[a]), a
+    assert hm.hm_compress_flat(tab.ctypes.data, blob.ctypes.data, 16384) == -1
+
+
 def test_isqrt(orc, hm):
     rnd = random.Random(1)
     vals = list(range(0, 5000)) + [rnd.randrange(0, 2**50) for _ in range(20000)]
