@@ -139,8 +139,8 @@ struct lstm_int_model {
   int sparse = 1;       // 1: layers whose recurrent weights are 2:4 run R h on the sparse MFMA (32-row kernel)
   int stack = 1;        // stacked launch (one layer per XCD): 0 never, 1 where it is expected to be faster, 2 wherever it can run
   int flag_sleep = 2;   // stacked launch: pause between two polls of the layer below's flag, x 64 clocks
-  double stack_step_us = 20.5;
-  int stack_prefetch_kb = 2048;  // stacked launch: KB of a layer's W asked for ahead of each W x  // expected time of one (step, row tile) item of the stacked launch
+  double stack_step_us = 0;  // expected time of one (step, row tile) item of the stacked launch; 0: stacked_us's own
+  int stack_prefetch_kb = 2048;  // stacked launch: KB of a layer's W asked for ahead of each W x
   bool stackable = false;            // every layer equal (and eligible): the stacked kernel can run the model
   int stack_ks = 0;
   const StackLayer *stack_layers = nullptr;  // [L] in the arena
@@ -234,31 +234,7 @@ StackPlan plan_stack(const lstm_int_model *m, int64_t T, int64_t B) {
   return w;
 }
 
-// Whether forward runs T steps of B rows as one stacked launch (a function of the model, its options, T
-// and B only: lstm_int_workspace_bytes and lstm_int_forward must agree).
-bool stack_chosen(const lstm_int_model *m, int64_t T, int64_t B) {
-  if (!m->stackable || m->stack == 0 || m->path == 1 || m->reverse) return false;
-  int ks = 0;
-  const LayerHost &h = m->host[0];
-  const int L = (int)m->host.size();
-  if (!stack_supported(h.N, h.H, (int)h.flags, m->dev[0].Ipad, L, (int)T, (int)B, &ks) || ks != m->stack_ks) return false;
-  if (kStackFlagsOff + (size_t)L * ((B + 31) / 32) * 128 > kSyncBytes) return false;  // flags behind the statistics words
-  if (m->stack == 2) return true;
-  // no call outgrows the library's own workspace (lstm_int_forward_static) because of this choice
-  if (plan_stack(m, T, B).total > (size_t)LSTM_INT_STATIC_WORKSPACE_BYTES &&
-      plan_workspace(m, T, B).total <= (size_t)LSTM_INT_STATIC_WORKSPACE_BYTES)
-    return false;
-  // Expected time of the two ways, in microseconds, from the times measured on a stack of 8 layers of 2048 cells,
-  // 640 outputs, whose layers ran on the kernels for groups of 16 and 32 rows.  (Groups of four rows and the
-  // one-workgroup kernel are faster, so smaller layers at few rows may do better one after the other than this
-  // says.)  One after the other: about 30 us per layer for the input GEMM launch and the weight prologue, and 8.1 us
-  // per step up to 128 rows, 11 us per 256 rows beyond.  Stacked: every layer walks its T * tiles items (step, tile
-  // of 32 rows) one after the other at about 20.5 us each, one item behind the layer below.
-  const double tiles = (double)((B + 31) / 32);
-  const double seq = L * (30.0 + T * (B <= 128 ? 8.1 : 11.0 * ((B + 255) / 256)));
-  const double stk = 25.0 + (T * tiles + L - 1) * m->stack_step_us;
-  return stk < seq;
-}
+bool stack_chosen(const lstm_int_model *m, int64_t T, int64_t B);  // below plan_rec, which it asks
 
 Requant make_requant(const int32_t *M, const int32_t *e, int first, int count, int cols_per_gate,
                      int zp) {
@@ -991,6 +967,64 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1) {
   p.groups = p2_groups;
   p.ok = true;
   return p;
+}
+
+// Expected time of the layers one after the other on the launch `p` names, in microseconds: per layer and launch what
+// does not depend on the number of steps (input GEMM, the weights into registers and LDS) and a step.  Fitted to calls of
+// 2 to 8 layers, 1 to 512 rows and 1 to 64 steps of 64 to 2048 cells with and without layer norm and projection (604
+// calls, within 10 % but for single launches that hide behind one another).
+double sequential_us(const LayerHost &h, const RecPlan &p, int L, int64_t T, int64_t B) {
+  const double ln = h.layer_norm() ? 1 : 0, pr = h.projection() ? 1 : 0;
+  const double mb = (8.0 * h.N * h.H + pr * h.N * h.H) * 1e-6;  // weights of a layer that reads its like
+  double once, step;
+  if (!p.ok) {  // a launch per operation and step
+    once = 15.0;
+    step = 15.0 + 0.01 * h.N;
+  } else if (p.solo) {
+    once = 9.0 + 0.044 * h.N;
+    step = 0.3 + 0.006 * h.N + ln * (0.0095 * h.N - 0.3);
+  } else if (p.quad) {
+    once = 15.5 + 1.5 * mb;
+    step = 1.0 + 0.00105 * h.N + ln * 1.5 + pr * 1.1;
+  } else {
+    once = 15.5 + 0.9 * mb;
+    step = (p.use16 ? 3.0 + 0.0006 * h.N : 3.5 + 0.001 * h.N) + ln * 2.0 + pr * 1.3;
+  }
+  const int64_t rows = p.ok ? (int64_t)p.ra.groups * p.ra.rows_pg : B;
+  return L * (once + T * step) * (double)((B + rows - 1) / rows);
+}
+
+// The same of the stacked launch: every layer walks its T * tiles items (step, tile of 32 rows) one item behind the
+// layer below.  A call of one item needs no exchange through a barrier and no second trip for W: half the time a layer.
+double stacked_us(const LayerHost &h, int L, int64_t T, int64_t B, double item_us) {
+  const double ln = h.layer_norm() ? 1 : 0, pr = h.projection() ? 1 : 0, H = h.H;
+  const double mb = (8.0 * h.N * h.H + pr * h.N * h.H) * 1e-6;
+  const double once = 11.0 + 1.2 * mb + ln * 2.0;
+  const int64_t items = T * ((B + 31) / 32);
+  const double item = item_us > 0     ? item_us
+                      : items == 1    ? 3.7 + 0.002 * H + ln * 1.9 + pr * (1.5 + 0.0011 * h.N)
+                                      : 5.0 + 0.0035 * H + 4.2e-6 * H * H + ln * 2.3 + pr * 0.003 * h.N;
+  return items == 1 ? once + 3.5 + (L - 1) * item : once + (double)(items + L - 2) * item;
+}
+
+// Whether forward runs T steps of B rows as one stacked launch (a function of the model, its options, T
+// and B only: lstm_int_workspace_bytes and lstm_int_forward must agree): where its expected time is the
+// shorter one.  Over the 604 calls above the choice costs 0.2 % against the better way of each; one time per step and
+// per item for all models, taken from 2048 cells, cost 3.2 % (256 cells, layer norm, 8 layers, 64 rows, 8 steps: 438 us
+// one after the other, 196 stacked; 1024 cells, 3 layers, 32 rows, 64 steps: 773, 1030).
+bool stack_chosen(const lstm_int_model *m, int64_t T, int64_t B) {
+  if (!m->stackable || m->stack == 0 || m->path == 1 || m->reverse) return false;
+  int ks = 0;
+  const LayerHost &h = m->host[0];
+  const int L = (int)m->host.size();
+  if (!stack_supported(h.N, h.H, (int)h.flags, m->dev[0].Ipad, L, (int)T, (int)B, &ks) || ks != m->stack_ks) return false;
+  if (kStackFlagsOff + (size_t)L * ((B + 31) / 32) * 128 > kSyncBytes) return false;  // flags behind the statistics words
+  if (m->stack == 2) return true;
+  // no call outgrows the library's own workspace (lstm_int_forward_static) because of this choice
+  if (plan_stack(m, T, B).total > (size_t)LSTM_INT_STATIC_WORKSPACE_BYTES &&
+      plan_workspace(m, T, B).total <= (size_t)LSTM_INT_STATIC_WORKSPACE_BYTES)
+    return false;
+  return stacked_us(h, L, T, B, m->stack_step_us) < sequential_us(h, plan_rec(m, 0, (int)T, (int)B), L, T, B);
 }
 
 // Synchronization scratch of a launch (plan_workspace's `sync`): barrier counters and placement words, statistics words.
