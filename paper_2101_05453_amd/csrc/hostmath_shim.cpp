@@ -112,7 +112,7 @@ int32_t hm_hidden(int32_t o, int32_t tc, int32_t M, int32_t r, int32_t zp) {
 }
 
 // The statistics run's buffers: out[0] = bytes of the allocation, then (offset, bytes)
-// of stats, raw, vec[2], act[2] and, per layer, of wop, rop, pop, wx, m, h0, c, pre.
+// of stats, raw, vec[2], act[2] and, per layer, of wop, rop, pop, wx, m, h, c, pre.
 void hm_calibrate_plan(const lstm_int_layer_params *layers, int32_t num_layers, int32_t T, int32_t B, int64_t *out) {
   const CalibratePlan p = calibrate_plan(layers, num_layers, T, B, 88);
   *out++ = (int64_t)p.total;
@@ -122,7 +122,7 @@ void hm_calibrate_plan(const lstm_int_layer_params *layers, int32_t num_layers, 
   };
   for (const CalibrateRegion *r : {&p.stats, &p.raw, &p.vec[0], &p.vec[1], &p.act[0], &p.act[1]}) put(*r);
   for (const CalibrateLayer &l : p.layers)
-    for (const CalibrateRegion *r : {&l.wop, &l.rop, &l.pop, &l.wx, &l.m, &l.h0, &l.c, &l.pre}) put(*r);
+    for (const CalibrateRegion *r : {&l.wop, &l.rop, &l.pop, &l.wx, &l.m, &l.h, &l.c, &l.pre}) put(*r);
 }
 
 // The library's offline phase on the host (what lstm_int_prepare runs before the upload); *checksum

@@ -66,6 +66,26 @@ def test_edges_of_the_products_and_of_the_cell(orc, I, N, H, flags, B, T):
     _compare(orc, layers, x)
 
 
+@pytest.mark.parametrize("I,N,H,flags,B,T", [
+    (16, 32, 32, wl.LAYER_NORM, 1, 3),                        # one group of 32 columns per gate
+    (24, 96, 96, wl.LAYER_NORM | wl.CIFG, 16, 4),
+    (24, 160, 48, wl.LAYER_NORM | wl.PROJECTION, 33, 3),      # two rows of tiles per workgroup, the last of one row
+    (16, 2080, 40, wl.LAYER_NORM | wl.PROJECTION, 3, 3),      # more than 64 groups per gate: two per lane
+    (16, 4096, 33, wl.LAYER_NORM | wl.PROJECTION | wl.CIFG, 2, 2),
+    (16, 2048, 64, wl.LAYER_NORM | wl.PROJECTION, 129, 2),    # blocks of 128: the sums from a pass over the row
+    (16, 96, 96, wl.LAYER_NORM | wl.PEEPHOLE, 5, 4),          # a gate's sum is not whole before the cell state is
+    (16, 64, 64, wl.LAYER_NORM, 256, 3),                      # the last batch with an extreme per thread
+    (16, 64, 64, wl.LAYER_NORM, 257, 3),
+    (16, 64, 64, 0, 300, 3),
+    (16, 516, 17, wl.PROJECTION, 5, 3),                       # a long k over four rows and 16 columns: remainders of all three
+    (16, 2048, 640, wl.PROJECTION, 16, 2),
+    (16, 3000, 3, wl.PROJECTION, 1, 2),
+])
+def test_sums_along_with_the_products_and_extremes_over_the_steps(orc, I, N, H, flags, B, T):
+    layers, x = wl.make_custom([I], N, H, flags, B, T, seed=N + B)
+    _compare(orc, layers, x)
+
+
 def test_c2_statistics_give_the_same_integer_model(orc):
     """At C2's shape the GPU statistics lead prepare to the very model the
     oracle's statistics lead to: every scale, multiplier and quantized tensor."""
