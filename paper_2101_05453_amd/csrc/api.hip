@@ -982,7 +982,7 @@ double sequential_us(const LayerHost &h, const RecPlan &p, int L, int64_t T, int
     step = 15.0 + 0.01 * h.N;
   } else if (p.solo) {
     once = 9.0 + 0.044 * h.N;
-    step = 0.3 + 0.006 * h.N + ln * (0.0095 * h.N - 0.3);
+    step = h.N <= 128 ? 0.28 + 0.0055 * h.N + ln * (0.0095 * h.N - 0.3) : 1.45 + ln * 1.55;  // 16 waves beyond 128 cells
   } else if (p.quad) {
     once = 15.5 + 1.5 * mb;
     step = 1.0 + 0.00105 * h.N + ln * 1.5 + pr * 1.1;

@@ -11,16 +11,16 @@ static int solo_form(int N, int H) {
   return -1;
 }
 static solo_fn pick_solo(int form, int fl) {
-  if (form == 0) return solo_pick_size<4, 1, 1>(fl);
-  if (form == 1) return solo_pick_size<8, 1, 2>(fl);
-  if (form == 2) return solo_pick_size<8, 2, 4>(fl);
+  if (form == 0) return solo_pick_size<4, 1>(fl);
+  if (form == 1) return solo_pick_size<8, 2>(fl);
+  if (form == 2) return solo_pick_size<16, 4>(fl);
   return nullptr;
 }
 
 // Where it is the faster one.  Time per step, us, this kernel / groups of 16 rows over several workgroups (before), up to
 // 1024 rows:   64 cells 0.9-1.1 / 2.6, with layer norm 1.8-1.9 / 4.4, and peephole 2.4 / 5.9
 //             128 cells 1.1-1.4 / 3.0-3.3,             2.2-2.5 / 4.7-5.1,              2.8-3.1 / 6.1-6.6
-//             256 cells 2.0-3.0 / 3.2-3.7,             4.1-4.7 / 4.8-5.4,              4.8-5.3 / 6.2-6.6
+//             256 cells 1.5-2.2 / 3.2-3.7,             3.1-3.6 / 4.8-5.4,              3.6-4.1 / 6.2-6.6
 // From 1025 rows on a second round of workgroups doubles it: still less up to 128 cells.
 bool solo_supported(int N, int H, int flags, int B) {
   const int form = solo_form(N, H);
@@ -60,7 +60,7 @@ hipError_t launch_solo(hipStream_t s, const RecArgs2 &a) {
   if (b.groups > 0) lds = lds > solo_lds_bytes(b) ? lds : solo_lds_bytes(b);
   RecArgs2 args = a;
   void *params[] = {&args};
-  return hipLaunchKernel(reinterpret_cast<const void *>(fn), dim3(f.groups + b.groups), dim3(form == 0 ? 256 : 512), params, lds, s);
+  return hipLaunchKernel(reinterpret_cast<const void *>(fn), dim3(f.groups + b.groups), dim3(form == 0 ? 256 : form == 1 ? 512 : 1024), params, lds, s);
 }
 
 }  // namespace lstm_int

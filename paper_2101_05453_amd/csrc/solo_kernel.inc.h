@@ -18,7 +18,11 @@
 // order; the W x terms are read in the layout the input GEMM writes for the 32-row
 // kernel.
 //
-// A wave takes CW blocks of 16 cells; WAVES * CW * 16 cells bound the layer.
+// A wave takes one block of 16 cells; WAVES * 16 cells bound the layer.  With 16 waves (129 to 256 cells) a lane has 128
+// registers, 64 of them weights: rescale constants are read from the arguments where they are used, layer-norm parameters
+// from LDS, and a layer-norm step works out lane numbers and addresses anew.  Eight waves of two blocks each have the
+// registers, and half as many waves to fill the gaps: 256 cells, 32 rows, a step without / with layer norm / and peephole
+// 1.85, 4.0, 4.9 us, with 16 waves 1.55, 3.1, 3.6.
 #pragma once
 
 #include "rec_kernel.inc.h"
@@ -26,17 +30,19 @@
 namespace lstm_int {
 
 // The LDS of a launch, from the front (solo_lds_bytes mirrors it): two h tiles, the m tile, statistics, tables, W_proj.
-template <int WAVES, int CW, int KS16, int FL>
+template <int WAVES, int KS16, int FL>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVES / 4, WAVES / 4))) void solo_kernel(RecArgs2 args) {
   constexpr bool cifg = FL & 1, ph = FL & 2, ln = FL & 4;
-  constexpr int NT = 64 * WAVES, NC = 16 * WAVES * CW, RG = 4;  // threads; cells and batch rows of the workgroup
-  constexpr bool LN_LDS = ln && CW > 1;  // layer-norm parameters in LDS: with two blocks per wave registers are short
+  constexpr int NT = 64 * WAVES, NC = 16 * WAVES, RG = 4;  // threads; cells and batch rows of the workgroup
+  constexpr bool LN_LDS = ln && WAVES > 8;  // layer-norm parameters in LDS
+  constexpr bool LEAN = WAVES == 16;
   constexpr int LS = KS16 * 64 + 16;           // row stride of the h and m tiles
   constexpr int g_first = cifg ? 1 : 0;
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int tid = threadIdx.x;
+  int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int c16 = lane & 15, q = lane >> 4;
+  int c16 = lane & 15, q = lane >> 4;
   const int which = (int)blockIdx.x >= args.d[0].groups ? 1 : 0;
   const RecDirArgs &a = args.d[which];
   const int row0 = ((int)blockIdx.x - (which ? args.d[0].groups : 0)) * RG;
@@ -92,31 +98,29 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
       }
     }
   }
-  const int blocks = a.Ncp >> 4;  // blocks of 16 cells the layer has (cells past N are zero weights)
-  v4i Wf[CW][4][KS16];            // [gate]: lane (c16, q) holds bytes 16 q.. of each 64-deep k step of cell c16's row
-  int32_t bh[CW][4], Pq[CW][3];
-  double wL[CW][4], wb[CW][4];    // not with LN_LDS
-#pragma unroll
-  for (int u = 0; u < CW; ++u) {
-    const int cb = wave + WAVES * u;
-    const bool real = cb < blocks;
+  const bool real = wave < (a.Ncp >> 4);  // the layer has this block of 16 cells (cells past N are zero weights)
+  v4i Wf[4][KS16];        // [gate]: lane (c16, q) holds bytes 16 q.. of each 64-deep k step of cell c16's row
+  int32_t bh[4], Pq[3];
+  double wL[4], wb[4];    // not with LN_LDS
+  {
+    const int cb = real ? wave : 0;
     // rec16_kernel's tile j holds, in row 4 q' + g, gate g of cell 4 q' + j
-    const int4 *src = a.R2h + (size_t)((real ? cb : 0) * 4 + (c16 & 3)) * a.ks16 * 64 + 4 * (c16 >> 2) + 16 * q;
+    const int4 *src = a.R2h + (size_t)(cb * 4 + (c16 & 3)) * a.ks16 * 64 + 4 * (c16 >> 2) + 16 * q;
     int4 w[4][KS16];
 #pragma unroll
     for (int g = 0; g < 4; ++g)
 #pragma unroll
       for (int ks = 0; ks < KS16; ++ks) w[g][ks] = real ? src[(size_t)ks * 64 + g] : int4{0, 0, 0, 0};
-    const size_t n = (real ? cb : 0) * 16 + c16;
+    const size_t n = cb * 16 + c16;
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      bh[u][g] = real ? a.bh4[(size_t)g * a.Ncp + n] : 0;
-      if (g < 3) Pq[u][g] = ph && real ? a.Pq3[(size_t)g * a.Ncp + n] : 0;
-      wL[u][g] = ln && real ? ln_weight_scaled(a.Lq4[(size_t)g * a.Ncp + n]) : 0.0;
-      wb[u][g] = ln && real ? ln_bias_scaled(a.qb4[(size_t)g * a.Ncp + n]) : 0.0;
+      bh[g] = real ? a.bh4[(size_t)g * a.Ncp + n] : 0;
+      if (g < 3) Pq[g] = ph && real ? a.Pq3[(size_t)g * a.Ncp + n] : 0;
+      wL[g] = ln && real ? ln_weight_scaled(a.Lq4[(size_t)g * a.Ncp + n]) : 0.0;
+      wb[g] = ln && real ? ln_bias_scaled(a.qb4[(size_t)g * a.Ncp + n]) : 0.0;
       if (LN_LDS && q == 0) {
-        LdL[g * NC + cb * 16 + c16] = wL[u][g];
-        bdL[g * NC + cb * 16 + c16] = wb[u][g];
+        LdL[g * NC + wave * 16 + c16] = wL[g];
+        bdL[g * NC + wave * 16 + c16] = wb[g];
       }
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -124,18 +128,29 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     for (int g = 0; g < 4; ++g)
 #pragma unroll
       for (int ks = 0; ks < KS16; ++ks) {
-        Wf[u][g][ks] = v4i{w[g][ks].x, w[g][ks].y, w[g][ks].z, w[g][ks].w};
-        asm volatile("" : "+a"(Wf[u][g][ks]));
+        Wf[g][ks] = v4i{w[g][ks].x, w[g][ks].y, w[g][ks].z, w[g][ks].w};
+        asm volatile("" : "+a"(Wf[g][ks]));
       }
     __builtin_amdgcn_sched_barrier(0);
   }
-  RescaleHi ps[4], pc[3], pl[4];
+  // rescale constants: kept, or with 16 waves (128 registers a lane, half of them weights) read again from the arguments
+  // where they are used
+  RescaleHi ps_[4], pc_[3], pl_[4];
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
-    ps[g] = rescale_hi_prepare(a.Mh[g], a.rh[g]);
-    pl[g] = rescale_hi_prepare(a.Mln[g], ln ? a.rln[g] : 33);
-    if (g < 3) pc[g] = rescale_hi_prepare(ph ? a.Mc[g] : 0, ph ? a.rc[g] : 33);
+    ps_[g] = rescale_hi_prepare(a.Mh[g], a.rh[g]);
+    pl_[g] = rescale_hi_prepare(a.Mln[g], ln ? a.rln[g] : 33);
+    if (g < 3) pc_[g] = rescale_hi_prepare(ph ? a.Mc[g] : 0, ph ? a.rc[g] : 33);
   }
+  typedef const __attribute__((address_space(4))) RecArgs2 *KernArgs;
+  auto fresh = [&] {
+    KernArgs k = (KernArgs)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(k));
+    return k;
+  };
+  auto ps = [&](KernArgs k, int g) { return LEAN ? rescale_hi_prepare(k->d[which].Mh[g], k->d[which].rh[g]) : ps_[g]; };
+  auto pl = [&](KernArgs k, int g) { return LEAN ? rescale_hi_prepare(k->d[which].Mln[g], k->d[which].rln[g]) : pl_[g]; };
+  auto pc = [&](KernArgs k, int j) { return LEAN ? rescale_hi_prepare(k->d[which].Mc[j], k->d[which].rc[j]) : pc_[j]; };
   if (tid < 16) red[tid] = 0;
   // the h tile before step 0; the other tile and m start as zeros (bytes past a row's real ones only meet zero weights)
   for (int i = tid; i < 3 * RG * LS / 4; i += NT) {
@@ -144,45 +159,34 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     reinterpret_cast<int32_t *>(hT)[i] = rr < RG && c < a.Hpad ? *reinterpret_cast<const int32_t *>(a.h0 + (size_t)row * a.Hpad + c) : 0;
   }
   // rows past the batch repeat the last one and are not stored
-  const bool row_ok = row0 + q < a.B;
-  const int row = row_ok ? row0 + q : a.B - 1;
-  int32_t creg[CW];
-#pragma unroll
-  for (int u = 0; u < CW; ++u) {
-    const int n = (wave + WAVES * u) * 16 + c16;
-    creg[u] = (a.c_in && n < a.N) ? a.c_in[(size_t)row * a.N + n] : 0;
-  }
+  bool row_ok = row0 + q < a.B;
+  int row = row_ok ? row0 + q : a.B - 1;
+  const int own = wave * 16 + c16;  // this lane's cell, and its output of the projection
+  int32_t creg = (a.c_in && own < a.N) ? a.c_in[(size_t)row * a.N + own] : 0;
   const double inv_n = 1.0 / (double)a.N;
   const bool pre_ln = ln && (a.rln[0] < 33 || a.rln[1] < 33 || a.rln[2] < 33 || a.rln[3] < 33);
   const bool pre_m = a.rm < 33;
-  const int T = a.T, pre_h = a.pre_h, rev = a.rev, N = a.N, H = a.H;
-  const RescaleHi pm = rescale_hi_prepare(a.Mm, a.rm), pp = rescale_hi_prepare(proj ? a.Mp : 0, proj ? a.rp : 33);
+  const int T = a.T, pre_h = a.pre_h, rev = a.rev, N = a.N, H = a.H, B = a.B;
+  const RescaleHi pm_ = rescale_hi_prepare(a.Mm, a.rm), pp_ = rescale_hi_prepare(proj ? a.Mp : 0, proj ? a.rp : 33);
   const int dom[3] = {a.lut[0].dom, a.lut[1].dom, a.lut[2].dom}, sh[3] = {a.lut[0].sh, a.lut[1].sh, a.lut[2].sh};
   const int32_t zp_m = a.zp_m, zp_h = a.zp_h, m_c = a.m_c;
-  int32_t bp[CW];  // projection bias of this lane's output in each of the wave's tiles of 16
-#pragma unroll
-  for (int u = 0; u < CW; ++u) {
-    const int o = (wave + WAVES * u) * 16 + c16;
-    bp[u] = proj && o < H ? a.bp2[o] : 0;
-  }
+  const int32_t bp = proj && own < H ? a.bp2[own] : 0;
 
   // W x terms: value (gate, cell) of row b is the int16 [2-gate half][lane][4 (gate % 2) + cell % 4] of the row's block;
   // two steps on their way (they come from memory, and a step is shorter than that)
   constexpr int AHEAD = 2;
-  int32_t txq[AHEAD][CW][4];
+  int32_t txq[AHEAD][4];
   const size_t tx_step = (size_t)(a.Bp >> 5) * (a.Ncp >> 3) * 1024;  // int16 values of one step
   const int16_t *const tx_base = reinterpret_cast<const int16_t *>(a.tx2) +
                                  ((size_t)(row >> 5) * (a.Ncp >> 3) + wave * 2 + (c16 >> 3)) * 1024 +
                                  ((row & 31) + 32 * ((c16 >> 2) & 1)) * 8 + (c16 & 3);
-  auto tx_request = [&](int t, int32_t (&dst)[CW][4]) {
+  auto tx_request = [&](int t, int32_t (&dst)[4]) {
     t = t < T ? t : T - 1;
     if (rev) t = T - 1 - t;
     const int16_t *src = tx_base + (size_t)t * tx_step;
 #pragma unroll
-    for (int u = 0; u < CW; ++u)
-#pragma unroll
-      for (int g = g_first; g < 4; ++g)  // a block the layer does not have: its gate sums are 0, as for padded cells
-        dst[u][g] = wave + WAVES * u < blocks ? src[u * WAVES * 2048 + (g >> 1) * 512 + (g & 1) * 4] : 0;
+    for (int g = g_first; g < 4; ++g)  // a block the layer does not have: its gate sums are 0, as for padded cells
+      dst[g] = real ? src[(g >> 1) * 512 + (g & 1) * 4] : 0;
   };
 #pragma unroll
   for (int s = 0; s < AHEAD; ++s) tx_request(s, txq[s]);
@@ -190,47 +194,42 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
   __syncthreads();
 
   // The sums of v and of v^2 over the cells of a row into red[gate][row], S2 in the bits above S1.  Squares are at most
-  // 2^30: the four of a quad of lanes fit 32 bits.  One block per wave: the four quads of a row add into the word (LDS
-  // atomics, four lanes to a word).  Two blocks: the quads first meet in the lanes too, S2 as two halves -- 64 times per
-  // step the four-lane atomics took 0.5 us more than that.
+  // 2^30: the four of a quad of lanes fit 32 bits, and the four quads of a row add into the word (LDS atomics, four lanes
+  // to a word; folding the quads in the lanes first, S2 as two halves, takes 0.1 to 0.2 us a step more at 256 cells).
   auto rot = [](int32_t x, auto ctrl) { return x + __builtin_amdgcn_mov_dpp(x, decltype(ctrl)::value, 0xF, 0xF, true); };
   auto add_stats = [&](int g, int32_t v) {
     using Q1 = std::integral_constant<int, 0xB1>;   // quad_perm [1,0,3,2]
     using Q2 = std::integral_constant<int, 0x4E>;   // quad_perm [2,3,0,1]
-    using R4 = std::integral_constant<int, 0x124>;  // row_ror:4
-    using R8 = std::integral_constant<int, 0x128>;  // row_ror:8
-    int32_t s1 = rot(rot(v, Q1{}), Q2{});
+    const int32_t s1 = rot(rot(v, Q1{}), Q2{});
     const uint32_t s2 = (uint32_t)rot(rot((int32_t)((uint32_t)v * (uint32_t)v), Q1{}), Q2{});
-    u64 S2 = s2;
-    if (CW > 1) {
-      s1 = rot(rot(s1, R4{}), R8{});
-      const uint32_t lo = (uint32_t)rot(rot((int32_t)(s2 & 0xFFFF), R4{}), R8{});
-      const uint32_t hi = (uint32_t)rot(rot((int32_t)(s2 >> 16), R4{}), R8{});
-      S2 = ((u64)hi << 16) + lo;
-    }
-    if (CW > 1 ? c16 == 0 : (lane & 3) == 0)
-      __hip_atomic_fetch_add(&red[g * 4 + q], (S2 << 24) + (u64)(int64_t)s1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if ((lane & 3) == 0)
+      __hip_atomic_fetch_add(&red[g * 4 + q], ((u64)s2 << 24) + (u64)(int64_t)s1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   };
   // gates g_lo..g_hi: one wave turns the sums into (mean, sigma) form
   auto statistics = [&](int g_lo, int g_hi) {
     __syncthreads();
-    if (tid < 64) {
-      const int item = lane & 15;  // (gate, row)
-      const bool here = lane < 16 && (item >> 2) >= g_lo && (item >> 2) <= g_hi;
+    if (wave == 0) {
+      int item = lane;  // (gate, row)
+      asm volatile("" : "+v"(item));  // worked out here, not kept through the step
+      const bool first16 = item < 16;
+      item &= 15;
+      const bool here = first16 && (item >> 2) >= g_lo && (item >> 2) <= g_hi;
       const int64_t pk = (int64_t)red[item];
       const int64_t S1 = ((pk + (1 << 23)) & 0xFFFFFF) - (1 << 23);  // 256 values of at most 32767: below 2^23
       const LnRow2 lr = ln_row2(S1, (pk - S1) >> 24, N, inv_n);
       const bool narrow = __builtin_amdgcn_ballot_w64(here && !ln_row_is_narrow(lr)) == 0;
       if (here) {
-        red[item] = 0;  // the next adds come after the barrier below
+        u64 zero = 0;
+        asm volatile("" : "+v"(zero));  // made here: as a constant of the loop it takes two registers
+        red[item] = zero;  // the next adds come after the barrier below
         lnrow[item] = lr;
       }
       if (lane == 0) flag[0] = narrow;
     }
     __syncthreads();
   };
-  // layer norm of K gate sums of block u
-  auto normalize = [&](auto count, int u, const int *gates, int32_t *v) {
+  // layer norm of K gate sums
+  auto normalize = [&](auto count, const int *gates, int32_t *v) {
     constexpr int K = decltype(count)::value;
     LnRow2 lr[K];
     double cL[K], cb[K];
@@ -238,10 +237,11 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     for (int k = 0; k < K; ++k) {
       const int g = gates[k];
       lr[k] = lnrow[g * 4 + q];
-      cL[k] = LN_LDS ? LdL[g * NC + (wave + WAVES * u) * 16 + c16] : wL[u][g];
-      cb[k] = LN_LDS ? bdL[g * NC + (wave + WAVES * u) * 16 + c16] : wb[u][g];
+      cL[k] = LN_LDS ? LdL[g * NC + wave * 16 + c16] : wL[g];
+      cb[k] = LN_LDS ? bdL[g * NC + wave * 16 + c16] : wb[g];
     }
     const bool narrow = __builtin_amdgcn_readfirstlane(flag[0]) != 0;
+    const KernArgs ka = fresh();
     __builtin_amdgcn_sched_barrier(0);
     if (narrow) {
 #pragma unroll
@@ -252,8 +252,9 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     }
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      if (pre_ln) v[k] = rescale_preshift(v[k], pl[gates[k]]);
-      v[k] = rescale_sat16_pre<0>(v[k], pl[gates[k]]);
+      const RescaleHi pg = pl(ka, gates[k]);
+      if (pre_ln) v[k] = rescale_preshift(v[k], pg);
+      v[k] = rescale_sat16_pre<0>(v[k], pg);
     }
   };
   // table values of |x| (table tb: 0 sigma, 1 tanh, 2 cell tanh) for K values at once; see rec_kernel's lookup
@@ -282,47 +283,53 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
   constexpr int32_t glo = ln ? -32767 : -32768;
   // first operand of the MFMA: result row 4 q is row q of the group; the other result rows read it too, and nobody uses
   // what comes of them
-  const int arow = c16 >> 2;
 
   for (int t = 0; t < T; ++t) {
+    if (LEAN && ln) {  // what follows from the lane is worked out in every step, not kept in registers that are not there
+      asm volatile("" : "+v"(lane));
+      c16 = lane & 15;
+      q = lane >> 4;
+      row_ok = row0 + q < B;
+      row = row_ok ? row0 + q : B - 1;
+    }
     const int8_t *hcur = hT + (t & 1) * RG * LS;
     int8_t *hnext = hT + ((t + 1) & 1) * RG * LS;
-    const size_t orow = (size_t)(rev ? T - 1 - t : t) * a.B + row;
-    int32_t gs[CW][4];
+    // this step's rows of the outputs; a lane's place in them fits 32 bits (at most 2048 rows)
+    const size_t orow0 = (size_t)(rev ? T - 1 - t : t) * a.B;
+    int8_t *const out_t = a.out + orow0 * a.Hpad, *const y_t = a.y ? a.y + orow0 * ldy : nullptr;
+    int32_t gs[4];
     {
       v4i hf[KS16];
 #pragma unroll
-      for (int ks = 0; ks < KS16; ++ks) hf[ks] = *reinterpret_cast<const v4i *>(hcur + arow * LS + (q << 4) + ks * 64);
+      for (int ks = 0; ks < KS16; ++ks) hf[ks] = *reinterpret_cast<const v4i *>(hcur + (c16 >> 2) * LS + (q << 4) + ks * 64);
+      v4i acc[4];
 #pragma unroll
-      for (int u = 0; u < CW; ++u) {
-        v4i acc[4];
+      for (int g = g_first; g < 4; ++g) {
+        acc[g] = v4i{0, 0, 0, 0};  // with the bias in it, four registers would be kept from step to step
 #pragma unroll
-        for (int g = g_first; g < 4; ++g) {
-          acc[g] = v4i{bh[u][g], 0, 0, 0};
+        for (int ks = 0; ks < KS16; ++ks) acc[g] = __builtin_amdgcn_mfma_i32_16x16x64_i8(hf[ks], Wf[g][ks], acc[g], 0, 0, 0);
+      }
+      // gate sums (Secs. 3.2.4/3.2.5); with a peephole the o gate is finished after c^t
+      const KernArgs ka = fresh();
+      auto gate_sums = [&](auto pre_tag) {
 #pragma unroll
-          for (int ks = 0; ks < KS16; ++ks) acc[g] = __builtin_amdgcn_mfma_i32_16x16x64_i8(hf[ks], Wf[u][g][ks], acc[g], 0, 0, 0);
+        for (int g = 0; g < 4; ++g) {
+          if (g < g_first) continue;
+          int32_t v = txq[0][g] + rescale_sat16_pre<decltype(pre_tag)::value>(acc[g][0] + bh[g], ps(ka, g));
+          if (ph && g < 2) v += rescale_sat16_pre(mul_i24(Pq[g < 3 ? g : 0], creg), pc(ka, g < 3 ? g : 0));
+          if (!(ph && g == 3)) v = clamp_i32(v, glo, 32767);
+          gs[g] = v;
         }
-        // gate sums (Secs. 3.2.4/3.2.5); with a peephole the o gate is finished after c^t
-        auto gate_sums = [&](auto pre_tag) {
+      };
+      if (pre_h == 0)
+        gate_sums(std::integral_constant<int, 0>{});
+      else if (pre_h == 1)
+        gate_sums(std::integral_constant<int, 1>{});
+      else
+        gate_sums(std::integral_constant<int, 2>{});
+      if (ln) {
 #pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            if (g < g_first) continue;
-            int32_t v = txq[0][u][g] + rescale_sat16_pre<decltype(pre_tag)::value>(acc[g][0], ps[g]);
-            if (ph && g < 2) v += rescale_sat16_pre(mul_i24(Pq[u][g < 3 ? g : 0], creg[u]), pc[g < 3 ? g : 0]);
-            if (!(ph && g == 3)) v = clamp_i32(v, glo, 32767);
-            gs[u][g] = v;
-          }
-        };
-        if (pre_h == 0)
-          gate_sums(std::integral_constant<int, 0>{});
-        else if (pre_h == 1)
-          gate_sums(std::integral_constant<int, 1>{});
-        else
-          gate_sums(std::integral_constant<int, 2>{});
-        if (ln) {
-#pragma unroll
-          for (int g = g_first; g < (ph ? 3 : 4); ++g) add_stats(g, gs[u][g]);
-        }
+        for (int g = g_first; g < (ph ? 3 : 4); ++g) add_stats(g, gs[g]);
       }
     }
     // the terms of the next step are taken over here, ahead of this step's stores: a wait for them further down would
@@ -330,48 +337,50 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
 #pragma unroll
     for (int s = 0; s + 1 < AHEAD; ++s)
 #pragma unroll
-      for (int u = 0; u < CW; ++u)
-#pragma unroll
-        for (int g = g_first; g < 4; ++g) {
-          txq[s][u][g] = txq[s + 1][u][g];
-          asm volatile("" : "+v"(txq[s][u][g]));
-        }
+      for (int g = g_first; g < 4; ++g) {
+        txq[s][g] = txq[s + 1][g];
+        asm volatile("" : "+v"(txq[s][g]));
+      }
     tx_request(t + AHEAD, txq[AHEAD - 1]);
     if (ln) statistics(g_first, ph ? 2 : 3);
 
     // layer norm, sigma / tanh, cell update (Secs. 3.2.6, 3.2.1, 3.2.9, 3.2.7)
-    int32_t xo[CW];
-#pragma unroll
-    for (int u = 0; u < CW; ++u) {
+    int32_t xo;
+    {
       // f, z, then o unless a peephole keeps it for later, then i unless it is coupled
       constexpr int KG = 4 - (ph ? 1 : 0) - (cifg ? 1 : 0);
       const int gates[4] = {1, 2, ph ? 0 : 3, 0}, tb[4] = {0, 1, 0, 0};
       int32_t x[4], tv[4];
 #pragma unroll
-      for (int k = 0; k < KG; ++k) x[k] = gs[u][gates[k]];
-      if (ln) normalize(std::integral_constant<int, KG>{}, u, gates, x);
+      for (int k = 0; k < KG; ++k) x[k] = gs[gates[k]];
+      if (ln && !LEAN) normalize(std::integral_constant<int, KG>{}, gates, x);
+      if (ln && LEAN) {  // two at a time
+        normalize(std::integral_constant<int, KG / 2>{}, gates, x);
+        normalize(std::integral_constant<int, KG - KG / 2>{}, gates + KG / 2, x + KG / 2);
+      }
       lookup(std::integral_constant<int, KG>{}, x, tb, tv);
-      const int32_t fg = mirror_sigmoid(x[0], tv[0]);
-      const int32_t ig = cifg ? cifg_input_gate(fg) : mirror_sigmoid(x[KG - 1], tv[KG - 1]);
-      xo[u] = ph ? 0 : mirror_sigmoid(x[2], tv[2]);
-      creg[u] = cell_update32(ig, mirror_tanh(x[1], tv[1]), fg, creg[u], m_c);
+      const int32_t fg = mirror_sigmoid_masked(x[0], tv[0]);
+      const int32_t ig = cifg ? cifg_input_gate(fg) : mirror_sigmoid_masked(x[KG - 1], tv[KG - 1]);
+      xo = ph ? 0 : mirror_sigmoid_masked(x[2], tv[2]);
+      creg = cell_update32(ig, mirror_tanh_masked(x[1], tv[1]), fg, creg, m_c);
       if (ph) {  // finish the o gate sum with P_o . c^t (eq. 5)
-        gs[u][3] = clamp_i32(gs[u][3] + rescale_sat16_pre(mul_i24(Pq[u][2], creg[u]), pc[2]), glo, 32767);
-        if (ln) add_stats(3, gs[u][3]);
+        gs[3] = clamp_i32(gs[3] + rescale_sat16_pre(mul_i24(Pq[2], creg), pc(fresh(), 2)), glo, 32767);
+        if (ln) add_stats(3, gs[3]);
       }
     }
     if (ph && ln) statistics(3, 3);
 
     // hidden state (Sec. 3.2.7)
-#pragma unroll
-    for (int u = 0; u < CW; ++u) {
-      const int cell = (wave + WAVES * u) * 16 + c16;
+    {
+      const int cell = wave * 16 + c16;
       const int tb[2] = {2, 0}, gates[1] = {3};
-      int32_t x[2] = {creg[u], gs[u][3]}, tv[2];
-      if (ph && ln) normalize(std::integral_constant<int, 1>{}, u, gates, x + 1);
+      int32_t x[2] = {creg, gs[3]}, tv[2];
+      if (ph && ln) normalize(std::integral_constant<int, 1>{}, gates, x + 1);
       lookup(std::integral_constant<int, ph ? 2 : 1>{}, x, tb, tv);
-      const int32_t o = ph ? mirror_sigmoid(x[1], tv[1]) : xo[u];
-      int32_t om = mul_i24(o, mirror_tanh(x[0], tv[0]));
+      const int32_t o = ph ? mirror_sigmoid_masked(x[1], tv[1]) : xo;
+      int32_t om = mul_i24(o, mirror_tanh_masked(x[0], tv[0]));
+      const KernArgs ka = fresh();
+      const RescaleHi pm = LEAN ? rescale_hi_prepare(ka->d[which].Mm, ka->d[which].rm) : pm_;
       if (pre_m) om = rescale_preshift(om, pm);
       const int8_t mq = (int8_t)sat8(rescale_sat16_pre<0>(om, pm) + zp_m);
       if (proj) {
@@ -379,8 +388,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
       } else {
         hnext[q * LS + cell] = mq;
         if (row_ok && cell < N) {
-          a.out[orow * a.Hpad + cell] = mq;
-          if (a.y) a.y[orow * ldy + cell] = mq;
+          out_t[(uint32_t)row * (uint32_t)a.Hpad + (uint32_t)cell] = mq;
+          if (y_t) y_t[(uint32_t)row * (uint32_t)ldy + (uint32_t)cell] = mq;
         }
       }
     }
@@ -388,51 +397,46 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     if (proj) {
       __syncthreads();
       v4i mf[KS16];
+      const KernArgs ka = fresh();
+      const RescaleHi pp = LEAN ? rescale_hi_prepare(ka->d[which].Mp, ka->d[which].rp) : pp_;
 #pragma unroll
-      for (int ks = 0; ks < KS16; ++ks) mf[ks] = *reinterpret_cast<const v4i *>(mT + arow * LS + (q << 4) + ks * 64);
+      for (int ks = 0; ks < KS16; ++ks) mf[ks] = *reinterpret_cast<const v4i *>(mT + (c16 >> 2) * LS + (q << 4) + ks * 64);
+      const int p0 = wave * 16;
+      if (p0 < H) {
+        v4i pacc = v4i{0, 0, 0, 0};
 #pragma unroll
-      for (int u = 0; u < CW; ++u) {
-        const int p0 = (wave + WAVES * u) * 16;
-        if (p0 < H) {
-          v4i pacc = v4i{bp[u], 0, 0, 0};
-#pragma unroll
-          for (int ks = 0; ks < KS16; ++ks)
-            pacc = __builtin_amdgcn_mfma_i32_16x16x64_i8(
-                mf[ks], *reinterpret_cast<const v4i *>(WpL + (p0 + c16) * LS + (q << 4) + ks * 64), pacc, 0, 0, 0);
-          const int8_t hq = (int8_t)sat8(rescale_sat16_pre(pacc[0], pp) + zp_h);
-          hnext[q * LS + p0 + c16] = hq;
-          if (row_ok && p0 + c16 < H) {
-            a.out[orow * a.Hpad + p0 + c16] = hq;
-            if (a.y) a.y[orow * ldy + p0 + c16] = hq;
-          }
+        for (int ks = 0; ks < KS16; ++ks)
+          pacc = __builtin_amdgcn_mfma_i32_16x16x64_i8(
+              mf[ks], *reinterpret_cast<const v4i *>(WpL + (p0 + c16) * LS + (q << 4) + ks * 64), pacc, 0, 0, 0);
+        const int8_t hq = (int8_t)sat8(rescale_sat16_pre(pacc[0] + bp, pp) + zp_h);
+        hnext[q * LS + p0 + c16] = hq;
+        if (row_ok && p0 + c16 < H) {
+          out_t[(uint32_t)row * (uint32_t)a.Hpad + (uint32_t)(p0 + c16)] = hq;
+          if (y_t) y_t[(uint32_t)row * (uint32_t)ldy + (uint32_t)(p0 + c16)] = hq;
         }
       }
     }
     __syncthreads();  // the next h tile is complete
   }
   if (a.c_out && row_ok) {
-#pragma unroll
-    for (int u = 0; u < CW; ++u) {
-      const int n = (wave + WAVES * u) * 16 + c16;
-      if (n < N) a.c_out[(size_t)row * N + n] = (int16_t)creg[u];
-    }
+    if (own < N) a.c_out[(size_t)row * N + own] = (int16_t)creg;
   }
 }
 
 typedef void (*solo_fn)(RecArgs2);
 
 // kernel for (flags & 7)
-template <int WAVES, int CW, int KS16>
+template <int WAVES, int KS16>
 solo_fn solo_pick_size(int fl) {
   switch (fl & 7) {
-    case 0: return solo_kernel<WAVES, CW, KS16, 0>;
-    case 1: return solo_kernel<WAVES, CW, KS16, 1>;
-    case 2: return solo_kernel<WAVES, CW, KS16, 2>;
-    case 3: return solo_kernel<WAVES, CW, KS16, 3>;
-    case 4: return solo_kernel<WAVES, CW, KS16, 4>;
-    case 5: return solo_kernel<WAVES, CW, KS16, 5>;
-    case 6: return solo_kernel<WAVES, CW, KS16, 6>;
-    default: return solo_kernel<WAVES, CW, KS16, 7>;
+    case 0: return solo_kernel<WAVES, KS16, 0>;
+    case 1: return solo_kernel<WAVES, KS16, 1>;
+    case 2: return solo_kernel<WAVES, KS16, 2>;
+    case 3: return solo_kernel<WAVES, KS16, 3>;
+    case 4: return solo_kernel<WAVES, KS16, 4>;
+    case 5: return solo_kernel<WAVES, KS16, 5>;
+    case 6: return solo_kernel<WAVES, KS16, 6>;
+    default: return solo_kernel<WAVES, KS16, 7>;
   }
 }
 
