@@ -50,8 +50,8 @@ size_t rec16_lds_bytes(const RecArgs &a) {
   const int items = 64;
   const bool proj = a.flags & 8;
   size_t tile = (((size_t)16 * (a.ks16 * 64 + 16) + 1023) / 1024 + 1) * 1024;
-  if (proj && tile < 4 * 2 * 4 * 64 * 4) tile = 4 * 2 * 4 * 64 * 4;
-  size_t n = tile + (size_t)items * 8 + (size_t)items * sizeof(LnRow2) + 2 * 4 * 64 * 8 + 4 * 64 * 4 + 4 * 64 * 2 +
+  if (proj && tile < 8 * 2 * 64 * 16) tile = 8 * 2 * 64 * 16;
+  size_t n = tile + 16 * 80 + (size_t)items * 8 + (size_t)items * sizeof(LnRow2) + 2 * 4 * 64 * 8 + 4 * 64 * 4 + 4 * 64 * 2 +
              256 /* PrmLds */ + 16 + 16 * 8 + 3 * 32 /* LutLds */;
   for (int i = 0; i < 3; ++i)
     if (i < 2 || a.lut[2].blob != a.lut[1].blob) n += (size_t)lut_wide_lds_bytes(a.lut[i].dom, a.lut[i].sh, a.lut[i].tail != 0);
@@ -82,9 +82,9 @@ hipError_t launch_rec16(hipStream_t s, const RecArgs &a, bool cooperative) {
   RecArgs args = a;
   void *params[] = {&args};
   if (cooperative)
-    return hipLaunchCooperativeKernel(reinterpret_cast<const void *>(fn), dim3(8 * slots), dim3(256), params,
+    return hipLaunchCooperativeKernel(reinterpret_cast<const void *>(fn), dim3(8 * slots), dim3(512), params,
                                       (unsigned)rec16_lds_bytes(a), s);
-  return hipLaunchKernel(reinterpret_cast<const void *>(fn), dim3(8 * slots), dim3(256), params,
+  return hipLaunchKernel(reinterpret_cast<const void *>(fn), dim3(8 * slots), dim3(512), params,
                          (unsigned)rec16_lds_bytes(a), s);
 }
 
@@ -99,7 +99,7 @@ hipError_t launch_rec16_pair(hipStream_t s, const RecArgs2 &a, bool cooperative)
   void *params[] = {&args};
   const auto launch = cooperative ? [](const void *k, dim3 g, dim3 t, void **p, size_t l, hipStream_t st) { return hipLaunchCooperativeKernel(k, g, t, p, (unsigned)l, st); }
                                   : [](const void *k, dim3 g, dim3 t, void **p, size_t l, hipStream_t st) { return hipLaunchKernel(k, g, t, p, l, st); };
-  return launch(reinterpret_cast<const void *>(fn), dim3(8 * slots), dim3(256), params, lf > lb ? lf : lb, s);
+  return launch(reinterpret_cast<const void *>(fn), dim3(8 * slots), dim3(512), params, lf > lb ? lf : lb, s);
 }
 
 }  // namespace lstm_int

@@ -4,12 +4,18 @@
 // chip and a workgroup's arithmetic per step is half as long).  FL: bit 0 CIFG,
 // bit 1 peephole, bit 2 layer norm; the projection is a runtime flag.
 //
-// Lane (r = lane % 16, q = lane / 16) of wave w owns batch row r of the group
-// and cells 16 w + 4 q + c, c = 0..3, of the workgroup's 64, all four gates:
-// weight tile j of the wave holds, in row 4 q' + gate, cell 16 w + 4 q' + j,
-// so that result value `gate` of tile j in that lane is (cell 4 q + j, gate).
-// The W x terms are read in the layout the input GEMM writes for the 32-row
-// kernel (two 16-byte loads per lane and step).
+// Eight waves, two to a block of 16 cells.  Lane (r = lane % 16, q = lane / 16)
+// of wave w = 2 b + s owns batch row r of the group and cells 16 b + 4 q + 2 s + c,
+// c = 0, 1, of the workgroup's 64, all four gates: weight tile j of the block
+// holds, in row 4 q' + gate, cell 16 b + 4 q' + j, so that result value `gate` of
+// the wave's tile c in that lane is (cell 4 q + 2 s + c, gate).  The W x terms are
+// read in the layout the input GEMM writes for the 32-row kernel.
+//
+// What bounds it: the exchanges of a step (two, one without a projection, and one
+// per round of statistics, 0.9 to 1.2 us each) and the instructions between them.
+// Two waves per SIMD issue those in less time than one of twice the work: 128 rows
+// of 2048 cells, projection to 640: 6.3 -> 5.9 us a step, with layer norm 8.3 -> 8.1,
+// and peephole 9.4 -> 9.2; 512 cells, 200 rows 3.1 -> 2.9, with layer norm 4.8 -> 4.6.
 #pragma once
 
 #include "rec_kernel.inc.h"
@@ -37,13 +43,15 @@ __device__ __forceinline__ int rec16_rev(const RecDirArgs &a) { return a.rev; }
 
 // PAIR: the launch runs two layers of one shape side by side, each possibly backward in time (RecArgs2).
 template <int KS16, int FL, bool PAIR = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void rec16_kernel(
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void rec16_kernel(
     std::conditional_t<PAIR, RecArgs2, RecArgs> args) {
   constexpr bool cifg = FL & 1, ph = FL & 2, ln = FL & 4;
   const long long t_start = (long long)wall_clock64();
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int r = lane & 15, q = lane >> 4;
+  const int tid = threadIdx.x;
+  int lane = tid & 63;
+  const int wave = KS16 > 10 ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
+  int r = lane & 15, q = lane >> 4;
   constexpr int g_first = cifg ? 1 : 0;
   const auto &a0 = rec16_args(args, 0);
   const int GS = a0.GS;
@@ -89,19 +97,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   auto time_of = [&](int t) { return rec16_rev(a) ? a.T - 1 - t : t; };
   constexpr int items = 64;                    // (gate, row) layer-norm rows of the group
   const int row0 = a.batch0 + group * 16;      // first batch row of the group
-  const int cellw = wave * 16 + 4 * q;         // + c, within the workgroup's 64 cells
+  int cellw = (wave >> 1) * 16 + 4 * q + 2 * (wave & 1);  // + c, within the workgroup's 64 cells
 
   // ---- LDS carve-up (rec16_lds_bytes mirrors it)
   constexpr int LS = KS16 * 64 + 16;  // h tile row stride: LS / 4 = 4 * odd (mod 64), reads are conflict-free
   constexpr int TILE_KB = (16 * LS + 1023) / 1024;
+  constexpr int MS = 80;  // row stride of the tile of 64 cells
+  // m or h of a step leaves through LDS, by one wave in stores of 16 bytes a lane, which are acknowledged 0.25 us before those
+  // of two bytes a lane from all waves.  Behind a second round of statistics the barrier that takes costs more: 2048 cells
+  // with peephole and layer norm 9.2 -> 9.5 us a step.
+  constexpr bool GATHER = !(ph && ln);
   uint8_t *p = lds;
   int8_t *hT = reinterpret_cast<int8_t *>(p);
-  int32_t *pred = reinterpret_cast<int32_t *>(p);  // projection partials reuse the h tile between steps
+  v4i *pred = reinterpret_cast<v4i *>(p);  // projection partials [8 waves][2 halves][64 lanes] reuse the h tile between steps
   {
     const size_t tile_bytes = (size_t)(TILE_KB + 1) * 1024;  // one spare chunk for the loads past the tile
-    const size_t pred_bytes = proj ? 4 * 2 * 4 * 64 * 4 : 0;
+    const size_t pred_bytes = proj ? 8 * 2 * 64 * 16 : 0;
     p += tile_bytes > pred_bytes ? tile_bytes : pred_bytes;
   }
+  int8_t *mS = reinterpret_cast<int8_t *>(p);            p += 16 * MS;  // hidden state of the step, on its way out
   u64 *red = reinterpret_cast<u64 *>(p);                 p += (size_t)items * 8;  // [item] sums
   LnRow2 *lnrow = reinterpret_cast<LnRow2 *>(p);         p += (size_t)items * sizeof(LnRow2);
   double *LdL = reinterpret_cast<double *>(p);           p += 4 * 64 * 8;
@@ -143,7 +157,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       const int nd = a.lut[i].dom >> 10;
       const int nb = (((a.lut[i].dom >> a.lut[i].sh) * 2) + 1023) >> 10;
       const int nt = a.lut[i].tail ? 3 : 0;
-      for (int c = wave; c < nd + nb + nt; c += 4) {
+      for (int c = wave; c < nd + nb + nt; c += 8) {
         const int so = c < nd ? c * 1024 : (c < nd + nb ? kLutWideBaseOff + (c - nd) * 1024 : kLutWideTailOff + (c - nd - nb) * 1024);
         dma(a.lut[i].blob + so + lane * 16, lutD[i] + c * 1024);
       }
@@ -159,7 +173,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     }
     const int wp_rows = my_ptiles * 32;
     const int wp_chunks = (wp_rows * WLS + 1023) >> 10;
-    for (int c = wave; c < wp_chunks; c += 4) {
+    for (int c = wave; c < wp_chunks; c += 8) {
       const int o = c * 1024 + lane * 16;
       const int rr = o / WLS, col_b = o - rr * WLS;
       const int8_t *src = a.Wp2;
@@ -170,14 +184,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       dma(src, WpL + c * 1024);
     }
   }
-  v4i Wf[4][KS16];
+  v4i Wf[2][KS16];
   {
-    const int4 *src = a.R2h + ((size_t)(member * 4 + wave) * 4) * KS16 * 64 + lane;
+    const int4 *src = a.R2h + ((size_t)(member * 4 + (wave >> 1)) * 4 + 2 * (wave & 1)) * KS16 * 64 + lane;
     // all loads of the slice are issued before the first value is pinned (a pin waits for its load);
-    // at the deepest k the staging registers do not hold four tiles, so two at a time
-    constexpr int TB = KS16 <= 10 ? 4 : 2;
+    // at the deepest k the staging registers do not hold both tiles
+    constexpr int TB = KS16 <= 10 ? 2 : 1;
 #pragma unroll
-    for (int j0 = 0; j0 < 4; j0 += TB) {
+    for (int j0 = 0; j0 < 2; j0 += TB) {
       int4 w[TB][KS16];
 #pragma unroll
       for (int j = 0; j < TB; ++j)
@@ -194,8 +208,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  {
-    const int g = tid >> 6, n = tid & 63;  // 256 threads = 4 gates x 64 cells
+  if (tid < 256) {
+    const int g = tid >> 6, n = tid & 63;  // 4 gates x 64 cells
     const size_t idx = (size_t)g * a.Ncp + member * 64 + n;
     LdL[tid] = ln_weight_scaled(a.Lq4[idx]);
     bdL[tid] = ln_bias_scaled(a.qb4[idx]);
@@ -213,22 +227,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     prm->zp_m = a.zp_m; prm->zp_h = a.zp_h;
     prm->m_c = a.m_c; prm->glo = -32767;
   }
-  for (int i = tid; i < 16 * LS / 16; i += 256) reinterpret_cast<int4 *>(hT)[i] = int4{0, 0, 0, 0};
+  for (int i = tid; i < 16 * LS / 16; i += 512) reinterpret_cast<int4 *>(hT)[i] = int4{0, 0, 0, 0};
 
-  // cell state of this lane's 4 cells of its row, kept in registers
-  const int row = row0 + r;
-  const int n0 = member * 64 + cellw;
-  int32_t creg[4];
+  // cell state of this lane's cells of its row, kept in registers
+  int row = row0 + r;
+  int n0 = member * 64 + cellw;
+  int32_t creg[2];
 #pragma unroll
-  for (int c = 0; c < 4; ++c)
+  for (int c = 0; c < 2; ++c)
     creg[c] = (a.c_in && row < a.B && n0 + c < a.N) ? a.c_in[(size_t)row * a.N + n0 + c] : 0;
 
-  // h tile staging: wave instruction (wave + 4 j) fills bytes [1024 c, 1024 (c + 1)) of the tile
-  constexpr int NCH = (TILE_KB + 3) / 4;
+  // h tile staging: wave instruction (wave + 8 j) fills bytes [1024 c, 1024 (c + 1)) of the tile
+  constexpr int NCH = (TILE_KB + 7) / 8;
   int hsrc[NCH];
 #pragma unroll
   for (int j = 0; j < NCH; ++j) {
-    const int o = (wave + 4 * j) * 1024 + lane * 16;
+    const int o = (wave + 8 * j) * 1024 + lane * 16;
     const int rr = o / LS, c = o - rr * LS;
     int rw = row0 + rr;
     rw = rw < a.B ? rw : a.B - 1;
@@ -269,23 +283,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   }
   TICK(10);  // everything before the first step
 
-  // the two 16-byte W x pieces of this lane for step t, read in the layout of the 32-row kernel:
-  // cell tile of 8 = 2 wave + q / 2, lane there = row % 32 + 32 * (q % 2)
-  v4i txn0, txn1;
+  // this lane's W x terms of step t, a pair of cells of each gate in a word, read in the layout of the 32-row kernel:
+  // cell tile of 8 = 2 (wave / 2) + q / 2, lane there = row % 32 + 32 * (q % 2), whose two pieces hold gates 0, 1 and 2, 3
+  // of four cells
+  int32_t txn[4];
   auto tx_request = [&](int t) {
     if (PAIR) t = time_of(t < a.T ? t : a.T - 1);
     size_t rb = ((size_t)t * a.Bp + row0) >> 5;
     const size_t rbmax = ((size_t)a.T * a.Bp) >> 5;
     rb = rb < rbmax ? rb : rbmax - 1;
-    const int4 *src = a.tx2 + ((rb * (size_t)(GS * 8) + member * 8 + wave * 2 + (q >> 1)) * 2) * 64 +
-                      ((row0 + r) & 31) + 32 * (q & 1);
+    const int32_t *src = reinterpret_cast<const int32_t *>(
+        a.tx2 + ((rb * (size_t)(GS * 8) + member * 8 + (wave >> 1) * 2 + (q >> 1)) * 2) * 64 + ((row0 + r) & 31) + 32 * (q & 1)) + (wave & 1);
     // read once: streaming loads keep the W x terms from displacing the exchange buffers in L2
-    txn0 = __builtin_nontemporal_load(reinterpret_cast<const v4i *>(src));
-    txn1 = __builtin_nontemporal_load(reinterpret_cast<const v4i *>(src + 64));
+#pragma unroll
+    for (int g = 0; g < 4; ++g) txn[g] = __builtin_nontemporal_load(src + (g >> 1) * 256 + (g & 1) * 2);
   };
   tx_request(0);
 
   for (int t = 0; t < a.T; ++t) {
+    if (KS16 > 10) {  // half of the registers are weights: what follows from the lane is worked out in every step
+      asm volatile("" : "+v"(lane));
+      r = lane & 15;
+      q = lane >> 4;
+      cellw = (wave >> 1) * 16 + 4 * q + 2 * (wave & 1);
+      row = row0 + r;
+      n0 = member * 64 + cellw;
+    }
     // ---- h^{t-1} rows of the group -> LDS
     {
       const int8_t *hp = t == 0 ? a.h0 : a.out + (size_t)time_of(t - 1) * a.B * a.Hpad;
@@ -293,34 +316,40 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       for (int j = 0; j < NCH; ++j)
         __builtin_amdgcn_global_load_lds(
             (const __attribute__((address_space(1))) void *)(hp + hsrc[j]),
-            (__attribute__((address_space(3))) void *)(lds + (wave + 4 * j < TILE_KB ? wave + 4 * j : TILE_KB) * 1024),
+            (__attribute__((address_space(3))) void *)(lds + (wave + 8 * j < TILE_KB ? wave + 8 * j : TILE_KB) * 1024),
             16, 0, 0);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
     __syncthreads();
     // the W x terms of this step were requested one step ahead (they come from HBM)
-    const int32_t txw[8] = {txn0.x, txn0.y, txn0.z, txn0.w, txn1.x, txn1.y, txn1.z, txn1.w};
+    const int32_t txw[4] = {txn[0], txn[1], txn[2], txn[3]};
     TICK(0);
 
-    // ---- R h on the MFMA: acc[j][gate] for cell 4 q + j; each tile's k loop runs to its end
+    // ---- R h on the MFMA: acc[j][gate] for the lane's cell j; each tile's k loop runs to its end
     // before the next tile starts (dependent 16x16x64 MFMAs issue back to back, rotating
     // accumulators do not)
-    v4i acc[4];
+    v4i acc[2];
     RescaleHi ph4[4];  // the R h rescale constants, read here so that the MFMAs cover the LDS round trip
 #pragma unroll
     for (int g = 0; g < 4; ++g) ph4[g] = prm->h[g];
     {
-      v4i hf[KS16];
+      constexpr int KC = KS16 <= 10 ? KS16 : KS16 / 2;  // k steps at a time: the deepest k leaves no registers for all
       const int8_t *hbase = hT + (size_t)r * LS + (q << 4);
 #pragma unroll
-      for (int ks = 0; ks < KS16; ++ks) hf[ks] = *reinterpret_cast<const v4i *>(hbase + ks * 64);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
+      for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int g = 0; g < 4; ++g) acc[j][g] = bhL[g * 64 + cellw + j];
 #pragma unroll
-        for (int ks = 0; ks < KS16; ++ks)
-          acc[j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(Wf[j][ks], hf[ks], acc[j], 0, 0, 0);
+      for (int k0 = 0; k0 < KS16; k0 += KC) {
+        v4i hf[KC];
+#pragma unroll
+        for (int ks = 0; ks < KC; ++ks) hf[ks] = *reinterpret_cast<const v4i *>(hbase + (k0 + ks) * 64);
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int ks = 0; ks < KC; ++ks)
+            acc[j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(Wf[j][k0 + ks], hf[ks], acc[j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
 
@@ -329,20 +358,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     // ---- gate sums (Secs. 3.2.4/3.2.5) and layer-norm partial statistics.
     // With a peephole the o gate keeps tx + th here and is finished after c^t.
     constexpr int32_t glo = ln ? -32767 : -32768;  // layer norm takes symmetric gate sums
-    int32_t gs[4][4];  // [gate][cell]
+    int32_t gs[4][2];  // [gate][cell]
     auto gate_sums = [&](auto pre_tag) {
       constexpr int PRE = decltype(pre_tag)::value;
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const RescaleHi pg = ph4[g];
         int32_t s1 = 0;
-        uint32_t s2 = 0;  // four squares of 16-bit values fit 32 bits
+        uint32_t s2 = 0;  // squares of 16-bit values
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const int idx = g * 4 + c;
+        for (int c = 0; c < 2; ++c) {
           const int32_t th = rescale_sat16_pre<PRE>(acc[c][g], pg);
-          const int32_t w = txw[idx >> 1];
-          const int32_t tx = (idx & 1) ? (w >> 16) : (int32_t)(int16_t)(w & 0xFFFF);
+          const int32_t tx = c ? (txw[g] >> 16) : (int32_t)(int16_t)(txw[g] & 0xFFFF);
           int32_t v = tx + th;
           if (ph && g < 2) v += rescale_sat16_pre(mul_i24(PqL[g * 64 + cellw + c], creg[c]), prm->c[g]);
           if (!(ph && g == 3)) v = clamp_i32(v, glo, 32767);
@@ -351,7 +378,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
           s2 += (uint32_t)v * (uint32_t)v;
         }
         if (ln && !(ph && g == 3)) {
-          // the 16 lanes of a row (4 per wave) add into one LDS word: no cross-lane traffic, no wait
+          // the 32 lanes of a row (4 per wave) add into one LDS word: no cross-lane traffic, no wait
           const int64_t pk = ((int64_t)(u64)s2 << 24) + s1;
           __hip_atomic_fetch_add(&red[g * 16 + r], (u64)pk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
@@ -363,8 +390,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       gate_sums(std::integral_constant<int, 1>{});
     else
       gate_sums(std::integral_constant<int, 2>{});
-    tx_request(t + 1);  // past the last step: the last block again, unused
-
     // statistics over the group's workgroups: as in rec_kernel (words that are never reset, the top
     // byte counts the adds); item = 16 gate + row
     auto publish_stats = [&](int round, int g_lo, int g_hi) {
@@ -422,10 +447,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       if (!collect_stats(0, g_first, ph ? 2 : 3)) return;
       TICK(4);
     }
+    // past the last step: the last block again, unused.  Not ahead of the statistics, whose wait takes 0.5 us longer beside
+    // loads from memory.
+    tx_request(t + 1);
 
     // ---- layer norm, sigma/tanh, cell update (Secs. 3.2.6, 3.2.1, 3.2.9, 3.2.7); LDS reads in batches
     // gates of `gmask` (bit g): gate sums -> layer norm -> xv[g][c]
-    auto normalize = [&](int gmask, int32_t (&xv)[4][4]) {
+    auto normalize = [&](int gmask, int32_t (&xv)[4][2]) {
       if (ln) {
         LnRow2 lr[4];
         bool wide = false;
@@ -441,14 +469,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
         for (int gp = 0; gp < 4; gp += 2) {
           if (!(gmask >> gp & 3)) continue;
-          double wL[2][4], wb[2][4];
+          double wL[2][2], wb[2][2];
           RescaleHi pl[2];
 #pragma unroll
           for (int g = gp; g < gp + 2; ++g)
             if (gmask >> g & 1) {
               pl[g - gp] = prm->ln[g];
 #pragma unroll
-              for (int c = 0; c < 4; ++c) {
+              for (int c = 0; c < 2; ++c) {
                 wL[g - gp][c] = LdL[g * 64 + cellw + c];
                 wb[g - gp][c] = bdL[g * 64 + cellw + c];
               }
@@ -458,7 +486,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
           for (int g = gp; g < gp + 2; ++g)
             if (gmask >> g & 1)
 #pragma unroll
-              for (int c = 0; c < 4; ++c) {
+              for (int c = 0; c < 2; ++c) {
                 int32_t v = decltype(narrow_tag)::value ? ln_second_stage_narrow(gs[g][c], lr[g], wL[g - gp][c], wb[g - gp][c])
                                                         : ln_second_stage(gs[g][c], lr[g], wL[g - gp][c], wb[g - gp][c]);
                 if (pre_ln) v = rescale_preshift(v, pl[g - gp]);
@@ -475,14 +503,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         for (int g = 0; g < 4; ++g)
           if (gmask >> g & 1)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) xv[g][c] = gs[g][c];
+            for (int c = 0; c < 2; ++c) xv[g][c] = gs[g][c];
       }
     };
     // table values of |x[g][c]| for the gates of gmask; tb[g] = which table (0 sigma, 1 tanh, 2 cell tanh);
     // see rec_kernel's lookup
-    auto lookup = [&](int gmask, const int32_t (&x)[4][4], const int (&tb)[4], int32_t (&out)[4][4]) {
-      int32_t mag[4][4];
-      uint32_t base[4][4], delta[4][4];
+    auto lookup = [&](int gmask, const int32_t (&x)[4][2], const int (&tb)[4], int32_t (&out)[4][2]) {
+      int32_t mag[4][2];
+      uint32_t base[4][2], delta[4][2];
       int32_t top[3] = {0, 0, 0};  // largest |x| looked up in each table
       LutLds lp[3];
 #pragma unroll
@@ -497,8 +525,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         if (gmask >> g & 1) {
           const int dom = lp[tb[g]].dom, sh = lp[tb[g]].sh;
 #pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            mag[g][c] = abs_i32(x[g][c]);
+          for (int c = 0; c < 2; ++c) {
+            mag[g][c] = abs_masked(x[g][c]);
             top[tb[g]] = top[tb[g]] > mag[g][c] ? top[tb[g]] : mag[g][c];
             const int32_t ai = mag[g][c] < dom ? mag[g][c] : dom - 1;
             base[g][c] = *reinterpret_cast<const uint16_t *>(lds + lp[tb[g]].offB + 2 * (ai >> sh));
@@ -510,7 +538,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       for (int g = 0; g < 4; ++g)
         if (gmask >> g & 1)
 #pragma unroll
-          for (int c = 0; c < 4; ++c) out[g][c] = (int32_t)(base[g][c] + delta[g][c]);
+          for (int c = 0; c < 2; ++c) out[g][c] = (int32_t)(base[g][c] + delta[g][c]);
       bool over = false;
 #pragma unroll
       for (int i = 0; i < 3; ++i) {
@@ -524,34 +552,34 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         for (int g = 0; g < 4; ++g)
           if ((gmask >> g & 1) && lp[tb[g]].offT) {
             const int dom = lp[tb[g]].dom;
-            const bool og = mag[g][0] >= dom || mag[g][1] >= dom || mag[g][2] >= dom || mag[g][3] >= dom;
+            const bool og = mag[g][0] >= dom || mag[g][1] >= dom;
             if (__builtin_amdgcn_ballot_w64(og) != 0) {
 #pragma unroll
-              for (int c = 0; c < 4; ++c)
+              for (int c = 0; c < 2; ++c)
                 if (mag[g][c] >= dom) out[g][c] = lut_wide_tail(lds + lp[tb[g]].offT, mag[g][c]);
             }
           }
       }
     };
     constexpr int gates_now = (cifg ? 0 : 1) | 2 | 4 | (ph ? 0 : 8);  // with a peephole the o gate waits for c^t
-    int32_t xv[4][4], tv[4][4];
+    int32_t xv[4][2], tv[4][2];
     normalize(gates_now, xv);
     {
       const int gate_tb[4] = {0, 0, 1, 0};
       lookup(gates_now, xv, gate_tb, tv);
     }
     const int32_t m_c = prm->m_c;
-    int32_t xo[4];
-    int32_t cx[4][4];  // slot 0: the new cell state, for its tanh; slot 3: the o gate with a peephole
+    int32_t xo[2];
+    int32_t cx[4][2];  // slot 0: the new cell state, for its tanh; slot 3: the o gate with a peephole
     {
       int32_t s1 = 0;
       uint32_t s2 = 0;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const int32_t fg = mirror_sigmoid(xv[1][c], tv[1][c]);
-        const int32_t ig = cifg ? cifg_input_gate(fg) : mirror_sigmoid(xv[0][c], tv[0][c]);
-        const int32_t zg = mirror_tanh(xv[2][c], tv[2][c]);
-        xo[c] = ph ? 0 : mirror_sigmoid(xv[3][c], tv[3][c]);
+      for (int c = 0; c < 2; ++c) {
+        const int32_t fg = mirror_sigmoid_masked(xv[1][c], tv[1][c]);
+        const int32_t ig = cifg ? cifg_input_gate(fg) : mirror_sigmoid_masked(xv[0][c], tv[0][c]);
+        const int32_t zg = mirror_tanh_masked(xv[2][c], tv[2][c]);
+        xo[c] = ph ? 0 : mirror_sigmoid_masked(xv[3][c], tv[3][c]);
         creg[c] = cell_update32(ig, zg, fg, creg[c], m_c);
         cx[0][c] = creg[c];
         if (ph) {  // finish the o gate sum with P_o . c^t (eq. 5)
@@ -571,7 +599,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     // ---- hidden state (Sec. 3.2.7): tanh of the new cell state in its own format (Sec. 3.2.2), and
     // with a peephole the layer norm and sigma of the o gate; the tanh does not wait for the o gate's
     // statistics, so it runs while they travel
-    int32_t tcv[4][4];
+    int32_t tcv[4][2];
     const int hid_tb[4] = {2, 2, 2, 0};
     if (ph && ln) {
       publish_stats(1, 3, 3);
@@ -581,36 +609,61 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       lookup(1, cx, hid_tb, tcv);
     }
     if (ph) {
-      int32_t ov[4][4];
+      int32_t ov[4][2];
       normalize(8, ov);
 #pragma unroll
-      for (int c = 0; c < 4; ++c) cx[3][c] = ov[3][c];
+      for (int c = 0; c < 2; ++c) cx[3][c] = ov[3][c];
       lookup(8, cx, hid_tb, tcv);
 #pragma unroll
-      for (int c = 0; c < 4; ++c) xo[c] = mirror_sigmoid(cx[3][c], tcv[3][c]);
+      for (int c = 0; c < 2; ++c) xo[c] = mirror_sigmoid_masked(cx[3][c], tcv[3][c]);
     }
     {
       const RescaleHi pm = prm->m;
       const int32_t zp_m = prm->zp_m;
       uint32_t pk = 0;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        int32_t om = mul_i24(xo[c], mirror_tanh(cx[0][c], tcv[0][c]));
+      for (int c = 0; c < 2; ++c) {
+        int32_t om = mul_i24(xo[c], mirror_tanh_masked(cx[0][c], tcv[0][c]));
         if (pre_m) om = rescale_preshift(om, pm);
         const int32_t mq = sat8(rescale_sat16_pre<0>(om, pm) + zp_m);
         pk |= (uint32_t)(mq & 0xFF) << (8 * c);
       }
-      if (row < a.B && n0 < a.N) {
+      if constexpr (GATHER) {
+        *reinterpret_cast<uint16_t *>(mS + r * MS + cellw) = (uint16_t)pk;
+      } else if (row < a.B && n0 < a.N) {
         if (proj) {
           // exchange buffer [t][row / 16][k step of 64 cells = member][row % 16][64 cells]: a wave's
           // load of one projection k step is one contiguous KB
           int8_t *mdst = a.mbuf + (size_t)t * a.Bp * a.npadp +
                          ((((size_t)(row >> 4) * (a.npadp >> 6) + member) * 16 + (row & 15)) << 6) + cellw;
-          *reinterpret_cast<uint32_t *>(mdst) = pk;
+          *reinterpret_cast<uint16_t *>(mdst) = (uint16_t)pk;
         } else {
           const size_t orow = (size_t)time_of(t) * a.B + row;
-          *reinterpret_cast<uint32_t *>(a.out + orow * a.Hpad + n0) = pk;
-          if (a.y) __builtin_nontemporal_store(pk, reinterpret_cast<uint32_t *>(a.y + orow * ldy + n0));
+          *reinterpret_cast<uint16_t *>(a.out + orow * a.Hpad + n0) = (uint16_t)pk;
+          if (a.y) __builtin_nontemporal_store((uint16_t)pk, reinterpret_cast<uint16_t *>(a.y + orow * ldy + n0));
+        }
+      }
+    }
+    if constexpr (GATHER) {
+      __syncthreads();
+      if (wave == 0) {
+        // the group's rows of these 64 cells in one store of 16 bytes a lane; cells past the last are written too, they
+        // meet zero weights
+        const int srow = row0 + (lane >> 2), n = member * 64 + 16 * (lane & 3);
+        const v4i piece = *reinterpret_cast<const v4i *>(mS + (lane >> 2) * MS + 16 * (lane & 3));
+        if (srow < a.B && n < a.N) {
+          if (proj) {  // the same exchange buffer
+            *reinterpret_cast<v4i *>(a.mbuf + (size_t)t * a.Bp * a.npadp +
+                                     (((size_t)(srow >> 4) * (a.npadp >> 6) + member) << 10) + lane * 16) = piece;
+          } else {
+            const size_t orow = (size_t)time_of(t) * a.B + srow;
+            *reinterpret_cast<v4i *>(a.out + orow * a.Hpad + n) = piece;
+            if (a.y) {  // N a multiple of four, y of four bytes
+#pragma unroll
+              for (int k = 0; k < 4; ++k)
+                if (n + 4 * k < a.N) __builtin_nontemporal_store(piece[k], reinterpret_cast<int32_t *>(a.y + orow * ldy + n + 4 * k));
+            }
+          }
         }
       }
     }
@@ -621,7 +674,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     // ---- projection (Sec. 3.2.8): tile pt of 32 outputs as two 16-wide halves, K = N split over the waves
     if (proj) {
       const int ksteps = a.npadp >> 6;
-      const int per_wave = (ksteps + 3) >> 2;
+      const int per_wave = (ksteps + 7) >> 3;
       const RescaleHi pp = prm->p;
       const int32_t zp_h = prm->zp_h;
       for (int pt = 0; pt < my_ptiles; ++pt) {
@@ -629,17 +682,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         v4i pacc[2] = {v4i{0, 0, 0, 0}, v4i{0, 0, 0, 0}};
         const int8_t *mbase = a.mbuf + (size_t)t * a.Bp * a.npadp + (((size_t)(row0 >> 4) * ksteps * 16 + r) << 6) + (q << 4);
         const int8_t *wbase = WpL + ((size_t)pt * 32 + r) * WLS + (q << 4);
-        // all loads of the wave's k steps first (at most 8: N <= 2048); steps past the end re-read the
+        // all loads of the wave's k steps first (at most 4: N <= 2048); steps past the end re-read the
         // last one against zero weights
-        int4 mv[8];
+        int4 mv[4];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
+        for (int k = 0; k < 4; ++k) {
           int kk = wave * per_wave + (k < per_wave ? k : per_wave - 1);
           kk = kk < ksteps ? kk : ksteps - 1;
           mv[k] = *reinterpret_cast<const int4 *>(mbase + (size_t)kk * 1024);
         }
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
+        for (int k = 0; k < 4; ++k) {
           int kk = wave * per_wave + (k < per_wave ? k : per_wave - 1);
           const bool real = k < per_wave && kk < ksteps;
           kk = kk < ksteps ? kk : ksteps - 1;
@@ -652,19 +705,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
           }
         }
 #pragma unroll
-        for (int ct = 0; ct < 2; ++ct)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) pred[((wave * 2 + ct) * 4 + v) * 64 + lane] = pacc[ct][v];
+        for (int ct = 0; ct < 2; ++ct) pred[(wave * 2 + ct) * 64 + lane] = pacc[ct];
         __syncthreads();
         if (tid < 128) {
           const int ct = wave;  // threads 0..127: waves 0 and 1
           const int p0 = ptile * 32 + ct * 16 + 4 * q;
+          v4i sum = pred[ct * 64 + lane];
+#pragma unroll
+          for (int w = 1; w < 8; ++w) sum += pred[(w * 2 + ct) * 64 + lane];
           uint32_t pk = 0;
 #pragma unroll
           for (int v = 0; v < 4; ++v) {
-            const int32_t s = pred[((0 * 2 + ct) * 4 + v) * 64 + lane] + pred[((1 * 2 + ct) * 4 + v) * 64 + lane] +
-                              pred[((2 * 2 + ct) * 4 + v) * 64 + lane] + pred[((3 * 2 + ct) * 4 + v) * 64 + lane] +
-                              (pt == 0 ? bpr[v] : a.bp2[p0 + v]);
+            const int32_t s = sum[v] + (pt == 0 ? bpr[v] : a.bp2[p0 + v]);
             const int32_t hq = sat8(rescale_sat16_pre(s, pp) + zp_h);
             pk |= (uint32_t)(hq & 0xFF) << (8 * v);
           }

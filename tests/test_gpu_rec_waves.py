@@ -1,4 +1,4 @@
-"""The division of a step over eight waves, in the 32-row and in the stacked kernel, at its edges: projections whose k steps
+"""The division of a step over eight waves, in the 32-row, the 16-row and the stacked kernel, at its edges: projections whose k steps
 do not divide by eight (waves with fewer steps, or none), an odd number of outputs, one and two output tiles per workgroup
 (partial sums through eight and through four slots of LDS), a second row tile, values beyond the part of the tables that LDS
 holds, and the hand-off between the layers of a one-step stack."""
@@ -26,6 +26,24 @@ def test_division_over_the_waves(orc, N, H, flags, B, T):
     layers, x = wl.make_custom([48], N, H, flags, B, T, seed=N + H + B, weight_param=0.9 / N ** 0.5)
     rows = None if B <= 70 else [0, 31, 32, 63, 64, 500, 959, 960, B - 1]
     run_and_compare(orc, layers, x, f"waves{N}h{H}", trace=False, rows=rows, options={"rows16": 0})
+
+
+@pytest.mark.parametrize("N,H,flags,B,T", [
+    (72, 9, PROJ, 5, 4),                    # two k steps of 64: most waves have none
+    (300, 131, PROJ | LN, 20, 4),           # five k steps; odd outputs
+    (1100, 33, PROJ | LN | PH, 17, 3),      # 18 k steps, three per wave: the last two waves have none
+    (1024, 640, PROJ | LN, 37, 3),          # two output tiles of some workgroups
+    (2048, 640, PROJ | LN | PH, 40, 3),     # four k steps per wave
+    (2048, 640, PROJ | CIFG, 16, 3),
+    (1024, 1024, LN | PH, 35, 3),           # the deepest recurrent product
+    (1024, 1024, CIFG, 1, 3),
+    (203, 203, LN, 21, 4),                  # the last piece of 16 cells of a row incomplete, rows of odd length
+    (332, 332, 0, 33, 4),                   # the same, rows of a multiple of four
+    (66, 66, LN | PH, 16, 4),               # a workgroup with two cells
+])
+def test_division_over_the_waves_of_16_rows(orc, N, H, flags, B, T):
+    layers, x = wl.make_custom([48], N, H, flags, B, T, seed=N + H + B, weight_param=0.9 / N ** 0.5)
+    run_and_compare(orc, layers, x, f"rows16_{N}h{H}", trace=False, options={"rows16": 2})
 
 
 @pytest.mark.parametrize("N,H,flags", [
