@@ -57,6 +57,28 @@ SruDims sru_dims(int I, int N, int G) {
   return SruDims{(I + 63) / 64 * 64, (N + 63) / 64 * 64, (G * N + 127) / 128 * 128};
 }
 
+// The rescale of an int8 value as (x M + add) >> sh with M of 24 bits, zero point and rounding in `add`: a multiply, an add
+// and a shift for the six instructions of the general form.  There are 256 inputs: the host looks for an M that gives the
+// general form's result for every one of them (usually there is one with 10 bits or more to spare).
+struct SmallRescale {
+  int32_t M = 0, add = 0, sh = 0;
+};
+SmallRescale find_small_rescale(int32_t M, int32_t r, int32_t zp) {
+  if (r < 3 || r > 62) return SmallRescale{};
+  const RescaleHi p = rescale_hi_prepare(M, r);
+  for (int sh = 22; sh >= 1; --sh) {
+    const double scaled = std::ldexp((double)M, sh - r);
+    if (scaled > 8388606.0 || scaled * 256.0 + std::ldexp(1.0, sh) > 2147483647.0) continue;
+    for (int64_t m = (int64_t)scaled; m <= (int64_t)scaled + 1; ++m) {
+      const int32_t add = (int32_t)((1 << (sh - 1)) - m * zp);
+      bool same = true;
+      for (int x = -128; x < 128 && same; ++x) same = (((int32_t)(x * m) + add) >> sh) == rescale_sat16_pre(x - zp, p);
+      if (same) return SmallRescale{(int32_t)m, add, sh};
+    }
+  }
+  return SmallRescale{};
+}
+
 struct SruLayerDev {
   const int8_t *W = nullptr;     // [cols_pad][Ip] slot-major rows, zero beyond the real extents
   const int32_t *bias = nullptr; // [cols_pad] folded constants
@@ -66,6 +88,7 @@ struct SruLayerDev {
   const int8_t *W2f = nullptr;
   const int32_t *b2 = nullptr;   // [tiles][32]
   int tiles = 0;                 // a multiple of 8 (cells padded to 64)
+  SmallRescale small;            // of the input, for a layer whose highway term it is
   // depths beyond that: the form of deep_gemm.hip
   DeepWeights deep;
   const int4 *Wd = nullptr;
@@ -175,6 +198,8 @@ int prepare_sru_layer(const sru_int_layer_params &p, const SruLayerHost *prev, S
 // the scan
 // ---------------------------------------------------------------------------
 
+typedef short v2i16 __attribute__((ext_vector_type(2)));
+
 constexpr int kDepth = 4;  // steps whose terms are in flight ahead of the one being computed
 constexpr int kSigEntries = 32776;  // the table's 32769 entries, to a multiple of 8
 constexpr int kSigFull = 65536;      // its values for every x, index x + 32768
@@ -195,6 +220,7 @@ struct SruScanArgs {
   // them is followed by a 16-bit clamp or, for the output, by an 8-bit one that the 16-bit clamp cannot change
   // (|zp_h| <= 128)
   RescaleHi ps, pv[2], ph;
+  SmallRescale small;  // x -> highway term once more, sh = 0: not there
   int16_t *c_state;    // [B][N] in/out
   int32_t zero_state;  // start from zeros instead of reading c_state
   int8_t *out;         // [T*B][ld_out] for the next layer's matmul, or NULL
@@ -214,13 +240,14 @@ struct SruScanArgs {
 // N is a multiple of 4 and y is 4-byte aligned (whole aligned pieces everywhere), no dumps, and the operands of the
 // elementwise rescales cannot overflow their left shift (their clamp is dropped).
 // FULL: sigma from a table of all 65536 values, 128 KB of LDS: a lookup is one add and one read instead of the magnitude
-// before and the mirroring after it (five instructions of about 38 per gate).  2048 cells, 256 rows, 64 steps, 267 MB:
-// 78 us per layer -> 70, 3.8 TB/s (98 -> 92 from tile-ordered terms, 300 MB).
-template <bool TILE, bool FAST, bool FULL>
+// before and the mirroring after it.
+// IDENT: of the fast forms, a layer whose highway term is its input.
+// 2048 cells, 256 rows, 64 steps: 78 us per layer with the smaller table, 70 with this one, 54 to 61 with the instructions of
+// fast_step, 267 MB, 4.4 TB/s and more (300 MB of tile-ordered terms, without the input, 98, 92 and 95: memory bounds it).
+template <bool TILE, bool FAST, bool FULL, bool IDENT>
 __global__ __launch_bounds__(FULL ? kScanBlockFull : kScanBlock) void sru_scan_kernel(SruScanArgs a) {
   constexpr int BLOCK = FULL ? kScanBlockFull : kScanBlock;
   constexpr int CPT = 4;             // cells per thread
-  constexpr int PRE = FAST ? 1 : 2;  // operand treatment of rescale_sat16_pre
   // the Q3.12 sigma table in LDS: the lookup sits in the chain from one step's state to the next, where a gather
   // from memory costs its full latency every step (measured at 1024 cells, B = 256, T = 64: 117 -> 68 us per layer)
   extern __shared__ __attribute__((aligned(16))) uint16_t sig_lds[];
@@ -228,7 +255,8 @@ __global__ __launch_bounds__(FULL ? kScanBlockFull : kScanBlock) void sru_scan_k
     const int4 *src = reinterpret_cast<const int4 *>(FULL ? a.sig_full : a.sig_tab);  // readable to a multiple of 16 bytes
     int4 *dst = reinterpret_cast<int4 *>(sig_lds);
 #pragma unroll 4
-    for (int i = threadIdx.x; i < (FULL ? kSigFull : kSigEntries) / 8; i += BLOCK) dst[i] = src[i];
+    for (int i = threadIdx.x; i < (FULL ? kSigFull : kSigEntries) / 8; i += BLOCK)
+      dst[FULL ? i ^ (kSigFull / 16) : i] = src[i];  // of all values: by the value as an unsigned number
     __syncthreads();  // before any thread leaves: every thread of the workgroup gets here
   }
   const int N = a.N;
@@ -255,7 +283,9 @@ __global__ __launch_bounds__(FULL ? kScanBlockFull : kScanBlock) void sru_scan_k
   const bool row_ok = row < a.B;
   const int rowc = row_ok ? row : a.B - 1;  // padded rows of the last row block compute on the last row; never stored
   const bool vec = FAST || (N & 3) == 0;    // runs of four cells are whole, aligned pieces
-  const bool identity = a.G == 3;
+  // of the requests; with tile-ordered terms a branch of the run, known as the answer is: without one the compiler moves a
+  // step's loads about (1024 cells, 256 rows, 64 steps: 59 us a layer with, 64 without)
+  const bool identity = FAST && !TILE ? IDENT : a.G == 3;
 
   int32_t cst[CPT], vf[CPT], vr[CPT];
 #pragma unroll
@@ -322,7 +352,86 @@ __global__ __launch_bounds__(FULL ? kScanBlockFull : kScanBlock) void sru_scan_k
   auto lo16 = [](int32_t w) { return (int32_t)(int16_t)(w & 0xFFFF); };
   auto hi16 = [](int32_t w) { return w >> 16; };
 
+  // FAST.  From two waves a SIMD issues a 32-bit add or shift every 2.15 clocks and a multiply, a clamp, a field extract or a
+  // packed 16-bit instruction every 4.26, and the instructions of a step are most of its time: saturated pairs and packed
+  // saturating sums instead of a clamp each, terms multiplied where they lie in their word, no clamp that another one covers.
+  auto fast_step = [&](int t, const Raw &r) {
+    const int32_t tz[2] = {r.p0.x, r.p0.y}, tf[2] = {r.p0.z, r.p0.w}, tr[2] = {r.p1.x, r.p1.y}, ts[2] = {r.p1.z, r.p1.w};
+    // sigma of a pair of sums: tx + v c, both saturated (Secs. 3.2.3, 3.2.1)
+    auto gates = [&](int32_t tx, const int32_t *v, const RescaleHi &p, int c, int32_t *out) {
+      const v2i16 tv = __builtin_amdgcn_cvt_pk_i16(rescale_hi_pre(__mul24(v[c], cst[c]), p), rescale_hi_pre(__mul24(v[c + 1], cst[c + 1]), p));
+      const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_elementwise_add_sat(__builtin_bit_cast(v2i16, tx), tv));
+      if constexpr (!FULL) {  // by magnitude
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const int32_t xi = i ? hi16((int32_t)w) : lo16((int32_t)w), s = xi >> 31;
+          const int32_t m = sig_lds[(xi ^ s) - s];
+          out[i] = (m ^ s) + (s & 32769);  // x < 0: ~m + 32769 = 32768 - m
+        }
+        return;
+      }
+      uint32_t lo = w << 1, hi = w >> 15;  // byte offsets, once the other half is masked out
+      asm("" : "+v"(lo));
+      asm("" : "+v"(hi));
+      // (addresses made here: the kernel's LDS is the table alone, from 0 on, and the compiler would add that 0)
+      typedef const __attribute__((address_space(3))) uint16_t *Entry;
+      out[0] = *(Entry)(lo & 0x1FFFE);
+      out[1] = *(Entry)(hi & 0x1FFFE);
+    };
+    // ((a b + 2^14) >> 15, a a gate's complement, b the low or high half of a word
+    auto weighted = [&](int32_t a, int32_t word, int half) {
+      int32_t v;
+      if (half)
+        asm("v_mad_i32_i16 %0, %1, %2, %3 op_sel:[0,1,0,0]" : "=v"(v) : "v"(a), "v"(word), "s"(16384));
+      else
+        asm("v_mad_i32_i16 %0, %1, %2, %3" : "=v"(v) : "v"(a), "v"(word), "s"(16384));
+      return v >> 15;
+    };
+    // there is no slot 3 then, but its registers must not be given to something else while the load is under way: that waits
+    // for the load, and with it for every other one ahead
+    if constexpr (TILE && IDENT) asm volatile("" : : "v"(ts[0]), "v"(ts[1]));
+    int32_t hx[CPT];  // the input itself, brought to the state's format
+    if constexpr (IDENT) {
+      if (a.small.sh) {
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) hx[c] = (__mul24((int8_t)(r.x4 >> (8 * c)), a.small.M) + a.small.add) >> a.small.sh;
+      } else {
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) hx[c] = rescale_sat16_pre<1>((int8_t)(r.x4 >> (8 * c)) - a.zp_x, a.ps);
+      }
+    }
+    int32_t f[CPT], g[CPT];
+#pragma unroll
+    for (int c = 0; c < CPT; c += 2) {
+      gates(tf[c >> 1], vf, a.pv[0], c, f + c);
+      gates(tr[c >> 1], vr, a.pv[1], c, g + c);
+    }
+    int32_t packed = 0;
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) {
+      // the Q3.12 table stays within 1..32767 (the host has checked): so does a complement (Sec. 3.2.9)
+      int32_t fbar = 32768 - f[c], gbar = 32768 - g[c];
+      asm("" : "+v"(fbar));  // (else the 24-bit product shifts its high bits out and back)
+      asm("" : "+v"(gbar));
+      // Sec. 3.2.7: products of a Q0.15 gate and a value in the state's format, each rounded back, saturating sum
+      const int32_t cn = sat16(((__mul24(f[c], cst[c]) + 16384) >> 15) + weighted(fbar, tz[c >> 1], c & 1));
+      const int32_t hw = IDENT ? (__mul24(gbar, hx[c]) + 16384) >> 15 : weighted(gbar, ts[c >> 1], c & 1);
+      const int32_t hn = sat16(((__mul24(g[c], cn) + 16384) >> 15) + hw);
+      cst[c] = cn;
+      // Sec. 3.2.8; the 16-bit clamp of the rescale changes nothing under the 8-bit one (|zp_h| <= 128)
+      const int32_t y = sat8(rescale_hi_pre((int32_t)((uint32_t)hn << a.ph.k), a.ph) + a.zp_h);
+      packed |= (int32_t)((uint32_t)(y & 0xFF) << (8 * c));
+    }
+    if (row_ok && n0 < N) {  // the only lane-dependent branch of a step
+      if (a.out) *reinterpret_cast<int32_t *>(out0 + (size_t)t * out_step) = packed;
+      if (a.y) *reinterpret_cast<int32_t *>(y0 + (size_t)t * y_step) = packed;
+    }
+  };
   auto step = [&](int t, const Raw &r) {
+    if constexpr (FAST) {
+      fast_step(t, r);
+      return;
+    }
     int32_t tx[4][CPT];  // [slot][cell]
     tx[0][0] = lo16(r.p0.x); tx[0][1] = hi16(r.p0.x); tx[0][2] = lo16(r.p0.y); tx[0][3] = hi16(r.p0.y);
     tx[1][0] = lo16(r.p0.z); tx[1][1] = hi16(r.p0.z); tx[1][2] = lo16(r.p0.w); tx[1][3] = hi16(r.p0.w);
@@ -331,26 +440,18 @@ __global__ __launch_bounds__(FULL ? kScanBlockFull : kScanBlock) void sru_scan_k
     if (identity) {  // the input itself, brought to the state's format
 #pragma unroll
       for (int c = 0; c < CPT; ++c)
-        tx[3][c] = rescale_sat16_pre<PRE>((int32_t)(int8_t)((r.x4 >> (8 * c)) & 0xFF) - a.zp_x, a.ps);
+        tx[3][c] = rescale_sat16_pre((int32_t)(int8_t)((r.x4 >> (8 * c)) & 0xFF) - a.zp_x, a.ps);
     }
     int32_t yv[CPT], hv[CPT], fv[CPT], rv[CPT], tvf[CPT], tvr[CPT];
 #pragma unroll
     for (int c = 0; c < CPT; ++c) {
       // both gates read the state before the step (Secs. 3.2.3, 3.2.1)
       // (all products here are of 16-bit values: the 24-bit multiply is exact)
-      tvf[c] = rescale_sat16_pre<FAST ? 0 : 2>(__mul24(vf[c], cst[c]), a.pv[0]);
-      tvr[c] = rescale_sat16_pre<FAST ? 0 : 2>(__mul24(vr[c], cst[c]), a.pv[1]);
-      // FAST: the Q3.12 table stays within 1..32767 (the host has checked), no clamp of a gate or its complement acts
-      auto sigmoid = [&](int32_t x) -> int32_t {
-        if (FULL) return sig_lds[x + 32768];
-        if (!FAST) return sigmoid_from_table(sig_lds, x);
-        const int32_t v = sig_lds[x < 0 ? -x : x];
-        return x < 0 ? 32768 - v : v;
-      };
-      auto complement = [&](int32_t v) { return FAST ? 32768 - v : cifg_input_gate(v); };  // Sec. 3.2.9
-      const int32_t f = sigmoid(sat16(tx[1][c] + tvf[c]));
-      const int32_t g = sigmoid(sat16(tx[2][c] + tvr[c]));
-      const int32_t fbar = complement(f), gbar = complement(g);
+      tvf[c] = rescale_sat16_pre(__mul24(vf[c], cst[c]), a.pv[0]);
+      tvr[c] = rescale_sat16_pre(__mul24(vr[c], cst[c]), a.pv[1]);
+      const int32_t f = sigmoid_from_table(sig_lds, sat16(tx[1][c] + tvf[c]));
+      const int32_t g = sigmoid_from_table(sig_lds, sat16(tx[2][c] + tvr[c]));
+      const int32_t fbar = cifg_input_gate(f), gbar = cifg_input_gate(g);  // Sec. 3.2.9
       // Sec. 3.2.7: products of a Q0.15 gate and a value in the state's format, each rounded back, saturating sum
       const int32_t cn = sat16(((__mul24(f, cst[c]) + 16384) >> 15) + ((__mul24(fbar, tx[0][c]) + 16384) >> 15));
       const int32_t hn = sat16(((__mul24(g, cn) + 16384) >> 15) + ((__mul24(gbar, tx[3][c]) + 16384) >> 15));
@@ -358,19 +459,12 @@ __global__ __launch_bounds__(FULL ? kScanBlockFull : kScanBlock) void sru_scan_k
       hv[c] = hn;
       fv[c] = f;
       rv[c] = g;
-      yv[c] = sat8(rescale_sat16_pre<PRE>(hn, a.ph) + a.zp_h);  // Sec. 3.2.8
+      yv[c] = sat8(rescale_sat16_pre(hn, a.ph) + a.zp_h);  // Sec. 3.2.8
     }
     const size_t tb = (size_t)t * a.B + row;
     int32_t packed = 0;
 #pragma unroll
     for (int c = 0; c < CPT; ++c) packed |= (int32_t)((uint32_t)(yv[c] & 0xFF) << (8 * c));
-    if (FAST) {
-      if (row_ok && n0 < N) {  // the only lane-dependent branch of a step
-        if (a.out) *reinterpret_cast<int32_t *>(out0 + (size_t)t * out_step) = packed;
-        if (a.y) *reinterpret_cast<int32_t *>(y0 + (size_t)t * y_step) = packed;
-      }
-      return;
-    }
     if (!row_ok) return;
     auto put = [&](int8_t *o, bool aligned) {
       if (vec && aligned) {
@@ -428,13 +522,19 @@ __global__ __launch_bounds__(FULL ? kScanBlockFull : kScanBlock) void sru_scan_k
 }
 
 typedef void (*scan_fn)(SruScanArgs);
-scan_fn pick_scan(bool tile, bool fast, bool full) {
-  if (tile) return full ? sru_scan_kernel<true, true, true> : fast ? sru_scan_kernel<true, true, false> : sru_scan_kernel<true, false, false>;
-  return full ? sru_scan_kernel<false, true, true> : fast ? sru_scan_kernel<false, true, false> : sru_scan_kernel<false, false, false>;
+// ident: of the fast forms (the general one looks it up)
+scan_fn pick_scan(bool tile, bool fast, bool full, bool ident) {
+  auto of = [&](auto t, auto i) -> scan_fn {
+    return full ? sru_scan_kernel<t, true, true, i> : fast ? sru_scan_kernel<t, true, false, i> : sru_scan_kernel<t, false, false, false>;
+  };
+  using Y = std::true_type;
+  using N = std::false_type;
+  return tile ? (ident ? of(Y(), Y()) : of(Y(), N())) : (ident ? of(N(), Y()) : of(N(), N()));
 }
 hipError_t scan_init() {
-  for (int v = 0; v < 6; ++v) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(pick_scan(v & 1, v >> 1 > 0, v >> 1 > 1)),
+  for (int v = 0; v < 12; ++v) {
+    const int form = v >> 2;
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(pick_scan(v & 1, form > 0, form > 1, v >> 1 & 1)),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
   }
@@ -592,6 +692,7 @@ int sru_int_prepare(const sru_int_layer_params *layers, int32_t num_layers, int3
       m->dev[l].W = reinterpret_cast<const int8_t *>(m->arena + offs[l].W);
       m->dev[l].bias = reinterpret_cast<const int32_t *>(m->arena + offs[l].bias);
       m->dev[l].vq = reinterpret_cast<const int16_t *>(m->arena + offs[l].vq);
+      if (m->host[l].G == 3) m->dev[l].small = find_small_rescale(m->host[l].Ms, 31 - m->host[l].es, m->host[l].zp_x);
       if (offs[l].tiles) {
         m->dev[l].W2f = reinterpret_cast<const int8_t *>(m->arena + offs[l].W2f);
         m->dev[l].b2 = reinterpret_cast<const int32_t *>(m->arena + offs[l].b2);
@@ -733,6 +834,7 @@ int sru_int_forward(const sru_int_model *m, const int8_t *x, int32_t T, int32_t 
     a.xin = in; a.ld_x = ld_in; a.zp_x = q.zp_x; a.zp_h = q.zp_h;
     a.vq = dv.vq;
     a.ps = rescale_hi_prepare(G == 3 ? q.Ms : 1 << 30, G == 3 ? 31 - q.es : 33);
+    a.small = dv.small;
     for (int j = 0; j < 2; ++j) a.pv[j] = rescale_hi_prepare(q.Mv[j], 31 - q.ev[j]);
     a.ph = rescale_hi_prepare(q.Mh, 31 - q.eh);
     a.c_state = c_state ? c_state + c_off : reinterpret_cast<int16_t *>(ws + w.c);
@@ -752,14 +854,14 @@ int sru_int_forward(const sru_int_model *m, const int8_t *x, int32_t T, int32_t 
     const int64_t threads = ws_gemm ? (int64_t)a.bp_blocks * ((N + 7) / 8) * 64 : (int64_t)B * ((N + 3) / 4);
     // The table of all values makes a step's instructions fewer, but a workgroup twice as large: as long as the other form's
     // workgroups have a compute unit each, half of the chip would idle.  Two layers, 64 steps, the other form -> this one,
-    // us:   256 of the other form's workgroups (1024 cells x 256 rows) 203 -> 293,  (2048 x 128) 274 -> 313
-    //       288 (1024 x 288) 303 -> 307,  (2048 x 144) 356 -> 354         320 (1024 x 320) 321 -> 322,  (2048 x 160) 372 -> 365
-    //       384 (2048 x 192) 438 -> 425   512 (2048 x 256) 524 -> 517
-    // From 320 on, then, and where the steps pay for loading it: 8 steps of 2048 x 256 32.4 -> 31.4.
+    // us:   256 of the other form's workgroups (1024 cells x 256 rows) 240 -> 345,  (2048 x 128) 271 -> 276
+    //       288 (1024 x 288) 357 -> 362,  (2048 x 144) 317 -> 297         320 (1024 x 320) 374 -> 379,  (2048 x 160) 339 -> 318
+    //       384 (1024 x 384) 425 -> 428,  (2048 x 192) 393 -> 370         512 (2048 x 256) 527 -> 516
+    // From 320 on, then, and where the steps pay for loading it: 8 steps of 2048 x 256 83.0 -> 81.5.
     const bool full = fast && threads >= (int64_t)320 * kScanBlock && T >= 8;
     const int block = full ? kScanBlockFull : kScanBlock;
     const size_t lds = (size_t)(full ? kSigFull : kSigEntries) * 2;
-    hipLaunchKernelGGL(pick_scan(ws_gemm, fast, full), dim3((unsigned)((threads + block - 1) / block)), dim3(block), lds, s, a);
+    hipLaunchKernelGGL(pick_scan(ws_gemm, fast, full, G == 3), dim3((unsigned)((threads + block - 1) / block)), dim3(block), lds, s, a);
     timed_end();
     in = out;
     ld_in = d.Kp;

@@ -124,6 +124,37 @@ def test_saturating_inputs_and_clipped_ranges(sru):
     equal("sat.y_untraced", lib_m.forward(xd).cpu().numpy(), yo)
 
 
+@pytest.mark.parametrize("inputs,N,B,T,wide", [
+    ([1040, 1040], 1040, 320, 9, False),  # all values of sigma in the LDS: row-major terms, the input as the highway term
+    ([600, 600], 600, 600, 9, False),     # tile-ordered terms, the input as the highway term
+    ([64, 1284], 1284, 258, 8, False),    # tile-ordered terms with W_s, then row-major ones of the general matmul
+    ([600, 600], 600, 600, 9, True),      # inputs beyond the state's format: no short form of the highway rescale
+    ([72, 72], 72, 5, 6, True),           # the smaller table
+    ([68, 68], 68, 5, 6, False),
+])
+def test_fast_forms_of_the_scan(sru, inputs, N, B, T, wide):
+    import torch
+
+    layers, x = wl.make_sru(inputs, N, B, T, seed=N + B, weight_param=1.0 / N ** 0.5, input_param=1.5)
+    sru.calibrate(layers, np.ascontiguousarray(x[:, :2]))
+    if wide:
+        for s in layers:
+            s.c_absmax = 0.9
+    lib_m, orc_m = both(sru, layers)
+    xq = quantize_x(x, orc_m.get_quant(0))
+    sel = np.array([0, 1, B // 2, B - 1])
+    rng = np.random.default_rng(3)
+    c0 = rng.integers(-32768, 32768, size=B * N * len(layers)).astype(np.int16)
+    co = np.concatenate([r.ravel() for r in state_rows(c0, layers, B, sel)])
+    yo, _ = orc_m.forward(xq[:, sel], c_state=co, threads=8)
+    for reg in (1, 0):
+        lib_m.set_option("register_gemm", reg)
+        cs = torch.from_numpy(c0.copy()).cuda()
+        equal(f"y[{reg}]", lib_m.forward(torch.from_numpy(xq).cuda(), c_state=cs).cpu().numpy()[:, sel], yo)
+        for g, w in zip(state_rows(cs.cpu().numpy(), layers, B, sel), state_rows(co, layers, len(sel), np.arange(len(sel)))):
+            equal(f"c_state[{reg}]", g, w)
+
+
 def test_speech_encoder_shapes_sampled_rows(sru):
     """Layers of the benchmark's width: N = 2048 at B = 256 (input 512, then 2048 = the general matmul and the
     input as the highway term) on rows spread over the row blocks, N = 1024 at B = 64 whole."""
