@@ -171,8 +171,8 @@ def bench_sru(args, np, torch, wl, binding):
     scan_bytes = sum(T * B * N * (2.0 * g + 1 + (1 if g == 3 else 0)) for g in G) / L
     gemm_ops = sum(2.0 * T * B * g * N * s.input_size for g, s in zip(G, layers)) / L
     # vector, scalar, LDS and memory instructions of the scan's compiled loops per cell and step (16 of those per round):
-    # 78 to 81, and 70 to 73 in the form with the large table, which batches of 320 * 256 threads of four cells take
-    instructions = 72.0 if T >= 8 and B * ((N + 3) // 4) >= 320 * 256 else 80.0
+    # 54 to 62, and 46 to 55 in the form with the large table, which batches of 320 * 256 threads of four cells take
+    instructions = 52.0 if T >= 8 and B * ((N + 3) // 4) >= 320 * 256 else 60.0
     out = {"metric": "sru_cell_steps_per_sec", "value": B * T * L / dt, "unit": "cell-steps/s", "n_gpus": 1,
            "steps": args.steps, "warmup": args.warmup, "ms_per_step": dt * 1e3, "higher_is_better": True,
            "scaling": "weak", "vs_baseline": None, "dtype": "int8", "data": "synthetic",
