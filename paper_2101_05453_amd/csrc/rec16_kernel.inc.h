@@ -102,20 +102,22 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // ---- LDS carve-up (rec16_lds_bytes mirrors it)
   constexpr int LS = KS16 * 64 + 16;  // h tile row stride: LS / 4 = 4 * odd (mod 64), reads are conflict-free
   constexpr int TILE_KB = (16 * LS + 1023) / 1024;
-  constexpr int MS = 80;  // row stride of the tile of 64 cells
   // m or h of a step leaves through LDS, by one wave in stores of 16 bytes a lane, which are acknowledged 0.25 us before those
   // of two bytes a lane from all waves.  Behind a second round of statistics the barrier that takes costs more: 2048 cells
   // with peephole and layer norm 9.2 -> 9.5 us a step.
   constexpr bool GATHER = !(ph && ln);
   uint8_t *p = lds;
   int8_t *hT = reinterpret_cast<int8_t *>(p);
+  // hidden state of the step on its way out, where the loads past the h tile go, which nobody reads: 16-byte pieces of row r
+  // at r * 64, exchanged by r / 4 so that rows in the same banks differ
+  int8_t *const mS = reinterpret_cast<int8_t *>(lds) + TILE_KB * 1024;
+  auto piece_at = [](int row, int piece) { return row * 64 + ((piece ^ (row >> 2)) << 4); };
   v4i *pred = reinterpret_cast<v4i *>(p);  // projection partials [8 waves][2 halves][64 lanes] reuse the h tile between steps
   {
     const size_t tile_bytes = (size_t)(TILE_KB + 1) * 1024;  // one spare chunk for the loads past the tile
     const size_t pred_bytes = proj ? 8 * 2 * 64 * 16 : 0;
     p += tile_bytes > pred_bytes ? tile_bytes : pred_bytes;
   }
-  int8_t *mS = reinterpret_cast<int8_t *>(p);            p += 16 * MS;  // hidden state of the step, on its way out
   u64 *red = reinterpret_cast<u64 *>(p);                 p += (size_t)items * 8;  // [item] sums
   LnRow2 *lnrow = reinterpret_cast<LnRow2 *>(p);         p += (size_t)items * sizeof(LnRow2);
   double *LdL = reinterpret_cast<double *>(p);           p += 4 * 64 * 8;
@@ -629,7 +631,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         pk |= (uint32_t)(mq & 0xFF) << (8 * c);
       }
       if constexpr (GATHER) {
-        *reinterpret_cast<uint16_t *>(mS + r * MS + cellw) = (uint16_t)pk;
+        *reinterpret_cast<uint16_t *>(mS + piece_at(r, cellw >> 4) + (cellw & 15)) = (uint16_t)pk;
       } else if (row < a.B && n0 < a.N) {
         if (proj) {
           // exchange buffer [t][row / 16][k step of 64 cells = member][row % 16][64 cells]: a wave's
@@ -650,7 +652,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         // the group's rows of these 64 cells in one store of 16 bytes a lane; cells past the last are written too, they
         // meet zero weights
         const int srow = row0 + (lane >> 2), n = member * 64 + 16 * (lane & 3);
-        const v4i piece = *reinterpret_cast<const v4i *>(mS + (lane >> 2) * MS + 16 * (lane & 3));
+        const v4i piece = *reinterpret_cast<const v4i *>(mS + piece_at(lane >> 2, lane & 3));
         if (srow < a.B && n < a.N) {
           if (proj) {  // the same exchange buffer
             *reinterpret_cast<v4i *>(a.mbuf + (size_t)t * a.Bp * a.npadp +
