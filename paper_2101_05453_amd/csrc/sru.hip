@@ -243,11 +243,19 @@ struct SruScanArgs {
 // before and the mirroring after it.
 // IDENT: of the fast forms, a layer whose highway term is its input.
 // 2048 cells, 256 rows, 64 steps: 78 us per layer with the smaller table, 70 with this one, 54 to 61 with the instructions of
-// fast_step, 267 MB, 4.4 TB/s and more (300 MB of tile-ordered terms, without the input, 98, 92 and 95: memory bounds it).
+// fast_step, 267 MB, 4.4 TB/s and more (300 MB of tile-ordered terms, without the input, 98, 92 and 93: memory
+// bounds it).
 template <bool TILE, bool FAST, bool FULL, bool IDENT>
 __global__ __launch_bounds__(FULL ? kScanBlockFull : kScanBlock) void sru_scan_kernel(SruScanArgs a) {
   constexpr int BLOCK = FULL ? kScanBlockFull : kScanBlock;
   constexpr int CPT = 4;             // cells per thread
+  // Whole rounds of steps without a test for the end ahead of each, so that a wait leaves the requests of the steps behind it
+  // in flight (row-major: with every request kept behind the step whose registers it refills).  With the tests, the form of
+  // tile-ordered terms with a highway matrix waited twice a round for all its requests.
+  // 64 steps, tests -> rounds, us: 2048 cells, 256 rows, tile order and matrix 98 -> 93, 16 rows 40 -> 33; 203 cells, 64 rows
+  // (the general form) 167 -> 162; 2048 x 256, row-major and identity, the large table 53.5 -> 53.2, 1280 x 256 49.8 -> 47.3.
+  // The other forms with the identity lose: 2048 x 64, row-major, the small table 45 -> 48, 1024 x 256 in tile order 62 -> 67.
+  constexpr bool ROUNDS = !IDENT || (FULL && !TILE);
   // the Q3.12 sigma table in LDS: the lookup sits in the chain from one step's state to the next, where a gather
   // from memory costs its full latency every step (measured at 1024 cells, B = 256, T = 64: 117 -> 68 us per layer)
   extern __shared__ __attribute__((aligned(16))) uint16_t sig_lds[];
@@ -284,8 +292,8 @@ __global__ __launch_bounds__(FULL ? kScanBlockFull : kScanBlock) void sru_scan_k
   const int rowc = row_ok ? row : a.B - 1;  // padded rows of the last row block compute on the last row; never stored
   const bool vec = FAST || (N & 3) == 0;    // runs of four cells are whole, aligned pieces
   // of the requests; with tile-ordered terms a branch of the run, known as the answer is: without one the compiler moves a
-  // step's loads about (1024 cells, 256 rows, 64 steps: 59 us a layer with, 64 without)
-  const bool identity = FAST && !TILE ? IDENT : a.G == 3;
+  // step's loads about (1024 cells, 256 rows, 64 steps: 62 us a layer with, 67 without)
+  const bool identity = FAST && !(TILE && IDENT) ? IDENT : a.G == 3;
 
   int32_t cst[CPT], vf[CPT], vr[CPT];
 #pragma unroll
@@ -504,15 +512,38 @@ __global__ __launch_bounds__(FULL ? kScanBlockFull : kScanBlock) void sru_scan_k
   const int T = a.T;
   Raw r0 = request(0), r1 = request(1 < T ? 1 : T - 1), r2 = request(2 < T ? 2 : T - 1), r3 = request(3 < T ? 3 : T - 1);
   static_assert(kDepth == 4, "four named registers sets");
-  for (int t = 0; t < T; t += kDepth) {
-    step(t, r0);
-    r0 = request(t + 4 < T ? t + 4 : T - 1);
+  if constexpr (ROUNDS) {
+    auto request_here = [&](int t) {
+      if constexpr (!TILE) __builtin_amdgcn_sched_barrier(0);
+      const Raw r = request(t < T ? t : T - 1);
+      if constexpr (!TILE) __builtin_amdgcn_sched_barrier(0);
+      return r;
+    };
+    int t = 0;
+    for (; t + 3 < T; t += kDepth) {
+      step(t, r0);
+      r0 = request_here(t + 4);
+      step(t + 1, r1);
+      r1 = request_here(t + 5);
+      step(t + 2, r2);
+      r2 = request_here(t + 6);
+      step(t + 3, r3);
+      r3 = request_here(t + 7);
+    }
+    if (t < T) step(t, r0);
     if (t + 1 < T) step(t + 1, r1);
-    r1 = request(t + 5 < T ? t + 5 : T - 1);
     if (t + 2 < T) step(t + 2, r2);
-    r2 = request(t + 6 < T ? t + 6 : T - 1);
-    if (t + 3 < T) step(t + 3, r3);
-    r3 = request(t + 7 < T ? t + 7 : T - 1);
+  } else {
+    for (int t = 0; t < T; t += kDepth) {
+      step(t, r0);
+      r0 = request(t + 4 < T ? t + 4 : T - 1);
+      if (t + 1 < T) step(t + 1, r1);
+      r1 = request(t + 5 < T ? t + 5 : T - 1);
+      if (t + 2 < T) step(t + 2, r2);
+      r2 = request(t + 6 < T ? t + 6 : T - 1);
+      if (t + 3 < T) step(t + 3, r3);
+      r3 = request(t + 7 < T ? t + 7 : T - 1);
+    }
   }
   if (row_ok) {
 #pragma unroll
