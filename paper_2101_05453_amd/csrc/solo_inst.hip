@@ -17,10 +17,11 @@ static solo_fn pick_solo(int form, int fl) {
   return nullptr;
 }
 
-// Where it is the faster one.  Time per step, us, this kernel / groups of 16 rows over several workgroups (before), up to
-// 1024 rows:   64 cells 0.9-1.1 / 2.6, with layer norm 1.8-1.9 / 4.4, and peephole 2.4 / 5.9
-//             128 cells 1.1-1.4 / 3.0-3.3,             2.2-2.5 / 4.7-5.1,              2.8-3.1 / 6.1-6.6
-//             256 cells 1.5-2.2 / 3.2-3.7,             3.1-3.6 / 4.8-5.4,              3.6-4.1 / 6.2-6.6
+// Where it is the faster one.  Time per step, us, this kernel (16 or 1024 rows alike; without - with a projection) / groups of
+// 16 rows over several workgroups, up to 1024 rows:
+//   64 cells 0.7-0.8 / 2.6,      with layer norm 1.5-1.6 / 4.4,      and peephole 2.1-2.3 / 5.9
+//  128 cells 0.8-1.0 / 3.0-3.3,                  1.8-2.0 / 4.7-5.1,               2.4-2.7 / 6.1-6.6
+//  256 cells 1.4-1.9 / 3.2-3.7,                  3.0-3.5 / 4.8-5.4,               3.6-4.1 / 6.2-6.6
 // From 1025 rows on a second round of workgroups doubles it: still less up to 128 cells.
 bool solo_supported(int N, int H, int flags, int B) {
   const int form = solo_form(N, H);
@@ -41,7 +42,7 @@ size_t solo_lds_bytes(const RecArgs &a) {
 
 hipError_t solo_init() {
   for (int form = 0; form < 3; ++form)
-    for (int fl = 0; fl < 8; ++fl) {
+    for (int fl = 0; fl < 16; ++fl) {
       hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(pick_solo(form, fl)),
                                          hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
       if (e != hipSuccess) return e;
@@ -52,7 +53,7 @@ hipError_t solo_init() {
 hipError_t launch_solo(hipStream_t s, const RecArgs2 &a) {
   const RecArgs &f = a.d[0], &b = a.d[1];
   const int form = solo_form(f.N, f.H);
-  solo_fn fn = pick_solo(form, f.flags & 7);
+  solo_fn fn = pick_solo(form, f.flags & 15);
   if (!fn || !f.R2h || f.rows_pg != 4 || f.groups != (f.B + 3) / 4 ||
       (b.groups > 0 && (!b.R2h || solo_form(b.N, b.H) != form || f.flags != b.flags || b.rows_pg != 4 || b.groups != (b.B + 3) / 4)))
     return hipErrorInvalidValue;

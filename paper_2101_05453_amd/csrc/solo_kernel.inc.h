@@ -23,6 +23,12 @@
 // from LDS, and a layer-norm step works out lane numbers and addresses anew.  Eight waves of two blocks each have the
 // registers, and half as many waves to fill the gaps: 256 cells, 32 rows, a step without / with layer norm / and peephole
 // 1.85, 4.0, 4.9 us, with 16 waves 1.55, 3.1, 3.6.
+//
+// Four and eight waves have the registers, and are the faster for keeping things in them: with the 16-wave form's economies
+// (LEAN) in their code 60 steps of 16 rows with peephole and layer norm took, without -> with, 39 cells 144 -> 152 us, 64 cells
+// 137 -> 145, 128 cells 155 -> 167.  Whether there is a projection is compiled in for them (39 cells, plain 60 -> 56 us, 128
+// cells 62 -> 57; the masks of mirror_*_masked instead of selects 57 -> 56 and 60 -> 57).  The 16-wave form looks the
+// projection up: compiled in, the plain forms and peephole or layer norm alone gain up to 3 %, 203 cells with both lose 4 %.
 #pragma once
 
 #include "rec_kernel.inc.h"
@@ -36,6 +42,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
   constexpr int NT = 64 * WAVES, NC = 16 * WAVES, RG = 4;  // threads; cells and batch rows of the workgroup
   constexpr bool LN_LDS = ln && WAVES > 8;  // layer-norm parameters in LDS
   constexpr bool LEAN = WAVES == 16;
+  constexpr bool ROW_ADDR = !LEAN && cifg && ph && ln;  // outputs addressed by their row, not within the step's rows
   constexpr int LS = KS16 * 64 + 16;           // row stride of the h and m tiles
   constexpr int g_first = cifg ? 1 : 0;
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
@@ -46,7 +53,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
   const int which = (int)blockIdx.x >= args.d[0].groups ? 1 : 0;
   const RecDirArgs &a = args.d[which];
   const int row0 = ((int)blockIdx.x - (which ? args.d[0].groups : 0)) * RG;
-  const bool proj = a.flags & 8;
+  const bool proj = LEAN ? a.flags & 8 : FL & 8;
   const int ldy = a.ldy;
 
   uint8_t *p = lds;
@@ -145,7 +152,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
   typedef const __attribute__((address_space(4))) RecArgs2 *KernArgs;
   auto fresh = [&] {
     KernArgs k = (KernArgs)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(k));
+    if constexpr (LEAN) asm volatile("" : "+s"(k));
     return k;
   };
   auto ps = [&](KernArgs k, int g) { return LEAN ? rescale_hi_prepare(k->d[which].Mh[g], k->d[which].rh[g]) : ps_[g]; };
@@ -208,9 +215,9 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
   // gates g_lo..g_hi: one wave turns the sums into (mean, sigma) form
   auto statistics = [&](int g_lo, int g_hi) {
     __syncthreads();
-    if (wave == 0) {
+    if (LEAN ? wave == 0 : tid < 64) {
       int item = lane;  // (gate, row)
-      asm volatile("" : "+v"(item));  // worked out here, not kept through the step
+      if constexpr (LEAN) asm volatile("" : "+v"(item));  // worked out here, not kept through the step
       const bool first16 = item < 16;
       item &= 15;
       const bool here = first16 && (item >> 2) >= g_lo && (item >> 2) <= g_hi;
@@ -220,7 +227,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
       const bool narrow = __builtin_amdgcn_ballot_w64(here && !ln_row_is_narrow(lr)) == 0;
       if (here) {
         u64 zero = 0;
-        asm volatile("" : "+v"(zero));  // made here: as a constant of the loop it takes two registers
+        if constexpr (LEAN) asm volatile("" : "+v"(zero));  // made here: as a constant of the loop it takes two registers
         red[item] = zero;  // the next adds come after the barrier below
         lnrow[item] = lr;
       }
@@ -305,7 +312,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
       v4i acc[4];
 #pragma unroll
       for (int g = g_first; g < 4; ++g) {
-        acc[g] = v4i{0, 0, 0, 0};  // with the bias in it, four registers would be kept from step to step
+        acc[g] = v4i{LEAN ? 0 : bh[g], 0, 0, 0};  // with 16 waves four registers too many to keep from step to step
 #pragma unroll
         for (int ks = 0; ks < KS16; ++ks) acc[g] = __builtin_amdgcn_mfma_i32_16x16x64_i8(hf[ks], Wf[g][ks], acc[g], 0, 0, 0);
       }
@@ -315,7 +322,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           if (g < g_first) continue;
-          int32_t v = txq[0][g] + rescale_sat16_pre<decltype(pre_tag)::value>(acc[g][0] + bh[g], ps(ka, g));
+          int32_t v = txq[0][g] + rescale_sat16_pre<decltype(pre_tag)::value>(acc[g][0] + (LEAN ? bh[g] : 0), ps(ka, g));
           if (ph && g < 2) v += rescale_sat16_pre(mul_i24(Pq[g < 3 ? g : 0], creg), pc(ka, g < 3 ? g : 0));
           if (!(ph && g == 3)) v = clamp_i32(v, glo, 32767);
           gs[g] = v;
@@ -388,8 +395,14 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
       } else {
         hnext[q * LS + cell] = mq;
         if (row_ok && cell < N) {
-          out_t[(uint32_t)row * (uint32_t)a.Hpad + (uint32_t)cell] = mq;
-          if (y_t) y_t[(uint32_t)row * (uint32_t)ldy + (uint32_t)cell] = mq;
+          if constexpr (ROW_ADDR) {
+            const size_t orow = orow0 + row;
+            a.out[orow * a.Hpad + cell] = mq;
+            if (a.y) a.y[orow * ldy + cell] = mq;
+          } else {
+            out_t[(uint32_t)row * (uint32_t)a.Hpad + (uint32_t)cell] = mq;
+            if (y_t) y_t[(uint32_t)row * (uint32_t)ldy + (uint32_t)cell] = mq;
+          }
         }
       }
     }
@@ -403,16 +416,22 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
       for (int ks = 0; ks < KS16; ++ks) mf[ks] = *reinterpret_cast<const v4i *>(mT + (c16 >> 2) * LS + (q << 4) + ks * 64);
       const int p0 = wave * 16;
       if (p0 < H) {
-        v4i pacc = v4i{0, 0, 0, 0};
+        v4i pacc = v4i{LEAN ? 0 : bp, 0, 0, 0};
 #pragma unroll
         for (int ks = 0; ks < KS16; ++ks)
           pacc = __builtin_amdgcn_mfma_i32_16x16x64_i8(
               mf[ks], *reinterpret_cast<const v4i *>(WpL + (p0 + c16) * LS + (q << 4) + ks * 64), pacc, 0, 0, 0);
-        const int8_t hq = (int8_t)sat8(rescale_sat16_pre(pacc[0] + bp, pp) + zp_h);
+        const int8_t hq = (int8_t)sat8(rescale_sat16_pre(pacc[0] + (LEAN ? bp : 0), pp) + zp_h);
         hnext[q * LS + p0 + c16] = hq;
         if (row_ok && p0 + c16 < H) {
-          out_t[(uint32_t)row * (uint32_t)a.Hpad + (uint32_t)(p0 + c16)] = hq;
-          if (y_t) y_t[(uint32_t)row * (uint32_t)ldy + (uint32_t)(p0 + c16)] = hq;
+          if constexpr (ROW_ADDR) {
+            const size_t orow = orow0 + row;
+            a.out[orow * a.Hpad + p0 + c16] = hq;
+            if (a.y) a.y[orow * ldy + p0 + c16] = hq;
+          } else {
+            out_t[(uint32_t)row * (uint32_t)a.Hpad + (uint32_t)(p0 + c16)] = hq;
+            if (y_t) y_t[(uint32_t)row * (uint32_t)ldy + (uint32_t)(p0 + c16)] = hq;
+          }
         }
       }
     }
@@ -425,10 +444,11 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
 
 typedef void (*solo_fn)(RecArgs2);
 
-// kernel for (flags & 7)
+// kernel for (flags & 15); with 16 waves the projection is looked up in the run
 template <int WAVES, int KS16>
 solo_fn solo_pick_size(int fl) {
-  switch (fl & 7) {
+  constexpr int P = WAVES == 16 ? 0 : 8;
+  switch (fl & (7 | P)) {
     case 0: return solo_kernel<WAVES, KS16, 0>;
     case 1: return solo_kernel<WAVES, KS16, 1>;
     case 2: return solo_kernel<WAVES, KS16, 2>;
@@ -436,7 +456,15 @@ solo_fn solo_pick_size(int fl) {
     case 4: return solo_kernel<WAVES, KS16, 4>;
     case 5: return solo_kernel<WAVES, KS16, 5>;
     case 6: return solo_kernel<WAVES, KS16, 6>;
-    default: return solo_kernel<WAVES, KS16, 7>;
+    case 7: return solo_kernel<WAVES, KS16, 7>;
+    case 8: return solo_kernel<WAVES, KS16, P>;
+    case 9: return solo_kernel<WAVES, KS16, P | 1>;
+    case 10: return solo_kernel<WAVES, KS16, P | 2>;
+    case 11: return solo_kernel<WAVES, KS16, P | 3>;
+    case 12: return solo_kernel<WAVES, KS16, P | 4>;
+    case 13: return solo_kernel<WAVES, KS16, P | 5>;
+    case 14: return solo_kernel<WAVES, KS16, P | 6>;
+    default: return solo_kernel<WAVES, KS16, P | 7>;
   }
 }
 

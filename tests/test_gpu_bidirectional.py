@@ -77,6 +77,16 @@ def test_both_directions_in_one_launch_of_the_16_row_kernel(orc, variant, N):
     test_bidirectional_outputs_side_by_side(orc, (variant | (wl.PROJECTION if proj else 0), [24], N, H, 21, 4), rows16=2)
 
 
+@pytest.mark.parametrize("N", [39, 128, 130, 256])  # four, eight and 16 waves; cells and outputs within a wave's block
+@pytest.mark.parametrize("proj", [0, 1])
+@pytest.mark.parametrize("variant", range(8))
+def test_both_directions_in_one_launch_of_the_one_workgroup_kernel(orc, variant, proj, N):
+    """Every instantiation of the one-workgroup kernel (CIFG, peephole, layer norm, projection) on both directions, the
+    last workgroup of each with fewer than four rows."""
+    H = N - 7 if proj else N
+    test_bidirectional_outputs_side_by_side(orc, (variant | (wl.PROJECTION if proj else 0), [24], N, H, 6, 4))
+
+
 @pytest.mark.parametrize("rows16", [1, 2])  # groups of four rows, of 16
 def test_status_words_of_a_shared_launch(rows16):
     """Both directions in one launch: a misplaced workgroup (test hook) is reported by both models, a wait that gave up by
