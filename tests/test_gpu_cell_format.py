@@ -13,11 +13,15 @@ LN, PH, PROJ, CIFG = wl.LAYER_NORM, wl.PEEPHOLE, wl.PROJECTION, wl.CIFG
 
 @pytest.mark.parametrize("N,H,flags,B,options", [
     (64, 64, 0, 3, {"stack": 0}),                               # one workgroup per group of rows
-    (203, 203, LN | PH, 9, {"stack": 0, "rows16": 1}),          # groups of four rows
+    (203, 203, LN | PH, 9, {"stack": 0, "rows16": 1}),          # the same, 16 waves
+    (320, 320, LN | PH, 9, {"stack": 0, "rows16": 1}),          # groups of four rows over several workgroups
+    (520, 130, CIFG | LN | PROJ, 30, {"stack": 0, "rows16": 1}),
     (320, 96, LN | PROJ, 21, {"stack": 0, "rows16": 2}),        # groups of 16 rows
     (512, 256, LN | PH | PROJ, 37, {"stack": 0, "rows16": 0}),  # groups of 32 rows
     (512, 256, LN | PH | PROJ, 37, {"stack": 2}),
     (320, 320, CIFG, 33, {"stack": 2}),
+    (200, 200, LN, 37, {"stack": 0, "rows16": 0, "sparse": 2}),  # groups of 32 rows, R pruned two of four
+    (512, 100, PH | PROJ, 40, {"stack": 0, "rows16": 0, "sparse": 2}),
 ])
 @pytest.mark.parametrize("m_c", [6, 7, 8])
 def test_wide_cell_formats(orc, N, H, flags, B, options, m_c):
@@ -27,6 +31,8 @@ def test_wide_cell_formats(orc, N, H, flags, B, options, m_c):
 
     T = 4
     layers, x = wl.make_custom([48, H], N, H, flags, B, T, seed=N + m_c, weight_param=0.9 / N ** 0.5)
+    if "sparse" in options:
+        wl.prune_2of4(layers)
     xd = calibrate_on_gpu(layers, x)
     for s in layers:
         s.c_absmax = 2.0 ** m_c - 1
