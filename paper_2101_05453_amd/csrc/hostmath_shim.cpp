@@ -4,6 +4,7 @@
 #include "calibrate_plan.h"
 #include "lstm_int_math.h"
 #include "model.h"
+#include "sru_plan.h"
 
 using namespace lstm_int;
 
@@ -124,6 +125,8 @@ void hm_calibrate_plan(const lstm_int_layer_params *layers, int32_t num_layers, 
   for (const CalibrateLayer &l : p.layers)
     for (const CalibrateRegion *r : {&l.wop, &l.rop, &l.pop, &l.wx, &l.m, &l.h, &l.c, &l.pre}) put(*r);
 }
+
+int hm_scan_takes_full_table(int tile, int64_t threads, int cus) { return scan_takes_full_table(tile != 0, threads, cus); }
 
 // The library's offline phase on the host (what lstm_int_prepare runs before the upload); *checksum
 // receives the sum of every quantized weight, bias and multiplier of every layer, for a cross-check.

@@ -29,6 +29,7 @@
 #include "lstm_int_math.h"
 #include "model.h"
 #include "persistent.h"
+#include "sru_plan.h"
 
 namespace lstm_int {
 
@@ -203,8 +204,6 @@ typedef short v2i16 __attribute__((ext_vector_type(2)));
 constexpr int kDepth = 4;  // steps whose terms are in flight ahead of the one being computed
 constexpr int kSigEntries = 32776;  // the table's 32769 entries, to a multiple of 8
 constexpr int kSigFull = 65536;      // its values for every x, index x + 32768
-constexpr int kScanBlock = 256;    // threads per workgroup of the scan (each workgroup holds a table: two per compute unit)
-constexpr int kScanBlockFull = 512;  // with the table of all values (128 KB): one workgroup per compute unit
 
 struct SruScanArgs {
   int32_t T, B, N, G;
@@ -883,13 +882,7 @@ int sru_int_forward(const sru_int_model *m, const int8_t *x, int32_t T, int32_t 
     const bool fast = !tr && (N & 3) == 0 && (reinterpret_cast<uintptr_t>(y) & 3) == 0 && 31 - q.ev[0] >= 32 &&
                       31 - q.ev[1] >= 32 && 31 - q.eh >= 18 && (G == 4 || 31 - q.es >= 11) && m->sig_inner;
     const int64_t threads = ws_gemm ? (int64_t)a.bp_blocks * ((N + 7) / 8) * 64 : (int64_t)B * ((N + 3) / 4);
-    // The table of all values makes a step's instructions fewer, but a workgroup twice as large: as long as the other form's
-    // workgroups have a compute unit each, half of the chip would idle.  Two layers, 64 steps, the other form -> this one,
-    // us:   256 of the other form's workgroups (1024 cells x 256 rows) 240 -> 345,  (2048 x 128) 271 -> 276
-    //       288 (1024 x 288) 357 -> 362,  (2048 x 144) 317 -> 297         320 (1024 x 320) 374 -> 379,  (2048 x 160) 339 -> 318
-    //       384 (1024 x 384) 425 -> 428,  (2048 x 192) 393 -> 370         512 (2048 x 256) 527 -> 516
-    // From 320 on, then, and where the steps pay for loading it: 8 steps of 2048 x 256 83.0 -> 81.5.
-    const bool full = fast && threads >= (int64_t)320 * kScanBlock && T >= 8;
+    const bool full = fast && scan_takes_full_table(ws_gemm, threads, m->num_cus);
     const int block = full ? kScanBlockFull : kScanBlock;
     const size_t lds = (size_t)(full ? kSigFull : kSigEntries) * 2;
     hipLaunchKernelGGL(pick_scan(ws_gemm, fast, full, G == 3), dim3((unsigned)((threads + block - 1) / block)), dim3(block), lds, s, a);

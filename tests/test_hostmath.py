@@ -347,3 +347,19 @@ def test_sparse_operand_packing(hm):
     ok = np.zeros(64, np.int8)
     ok[[7, 8, 9, 12]] = 1  # spans two groups
     assert hm.hm_sparse24_row_ok(ok.ctypes.data, 64) == 1
+
+
+@pytest.mark.parametrize("tile,cells,rows,full", [
+    # one side of the rule and the other, and the sizes at which both sides were timed (csrc/sru_plan.h)
+    (False, 2048, 128, False), (False, 2048, 129, True), (False, 2048, 144, True), (False, 2048, 512, True),
+    (False, 1028, 255, False), (False, 1028, 256, True), (False, 1280, 1, False),
+    (True, 1024, 256, False), (True, 1024, 288, False), (True, 1024, 320, False), (True, 1024, 384, False), (True, 1024, 512, False),
+    (True, 2048, 144, False), (True, 2048, 256, False), (True, 1024, 640, False), (True, 1024, 768, False),
+    (True, 1024, 800, True), (True, 1024, 896, True), (True, 1024, 1024, True), (True, 2048, 512, True), (True, 1024, 1025, False),
+])
+def test_choice_of_the_scans_table(hm, tile, cells, rows, full):
+    f = hm.hm_scan_takes_full_table
+    f.argtypes, f.restype = [C.c_int, C.c_int64, C.c_int], C.c_int
+    threads = (rows + 31) // 32 * ((cells + 7) // 8) * 64 if tile else rows * ((cells + 3) // 4)
+    assert bool(f(tile, threads, 256)) == full
+    assert not f(tile, threads, 0)  # an unknown device
