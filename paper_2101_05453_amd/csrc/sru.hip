@@ -380,7 +380,8 @@ __global__ __launch_bounds__(FULL ? kScanBlockFull : kScanBlock) void sru_scan_k
       uint32_t lo = w << 1, hi = w >> 15;  // byte offsets, once the other half is masked out
       asm("" : "+v"(lo));
       asm("" : "+v"(hi));
-      // (addresses made here: the kernel's LDS is the table alone, from 0 on, and the compiler would add that 0)
+      // (addresses made here: the kernel's LDS is the table alone, from 0 on -- scan_init checks it -- and the compiler would add
+      // that 0)
       typedef const __attribute__((address_space(3))) uint16_t *Entry;
       out[0] = *(Entry)(lo & 0x1FFFE);
       out[1] = *(Entry)(hi & 0x1FFFE);
@@ -564,9 +565,13 @@ scan_fn pick_scan(bool tile, bool fast, bool full, bool ident) {
 hipError_t scan_init() {
   for (int v = 0; v < 12; ++v) {
     const int form = v >> 2;
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(pick_scan(v & 1, form > 0, form > 1, v >> 1 & 1)),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    const void *fn = reinterpret_cast<const void *>(pick_scan(v & 1, form > 0, form > 1, v >> 1 & 1));
+    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
+    // the lookups of the large table take it to begin at LDS address 0: no statically allocated LDS ahead of it
+    hipFuncAttributes attr;
+    if ((e = hipFuncGetAttributes(&attr, fn)) != hipSuccess) return e;
+    if (attr.sharedSizeBytes != 0) return hipErrorInvalidConfiguration;
   }
   return hipSuccess;
 }
