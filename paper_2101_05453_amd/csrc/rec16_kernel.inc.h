@@ -97,7 +97,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   auto time_of = [&](int t) { return rec16_rev(a) ? a.T - 1 - t : t; };
   constexpr int items = 64;                    // (gate, row) layer-norm rows of the group
   const int row0 = a.batch0 + group * 16;      // first batch row of the group
-  int cellw = (wave >> 1) * 16 + 4 * q + 2 * (wave & 1);  // + c, within the workgroup's 64 cells
+  constexpr int CPL = 2;                       // cells of a lane: whatever runs over them counts to this
+  int cellw = (wave >> 1) * 16 + 4 * q + CPL * (wave & 1);  // + c, within the workgroup's 64 cells
 
   // ---- LDS carve-up (rec16_lds_bytes mirrors it)
   constexpr int LS = KS16 * 64 + 16;  // h tile row stride: LS / 4 = 4 * odd (mod 64), reads are conflict-free
@@ -186,14 +187,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       dma(src, WpL + c * 1024);
     }
   }
-  v4i Wf[2][KS16];
+  v4i Wf[CPL][KS16];
   {
-    const int4 *src = a.R2h + ((size_t)(member * 4 + (wave >> 1)) * 4 + 2 * (wave & 1)) * KS16 * 64 + lane;
+    const int4 *src = a.R2h + ((size_t)(member * 4 + (wave >> 1)) * 4 + CPL * (wave & 1)) * KS16 * 64 + lane;
     // all loads of the slice are issued before the first value is pinned (a pin waits for its load);
     // at the deepest k the staging registers do not hold both tiles
-    constexpr int TB = KS16 <= 10 ? 2 : 1;
+    constexpr int TB = KS16 <= 10 ? CPL : 1;
 #pragma unroll
-    for (int j0 = 0; j0 < 2; j0 += TB) {
+    for (int j0 = 0; j0 < CPL; j0 += TB) {
       int4 w[TB][KS16];
 #pragma unroll
       for (int j = 0; j < TB; ++j)
@@ -234,9 +235,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // cell state of this lane's cells of its row, kept in registers
   int row = row0 + r;
   int n0 = member * 64 + cellw;
-  int32_t creg[2];
+  int32_t creg[CPL];
 #pragma unroll
-  for (int c = 0; c < 2; ++c)
+  for (int c = 0; c < CPL; ++c)
     creg[c] = (a.c_in && row < a.B && n0 + c < a.N) ? a.c_in[(size_t)row * a.N + n0 + c] : 0;
 
   // h tile staging: wave instruction (wave + 8 j) fills bytes [1024 c, 1024 (c + 1)) of the tile
@@ -330,7 +331,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // ---- R h on the MFMA: acc[j][gate] for the lane's cell j; each tile's k loop runs to its end
     // before the next tile starts (dependent 16x16x64 MFMAs issue back to back, rotating
     // accumulators do not)
-    v4i acc[2];
+    v4i acc[CPL];
     RescaleHi ph4[4];  // the R h rescale constants, read here so that the MFMAs cover the LDS round trip
 #pragma unroll
     for (int g = 0; g < 4; ++g) ph4[g] = prm->h[g];
@@ -338,7 +339,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       constexpr int KC = KS16 <= 10 ? KS16 : KS16 / 2;  // k steps at a time: the deepest k leaves no registers for all
       const int8_t *hbase = hT + (size_t)r * LS + (q << 4);
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < CPL; ++j)
 #pragma unroll
         for (int g = 0; g < 4; ++g) acc[j][g] = bhL[g * 64 + cellw + j];
 #pragma unroll
@@ -347,7 +348,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
         for (int ks = 0; ks < KC; ++ks) hf[ks] = *reinterpret_cast<const v4i *>(hbase + (k0 + ks) * 64);
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < CPL; ++j)
 #pragma unroll
           for (int ks = 0; ks < KC; ++ks)
             acc[j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(Wf[j][k0 + ks], hf[ks], acc[j], 0, 0, 0);
@@ -360,7 +361,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // ---- gate sums (Secs. 3.2.4/3.2.5) and layer-norm partial statistics.
     // With a peephole the o gate keeps tx + th here and is finished after c^t.
     constexpr int32_t glo = ln ? -32767 : -32768;  // layer norm takes symmetric gate sums
-    int32_t gs[4][2];  // [gate][cell]
+    int32_t gs[4][CPL];  // [gate][cell]
     auto gate_sums = [&](auto pre_tag) {
       constexpr int PRE = decltype(pre_tag)::value;
 #pragma unroll
@@ -369,7 +370,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         int32_t s1 = 0;
         uint32_t s2 = 0;  // squares of 16-bit values
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
+        for (int c = 0; c < CPL; ++c) {
           const int32_t th = rescale_sat16_pre<PRE>(acc[c][g], pg);
           const int32_t tx = c ? (txw[g] >> 16) : (int32_t)(int16_t)(txw[g] & 0xFFFF);
           int32_t v = tx + th;
@@ -455,7 +456,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
     // ---- layer norm, sigma/tanh, cell update (Secs. 3.2.6, 3.2.1, 3.2.9, 3.2.7); LDS reads in batches
     // gates of `gmask` (bit g): gate sums -> layer norm -> xv[g][c]
-    auto normalize = [&](int gmask, int32_t (&xv)[4][2]) {
+    auto normalize = [&](int gmask, int32_t (&xv)[4][CPL]) {
       if (ln) {
         LnRow2 lr[4];
         bool wide = false;
@@ -471,14 +472,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
         for (int gp = 0; gp < 4; gp += 2) {
           if (!(gmask >> gp & 3)) continue;
-          double wL[2][2], wb[2][2];
+          double wL[2][CPL], wb[2][CPL];
           RescaleHi pl[2];
 #pragma unroll
           for (int g = gp; g < gp + 2; ++g)
             if (gmask >> g & 1) {
               pl[g - gp] = prm->ln[g];
 #pragma unroll
-              for (int c = 0; c < 2; ++c) {
+              for (int c = 0; c < CPL; ++c) {
                 wL[g - gp][c] = LdL[g * 64 + cellw + c];
                 wb[g - gp][c] = bdL[g * 64 + cellw + c];
               }
@@ -488,7 +489,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
           for (int g = gp; g < gp + 2; ++g)
             if (gmask >> g & 1)
 #pragma unroll
-              for (int c = 0; c < 2; ++c) {
+              for (int c = 0; c < CPL; ++c) {
                 int32_t v = decltype(narrow_tag)::value ? ln_second_stage_narrow(gs[g][c], lr[g], wL[g - gp][c], wb[g - gp][c])
                                                         : ln_second_stage(gs[g][c], lr[g], wL[g - gp][c], wb[g - gp][c]);
                 if (pre_ln) v = rescale_preshift(v, pl[g - gp]);
@@ -505,14 +506,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         for (int g = 0; g < 4; ++g)
           if (gmask >> g & 1)
 #pragma unroll
-            for (int c = 0; c < 2; ++c) xv[g][c] = gs[g][c];
+            for (int c = 0; c < CPL; ++c) xv[g][c] = gs[g][c];
       }
     };
     // table values of |x[g][c]| for the gates of gmask; tb[g] = which table (0 sigma, 1 tanh, 2 cell tanh);
     // see rec_kernel's lookup
-    auto lookup = [&](int gmask, const int32_t (&x)[4][2], const int (&tb)[4], int32_t (&out)[4][2]) {
-      int32_t mag[4][2];
-      uint32_t base[4][2], delta[4][2];
+    auto lookup = [&](int gmask, const int32_t (&x)[4][CPL], const int (&tb)[4], int32_t (&out)[4][CPL]) {
+      int32_t mag[4][CPL];
+      uint32_t base[4][CPL], delta[4][CPL];
       int32_t top[3] = {0, 0, 0};  // largest |x| looked up in each table
       LutLds lp[3];
 #pragma unroll
@@ -527,7 +528,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         if (gmask >> g & 1) {
           const int dom = lp[tb[g]].dom, sh = lp[tb[g]].sh;
 #pragma unroll
-          for (int c = 0; c < 2; ++c) {
+          for (int c = 0; c < CPL; ++c) {
             mag[g][c] = abs_masked(x[g][c]);
             top[tb[g]] = top[tb[g]] > mag[g][c] ? top[tb[g]] : mag[g][c];
             const int32_t ai = mag[g][c] < dom ? mag[g][c] : dom - 1;
@@ -540,7 +541,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       for (int g = 0; g < 4; ++g)
         if (gmask >> g & 1)
 #pragma unroll
-          for (int c = 0; c < 2; ++c) out[g][c] = (int32_t)(base[g][c] + delta[g][c]);
+          for (int c = 0; c < CPL; ++c) out[g][c] = (int32_t)(base[g][c] + delta[g][c]);
       bool over = false;
 #pragma unroll
       for (int i = 0; i < 3; ++i) {
@@ -557,27 +558,27 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             const bool og = mag[g][0] >= dom || mag[g][1] >= dom;
             if (__builtin_amdgcn_ballot_w64(og) != 0) {
 #pragma unroll
-              for (int c = 0; c < 2; ++c)
+              for (int c = 0; c < CPL; ++c)
                 if (mag[g][c] >= dom) out[g][c] = lut_wide_tail(lds + lp[tb[g]].offT, mag[g][c]);
             }
           }
       }
     };
     constexpr int gates_now = (cifg ? 0 : 1) | 2 | 4 | (ph ? 0 : 8);  // with a peephole the o gate waits for c^t
-    int32_t xv[4][2], tv[4][2];
+    int32_t xv[4][CPL], tv[4][CPL];
     normalize(gates_now, xv);
     {
       const int gate_tb[4] = {0, 0, 1, 0};
       lookup(gates_now, xv, gate_tb, tv);
     }
     const int32_t m_c = prm->m_c;
-    int32_t xo[2];
-    int32_t cx[4][2];  // slot 0: the new cell state, for its tanh; slot 3: the o gate with a peephole
+    int32_t xo[CPL];
+    int32_t cx[4][CPL];  // slot 0: the new cell state, for its tanh; slot 3: the o gate with a peephole
     {
       int32_t s1 = 0;
       uint32_t s2 = 0;
 #pragma unroll
-      for (int c = 0; c < 2; ++c) {
+      for (int c = 0; c < CPL; ++c) {
         const int32_t fg = mirror_sigmoid_masked(xv[1][c], tv[1][c]);
         const int32_t ig = cifg ? cifg_input_gate(fg) : mirror_sigmoid_masked(xv[0][c], tv[0][c]);
         const int32_t zg = mirror_tanh_masked(xv[2][c], tv[2][c]);
@@ -601,7 +602,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // ---- hidden state (Sec. 3.2.7): tanh of the new cell state in its own format (Sec. 3.2.2), and
     // with a peephole the layer norm and sigma of the o gate; the tanh does not wait for the o gate's
     // statistics, so it runs while they travel
-    int32_t tcv[4][2];
+    int32_t tcv[4][CPL];
     const int hid_tb[4] = {2, 2, 2, 0};
     if (ph && ln) {
       publish_stats(1, 3, 3);
@@ -611,20 +612,20 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       lookup(1, cx, hid_tb, tcv);
     }
     if (ph) {
-      int32_t ov[4][2];
+      int32_t ov[4][CPL];
       normalize(8, ov);
 #pragma unroll
-      for (int c = 0; c < 2; ++c) cx[3][c] = ov[3][c];
+      for (int c = 0; c < CPL; ++c) cx[3][c] = ov[3][c];
       lookup(8, cx, hid_tb, tcv);
 #pragma unroll
-      for (int c = 0; c < 2; ++c) xo[c] = mirror_sigmoid_masked(cx[3][c], tcv[3][c]);
+      for (int c = 0; c < CPL; ++c) xo[c] = mirror_sigmoid_masked(cx[3][c], tcv[3][c]);
     }
     {
       const RescaleHi pm = prm->m;
       const int32_t zp_m = prm->zp_m;
       uint32_t pk = 0;
 #pragma unroll
-      for (int c = 0; c < 2; ++c) {
+      for (int c = 0; c < CPL; ++c) {
         int32_t om = mul_i24(xo[c], mirror_tanh_masked(cx[0][c], tcv[0][c]));
         if (pre_m) om = rescale_preshift(om, pm);
         const int32_t mq = sat8(rescale_sat16_pre<0>(om, pm) + zp_m);
@@ -762,7 +763,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     int n1 = n0;
     asm volatile("" : "+v"(n1));  // computed here: shared with the prologue it would hold registers through the loop
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
+    for (int c = 0; c < CPL; ++c)
       if (n1 + c < a.N) a.c_out[(size_t)row * a.N + n1 + c] = (int16_t)creg[c];
   }
 }
