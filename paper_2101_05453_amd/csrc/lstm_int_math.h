@@ -294,7 +294,7 @@ LSTM_HD int32_t rescale_sat16_pre(int32_t a, const RescaleHi &p) {
 #endif
   return sat16((hi + p.add) >> p.sh);
 }
-// rescale(a, M, r) without the saturation, for an operand that needs no treatment (at most 2^30 in magnitude)
+// rescale(a, M, r) without the saturation: p.k == 0, or the operand (or a factor of it) has been shifted left by p.k already
 LSTM_HD int32_t rescale_hi_pre(int32_t a, const RescaleHi &p) {
 #if defined(__HIP_DEVICE_COMPILE__)
   const int32_t hi = __mulhi(a, p.M);

@@ -301,7 +301,9 @@ __global__ __launch_bounds__(FULL ? kScanBlockFull : kScanBlock) void sru_scan_k
     cst[c] = (n < N && !a.zero_state) ? a.c_state[(size_t)rowc * N + n] : 0;
     vf[c] = n < N ? a.vq[n] : 0;
     vr[c] = n < N ? a.vq[N + n] : 0;
-    if (FAST) {  // the operand's left shift of the rescale, by at most one, on the factor that stays
+    // the operand's left shift of the rescale on the factor that stays, for the rescale_hi_pre of a gate's sum: by one at most
+    // (the choice of the fast forms sees to that), so that twice 32767 * 32768 still fits
+    if (FAST) {
       vf[c] = (int32_t)((uint32_t)vf[c] << a.pv[0].k);
       vr[c] = (int32_t)((uint32_t)vr[c] << a.pv[1].k);
     }
@@ -883,7 +885,8 @@ int sru_int_forward(const sru_int_model *m, const int8_t *x, int32_t T, int32_t 
       a.tr_tx = tr->tx; a.tr_tv = tr->tv; a.tr_act = tr->act; a.tr_c = tr->c; a.tr_h16 = tr->h16; a.tr_y = tr->y;
     }
     timed_begin(SRU_INT_K_SCAN);
-    // the specialization that drops the checks the host can make once (see sru_scan_kernel)
+    // the specialization that drops the checks the host can make once (see sru_scan_kernel); the shifts: operands that the
+    // rescale's left shift of at most 1 (v, 31 bits), 15 (the state, 16 bits) and 22 (the input, 9 bits) keeps within 32 bits
     const bool fast = !tr && (N & 3) == 0 && (reinterpret_cast<uintptr_t>(y) & 3) == 0 && 31 - q.ev[0] >= 32 &&
                       31 - q.ev[1] >= 32 && 31 - q.eh >= 18 && (G == 4 || 31 - q.es >= 11) && m->sig_inner;
     const int64_t threads = ws_gemm ? (int64_t)a.bp_blocks * ((N + 7) / 8) * 64 : (int64_t)B * ((N + 3) / 4);

@@ -155,6 +155,38 @@ def test_fast_forms_of_the_scan(sru, inputs, N, B, T, wide):
             equal(f"c_state[{reg}]", g, w)
 
 
+@pytest.mark.parametrize("inputs,N,B", [
+    ([64, 72], 72, 5),         # tile-ordered terms, the smaller table
+    ([1040, 1040], 1040, 280),  # row-major terms, the table of all values
+])
+@pytest.mark.parametrize("v,shift", [(300.0, 32), (150.0, 33)])  # of v c to the gate's format: an operand to shift, and none
+def test_recurrent_vectors_of_a_wide_range(sru, inputs, N, B, v, shift):
+    """One large element of v in cells of eight integer bits: the other elements are a few units, so that v c lies within the
+    gate's range for many states."""
+    import torch
+
+    layers, x = wl.make_sru(inputs, N, B, 5, seed=N, weight_param=1.0 / N ** 0.5, input_param=1.5)
+    sru.calibrate(layers, np.ascontiguousarray(x[:, :2]))
+    for s in layers:
+        s.c_absmax = 2.0 ** 8 - 1
+        for j in range(2):
+            s.v[j] = np.random.default_rng(j).uniform(-0.1, 0.1, size=N).astype(np.float32)
+            s.v[j][3] = v
+    lib_m, orc_m = both(sru, layers)
+    for l in range(len(layers)):
+        assert [31 - e for e in orc_m.get_quant(l)["ev"]] == [shift, shift]
+    xq = quantize_x(x, orc_m.get_quant(0))
+    sel = np.array([0, 1, B // 2, B - 1])
+    c0 = np.random.default_rng(3).integers(-8192, 8192, size=B * N * len(layers)).astype(np.int16)
+    c0[3::2 * N], c0[N + 3::2 * N] = -32768, 32767  # beside the large element: the largest products
+    co = np.concatenate([r.ravel() for r in state_rows(c0, layers, B, sel)])
+    yo, _ = orc_m.forward(np.ascontiguousarray(xq[:, sel]), c_state=co, threads=8)
+    cs = torch.from_numpy(c0.copy()).cuda()
+    equal("y", lib_m.forward(torch.from_numpy(xq).cuda(), c_state=cs).cpu().numpy()[:, sel], yo)
+    for g, w in zip(state_rows(cs.cpu().numpy(), layers, B, sel), state_rows(co, layers, len(sel), np.arange(len(sel)))):
+        equal("c_state", g, w)
+
+
 def test_speech_encoder_shapes_sampled_rows(sru):
     """Layers of the benchmark's width: N = 2048 at B = 256 (input 512, then 2048 = the general matmul and the
     input as the highway term) on rows spread over the row blocks, N = 1024 at B = 64 whole."""
