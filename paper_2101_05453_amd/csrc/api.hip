@@ -970,48 +970,61 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1) {
 }
 
 // Expected time of the layers one after the other on the launch `p` names, in microseconds: per layer and launch what
-// does not depend on the number of steps (input GEMM, the weights into registers and LDS) and a step.  Fitted to calls of
-// 2 to 8 layers, 1 to 512 rows and 1 to 64 steps of 64 to 2048 cells with and without layer norm and projection (604
-// calls, within 10 % but for single launches that hide behind one another).
+// does not depend on the number of steps (input GEMM, the weights into registers and LDS) and a step.  Both formulas are
+// fitted to 1452 calls of 2 to 8 layers of 48 to 2048 cells with all options, 1 to 512 rows and 1 to 64 steps.
 double sequential_us(const LayerHost &h, const RecPlan &p, int L, int64_t T, int64_t B) {
   const double ln = h.layer_norm() ? 1 : 0, pr = h.projection() ? 1 : 0;
+  const double late_o = h.layer_norm() && h.peephole() ? 1 : 0;  // a second round of statistics
   const double mb = (8.0 * h.N * h.H + pr * h.N * h.H) * 1e-6;  // weights of a layer that reads its like
+  const double n = h.N * 1e-3, widest = std::max(h.N, h.H);
   double once, step;
   if (!p.ok) {  // a launch per operation and step
     once = 15.0;
-    step = 15.0 + 0.01 * h.N;
+    step = 15.0 + 10.0 * n;
+  } else if (p.solo && widest <= 64) {  // four waves
+    once = 12.0;
+    step = 0.59 + 0.86 * ln + 0.57 * late_o + 0.09 * pr;
+  } else if (p.solo && widest <= 128) {  // eight
+    once = 12.5;
+    step = 0.73 + 1.01 * ln + 0.68 * late_o + 0.22 * pr;
   } else if (p.solo) {
-    once = 9.0 + 0.044 * h.N;
-    step = h.N <= 128 ? 0.28 + 0.0055 * h.N + ln * (0.0095 * h.N - 0.3) : 1.45 + ln * 1.55;  // 16 waves beyond 128 cells
+    once = 17.9;
+    step = 1.50 + 1.57 * ln + 0.72 * late_o + 0.19 * pr;
   } else if (p.quad) {
-    once = 15.5 + 1.5 * mb;
-    step = 1.0 + 0.00105 * h.N + ln * 1.5 + pr * 1.1;
+    once = 14.6 + 1.48 * mb;
+    step = 0.96 + 1.21 * n + 1.48 * ln + 1.14 * late_o + 0.94 * pr;
+  } else if (p.use16) {
+    once = 11.8 + 1.17 * mb;
+    step = 3.04 + 0.60 * n + 1.91 * ln + 1.12 * late_o + 1.50 * pr;
   } else {
-    once = 15.5 + 0.9 * mb;
-    step = (p.use16 ? 3.0 + 0.0006 * h.N : 3.5 + 0.001 * h.N) + ln * 2.0 + pr * 1.3;
+    once = 7.5 + 1.69 * mb;
+    step = (4.33 + 1.20 * n + 1.77 * ln + 1.49 * late_o + 1.81 * pr) * (p.ra.rows_pg > 32 ? 1.5 : 1.0);
   }
   const int64_t rows = p.ok ? (int64_t)p.ra.groups * p.ra.rows_pg : B;
   return L * (once + T * step) * (double)((B + rows - 1) / rows);
 }
 
 // The same of the stacked launch: every layer walks its T * tiles items (step, tile of 32 rows) one item behind the
-// layer below.  A call of one item needs no exchange through a barrier and no second trip for W: half the time a layer.
+// layer below.  A call of one item needs no exchange through a barrier and no second trip for W.
 double stacked_us(const LayerHost &h, int L, int64_t T, int64_t B, double item_us) {
-  const double ln = h.layer_norm() ? 1 : 0, pr = h.projection() ? 1 : 0, H = h.H;
-  const double mb = (8.0 * h.N * h.H + pr * h.N * h.H) * 1e-6;
-  const double once = 11.0 + 1.2 * mb + ln * 2.0;
+  const double ln = h.layer_norm() ? 1 : 0, pr = h.projection() ? 1 : 0, late_o = h.layer_norm() && h.peephole() ? 1 : 0;
+  const double mb = (8.0 * h.N * h.H + pr * h.N * h.H) * 1e-6, n = h.N * 1e-3, w = h.H * 1e-3;
   const int64_t items = T * ((B + 31) / 32);
-  const double item = item_us > 0     ? item_us
-                      : items == 1    ? 3.7 + 0.002 * H + ln * 1.9 + pr * (1.5 + 0.0011 * h.N)
-                                      : 5.0 + 0.0035 * H + 4.2e-6 * H * H + ln * 2.3 + pr * 0.003 * h.N;
-  return items == 1 ? once + 3.5 + (L - 1) * item : once + (double)(items + L - 2) * item;
+  if (items == 1) {
+    const double layer = item_us > 0 ? item_us : 3.26 + 1.96 * w + 2.15 * ln + 1.76 * late_o + pr * (2.55 + 1.44 * n);
+    return 10.6 + 0.70 * mb + L * layer;
+  }
+  const double item = item_us > 0 ? item_us : 4.96 + 3.50 * w + 3.85 * w * w + 2.17 * ln + 1.68 * late_o + pr * (2.35 + 1.69 * n);
+  return 14.0 + 1.47 * mb + (double)(items + L - 2) * item;
 }
 
 // Whether forward runs T steps of B rows as one stacked launch (a function of the model, its options, T
 // and B only: lstm_int_workspace_bytes and lstm_int_forward must agree): where its expected time is the
-// shorter one.  Over the 604 calls above the choice costs 0.2 % against the better way of each; one time per step and
-// per item for all models, taken from 2048 cells, cost 3.2 % (256 cells, layer norm, 8 layers, 64 rows, 8 steps: 438 us
-// one after the other, 196 stacked; 1024 cells, 3 layers, 32 rows, 64 steps: 773, 1030).
+// shorter one.  The formulas are off by 3 to 5 % at the median and up to 20 % and more in single calls, but a wrong choice is
+// a close one: over 620 calls that were not in the fit it costs 0.2 % against the better way of each (48 cells, 8 layers, layer
+// norm and a projection, 2 rows, 44 steps: 643 us one after the other, 441 stacked; 128 cells, 6 layers, 128 rows, 2 steps: 88,
+// 113).  A fit without peephole and layer norm together, coupled gates and widths between the powers of two cost 1.2 %, one
+// time per step and item for all models, from 2048 cells, 4.7 %.
 bool stack_chosen(const lstm_int_model *m, int64_t T, int64_t B) {
   if (!m->stackable || m->stack == 0 || m->path == 1 || m->reverse) return false;
   int ks = 0;

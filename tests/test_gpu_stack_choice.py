@@ -7,7 +7,7 @@ import lstm_workloads as wl
 from parity_util import assert_equal, prepare_both
 
 pytestmark = pytest.mark.gpu
-LN, PROJ = wl.LAYER_NORM, wl.PROJECTION
+LN, PH, PROJ, CIFG = wl.LAYER_NORM, wl.PEEPHOLE, wl.PROJECTION, wl.CIFG
 
 
 def forward_counted(model, xd):
@@ -29,6 +29,11 @@ def forward_counted(model, xd):
     (2, 512, 512, 0, 8, 16, False),       # 130, 85
     (8, 1024, 256, LN | PROJ, 1, 1, True),
     (4, 320, 320, LN, 1000, 2, False),    # the 32-row kernel
+    (6, 64, 64, LN | PH, 12, 64, True),   # 597, 857
+    (8, 48, 16, LN | PROJ, 2, 44, True),  # 441, 643
+    (3, 112, 32, PROJ, 13, 9, False),     # 93, 60
+    (3, 80, 72, PH | PROJ, 44, 2, False),  # 65, 47
+    (5, 192, 40, CIFG | LN | PROJ, 81, 5, False),  # 199, 154
 ])
 def test_the_faster_way_is_taken(orc, L, N, H, flags, B, T, stacked):
     import torch
