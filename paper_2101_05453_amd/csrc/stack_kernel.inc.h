@@ -822,7 +822,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         v16i pacc;
 #pragma unroll
         for (int v = 0; v < 16; ++v) pacc[v] = 0;
-        if (ksteps == 64) {  // N = 2048: eight steps for every wave
+        if (kmine == 8) {  // straight, as in rec_kernel (8 layers of 2048 cells, 32 rows, one step 110.6 -> 107.7 us)
 #pragma unroll
           for (int k = 0; k < 8; ++k) mv[k] = *reinterpret_cast<const v4i *>(mrow + moff + k * 1024);
           __builtin_amdgcn_sched_barrier(0);

@@ -19,6 +19,7 @@ LN, PH, PROJ, CIFG = wl.LAYER_NORM, wl.PEEPHOLE, wl.PROJECTION, wl.CIFG
     (1024, 640, PROJ | LN, 37, 3),          # two output tiles of some workgroups, four slots
     (640, 640, PROJ | CIFG, 64, 3),         # the same at another width
     (2048, 640, PROJ | LN | PH, 40, 3),     # eight k steps per wave
+    (1850, 96, PROJ | LN, 40, 3),           # the same, the last wave with four
     (1024, 1024, LN, 70, 3),                # the deepest recurrent product
     (640, 600, PROJ | LN, 1000, 2),         # two row tiles, two output tiles
 ])
@@ -70,6 +71,8 @@ def test_saturated_gates(orc, N, H, flags):
     (64, 72, 9, PROJ | CIFG, 37, 3),         # two row tiles: the first workgroup's word behind the barrier
     (64, 1100, 33, PROJ | LN | PH, 33, 2),
     (128, 1024, 640, PROJ | LN, 40, 2),
+    (64, 1856, 96, PROJ | LN, 40, 2),        # eight k steps per wave, the last with four
+    (64, 2048, 96, PROJ | LN, 9, 1),         # eight for all
 ])
 def test_division_over_the_waves_of_a_stack(orc, I, N, H, flags, B, T):
     layers, x = wl.make_custom([I, H, H], N, H, flags, B, T, seed=N + H + B, weight_param=0.9 / N ** 0.5)
