@@ -126,6 +126,21 @@ void hm_calibrate_plan(const lstm_int_layer_params *layers, int32_t num_layers, 
     for (const CalibrateRegion *r : {&l.wop, &l.rop, &l.pop, &l.wx, &l.m, &l.h, &l.c, &l.pre}) put(*r);
 }
 
+// The regions of it that only some layers have: (offset, bytes) of the running extremes, which lie in `stats`, then per layer
+// of part and amax (0 bytes: not there).
+void hm_calibrate_plan_sums(const lstm_int_layer_params *layers, int32_t num_layers, int32_t T, int32_t B, int64_t *out) {
+  const CalibratePlan p = calibrate_plan(layers, num_layers, T, B, 88);
+  auto put = [&](const CalibrateRegion &r) {
+    *out++ = (int64_t)r.off;
+    *out++ = (int64_t)r.bytes;
+  };
+  put(p.ext);
+  for (const CalibrateLayer &l : p.layers) {
+    put(l.part);
+    put(l.amax);
+  }
+}
+
 int hm_scan_takes_full_table(int tile, int64_t threads, int cus) { return scan_takes_full_table(tile != 0, threads, cus); }
 
 // The library's offline phase on the host (what lstm_int_prepare runs before the upload); *checksum

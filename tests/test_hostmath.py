@@ -301,6 +301,45 @@ def test_statistics_run_of_unlike_layers_needs_no_more_than_its_layers(hm):
     assert fixed[4][1] == 8 * T * B * 1504 and fixed[5][1] == 8 * T * B * 48
 
 
+@pytest.mark.parametrize("N,flags,B,gates", [
+    (1024, 4, 16, 4), (96, 4 | 1, 5, 3), (2048, 4 | 8, 31, 4),  # the products leave the layer norm's sums
+    (1500, 4, 16, 0), (1024, 4 | 2, 16, 0), (1024, 0, 16, 0), (4128, 4, 16, 0),  # no whole groups, peephole, no norm, too wide
+    (4096, 4, 512, 0),  # products in blocks of 128 x 128
+])
+def test_statistics_runs_sums_have_places_of_their_own(hm, N, flags, B, gates):
+    """What the products of a step leave for the layer norm (sum and squares, largest value per row and 32 columns) and the
+    running extremes: as large as the kernels' indices reach, inside the allocation, and over no other buffer in use."""
+    from types import SimpleNamespace
+
+    from paper_2101_05453_amd import binding
+
+    H, first = 40 if flags & 8 else N, 1 if flags & 1 else 0
+    z = lambda *s: np.zeros(s, np.float32)  # noqa: E731
+    layers = [SimpleNamespace(input_size=I, num_cells=N, output_size=H, flags=flags, W=[None] * first + [z(N, I)] * (4 - first),
+                              R=[None] * first + [z(N, H)] * (4 - first), b=[None] * first + [z(N)] * (4 - first),
+                              P=[z(N)] * 3, Lw=[None] * first + [z(N)] * (4 - first), Wproj=z(H, N), bproj=z(H), x_min=0.0, x_max=0.0,
+                              h_min=0.0, h_max=0.0, m_min=0.0, m_max=0.0, c_absmax=0.0, g_absmax=[0.0] * 4) for I in (24, H)]
+    arr, keep = binding.marshal_layers(layers)
+    out, sums = np.zeros(1 + 2 * (6 + 8 * 2), np.int64), np.zeros(2 * (1 + 2 * 2), np.int64)
+    hm.hm_calibrate_plan(arr, 2, 4, B, out.ctypes.data_as(C.c_void_p))
+    hm.hm_calibrate_plan_sums(arr, 2, 4, B, sums.ctypes.data_as(C.c_void_p))
+    del keep
+    total, r = int(out[0]), out[1:].reshape(-1, 2)
+    ext, rest = sums[:2], sums[2:].reshape(2, 2, 2)
+    assert r[0][0] + 2 * 88 <= ext[0] and ext[0] + ext[1] <= r[0][0] + r[0][1]  # behind the statistics, within their region
+    slices = 1 if flags & 6 == 6 else max(1, min(256 // B, (N + 127) // 128))
+    own_sums = flags & 4 and not gates
+    assert ext[1] == (8 * B * slices * (7 * 512 if own_sums else 3 * 128) if B <= 256 and N <= 4096 else 0)
+    for l in range(2):
+        part, amax = rest[l]
+        # element (b, group) of the products' N gates / 32 groups of columns, two values each of part
+        assert part[1] >= 8 * 2 * B * gates * N // 32 and amax[1] >= 8 * B * gates * N // 32
+        if not gates:
+            assert part[1] == 0 and amax[1] == 0
+        spans = sorted((int(o), int(o + b)) for o, b in np.concatenate([r[:6], r[6:].reshape(2, 8, 2)[l], rest[l]]) if b)
+        assert all(a[1] <= b[0] for a, b in zip(spans, spans[1:])) and spans[-1][1] <= total
+
+
 def test_sparse_operand_packing(hm):
     """The 2:4 compressed form of recurrent weight rows (sparse MFMA operands): unpacking every lane's
     values through its index bits, at the k positions the layout states, gives the row back; and the
