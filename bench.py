@@ -170,9 +170,17 @@ def bench_sru(args, np, torch, wl, binding):
     G = [4 if s.W[3] is not None else 3 for s in layers]
     scan_bytes = sum(T * B * N * (2.0 * g + 1 + (1 if g == 3 else 0)) for g in G) / L
     gemm_ops = sum(2.0 * T * B * g * N * s.input_size for g, s in zip(G, layers)) / L
-    # vector, scalar, LDS and memory instructions of the scan's compiled loops per cell and step (16 of those per round):
-    # 54 to 62, and 46 to 55 in the form with the large table, which batches of 320 * 256 threads of four cells take
-    instructions = 52.0 if T >= 8 and B * ((N + 3) // 4) >= 320 * 256 else 60.0
+    # vector, scalar, LDS and memory instructions of the scan's compiled loops per cell and step (16 of those per round), by
+    # the form a layer takes: input up to 1024 wide (terms in tile order) or wider, a highway matrix or none, the small table of
+    # sigma or the large one (csrc/sru_plan.h)
+    def scan_instructions(s, g):
+        tile = s.input_size <= 1024
+        threads = (B + 31) // 32 * ((N + 7) // 8) * 64 if tile else B * ((N + 3) // 4)
+        small = (threads + 255) // 256
+        large = small > 256 if not tile else small > 512 and (small % 512 == 0 or small % 512 > 256)
+        return {(True, 3): (64, 56), (True, 4): (51, 43), (False, 3): (65, 56), (False, 4): (53, 45)}[tile, g][large]
+
+    instructions = sum(scan_instructions(s, g) for g, s in zip(G, layers)) / L
     out = {"metric": "sru_cell_steps_per_sec", "value": B * T * L / dt, "unit": "cell-steps/s", "n_gpus": 1,
            "steps": args.steps, "warmup": args.warmup, "ms_per_step": dt * 1e3, "higher_is_better": True,
            "scaling": "weak", "vs_baseline": None, "dtype": "int8", "data": "synthetic",

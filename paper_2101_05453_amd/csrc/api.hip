@@ -89,7 +89,7 @@ struct LayerDev {
   int8_t *W2 = nullptr;     // [GS*8][32][Ipad]
   int8_t *W2f = nullptr;    // the same in MFMA operand order [GS*8][Ipad/32][64 lanes][16] (Ipad <= 1024), else NULL
   int32_t *bx2 = nullptr;   // [GS*8][32]
-  int4 *R2 = nullptr;       // [GS][4][2][ks][64]
+  int4 *R2 = nullptr;       // [GS][8 tiles][ks][64]
   int4 *R2s = nullptr;      // the same weights in the 2:4 compressed form (persistent.h), or NULL: R is not 2:4
   bool p16 = false;         // the 16-row kernel takes this layer (small batches)
   int ks16 = 0;

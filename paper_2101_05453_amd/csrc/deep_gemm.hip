@@ -15,9 +15,10 @@
 // and the lane of a global -> LDS load fetches the piece that belongs at its place.
 //
 // 16384 x 6144 x 2048: 200 us = 2.06 POP/s (the general matmul on the same box: 238), 8192 rows 99 (118), 2048 rows 32 (39),
-// 256 rows 12.5 (15).  What bounds it is the power the chip allows for MFMAs and stores together, as in in_gemm.hip: without
-// the operands' LDS reads, without the barriers or without the exchange it takes the same 190 to 200 us, without the stores
-// or without the loads of x 168; the MFMAs are busy 57 % of the clocks it runs at.  Streaming stores: no difference.
+// 256 rows 12.5 (15).  The chip runs it at 1.9 to 1.95 GHz, what its power leaves for MFMAs with stores, as in in_gemm.hip, and
+// the MFMAs are busy 50 to 54 % of those clocks.  No single part holds the rest: without the operands' LDS reads, without the
+// barriers or without the exchange it takes the same 190 to 200 us, without the stores or without the loads of x 168.
+// Streaming stores: no difference.
 #include <cstring>
 #include <type_traits>
 

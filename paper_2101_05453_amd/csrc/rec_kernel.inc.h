@@ -726,7 +726,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       // without one is flat from there on, and the clamped index was the lookup).  How often that happens is
       // the launch's choice of prefix: with 16384 entries (|x| < 4 in Q3.12) about one layer-norm output in a
       // thousand, i.e. some lane of most batches -- and the step then waits for the slowest of the group's
-      // 128 waves; with 24576 entries it is one in a million.  The tests narrow down from the batch to the
+      // 256 waves; with 24576 entries it is one in a million.  The tests narrow down from the batch to the
       // gate to the cell.
       if (!TAILS) return;
       bool over = false;

@@ -188,7 +188,7 @@ def test_recurrent_vectors_of_a_wide_range(sru, inputs, N, B, v, shift):
 
 
 def test_speech_encoder_shapes_sampled_rows(sru):
-    """Layers of the benchmark's width: N = 2048 at B = 256 (input 512, then 2048 = the general matmul and the
+    """Layers of the benchmark's width: N = 2048 at B = 256 (input 512, then 2048 = the matmul of deep inputs and the
     input as the highway term) on rows spread over the row blocks, N = 1024 at B = 64 whole."""
     layers, x = wl.make_sru([512, 2048], 2048, 256, 6, seed=3, weight_param=0.03)
     compare_all(sru, layers, x, "sru2048", rows=[0, 15, 16, 100, 127, 128, 200, 255])
@@ -198,8 +198,8 @@ def test_speech_encoder_shapes_sampled_rows(sru):
 
 def test_benchmark_configuration_sampled_rows(sru):
     """The configuration bench.py --sru times, two of its four layers (2048 cells, input 512 then 2048, B = 256,
-    T = 64: 16384-row matmuls on the register-resident GEMM and on the general matmul's widest tile, both forms of
-    the scan) on three rows of different row blocks."""
+    T = 64: 16384-row matmuls on both register-resident forms and, with them switched off, on the general matmul's
+    widest tile; both forms of the scan) on three rows of different row blocks."""
     layers, x = wl.make_sru([512, 2048], 2048, 256, 64, seed=0, weight_param=0.03)
     compare_all(sru, layers, x, "sru_bench", rows=[0, 100, 255], calibration_rows=16)  # statistics from 16 rows (Sec. 4)
 
