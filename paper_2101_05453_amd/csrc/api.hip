@@ -591,7 +591,7 @@ int upload(lstm_int_model *m) {
   m->tanh3 = reinterpret_cast<const uint16_t *>(dbase + tab_off[3]);
   m->wsig3 = wide_sig;
   m->wtanh3 = wide_tab[3];
-  if (rec_init() != hipSuccess || rec16_init() != hipSuccess || solo_init() != hipSuccess || quad_init() != hipSuccess || in_gemm_init() != hipSuccess || gemm_init() != hipSuccess || stack_init() != hipSuccess)
+  if (rec_init() != hipSuccess || rec16_init() != hipSuccess || solo_init() != hipSuccess || row_init() != hipSuccess || quad_init() != hipSuccess || in_gemm_init() != hipSuccess || gemm_init() != hipSuccess || stack_init() != hipSuccess)
     return LSTM_INT_E_DEVICE;
   // The stacked kernel runs models whose layers are all alike (same cells, width and variant; every layer
   // above the first reads the layer below), up to 8 of them, within the shift and table limits of the
@@ -829,7 +829,9 @@ struct RecPlan {
   RecArgs ra;
   int groups = 0;      // most groups in one launch
   bool ok = false, use16 = false;
-  bool solo = false, quad = false;  // with use16: the one-workgroup kernel / the four-row kernel instead of the 16-row one
+  // with use16: the one-workgroup kernel (row: the one with a workgroup per batch row) / the four-row kernel instead of the
+  // 16-row one
+  bool solo = false, row = false, quad = false;
 };
 
 // share: launches' worth of groups that are to fit one launch (2: both directions of a bidirectional layer)
@@ -899,10 +901,16 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1) {
     RecArgs r1 = ra;
     r1.R2h = d.R2h; r1.ks16 = d.ks16; r1.rows_pg = 4; r1.groups = (B + 3) / 4;
     r1.Wp2 = d.Wp2; r1.bp2 = d.bp2; r1.ptiles = d.ptiles; r1.prow = 32;
-    if (solo_lds_bytes(r1) <= 160 * 1024) {
+    const bool row = row_supported(h.N, h.H, (int)h.flags, B * share);
+    if (row) {
+      r1.rows_pg = 1;
+      r1.groups = B;
+    }
+    if ((row ? row_lds_bytes(r1) : solo_lds_bytes(r1)) <= 160 * 1024) {
       ra = r1;
       p2_groups = r1.groups;
       p.solo = p.use16 = true;
+      p.row = row;
     }
   }
   // larger layers, batches small enough for it: groups of four rows
@@ -934,7 +942,7 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1) {
     ra.R2 = d.R2s;
     ra.sparse = 1;
   }
-  auto lds_need = [&]() { return p.quad ? quad_lds_bytes(ra) : p.solo ? solo_lds_bytes(ra) : p.use16 ? rec16_lds_bytes(ra) : rec_lds_bytes(ra); };
+  auto lds_need = [&]() { return p.quad ? quad_lds_bytes(ra) : p.row ? row_lds_bytes(ra) : p.solo ? solo_lds_bytes(ra) : p.use16 ? rec16_lds_bytes(ra) : rec_lds_bytes(ra); };
   // What LDS is left goes to longer prefixes of the two gate tables, 1 KB at a time in turn: a value
   // beyond the prefix costs the whole group a detour (rec_kernel.inc.h, lookup), and with 24576 entries
   // (|x| < 6 in Q3.12) there is about one per million layer-norm outputs instead of one per thousand.
@@ -971,7 +979,8 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1) {
 
 // Expected time of the layers one after the other on the launch `p` names, in microseconds: per layer and launch what
 // does not depend on the number of steps (input GEMM, the weights into registers and LDS) and a step.  Both formulas are
-// fitted to 1452 calls of 2 to 8 layers of 48 to 2048 cells with all options, 1 to 512 rows and 1 to 64 steps.
+// fitted to 1452 calls of 2 to 8 layers of 48 to 2048 cells with all options, 1 to 512 rows and 1 to 64 steps; for layers of up
+// to 256 cells with a workgroup per row, and for those as a stack, to 995 calls of 8 to 256 cells.
 double sequential_us(const LayerHost &h, const RecPlan &p, int L, int64_t T, int64_t B) {
   const double ln = h.layer_norm() ? 1 : 0, pr = h.projection() ? 1 : 0;
   const double late_o = h.layer_norm() && h.peephole() ? 1 : 0;  // a second round of statistics
@@ -981,7 +990,16 @@ double sequential_us(const LayerHost &h, const RecPlan &p, int L, int64_t T, int
   if (!p.ok) {  // a launch per operation and step
     once = 15.0;
     step = 15.0 + 10.0 * n;
-  } else if (p.solo && widest <= 64) {  // four waves
+  } else if (p.row && widest <= 64) {  // a workgroup per row: four waves
+    once = 11.8;
+    step = 0.50 + 0.45 * ln + 0.57 * late_o + 0.12 * pr;
+  } else if (p.row && widest <= 128) {  // eight
+    once = 12.6;
+    step = 0.61 + 0.73 * ln + 0.74 * late_o + 0.14 * pr;
+  } else if (p.row) {
+    once = 17.7;
+    step = 1.18 + 0.70 * ln + 1.26 * late_o + 0.30 * pr;
+  } else if (p.solo && widest <= 64) {  // a workgroup per four rows: four waves
     once = 12.0;
     step = 0.59 + 0.86 * ln + 0.57 * late_o + 0.09 * pr;
   } else if (p.solo && widest <= 128) {  // eight
@@ -1010,6 +1028,10 @@ double stacked_us(const LayerHost &h, int L, int64_t T, int64_t B, double item_u
   const double ln = h.layer_norm() ? 1 : 0, pr = h.projection() ? 1 : 0, late_o = h.layer_norm() && h.peephole() ? 1 : 0;
   const double mb = (8.0 * h.N * h.H + pr * h.N * h.H) * 1e-6, n = h.N * 1e-3, w = h.H * 1e-3;
   const int64_t items = T * ((B + 31) / 32);
+  if (h.N <= 256 && h.H <= 256 && item_us <= 0) {
+    if (items == 1) return 10.3 + L * (3.61 + 0.88 * w + 1.97 * ln + 1.74 * late_o + pr * (2.18 + 8.95 * n));
+    return 12.8 + (double)(items + L - 2) * (3.94 + 22.9 * w - 65.4 * w * w + 2.20 * ln + 1.90 * late_o + pr * (1.98 + 9.74 * n));
+  }
   if (items == 1) {
     const double layer = item_us > 0 ? item_us : 3.26 + 1.96 * w + 2.15 * ln + 1.76 * late_o + pr * (2.55 + 1.44 * n);
     return 10.6 + 0.70 * mb + L * layer;
@@ -1037,7 +1059,8 @@ bool stack_chosen(const lstm_int_model *m, int64_t T, int64_t B) {
   if (plan_stack(m, T, B).total > (size_t)LSTM_INT_STATIC_WORKSPACE_BYTES &&
       plan_workspace(m, T, B).total <= (size_t)LSTM_INT_STATIC_WORKSPACE_BYTES)
     return false;
-  return stacked_us(h, L, T, B, m->stack_step_us) < sequential_us(h, plan_rec(m, 0, (int)T, (int)B), L, T, B);
+  // where they come out within 3 % of each other, one launch instead of two per layer: less for the host to do
+  return stacked_us(h, L, T, B, m->stack_step_us) < 1.03 * sequential_us(h, plan_rec(m, 0, (int)T, (int)B), L, T, B);
 }
 
 // Synchronization scratch of a launch (plan_workspace's `sync`): barrier counters and placement words, statistics words.
@@ -1240,7 +1263,7 @@ int lstm_int_forward(const lstm_int_model *cm, const int8_t *x, int32_t T, int32
             static_cast<RecArgs &>(one.d[0]) = ra;
             one.d[0].ldy = h.H;
           }
-          if ((plan.solo ? launch_solo(s, one) : plan.quad ? launch_quad(s, one, coop) : use16 ? launch_rec16(s, ra, coop) : launch_rec(s, ra, coop)) != hipSuccess)
+          if ((plan.row ? launch_row(s, one) : plan.solo ? launch_solo(s, one) : plan.quad ? launch_quad(s, one, coop) : use16 ? launch_rec16(s, ra, coop) : launch_rec(s, ra, coop)) != hipSuccess)
             return LSTM_INT_E_DEVICE;
         }
       }
@@ -1381,7 +1404,7 @@ static bool pair_chosen(const lstm_int_model *f, const lstm_int_model *b, int32_
     if (hf.N != hb.N || hf.H != hb.H || hf.flags != hb.flags || hf.I != hb.I) return false;
     if ((f->sparse == 2 && f->dev[l].R2s) || (b->sparse == 2 && b->dev[l].R2s)) return false;
     const RecPlan pf = plan_rec(f, (int)l, T, B, 2), pb = plan_rec(b, (int)l, T, B, 2);
-    if (!pf.ok || !pb.ok || !pf.use16 || !pb.use16 || pf.solo != pb.solo || pf.quad != pb.quad) return false;
+    if (!pf.ok || !pb.ok || !pf.use16 || !pb.use16 || pf.solo != pb.solo || pf.row != pb.row || pf.quad != pb.quad) return false;
     if (!pf.solo && pf.groups + pb.groups > 8 * (32 / pf.ra.GS)) return false;
   }
   return true;
@@ -1477,7 +1500,7 @@ static int forward_pair(lstm_int_model *const (&m)[2], const int8_t *x, int32_t 
     if (!plan[0].solo) plant_misplaced(m[0], s, base[0] + ws[0].sync);
     Timed t0(m[0]->prof, s, LSTM_INT_K_RECURRENT), t1(m[1]->prof, s, LSTM_INT_K_RECURRENT);
     const bool coop = m[0]->cooperative != 0;
-    if ((plan[0].solo ? launch_solo(s, pair) : plan[0].quad ? launch_quad(s, pair, coop) : launch_rec16_pair(s, pair, coop)) != hipSuccess)
+    if ((plan[0].row ? launch_row(s, pair) : plan[0].solo ? launch_solo(s, pair) : plan[0].quad ? launch_quad(s, pair, coop) : launch_rec16_pair(s, pair, coop)) != hipSuccess)
       return LSTM_INT_E_DEVICE;
   }
   for (int i = 0; i < 2; ++i) {

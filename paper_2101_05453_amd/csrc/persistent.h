@@ -245,6 +245,13 @@ size_t solo_lds_bytes(const RecArgs &a);
 hipError_t launch_solo(hipStream_t s, const RecArgs2 &a);
 hipError_t solo_init();
 
+// The same, one workgroup per batch row (row_kernel.inc.h), for small batches.  As above with rows_pg = 1, groups = B; rows =
+// batch rows of the launch, both directions' together.
+bool row_supported(int N, int H, int flags, int rows);
+size_t row_lds_bytes(const RecArgs &a);
+hipError_t launch_row(hipStream_t s, const RecArgs2 &a);
+hipError_t row_init();
+
 constexpr int kQuadWgWords = 64 + 64 + 2 * 16;  // exchange words of a workgroup per slot: h, m, two rounds of statistics
 // The same step on groups of four batch rows for larger layers and small batches (quad_kernel.inc.h).  Takes RecArgs2
 // always; rows_pg = 4, groups = ceil(B / 4), ldy set; `share` launches' worth of groups must fit one (2 for a pair).

@@ -70,6 +70,16 @@ __device__ __forceinline__ int *other_status() {
                                                            offsetof(RecArgs, status));
 }
 
+// Adds into a word of LDS, in an asm with no result.  Ahead of an LDS atomic the compiler waits for every operation on global
+// memory that is on its way, because one of them may be a transfer into LDS (and does so whether or not the kernel has waited
+// for those): here the terms of later steps and the stores of the output, a round trip to memory in the middle of a step.
+// The compiler does not know that LDS has work to do either: a lds_barrier has to come before what reads the word.
+__device__ __forceinline__ void lds_add_u64(u64 *word, u64 v) {
+  asm volatile("ds_add_u64 %0, %1" ::"v"((uint32_t)(uintptr_t)(__attribute__((address_space(3))) u64 *)word), "v"(v) : "memory");
+}
+// A barrier of the workgroup that waits for LDS only.  __syncthreads waits for every load and store of the wave besides.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // Per-layer constants, kept in LDS and read where they are used: as kernel
 // arguments they would all be live in scalar registers across the time loop.
 struct PrmLds {  // 256 bytes (kPrmLdsBytes in persistent.hip)

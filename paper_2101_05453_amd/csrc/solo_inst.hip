@@ -17,7 +17,7 @@ static solo_fn pick_solo(int form, int fl) {
   return nullptr;
 }
 
-// Where it is the faster one.  Time per step, us, this kernel (16 or 1024 rows alike; without - with a projection) / groups of
+// Where it is the faster one (up to 256 rows row_kernel is faster still, row_inst.hip).  Time per step, us, this kernel (16 or 1024 rows alike; without - with a projection) / groups of
 // 16 rows over several workgroups, up to 1024 rows:
 //   64 cells 0.7-0.8 / 2.6,      with layer norm 1.5-1.6 / 4.4,      and peephole 2.1-2.3 / 5.9
 //  128 cells 0.8-1.0 / 3.0-3.3,                  1.8-2.0 / 4.7-5.1,               2.4-2.7 / 6.1-6.6

@@ -1,0 +1,63 @@
+"""Layers of up to 256 cells with a workgroup per batch row: step counts around the ring of W x terms, every combination of options
+in each of the three forms, widths that leave lanes and waves without cells, the last batch of that kernel and the first of the
+four-row one (whose variants run here too), and both directions of a bidirectional layer in one launch on either side."""
+import numpy as np
+import pytest
+
+import lstm_workloads as wl
+from paper_2101_05453_amd import binding
+from parity_util import assert_equal, prepare_both, run_and_compare
+
+pytestmark = pytest.mark.gpu
+LN, PH, PROJ, CIFG = wl.LAYER_NORM, wl.PEEPHOLE, wl.PROJECTION, wl.CIFG
+
+
+@pytest.mark.parametrize("N,H", [(5, 5), (64, 64), (50, 33), (65, 65), (128, 100), (100, 128), (129, 129), (200, 256), (256, 80)])
+@pytest.mark.parametrize("T", [1, 8, 9, 17, 36])
+def test_steps_around_the_ring(orc, N, H, T):
+    flags = ((0, LN, PH | LN, CIFG | LN)[T % 4]) | (PROJ if N != H else 0)
+    layers, x = wl.make_custom([24, H], N, H, flags, 3, T, seed=N + T, weight_param=0.9 / N ** 0.5)
+    run_and_compare(orc, layers, x, f"row{N}h{H}t{T}", trace=False, options={"stack": 0})
+
+
+@pytest.mark.parametrize("flags", range(16))
+@pytest.mark.parametrize("N", [40, 120, 250])
+@pytest.mark.parametrize("B", [2, 259])
+def test_every_variant(orc, N, B, flags):
+    H = N - 9 if flags & PROJ else N
+    layers, x = wl.make_custom([32], N, H, flags, B, 5, seed=N + flags, weight_param=0.9 / N ** 0.5)
+    run_and_compare(orc, layers, x, f"row{N}b{B}f{flags}", trace=False, rows=sorted({0, 1, B // 2, B - 2, B - 1}))
+
+
+@pytest.mark.parametrize("N,flags", [(64, LN), (100, PH | LN), (256, 0), (203, PH | LN | PROJ)])
+def test_last_batch_of_a_row_per_workgroup(orc, N, flags):
+    import torch
+
+    layers, x = wl.make_custom([40], N, N - 3 if flags & PROJ else N, flags, 257, 11, seed=N, weight_param=0.9 / N ** 0.5)
+    lib_model, orc_model, xq = prepare_both(orc, layers, x)
+    rows = [0, 1, 4, 127, 128, 251, 254, 255]
+    want = np.asarray(orc.forward(orc_model, np.ascontiguousarray(xq[:, rows])))
+    for B in (255, 256, 257):
+        y = lib_model.forward(torch.from_numpy(np.ascontiguousarray(xq[:, :B])).cuda()).cpu().numpy()
+        at = [i for i, r in enumerate(rows) if r < B]
+        assert_equal(f"y B={B}", y[:, [rows[i] for i in at]], want[:, at])
+    assert lib_model.device_status() == 0
+
+
+@pytest.mark.parametrize("B", [1, 128, 129])
+def test_two_directions(orc, B):
+    import torch
+
+    layers, x = wl.make_custom([40], 96, 96, LN, B, 19, seed=5, weight_param=0.09)
+    back, _ = wl.make_custom([40], 96, 96, LN, B, 19, seed=6, weight_param=0.09)
+    fwd, ofwd, xq = prepare_both(orc, layers, x)
+    bwd, obwd, _ = prepare_both(orc, back, x)
+    q = bwd.get_quant(0)
+    if (q["s_x"], q["zp_x"]) != (fwd.get_quant(0)["s_x"], fwd.get_quant(0)["zp_x"]):
+        pytest.skip("the two directions read one quantized input")
+    bwd.set_option("reverse", 1)
+    y = binding.forward_bidirectional(fwd, bwd, torch.from_numpy(xq).cuda()).cpu().numpy()
+    rows = sorted({0, B // 2, B - 1})
+    xs = np.ascontiguousarray(xq[:, rows])
+    assert_equal("forward", y[:, rows, :96], np.asarray(orc.forward(ofwd, xs)))
+    assert_equal("backward", y[:, rows, 96:], np.asarray(orc.forward(obwd, np.ascontiguousarray(xs[::-1])))[::-1])
