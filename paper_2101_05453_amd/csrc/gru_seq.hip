@@ -19,9 +19,9 @@
 // What bounds them: the chain of a step, instruction issue of the cell (about 300 instructions per row tile of 16) and the
 // exchange (1 us among 2 to 32 workgroups), not the product: 0.65 us of 3.7 at 2048 cells and 64 rows.  Time per step (us),
 // one launch per step, which re-reads the weights from L2 (before; up to 1024 cells 3.6 in one launch) -> these kernels:
-//    512 cells, 16 rows   3.6 -> 1.5     1024 cells, 128 rows  3.7 -> 2.9     2048 cells, 16 rows   8.4 -> 3.3
+//    512 cells, 16 rows   3.6 -> 1.3     1024 cells, 128 rows  3.7 -> 2.9     2048 cells, 16 rows   8.4 -> 2.4
 //    512 cells, 256 rows  3.7 -> 2.7     1024 cells, 512 rows  10.5 -> 4.6    2048 cells, 256 rows  13.4 -> 5.7
-// (both tiles of 32 rows in one turn: 6.1; without any exchange it would take 4.9)
+// (2048 cells, 256 rows, both tiles of 32 rows in one turn: 6.1; without any exchange it would take 4.9)
 //
 // Placement and the waits that end are those of the LSTM's recurrent kernels (rec_kernel.inc.h).
 #include "gru_seq.h"
@@ -254,10 +254,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         v4i hf[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) hf[u] = *reinterpret_cast<const v4i *>(hcur + arow * LS + (q << 4) + (k0 + u) * 64);
+        // a gate's products one after the other: dependent 16x16x64 MFMAs issue back to back, rotating accumulators do not (with
+        // four k steps there is nothing in it)
+        if constexpr (KS >= 8) {
+          __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int u = 0; u < U; ++u)
+          for (int g = 0; g < 3; ++g)
 #pragma unroll
-          for (int g = 0; g < 3; ++g) acc[g] = __builtin_amdgcn_mfma_i32_16x16x64_i8(hf[u], Wf[g][k0 + u], acc[g], 0, 0, 0);
+            for (int u = 0; u < U; ++u) acc[g] = __builtin_amdgcn_mfma_i32_16x16x64_i8(hf[u], Wf[g][k0 + u], acc[g], 0, 0, 0);
+        } else {
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int g = 0; g < 3; ++g) acc[g] = __builtin_amdgcn_mfma_i32_16x16x64_i8(hf[u], Wf[g][k0 + u], acc[g], 0, 0, 0);
+        }
       }
       if (pre) {
 #pragma unroll
@@ -293,37 +303,60 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
           __hip_atomic_store(words + q * row_words + member * 16 + wave * 4 + (c16 >> 2), (u64)(uint32_t)w | (u64)(uint32_t)w2 << 32,
                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
-      // a thread polls its words, U of them per round, until all carry the tag
-      constexpr int U = KS >= 16 ? 4 : (KS + 3) / 4;
-      const u64 want = (u64)((tag ^ never) * 0x01000100u) << 32 | (u64)((tag ^ never) * 0x01000100u);
-      const int total = 4 * row_words;
+      if constexpr (KS >= 8) {
+        // a thread polls its words, two of them per load (poll_pairs), until all carry the tag.  With the products in order and
+        // this, 100 steps of 512 cells, 16 rows 149 -> 138 us, 64 of 1024 cells 141 -> 120, of 2048 cells, 32 rows 220 -> 178.
+        const int pairs = 2 * row_words;  // a row's words are a multiple of 16
+        const uint32_t want = (tag ^ never) * 0x01000100u;
+        constexpr int U = KS >= 16 ? 2 : 1;
 #pragma unroll 1
-      for (int base = 0; base < total; base += 256 * U) {
-        u64 v8[U];
-        int budget = a.spin_limit;
-        for (;;) {
-          bool ok = true;
+        for (int base = 0; base < pairs; base += 256 * U) {
+          unsigned at[U];
+          v4i w[U];
 #pragma unroll
-          for (int k = 0; k < U; ++k) {
-            const int w = base + k * 256 + tid;
-            v8[k] = w < total ? __hip_atomic_load(words + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : want;
+          for (int k = 0; k < U; ++k) at[k] = base + k * 256 + tid < pairs ? (unsigned)(base + k * 256 + tid) * 16 : 0;
+          int budget = a.spin_limit;
+          for (;;) {
+            poll_pairs(words, at, w);
+            uint32_t off = 0;
+#pragma unroll
+            for (int k = 0; k < U; ++k)
+#pragma unroll
+              for (int i = 0; i < 4; ++i) off |= (uint32_t)w[k][i] ^ want;
+            if (__builtin_amdgcn_ballot_w64((off & 0xFF00FF00u) != 0) == 0) break;
+            if (gru_spent(a, budget)) {
+              __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              flag[0] = 0;
+              break;
+            }
           }
 #pragma unroll
-          for (int k = 0; k < U; ++k) ok = ok && (v8[k] & 0xFF00FF00FF00FF00ull) == want;
-          if (__builtin_amdgcn_ballot_w64(!ok) == 0) break;
+          for (int k = 0; k < U; ++k) {
+            const int c = base + k * 256 + tid;
+            if (c < pairs) {
+              const int half = row_words >> 1, rr = (c >= half) + (c >= 2 * half) + (c >= 3 * half);
+              *reinterpret_cast<v2i *>(hnext + rr * LS + 8 * (c - rr * half)) =
+                  v2i{(int)__builtin_amdgcn_perm((uint32_t)w[k][1], (uint32_t)w[k][0], 0x06040200u),
+                      (int)__builtin_amdgcn_perm((uint32_t)w[k][3], (uint32_t)w[k][2], 0x06040200u)};
+            }
+          }
+        }
+      } else {  // up to 256 cells a thread has one word at most (in pairs half of the threads would have none: 2 to 4 % longer)
+        const u64 want = (u64)((tag ^ never) * 0x01000100u) << 32 | (u64)((tag ^ never) * 0x01000100u);
+        u64 w = want;
+        int budget = a.spin_limit;
+        for (;;) {
+          if (tid < 4 * row_words) w = __hip_atomic_load(words + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (__builtin_amdgcn_ballot_w64((w & 0xFF00FF00FF00FF00ull) != want) == 0) break;
           if (gru_spent(a, budget)) {
             __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             flag[0] = 0;
             break;
           }
         }
-#pragma unroll
-        for (int k = 0; k < U; ++k) {
-          const int w = base + k * 256 + tid;
-          if (w < total) {
-            const int rr = (w >= row_words) + (w >= 2 * row_words) + (w >= 3 * row_words), c = w - rr * row_words;
-            *reinterpret_cast<uint32_t *>(hnext + rr * LS + 4 * c) = __builtin_amdgcn_perm((uint32_t)(v8[k] >> 32), (uint32_t)v8[k], 0x06040200u);
-          }
+        if (tid < 4 * row_words) {
+          const int rr = (tid >= row_words) + (tid >= 2 * row_words) + (tid >= 3 * row_words), c = tid - rr * row_words;
+          *reinterpret_cast<uint32_t *>(hnext + rr * LS + 4 * c) = __builtin_amdgcn_perm((uint32_t)(w >> 32), (uint32_t)w, 0x06040200u);
         }
       }
       wait_vmem();  // the W x terms asked for a step ago are in LDS (a wave may have had nothing to poll)

@@ -30,15 +30,20 @@
 // and 3, the layer output is stored by wave 1, each right after the step's last
 // exchange; the statistics are polled by wave 0.
 //
+// The h and m words are polled 16 bytes per load (poll_pairs): what a poll costs is
+// its loads.
+//
 // What bounds it: the chain of a step -- one exchange (two with a projection; and
-// one per round of statistics), 0.9 to 1.5 us each -- and the ~150 to 250
-// instructions a wave issues between them.  Time per step at batch 16, rec16_kernel
-// -> this kernel (us):     no layer norm    layer norm    and peephole
-//   320 cells                3.31 -> 1.81   4.73 -> 3.07    6.06 -> 4.13
-//   512 cells                3.31 -> 1.87   4.72 -> 3.15    5.97 -> 4.24
-//   1024 cells               3.92 -> 2.40   5.52 -> 3.90    6.94 -> 5.61
-//   1024, 256 outputs        5.40 -> 3.29   6.92 -> 4.74    8.36 -> 6.01
-//   2048, 640 outputs        5.82 -> 4.74   7.76 -> 6.58    8.96 -> 8.04
+// one per round of statistics), 0.8 to 1.3 us each -- and the ~150 to 250
+// instructions a wave issues between them.  Time per step at batch 16 (250 against
+// 50 steps), rec16_kernel -> this kernel with 8 bytes per load -> 16 (us):
+//                            no layer norm          layer norm            and peephole
+//   320 cells              3.31 -> 1.53 -> 1.44   4.73 -> 2.81 -> 2.76   6.06 -> 3.92 -> 3.89
+//   512 cells              3.31 -> 1.58 -> 1.46   4.72 -> 2.85 -> 2.79   5.97 -> 3.96 -> 3.90
+//   1024 cells             3.92 -> 2.03 -> 1.80   5.52 -> 3.59 -> 3.32   6.94 -> 4.88 -> 4.62
+//   1024, 256 outputs      5.40 -> 2.99 -> 2.71   6.92 -> 4.46 -> 4.24   8.36 -> 5.76 -> 5.49
+//   2048, 640 outputs      5.82 -> 4.38 -> 3.82   7.76 -> 6.20 -> 5.58   8.96 -> 7.70 -> 7.14
+// (the first column with the input matmul's share in it)
 #pragma once
 
 #include "rec_kernel.inc.h"
@@ -268,25 +273,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     --budget;
     return (budget & 15) == 0 && (budget <= 0 || __hip_atomic_load(a.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0);
   };
-  // (value, tag) words of `row_words` per row -> an LDS tile; a thread polls its words, U of them per round, until all
-  // carry the tag
+  // (value, tag) words of `row_words` per row, a multiple of four, -> an LDS tile; a thread polls its words, two per load and U
+  // loads per round, until all carry the tag
   auto poll_tile = [&](auto count, const u64 *src, int row_words, unsigned tag, int8_t *dst, int ld) {
     constexpr int U = decltype(count)::value;
-    const u64 want = (u64)((tag & 0xFF) * 0x01000100u) << 32 | (u64)((tag & 0xFF) * 0x01000100u);
-    const int total = 4 * row_words;
-    for (int base = 0; base < total; base += 256 * U) {
-      u64 v[U];
+    const uint32_t want = (tag & 0xFF) * 0x01000100u;
+    const int half = row_words >> 1, pairs = 4 * half;
+    for (int base = 0; base < pairs; base += 256 * U) {
+      unsigned at[U];
+      v4i w[U];
+#pragma unroll
+      for (int k = 0; k < U; ++k) at[k] = base + k * 256 + tid < pairs ? (unsigned)(base + k * 256 + tid) * 16 : 0;
       int budget = a.spin_limit;
       for (;;) {
-        bool ok = true;
+        poll_pairs(src, at, w);
+        uint32_t off = 0;
 #pragma unroll
-        for (int k = 0; k < U; ++k) {
-          const int w = base + k * 256 + tid;
-          v[k] = w < total ? __hip_atomic_load(src + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : want;
-        }
+        for (int k = 0; k < U; ++k)
 #pragma unroll
-        for (int k = 0; k < U; ++k) ok = ok && (v[k] & 0xFF00FF00FF00FF00ull) == want;
-        if (__builtin_amdgcn_ballot_w64(!ok) == 0) break;
+          for (int i = 0; i < 4; ++i) off |= (uint32_t)w[k][i] ^ want;
+        if (__builtin_amdgcn_ballot_w64((off & 0xFF00FF00u) != 0) == 0) break;
         if (spent(budget)) {
           give_up();
           break;
@@ -294,11 +300,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       }
 #pragma unroll
       for (int k = 0; k < U; ++k) {
-        const int w = base + k * 256 + tid;
-        if (w < total) {
-          const int rr = (w >= row_words) + (w >= 2 * row_words) + (w >= 3 * row_words), c = w - rr * row_words;
-          *reinterpret_cast<uint32_t *>(dst + rr * ld + 4 * c) =
-              __builtin_amdgcn_perm((uint32_t)(v[k] >> 32), (uint32_t)v[k], 0x06040200u);
+        const int c = base + k * 256 + tid;
+        if (c < pairs) {
+          const int rr = (c >= half) + (c >= 2 * half) + (c >= 3 * half);
+          *reinterpret_cast<v2i *>(dst + rr * ld + 8 * (c - rr * half)) =
+              v2i{(int)__builtin_amdgcn_perm((uint32_t)w[k][1], (uint32_t)w[k][0], 0x06040200u),
+                  (int)__builtin_amdgcn_perm((uint32_t)w[k][3], (uint32_t)w[k][2], 0x06040200u)};
         }
       }
     }
@@ -522,9 +529,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     // projection (Sec. 3.2.8): a tile of 16 outputs per wave, the whole depth in one wave
     if (proj && my_tiles > 0) {
       if (GS <= 16)
-        poll_tile(std::integral_constant<int, 4>{}, xm + (size_t)(t & 1) * slot_words, m_row_words, tag ^ never, mT, MLS);
+        poll_tile(std::integral_constant<int, 2>{}, xm + (size_t)(t & 1) * slot_words, m_row_words, tag ^ never, mT, MLS);
       else
-        poll_tile(std::integral_constant<int, 8>{}, xm + (size_t)(t & 1) * slot_words, m_row_words, tag ^ never, mT, MLS);
+        poll_tile(std::integral_constant<int, 4>{}, xm + (size_t)(t & 1) * slot_words, m_row_words, tag ^ never, mT, MLS);
       __syncthreads();
       if (flag[0] == 0) return;
       if (has_tile) {
@@ -546,7 +553,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         publish(xh + (size_t)(t & 1) * slot_words + q * h_row_words + (p0 >> 2) + (c16 >> 2), hq, tag);
       }
     }
-    poll_tile(std::integral_constant<int, (KS16 + 3) / 4>{}, xh + (size_t)(t & 1) * slot_words, h_row_words, tag ^ never, hnext, LS);
+    poll_tile(std::integral_constant<int, KS16 <= 8 ? 1 : 2>{}, xh + (size_t)(t & 1) * slot_words, h_row_words, tag ^ never, hnext, LS);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the W x terms asked for a step ago are in LDS (a wave may have had nothing to poll)
     __syncthreads();
     if (flag[0] == 0) return;

@@ -80,6 +80,27 @@ __device__ __forceinline__ void lds_add_u64(u64 *word, u64 v) {
 // A barrier of the workgroup that waits for LDS only.  __syncthreads waits for every load and store of the wave besides.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// A poll of (value, tag) byte pairs, 16 bytes per lane, at agent scope (past the L1): w[k] = the 16 bytes at base + at[k].  A load
+// of that width may be torn, and a pair vouches for its own value only: that is enough where every pair's tag is looked at.
+// What a poll costs is its loads: with 8 bytes per lane, twice as many of them, an exchange takes 0.1 us (512 cells) to
+// 0.4 us (2048 cells, 640 outputs) longer.
+__device__ __forceinline__ void poll_pairs(const u64 *base, const unsigned (&at)[1], v4i (&w)[1]) {
+  asm volatile("global_load_dwordx4 %0, %1, %2 sc1\n\ts_waitcnt vmcnt(0)" : "=&v"(w[0]) : "v"(at[0]), "s"(base) : "memory");
+}
+__device__ __forceinline__ void poll_pairs(const u64 *base, const unsigned (&at)[2], v4i (&w)[2]) {
+  asm volatile("global_load_dwordx4 %0, %2, %4 sc1\n\tglobal_load_dwordx4 %1, %3, %4 sc1\n\ts_waitcnt vmcnt(0)"
+               : "=&v"(w[0]), "=&v"(w[1])
+               : "v"(at[0]), "v"(at[1]), "s"(base)
+               : "memory");
+}
+__device__ __forceinline__ void poll_pairs(const u64 *base, const unsigned (&at)[4], v4i (&w)[4]) {
+  asm volatile("global_load_dwordx4 %0, %4, %8 sc1\n\tglobal_load_dwordx4 %1, %5, %8 sc1\n\t"
+               "global_load_dwordx4 %2, %6, %8 sc1\n\tglobal_load_dwordx4 %3, %7, %8 sc1\n\ts_waitcnt vmcnt(0)"
+               : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3])
+               : "v"(at[0]), "v"(at[1]), "v"(at[2]), "v"(at[3]), "s"(base)
+               : "memory");
+}
+
 // Per-layer constants, kept in LDS and read where they are used: as kernel
 // arguments they would all be live in scalar registers across the time loop.
 struct PrmLds {  // 256 bytes (kPrmLdsBytes in persistent.hip)
