@@ -50,6 +50,14 @@ int hm_ln_row_is_narrow(const int16_t *q, int32_t n) {
   }
   return ln_row_is_narrow(ln_row2(s1, s2, n, 1.0 / (double)n)) ? 1 : 0;
 }
+// mean and variance of `count` rows of n values each from their sums
+void hm_ln_moments(const int64_t *s1, const int64_t *s2, int32_t n, int64_t count, int64_t *mean, int64_t *var) {
+  for (int64_t i = 0; i < count; ++i) {
+    const LnMoments m = ln_moments(s1[i], s2[i], n, 1.0 / (double)n);
+    mean[i] = (int64_t)m.mean;
+    var[i] = (int64_t)m.var;
+  }
+}
 // the pieces of ln_row2 from estimates that are off by the given relative errors
 int64_t hm_ln_sigma(int64_t var, double rsq_error) {
   LnEstimates est;

@@ -36,13 +36,13 @@
 // What bounds it: the chain of a step -- one exchange (two with a projection; and
 // one per round of statistics), 0.8 to 1.3 us each -- and the ~150 to 250
 // instructions a wave issues between them.  Time per step at batch 16 (250 against
-// 50 steps), rec16_kernel -> this kernel with 8 bytes per load -> 16 (us):
+// 50 steps), rec16_kernel -> this kernel with 8 bytes per load -> now (us):
 //                            no layer norm          layer norm            and peephole
-//   320 cells              3.31 -> 1.53 -> 1.44   4.73 -> 2.81 -> 2.76   6.06 -> 3.92 -> 3.89
-//   512 cells              3.31 -> 1.58 -> 1.46   4.72 -> 2.85 -> 2.79   5.97 -> 3.96 -> 3.90
-//   1024 cells             3.92 -> 2.03 -> 1.80   5.52 -> 3.59 -> 3.32   6.94 -> 4.88 -> 4.62
-//   1024, 256 outputs      5.40 -> 2.99 -> 2.71   6.92 -> 4.46 -> 4.24   8.36 -> 5.76 -> 5.49
-//   2048, 640 outputs      5.82 -> 4.38 -> 3.82   7.76 -> 6.20 -> 5.58   8.96 -> 7.70 -> 7.14
+//   320 cells              3.31 -> 1.53 -> 1.44   4.73 -> 2.81 -> 2.66   6.06 -> 3.92 -> 3.72
+//   512 cells              3.31 -> 1.58 -> 1.46   4.72 -> 2.85 -> 2.69   5.97 -> 3.96 -> 3.73
+//   1024 cells             3.92 -> 2.03 -> 1.80   5.52 -> 3.59 -> 3.25   6.94 -> 4.88 -> 4.46
+//   1024, 256 outputs      5.40 -> 2.99 -> 2.71   6.92 -> 4.46 -> 4.14   8.36 -> 5.76 -> 5.35
+//   2048, 640 outputs      5.82 -> 4.38 -> 3.82   7.76 -> 6.20 -> 5.54   8.96 -> 7.70 -> 6.95
 // (the first column with the input matmul's share in it)
 #pragma once
 

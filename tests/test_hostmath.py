@@ -186,6 +186,29 @@ def test_layernorm_matches_oracle(orc, hm):
     assert forms[0] > 100 and forms[1] > 100, forms
 
 
+def test_row_moments_without_corrections(hm):
+    """Mean and variance from the sums, in whole numbers: every row length, sums whose quotients lie next to a whole number on
+    either side, the largest sums, and some in between."""
+    rng = np.random.default_rng(12)
+    hm.hm_ln_moments.argtypes = [C.c_void_p, C.c_void_p, C.c_int32, C.c_int64, C.c_void_p, C.c_void_p]
+    for n in range(1, 4097):
+        half = n >> 1
+        # S1 2^10 + half next to a multiple of n, for multiples over the whole range
+        m = rng.integers(-(2**25), 2**25, 12)
+        s1 = np.concatenate([(m * n - half) // 1024, (m * n - half) // 1024 + 1, [-32768 * n, 32767 * n, 0, 1, -1, n - 1]])
+        s1 = np.clip(s1, -32768 * n, 32767 * n).astype(np.int64)
+        m = rng.integers(0, 2**30, len(s1))
+        s2 = m * n + rng.choice([0, 1, -1, half, half + 1, half - 1, n - 1], len(s1))
+        s2[:3] = [0, n * 2**30, n * 2**30 - 1]
+        s2 = np.clip(s2, 0, n * 2**30).astype(np.int64)
+        mean, var = np.zeros_like(s1), np.zeros_like(s1)
+        hm.hm_ln_moments(s1.ctypes.data, s2.ctypes.data, n, len(s1), mean.ctypes.data, var.ctypes.data)
+        for k in range(len(s1)):
+            want = (int(s1[k]) * 1024 + half) // n
+            assert mean[k] == want, (n, s1[k])
+            assert var[k] == max(0, ((int(s2[k]) << 20) + half) // n - want * want), (n, s1[k], s2[k])
+
+
 # What the hardware's estimates of 1 / sqrt and 1 / x may be off by is 2^-23 (relative); the tests allow twice that.
 ESTIMATE_ERRORS = (0.0, 2.0**-23, -(2.0**-23), 2.0**-22, -(2.0**-22))
 
