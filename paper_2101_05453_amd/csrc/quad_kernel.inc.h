@@ -553,7 +553,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         publish(xh + (size_t)(t & 1) * slot_words + q * h_row_words + (p0 >> 2) + (c16 >> 2), hq, tag);
       }
     }
-    poll_tile(std::integral_constant<int, KS16 <= 8 ? 1 : 2>{}, xh + (size_t)(t & 1) * slot_words, h_row_words, tag ^ never, hnext, LS);
+    // a wave without words (narrow projections) does not poll: its loads of some word or other cost as much as the others'
+    if (!proj || wave * 64 < 2 * h_row_words)
+      poll_tile(std::integral_constant<int, KS16 <= 8 ? 1 : 2>{}, xh + (size_t)(t & 1) * slot_words, h_row_words, tag ^ never, hnext, LS);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the W x terms asked for a step ago are in LDS (a wave may have had nothing to poll)
     __syncthreads();
     if (flag[0] == 0) return;
