@@ -351,7 +351,8 @@ def main():
     if model.device_status() != 0:
         sys.exit(f"bench.py: device status {model.device_status()} after the profiled loop; the timing is void")
     persistent = prof["cell"]["launches"] == 0  # the per-step path launches a cell kernel per step
-    stacked = persistent and prof["input_gemm"]["launches"] == 0  # all layers in one launch, W x computed per step
+    # W x computed in the recurrent launches, of all layers at once or (small layers and batches) of one
+    stacked = persistent and prof["input_gemm"]["launches"] == 0
     work = {}
     for q in quants:
         for k, v in algorithmic_work(q, B, T, persistent).items():

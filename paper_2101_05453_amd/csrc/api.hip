@@ -990,15 +990,19 @@ double sequential_us(const LayerHost &h, const RecPlan &p, int L, int64_t T, int
   if (!p.ok) {  // a launch per operation and step
     once = 15.0;
     step = 15.0 + 10.0 * n;
-  } else if (p.row && widest <= 64) {  // a workgroup per row: four waves
-    once = 11.8;
-    step = 0.50 + 0.45 * ln + 0.57 * late_o + 0.12 * pr;
-  } else if (p.row && widest <= 128) {  // eight
-    once = 12.6;
-    step = 0.61 + 0.73 * ln + 0.74 * late_o + 0.14 * pr;
-  } else if (p.row) {
-    once = 17.7;
-    step = 1.18 + 0.70 * ln + 1.26 * late_o + 0.30 * pr;
+  } else if (p.row) {  // a workgroup per row; W x in the launch itself or not
+    const int64_t chunks = (T + 15) / 16;
+    const bool own = row_takes_input(h.N, h.H, round_up(h.H, 64), (int)T, (int)B);
+    if (widest <= 64) {
+      once = own ? 8.0 + 1.5 * (double)(chunks - 1) : 12.5;
+      step = 0.37 + 0.45 * ln + 0.56 * late_o + 0.14 * pr;
+    } else if (widest <= 128) {
+      once = own ? 8.6 + 1.3 * (double)(chunks - 1) : 13.2;
+      step = 0.51 + 0.58 * ln + 0.64 * late_o + 0.15 * pr;
+    } else {
+      once = own ? 13.2 : 18.7;
+      step = 0.97 + 0.52 * ln + 0.91 * late_o + 0.31 * pr;
+    }
   } else if (p.solo && widest <= 64) {  // a workgroup per four rows: four waves
     once = 12.0;
     step = 0.59 + 0.86 * ln + 0.57 * late_o + 0.09 * pr;
@@ -1029,8 +1033,8 @@ double stacked_us(const LayerHost &h, int L, int64_t T, int64_t B, double item_u
   const double mb = (8.0 * h.N * h.H + pr * h.N * h.H) * 1e-6, n = h.N * 1e-3, w = h.H * 1e-3;
   const int64_t items = T * ((B + 31) / 32);
   if (h.N <= 256 && h.H <= 256 && item_us <= 0) {
-    if (items == 1) return 10.3 + L * (3.61 + 0.88 * w + 1.97 * ln + 1.74 * late_o + pr * (2.18 + 8.95 * n));
-    return 12.8 + (double)(items + L - 2) * (3.94 + 22.9 * w - 65.4 * w * w + 2.20 * ln + 1.90 * late_o + pr * (1.98 + 9.74 * n));
+    if (items == 1) return 10.0 + L * (3.56 + 0.89 * w + 1.98 * ln + 1.65 * late_o + pr * (2.11 + 9.17 * n));
+    return 12.2 + (double)(items + L - 2) * (3.97 + 23.2 * w - 67.2 * w * w + 2.18 * ln + 1.77 * late_o + pr * (1.91 + 9.77 * n));
   }
   if (items == 1) {
     const double layer = item_us > 0 ? item_us : 3.26 + 1.96 * w + 2.15 * ln + 1.76 * late_o + pr * (2.55 + 1.44 * n);
@@ -1059,8 +1063,11 @@ bool stack_chosen(const lstm_int_model *m, int64_t T, int64_t B) {
   if (plan_stack(m, T, B).total > (size_t)LSTM_INT_STATIC_WORKSPACE_BYTES &&
       plan_workspace(m, T, B).total <= (size_t)LSTM_INT_STATIC_WORKSPACE_BYTES)
     return false;
-  // where they come out within 3 % of each other, one launch instead of two per layer: less for the host to do
-  return stacked_us(h, L, T, B, m->stack_step_us) < 1.03 * sequential_us(h, plan_rec(m, 0, (int)T, (int)B), L, T, B);
+  // Layers of a workgroup per row are short, and every one is a launch more for the host: one launch for all of them is taken
+  // as long as it costs the device no more than 7 % per layer (8 layers of 128 cells, layer norm, 64 rows, 8 steps: 139 us one
+  // after the other, 188 stacked).
+  const RecPlan p = plan_rec(m, 0, (int)T, (int)B);
+  return stacked_us(h, L, T, B, m->stack_step_us) < (p.row ? 1.0 + 0.07 * L : 1.0) * sequential_us(h, p, L, T, B);
 }
 
 // Synchronization scratch of a launch (plan_workspace's `sync`): barrier counters and placement words, statistics words.
@@ -1202,10 +1209,18 @@ int lstm_int_forward(const lstm_int_model *cm, const int8_t *x, int32_t T, int32
       const int launch_rows = p2_groups * ra.rows_pg;
       // the kernels write y in words of four cells; rows that are no multiple of four are copied afterwards
       const bool y_after = last && !rev && !proj && (h.N & 3);
-      {
-        InGemmArgs ga = plan_in_gemm(m, l, T, B);
-        ga.A = in; ga.lda = ld_in;
-        ga.cols = in == x ? h.I : 0;
+      InGemmArgs ga = plan_in_gemm(m, l, T, B);
+      ga.A = in; ga.lda = ld_in;
+      ga.cols = in == x ? h.I : 0;
+      RowInput own_input;  // W x in the recurrent launch itself
+      memset(&own_input, 0, sizeof(own_input));
+      if (plan.row && row_takes_input(h.N, h.H, d.Ipad, T, B) && in_gemm_ws_supported(ga)) {
+        Timed t(m->prof, s, LSTM_INT_K_OTHER);
+        flush_pending();
+        row_set_input(own_input, ga);
+        own_input.h_src = h_state ? h_state + h_off : nullptr;
+        own_input.h_dst = h_state ? h_state + h_off : nullptr;
+      } else {
         ga.tx2 = reinterpret_cast<int4 *>(tx);
         // initial h (given, or real 0 = zp_h), the cleared words of the first launch and the previous layer's
         // final h on its way to the state buffer: done by the input GEMM's workgroups ahead of their own
@@ -1263,13 +1278,13 @@ int lstm_int_forward(const lstm_int_model *cm, const int8_t *x, int32_t T, int32
             static_cast<RecArgs &>(one.d[0]) = ra;
             one.d[0].ldy = h.H;
           }
-          if ((plan.row ? launch_row(s, one) : plan.solo ? launch_solo(s, one) : plan.quad ? launch_quad(s, one, coop) : use16 ? launch_rec16(s, ra, coop) : launch_rec(s, ra, coop)) != hipSuccess)
+          if ((plan.row ? launch_row(s, RowArgs{one, {own_input, {}}}) : plan.solo ? launch_solo(s, one) : plan.quad ? launch_quad(s, one, coop) : use16 ? launch_rec16(s, ra, coop) : launch_rec(s, ra, coop)) != hipSuccess)
             return LSTM_INT_E_DEVICE;
         }
       }
       {
         Timed t(m->prof, s, LSTM_INT_K_OTHER);
-        if (h_state) {
+        if (h_state && !own_input.x) {
           pend.src = out + (size_t)(T - 1) * step_out;
           pend.ld = d.Hpad;
           pend.dst = h_state + h_off;
@@ -1443,8 +1458,16 @@ static int forward_pair(lstm_int_model *const (&m)[2], const int8_t *x, int32_t 
   size_t h_off[2] = {0, 0}, c_off[2] = {0, 0};
   for (int l = 0; l < L; ++l) {
     RecArgs2 pair;
+    RowInput input[2];  // W x in the recurrent launch itself
+    memset(input, 0, sizeof(input));
     RecPlan plan[2] = {plan_rec(m[0], l, T, B, 2), plan_rec(m[1], l, T, B, 2)};
     const int groups = plan[0].groups + plan[1].groups;
+    bool own_input = plan[0].row && row_takes_input(m[0]->host[l].N, m[0]->host[l].H, m[0]->dev[l].Ipad, T, B);  // of both or neither
+    for (int i = 0; i < 2; ++i) {
+      InGemmArgs ga = plan_in_gemm(m[i], l, T, B);
+      ga.A = in[i]; ga.lda = ld_in[i];
+      own_input = own_input && in_gemm_ws_supported(ga);
+    }
     for (int i = 0; i < 2; ++i) {
       const LayerHost &h = m[i]->host[l];
       const LayerDev &d = m[i]->dev[l];
@@ -1457,7 +1480,13 @@ static int forward_pair(lstm_int_model *const (&m)[2], const int8_t *x, int32_t 
       ga.tx2 = reinterpret_cast<int4 *>(base[i] + ws[i].tx);
       uint8_t *sync = base[0] + ws[0].sync;
       const int64_t clear = i == 0 ? sync_bytes(plan[0], groups) : 0;
-      if (in_gemm_ws_supported(ga)) {
+      if (own_input) {
+        Timed t(m[i]->prof, s, LSTM_INT_K_OTHER);
+        if (pend[i].dst) launch_copy_rows_i8(s, pend[i].src, pend[i].ld, pend[i].dst, pend[i].cols, B, pend[i].cols, 0);
+        row_set_input(input[i], ga);
+        input[i].h_src = h_src;
+        input[i].h_dst = h_state[i] ? h_state[i] + h_off[i] : nullptr;
+      } else if (in_gemm_ws_supported(ga)) {
         ga.has_init = 1;
         ga.init.h_src = h_src; ga.init.ld_src = h.H;
         ga.init.h0 = h0; ga.init.ld_h0 = d.Hpad; ga.init.rows = B; ga.init.cols = h.H; ga.init.zp = h.zp_h;
@@ -1486,7 +1515,7 @@ static int forward_pair(lstm_int_model *const (&m)[2], const int8_t *x, int32_t 
       if (!plan[0].solo) set_sync(ra, m[0], sync);
       if (!rec_extents_ok(ra, ws[i], T, 0, h.projection())) return LSTM_INT_E_WORKSPACE;
       pend[i].dst = nullptr;
-      if (h_state[i]) {
+      if (h_state[i] && !own_input) {
         pend[i].src = i ? out : out + (size_t)(T - 1) * B * d.Hpad;
         pend[i].ld = d.Hpad;
         pend[i].dst = h_state[i] + h_off[i];
@@ -1500,7 +1529,7 @@ static int forward_pair(lstm_int_model *const (&m)[2], const int8_t *x, int32_t 
     if (!plan[0].solo) plant_misplaced(m[0], s, base[0] + ws[0].sync);
     Timed t0(m[0]->prof, s, LSTM_INT_K_RECURRENT), t1(m[1]->prof, s, LSTM_INT_K_RECURRENT);
     const bool coop = m[0]->cooperative != 0;
-    if ((plan[0].row ? launch_row(s, pair) : plan[0].solo ? launch_solo(s, pair) : plan[0].quad ? launch_quad(s, pair, coop) : launch_rec16_pair(s, pair, coop)) != hipSuccess)
+    if ((plan[0].row ? launch_row(s, RowArgs{pair, {input[0], input[1]}}) : plan[0].solo ? launch_solo(s, pair) : plan[0].quad ? launch_quad(s, pair, coop) : launch_rec16_pair(s, pair, coop)) != hipSuccess)
       return LSTM_INT_E_DEVICE;
   }
   for (int i = 0; i < 2; ++i) {

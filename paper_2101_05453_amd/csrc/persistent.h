@@ -245,11 +245,29 @@ size_t solo_lds_bytes(const RecArgs &a);
 hipError_t launch_solo(hipStream_t s, const RecArgs2 &a);
 hipError_t solo_init();
 
-// The same, one workgroup per batch row (row_kernel.inc.h), for small batches.  As above with rows_pg = 1, groups = B; rows =
-// batch rows of the launch, both directions' together.
+// The same, one workgroup per batch row (row_kernel.inc.h), for small batches: rows_pg = 1, groups = B, rows = batch rows of the
+// launch, both directions' together.
+struct RowInput {  // W x in the launch itself instead of tx2 (x == NULL): then h0 is not read either, and h_src, h_dst are used
+  const int8_t *x;   // [T B, ldx], 16-byte rows
+  int ldx, cols;     // bytes of a row that may be read, a multiple of 16
+  const int8_t *W2f; // as InGemmArgs
+  const int32_t *bx2;
+  int kx;            // 64-byte k steps
+  int pre;
+  RescaleHi rs[4];
+  const int8_t *h_src;  // [B, H] or NULL (the zero point)
+  int8_t *h_dst;        // [B, H] or NULL: h of the last step
+};
+struct RowArgs {
+  RecArgs2 rec;
+  RowInput in[2];
+};
 bool row_supported(int N, int H, int flags, int rows);
+// whether W x of T steps of B rows is the faster in the launch itself; kpad: bytes of a weight row
+bool row_takes_input(int N, int H, int kpad, int T, int B);
+void row_set_input(RowInput &in, const InGemmArgs &g);
 size_t row_lds_bytes(const RecArgs &a);
-hipError_t launch_row(hipStream_t s, const RecArgs2 &a);
+hipError_t launch_row(hipStream_t s, const RowArgs &a);
 hipError_t row_init();
 
 constexpr int kQuadWgWords = 64 + 64 + 2 * 16;  // exchange words of a workgroup per slot: h, m, two rounds of statistics

@@ -1,4 +1,4 @@
-// The recurrent kernel with one batch row per workgroup (row_kernel.inc.h): instantiations and host side.
+// The recurrent kernel with one batch row per workgroup (row_kernel.inc.h): host side (instantiations: row_inst_*.hip).
 #include "row_kernel.inc.h"
 
 namespace lstm_int {
@@ -10,10 +10,14 @@ static int row_form(int N, int H) {
     if (N <= kRowCells[i] && H <= kRowCells[i]) return i;
   return -1;
 }
-static row_fn pick_row(int form, int fl) {
-  if (form == 0) return row_pick_size<4, 1>(fl);
-  if (form == 1) return row_pick_size<8, 2>(fl);
-  if (form == 2) return row_pick_size<16, 4>(fl);
+// row_inst_{64,128,256}.hip
+row_fn row_pick_64(int fl, bool own);
+row_fn row_pick_128(int fl, bool own);
+row_fn row_pick_256(int fl, bool own);
+static row_fn pick_row(int form, int fl, bool own) {
+  if (form == 0) return row_pick_64(fl, own);
+  if (form == 1) return row_pick_128(fl, own);
+  if (form == 2) return row_pick_256(fl, own);
   return nullptr;
 }
 
@@ -36,7 +40,7 @@ size_t row_lds_bytes(const RecArgs &a) {
   const size_t NC = kRowCells[form];
   size_t n = 3 * NC + 16 * 8 + 4 * sizeof(LnRow2) + 64 + 128;
   n = (n + 1023) & ~(size_t)1023;
-  n += row_ahead(NC / 16) * (NC / 16) * 128 + (form == 2 && (a.flags & 4) ? 1024 * 16 : 0);
+  n += (NC / 16) * (size_t)row_terms_bytes((int)NC / 16, a.T) + (form == 2 && (a.flags & 4) ? 1024 * 16 : 0);
   for (int i = 0; i < 3; ++i)
     if (i < 2 || a.lut[2].blob != a.lut[1].blob) n += (size_t)lut_wide_lds_bytes(a.lut[i].dom, a.lut[i].sh, a.lut[i].tail != 0);
   if (form == 2 && (a.flags & 8)) n += (size_t)((a.H + 15) & ~15) * (NC + 16);
@@ -45,26 +49,58 @@ size_t row_lds_bytes(const RecArgs &a) {
 
 hipError_t row_init() {
   for (int form = 0; form < 3; ++form)
-    for (int fl = 0; fl < 16; ++fl) {
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(pick_row(form, fl)),
+    for (int k = 0; k < 32; ++k) {
+      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(pick_row(form, k >> 1, k & 1)),
                                          hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
       if (e != hipSuccess) return e;
     }
   return hipSuccess;
 }
 
-hipError_t launch_row(hipStream_t s, const RecArgs2 &a) {
-  const RecArgs &f = a.d[0], &b = a.d[1];
+// The input GEMM's launch takes 5 us and more, its weights and its output on top; W x in the launch itself takes 1.4 us for every
+// 16 steps and a microsecond for every 95 KB of weights, which come anew with each.  us per call, GEMM -> in the launch itself:
+//     cells, inputs       64, 64          64, 1024        128, 256        128, 1024       256, 64         256, 1024
+//     1 row, 4 steps      14.6 -> 11.6    18.0 -> 13.2    16.4 -> 13.6    20.2 -> 16.4    23.9 -> 20.7    27.9 -> 28.5
+//     1 row, 16           25.3 -> 21.8    29.4 -> 24.4    30.9 -> 26.4    34.9 -> 31.1    43.9 -> 39.8    48.0 -> 51.8
+//     1 row, 32           25.9 -> 24.5    29.6 -> 29.1    30.0 -> 27.9    33.9 -> 37.5
+//     256 rows, 32        32.2 -> 25.7    35.5 -> 30.4    37.6 -> 29.1    42.1 -> 39.2
+//     1 row, 64           68.1 -> 69.3    72.8 -> 80.6    84.2 -> 84.9    88.5 -> 104.2
+bool row_takes_input(int N, int H, int kpad, int T, int B) {
+  const int form = row_form(N, H);
+  if (form < 0 || T > row_input_steps(kRowCells[form] / 16)) return false;
+  const double kb = 4.0 * ((N + 15) / 16 * 16) * kpad / 1024, out_mb = 8e-6 * T * B * N;
+  return (T + 15) / 16 * (1.4 + kb / 95) < 5.0 + kpad / 250.0 + out_mb / 3.5;
+}
+
+void row_set_input(RowInput &in, const InGemmArgs &g) {
+  in.x = g.A;
+  in.ldx = g.lda;
+  in.cols = g.cols ? g.cols : g.kpad;
+  in.W2f = g.W2f;
+  in.bx2 = g.bx2;
+  in.kx = g.kpad / 64;
+  in.pre = g.pre;
+  for (int i = 0; i < 4; ++i) {
+    in.rs[i] = rescale_hi_prepare(g.M[i], g.r[i]);
+    if (in.rs[i].k != 0) in.pre = 2;
+  }
+}
+
+hipError_t launch_row(hipStream_t s, const RowArgs &a) {
+  const RecArgs &f = a.rec.d[0], &b = a.rec.d[1];
   const int form = row_form(f.N, f.H);
-  row_fn fn = pick_row(form, f.flags & 15);
+  const bool own = a.in[0].x != nullptr;
+  row_fn fn = pick_row(form, f.flags & 15, own);
   if (!fn || !f.R2h || f.rows_pg != 1 || f.groups != f.B ||
-      (b.groups > 0 && (!b.R2h || row_form(b.N, b.H) != form || f.flags != b.flags || b.rows_pg != 1 || b.groups != b.B)))
+      (own && f.T > row_input_steps(kRowCells[form] / 16)) ||
+      (b.groups > 0 && (!b.R2h || row_form(b.N, b.H) != form || f.flags != b.flags || b.rows_pg != 1 || b.groups != b.B || own != (a.in[1].x != nullptr))))
     return hipErrorInvalidValue;
   size_t lds = row_lds_bytes(f);
   if (b.groups > 0) lds = lds > row_lds_bytes(b) ? lds : row_lds_bytes(b);
-  RecArgs2 args = a;
+  RowArgs args = a;
+  const int blocks = ((f.N > f.H ? f.N : f.H) + 15) / 16;  // a wave each; four at least, which bring the tables in sooner
   void *params[] = {&args};
-  return hipLaunchKernel(reinterpret_cast<const void *>(fn), dim3(f.groups + b.groups), dim3(64 * (((f.N > f.H ? f.N : f.H) + 15) / 16)), params, lds, s);
+  return hipLaunchKernel(reinterpret_cast<const void *>(fn), dim3(f.groups + b.groups), dim3(64 * (blocks < 4 ? 4 : blocks)), params, lds, s);
 }
 
 }  // namespace lstm_int

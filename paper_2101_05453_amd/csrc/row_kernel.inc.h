@@ -28,11 +28,17 @@ namespace lstm_int {
 // Steps whose W x terms are on their way.  A wave waits until at most so many of its memory operations are open, two stores per
 // step among them: a term has at least five steps of 0.4 us, with 16 waves two of 1.2 us, to come from memory.
 constexpr int row_ahead(int waves) { return waves == 16 ? 8 : 16; }
+// Most steps whose W x terms a launch computes itself, all of them ahead of its first step, and bytes of LDS for a wave's terms.
+constexpr int row_input_steps(int waves) { return waves == 16 ? 16 : 64; }
+__host__ __device__ constexpr int row_terms_bytes(int waves, int T) {
+  return (T <= row_input_steps(waves) && T > row_ahead(waves) ? T : row_ahead(waves)) * 128;
+}
 
 // The LDS of a launch, from the front (row_lds_bytes mirrors it): h twice, m, sums, statistics, W x terms, tables.
-// FL: bit 0 coupled gates, bit 1 peephole, bit 2 layer norm, bit 3 projection.
-template <int WAVES, int KS16, int FL>
-__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVES == 4 ? 2 : WAVES / 4, WAVES == 4 ? 2 : WAVES / 4))) void row_kernel(RecArgs2 args) {
+// FL: bit 0 coupled gates, bit 1 peephole, bit 2 layer norm, bit 3 projection.  OWN: W x is computed here (RowInput).
+template <int WAVES, int KS16, int FL, bool OWN>
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVES == 4 ? 2 : WAVES / 4, WAVES == 4 ? 2 : WAVES / 4))) void row_kernel(RowArgs all) {
+  const RecArgs2 &args = all.rec;
   constexpr bool cifg = FL & 1, ph = FL & 2, ln = FL & 4, proj = FL & 8;
   constexpr int NC = 16 * WAVES;  // cells and outputs of the workgroup at most
   const int waves = (int)(blockDim.x >> 6), NT = (int)blockDim.x;  // as many as the layer has blocks of 16 cells or outputs
@@ -51,6 +57,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
   const int which = (int)blockIdx.x >= args.d[0].groups ? 1 : 0;
   const RecDirArgs &a = args.d[which];
   const int row = (int)blockIdx.x - (which ? args.d[0].groups : 0);
+  const RowInput &in = all.in[which];
   const int T = a.T, N = a.N, H = a.H, rev = a.rev, ldy = a.ldy;
 
   uint8_t *p = lds;
@@ -61,7 +68,9 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
   int *flag = reinterpret_cast<int *>(p);         p += 64;  // 1: every gate's sigma >= 2^12
   v4i *tables = reinterpret_cast<v4i *>(p);       p += 128;  // LEAN: [gates, second lookups][lane group]
   p = lds + (((size_t)(p - lds) + 1023) & ~(size_t)1023);
-  uint8_t *txL = p + wave * 128;                  p += AHEAD * WAVES * 128;  // [step % AHEAD][wave][8 pieces of 16 bytes]
+  // W x terms: [step % AHEAD][wave][8 pieces of 16 bytes], or, computed here, [step][wave][gate][16 cells]
+  uint8_t *const txL = p + wave * 128;
+  p += WAVES * row_terms_bytes(WAVES, T);
   double *const lnL = reinterpret_cast<double *>(p) + tid * 2;  // LEAN: layer-norm weight and bias of the lane's gate and cell
   p += ln && LEAN ? 64 * WAVES * 16 : 0;
   const bool share_tanh = a.lut[2].blob == a.lut[1].blob;
@@ -94,6 +103,51 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     }
   }
   const bool real = wave < (a.Ncp >> 4);  // the layer has this block of 16 cells (cells past N are zero weights)
+  // W x of all steps of the row, 16 at a time: the steps are the rows of the MFMA's first operand (step t0 + lane % 16), the second is the
+  // input GEMM's operand of two tiles of eight cells, gathered; a lane ends with cell c16 in steps 4 q + v.
+  auto input_terms = [&](int t0) {
+    const int t = t0 + c16 < T ? t0 + c16 : T - 1;
+    const int8_t *xr = in.x + ((size_t)(rev ? T - 1 - t : t) * a.B + row) * in.ldx + (q << 4);
+    const int8_t *wr = in.W2f + ((size_t)(wave * 2 + (c16 >> 3)) * 2 * in.kx + (q >> 1)) * 1024 + ((c16 & 7) + 32 * (q & 1)) * 16;
+    const int32_t *br = in.bx2 + (wave * 2 + (c16 >> 3)) * 32 + (c16 & 7);
+    v4i acc[4];
+#pragma unroll
+    for (int g = g_first; g < 4; ++g) {
+      const int32_t b = br[8 * g];
+      acc[g] = v4i{b, b, b, b};
+    }
+    constexpr int U = 4;  // k steps whose operands are on their way together
+    for (int k0 = 0; k0 < in.kx; k0 += U) {
+      v4i xf[U], wf[U][4];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int ks = k0 + u < in.kx ? k0 + u : in.kx - 1;
+        xf[u] = v4i{0, 0, 0, 0};
+        if (ks * 64 + (q << 4) < in.cols && k0 + u < in.kx) xf[u] = *reinterpret_cast<const v4i *>(xr + ks * 64);
+#pragma unroll
+        for (int g = g_first; g < 4; ++g) wf[u][g] = *reinterpret_cast<const v4i *>(wr + (size_t)ks * 2048 + g * 128);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int g = g_first; g < 4; ++g) acc[g] = __builtin_amdgcn_mfma_i32_16x16x64_i8(xf[u], wf[u][g], acc[g], 0, 0, 0);
+    }
+#pragma unroll
+    for (int g = g_first; g < 4; ++g)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        int32_t s = acc[g][v];
+        if (in.pre) {
+          asm volatile("" : "+v"(s));
+          s = rescale_preshift(s, in.rs[g]);
+        }
+        if (t0 + 4 * q + v < T) *reinterpret_cast<int16_t *>(txL + (t0 + 4 * q + v) * WAVES * 128 + g * 32 + c16 * 2) = (int16_t)rescale_sat16_pre<0>(s, in.rs[g]);
+      }
+  };
+  // (with LEAN ahead of the recurrent weights, which take the registers)
+  if (OWN && real)
+    for (int t0 = 0; t0 < T; t0 += 16) input_terms(t0);
   v4i Wf[4][KS16];  // [gate]: lane (c16, q) holds bytes 16 q.. of each 64-deep k step of cell c16's row
   v4i Wp[proj && !LEAN ? KS16 : 1];  // W_proj: the same of output 16 wave + c16
   const size_t n = (real ? wave : 0) * 16 + c16;
@@ -154,7 +208,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     return LEAN ? Rescale{v.M, 0, v.sh - 1} : Rescale{v.M, v.add, v.sh};
   };
   auto rescaled16 = [&](int32_t v, const Rescale &c, bool low_shifts, auto shift_of) {
-    if (low_shifts) {
+    if (__builtin_expect(low_shifts, 0)) {
       asm volatile("" : "+v"(v));  // a branch, not both ways and a select
       const int32_t r = shift_of();
       v = rescale_preshift(v, RescaleHi{0, 0, 0, r < 33 ? 33 - r : 0});
@@ -190,8 +244,11 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
 
   if (tid < 16) red[tid] = 0;
   // h before step 0; the other half and m start as zeros (bytes past the real ones only meet zero weights)
-  for (int i = tid; i < 3 * NC / 4; i += NT)
-    reinterpret_cast<int32_t *>(hT)[i] = i < NC / 4 && 4 * i < a.Hpad ? *reinterpret_cast<const int32_t *>(a.h0 + (size_t)row * a.Hpad + 4 * i) : 0;
+  for (int i = tid; i < 3 * NC; i += NT) {
+    int8_t v = 0;
+    if (i < H) v = !OWN ? a.h0[(size_t)row * a.Hpad + i] : in.h_src ? in.h_src[(size_t)row * H + i] : (int8_t)a.zp_h;
+    hT[i] = v;
+  }
   const int cell = wave * 16 + c16;  // this lane's cell, and its output of the projection
   int32_t creg = (a.c_in && cell < N) ? a.c_in[(size_t)row * N + cell] : 0;
   const double inv_n = 1.0 / (double)N;
@@ -216,8 +273,9 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     if (lane < 8) dma(tx_src, txL + (t & (AHEAD - 1)) * WAVES * 128);
     tx_src += t + 1 < T ? tx_ahead : 0;
   };
-  const int tx_at = ((c16 >> 3) * 4 + (gq >> 1) * 2 + ((c16 >> 2) & 1)) * 16 + ((gq & 1) * 4 + (c16 & 3)) * 2;
-  for (int s = 0; s < AHEAD && s < T; ++s) tx_request(s);
+  const int tx_at = OWN ? gq * 32 + c16 * 2 : ((c16 >> 3) * 4 + (gq >> 1) * 2 + ((c16 >> 2) & 1)) * 16 + ((gq & 1) * 4 + (c16 & 3)) * 2;
+  if (!OWN)
+    for (int s = 0; s < AHEAD && s < T; ++s) tx_request(s);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
 
@@ -261,7 +319,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
       cb = lnL[1];
       narrow = __builtin_amdgcn_readfirstlane(flag[0]) != 0;
     }
-    if (narrow) {
+    if (__builtin_expect(narrow, 1)) {
       v = ln_second_stage_narrow(v, lr, cL, cb);
     } else {
       asm volatile("" : "+v"(v));
@@ -278,7 +336,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     const uint32_t base = *reinterpret_cast<const uint16_t *>(lds + tb[1] + 2 * (ai >> tb[2]));
     const uint32_t delta = lds[tb[3] + ai];
     int32_t v = (int32_t)(base + delta);
-    if (__builtin_amdgcn_ballot_w64(mag > tb[0]) != 0) {
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(mag > tb[0]) != 0, 0)) {
       const int tail = tail_of();
       if (tail && mag > tb[0]) v = lut_wide_tail(lds + tail, mag);
     }
@@ -300,8 +358,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
 #pragma unroll
     for (int ks = 0; ks < KS16; ++ks) hf[ks] = *reinterpret_cast<const v4i *>(hcur + (q << 4) + ks * 64);
     // the terms of this step: the loads of the steps ahead are younger (and stores among them make the wait stricter)
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AHEAD - 1) : "memory");
-    const int32_t tx = *reinterpret_cast<const int16_t *>(txL + (t & (AHEAD - 1)) * WAVES * 128 + tx_at);
+    if (!OWN) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AHEAD - 1) : "memory");
+    const int32_t tx = *reinterpret_cast<const int16_t *>(txL + (OWN ? t : t & (AHEAD - 1)) * WAVES * 128 + tx_at);
     if (ln && tid < 8) red[((t + 1) & 1) * 8 + tid] = 0;  // read in the step before, added to in the next one
     int32_t acc[4];
 #pragma unroll
@@ -319,7 +377,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     v = clamp_i32(v, glo, 32767);
     if (ln) add_stats(sums + q, v, true);
     asm volatile("" ::"v"(v));  // the term has been read: its place takes the one of a later step
-    tx_request(t + AHEAD);
+    if (!OWN) tx_request(t + AHEAD);
     // layer norm, sigma / tanh (Secs. 3.2.6, 3.2.1)
     if (ln) v = normalize(sums + q, v, !(ph && q == 3));
     const int32_t act = activation(v, 0, q == 2, [&] { return q == 2 ? offT[1] : offT[0]; });
@@ -347,7 +405,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
       tc = activation(creg, 1, true, [&] { return offT[2]; });
     }
     int32_t om = mul_i24(og, tc);
-    if (pre_m) {
+    if (__builtin_expect(pre_m, 0)) {
       asm volatile("" : "+v"(om));
       om = rescale_preshift(om, pm);
     }
@@ -363,7 +421,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
                                                        LEAN ? *reinterpret_cast<const v4i *>(WpL + cell * LS + (q << 4) + ks * 64) : Wp[LEAN ? 0 : ks],
                                                        pacc, 0, 0, 0);
         int32_t sum = pacc[0] + bp;
-        if (pre_p) {
+        if (__builtin_expect(pre_p, 0)) {
           asm volatile("" : "+v"(sum));
           sum = rescale_preshift(sum, pp);
         }
@@ -380,31 +438,33 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     y += y_step;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing is on its way into LDS when the workgroup gives it back
+  if (OWN && in.h_dst)
+    for (int i = tid; i < H; i += NT) in.h_dst[(size_t)row * H + i] = hT[(T & 1) * NC + i];
   if (a.c_out && q == 0 && cell < N) a.c_out[(size_t)row * N + cell] = (int16_t)creg;
 }
 
-typedef void (*row_fn)(RecArgs2);
+typedef void (*row_fn)(RowArgs);
 
 // kernel for (flags & 15)
-template <int WAVES, int KS16>
+template <int WAVES, int KS16, bool OWN>
 row_fn row_pick_size(int fl) {
   switch (fl & 15) {
-    case 0: return row_kernel<WAVES, KS16, 0>;
-    case 1: return row_kernel<WAVES, KS16, 1>;
-    case 2: return row_kernel<WAVES, KS16, 2>;
-    case 3: return row_kernel<WAVES, KS16, 3>;
-    case 4: return row_kernel<WAVES, KS16, 4>;
-    case 5: return row_kernel<WAVES, KS16, 5>;
-    case 6: return row_kernel<WAVES, KS16, 6>;
-    case 7: return row_kernel<WAVES, KS16, 7>;
-    case 8: return row_kernel<WAVES, KS16, 8>;
-    case 9: return row_kernel<WAVES, KS16, 9>;
-    case 10: return row_kernel<WAVES, KS16, 10>;
-    case 11: return row_kernel<WAVES, KS16, 11>;
-    case 12: return row_kernel<WAVES, KS16, 12>;
-    case 13: return row_kernel<WAVES, KS16, 13>;
-    case 14: return row_kernel<WAVES, KS16, 14>;
-    default: return row_kernel<WAVES, KS16, 15>;
+    case 0: return row_kernel<WAVES, KS16, 0, OWN>;
+    case 1: return row_kernel<WAVES, KS16, 1, OWN>;
+    case 2: return row_kernel<WAVES, KS16, 2, OWN>;
+    case 3: return row_kernel<WAVES, KS16, 3, OWN>;
+    case 4: return row_kernel<WAVES, KS16, 4, OWN>;
+    case 5: return row_kernel<WAVES, KS16, 5, OWN>;
+    case 6: return row_kernel<WAVES, KS16, 6, OWN>;
+    case 7: return row_kernel<WAVES, KS16, 7, OWN>;
+    case 8: return row_kernel<WAVES, KS16, 8, OWN>;
+    case 9: return row_kernel<WAVES, KS16, 9, OWN>;
+    case 10: return row_kernel<WAVES, KS16, 10, OWN>;
+    case 11: return row_kernel<WAVES, KS16, 11, OWN>;
+    case 12: return row_kernel<WAVES, KS16, 12, OWN>;
+    case 13: return row_kernel<WAVES, KS16, 13, OWN>;
+    case 14: return row_kernel<WAVES, KS16, 14, OWN>;
+    default: return row_kernel<WAVES, KS16, 15, OWN>;
   }
 }
 

@@ -61,3 +61,26 @@ def test_two_directions(orc, B):
     xs = np.ascontiguousarray(xq[:, rows])
     assert_equal("forward", y[:, rows, :96], np.asarray(orc.forward(ofwd, xs)))
     assert_equal("backward", y[:, rows, 96:], np.asarray(orc.forward(obwd, np.ascontiguousarray(xs[::-1])))[::-1])
+
+
+@pytest.mark.parametrize("N,T", [(48, 15), (48, 16), (64, 17), (64, 33), (30, 64), (30, 65), (128, 16), (100, 31), (128, 48), (250, 16), (250, 17)])
+@pytest.mark.parametrize("I", [16, 48, 75, 208])
+def test_input_product_in_the_launch(orc, N, T, I):
+    """W x of up to 64 steps (up to 128 cells, few weights) or 16 steps in the recurrent launch: chunks of 16 steps, rows of x in
+    place and through the padded copy, depths that end within a 64-byte step; else the input GEMM."""
+    flags = (LN, 0, PH | LN | PROJ, CIFG)[(N + T + I) % 4]
+    layers, x = wl.make_custom([I, N], N, N, flags, 5, T, seed=N + T + I, weight_param=0.9 / N ** 0.5)
+    run_and_compare(orc, layers, x, f"rowin{N}t{T}i{I}", trace=False, options={"stack": 0})
+
+
+def test_input_product_counts(orc):
+    """On which side of the rule a call is, by the launches of the input GEMM."""
+    import torch
+
+    layers, x = wl.make_custom([64], 64, 64, 0, 2, 80, seed=3, weight_param=0.1)
+    model, _, xq = prepare_both(orc, layers, x)
+    for T, launches in ((1, 0), (16, 0), (32, 0), (80, 1)):
+        model.profile_begin()
+        model.forward(torch.from_numpy(np.ascontiguousarray(xq[:T])).cuda())
+        torch.cuda.synchronize()
+        assert model.profile_end()["input_gemm"]["launches"] == launches, T
