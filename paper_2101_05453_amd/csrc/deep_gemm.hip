@@ -14,11 +14,17 @@
 // piece p of row r lies at position p ^ (r % 16), which leaves the operand reads (lane = row % 32) free of bank conflicts,
 // and the lane of a global -> LDS load fetches the piece that belongs at its place.
 //
-// 16384 x 6144 x 2048: 200 us = 2.06 POP/s (the general matmul on the same box: 238), 8192 rows 99 (118), 2048 rows 32 (39),
-// 256 rows 12.5 (15).  The chip runs it at 1.9 to 1.95 GHz, what its power leaves for MFMAs with stores, as in in_gemm.hip, and
-// the MFMAs are busy 50 to 54 % of those clocks.  No single part holds the rest: without the operands' LDS reads, without the
-// barriers or without the exchange it takes the same 190 to 200 us, without the stores or without the loads of x 168.
-// Streaming stores: no difference.
+// The results leave through 8 KB of LDS.  Written straight from the lanes that hold them, a store covered 32 bytes of each of
+// 32 rows: 200 us for 16384 x 6144 x 2048 (168 without stores); four rows of 256 bytes at a time: 187.
+//
+// Under the MFMAs every instruction must find an issue slot: 64 clocks per k step, for one wave on its SIMD.  Hence the stores
+// whose bounds the buffer descriptor checks (a branch around them gathered the requantization of four pieces in one lump of 40
+// instructions), the requantization spread over two stages at S = 4, waits for the LDS writes alone, and descriptors made from
+// 32-bit row counts, one per block, between MFMAs (32 scalar instructions in front of a block's second MFMA before): 187 -> 180.
+//
+// 16384 x 6144 x 2048: 180 us = 2.29 POP/s (the general matmul on the same box: 238), 8192 rows 91 (118), 2048 rows 29.5 (39),
+// 256 rows 12 (15).  The chip runs it at 1.9 to 1.95 GHz, what its power leaves for MFMAs with stores, as in in_gemm.hip; called
+// back to back for long it takes 10 % more.  Operands read eight k steps ahead instead of four, streaming stores: no difference.
 #include <cstring>
 #include <type_traits>
 
@@ -39,17 +45,22 @@ typedef __amdgpu_buffer_rsrc_t rsrc_t;
 __device__ __forceinline__ rsrc_t make_rsrc(const int8_t *base, int bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t *>(base), 0, bytes, 0x00020000);  // raw, stride 0
 }
+__device__ __forceinline__ void rsrc_store16(rsrc_t r, v4i v, unsigned offset) {  // nothing where it lies beyond the end
+  __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)offset, 0, 0);
+}
 __device__ __forceinline__ void rsrc_load_lds16(rsrc_t r, uint8_t *dst, unsigned offset) {  // lane l: 16 bytes to dst + 16 l
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)dst, 16, (int)offset, 0, 0, 0);
 }
 #else
 typedef int rsrc_t;
 __device__ rsrc_t make_rsrc(const int8_t *, int) { return 0; }
+__device__ void rsrc_store16(rsrc_t, v4i, unsigned) {}
 __device__ void rsrc_load_lds16(rsrc_t, uint8_t *, unsigned) {}
 #endif
 
 constexpr int kStage = 16384;     // bytes of a stage
 constexpr int kExchange = 16384;  // partial sums: 4 KB per wave
+constexpr int kOutTile = 8192;    // results: 32 rows x 128 columns
 
 // S: stages per block; a half of the depth is 8 S k steps of 32.  PRE: operand treatment of the rescale (DeepGemmArgs::pre).
 template <int S, int PRE>
@@ -79,11 +90,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const int r = 2 * (4 * wave + j) + b2, p = col ^ (r & 15);
     voff[j] = (unsigned)(r * a.lda + (p >= 16 ? KH * 32 - 256 : 0) + p * 16);
   }
-  const long long bytes_total = (long long)(a.M - 1) * a.lda + a.kpad;
   auto block_rsrc = [&](int rb) {
     const int b = rb < rb1 ? rb : rb1 - 1;  // past the end: the last block again, into stages nobody reads
-    const long long at = (long long)b * 32 * a.lda, left = bytes_total - at;
-    return make_rsrc(a.A + at, (int)(left < 0x7FFFFFFF ? left : 0x7FFFFFFF));
+    const int rows = a.M - 1 - b * 32;  // a block's loads reach at most 4 KB past its rows, rows of over 1 KB
+    return make_rsrc(a.A + (long long)b * 32 * a.lda, (int)((unsigned)(rows < 63 ? rows : 63) * a.lda + a.kpad));
   };
   auto load_piece = [&](rsrc_t r, int slot, int s, int j) {
     rsrc_load_lds16(r, lds + slot * kStage + (4 * wave + j) * 1024, voff[j] + s * 256);
@@ -124,15 +134,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     bias[4 * q] = b.x; bias[4 * q + 1] = b.y; bias[4 * q + 2] = b.z; bias[4 * q + 3] = b.w;
   }
   RescaleHi rs[2];
-  bool valid[2];
-  unsigned ooff[2];
 #pragma unroll
   for (int p = 0; p < 2; ++p) {
-    const int pc = tile * 32 + 16 * p, gate = pc / a.Np, n0 = pc - gate * a.Np + 8 * b2;
+    const int gate = (tile * 32 + 16 * p) / a.Np;
     rs[p] = a.rs[gate < 3 ? gate : 3];
-    valid[p] = gate < a.G && n0 < a.N;
-    ooff[p] = ((unsigned)col * a.ldc + gate * a.N + n0) * 2;
   }
+  // Results leave through LDS, rows of 256 bytes, piece q of row r at q ^ (r % 16): a store covers four whole rows (half rows
+  // where a gate ends in the block) instead of 32 bytes of 32 rows.
+  unsigned ooff[2];
+  {
+    const int pc = cb * 128 + (lane & 15) * 8, gate = pc / a.Np, n0 = pc - gate * a.Np;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      ooff[i] = gate < a.G && n0 < a.N ? ((unsigned)(8 * wave + 4 * i + (lane >> 4)) * a.ldc + gate * a.N + n0) * 2 : 0x80000000u;
+  }
+  uint8_t *ot = lds + R * kStage + kExchange;
+  auto out_rsrc = [&](int rb) {  // block rb of the output; beyond the last row, or ahead of the first block, nothing is stored
+    const int rows = a.M - rb * 32;
+    return make_rsrc(reinterpret_cast<const int8_t *>(a.out + (long long)rb * 32 * a.ldc), rb < rb0 ? 0 : (rows < 32 ? rows : 32) * a.ldc * 2);
+  };
 
   // operand addresses within a stage
   const int x0 = col * 512 + kh * 256 + ((b2 ^ (col & 15)) << 4);
@@ -151,29 +171,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     return __builtin_bit_cast(int32_t, pk);  // both halves saturated
   };
   int32_t word[4];
-  auto piece_pair = [&](const v16i &v, int p, int rb) {  // results 2 p, 2 p + 1; four make a 16-byte piece
+  auto piece_pair = [&](const v16i &v, int p) {  // results 2 p, 2 p + 1; four make a 16-byte piece
     word[p & 3] = requant(v[2 * p], v[2 * p + 1], rs[p >> 2]);
-    if ((p & 3) == 3 && valid[p >> 2] && rb * 32 + col < a.M) {
-      uint8_t *o = reinterpret_cast<uint8_t *>(a.out + (size_t)rb * 32 * a.ldc) + ooff[p >> 2];
-      *reinterpret_cast<v4i *>(o) = v4i{word[0], word[1], word[2], word[3]};
-    }
+    if ((p & 3) == 3)
+      *reinterpret_cast<v4i *>(ot + col * 256 + (((pair * 2 + kh) * 4 + 2 * (p >> 2) + b2) ^ (col & 15)) * 16) =
+          v4i{word[0], word[1], word[2], word[3]};
+  };
+  auto store_rows = [&](int i, rsrc_t r) {
+    const int row = 8 * wave + 4 * i + (lane >> 4);
+    rsrc_store16(r, *reinterpret_cast<const v4i *>(ot + row * 256 + ((lane & 15) ^ (row & 15)) * 16), ooff[i]);
   };
 
   constexpr int DEPTH = 4;
   v4i xf[DEPTH];
   auto operand = [&](int slot, int k) { return *reinterpret_cast<const v4i *>(lds + slot * kStage + (x0 ^ (k << 5))); };
   v16i other;  // the partner's sums of this wave's tile
+  rsrc_t rx = block_rsrc(rb0 + 1), ro = out_rsrc(rb0 - 1);  // the block whose stages are being asked for, the one being stored
   // Stage s of block rb (ring position P S + s): 16 MFMAs; under them the loads of the stage 2 S - 1 later, into the place of
   // the stage just done, and, in the first three stages, what the block before still needs: its sums handed over (s = 0), the
-  // partner's read (s = 1, behind a barrier that waits for the LDS writes), requantization and stores (s = 2).
+  // partner's read (s = 1, behind a barrier that waits for the LDS writes), requantization into LDS (s = 2)
+  // (S = 4: s = 2 and 3), and in the next block's first stage the stores of the rows.
   // At the top of a stage the loads of the next one are complete: 4 (R - 3) are younger (stores among them only make the wait
   // stricter), and past the barrier that holds for every wave, so operands are read ahead across the stage's end.
-  auto stage = [&](auto p_tag, auto s_tag, auto have_tag, int rb, rsrc_t r1, rsrc_t r2, v16i (&acc)[2], v16i (&prev)[2]) {
+  auto stage = [&](auto p_tag, auto s_tag, auto have_tag, int rb, v16i (&acc)[2], v16i (&prev)[2]) {
     constexpr int P = decltype(p_tag)::value, s = decltype(s_tag)::value;
     constexpr bool HAVE = decltype(have_tag)::value;
     constexpr int slot = P * S + s, next = (slot + 1) % R, target = (slot + R - 1) % R;
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * (R - 3)) : "memory");
-    if (HAVE && s == 1) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    // this wave's LDS writes of the stage before are done; the operand reads after them may be under way
+    if (HAVE && s == 0) asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(S > 3 ? 1 : 0) : "memory");
+    if (HAVE && s == 1) asm volatile("s_waitcnt lgkmcnt(4)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 #pragma unroll
@@ -191,7 +218,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         }
       }
       xf[k % DEPTH] = k + DEPTH < 8 ? operand(slot, k + DEPTH) : operand(next, k + DEPTH - 8);
-      if (k % 2 == 0) load_piece(s == 0 ? r1 : r2, target, s == 0 ? S - 1 : s - 1, k / 2);
+      if (k % 2 == 0) load_piece(rx, target, s == 0 ? S - 1 : s - 1, k / 2);
       if (HAVE && s == 0 && k < 4)
         *reinterpret_cast<v4i *>(ex + wave * 4096 + k * 1024 + lane * 16) =
             v4i{prev[1][4 * k], prev[1][4 * k + 1], prev[1][4 * k + 2], prev[1][4 * k + 3]};
@@ -203,16 +230,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       if (HAVE && s == 1 && k >= 4)
 #pragma unroll
         for (int c = 0; c < 4; ++c) prev[0][4 * (k - 4) + c] += other[4 * (k - 4) + c];
-      if (HAVE && s == 2) piece_pair(prev[0], k, rb - 1);
+      if (HAVE && s == 2 && S == 3) piece_pair(prev[0], k);
+      if (HAVE && s >= 2 && S > 3 && k % 2 == 0) piece_pair(prev[0], 4 * (s - 2) + k / 2);
+      if (HAVE && s == 0 && k == 3) ro = out_rsrc(rb - 2);
+      if (HAVE && s == 0 && k >= 4 && k % 2 == 0) store_rows(k / 2 - 2, ro);
+      if (s == 0 && k == 7) rx = block_rsrc(rb + 2);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
   auto block = [&](auto p_tag, auto have_tag, int rb, v16i (&acc)[2], v16i (&prev)[2]) {
-    const rsrc_t r1 = block_rsrc(rb + 1), r2 = block_rsrc(rb + 2);
-    stage(p_tag, std::integral_constant<int, 0>{}, have_tag, rb, r1, r2, acc, prev);
-    stage(p_tag, std::integral_constant<int, 1>{}, have_tag, rb, r1, r2, acc, prev);
-    stage(p_tag, std::integral_constant<int, 2>{}, have_tag, rb, r1, r2, acc, prev);
-    if constexpr (S > 3) stage(p_tag, std::integral_constant<int, 3>{}, have_tag, rb, r1, r2, acc, prev);
+    stage(p_tag, std::integral_constant<int, 0>{}, have_tag, rb, acc, prev);
+    stage(p_tag, std::integral_constant<int, 1>{}, have_tag, rb, acc, prev);
+    stage(p_tag, std::integral_constant<int, 2>{}, have_tag, rb, acc, prev);
+    if constexpr (S > 3) stage(p_tag, std::integral_constant<int, 3>{}, have_tag, rb, acc, prev);
     asm volatile("" : "+v"(acc[0]), "+v"(acc[1]));
   };
   const std::integral_constant<int, 0> p0{};
@@ -231,7 +261,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   }
   // the last block's sums, after the last even block (accA) or one more odd one (accB)
   auto finish = [&](v16i (&last)[2]) {
-    __builtin_amdgcn_s_barrier();  // the exchange area's last readers are done (they waited for what they read)
+    __syncthreads();
+    const rsrc_t rp = out_rsrc(rb1 - 2);  // the rows of the block before
+    store_rows(0, rp);
+    store_rows(1, rp);
+    __syncthreads();  // the last readers of the exchange area and of the rows are done
 #pragma unroll
     for (int k = 0; k < 4; ++k)
       *reinterpret_cast<v4i *>(ex + wave * 4096 + k * 1024 + lane * 16) =
@@ -244,7 +278,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       for (int c = 0; c < 4; ++c) last[0][4 * k + c] += o[c];
     }
 #pragma unroll
-    for (int p = 0; p < 8; ++p) piece_pair(last[0], p, rb1 - 1);
+    for (int p = 0; p < 8; ++p) piece_pair(last[0], p);
+    __syncthreads();
+    const rsrc_t ro = out_rsrc(rb1 - 1);
+    store_rows(0, ro);
+    store_rows(1, ro);
   };
   if (rb < rb1) {
     block(p1, std::true_type{}, rb, accB, accA);
@@ -256,7 +294,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 
 template <int S>
 constexpr unsigned lds_bytes_s() {
-  return 2u * S * kStage + kExchange;
+  return 2u * S * kStage + kExchange + kOutTile;
 }
 
 template <int S>

@@ -828,7 +828,7 @@ int sru_int_forward(const sru_int_model *m, const int8_t *x, int32_t T, int32_t 
     ga.tx2 = reinterpret_cast<int4 *>(ws + w.tx);
     const bool ws_gemm = m->register_gemm && !tr && dv.W2f && m->num_cus == 256 && in_gemm_ws_supported(ga);
     // depths beyond 1024: the weights in registers as well (deep_gemm.hip), in any batch: 16384 rows x 6144 columns x 2048
-    // 238 -> 200 us, 256 rows 15 -> 12; 1280 columns x 1088 and less, 64 to 256 rows: the same as the general matmul
+    // 238 -> 180 us, 256 rows 15 -> 12; 1280 columns x 1088 and less, 64 to 256 rows: the same as the general matmul
     DeepGemmArgs da{};
     da.lda = d.Ip; da.M = (int)TB; da.kpad = d.Ip; da.Wd = dv.Wd; da.bias = dv.bd;
     da.G = G; da.N = N; da.out = tx; da.ldc = G * N;
