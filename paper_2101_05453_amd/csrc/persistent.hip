@@ -200,9 +200,11 @@ bool rec_supported(int N, int H, int flags, int B, int *ks, int *rt, int *groups
     if (!k && cand >= need) k = cand;
   if (!k) return false;
   const int max_groups = 8 * (32 / GS);
-  // 64 rows per group when 32 would need more than one launch; the largest
-  // register-resident slice (k = 32) leaves no room for the second row tile
-  int r = ((B + 31) / 32 > max_groups && k < 32) ? 2 : 1;
+  // 64 rows per group when 32 would need more than one launch: every wait of a step then serves both tiles.  With the largest
+  // register-resident slice (k = 32) a projection leaves no registers for the second tile (16 to 62 of them spilled).  Two
+  // launches -> one of two tiles, 60 steps: 1024 cells, 1024 rows 684 -> 685 us, with layer norm 1003 -> 851, coupled gates
+  // 752 -> 675, both 896 -> 795, layer norm and peephole 1089 -> 1017; 600 rows 0.86, 0.82, 0.79, 0.82 and 0.90 of the time.
+  int r = ((B + 31) / 32 > max_groups && (k < 32 || !(flags & 8))) ? 2 : 1;
   int g = (B + 32 * r - 1) / (32 * r);
   if (g > max_groups) g = max_groups;  // the rest of the batch goes to further launches
   *ks = k;

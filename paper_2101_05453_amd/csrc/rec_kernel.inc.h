@@ -379,14 +379,17 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   constexpr int TILE_KB = (rows_pg * LS + 1023) / 1024;
   constexpr int NCH = (TILE_KB + WAVES - 1) / WAVES;  // chunks per wave
   unsigned hsrc[NCH];
-#pragma unroll
-  for (int j = 0; j < NCH; ++j) {
+  constexpr bool HSRC_KEPT = !(RT > 1 && KS > 20);  // two tiles at the longest k have no registers for it
+  auto h_source = [&](int j, int lane) {
     const int o = (wave + WAVES * j) * 1024 + lane * 16;
     const int r = o / LS, c = o - r * LS;
     int row = row0 + r;
     row = row < a.B ? row : a.B - 1;
-    hsrc[j] = (r < rows_pg && c < a.Hpad) ? (unsigned)(row * a.Hpad + c) : 0u;
-  }
+    return (r < rows_pg && c < a.Hpad) ? (unsigned)(row * a.Hpad + c) : 0u;
+  };
+  if (HSRC_KEPT)
+#pragma unroll
+    for (int j = 0; j < NCH; ++j) hsrc[j] = h_source(j, lane);
 
   if (my_ptiles > 0 && tid < 32) bpL[tid] = a.bp2[member * 32 + tid];  // the first tile's projection bias
 
@@ -472,7 +475,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
       for (int j = 0; j < NCH; ++j)
         if (WAVES * (j + 1) <= TILE_KB || wave + WAVES * j < TILE_KB) {
-          unsigned o = hsrc[j];
+          unsigned o = HSRC_KEPT ? hsrc[j] : h_source(j, lane);
           asm volatile("" : "+v"(o));  // widened here, not kept widened
           __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(hp + o),
                                            (__attribute__((address_space(3))) void *)(hT + (wave + WAVES * j) * 1024), 16, 0, 0);
@@ -801,7 +804,27 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         narrow = __builtin_amdgcn_ballot_w64(wide) == 0;
       }
       int32_t xv[4][4], tv[4][4];
-      if ((!ln || narrow) && !tails) {
+      if constexpr (RT > 1 && KS > 20) {
+        // two tiles at the longest k: two gates at a time, which leaves the registers for the other tile's gate sums
+        auto two_gates = [&](int gmask) {
+          if ((!ln || narrow) && !tails) {
+            normalize(rt, gmask, lr, xv, true, std::false_type{});
+            lookup(gmask, xv, gate_tb, tv, std::false_type{});
+          } else {
+            asm volatile("");
+            if (narrow) {
+              normalize(rt, gmask, lr, xv, true, std::true_type{});
+            } else {
+              asm volatile("");
+              normalize(rt, gmask, lr, xv, false, std::true_type{});
+            }
+            lookup(gmask, xv, gate_tb, tv, std::true_type{});
+          }
+        };
+        two_gates(gates_now & 3);
+        __builtin_amdgcn_sched_barrier(0);
+        two_gates(gates_now & 12);
+      } else if ((!ln || narrow) && !tails) {
         normalize(rt, gates_now, lr, xv, true, std::false_type{});
         lookup(gates_now, xv, gate_tb, tv, std::false_type{});
       } else {
@@ -1064,9 +1087,9 @@ rec_fn rec_pick_ks(int rt, int fl) {
   if constexpr (KS < 32) {
     LSTM_REC_CASE(2, 0) LSTM_REC_CASE(2, 1) LSTM_REC_CASE(2, 2) LSTM_REC_CASE(2, 3)
     LSTM_REC_CASE(2, 4) LSTM_REC_CASE(2, 5) LSTM_REC_CASE(2, 6) LSTM_REC_CASE(2, 7)
-    LSTM_REC_CASE(2, 8) LSTM_REC_CASE(2, 9) LSTM_REC_CASE(2, 10) LSTM_REC_CASE(2, 11)
-    LSTM_REC_CASE(2, 12) LSTM_REC_CASE(2, 13) LSTM_REC_CASE(2, 14) LSTM_REC_CASE(2, 15)
   }
+  LSTM_REC_CASE(2, 8) LSTM_REC_CASE(2, 9) LSTM_REC_CASE(2, 10) LSTM_REC_CASE(2, 11)
+  LSTM_REC_CASE(2, 12) LSTM_REC_CASE(2, 13) LSTM_REC_CASE(2, 14) LSTM_REC_CASE(2, 15)
 #undef LSTM_REC_CASE
   return nullptr;
 }

@@ -29,6 +29,17 @@ def test_division_over_the_waves(orc, N, H, flags, B, T):
     run_and_compare(orc, layers, x, f"waves{N}h{H}", trace=False, rows=rows, options={"rows16": 0})
 
 
+@pytest.mark.parametrize("flags", [0, CIFG, PH, CIFG | PH, LN, LN | CIFG, LN | PH, LN | PH | CIFG])
+@pytest.mark.parametrize("N,B,rows", [
+    (1024, 513, [0, 31, 32, 63, 64, 511, 512]),             # a last group of one row: its second tile is empty
+    (650, 1090, [0, 63, 545, 575, 576, 1023, 1024, 1089]),  # a second launch, whose last tile is ragged
+])
+def test_two_row_tiles_at_the_deepest_k(orc, N, B, rows, flags):
+    """Groups of 64 rows where R h is 1024 deep: every form without a projection."""
+    layers, x = wl.make_custom([24], N, N, flags, B, 3, seed=N + B + flags, weight_param=0.9 / N ** 0.5)
+    run_and_compare(orc, layers, x, f"two{N}b{B}f{flags}", trace=False, rows=rows, options={"rows16": 0})
+
+
 @pytest.mark.parametrize("N,H,flags,B,T", [
     (72, 9, PROJ, 5, 4),                    # two k steps of 64: most waves have none
     (300, 131, PROJ | LN, 20, 4),           # five k steps; odd outputs
