@@ -35,6 +35,19 @@ def test_edges_of_the_persistent_kernels(gru, inputs, N, B, T):  # noqa: F811
     run_both_paths(gru, layers, x, f"gru{inputs}x{N}b{B}", rows=rows, splits=[(0, 1), (1, T)])
 
 
+@pytest.mark.parametrize("inputs,N,B,T", [
+    ([20], 64, 1030, 7),          # 16 rows, one workgroup per group; the second half of the depth is empty
+    ([20], 64, 4100, 7),          # 32 rows of the same, the last group of four rows
+    ([20], 130, 1300, 8),         # the input terms of four turns and more through three places
+    ([20], 520, 500, 7),          # nine k steps: eight and one
+    ([20, 1203], 1203, 150, 7),   # row-major input terms
+])
+def test_halves_of_the_depth_and_turns_of_the_tiles(gru, inputs, N, B, T):  # noqa: F811
+    layers, x = wl.make_gru(inputs, N, B, T, seed=N + B, weight_param=0.9 / N ** 0.5, input_param=1.5)
+    rows = sorted({0, 15, 16, 31, 32, B // 2, B - 3, B - 1})
+    run_both_paths(gru, layers, x, f"halves{inputs}x{N}b{B}", rows=rows)
+
+
 @pytest.mark.parametrize("B", [40, 1100])
 def test_waits_give_up_and_the_model_recovers(gru, B):  # noqa: F811
     """Both exchanges: with the test hook a wait ends at its limit and the status word says so."""
