@@ -269,7 +269,8 @@ bool rec_extents_ok(const RecArgs &ra, const Workspace &ws, int T_all, int t0, b
   if (has_proj && (size_t)ra.T * Bp * ra.npadp > ws.m2_bytes) return false;
   // counters [groups][64] words and statistics accumulators [groups][4][256] 64-bit words
   if (solo) return true;
-  if ((size_t)ra.groups * 64 * 4 > (size_t)256 * 64 * 4 || (size_t)ra.groups * kStatGroupBytes > (size_t)256 * kStatGroupBytes)
+  const size_t group_bytes = kStatGroupBytes + (ra.flags & kTaggedState ? (size_t)tagged_group_words(ra.H) * 8 : 0);
+  if ((size_t)ra.groups * 64 * 4 > (size_t)256 * 64 * 4 || (size_t)ra.groups * group_bytes > (size_t)256 * kStatGroupBytes)
     return false;
   return true;
 }
@@ -931,6 +932,10 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1) {
     RecArgs r16 = ra;
     r16.R2h = d.R2h; r16.ks16 = d.ks16; r16.rows_pg = 16; r16.groups = g16;
     r16.Wp2 = d.Wp2; r16.bp2 = d.bp2; r16.ptiles = d.ptiles; r16.prow = 32;
+    // the exchange words share the region of the statistics words with all groups of the launch
+    r16.flags &= ~kFourPredSlots;
+    if (d.GS > 1 && (int64_t)256 * 64 * 4 + (int64_t)g16 * share * (kStatGroupBytes + tagged_group_words(h.H) * 8) <= (int64_t)kSyncBytes)
+      r16.flags |= kTaggedState;
     if (rec16_lds_bytes(r16) <= 160 * 1024) {
       ra = r16;
       p2_groups = g16;
@@ -1084,7 +1089,9 @@ void set_sync(RecArgs &ra, const lstm_int_model *m, uint8_t *sync) {
 int64_t sync_bytes(int groups) { return (int64_t)256 * 64 * 4 + (int64_t)groups * (int64_t)kStatGroupBytes; }
 // ... as the plan's kernel uses it (the four-row kernel's exchange words lie where the statistics words are)
 int64_t sync_bytes(const RecPlan &p, int groups) {
-  return p.solo ? 0 : p.quad ? (int64_t)256 * 64 * 4 + (int64_t)groups * p.ra.GS * kQuadWgBytes : sync_bytes(groups);
+  return p.solo ? 0
+         : p.quad ? (int64_t)256 * 64 * 4 + (int64_t)groups * p.ra.GS * kQuadWgBytes
+                  : sync_bytes(groups) + (p.ra.flags & kTaggedState ? (int64_t)groups * tagged_group_words(p.ra.H) * 8 : 0);
 }
 
 // The hoisted W x of layer l (its output goes to ga.tx2, in the tile order of the recurrent kernels).

@@ -132,10 +132,15 @@ __host__ __device__ inline bool stat_two_sets(int GS) { return GS >= 16; }
 // rec_kernel: the eight waves' partial sums of the projection go through four slots of LDS instead of eight, two waves to a
 // slot one after the other (where W_proj and the tables leave no room for eight: 1024 cells with 640 outputs)
 constexpr int kFourPredSlots = 256;
+// rec16_kernel: the hidden state travels as (value, tag) byte pairs, behind the statistics words of the group: two slots of 16
+// rows of H cells rounded up to 8
+constexpr int kTaggedState = 512;
+__host__ __device__ inline int tagged_row(int H) { return (H + 7) & ~7; }
+__host__ __device__ inline int tagged_group_words(int H) { return tagged_row(H) * 8; }  // 64-bit words of a group, both slots
 
 struct RecArgs {
   int T, B, N, H, Hpad;
-  int flags;      // the layer's; rec_kernel: | kFourPredSlots
+  int flags;      // the layer's; rec_kernel: | kFourPredSlots; rec16_kernel: | kTaggedState
   int m_c;
   int GS;         // workgroups (compute units) per group = cells / 64
   int groups;     // groups in this launch, each owns rows_pg batch rows

@@ -11,11 +11,19 @@
 // the wave's tile c in that lane is (cell 4 q + 2 s + c, gate).  The W x terms are
 // read in the layout the input GEMM writes for the 32-row kernel.
 //
+// The hidden state travels as (value, tag) byte pairs, the tag being the step (kTaggedState, quad_kernel.inc.h has more on it):
+// 16 bytes a thread hold eight cells, and who needs them polls them, up to four loads a thread.  Through the layer output, the
+// group's counter and a load of the tile behind it (the way m still goes, 64 KB as pairs for each workgroup with outputs), 200
+// steps (us): 1024 cells, 128 rows 763 -> 628, layer norm 1125 -> 1017; 512 cells, 200 rows 630 -> 501, layer norm 969 -> 862; two
+// directions of 512 cells, 100 rows, 100 steps 356 -> 272; 2048 cells, 640 outputs, layer norm, peephole, 128 rows 1897 -> 1833.
+// The counter remains where one workgroup is the group, and where the words of all groups find no room.
+//
 // What bounds it: the exchanges of a step (two, one without a projection, and one
-// per round of statistics, 0.9 to 1.2 us each) and the instructions between them.
+// per round of statistics, 0.6 to 1.2 us each) and the instructions between them.
 // Two waves per SIMD issue those in less time than one of twice the work: 128 rows
 // of 2048 cells, projection to 640: 6.3 -> 5.9 us a step, with layer norm 8.3 -> 8.1,
-// and peephole 9.4 -> 9.2; 512 cells, 200 rows 3.1 -> 2.9, with layer norm 4.8 -> 4.6.
+// and peephole 9.4 -> 9.2; 512 cells, 200 rows 3.1 -> 2.9, with layer norm 4.8 -> 4.6
+// (before the tagged words).
 #pragma once
 
 #include "rec_kernel.inc.h"
@@ -270,7 +278,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   unsigned epoch = 0;
   unsigned *counter = a.counters + gl * 64;
   // one set of words: two sets (as in rec_kernel) made this kernel 2-3 % slower, at 8 and at 32 workgroups per group
-  u64 *accS = a.acc + (size_t)gl * kStatGroupWords;  // [round][S1|S2][item], item < 64
+  const bool tagged = a.flags & kTaggedState;
+  const int Hr = tagged_row(a.H);                    // cells of a row of the exchange
+  u64 *accS = a.acc + (size_t)gl * (kStatGroupWords + (tagged ? tagged_group_words(a.H) : 0));  // [round][S1|S2][item], item < 64
+  u64 *const xh = accS + kStatGroupWords;            // [2 slots][16 rows][Hr] (value, tag)
+  const unsigned never = a.extra_arrivals ? 0x80u : 0;  // tests: a tag nobody stores in so few steps
   int64_t prevS[2][2] = {{0, 0}, {0, 0}};       // this thread's item, per round: S1, S2
   const double inv_n = 1.0 / (double)a.N;
   const bool pre_ln = a.rln[0] < 33 || a.rln[1] < 33 || a.rln[2] < 33 || a.rln[3] < 33;
@@ -303,6 +315,78 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   };
   tx_request(0);
 
+  // The state of a step in words of (value, tag) pairs, the tag being the step: a thread polls the pieces of eight cells it
+  // needs until all carry the tag, U of them at a time, and puts them into the tile.  No acknowledgement, no counter, no load
+  // after the barrier.
+  const int row_pieces = Hr >> 3;
+  auto poll_state = [&](auto count, int t) {
+    constexpr int U = decltype(count)::value;
+    const uint32_t want = (((unsigned)t + 1) & 0xFF ^ never) * 0x01000100u;
+    const u64 *src = xh + (size_t)(t & 1) * Hr * 4;
+    unsigned at[U];
+    v4i w[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) at[k] = k * 512 + tid < 16 * row_pieces ? (unsigned)(k * 512 + tid) * 16 : 0;
+    int budget = a.spin_limit;
+    for (;;) {
+      poll_pairs(src, at, w);
+      uint32_t off = 0;
+#pragma unroll
+      for (int k = 0; k < U; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) off |= (uint32_t)w[k][i] ^ want;
+      if (__builtin_amdgcn_ballot_w64((off & 0xFF00FF00u) != 0) == 0) break;
+      --budget;
+      if ((budget & 15) == 0 && (budget <= 0 || __hip_atomic_load(a.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
+        __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        flag[0] = 0;
+        break;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const int c = k * 512 + tid;
+      if (c < 16 * row_pieces) {
+        const int rr = c / row_pieces;
+        *reinterpret_cast<v2i *>(hT + rr * LS + 8 * (c - rr * row_pieces)) =
+            v2i{(int)__builtin_amdgcn_perm((uint32_t)w[k][1], (uint32_t)w[k][0], 0x06040200u),
+                (int)__builtin_amdgcn_perm((uint32_t)w[k][3], (uint32_t)w[k][2], 0x06040200u)};
+      }
+    }
+  };
+  // Tagged state: the layer output of step t, which nobody waits for, behind the polls of the next step
+  uint32_t hkeep = 0;
+  auto store_output = [&](int t) {
+    if (proj) {
+      const int p0 = member * 32 + 16 * wave + 4 * q;
+      if (my_ptiles > 0 && wave < 2 && row < a.B && p0 < a.H) {
+        const size_t orow = (size_t)time_of(t) * a.B + row;
+        int8_t *od = a.out + orow * a.Hpad + p0;
+        if (p0 + 3 < a.H) {
+          *reinterpret_cast<uint32_t *>(od) = hkeep;
+        } else {
+          for (int c = 0; c < 4 && p0 + c < a.H; ++c) od[c] = (int8_t)(hkeep >> (8 * c));
+        }
+        if (a.y) {
+          int8_t *yd = a.y + orow * ldy + p0;
+          for (int c = 0; c < 4 && p0 + c < a.H; ++c) yd[c] = (int8_t)(hkeep >> (8 * c));
+        }
+      }
+    } else if (GATHER && wave == 1) {
+      const int srow = row0 + (lane >> 2), n = member * 64 + 16 * (lane & 3);
+      const v4i piece = *reinterpret_cast<const v4i *>(mS + piece_at(lane >> 2, lane & 3));
+      if (srow < a.B && n < a.N) {
+        const size_t orow = (size_t)time_of(t) * a.B + srow;
+        *reinterpret_cast<v4i *>(a.out + orow * a.Hpad + n) = piece;
+        if (a.y) {  // N a multiple of four, y of four bytes
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+            if (n + 4 * k < a.N) __builtin_nontemporal_store(piece[k], reinterpret_cast<int32_t *>(a.y + orow * ldy + n + 4 * k));
+        }
+      }
+    }
+  };
+
   for (int t = 0; t < a.T; ++t) {
     if (KS16 > 10) {  // half of the registers are weights: what follows from the lane is worked out in every step
       asm volatile("" : "+v"(lane));
@@ -313,7 +397,18 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       n0 = member * 64 + cellw;
     }
     // ---- h^{t-1} rows of the group -> LDS
-    {
+    if (tagged && t > 0) {
+      // pieces of this wave: a wave without any does not poll, its loads would cost as much as the others'
+      const int mine = (16 * row_pieces - wave * 64 + 511) >> 9;
+      if (mine >= 4)
+        poll_state(std::integral_constant<int, 4>{}, t - 1);
+      else if (mine == 3)
+        poll_state(std::integral_constant<int, 3>{}, t - 1);
+      else if (mine == 2)
+        poll_state(std::integral_constant<int, 2>{}, t - 1);
+      else if (mine == 1)
+        poll_state(std::integral_constant<int, 1>{}, t - 1);
+    } else {
       const int8_t *hp = t == 0 ? a.h0 : a.out + (size_t)time_of(t - 1) * a.B * a.Hpad;
 #pragma unroll
       for (int j = 0; j < NCH; ++j)
@@ -324,6 +419,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
     __syncthreads();
+    if (tagged && t > 0) {
+      if (flag[0] == 0) return;
+      store_output(t - 1);
+    }
     // the W x terms of this step were requested one step ahead (they come from HBM)
     const int32_t txw[4] = {txn[0], txn[1], txn[2], txn[3]};
     TICK(0);
@@ -633,17 +732,24 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       }
       if constexpr (GATHER) {
         *reinterpret_cast<uint16_t *>(mS + piece_at(r, cellw >> 4) + (cellw & 15)) = (uint16_t)pk;
-      } else if (row < a.B && n0 < a.N) {
-        if (proj) {
-          // exchange buffer [t][row / 16][k step of 64 cells = member][row % 16][64 cells]: a wave's
-          // load of one projection k step is one contiguous KB
-          int8_t *mdst = a.mbuf + (size_t)t * a.Bp * a.npadp +
-                         ((((size_t)(row >> 4) * (a.npadp >> 6) + member) * 16 + (row & 15)) << 6) + cellw;
-          *reinterpret_cast<uint16_t *>(mdst) = (uint16_t)pk;
-        } else {
-          const size_t orow = (size_t)time_of(t) * a.B + row;
-          *reinterpret_cast<uint16_t *>(a.out + orow * a.Hpad + n0) = (uint16_t)pk;
-          if (a.y) __builtin_nontemporal_store((uint16_t)pk, reinterpret_cast<uint16_t *>(a.y + orow * ldy + n0));
+      } else {
+        if (tagged && !proj && n0 < Hr) {
+          const uint32_t tag = ((unsigned)t + 1) & 0xFF;
+          *reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(xh + (size_t)(t & 1) * Hr * 4) + (r * Hr + n0) * 2) =
+              __builtin_amdgcn_perm(pk, tag, 0x00050004u);
+        }
+        if (row < a.B && n0 < a.N) {
+          if (proj) {
+            // exchange buffer [t][row / 16][k step of 64 cells = member][row % 16][64 cells]: a wave's
+            // load of one projection k step is one contiguous KB
+            int8_t *mdst = a.mbuf + (size_t)t * a.Bp * a.npadp +
+                           ((((size_t)(row >> 4) * (a.npadp >> 6) + member) * 16 + (row & 15)) << 6) + cellw;
+            *reinterpret_cast<uint16_t *>(mdst) = (uint16_t)pk;
+          } else {
+            const size_t orow = (size_t)time_of(t) * a.B + row;
+            *reinterpret_cast<uint16_t *>(a.out + orow * a.Hpad + n0) = (uint16_t)pk;
+            if (a.y) __builtin_nontemporal_store((uint16_t)pk, reinterpret_cast<uint16_t *>(a.y + orow * ldy + n0));
+          }
         }
       }
     }
@@ -654,7 +760,18 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         // meet zero weights
         const int srow = row0 + (lane >> 2), n = member * 64 + 16 * (lane & 3);
         const v4i piece = *reinterpret_cast<const v4i *>(mS + piece_at(lane >> 2, lane & 3));
-        if (srow < a.B && n < a.N) {
+        if (tagged && !proj) {
+          const uint32_t tag = ((unsigned)t + 1) & 0xFF;
+          uint8_t *dst = reinterpret_cast<uint8_t *>(xh + (size_t)(t & 1) * Hr * 4) + ((lane >> 2) * Hr + n) * 2;
+#pragma unroll
+          for (int k = 0; k < 2; ++k)
+            if (n + 8 * k < Hr) {
+              v4i w;
+#pragma unroll
+              for (int i = 0; i < 4; ++i) w[i] = (int)__builtin_amdgcn_perm((uint32_t)piece[2 * k + (i >> 1)], tag, i & 1 ? 0x00070006u : 0x00050004u);
+              *reinterpret_cast<v4i *>(dst + 16 * k) = w;
+            }
+        } else if (srow < a.B && n < a.N) {
           if (proj) {  // the same exchange buffer
             *reinterpret_cast<v4i *>(a.mbuf + (size_t)t * a.Bp * a.npadp +
                                      (((size_t)(srow >> 4) * (a.npadp >> 6) + member) << 10) + lane * 16) = piece;
@@ -671,7 +788,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       }
     }
     TICK(6);
-    if (!group_sync(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, a.sync_sleep, a.poll_sleep, flag)) return;
+    if ((proj || !tagged) && !group_sync(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, a.sync_sleep, a.poll_sleep, flag)) return;
     TICK(7);
 
     // ---- projection (Sec. 3.2.8): tile pt of 32 outputs as two 16-wide halves, K = N split over the waves
@@ -723,7 +840,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             const int32_t hq = sat8(rescale_sat16_pre(s, pp) + zp_h);
             pk |= (uint32_t)(hq & 0xFF) << (8 * v);
           }
-          if (row < a.B && p0 < a.H) {
+          if (tagged && p0 < Hr) {
+            const uint32_t tag = ((unsigned)t + 1) & 0xFF;
+            *reinterpret_cast<v2i *>(reinterpret_cast<uint8_t *>(xh + (size_t)(t & 1) * Hr * 4) + (r * Hr + p0) * 2) =
+                v2i{(int)__builtin_amdgcn_perm(pk, tag, 0x00050004u), (int)__builtin_amdgcn_perm(pk, tag, 0x00070006u)};
+          }
+          if (tagged && pt == 0) {
+            hkeep = pk;
+          } else if (row < a.B && p0 < a.H) {
             const size_t orow = (size_t)time_of(t) * a.B + row;
             int8_t *od = a.out + orow * a.Hpad + p0;
             if (p0 + 3 < a.H) {
@@ -740,12 +864,17 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         __syncthreads();
       }
       TICK(8);
-      if (!group_sync(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, my_ptiles == 0 ? a.idle_sleep : 0,
-                      my_ptiles == 0 ? a.idle_poll_sleep : a.poll_sleep, flag))
+      if (tagged) {
+        if (my_ptiles == 0)
+          for (int i = 0; i < a.idle_sleep; ++i) __builtin_amdgcn_s_sleep(1);
+      } else if (!group_sync(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, my_ptiles == 0 ? a.idle_sleep : 0,
+                             my_ptiles == 0 ? a.idle_poll_sleep : a.poll_sleep, flag)) {
         return;
+      }
       TICK(9);
     }
   }
+  if (tagged) store_output(a.T - 1);
   if (timing)
     for (int i = 0; i < 11; ++i) a.ticks[i] += (long long)tickL[i];
   if (a.ticks && tid == 0) {

@@ -93,6 +93,13 @@ __device__ __forceinline__ void poll_pairs(const u64 *base, const unsigned (&at)
                : "v"(at[0]), "v"(at[1]), "s"(base)
                : "memory");
 }
+__device__ __forceinline__ void poll_pairs(const u64 *base, const unsigned (&at)[3], v4i (&w)[3]) {
+  asm volatile("global_load_dwordx4 %0, %3, %6 sc1\n\tglobal_load_dwordx4 %1, %4, %6 sc1\n\t"
+               "global_load_dwordx4 %2, %5, %6 sc1\n\ts_waitcnt vmcnt(0)"
+               : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2])
+               : "v"(at[0]), "v"(at[1]), "v"(at[2]), "s"(base)
+               : "memory");
+}
 __device__ __forceinline__ void poll_pairs(const u64 *base, const unsigned (&at)[4], v4i (&w)[4]) {
   asm volatile("global_load_dwordx4 %0, %4, %8 sc1\n\tglobal_load_dwordx4 %1, %5, %8 sc1\n\t"
                "global_load_dwordx4 %2, %6, %8 sc1\n\tglobal_load_dwordx4 %3, %7, %8 sc1\n\ts_waitcnt vmcnt(0)"

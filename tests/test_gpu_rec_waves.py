@@ -58,6 +58,22 @@ def test_division_over_the_waves_of_16_rows(orc, N, H, flags, B, T):
     run_and_compare(orc, layers, x, f"rows16_{N}h{H}", trace=False, options={"rows16": 2})
 
 
+@pytest.mark.parametrize("N,H,flags,B,T", [
+    (130, 130, 0, 20, 300),                  # the tags wrap at 256 steps; a last piece of eight cells with two
+    (203, 203, LN, 21, 4),                   # rows of 208: the 16 cells of a lane end half way
+    (332, 332, LN | PH, 33, 4),              # pairs straight from the lanes that make them
+    (1024, 1024, CIFG, 128, 4),              # four pieces a thread, every compute unit
+    (1100, 33, PROJ | PH, 17, 4),            # fewer pieces than threads: waves without any
+    (700, 640, PROJ | LN, 40, 4),            # two and a half pieces a thread, two output tiles of some workgroups
+    (128, 1000, PROJ | LN, 900, 3),          # no room for the words of so many groups: the counter
+    (64, 64, LN, 20, 4),                     # one workgroup: nothing to exchange
+])
+def test_state_in_tagged_words(orc, N, H, flags, B, T):
+    layers, x = wl.make_custom([40], N, H, flags, B, T, seed=N + H + T, weight_param=0.9 / N ** 0.5)
+    rows = None if B <= 40 else [0, 15, 16, 17, B // 2, B - 1]
+    run_and_compare(orc, layers, x, f"tags{N}h{H}", trace=False, rows=rows, options={"rows16": 2})
+
+
 @pytest.mark.parametrize("N,H,flags", [
     (320, 320, 0), (320, 320, LN | PH),  # the tables whole in LDS
     (1024, 640, LN | PROJ),              # W_proj leaves no room for that: lookups beyond the prefix
