@@ -49,7 +49,7 @@ bool rec16_supported(int N, int H, int flags, int B, int *ks16, int *groups) {
 size_t rec16_lds_bytes(const RecArgs &a) {
   const int items = 64;
   const bool proj = a.flags & 8;
-  size_t tile = (((size_t)16 * (a.ks16 * 64 + 16) + 1023) / 1024 + 1) * 1024;
+  size_t tile = (((size_t)16 * (a.ks16 * 64 + 16) + 1023) / 1024 + 1) * 1024 + (a.flags & (4 | 8) ? 0 : 1024);
   if (proj && tile < 8 * 2 * 64 * 16) tile = 8 * 2 * 64 * 16;
   size_t n = tile + (size_t)items * 8 + (size_t)items * sizeof(LnRow2) + 2 * 4 * 64 * 8 + 4 * 64 * 4 + 4 * 64 * 2 +
              256 /* PrmLds */ + 16 + 16 * 8 + 3 * 32 /* LutLds */;

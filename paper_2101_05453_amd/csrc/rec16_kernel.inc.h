@@ -118,12 +118,15 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   uint8_t *p = lds;
   int8_t *hT = reinterpret_cast<int8_t *>(p);
   // hidden state of the step on its way out, where the loads past the h tile go, which nobody reads: 16-byte pieces of row r
-  // at r * 64, exchanged by r / 4 so that rows in the same banks differ
-  int8_t *const mS = reinterpret_cast<int8_t *>(lds) + TILE_KB * 1024;
+  // at r * 64, exchanged by r / 4 so that rows in the same banks differ.  With neither layer norm nor a projection two of them by
+  // turns: no barrier lies between the barrier behind which wave 1 reads it once more (store_output) and the next hidden state.
+  const int mflip = ln || proj ? 0 : 1024;
+  int8_t *const mS0 = reinterpret_cast<int8_t *>(lds) + TILE_KB * 1024;
+  auto mS_of = [&](int t) { return mS0 + (t & 1) * mflip; };
   auto piece_at = [](int row, int piece) { return row * 64 + ((piece ^ (row >> 2)) << 4); };
   v4i *pred = reinterpret_cast<v4i *>(p);  // projection partials [8 waves][2 halves][64 lanes] reuse the h tile between steps
   {
-    const size_t tile_bytes = (size_t)(TILE_KB + 1) * 1024;  // one spare chunk for the loads past the tile
+    const size_t tile_bytes = (size_t)(TILE_KB + 1) * 1024 + mflip;  // one spare chunk for the loads past the tile
     const size_t pred_bytes = proj ? 8 * 2 * 64 * 16 : 0;
     p += tile_bytes > pred_bytes ? tile_bytes : pred_bytes;
   }
@@ -374,7 +377,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       }
     } else if (GATHER && wave == 1) {
       const int srow = row0 + (lane >> 2), n = member * 64 + 16 * (lane & 3);
-      const v4i piece = *reinterpret_cast<const v4i *>(mS + piece_at(lane >> 2, lane & 3));
+      const v4i piece = *reinterpret_cast<const v4i *>(mS_of(t) + piece_at(lane >> 2, lane & 3));
       if (srow < a.B && n < a.N) {
         const size_t orow = (size_t)time_of(t) * a.B + srow;
         *reinterpret_cast<v4i *>(a.out + orow * a.Hpad + n) = piece;
@@ -731,7 +734,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         pk |= (uint32_t)(mq & 0xFF) << (8 * c);
       }
       if constexpr (GATHER) {
-        *reinterpret_cast<uint16_t *>(mS + piece_at(r, cellw >> 4) + (cellw & 15)) = (uint16_t)pk;
+        *reinterpret_cast<uint16_t *>(mS_of(t) + piece_at(r, cellw >> 4) + (cellw & 15)) = (uint16_t)pk;
       } else {
         if (tagged && !proj && n0 < Hr) {
           const uint32_t tag = ((unsigned)t + 1) & 0xFF;
@@ -759,7 +762,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         // the group's rows of these 64 cells in one store of 16 bytes a lane; cells past the last are written too, they
         // meet zero weights
         const int srow = row0 + (lane >> 2), n = member * 64 + 16 * (lane & 3);
-        const v4i piece = *reinterpret_cast<const v4i *>(mS + piece_at(lane >> 2, lane & 3));
+        const v4i piece = *reinterpret_cast<const v4i *>(mS_of(t) + piece_at(lane >> 2, lane & 3));
         if (tagged && !proj) {
           const uint32_t tag = ((unsigned)t + 1) & 0xFF;
           uint8_t *dst = reinterpret_cast<uint8_t *>(xh + (size_t)(t & 1) * Hr * 4) + ((lane >> 2) * Hr + n) * 2;
