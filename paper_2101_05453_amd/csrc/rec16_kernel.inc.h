@@ -14,7 +14,7 @@
 // The hidden state travels as (value, tag) byte pairs, the tag being the step (kTaggedState, quad_kernel.inc.h has more on it):
 // 16 bytes a thread hold eight cells, and who needs them polls them, up to four loads a thread.  Through the layer output, the
 // group's counter and a load of the tile behind it (the way m still goes, 64 KB as pairs for each workgroup with outputs), 200
-// steps (us): 1024 cells, 128 rows 763 -> 628, layer norm 1125 -> 1017; 512 cells, 200 rows 630 -> 501, layer norm 969 -> 862; two
+// steps (us): 1024 cells, 128 rows 763 -> 616, layer norm 1125 -> 955; 512 cells, 200 rows 630 -> 519, layer norm 969 -> 855; two
 // directions of 512 cells, 100 rows, 100 steps 356 -> 272; 2048 cells, 640 outputs, layer norm, peephole, 128 rows 1897 -> 1833.
 // The counter remains where one workgroup is the group, and where the words of all groups find no room.
 //
