@@ -269,7 +269,7 @@ bool rec_extents_ok(const RecArgs &ra, const Workspace &ws, int T_all, int t0, b
   if (has_proj && (size_t)ra.T * Bp * ra.npadp > ws.m2_bytes) return false;
   // counters [groups][64] words and statistics accumulators [groups][4][256] 64-bit words
   if (solo) return true;
-  const size_t group_bytes = kStatGroupBytes + (ra.flags & kTaggedState ? (size_t)tagged_group_words(ra.H) * 8 : 0);
+  const size_t group_bytes = kStatGroupBytes + (ra.flags & kTaggedState ? (size_t)tagged_group_words(ra.H, ra.rows_pg) * 8 : 0);
   if ((size_t)ra.groups * 64 * 4 > (size_t)256 * 64 * 4 || (size_t)ra.groups * group_bytes > (size_t)256 * kStatGroupBytes)
     return false;
   return true;
@@ -835,6 +835,7 @@ struct RecPlan {
   bool solo = false, row = false, quad = false;
 };
 
+int64_t sync_bytes(int groups);
 // share: launches' worth of groups that are to fit one launch (2: both directions of a bidirectional layer)
 RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1) {
   const LayerHost &h = m->host[l];
@@ -934,7 +935,7 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1) {
     r16.Wp2 = d.Wp2; r16.bp2 = d.bp2; r16.ptiles = d.ptiles; r16.prow = 32;
     // the exchange words share the region of the statistics words with all groups of the launch
     r16.flags &= ~kFourPredSlots;
-    if (d.GS > 1 && (int64_t)256 * 64 * 4 + (int64_t)g16 * share * (kStatGroupBytes + tagged_group_words(h.H) * 8) <= (int64_t)kSyncBytes)
+    if (d.GS > 1 && (int64_t)256 * 64 * 4 + (int64_t)g16 * share * (kStatGroupBytes + tagged_group_words(h.H, 16) * 8) <= (int64_t)kSyncBytes)
       r16.flags |= kTaggedState;
     if (rec16_lds_bytes(r16) <= 160 * 1024) {
       ra = r16;
@@ -976,6 +977,9 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1) {
     if (m->sync_sleep < 0 && d.GS >= 16) ra.sync_sleep = 8;
     ra.flags &= ~kFourPredSlots;
     if (lds_need() > 160 * 1024) ra.flags |= kFourPredSlots;
+    // one tile of outputs per workgroup, whole pieces of eight of them, and room behind the statistics words of all groups
+    if (rec_tagged(ra) && sync_bytes(p2_groups) + (int64_t)p2_groups * tagged_group_words(h.H, 32) * 8 <= (int64_t)kSyncBytes)
+      ra.flags |= kTaggedState;
   }
   p.groups = p2_groups;
   p.ok = true;
@@ -1091,7 +1095,7 @@ int64_t sync_bytes(int groups) { return (int64_t)256 * 64 * 4 + (int64_t)groups 
 int64_t sync_bytes(const RecPlan &p, int groups) {
   return p.solo ? 0
          : p.quad ? (int64_t)256 * 64 * 4 + (int64_t)groups * p.ra.GS * kQuadWgBytes
-                  : sync_bytes(groups) + (p.ra.flags & kTaggedState ? (int64_t)groups * tagged_group_words(p.ra.H) * 8 : 0);
+                  : sync_bytes(groups) + (p.ra.flags & kTaggedState ? (int64_t)groups * tagged_group_words(p.ra.H, p.ra.rows_pg) * 8 : 0);
 }
 
 // The hoisted W x of layer l (its output goes to ga.tx2, in the tile order of the recurrent kernels).

@@ -132,15 +132,15 @@ __host__ __device__ inline bool stat_two_sets(int GS) { return GS >= 16; }
 // rec_kernel: the eight waves' partial sums of the projection go through four slots of LDS instead of eight, two waves to a
 // slot one after the other (where W_proj and the tables leave no room for eight: 1024 cells with 640 outputs)
 constexpr int kFourPredSlots = 256;
-// rec16_kernel: the hidden state travels as (value, tag) byte pairs, behind the statistics words of the group: two slots of 16
-// rows of H cells rounded up to 8
+// rec16_kernel, rec_kernel: the hidden state travels as (value, tag) byte pairs, behind the statistics words of the group: two
+// slots of the group's rows (16, 32) of H cells rounded up to 8
 constexpr int kTaggedState = 512;
 __host__ __device__ inline int tagged_row(int H) { return (H + 7) & ~7; }
-__host__ __device__ inline int tagged_group_words(int H) { return tagged_row(H) * 8; }  // 64-bit words of a group, both slots
+__host__ __device__ inline int tagged_group_words(int H, int rows) { return tagged_row(H) * rows / 2; }  // 64-bit words of a group, both slots
 
 struct RecArgs {
   int T, B, N, H, Hpad;
-  int flags;      // the layer's; rec_kernel: | kFourPredSlots; rec16_kernel: | kTaggedState
+  int flags;      // the layer's; rec_kernel: | kFourPredSlots; rec_kernel, rec16_kernel: | kTaggedState
   int m_c;
   int GS;         // workgroups (compute units) per group = cells / 64
   int groups;     // groups in this launch, each owns rows_pg batch rows
@@ -227,6 +227,8 @@ inline size_t rec_sparse_bytes(int GS, int ks) { return (size_t)GS * 4 * 2 * (ks
 bool rec_supported(int N, int H, int flags, int B, int *ks, int *rt, int *groups);
 // Dynamic LDS bytes of the recurrent kernel for these arguments.
 size_t rec_lds_bytes(const RecArgs &a);
+// whether rec_kernel can hand the hidden state on in tagged words (kTaggedState), room for them aside
+bool rec_tagged(const RecArgs &a);
 // Returns hipSuccess or the launch error.
 hipError_t launch_rec(hipStream_t s, const RecArgs &a, bool cooperative);
 // One-time per process: raises the kernels' dynamic LDS limits.

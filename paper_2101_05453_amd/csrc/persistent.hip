@@ -213,6 +213,10 @@ bool rec_supported(int N, int H, int flags, int B, int *ks, int *rt, int *groups
   return true;
 }
 
+bool rec_tagged(const RecArgs &a) {
+  return a.rows_pg == 32 && !a.sparse && a.ks <= 20 && (a.flags & 8) && a.GS > 1 && a.ptiles <= a.GS && (a.H & 7) == 0 && a.H >= 16;
+}
+
 size_t rec_lds_bytes(const RecArgs &a) {
   const int items = (a.rows_pg / 32) * 128;
   const bool proj = a.flags & 8;

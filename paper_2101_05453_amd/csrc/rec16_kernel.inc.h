@@ -283,7 +283,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // one set of words: two sets (as in rec_kernel) made this kernel 2-3 % slower, at 8 and at 32 workgroups per group
   const bool tagged = a.flags & kTaggedState;
   const int Hr = tagged_row(a.H);                    // cells of a row of the exchange
-  u64 *accS = a.acc + (size_t)gl * (kStatGroupWords + (tagged ? tagged_group_words(a.H) : 0));  // [round][S1|S2][item], item < 64
+  u64 *accS = a.acc + (size_t)gl * (kStatGroupWords + (tagged ? tagged_group_words(a.H, 16) : 0));  // [round][S1|S2][item], item < 64
   u64 *const xh = accS + kStatGroupWords;            // [2 slots][16 rows][Hr] (value, tag)
   const unsigned never = a.extra_arrivals ? 0x80u : 0;  // tests: a tag nobody stores in so few steps
   int64_t prevS[2][2] = {{0, 0}, {0, 0}};       // this thread's item, per round: S1, S2

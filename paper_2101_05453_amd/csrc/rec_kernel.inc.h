@@ -108,6 +108,15 @@ __device__ __forceinline__ void poll_pairs(const u64 *base, const unsigned (&at)
                : "memory");
 }
 
+__device__ __forceinline__ void poll_pairs(const u64 *base, const unsigned (&at)[5], v4i (&w)[5]) {
+  asm volatile("global_load_dwordx4 %0, %5, %10 sc1\n\tglobal_load_dwordx4 %1, %6, %10 sc1\n\t"
+               "global_load_dwordx4 %2, %7, %10 sc1\n\tglobal_load_dwordx4 %3, %8, %10 sc1\n\t"
+               "global_load_dwordx4 %4, %9, %10 sc1\n\ts_waitcnt vmcnt(0)"
+               : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3]), "=&v"(w[4])
+               : "v"(at[0]), "v"(at[1]), "v"(at[2]), "v"(at[3]), "v"(at[4]), "s"(base)
+               : "memory");
+}
+
 // Per-layer constants, kept in LDS and read where they are used: as kernel
 // arguments they would all be live in scalar registers across the time loop.
 struct PrmLds {  // 256 bytes (kPrmLdsBytes in persistent.hip)
@@ -229,6 +238,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
   // ---- LDS carve-up (rec_lds_bytes mirrors it): what has a fixed size first, at offsets known to the compiler
   constexpr int LS = KS * 32 + 16;  // h tile row stride
+  constexpr bool kTaggedForm = RT == 1 && !SP && !(FL & 8) && KS <= 20;  // rec_tagged is the host's side of this
   uint8_t *p = lds;
   u64 *red = reinterpret_cast<u64 *>(p);                 p += (size_t)items * 8;
   LnRow2 *lnrow = reinterpret_cast<LnRow2 *>(p);         p += (size_t)items * sizeof(LnRow2);
@@ -410,7 +420,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
   unsigned epoch = 0;
   unsigned *counter = a.counters + group * 64;
-  u64 *accS = a.acc + (size_t)group * kStatGroupWords;  // [set][round][S1|S2][item]
+  // The hidden state in tagged words as in rec16_kernel, where a layer has a projection and a group one row tile of at most 640
+  // outputs, one tile of them per workgroup
+  const bool tagged = kTaggedForm && proj && (a.flags & kTaggedState);
+  u64 *accS = a.acc + (size_t)group * (kStatGroupWords + (tagged ? tagged_group_words(a.H, 32) : 0));  // [set][round][S1|S2][item]
+  u64 *const xh = accS + kStatGroupWords;  // [2 slots][32 rows][H] (value, tag)
   uint32_t prev1[2] = {0, 0};  // this thread's item, per round: the sums of the statistics words as last read
   u64 prev2[2] = {0, 0};
   const int g_first = cifg ? 1 : 0;
@@ -465,6 +479,59 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   };
   if (RT == 1 && a.T > 0) load_tx(0);
 
+  // as in rec16_kernel
+  const unsigned never = a.extra_arrivals ? 0x80u : 0;  // tests: a tag nobody stores in so few steps
+  const int row_pieces = a.H >> 3;
+  const uint32_t per_piece = tagged ? 0xFFFFFFFFu / (uint32_t)row_pieces + 1 : 0;  // c / row_pieces = high word of c per_piece, c < 2^12, two pieces or more
+  auto poll_state = [&](auto count, int t, int tid) {
+    constexpr int U = decltype(count)::value;
+    const uint32_t want = (((unsigned)t + 1) & 0xFF ^ never) * 0x01000100u;
+    const u64 *src = xh + (size_t)(t & 1) * a.H * 8;
+    unsigned at[U];
+    v4i w[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) at[k] = k * 512 + tid < 32 * row_pieces ? (unsigned)(k * 512 + tid) * 16 : 0;
+    int budget = a.spin_limit;
+    for (;;) {
+      poll_pairs(src, at, w);
+      uint32_t off = 0;
+#pragma unroll
+      for (int k = 0; k < U; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) off |= (uint32_t)w[k][i] ^ want;
+      if (__builtin_amdgcn_ballot_w64((off & 0xFF00FF00u) != 0) == 0) break;
+      --budget;
+      if ((budget & 15) == 0 && (budget <= 0 || __hip_atomic_load(a.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
+        __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        flag[0] = 0;
+        break;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const int c = k * 512 + tid;
+      if (c < 32 * row_pieces) {
+        const int rr = (int)__umulhi((uint32_t)c, per_piece);
+        *reinterpret_cast<v2i *>(hT + rr * LS + 8 * (c - rr * row_pieces)) =
+            v2i{(int)__builtin_amdgcn_perm((uint32_t)w[k][1], (uint32_t)w[k][0], 0x06040200u),
+                (int)__builtin_amdgcn_perm((uint32_t)w[k][3], (uint32_t)w[k][2], 0x06040200u)};
+      }
+    }
+  };
+  uint32_t hkeep = 0;  // this thread's two outputs of the step
+  auto store_output = [&](int t, int lane) {
+    const int col = lane & 31, pl = 4 * wave + 2 * (lane >> 5), p0 = member * a.prow + pl;
+    if (my_ptiles > 0 && 4 * wave < a.prow && row0 + col < a.B && p0 < a.H) {
+      const size_t orow0 = (size_t)t * a.B + row0;
+      *reinterpret_cast<uint16_t *>(a.out + orow0 * a.Hpad + member * a.prow + (unsigned)(col * a.Hpad + pl)) = (uint16_t)hkeep;
+      if (a.y) {
+        int8_t *yd = a.y + orow0 * a.H + member * a.prow + (unsigned)(col * a.H + pl);
+        yd[0] = (int8_t)hkeep;
+        if (p0 + 1 < a.H) yd[1] = (int8_t)(hkeep >> 8);
+      }
+    }
+  };
+
   const int tid0 = tid;
   const bool tails = a.lut[0].tail | a.lut[1].tail | a.lut[2].tail;  // some table's LDS copy ends before its flat part
   // this lane's operand row of W_proj; rows beyond a tile's prow outputs re-read row 0: their results are never stored
@@ -476,7 +543,19 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63, col = lane & 31, b2 = lane >> 5, cell_w = wave * 8 + 4 * b2;
     // ---- h^{t-1} rows of the group -> LDS
-    {
+    if (kTaggedForm && tagged && t > 0) {
+      const int mine = (4 * a.H - wave * 64 + 511) >> 9;  // pieces of eight cells for a thread of this wave, 32 rows of H / 8
+      if (mine >= 5)
+        poll_state(std::integral_constant<int, 5>{}, t - 1, tid);
+      else if (mine == 4)
+        poll_state(std::integral_constant<int, 4>{}, t - 1, tid);
+      else if (mine == 3)
+        poll_state(std::integral_constant<int, 3>{}, t - 1, tid);
+      else if (mine == 2)
+        poll_state(std::integral_constant<int, 2>{}, t - 1, tid);
+      else if (mine == 1)
+        poll_state(std::integral_constant<int, 1>{}, t - 1, tid);
+    } else {
       const int8_t *hp = t == 0 ? a.h0 : a.out + (size_t)(t - 1) * a.B * a.Hpad;
       asm volatile("" : "+s"(hp));  // one scalar base: not a pointer per lane for each of the two
 #pragma unroll
@@ -490,6 +569,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
     __syncthreads();
+    if (kTaggedForm && tagged && t > 0) {
+      if (flag[0] == 0) return;
+      store_output(t - 1, lane);
+    }
     if (RT > 1) load_tx(t);
     TICK(0);
 
@@ -1015,7 +1098,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
             for (int c = 0; c < 2; ++c)
               hq[c] = (uint32_t)(sat8(rescale_sat16_pre(sum[c] + (pt == 0 ? bpL[pl + c] : a.bp2[ptile * 32 + pl + c]), pp) + zp_h) & 0xFF);
-            if (row0 + rt * 32 + col < a.B && p0 < a.H) {
+            if (kTaggedForm && tagged) {  // rows beyond the batch too
+              hkeep = hq[0] | hq[1] << 8;
+              const uint32_t tag = ((unsigned)t + 1) & 0xFF;
+              if (p0 < a.H)
+                *reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(xh + (size_t)(t & 1) * a.H * 8) + (unsigned)(col * a.H + p0) * 2) =
+                    __builtin_amdgcn_perm(hkeep, tag, 0x00050004u);
+            } else if (row0 + rt * 32 + col < a.B && p0 < a.H) {
               const size_t orow0 = (size_t)t * a.B + row0 + rt * 32;
               int8_t *od = a.out + orow0 * a.Hpad + ptile * a.prow + (unsigned)(col * a.Hpad + pl);
               // outputs past H fall into the padding of the row (and only ever meet zero weights)
@@ -1028,17 +1117,22 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             }
           }
           // the last tile's partial sums are overwritten behind the group barrier only
-          if (pt + 1 < my_ptiles || rt + 1 < RT) __syncthreads();
+          if (pt + 1 < my_ptiles || rt + 1 < RT || (kTaggedForm && tagged)) __syncthreads();
         }
       }
       TICK(8);
-      if (!group_sync(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, my_ptiles == 0 ? a.idle_sleep : 0,
-                      my_ptiles == 0 ? a.idle_poll_sleep : a.poll_sleep, flag))
+      if (kTaggedForm && tagged) {
+        if (my_ptiles == 0)
+          for (int i = 0; i < a.idle_sleep; ++i) __builtin_amdgcn_s_sleep(1);
+      } else if (!group_sync(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, my_ptiles == 0 ? a.idle_sleep : 0,
+                             my_ptiles == 0 ? a.idle_poll_sleep : a.poll_sleep, flag)) {
         return;
+      }
       TICK(9);
     }
   }
 #undef TICK
+  if (kTaggedForm && tagged) store_output(a.T - 1, lane);
   if (timing && lane == 0)
     for (int i = 0; i < 11; ++i) a.ticks[i] += (long long)tickL[i];
   if (a.ticks && tid == 0) {

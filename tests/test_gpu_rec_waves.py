@@ -74,6 +74,22 @@ def test_state_in_tagged_words(orc, N, H, flags, B, T):
     run_and_compare(orc, layers, x, f"tags{N}h{H}", trace=False, rows=rows, options={"rows16": 2})
 
 
+@pytest.mark.parametrize("N,H,flags,B,T", [
+    (130, 16, PROJ, 40, 300),                # the tags wrap at 256 steps; one wave polls
+    (200, 72, PROJ | LN, 33, 4),             # a second group of one row; the last pieces end within a wave
+    (512, 256, PROJ | CIFG, 70, 4),          # two pieces a thread
+    (700, 408, PROJ | LN | PH, 64, 4),       # three and four pieces
+    (2048, 640, PROJ | LN, 300, 3),          # five; every compute unit, and a second launch
+    (1024, 644, PROJ | LN, 40, 3),           # deeper, and no whole pieces: the counter
+    (512, 100, PROJ, 40, 3),                 # no whole pieces
+    (320, 416, PROJ, 40, 3),                 # more tiles of outputs than workgroups
+])
+def test_state_in_tagged_words_of_32_rows(orc, N, H, flags, B, T):
+    layers, x = wl.make_custom([40], N, H, flags, B, T, seed=N + H + T, weight_param=0.9 / N ** 0.5)
+    rows = None if B <= 40 else sorted({0, 31, 32, B // 2, B - 1})
+    run_and_compare(orc, layers, x, f"tags32_{N}h{H}", trace=False, rows=rows, options={"rows16": 0})
+
+
 @pytest.mark.parametrize("N,H,flags", [
     (320, 320, 0), (320, 320, LN | PH),  # the tables whole in LDS
     (1024, 640, LN | PROJ),              # W_proj leaves no room for that: lookups beyond the prefix
