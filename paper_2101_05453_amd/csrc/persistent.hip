@@ -214,7 +214,8 @@ bool rec_supported(int N, int H, int flags, int B, int *ks, int *rt, int *groups
 }
 
 bool rec_tagged(const RecArgs &a) {
-  return a.rows_pg == 32 && !a.sparse && a.ks <= 20 && (a.flags & 8) && a.GS > 1 && a.ptiles <= a.GS && (a.H & 7) == 0 && a.H >= 16;
+  const bool outputs_ok = !(a.flags & 8) || (a.ptiles <= a.GS && (a.H & 7) == 0 && a.H >= 16);
+  return a.rows_pg == 32 && !a.sparse && a.ks <= 20 && a.GS > 1 && outputs_ok;
 }
 
 size_t rec_lds_bytes(const RecArgs &a) {

@@ -238,7 +238,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
   // ---- LDS carve-up (rec_lds_bytes mirrors it): what has a fixed size first, at offsets known to the compiler
   constexpr int LS = KS * 32 + 16;  // h tile row stride
-  constexpr bool kTaggedForm = RT == 1 && !SP && !(FL & 8) && KS <= 20;  // rec_tagged is the host's side of this
+  constexpr bool kTaggedForm = RT == 1 && !SP && KS <= 20;  // rec_tagged is the host's side of this
   uint8_t *p = lds;
   u64 *red = reinterpret_cast<u64 *>(p);                 p += (size_t)items * 8;
   LnRow2 *lnrow = reinterpret_cast<LnRow2 *>(p);         p += (size_t)items * sizeof(LnRow2);
@@ -420,11 +420,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
   unsigned epoch = 0;
   unsigned *counter = a.counters + group * 64;
-  // The hidden state in tagged words as in rec16_kernel, where a layer has a projection and a group one row tile of at most 640
-  // outputs, one tile of them per workgroup
-  const bool tagged = kTaggedForm && proj && (a.flags & kTaggedState);
+  // The hidden state in tagged words as in rec16_kernel, where a group has one row tile and at most 640 outputs; of a projection one
+  // tile of them per workgroup
+  const bool tagged = kTaggedForm && (a.flags & kTaggedState);
+  const int Hr = FL & 8 ? tagged_row(a.H) : a.H;  // outputs of a projection are whole pieces
   u64 *accS = a.acc + (size_t)group * (kStatGroupWords + (tagged ? tagged_group_words(a.H, 32) : 0));  // [set][round][S1|S2][item]
-  u64 *const xh = accS + kStatGroupWords;  // [2 slots][32 rows][H] (value, tag)
+  u64 *const xh = accS + kStatGroupWords;  // [2 slots][32 rows][Hr] (value, tag)
   uint32_t prev1[2] = {0, 0};  // this thread's item, per round: the sums of the statistics words as last read
   u64 prev2[2] = {0, 0};
   const int g_first = cifg ? 1 : 0;
@@ -481,12 +482,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
   // as in rec16_kernel
   const unsigned never = a.extra_arrivals ? 0x80u : 0;  // tests: a tag nobody stores in so few steps
-  const int row_pieces = a.H >> 3;
+  const int row_pieces = Hr >> 3;
   const uint32_t per_piece = tagged ? 0xFFFFFFFFu / (uint32_t)row_pieces + 1 : 0;  // c / row_pieces = high word of c per_piece, c < 2^12, two pieces or more
   auto poll_state = [&](auto count, int t, int tid) {
     constexpr int U = decltype(count)::value;
     const uint32_t want = (((unsigned)t + 1) & 0xFF ^ never) * 0x01000100u;
-    const u64 *src = xh + (size_t)(t & 1) * a.H * 8;
+    const u64 *src = xh + (size_t)(t & 1) * Hr * 8;
     unsigned at[U];
     v4i w[U];
 #pragma unroll
@@ -518,8 +519,17 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       }
     }
   };
-  uint32_t hkeep = 0;  // this thread's two outputs of the step
+  uint32_t hkeep = 0;  // this thread's outputs of the step, four, or two of a projection
   auto store_output = [&](int t, int lane) {
+    if (FL & 8) {
+      const int col = lane & 31, cell_w = wave * 8 + 4 * (lane >> 5);
+      if (row0 + col < a.B && member * 64 + cell_w < a.N) {
+        const size_t orow0 = (size_t)t * a.B + row0;
+        *reinterpret_cast<uint32_t *>(a.out + orow0 * a.Hpad + member * 64 + (unsigned)(col * a.Hpad + cell_w)) = hkeep;
+        if (a.y) __builtin_nontemporal_store(hkeep, reinterpret_cast<uint32_t *>(a.y + orow0 * a.H + member * 64 + (unsigned)(col * a.H + cell_w)));
+      }
+      return;
+    }
     const int col = lane & 31, pl = 4 * wave + 2 * (lane >> 5), p0 = member * a.prow + pl;
     if (my_ptiles > 0 && 4 * wave < a.prow && row0 + col < a.B && p0 < a.H) {
       const size_t orow0 = (size_t)t * a.B + row0;
@@ -544,7 +554,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int lane = tid & 63, col = lane & 31, b2 = lane >> 5, cell_w = wave * 8 + 4 * b2;
     // ---- h^{t-1} rows of the group -> LDS
     if (kTaggedForm && tagged && t > 0) {
-      const int mine = (4 * a.H - wave * 64 + 511) >> 9;  // pieces of eight cells for a thread of this wave, 32 rows of H / 8
+      const int mine = (4 * Hr - wave * 64 + 511) >> 9;  // pieces of eight cells for a thread of this wave, 32 rows of Hr / 8
       if (mine >= 5)
         poll_state(std::integral_constant<int, 5>{}, t - 1, tid);
       else if (mine == 4)
@@ -1007,7 +1017,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         const int32_t mq = sat8(rescale_sat16_pre<0>(om, pm) + zp_m);
         pk |= (uint32_t)(mq & 0xFF) << (8 * c);
       }
-      if (row < a.B && n0 < a.N) {  // cells past N fill padding of the row (and only ever meet zero weights)
+      if (kTaggedForm && (FL & 8) && tagged) {  // rows beyond the batch and cells up to whole pieces too
+        hkeep = pk;
+        const uint32_t tag = ((unsigned)t + 1) & 0xFF;
+        if (n0 < Hr)
+          *reinterpret_cast<v2i *>(reinterpret_cast<uint8_t *>(xh + (size_t)(t & 1) * Hr * 8) + (unsigned)(col * Hr + n0) * 2) =
+              v2i{(int)__builtin_amdgcn_perm(pk, tag, 0x00050004u), (int)__builtin_amdgcn_perm(pk, tag, 0x00070006u)};
+      } else if (row < a.B && n0 < a.N) {  // cells past N fill padding of the row (and only ever meet zero weights)
         // scalar bases, 32-bit offsets of the lane: pointers of the lane's own would be held through the loop
         int8_t *mb = mdst + (proj ? ((size_t)((row0 >> 5) + rt) * (a.npadp >> 5) + member * 2 + (wave >> 2)) * 1024
                                   : (size_t)(row0 + rt * 32) * a.Hpad + member * 64);
@@ -1021,6 +1037,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     TICK(6);
     if (proj) {
       if (!group_sync(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, a.sync_sleep, a.poll_sleep, flag)) return;
+    } else if (kTaggedForm && (FL & 8) && tagged) {
+      if (!ln) __syncthreads();  // every wave is past R h: the h tile may be filled again
     } else {
       if (!group_sync(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, a.sync_sleep, a.poll_sleep, flag)) return;
     }
@@ -1102,7 +1120,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
               hkeep = hq[0] | hq[1] << 8;
               const uint32_t tag = ((unsigned)t + 1) & 0xFF;
               if (p0 < a.H)
-                *reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(xh + (size_t)(t & 1) * a.H * 8) + (unsigned)(col * a.H + p0) * 2) =
+                *reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(xh + (size_t)(t & 1) * Hr * 8) + (unsigned)(col * Hr + p0) * 2) =
                     __builtin_amdgcn_perm(hkeep, tag, 0x00050004u);
             } else if (row0 + rt * 32 + col < a.B && p0 < a.H) {
               const size_t orow0 = (size_t)t * a.B + row0 + rt * 32;

@@ -83,6 +83,12 @@ def test_state_in_tagged_words(orc, N, H, flags, B, T):
     (1024, 644, PROJ | LN, 40, 3),           # deeper, and no whole pieces: the counter
     (512, 100, PROJ, 40, 3),                 # no whole pieces
     (320, 416, PROJ, 40, 3),                 # more tiles of outputs than workgroups
+    (130, 130, 0, 40, 300),                  # no projection: the tags wrap; a last piece of eight cells with two
+    (203, 203, LN, 33, 4),                   # rows of 208
+    (332, 332, LN | PH, 70, 4),
+    (512, 512, CIFG, 600, 3),
+    (640, 640, 0, 40, 5),                    # five pieces a thread
+    (644, 644, LN, 40, 3),                   # deeper: the counter
 ])
 def test_state_in_tagged_words_of_32_rows(orc, N, H, flags, B, T):
     layers, x = wl.make_custom([40], N, H, flags, B, T, seed=N + H + T, weight_param=0.9 / N ** 0.5)
