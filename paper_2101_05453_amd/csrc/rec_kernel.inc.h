@@ -507,6 +507,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         flag[0] = 0;
         break;
       }
+      if (!(FL & 8) && my_ptiles == 0)  // nothing to do meanwhile: these polls delay the others' loads of m
+        for (int i = 0; i < a.idle_poll_sleep; ++i) __builtin_amdgcn_s_sleep(1);
     }
 #pragma unroll
     for (int k = 0; k < U; ++k) {
