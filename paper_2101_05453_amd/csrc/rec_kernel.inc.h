@@ -420,8 +420,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
   unsigned epoch = 0;
   unsigned *counter = a.counters + group * 64;
-  // The hidden state in tagged words as in rec16_kernel, where a group has one row tile and at most 640 outputs; of a projection one
-  // tile of them per workgroup
+  // The hidden state in tagged words as in rec16_kernel, where a group has one row tile and at most 640 outputs (five loads of 16
+  // bytes a thread and poll; two tiles or 1024 outputs would be eight and more); of a projection one tile of them per workgroup.
+  // Counter -> words, 64 steps (us): 2048 cells, 640 outputs, 256 rows 575 -> 567, layer norm 695 -> 652, and peephole 802 -> 763; 1024
+  // cells, 512 outputs, 512 rows, layer norm 649 -> 610; 512 cells, 1024 rows, layer norm 449 -> 442; 320 cells, 1400 rows 328 -> 302
   const bool tagged = kTaggedForm && (a.flags & kTaggedState);
   const int Hr = FL & 8 ? tagged_row(a.H) : a.H;  // outputs of a projection are whole pieces
   u64 *accS = a.acc + (size_t)group * (kStatGroupWords + (tagged ? tagged_group_words(a.H, 32) : 0));  // [set][round][S1|S2][item]
@@ -507,7 +509,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         flag[0] = 0;
         break;
       }
-      if (!(FL & 8) && my_ptiles == 0)  // nothing to do meanwhile: these polls delay the others' loads of m
+      // nothing to do meanwhile: these polls delay the others' loads of m (1664 cells, 640 outputs, 200 rows 724 -> 622 us)
+      if (!(FL & 8) && my_ptiles == 0)
         for (int i = 0; i < a.idle_poll_sleep; ++i) __builtin_amdgcn_s_sleep(1);
     }
 #pragma unroll
