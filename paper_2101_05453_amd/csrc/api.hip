@@ -898,7 +898,9 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1) {
     ra.groups = p2_groups;
   }
   if (!ok || !lut_ok || rec_lds_bytes(ra) > 160 * 1024) return p;
-  // layers of up to 256 cells: one workgroup per 4 rows, nothing to exchange
+  // layers of up to 256 cells: one workgroup per row or per 4 rows, nothing to exchange.  LDS is counted for W x in the launch
+  // itself where it may be there: a launch without takes no more, the pieces of a long sequence among them
+  bool row_own = false;
   if (m->rows16 == 1 && d.p16 && solo_supported(h.N, h.H, (int)h.flags, B)) {
     RecArgs r1 = ra;
     r1.R2h = d.R2h; r1.ks16 = d.ks16; r1.rows_pg = 4; r1.groups = (B + 3) / 4;
@@ -907,8 +909,9 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1) {
     if (row) {
       r1.rows_pg = 1;
       r1.groups = B;
+      row_own = row_takes_input(h.N, h.H, d.Ipad, T, B);
     }
-    if ((row ? row_lds_bytes(r1) : solo_lds_bytes(r1)) <= 160 * 1024) {
+    if ((row ? row_lds_bytes(r1, row_own) : solo_lds_bytes(r1)) <= 160 * 1024) {
       ra = r1;
       p2_groups = r1.groups;
       p.solo = p.use16 = true;
@@ -948,7 +951,7 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1) {
     ra.R2 = d.R2s;
     ra.sparse = 1;
   }
-  auto lds_need = [&]() { return p.quad ? quad_lds_bytes(ra) : p.row ? row_lds_bytes(ra) : p.solo ? solo_lds_bytes(ra) : p.use16 ? rec16_lds_bytes(ra) : rec_lds_bytes(ra); };
+  auto lds_need = [&]() { return p.quad ? quad_lds_bytes(ra) : p.row ? row_lds_bytes(ra, row_own) : p.solo ? solo_lds_bytes(ra) : p.use16 ? rec16_lds_bytes(ra) : rec_lds_bytes(ra); };
   // What LDS is left goes to longer prefixes of the two gate tables, 1 KB at a time in turn: a value
   // beyond the prefix costs the whole group a detour (rec_kernel.inc.h, lookup), and with 24576 entries
   // (|x| < 6 in Q3.12) there is about one per million layer-norm outputs instead of one per thousand.

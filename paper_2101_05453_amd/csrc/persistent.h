@@ -273,7 +273,7 @@ bool row_supported(int N, int H, int flags, int rows);
 // whether W x of T steps of B rows is the faster in the launch itself; kpad: bytes of a weight row
 bool row_takes_input(int N, int H, int kpad, int T, int B);
 void row_set_input(RowInput &in, const InGemmArgs &g);
-size_t row_lds_bytes(const RecArgs &a);
+size_t row_lds_bytes(const RecArgs &a, bool own);  // own: W x in the launch itself
 hipError_t launch_row(hipStream_t s, const RowArgs &a);
 hipError_t row_init();
 

@@ -34,13 +34,13 @@ bool row_supported(int N, int H, int flags, int rows) {
   return form >= 0 && ((flags & 8) || H == N) && rows <= 256;
 }
 
-size_t row_lds_bytes(const RecArgs &a) {
+size_t row_lds_bytes(const RecArgs &a, bool own) {
   const int form = row_form(a.N, a.H);
   if (form < 0) return (size_t)1 << 30;
   const size_t NC = kRowCells[form];
   size_t n = 3 * NC + 16 * 8 + 4 * sizeof(LnRow2) + 64 + 128;
   n = (n + 1023) & ~(size_t)1023;
-  n += (NC / 16) * (size_t)row_terms_bytes((int)NC / 16, a.T) + (form == 2 && (a.flags & 4) ? 1024 * 16 : 0);
+  n += (NC / 16) * (size_t)row_terms_bytes((int)NC / 16, a.T, own) + (form == 2 && (a.flags & 4) ? 1024 * 16 : 0);
   for (int i = 0; i < 3; ++i)
     if (i < 2 || a.lut[2].blob != a.lut[1].blob) n += (size_t)lut_wide_lds_bytes(a.lut[i].dom, a.lut[i].sh, a.lut[i].tail != 0);
   if (form == 2 && (a.flags & 8)) n += (size_t)((a.H + 15) & ~15) * (NC + 16);
@@ -95,8 +95,8 @@ hipError_t launch_row(hipStream_t s, const RowArgs &a) {
       (own && f.T > row_input_steps(kRowCells[form] / 16)) ||
       (b.groups > 0 && (!b.R2h || row_form(b.N, b.H) != form || f.flags != b.flags || b.rows_pg != 1 || b.groups != b.B || own != (a.in[1].x != nullptr))))
     return hipErrorInvalidValue;
-  size_t lds = row_lds_bytes(f);
-  if (b.groups > 0) lds = lds > row_lds_bytes(b) ? lds : row_lds_bytes(b);
+  size_t lds = row_lds_bytes(f, own);
+  if (b.groups > 0) lds = lds > row_lds_bytes(b, own) ? lds : row_lds_bytes(b, own);
   RowArgs args = a;
   const int blocks = ((f.N > f.H ? f.N : f.H) + 15) / 16;  // a wave each; four at least, which bring the tables in sooner
   void *params[] = {&args};

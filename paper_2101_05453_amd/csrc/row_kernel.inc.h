@@ -28,10 +28,11 @@ namespace lstm_int {
 // Steps whose W x terms are on their way.  A wave waits until at most so many of its memory operations are open, two stores per
 // step among them: a term has at least five steps of 0.4 us, with 16 waves two of 1.2 us, to come from memory.
 constexpr int row_ahead(int waves) { return waves == 16 ? 8 : 16; }
-// Most steps whose W x terms a launch computes itself, all of them ahead of its first step, and bytes of LDS for a wave's terms.
+// Most steps whose W x terms a launch computes itself, all of them ahead of its first step, and bytes of LDS for a wave's terms:
+// those of all steps then, and otherwise of the steps on their way, however many steps the launch has.
 constexpr int row_input_steps(int waves) { return waves == 16 ? 16 : 64; }
-__host__ __device__ constexpr int row_terms_bytes(int waves, int T) {
-  return (T <= row_input_steps(waves) && T > row_ahead(waves) ? T : row_ahead(waves)) * 128;
+__host__ __device__ constexpr int row_terms_bytes(int waves, int T, bool own) {
+  return (own && T > row_ahead(waves) ? T : row_ahead(waves)) * 128;
 }
 
 // The LDS of a launch, from the front (row_lds_bytes mirrors it): h twice, m, sums, statistics, W x terms, tables.
@@ -70,7 +71,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
   p = lds + (((size_t)(p - lds) + 1023) & ~(size_t)1023);
   // W x terms: [step % AHEAD][wave][8 pieces of 16 bytes], or, computed here, [step][wave][gate][16 cells]
   uint8_t *const txL = p + wave * 128;
-  p += WAVES * row_terms_bytes(WAVES, T);
+  p += WAVES * row_terms_bytes(WAVES, T, OWN);
   double *const lnL = reinterpret_cast<double *>(p) + tid * 2;  // LEAN: layer-norm weight and bias of the lane's gate and cell
   p += ln && LEAN ? 64 * WAVES * 16 : 0;
   const bool share_tanh = a.lut[2].blob == a.lut[1].blob;

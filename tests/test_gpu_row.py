@@ -84,3 +84,11 @@ def test_input_product_counts(orc):
         model.forward(torch.from_numpy(np.ascontiguousarray(xq[:T])).cuda())
         torch.cuda.synchronize()
         assert model.profile_end()["input_gemm"]["launches"] == launches, T
+
+
+@pytest.mark.parametrize("N,flags,T", [(256, LN | PROJ, (1 << 14) + 12), (128, LN | PROJ, (1 << 14) + 60)])
+def test_the_last_piece_of_a_long_sequence(orc, N, flags, T):
+    """Beyond 2^14 steps a layer runs in pieces.  The last one is short enough here for a launch that keeps the W x terms of all its
+    steps in LDS, but it does not compute them: it needs the ring of the pieces before, beside tables that fill the LDS."""
+    layers, x = wl.make_custom([16], N, N, flags, 1, T, seed=23, weight_param=0.9 / N ** 0.5)
+    run_and_compare(orc, layers, x, f"rowlong{N}", trace=False)
