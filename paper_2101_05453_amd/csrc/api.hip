@@ -891,8 +891,12 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1) {
   const bool lut0 = set_lut(0, m->wsig3), lut1 = set_lut(1, m->wtanh3), lut2 = set_lut(2, d.wtanhc);
   const bool lut_ok = lut0 && lut1 && lut2;
   ra.flags |= kFourPredSlots;
-  if (ok && ra.rows_pg == 64 && lut_ok && rec_lds_bytes(ra) > 160 * 1024) {
-    // two row tiles per group do not fit the LDS: one tile per group, more launches over the batch
+  // 2:4 recurrent weights at the longest k, and a call that must run the sparse form, which has one row tile per group.  (Left the
+  // choice, the dense form with two tiles is the faster one where it is one launch, 1024 cells, 60 steps, dense / sparse, us: 600
+  // rows 512 / 560, layer norm 748 / 785, coupled gates too 677 / 782; 1024 rows 637 / 618, 840 / 849, 795 / 859.)
+  const bool sparse_asked = ra.ks == 32 && m->sparse == 2 && d.R2s;
+  if (ok && ra.rows_pg == 64 && lut_ok && (rec_lds_bytes(ra) > 160 * 1024 || sparse_asked)) {
+    // two row tiles per group do not fit the LDS, or are not wanted: one tile per group, more launches over the batch
     ra.rows_pg = 32;
     p2_groups = std::min(8 * (32 / d.GS), (B + 31) / 32);
     ra.groups = p2_groups;

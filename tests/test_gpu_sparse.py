@@ -55,6 +55,8 @@ def test_sparse_variants(orc, flags):
     ([256, 512], 512, 512, wl.LAYER_NORM, 48, 6, [0, 31, 32, 47]),              # the C2 layer, k depth 20
     ([640, 640], 2048, 640, wl.LAYER_NORM | wl.PROJECTION, 256, 6, "edges"),    # the C4 layer at its batch: all 8 XCDs
     ([1024], 1024, 1024, wl.CIFG | wl.LAYER_NORM, 200, 3, [0, 31, 96, 199]),    # the C5 layer (k depth 32)
+    ([64], 1024, 1024, wl.LAYER_NORM, 600, 3, [0, 31, 255, 256, 511, 512, 599]),  # more rows than one launch of groups of 32 holds
+    ([64], 700, 700, 0, 750, 2, [0, 255, 511, 575, 576, 749]),                  # the same, 11 workgroups per group
 ])
 def test_sparse_shapes(orc, case):
     inputs, N, H, flags, B, T, rows = case
