@@ -833,6 +833,7 @@ struct RecPlan {
   // with use16: the one-workgroup kernel (row: the one with a workgroup per batch row) / the four-row kernel instead of the
   // 16-row one
   bool solo = false, row = false, quad = false;
+  bool rest32 = false;  // groups of 64 rows: a rest of the batch that fits one launch of groups of 32 runs as those
 };
 
 int64_t sync_bytes(int groups);
@@ -989,6 +990,7 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1) {
       ra.flags |= kTaggedState;
   }
   p.groups = p2_groups;
+  p.rest32 = !p.use16 && ra.rows_pg == 64 && ra.ks == 32 && B > p2_groups * 64;
   p.ok = true;
   return p;
 }
@@ -1281,6 +1283,16 @@ int lstm_int_forward(const lstm_int_model *cm, const int8_t *x, int32_t T, int32
         ra.c_out = (c_state || t0 + tc < T) ? c_carry : nullptr;
         for (int b0 = 0; b0 < B; b0 += launch_rows) {
           ra.batch0 = b0;
+          // What full launches of two row tiles per group leave over, where a launch of one tile holds it: half the work per group,
+          // in the sparse form for 2:4 weights.  (At the longest k, 1400 rows, 60 steps, all two tiles -> this, us: 1024 cells 1196 ->
+          // 1076, layer norm 1573 -> 1311, coupled gates too 1466 -> 1230, layer norm and peephole 1881 -> 1504; 2:4 weights 1201 ->
+          // 1013, 1556 -> 1241, 1462 -> 1206, 1859 -> 1486.)
+          if (plan.rest32) {
+            const bool rest = B - b0 <= p2_groups * 32;
+            ra.rows_pg = rest ? 32 : 64;
+            ra.sparse = rest && m->sparse && d.R2s;
+            ra.R2 = ra.sparse ? d.R2s : d.R2;
+          }
           ra.groups = std::min(p2_groups, (B - b0 + ra.rows_pg - 1) / ra.rows_pg);
           if (!plan.solo && (b0 > 0 || t0 > 0)) {
             Timed t(m->prof, s, LSTM_INT_K_OTHER);

@@ -32,12 +32,29 @@ def test_division_over_the_waves(orc, N, H, flags, B, T):
 @pytest.mark.parametrize("flags", [0, CIFG, PH, CIFG | PH, LN, LN | CIFG, LN | PH, LN | PH | CIFG])
 @pytest.mark.parametrize("N,B,rows", [
     (1024, 513, [0, 31, 32, 63, 64, 511, 512]),             # a last group of one row: its second tile is empty
-    (650, 1090, [0, 63, 545, 575, 576, 1023, 1024, 1089]),  # a second launch, whose last tile is ragged
+    (650, 1090, [0, 63, 545, 575, 576, 1023, 1024, 1089]),  # a second launch, of groups of 32
+    (650, 1590, [0, 63, 1023, 1024, 1087, 1088, 1589]),     # a second launch, whose last tile is ragged
 ])
 def test_two_row_tiles_at_the_deepest_k(orc, N, B, rows, flags):
     """Groups of 64 rows where R h is 1024 deep: every form without a projection."""
     layers, x = wl.make_custom([24], N, N, flags, B, 3, seed=N + B + flags, weight_param=0.9 / N ** 0.5)
     run_and_compare(orc, layers, x, f"two{N}b{B}f{flags}", trace=False, rows=rows, options={"rows16": 0})
+
+
+@pytest.mark.parametrize("pruned", [0, 1])
+@pytest.mark.parametrize("N,B,flags", [
+    (1024, 1025, LN),            # one row is left
+    (1024, 1536, 0),             # as many as one launch of groups of 32 holds
+    (1024, 1537, CIFG | LN),     # one more: two tiles again
+    (650, 1100, LN | PH), (650, 1500, CIFG),
+])
+def test_what_two_row_tiles_leave_over(orc, N, B, flags, pruned):
+    """Rows beyond the last full launch of groups of 64 run in groups of 32 where one launch holds them, in the sparse form where
+    the recurrent weights are 2:4."""
+    layers, x = wl.make_custom([24], N, N, flags, B, 3, seed=N + B + flags, weight_param=0.9 / N ** 0.5)
+    if pruned:
+        wl.prune_2of4(layers)
+    run_and_compare(orc, layers, x, f"rest{N}b{B}f{flags}", trace=False, rows=[0, 63, 1023, 1024, (1024 + B) // 2, B - 2, B - 1])
 
 
 @pytest.mark.parametrize("N,H,flags,B,T", [
