@@ -1064,11 +1064,11 @@ double stacked_us(const LayerHost &h, int L, int64_t T, int64_t B, double item_u
 
 // Whether forward runs T steps of B rows as one stacked launch (a function of the model, its options, T
 // and B only: lstm_int_workspace_bytes and lstm_int_forward must agree): where its expected time is the
-// shorter one.  The formulas are off by 3 to 5 % at the median and up to 20 % and more in single calls, but a wrong choice is
-// a close one: over 620 calls that were not in the fit it costs 0.2 % against the better way of each (48 cells, 8 layers, layer
-// norm and a projection, 2 rows, 44 steps: 643 us one after the other, 441 stacked; 128 cells, 6 layers, 128 rows, 2 steps: 88,
-// 113).  A fit without peephole and layer norm together, coupled gates and widths between the powers of two cost 1.2 %, one
-// time per step and item for all models, from 2048 cells, 4.7 %.
+// shorter one.  The formulas are off by 2 to 5 % at the median (12 % with a workgroup of 16 waves per row) and up to 40 % in
+// single calls, but a wrong choice is a close one: over 800 calls that were not in the fit it costs 0.3 % against the better way
+// of each, and more than 2 % in 26 of them (228 cells, projection to 88, six layers, 21 rows, 57 steps: 741 us one after the
+// other, as chosen, 623 stacked).  Taking the stacked launch as long as it costs no more than 7 % per layer, for the sake of the
+// launches, cost 4 % over the 585 of them with up to 256 cells; with the host waiting for each call it was no better.
 bool stack_chosen(const lstm_int_model *m, int64_t T, int64_t B) {
   if (!m->stackable || m->stack == 0 || m->path == 1 || m->reverse) return false;
   int ks = 0;
@@ -1081,11 +1081,7 @@ bool stack_chosen(const lstm_int_model *m, int64_t T, int64_t B) {
   if (plan_stack(m, T, B).total > (size_t)LSTM_INT_STATIC_WORKSPACE_BYTES &&
       plan_workspace(m, T, B).total <= (size_t)LSTM_INT_STATIC_WORKSPACE_BYTES)
     return false;
-  // Layers of a workgroup per row are short, and every one is a launch more for the host: one launch for all of them is taken
-  // as long as it costs the device no more than 7 % per layer (8 layers of 128 cells, layer norm, 64 rows, 8 steps: 139 us one
-  // after the other, 188 stacked).
-  const RecPlan p = plan_rec(m, 0, (int)T, (int)B);
-  return stacked_us(h, L, T, B, m->stack_step_us) < (p.row ? 1.0 + 0.07 * L : 1.0) * sequential_us(h, p, L, T, B);
+  return stacked_us(h, L, T, B, m->stack_step_us) < sequential_us(h, plan_rec(m, 0, (int)T, (int)B), L, T, B);
 }
 
 // Synchronization scratch of a launch (plan_workspace's `sync`): barrier counters and placement words, statistics words.

@@ -1,5 +1,5 @@
 """Which of the two ways a model of equal layers runs, layer after layer or as one stacked launch, by the number of launches, at
-sizes where one way is well ahead; both ways give the oracle's integers."""
+sizes where one way is well ahead and at some where it is close; both ways give the oracle's integers."""
 import numpy as np
 import pytest
 
@@ -21,19 +21,24 @@ def forward_counted(model, xd):
 
 
 @pytest.mark.parametrize("L,N,H,flags,B,T,stacked", [
-    (8, 256, 256, LN, 64, 8, True),       # 196 us against 438
-    (2, 256, 256, LN, 4, 4, True),        # 46, 73
-    (8, 128, 128, LN, 64, 8, True),       # 195, 227
-    (3, 1024, 1024, LN, 32, 64, False),   # 1030, 773
-    (3, 64, 64, 0, 32, 64, False),        # 340, 183
-    (2, 512, 512, 0, 8, 16, False),       # 130, 85
-    (8, 1024, 256, LN | PROJ, 1, 1, True),
-    (4, 320, 320, LN, 1000, 2, False),    # the 32-row kernel
-    (6, 64, 64, LN | PH, 12, 64, True),   # 597, 857
-    (8, 48, 16, LN | PROJ, 2, 44, True),  # 441, 643
-    (3, 112, 32, PROJ, 13, 9, False),     # 93, 60
-    (3, 80, 72, PH | PROJ, 44, 2, False),  # 65, 47
-    (5, 192, 40, CIFG | LN | PROJ, 81, 5, False),  # 199, 154
+    # us stacked, one after the other
+    (8, 256, 256, LN, 64, 8, True),       # 193, 232
+    (2, 256, 256, LN, 4, 4, False),       # 45, 42
+    (8, 128, 128, LN, 64, 8, False),      # 192, 143
+    (3, 1024, 1024, LN, 32, 64, False),   # 1050, 707
+    (3, 64, 64, 0, 32, 64, False),        # 335, 117
+    (2, 512, 512, 0, 8, 16, False),       # 125, 76
+    (8, 1024, 256, LN | PROJ, 1, 1, True),  # 81, 163
+    (4, 320, 320, LN, 1000, 2, False),    # 640, 106: the 32-row kernel
+    (6, 64, 64, LN | PH, 12, 64, False),  # 591, 583
+    (8, 48, 16, LN | PROJ, 2, 44, False),  # 430, 414
+    (3, 112, 32, PROJ, 13, 9, False),     # 91, 42
+    (3, 80, 72, PH | PROJ, 44, 2, False),  # 66, 31
+    (5, 192, 40, CIFG | LN | PROJ, 81, 5, False),  # 197, 94
+    (6, 128, 128, 0, 32, 48, False),      # 304, 223
+    (8, 240, 240, LN, 1, 2, True),        # 69, 143
+    (7, 144, 28, LN | PROJ, 3, 1, True),  # 65, 90
+    (7, 188, 188, LN | PH, 31, 15, True),  # 204, 306
 ])
 def test_the_faster_way_is_taken(orc, L, N, H, flags, B, T, stacked):
     import torch
