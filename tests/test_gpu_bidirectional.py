@@ -80,11 +80,21 @@ def test_both_directions_in_one_launch_of_the_16_row_kernel(orc, variant, N):
 @pytest.mark.parametrize("N", [39, 128, 130, 256])  # four, eight and 16 waves; cells and outputs within a wave's block
 @pytest.mark.parametrize("proj", [0, 1])
 @pytest.mark.parametrize("variant", range(8))
-def test_both_directions_in_one_launch_of_the_one_workgroup_kernel(orc, variant, proj, N):
-    """Every instantiation of the one-workgroup kernel (CIFG, peephole, layer norm, projection) on both directions, the
-    last workgroup of each with fewer than four rows."""
+@pytest.mark.parametrize("B", [6, 130])
+def test_both_directions_in_one_launch_of_the_one_workgroup_kernels(orc, B, variant, proj, N):
+    """Every instantiation of the kernels without exchange (CIFG, peephole, layer norm, projection) on both directions: a workgroup
+    per row (6 rows), a workgroup per four rows, the last of each direction with two (130, beyond 256 rows of both together)."""
     H = N - 7 if proj else N
-    test_bidirectional_outputs_side_by_side(orc, (variant | (wl.PROJECTION if proj else 0), [24], N, H, 6, 4))
+    test_bidirectional_outputs_side_by_side(orc, (variant | (wl.PROJECTION if proj else 0), [24], N, H, B, 4))
+
+
+@pytest.mark.parametrize("N,T", [(64, 70), (39, 100), (128, 70), (250, 17), (250, 40)])
+@pytest.mark.parametrize("flags", [0, wl.LAYER_NORM | wl.PEEPHOLE, wl.CIFG | wl.LAYER_NORM | wl.PROJECTION])
+def test_both_directions_with_a_row_per_workgroup_from_the_input_matmul(orc, flags, N, T):
+    """A workgroup per row where W x is not computed in its launch: the terms of both directions through the ring, the backward
+    ones from the last step down; two layers, both ends' states."""
+    H = N - 3 if flags & wl.PROJECTION else N
+    test_bidirectional_outputs_side_by_side(orc, (flags, [24, H], N, H, 3, T))
 
 
 @pytest.mark.parametrize("rows16", [1, 2])  # groups of four rows, of 16
