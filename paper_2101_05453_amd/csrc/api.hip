@@ -833,6 +833,7 @@ struct RecPlan {
   // with use16: the one-workgroup kernel (row: the one with a workgroup per batch row) / the four-row kernel instead of the
   // 16-row one
   bool solo = false, row = false, quad = false;
+  bool row_own = false;  // with row: W x in the launch itself, where its input allows it
   bool rest32 = false;  // groups of 64 rows: a rest of the batch that fits one launch of groups of 32 runs as those
 };
 
@@ -903,28 +904,32 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1) {
     ra.groups = p2_groups;
   }
   if (!ok || !lut_ok || rec_lds_bytes(ra) > 160 * 1024) return p;
-  // layers of up to 256 cells: one workgroup per row or per 4 rows, nothing to exchange.  LDS is counted for W x in the launch
-  // itself where it may be there: a launch without takes no more, the pieces of a long sequence among them
-  bool row_own = false;
+  int g4 = 0;
+  // layers of up to 256 cells: one workgroup per row or per 4 rows, nothing to exchange
   if (m->rows16 == 1 && d.p16 && solo_supported(h.N, h.H, (int)h.flags, B)) {
     RecArgs r1 = ra;
     r1.R2h = d.R2h; r1.ks16 = d.ks16; r1.rows_pg = 4; r1.groups = (B + 3) / 4;
     r1.Wp2 = d.Wp2; r1.bp2 = d.bp2; r1.ptiles = d.ptiles; r1.prow = 32;
-    const bool row = row_supported(h.N, h.H, (int)h.flags, B * share);
-    if (row) {
+    // With a wide projection the tables of some cell formats leave the form per row no room for the terms of all steps (256 cells,
+    // 224 outputs, layer norm, 12 steps, 64 rows, us: groups of four rows over several workgroups 57, per row without them 45), or
+    // none at all.  (LDS for W x in the launch is enough for a launch without, the pieces of a long sequence among them.)
+    const bool small = row_supported(h.N, h.H, (int)h.flags, B * share);
+    p.row = small && row_lds_bytes(r1, false) <= 160 * 1024;
+    // Then groups of four rows over several workgroups are ahead with layer norm alone, else one workgroup per four rows: 256 cells
+    // and outputs, 64 rows, 100 steps 363 us against 376, coupled gates 352 against 327, peephole 466 against 440, both 444, 384.
+    const bool spread = small && !p.row && (h.flags & 7) == 4 && quad_supported(h.N, h.H, (int)h.flags, B, share, &g4);
+    p.row_own = p.row && row_takes_input(h.N, h.H, d.Ipad, T, B) && row_lds_bytes(r1, true) <= 160 * 1024;
+    if (p.row) {
       r1.rows_pg = 1;
       r1.groups = B;
-      row_own = row_takes_input(h.N, h.H, d.Ipad, T, B);
     }
-    if ((row ? row_lds_bytes(r1, row_own) : solo_lds_bytes(r1)) <= 160 * 1024) {
+    if (p.row || (!spread && solo_lds_bytes(r1) <= 160 * 1024)) {
       ra = r1;
       p2_groups = r1.groups;
       p.solo = p.use16 = true;
-      p.row = row;
     }
   }
   // larger layers, batches small enough for it: groups of four rows
-  int g4 = 0;
   if (!p.solo && m->rows16 == 1 && d.p16 && quad_supported(h.N, h.H, (int)h.flags, B, share, &g4)) {
     RecArgs r4 = ra;
     r4.R2h = d.R2h; r4.ks16 = d.ks16; r4.rows_pg = 4; r4.groups = g4;
@@ -956,7 +961,7 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1) {
     ra.R2 = d.R2s;
     ra.sparse = 1;
   }
-  auto lds_need = [&]() { return p.quad ? quad_lds_bytes(ra) : p.row ? row_lds_bytes(ra, row_own) : p.solo ? solo_lds_bytes(ra) : p.use16 ? rec16_lds_bytes(ra) : rec_lds_bytes(ra); };
+  auto lds_need = [&]() { return p.quad ? quad_lds_bytes(ra) : p.row ? row_lds_bytes(ra, p.row_own) : p.solo ? solo_lds_bytes(ra) : p.use16 ? rec16_lds_bytes(ra) : rec_lds_bytes(ra); };
   // What LDS is left goes to longer prefixes of the two gate tables, 1 KB at a time in turn: a value
   // beyond the prefix costs the whole group a detour (rec_kernel.inc.h, lookup), and with 24576 entries
   // (|x| < 6 in Q3.12) there is about one per million layer-norm outputs instead of one per thousand.
@@ -1230,7 +1235,7 @@ int lstm_int_forward(const lstm_int_model *cm, const int8_t *x, int32_t T, int32
       ga.cols = in == x ? h.I : 0;
       RowInput own_input;  // W x in the recurrent launch itself
       memset(&own_input, 0, sizeof(own_input));
-      if (plan.row && row_takes_input(h.N, h.H, d.Ipad, T, B) && in_gemm_ws_supported(ga)) {
+      if (plan.row_own && in_gemm_ws_supported(ga)) {
         Timed t(m->prof, s, LSTM_INT_K_OTHER);
         flush_pending();
         row_set_input(own_input, ga);
@@ -1488,7 +1493,7 @@ static int forward_pair(lstm_int_model *const (&m)[2], const int8_t *x, int32_t 
     memset(input, 0, sizeof(input));
     RecPlan plan[2] = {plan_rec(m[0], l, T, B, 2), plan_rec(m[1], l, T, B, 2)};
     const int groups = plan[0].groups + plan[1].groups;
-    bool own_input = plan[0].row && row_takes_input(m[0]->host[l].N, m[0]->host[l].H, m[0]->dev[l].Ipad, T, B);  // of both or neither
+    bool own_input = plan[0].row_own && plan[1].row_own;  // of both or neither
     for (int i = 0; i < 2; ++i) {
       InGemmArgs ga = plan_in_gemm(m[i], l, T, B);
       ga.A = in[i]; ga.lda = ld_in[i];

@@ -6,7 +6,7 @@ import pytest
 
 import lstm_workloads as wl
 from paper_2101_05453_amd import binding
-from parity_util import assert_equal, prepare_both, run_and_compare
+from parity_util import assert_equal, calibrate_on_gpu, prepare_both, run_and_compare
 
 pytestmark = pytest.mark.gpu
 LN, PH, PROJ, CIFG = wl.LAYER_NORM, wl.PEEPHOLE, wl.PROJECTION, wl.CIFG
@@ -86,9 +86,36 @@ def test_input_product_counts(orc):
         assert model.profile_end()["input_gemm"]["launches"] == launches, T
 
 
-@pytest.mark.parametrize("N,flags,T", [(256, LN | PROJ, (1 << 14) + 12), (128, LN | PROJ, (1 << 14) + 60)])
-def test_the_last_piece_of_a_long_sequence(orc, N, flags, T):
+@pytest.mark.parametrize("N,H,T", [(256, 200, (1 << 14) + 12), (128, 128, (1 << 14) + 60)])
+def test_the_last_piece_of_a_long_sequence(orc, N, H, T):
     """Beyond 2^14 steps a layer runs in pieces.  The last one is short enough here for a launch that keeps the W x terms of all its
-    steps in LDS, but it does not compute them: it needs the ring of the pieces before, beside tables that fill the LDS."""
-    layers, x = wl.make_custom([16], N, N, flags, 1, T, seed=23, weight_param=0.9 / N ** 0.5)
-    run_and_compare(orc, layers, x, f"rowlong{N}", trace=False)
+    steps in LDS, but it does not compute them: it needs the ring of the pieces before, beside tables that (256 cells) fill the LDS."""
+    layers, x = wl.make_custom([16], N, H, LN | PROJ, 1, T, seed=23, weight_param=0.9 / N ** 0.5)
+    model, _ = run_and_compare(orc, layers, x, f"rowlong{N}", trace=False)
+    assert model.get_quant(0)["m_c"] <= 2  # three tables, none of them short
+
+
+@pytest.mark.parametrize("H,flags,m_c,T,own", [
+    (256, LN | PROJ | PH, 2, 12, 0), (256, LN | PROJ | CIFG, 1, 40, 0),  # no room for the form per row: four rows per workgroup
+    (224, LN | PROJ, 2, 12, 0), (256, PROJ, 0, 16, 0), (256, LN | PROJ, 4, 12, 0),  # none for the terms of all steps
+    (224, LN | PROJ, 2, 40, 0), (160, LN | PROJ, 2, 12, 1), (256, PROJ, 3, 16, 1), (256, LN | PROJ, 4, 8, 1),
+])
+def test_wide_projections_in_every_cell_format(orc, H, flags, m_c, T, own):
+    """The tables of a cell format and a wide projection beside each other in LDS: whichever of the kernels without exchange has
+    the room runs, with its own W x or the input matmul's."""
+    import torch
+
+    layers, x = wl.make_custom([48], 256, H, flags, 9, T, seed=H + m_c, weight_param=0.06)
+    xd = calibrate_on_gpu(layers, x)
+    layers[0].c_absmax = 0.9 * 2.0 ** m_c
+    model, oracle = binding.prepare(layers), orc.prepare(layers)
+    assert oracle.layer(0)["m_c"] == m_c
+    xq = model.quantize_input(xd)
+    model.set_option("spin_limit", 64)
+    model.set_option("barrier_never_completes", 1)  # a kernel whose workgroups meet would give up
+    model.profile_begin()
+    y = model.forward(xq).cpu().numpy()
+    launches = {k: v["launches"] for k, v in model.profile_end().items()}
+    assert model.device_status() == 0 and launches["recurrent"] == 1 and launches["cell"] == 0
+    assert launches["input_gemm"] == 1 - own
+    assert_equal("y", y, np.asarray(orc.forward(oracle, xq.cpu().numpy())))
