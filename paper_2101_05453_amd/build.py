@@ -21,10 +21,6 @@ EXTRA_FLAGS = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] for f in ("in_gemm.hip"
 # (eight layers of 2048 cells, 256 rows: 5530 -> 5340 us)
 for _f in ("rec_inst_8.hip", "rec_inst_20.hip", "rec_inst_32.hip", "rec_sparse_inst_8.hip", "rec_sparse_inst_20.hip", "rec_sparse_inst_32.hip", "stack_inst_8.hip", "stack_inst_20.hip", "stack_inst_32.hip", "row_inst_64.hip", "row_inst_128.hip", "row_inst_256.hip", "gru_rows.hip"):
     EXTRA_FLAGS[_f] = EXTRA_FLAGS[_f] + ["-mllvm", "-disable-lsr", "-mllvm", "-disable-machine-licm"]
-# rec16_kernel at the deepest k: the second of them alone (200 steps of 128 rows, 1024 cells, layer norm 1009 -> 955 us, coupled gates too
-# 976 -> 940, layer norm and peephole 1322 -> 1301, none of them 625 -> 618; with both 971, 936, 1289 and 629).  Its smaller forms are
-# slower with either: 2048 cells projected to 640, layer norm 1580 -> 1601 and 1767.
-EXTRA_FLAGS["rec16_inst_16.hip"] = EXTRA_FLAGS["rec16_inst_16.hip"] + ["-mllvm", "-disable-machine-licm"]
 
 
 def _compile(src, verbose):

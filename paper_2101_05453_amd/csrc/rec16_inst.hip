@@ -8,26 +8,29 @@ namespace lstm_int {
 static const int kKS16[] = {4, 10, 16};
 
 typedef void (*rec_fn)(RecArgs);
-rec_fn rec16_pick_4(int fl);   // rec16_inst_4.hip
-rec_fn rec16_pick_10(int fl);  // rec16_inst_10.hip
-rec_fn rec16_pick_16(int fl);  // rec16_inst_16.hip
-static rec_fn pick16(int ks16, int fl) {
-  if (ks16 == 4) return rec16_pick_4(fl);
-  if (ks16 == 10) return rec16_pick_10(fl);
-  if (ks16 == 16) return rec16_pick_16(fl);
+rec_fn rec16_pick_4(int fl, int tag);   // rec16_inst_4.hip
+rec_fn rec16_pick_10(int fl, int tag);  // rec16_inst_10.hip
+rec_fn rec16_pick_16(int fl, int tag);  // rec16_inst_16.hip
+static rec_fn pick16(int ks16, int fl, int tag) {
+  if (ks16 == 4) return rec16_pick_4(fl, tag);
+  if (ks16 == 10) return rec16_pick_10(fl, tag);
+  if (ks16 == 16) return rec16_pick_16(fl, tag);
   return nullptr;
 }
 
 typedef void (*rec16_pair_fn)(RecArgs2);
-rec16_pair_fn rec16_pick_pair_4(int fl);
-rec16_pair_fn rec16_pick_pair_10(int fl);
-rec16_pair_fn rec16_pick_pair_16(int fl);
-static rec16_pair_fn pick16_pair(int ks16, int fl) {
-  if (ks16 == 4) return rec16_pick_pair_4(fl);
-  if (ks16 == 10) return rec16_pick_pair_10(fl);
-  if (ks16 == 16) return rec16_pick_pair_16(fl);
+rec16_pair_fn rec16_pick_pair_4(int fl, int tag);
+rec16_pair_fn rec16_pick_pair_10(int fl, int tag);
+rec16_pair_fn rec16_pick_pair_16(int fl, int tag);
+static rec16_pair_fn pick16_pair(int ks16, int fl, int tag) {
+  if (ks16 == 4) return rec16_pick_pair_4(fl, tag);
+  if (ks16 == 10) return rec16_pick_pair_10(fl, tag);
+  if (ks16 == 16) return rec16_pick_pair_16(fl, tag);
   return nullptr;
 }
+
+// the kernel's TAG
+static int rec16_tag(int flags) { return !(flags & kTaggedState) ? 0 : flags & 8 ? 2 : 1; }
 
 bool rec16_supported(int N, int H, int flags, int B, int *ks16, int *groups) {
   if (N > 2048 || B < 1) return false;
@@ -49,7 +52,7 @@ bool rec16_supported(int N, int H, int flags, int B, int *ks16, int *groups) {
 size_t rec16_lds_bytes(const RecArgs &a) {
   const int items = 64;
   const bool proj = a.flags & 8;
-  size_t tile = (((size_t)16 * (a.ks16 * 64 + 16) + 1023) / 1024 + 1) * 1024 + (a.flags & (4 | 8) ? 0 : 1024);
+  size_t tile = (((size_t)16 * (a.ks16 * 64 + 16) + 1023) / 1024 + 1) * 1024 + (a.flags & kTaggedState && !(a.flags & (4 | 8)) ? 1024 : 0);
   if (proj && tile < 8 * 2 * 64 * 16) tile = 8 * 2 * 64 * 16;
   size_t n = tile + (size_t)items * 8 + (size_t)items * sizeof(LnRow2) + 2 * 4 * 64 * 8 + 4 * 64 * 4 + 4 * 64 * 2 +
              256 /* PrmLds */ + 16 + 16 * 8 + 3 * 32 /* LutLds */;
@@ -64,11 +67,12 @@ size_t rec16_lds_bytes(const RecArgs &a) {
 
 hipError_t rec16_init() {
   for (int ks : kKS16)
-    for (int fl = 0; fl < 8; ++fl) {
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(pick16(ks, fl)),
+    for (int i = 0; i < 24; ++i) {
+      const int fl = i & 7, tag = i >> 3;
+      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(pick16(ks, fl, tag)),
                                          hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
       if (e != hipSuccess) return e;
-      e = hipFuncSetAttribute(reinterpret_cast<const void *>(pick16_pair(ks, fl)), hipFuncAttributeMaxDynamicSharedMemorySize,
+      e = hipFuncSetAttribute(reinterpret_cast<const void *>(pick16_pair(ks, fl, tag)), hipFuncAttributeMaxDynamicSharedMemorySize,
                               160 * 1024);
       if (e != hipSuccess) return e;
     }
@@ -76,7 +80,7 @@ hipError_t rec16_init() {
 }
 
 hipError_t launch_rec16(hipStream_t s, const RecArgs &a, bool cooperative) {
-  rec_fn fn = pick16(a.ks16, a.flags & 7);
+  rec_fn fn = pick16(a.ks16, a.flags & 7, rec16_tag(a.flags));
   if (!fn || !a.R2h) return hipErrorInvalidValue;
   const int slots = a.GS * ((a.groups + 7) / 8);
   RecArgs args = a;
@@ -90,7 +94,7 @@ hipError_t launch_rec16(hipStream_t s, const RecArgs &a, bool cooperative) {
 
 hipError_t launch_rec16_pair(hipStream_t s, const RecArgs2 &a, bool cooperative) {
   const RecArgs &f = a.d[0], &b = a.d[1];
-  rec16_pair_fn fn = pick16_pair(f.ks16, f.flags & 7);
+  rec16_pair_fn fn = pick16_pair(f.ks16, f.flags & 7, rec16_tag(f.flags));
   if (!fn || !f.R2h || !b.R2h || f.GS != b.GS || f.ks16 != b.ks16 || f.flags != b.flags || f.groups + b.groups > 8 * (32 / f.GS))
     return hipErrorInvalidValue;
   const int slots = f.GS * ((f.groups + b.groups + 7) / 8);

@@ -2,6 +2,6 @@
 #include "rec16_kernel.inc.h"
 
 namespace lstm_int {
-rec_fn rec16_pick_10(int fl) { return rec16_pick_ks<10>(fl); }
-rec16_pair_fn rec16_pick_pair_10(int fl) { return rec16_pick_ks<10, true, rec16_pair_fn>(fl); }
+rec_fn rec16_pick_10(int fl, int tag) { return rec16_pick_ks<10>(fl, tag); }
+rec16_pair_fn rec16_pick_pair_10(int fl, int tag) { return rec16_pick_ks<10, true, rec16_pair_fn>(fl, tag); }
 }  // namespace lstm_int

@@ -2,6 +2,6 @@
 #include "rec16_kernel.inc.h"
 
 namespace lstm_int {
-rec_fn rec16_pick_16(int fl) { return rec16_pick_ks<16>(fl); }
-rec16_pair_fn rec16_pick_pair_16(int fl) { return rec16_pick_ks<16, true, rec16_pair_fn>(fl); }
+rec_fn rec16_pick_16(int fl, int tag) { return rec16_pick_ks<16>(fl, tag); }
+rec16_pair_fn rec16_pick_pair_16(int fl, int tag) { return rec16_pick_ks<16, true, rec16_pair_fn>(fl, tag); }
 }  // namespace lstm_int

@@ -2,6 +2,6 @@
 #include "rec16_kernel.inc.h"
 
 namespace lstm_int {
-rec_fn rec16_pick_4(int fl) { return rec16_pick_ks<4>(fl); }
-rec16_pair_fn rec16_pick_pair_4(int fl) { return rec16_pick_ks<4, true, rec16_pair_fn>(fl); }
+rec_fn rec16_pick_4(int fl, int tag) { return rec16_pick_ks<4>(fl, tag); }
+rec16_pair_fn rec16_pick_pair_4(int fl, int tag) { return rec16_pick_ks<4, true, rec16_pair_fn>(fl, tag); }
 }  // namespace lstm_int

@@ -13,17 +13,22 @@
 //
 // The hidden state travels as (value, tag) byte pairs, the tag being the step (kTaggedState, quad_kernel.inc.h has more on it):
 // 16 bytes a thread hold eight cells, and who needs them polls them, up to four loads a thread.  Through the layer output, the
-// group's counter and a load of the tile behind it (the way m still goes, 64 KB as pairs for each workgroup with outputs), 200
-// steps (us): 1024 cells, 128 rows 763 -> 616, layer norm 1125 -> 955; 512 cells, 200 rows 630 -> 519, layer norm 969 -> 855; two
-// directions of 512 cells, 100 rows, 100 steps 356 -> 272; 2048 cells, 640 outputs, layer norm, peephole, 128 rows 1897 -> 1833.
-// The counter remains where one workgroup is the group, and where the words of all groups find no room.
+// group's counter and a load of the tile behind it (the way m still goes, 64 KB as pairs for each workgroup with outputs) -> this,
+// 200 steps, us:
+//   1024 cells, 128 rows  788 -> 606, layer norm 1127 -> 908       512 cells, 200 rows  653 -> 510, layer norm 971 -> 774
+//   two directions of 512 cells, 100 rows, 100 steps 364 -> 271    512 cells, 256 outputs, layer norm, 200 rows 1382 -> 1158
+//   2048 cells, 640 outputs, 128 rows 1168 -> 999, layer norm 1592 -> 1396, and peephole 1868 -> 1653; 160 outputs, layer norm 1577 -> 1314
+// The counter remains where one workgroup is the group, and where the words of all groups find no room.  Either way is a form of its
+// own (TAG): with both in one kernel, chosen by a test in the step loop, the registers that each keeps for itself spilled (12 to
+// 80 bytes a lane at 2048 cells with layer norm, three times the scalar ones everywhere), and the same calls took 632, 950, 533, 847,
+// 277, 1253, 1158, 1544, 1792 and 1958 us, the ones through the counter up to 25 % longer than alone.
 //
 // What bounds it: the exchanges of a step (two, one without a projection, and one
 // per round of statistics, 0.6 to 1.2 us each) and the instructions between them.
 // Two waves per SIMD issue those in less time than one of twice the work: 128 rows
 // of 2048 cells, projection to 640: 6.3 -> 5.9 us a step, with layer norm 8.3 -> 8.1,
 // and peephole 9.4 -> 9.2; 512 cells, 200 rows 3.1 -> 2.9, with layer norm 4.8 -> 4.6
-// (before the tagged words).
+// (before the tagged words).  Machine LICM off, which the deepest k needed with both ways in one kernel, makes it 1 to 2 % slower.
 #pragma once
 
 #include "rec_kernel.inc.h"
@@ -50,7 +55,8 @@ __device__ __forceinline__ int rec16_rev(const RecArgs &) { return 0; }
 __device__ __forceinline__ int rec16_rev(const RecDirArgs &a) { return a.rev; }
 
 // PAIR: the launch runs two layers of one shape side by side, each possibly backward in time (RecArgs2).
-template <int KS16, int FL, bool PAIR = false>
+// TAG: 0 = the state through the counter; 1, 2 = in tagged words, without and with a projection (rec16_tag).
+template <int KS16, int FL, bool PAIR, int TAG>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void rec16_kernel(
     std::conditional_t<PAIR, RecArgs2, RecArgs> args) {
   constexpr bool cifg = FL & 1, ph = FL & 2, ln = FL & 4;
@@ -99,7 +105,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int which = PAIR && gl >= a0.groups ? 1 : 0;
   const auto &a = rec16_args(args, which);
   const int group = gl - (which ? a0.groups : 0);
-  const bool proj = a.flags & 8;
+  const bool proj = TAG == 0 ? (a.flags & 8) != 0 : TAG == 2;
   const int ldy = rec16_ldy(a);
   // time of step t
   auto time_of = [&](int t) { return rec16_rev(a) ? a.T - 1 - t : t; };
@@ -120,7 +126,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // hidden state of the step on its way out, where the loads past the h tile go, which nobody reads: 16-byte pieces of row r
   // at r * 64, exchanged by r / 4 so that rows in the same banks differ.  With neither layer norm nor a projection two of them by
   // turns: no barrier lies between the barrier behind which wave 1 reads it once more (store_output) and the next hidden state.
-  const int mflip = ln || proj ? 0 : 1024;
+  constexpr int mflip = TAG == 1 && !ln ? 1024 : 0;
   int8_t *const mS0 = reinterpret_cast<int8_t *>(lds) + TILE_KB * 1024;
   auto mS_of = [&](int t) { return mS0 + (t & 1) * mflip; };
   auto piece_at = [](int row, int piece) { return row * 64 + ((piece ^ (row >> 2)) << 4); };
@@ -262,6 +268,15 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     rw = rw < a.B ? rw : a.B - 1;
     hsrc[j] = (rr < 16 && c < a.Hpad) ? rw * a.Hpad + c : 0;
   }
+  auto load_tile = [&](const int8_t *hp) {
+#pragma unroll
+    for (int j = 0; j < NCH; ++j)
+      __builtin_amdgcn_global_load_lds(
+          (const __attribute__((address_space(1))) void *)(hp + hsrc[j]),
+          (__attribute__((address_space(3))) void *)(lds + (wave + 8 * j < TILE_KB ? wave + 8 * j : TILE_KB) * 1024),
+          16, 0, 0);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  };
 
   // projection: thread (ct = tid / 64 < 2, lane) finishes outputs 16 ct + 4 q + 0..3 of row r
   int32_t bpr[4] = {0, 0, 0, 0};
@@ -281,7 +296,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   unsigned epoch = 0;
   unsigned *counter = a.counters + gl * 64;
   // one set of words: two sets (as in rec_kernel) made this kernel 2-3 % slower, at 8 and at 32 workgroups per group
-  const bool tagged = a.flags & kTaggedState;
+  constexpr bool tagged = TAG != 0;
   const int Hr = tagged_row(a.H);                    // cells of a row of the exchange
   u64 *accS = a.acc + (size_t)gl * (kStatGroupWords + (tagged ? tagged_group_words(a.H, 16) : 0));  // [round][S1|S2][item], item < 64
   u64 *const xh = accS + kStatGroupWords;            // [2 slots][16 rows][Hr] (value, tag)
@@ -317,11 +332,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int g = 0; g < 4; ++g) txn[g] = __builtin_nontemporal_load(src + (g >> 1) * 256 + (g & 1) * 2);
   };
   tx_request(0);
+  if (tagged) load_tile(a.h0);
 
   // The state of a step in words of (value, tag) pairs, the tag being the step: a thread polls the pieces of eight cells it
   // needs until all carry the tag, U of them at a time, and puts them into the tile.  No acknowledgement, no counter, no load
   // after the barrier.
   const int row_pieces = Hr >> 3;
+  const uint32_t per_piece = (1u << 20) / (uint32_t)row_pieces + 1;  // c / row_pieces = c per_piece / 2^20: c < 16 row_pieces, row_pieces <= 128
   auto poll_state = [&](auto count, int t) {
     constexpr int U = decltype(count)::value;
     const uint32_t want = (((unsigned)t + 1) & 0xFF ^ never) * 0x01000100u;
@@ -350,7 +367,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int k = 0; k < U; ++k) {
       const int c = k * 512 + tid;
       if (c < 16 * row_pieces) {
-        const int rr = c / row_pieces;
+        const int rr = (int)((uint32_t)c * per_piece >> 20);
         *reinterpret_cast<v2i *>(hT + rr * LS + 8 * (c - rr * row_pieces)) =
             v2i{(int)__builtin_amdgcn_perm((uint32_t)w[k][1], (uint32_t)w[k][0], 0x06040200u),
                 (int)__builtin_amdgcn_perm((uint32_t)w[k][3], (uint32_t)w[k][2], 0x06040200u)};
@@ -400,9 +417,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       n0 = member * 64 + cellw;
     }
     // ---- h^{t-1} rows of the group -> LDS
-    if (tagged && t > 0) {
+    if (tagged) {
       // pieces of this wave: a wave without any does not poll, its loads would cost as much as the others'
-      const int mine = (16 * row_pieces - wave * 64 + 511) >> 9;
+      // 32 KB a poll: a first one too early delays the arrivals (1024 cells, 120 rows, 60 steps 196 -> 189 us, layer norm 291 -> 285)
+      if (TAG == 1 && KS16 > 10 && GATHER && t > 0) __builtin_amdgcn_s_sleep(3);
+      const int mine = t > 0 ? (16 * row_pieces - wave * 64 + 511) >> 9 : 0;
       if (mine >= 4)
         poll_state(std::integral_constant<int, 4>{}, t - 1);
       else if (mine == 3)
@@ -412,14 +431,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       else if (mine == 1)
         poll_state(std::integral_constant<int, 1>{}, t - 1);
     } else {
-      const int8_t *hp = t == 0 ? a.h0 : a.out + (size_t)time_of(t - 1) * a.B * a.Hpad;
-#pragma unroll
-      for (int j = 0; j < NCH; ++j)
-        __builtin_amdgcn_global_load_lds(
-            (const __attribute__((address_space(1))) void *)(hp + hsrc[j]),
-            (__attribute__((address_space(3))) void *)(lds + (wave + 8 * j < TILE_KB ? wave + 8 * j : TILE_KB) * 1024),
-            16, 0, 0);
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      load_tile(t == 0 ? a.h0 : a.out + (size_t)time_of(t - 1) * a.B * a.Hpad);
     }
     __syncthreads();
     if (tagged && t > 0) {
@@ -867,13 +879,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         __syncthreads();
       }
       TICK(8);
-      if (tagged) {
-        if (my_ptiles == 0)
-          for (int i = 0; i < a.idle_sleep; ++i) __builtin_amdgcn_s_sleep(1);
-      } else if (!group_sync(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, my_ptiles == 0 ? a.idle_sleep : 0,
-                             my_ptiles == 0 ? a.idle_poll_sleep : a.poll_sleep, flag)) {
+      // Tagged: workgroups without outputs poll the state at once and without a pause.  Late for the next step they hold up its
+      // statistics and its m: with the counter's first pause of 64 2048 cells, 640 outputs, layer norm, 40 steps of 40 rows take 381 us,
+      // and pauses of 12 between the polls 368, with none 285.
+      if (!tagged && !group_sync(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, my_ptiles == 0 ? a.idle_sleep : 0,
+                                 my_ptiles == 0 ? a.idle_poll_sleep : a.poll_sleep, flag))
         return;
-      }
       TICK(9);
     }
   }
@@ -905,18 +916,23 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 typedef void (*rec16_pair_fn)(RecArgs2);
 
 // kernel for (flags & 7) at k depth KS16
-template <int KS16, bool PAIR = false, class Fn = rec_fn>
-Fn rec16_pick_ks(int fl) {
+template <int KS16, bool PAIR, int TAG, class Fn>
+Fn rec16_pick_tag(int fl) {
   switch (fl & 7) {
-    case 0: return rec16_kernel<KS16, 0, PAIR>;
-    case 1: return rec16_kernel<KS16, 1, PAIR>;
-    case 2: return rec16_kernel<KS16, 2, PAIR>;
-    case 3: return rec16_kernel<KS16, 3, PAIR>;
-    case 4: return rec16_kernel<KS16, 4, PAIR>;
-    case 5: return rec16_kernel<KS16, 5, PAIR>;
-    case 6: return rec16_kernel<KS16, 6, PAIR>;
-    default: return rec16_kernel<KS16, 7, PAIR>;
+    case 0: return rec16_kernel<KS16, 0, PAIR, TAG>;
+    case 1: return rec16_kernel<KS16, 1, PAIR, TAG>;
+    case 2: return rec16_kernel<KS16, 2, PAIR, TAG>;
+    case 3: return rec16_kernel<KS16, 3, PAIR, TAG>;
+    case 4: return rec16_kernel<KS16, 4, PAIR, TAG>;
+    case 5: return rec16_kernel<KS16, 5, PAIR, TAG>;
+    case 6: return rec16_kernel<KS16, 6, PAIR, TAG>;
+    default: return rec16_kernel<KS16, 7, PAIR, TAG>;
   }
+}
+template <int KS16, bool PAIR = false, class Fn = rec_fn>
+Fn rec16_pick_ks(int fl, int tag) {
+  if (tag == 0) return rec16_pick_tag<KS16, PAIR, 0, Fn>(fl);
+  return tag == 1 ? rec16_pick_tag<KS16, PAIR, 1, Fn>(fl) : rec16_pick_tag<KS16, PAIR, 2, Fn>(fl);
 }
 
 }  // namespace lstm_int

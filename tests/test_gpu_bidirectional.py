@@ -69,10 +69,10 @@ def test_both_directions_in_one_launch(orc, case):
 
 @pytest.mark.parametrize("N", [130, 320, 650])  # the three k depths
 @pytest.mark.parametrize("variant", range(8))
-def test_both_directions_in_one_launch_of_the_16_row_kernel(orc, variant, N):
+@pytest.mark.parametrize("proj", [0, 1])
+def test_both_directions_in_one_launch_of_the_16_row_kernel(orc, proj, variant, N):
     """Every instantiation of the 16-row kernel that runs two directions side by side (CIFG, peephole, layer norm), with
     and without a projection, two groups per direction."""
-    proj = (variant + N) % 20 < 10
     H = N - 5 if proj else N
     test_bidirectional_outputs_side_by_side(orc, (variant | (wl.PROJECTION if proj else 0), [24], N, H, 21, 4), rows16=2)
 

@@ -41,6 +41,20 @@ def test_two_row_tiles_at_the_deepest_k(orc, N, B, rows, flags):
     run_and_compare(orc, layers, x, f"two{N}b{B}f{flags}", trace=False, rows=rows, options={"rows16": 0})
 
 
+@pytest.mark.parametrize("variant", range(8))  # coupled gates, peephole, layer norm
+@pytest.mark.parametrize("N,H,B", [
+    (60, 60, 33), (60, 40, 33), (60, 300, 20), (60, 700, 20),  # one workgroup per group: the state through the layer output
+    (100, 400, 1500), (100, 700, 1200),  # two, and no room for the tagged words of all groups
+    (200, 200, 40), (600, 600, 40), (700, 700, 21),  # tagged words
+    (200, 150, 40), (600, 300, 40), (1100, 650, 21), (1100, 16, 21),  # with a projection; workgroups without outputs
+])
+def test_every_form_of_the_16_row_kernel(orc, N, H, B, variant):
+    flags = variant | (PROJ if H != N else 0)
+    layers, x = wl.make_custom([24], N, H, flags, B, 4, seed=N + H + variant, weight_param=0.9 / N ** 0.5)
+    run_and_compare(orc, layers, x, f"r16_{N}_{H}_{flags}", trace=False, rows=None if B <= 40 else [0, 15, 16, 31, B // 2, B - 2, B - 1],
+                    options={"rows16": 2})
+
+
 @pytest.mark.parametrize("pruned", [0, 1])
 @pytest.mark.parametrize("N,B,flags", [
     (1024, 1025, LN),            # one row is left
