@@ -319,10 +319,9 @@ int lstm_int_forward_bidirectional(const lstm_int_model *fwd, const lstm_int_mod
  *           groups of 16 workgroups and more, else 4.
  *   "idle_sleep", "idle_poll_sleep": the same for the workgroups that have no
  *           projection tile, behind the projection: pause before their first
- *           poll and between polls (defaults 64 and 12) of the barrier there or,
- *           where groups of 32 rows have none because the hidden state carries
- *           the step it belongs to, of that state.  Groups of 16 rows whose
- *           state does so poll it without a pause, whatever the options say.
+ *           poll and between polls (defaults 64 and 12) of the barrier there.
+ *           Where the hidden state carries the step it belongs to (groups of 16
+ *           and 32 rows mostly) there is no barrier, and these do nothing.
  *   "sparse": 1 (default) runs the recurrent product of a layer whose quantized
  *           recurrent weights are 2:4 along the contraction (at most two nonzeros
  *           in every aligned group of four h inputs; see lstm_int_sparse_layers)

@@ -189,8 +189,8 @@ struct RecArgs {
   int poll_sleep, stats_sleep;  // pauses between two polls of a barrier / of the statistics words, x 64 clocks
   int stats_first_sleep;  // pause before the first poll of the statistics words
   int sync_sleep;  // pause before the first poll of the barrier at which all workgroups arrive together
-  int idle_sleep, idle_poll_sleep;  // workgroups without a projection tile, at the barrier after the projection or, in the 32-row
-                                    // kernel, the tagged state: pause before the first poll, and between polls
+  int idle_sleep, idle_poll_sleep;  // workgroups without a projection tile, at the barrier after the projection, where there is
+                                    // one (not with kTaggedState): pause before the first poll, and between polls
   long long *ticks;  // NULL, or [16] phase timers of workgroup 0 (diagnostics)
   int extra_arrivals;  // 0; tests set 1: every group barrier then waits for an arrival that never comes, so that
                        // the bounded waits give up (and every workgroup leaves the kernel) on demand

@@ -236,9 +236,9 @@ size_t rec_lds_bytes(const RecArgs &a) {
 }
 
 typedef void (*rec_fn)(RecArgs);
-rec_fn rec_pick_8(int rt, int fl);   // rec_inst_8.hip
-rec_fn rec_pick_20(int rt, int fl);  // rec_inst_20.hip
-rec_fn rec_pick_32(int rt, int fl);  // rec_inst_32.hip
+rec_fn rec_pick_8(int rt, int fl, bool tag);   // rec_inst_8.hip
+rec_fn rec_pick_20(int rt, int fl, bool tag);  // rec_inst_20.hip
+rec_fn rec_pick_32(int rt, int fl, bool tag);  // rec_inst_32.hip
 rec_fn rec_pick_sparse_8(int fl);   // rec_sparse_inst_8.hip
 rec_fn rec_pick_sparse_20(int fl);  // rec_sparse_inst_20.hip
 rec_fn rec_pick_sparse_32(int fl);  // rec_sparse_inst_32.hip
@@ -248,18 +248,18 @@ static rec_fn pick_sparse(int ks, int fl) {
   if (ks == 32) return rec_pick_sparse_32(fl);
   return nullptr;
 }
-static rec_fn pick(int ks, int rt, int fl) {
-  if (ks == 8) return rec_pick_8(rt, fl);
-  if (ks == 20) return rec_pick_20(rt, fl);
-  if (ks == 32) return rec_pick_32(rt, fl);
+static rec_fn pick(int ks, int rt, int fl, bool tag) {
+  if (ks == 8) return rec_pick_8(rt, fl, tag);
+  if (ks == 20) return rec_pick_20(rt, fl, tag);
+  if (ks == 32) return rec_pick_32(rt, fl, tag);
   return nullptr;
 }
 
 hipError_t rec_init() {
   for (int ks : kKS)
-    for (int rt = 1; rt <= 2; ++rt)
+    for (int form = 0; form < 3; ++form)  // one row tile, two, one with the state in tagged words
       for (int fl = 0; fl < 16; ++fl) {
-        rec_fn fn = pick(ks, rt, fl);
+        rec_fn fn = pick(ks, form == 1 ? 2 : 1, fl, form == 2);
         if (!fn) continue;
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
@@ -277,7 +277,7 @@ hipError_t rec_init() {
 hipError_t launch_rec(hipStream_t s, const RecArgs &a, bool cooperative) {
   const int fl = (a.flags & 7) | ((a.flags & 8) ? 0 : 8);  // bit 3: no projection
   if (a.sparse && a.rows_pg != 32) return hipErrorInvalidValue;
-  rec_fn fn = a.sparse ? pick_sparse(a.ks, fl) : pick(a.ks, a.rows_pg / 32, fl);
+  rec_fn fn = a.sparse ? pick_sparse(a.ks, fl) : pick(a.ks, a.rows_pg / 32, fl, a.flags & kTaggedState);
   if (!fn) return hipErrorInvalidValue;
   const int slots = a.GS * ((a.groups + 7) / 8);
   RecArgs args = a;

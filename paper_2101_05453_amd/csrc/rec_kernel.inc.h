@@ -177,8 +177,10 @@ __device__ __forceinline__ int32_t mirror_tanh_masked(int32_t x, int32_t t) {
 // FL: bit 0 CIFG, bit 1 peephole, bit 2 layer norm, bit 3 "no projection" (compile
 // time, so that the code carries no tests of them); with bit 3 clear the
 // projection is a runtime flag.  SP: the recurrent weights are in the 2:4
-// compressed form (persistent.h) and R h runs on the sparse MFMA.
-template <int KS, int RT, int FL, bool SP = false>
+// compressed form (persistent.h) and R h runs on the sparse MFMA.  TAG: the
+// hidden state travels in tagged words (kTaggedState) instead of through the
+// group's counter: a form of its own, as in rec16_kernel.
+template <int KS, int RT, int FL, bool SP = false, bool TAG = false>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void rec_kernel(RecArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   const long long t_start = (long long)wall_clock64();
@@ -238,7 +240,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
   // ---- LDS carve-up (rec_lds_bytes mirrors it): what has a fixed size first, at offsets known to the compiler
   constexpr int LS = KS * 32 + 16;  // h tile row stride
-  constexpr bool kTaggedForm = RT == 1 && !SP && KS <= 20;  // rec_tagged is the host's side of this
+  static_assert(!TAG || (RT == 1 && !SP && KS <= 20));  // rec_tagged is the host's side of this
   uint8_t *p = lds;
   u64 *red = reinterpret_cast<u64 *>(p);                 p += (size_t)items * 8;
   LnRow2 *lnrow = reinterpret_cast<LnRow2 *>(p);         p += (size_t)items * sizeof(LnRow2);
@@ -396,7 +398,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   constexpr int TILE_KB = (rows_pg * LS + 1023) / 1024;
   constexpr int NCH = (TILE_KB + WAVES - 1) / WAVES;  // chunks per wave
   unsigned hsrc[NCH];
-  constexpr bool HSRC_KEPT = !(RT > 1 && KS > 20);  // two tiles at the longest k have no registers for it
+  constexpr bool HSRC_KEPT = !TAG && !(RT > 1 && KS > 20);  // two tiles at the longest k have no registers for it
   auto h_source = [&](int j, int lane) {
     const int o = (wave + WAVES * j) * 1024 + lane * 16;
     const int r = o / LS, c = o - r * LS;
@@ -422,11 +424,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   unsigned *counter = a.counters + group * 64;
   // The hidden state in tagged words as in rec16_kernel, where a group has one row tile and at most 640 outputs (five loads of 16
   // bytes a thread and poll; two tiles or 1024 outputs would be eight and more); of a projection one tile of them per workgroup.
-  // Counter -> words, 64 steps (us): 2048 cells, 640 outputs, 256 rows 575 -> 567, layer norm 695 -> 652, and peephole 802 -> 763; 1024
-  // cells, 512 outputs, 512 rows, layer norm 649 -> 610; 512 cells, 1024 rows, layer norm 449 -> 442; 320 cells, 1400 rows 328 -> 302
-  const bool tagged = kTaggedForm && (a.flags & kTaggedState);
+  // Counter -> words, 64 steps (us): 2048 cells, 640 outputs, 256 rows 553 -> 526, layer norm 685 -> 631, and peephole 794 -> 739; 160
+  // outputs, layer norm 688 -> 551; 1024 cells, 512 outputs, 512 rows, layer norm 640 -> 581; 512 cells, 1024 rows, layer norm 460 -> 449;
+  // 320 cells, 1400 rows 345 -> 314.  (Both ways in one kernel, with the counter's pauses for the workgroups without outputs: 539, 641,
+  // 756, 574, 594, 458 and 319, and 2 to 5 % on the calls through the counter.)
   const int Hr = FL & 8 ? tagged_row(a.H) : a.H;  // outputs of a projection are whole pieces
-  u64 *accS = a.acc + (size_t)group * (kStatGroupWords + (tagged ? tagged_group_words(a.H, 32) : 0));  // [set][round][S1|S2][item]
+  u64 *accS = a.acc + (size_t)group * (kStatGroupWords + (TAG ? tagged_group_words(a.H, 32) : 0));  // [set][round][S1|S2][item]
   u64 *const xh = accS + kStatGroupWords;  // [2 slots][32 rows][Hr] (value, tag)
   uint32_t prev1[2] = {0, 0};  // this thread's item, per round: the sums of the statistics words as last read
   u64 prev2[2] = {0, 0};
@@ -485,7 +488,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // as in rec16_kernel
   const unsigned never = a.extra_arrivals ? 0x80u : 0;  // tests: a tag nobody stores in so few steps
   const int row_pieces = Hr >> 3;
-  const uint32_t per_piece = tagged ? 0xFFFFFFFFu / (uint32_t)row_pieces + 1 : 0;  // c / row_pieces = high word of c per_piece, c < 2^12, two pieces or more
+  const uint32_t per_piece = TAG ? 0xFFFFFFFFu / (uint32_t)row_pieces + 1 : 0;  // c / row_pieces = high word of c per_piece, c < 2^12, two pieces or more
   auto poll_state = [&](auto count, int t, int tid) {
     constexpr int U = decltype(count)::value;
     const uint32_t want = (((unsigned)t + 1) & 0xFF ^ never) * 0x01000100u;
@@ -509,9 +512,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         flag[0] = 0;
         break;
       }
-      // nothing to do meanwhile: these polls delay the others' loads of m (1664 cells, 640 outputs, 200 rows 724 -> 622 us)
-      if (!(FL & 8) && my_ptiles == 0)
-        for (int i = 0; i < a.idle_poll_sleep; ++i) __builtin_amdgcn_s_sleep(1);
+      // a workgroup without outputs has nothing to do meanwhile, and its polls delay the others' loads of m
+      if (!(FL & 8) && my_ptiles == 0) __builtin_amdgcn_s_sleep(2);
     }
 #pragma unroll
     for (int k = 0; k < U; ++k) {
@@ -551,6 +553,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const bool tails = a.lut[0].tail | a.lut[1].tail | a.lut[2].tail;  // some table's LDS copy ends before its flat part
   // this lane's operand row of W_proj; rows beyond a tile's prow outputs re-read row 0: their results are never stored
   const int wp_lane = (col < a.prow ? col : 0) * WLS + (b2 << 4);
+  if (TAG) {  // h before the first step
+#pragma unroll
+    for (int j = 0; j < NCH; ++j)
+      if (WAVES * (j + 1) <= TILE_KB || wave + WAVES * j < TILE_KB)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(a.h0 + h_source(j, lane)),
+                                         (__attribute__((address_space(3))) void *)(hT + (wave + WAVES * j) * 1024), 16, 0, 0);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  }
   for (int t = 0; t < a.T; ++t) {
     // Addresses of a lane are computed anew in every step: kept from before the loop they would cost registers that the
     // compiler then finds in scratch memory, whose loads return behind the W x terms on their way from HBM.
@@ -558,8 +568,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63, col = lane & 31, b2 = lane >> 5, cell_w = wave * 8 + 4 * b2;
     // ---- h^{t-1} rows of the group -> LDS
-    if (kTaggedForm && tagged && t > 0) {
-      const int mine = (4 * Hr - wave * 64 + 511) >> 9;  // pieces of eight cells for a thread of this wave, 32 rows of Hr / 8
+    if (TAG) {
+      const int mine = t > 0 ? (4 * Hr - wave * 64 + 511) >> 9 : 0;  // pieces of eight cells for a thread of this wave, 32 rows of Hr / 8
       if (mine >= 5)
         poll_state(std::integral_constant<int, 5>{}, t - 1, tid);
       else if (mine == 4)
@@ -584,7 +594,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
     __syncthreads();
-    if (kTaggedForm && tagged && t > 0) {
+    if (TAG && t > 0) {
       if (flag[0] == 0) return;
       store_output(t - 1, lane);
     }
@@ -1022,7 +1032,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         const int32_t mq = sat8(rescale_sat16_pre<0>(om, pm) + zp_m);
         pk |= (uint32_t)(mq & 0xFF) << (8 * c);
       }
-      if (kTaggedForm && (FL & 8) && tagged) {  // rows beyond the batch and cells up to whole pieces too
+      if (TAG && (FL & 8)) {  // rows beyond the batch and cells up to whole pieces too
         hkeep = pk;
         const uint32_t tag = ((unsigned)t + 1) & 0xFF;
         if (n0 < Hr)
@@ -1042,7 +1052,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     TICK(6);
     if (proj) {
       if (!group_sync(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, a.sync_sleep, a.poll_sleep, flag)) return;
-    } else if (kTaggedForm && (FL & 8) && tagged) {
+    } else if (TAG && (FL & 8)) {
       if (!ln) __syncthreads();  // every wave is past R h: the h tile may be filled again
     } else {
       if (!group_sync(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, a.sync_sleep, a.poll_sleep, flag)) return;
@@ -1121,7 +1131,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
             for (int c = 0; c < 2; ++c)
               hq[c] = (uint32_t)(sat8(rescale_sat16_pre(sum[c] + (pt == 0 ? bpL[pl + c] : a.bp2[ptile * 32 + pl + c]), pp) + zp_h) & 0xFF);
-            if (kTaggedForm && tagged) {  // rows beyond the batch too
+            if (TAG) {  // rows beyond the batch too
               hkeep = hq[0] | hq[1] << 8;
               const uint32_t tag = ((unsigned)t + 1) & 0xFF;
               if (p0 < a.H)
@@ -1140,22 +1150,21 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             }
           }
           // the last tile's partial sums are overwritten behind the group barrier only
-          if (pt + 1 < my_ptiles || rt + 1 < RT || (kTaggedForm && tagged)) __syncthreads();
+          if (pt + 1 < my_ptiles || rt + 1 < RT || TAG) __syncthreads();
         }
       }
       TICK(8);
-      if (kTaggedForm && tagged) {
-        if (my_ptiles == 0)
-          for (int i = 0; i < a.idle_sleep; ++i) __builtin_amdgcn_s_sleep(1);
-      } else if (!group_sync(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, my_ptiles == 0 ? a.idle_sleep : 0,
-                             my_ptiles == 0 ? a.idle_poll_sleep : a.poll_sleep, flag)) {
+      // (TAG: without outputs a workgroup goes on to its polls at once, as in rec16_kernel; 1088 cells, 160 outputs, layer norm, 250 rows,
+      // 40 steps with a first pause of 64 and 12 between polls 0.98 of the counter's time, with 0 and 2 0.88, with no pause 0.88, but at
+      // 1792 cells, 640 outputs 0.922, 0.929 and 0.939)
+      if (!TAG && !group_sync(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, my_ptiles == 0 ? a.idle_sleep : 0,
+                              my_ptiles == 0 ? a.idle_poll_sleep : a.poll_sleep, flag))
         return;
-      }
       TICK(9);
     }
   }
 #undef TICK
-  if (kTaggedForm && tagged) store_output(a.T - 1, lane);
+  if (TAG) store_output(a.T - 1, lane);
   if (timing && lane == 0)
     for (int i = 0; i < 11; ++i) a.ticks[i] += (long long)tickL[i];
   if (a.ticks && tid == 0) {
@@ -1201,9 +1210,20 @@ rec_fn rec_pick_sparse_ks(int fl) {
 
 // kernel for (rt, flags & 7) at k depth KS
 template <int KS>
-rec_fn rec_pick_ks(int rt, int fl) {
+rec_fn rec_pick_ks(int rt, int fl, bool tag) {
 #define LSTM_REC_CASE(R, F) \
   if (rt == R && fl == F) return rec_kernel<KS, R, F>;
+#define LSTM_REC_TAG(F) \
+  if (rt == 1 && fl == F) return rec_kernel<KS, 1, F, false, true>;
+  if constexpr (KS <= 20) {
+    if (tag) {
+      LSTM_REC_TAG(0) LSTM_REC_TAG(1) LSTM_REC_TAG(2) LSTM_REC_TAG(3)
+      LSTM_REC_TAG(4) LSTM_REC_TAG(5) LSTM_REC_TAG(6) LSTM_REC_TAG(7)
+      LSTM_REC_TAG(8) LSTM_REC_TAG(9) LSTM_REC_TAG(10) LSTM_REC_TAG(11)
+      LSTM_REC_TAG(12) LSTM_REC_TAG(13) LSTM_REC_TAG(14) LSTM_REC_TAG(15)
+    }
+  }
+  if (tag) return nullptr;
   LSTM_REC_CASE(1, 0) LSTM_REC_CASE(1, 1) LSTM_REC_CASE(1, 2) LSTM_REC_CASE(1, 3)
   LSTM_REC_CASE(1, 4) LSTM_REC_CASE(1, 5) LSTM_REC_CASE(1, 6) LSTM_REC_CASE(1, 7)
   LSTM_REC_CASE(1, 8) LSTM_REC_CASE(1, 9) LSTM_REC_CASE(1, 10) LSTM_REC_CASE(1, 11)
@@ -1214,6 +1234,7 @@ rec_fn rec_pick_ks(int rt, int fl) {
   }
   LSTM_REC_CASE(2, 8) LSTM_REC_CASE(2, 9) LSTM_REC_CASE(2, 10) LSTM_REC_CASE(2, 11)
   LSTM_REC_CASE(2, 12) LSTM_REC_CASE(2, 13) LSTM_REC_CASE(2, 14) LSTM_REC_CASE(2, 15)
+#undef LSTM_REC_TAG
 #undef LSTM_REC_CASE
   return nullptr;
 }

@@ -55,6 +55,17 @@ def test_every_form_of_the_16_row_kernel(orc, N, H, B, variant):
                     options={"rows16": 2})
 
 
+@pytest.mark.parametrize("variant", range(8))
+@pytest.mark.parametrize("N,H", [
+    (60, 60), (200, 150), (600, 301), (700, 700), (1100, 700),  # the state through the layer output
+    (200, 200), (600, 600), (200, 152), (600, 304), (1100, 16),  # tagged words
+])
+def test_every_form_of_the_32_row_kernel(orc, N, H, variant):
+    flags = variant | (PROJ if H != N else 0)
+    layers, x = wl.make_custom([24], N, H, flags, 37, 4, seed=N + H + variant, weight_param=0.9 / N ** 0.5)
+    run_and_compare(orc, layers, x, f"r32_{N}_{H}_{flags}", trace=False, options={"rows16": 0})
+
+
 @pytest.mark.parametrize("pruned", [0, 1])
 @pytest.mark.parametrize("N,B,flags", [
     (1024, 1025, LN),            # one row is left
