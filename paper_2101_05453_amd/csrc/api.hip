@@ -1070,8 +1070,8 @@ double stacked_us(const LayerHost &h, int L, int64_t T, int64_t B, double item_u
 // Whether forward runs T steps of B rows as one stacked launch (a function of the model, its options, T
 // and B only: lstm_int_workspace_bytes and lstm_int_forward must agree): where its expected time is the
 // shorter one.  The formulas are off by 2 to 5 % at the median (12 % with a workgroup of 16 waves per row) and up to 40 % in
-// single calls, but a wrong choice is a close one: over 800 calls that were not in the fit it costs 0.3 % against the better way
-// of each, and more than 2 % in 26 of them (228 cells, projection to 88, six layers, 21 rows, 57 steps: 741 us one after the
+// single calls, but a wrong choice is a close one: over 1034 calls that were not in the fit it costs 0.3 % against the better way
+// of each, and more than 2 % in 30 of them (228 cells, projection to 88, six layers, 21 rows, 57 steps: 741 us one after the
 // other, as chosen, 623 stacked).  Taking the stacked launch as long as it costs no more than 7 % per layer, for the sake of the
 // launches, cost 4 % over the 585 of them with up to 256 cells; with the host waiting for each call it was no better.
 bool stack_chosen(const lstm_int_model *m, int64_t T, int64_t B) {
