@@ -351,15 +351,16 @@ def main():
     if model.device_status() != 0:
         sys.exit(f"bench.py: device status {model.device_status()} after the profiled loop; the timing is void")
     persistent = prof["cell"]["launches"] == 0  # the per-step path launches a cell kernel per step
-    # W x computed in the recurrent launches, of all layers at once or (small layers and batches) of one
-    stacked = persistent and prof["input_gemm"]["launches"] == 0
+    # W x computed in the recurrent launches, of all layers at once (stacked) or, small layers and batches, of one
+    own_input = persistent and prof["input_gemm"]["launches"] == 0
+    stacked = own_input and L > 1 and prof["recurrent"]["launches"] == args.steps
     work = {}
     for q in quants:
         for k, v in algorithmic_work(q, B, T, persistent).items():
             e = work.setdefault(k, {"ops": 0.0, "bytes": 0.0, "bytes_resident": 0.0, "launches": 0})
             for f in e:
                 e[f] += v.get(f, v["bytes"] if f == "bytes_resident" else 0)
-    if stacked:
+    if own_input:
         # the one kernel does the input GEMM's work too: its ops, its weights once per step, and x; no W x terms
         # go through memory (the 2 B G N bytes per step that the recurrent figure counts for reading them stay in,
         # as the price of comparing both ways against the same figure)
@@ -398,7 +399,7 @@ def main():
     roof.update({"kernel": dominant, "avg_launch_us": d["avg_us"], "traffic": None,
                  "path": "stacked" if stacked else ("persistent" if persistent else "per-step"), "kernels": kernels})
     tpath = os.path.join(ROOT, "profiles", "hbm_traffic.json")
-    if os.path.exists(tpath) and not (args.batch or args.seq_len or stacked):  # HBM bytes per launch from rocprofv3 --pmc runs (see profiles/)
+    if os.path.exists(tpath) and not (args.batch or args.seq_len or own_input):  # HBM bytes per launch from rocprofv3 --pmc runs (see profiles/)
         rec = json.load(open(tpath)).get(args.config, {}).get(dominant)
         if rec:
             roof["traffic"] = rec["bytes_per_launch"]
