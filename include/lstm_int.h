@@ -285,8 +285,10 @@ int lstm_int_forward_bidirectional(const lstm_int_model *fwd, const lstm_int_mod
  *           run in a variant of the persistent kernel that works on groups of
  *           16 rows (more compute units busy, half the arithmetic per
  *           workgroup and step), of 4 rows where that still fits one launch, or, for
- *           layers of up to 256 cells, one workgroup per 4 rows; 2 = groups of
- *           16 rows only; 0 = always groups of 32 or 64 rows.
+ *           layers of up to 256 cells, one workgroup per row (up to 256 rows,
+ *           both directions of a bidirectional layer together) or per 4 rows (up
+ *           to 2048 rows, 1024 beyond 128 cells); 2 = groups of 16 rows only;
+ *           0 = always groups of 32 or 64 rows.
  *   "cooperative_launch": the persistent kernel needs all its workgroups (one
  *           per compute unit, up to all of them) on the device at once.
  *           0 (default) = plain launch: that holds when nothing else occupies
@@ -329,8 +331,10 @@ int lstm_int_forward_bidirectional(const lstm_int_model *fwd, const lstm_int_mod
  *           runs; 0 = always the dense product; 2 = as 1, but a forward call in
  *           which such a layer would run the dense product (batch too small or too
  *           large for that kernel, stacked launch, a trace request) fails with
- *           LSTM_INT_E_UNSUPPORTED instead.  The results are the same integers
- *           either way.
+ *           LSTM_INT_E_UNSUPPORTED instead; layers of 641 to 1024 cells without a
+ *           projection, which run large batches in groups of 64 rows otherwise,
+ *           keep groups of 32 for it.  The results are the same integers either
+ *           way.
  *   "reset_status": clears the device status word (see lstm_int_device_status)
  *           after a wait gave up; synchronizes the device.
  *   "phase_timing": nonzero makes workgroup 0 of the persistent kernel add the

@@ -12,7 +12,7 @@ LN, PH, PROJ, CIFG = wl.LAYER_NORM, wl.PEEPHOLE, wl.PROJECTION, wl.CIFG
 
 
 @pytest.mark.parametrize("N,H,flags,B,options", [
-    (64, 64, 0, 3, {"stack": 0}),                               # one workgroup per group of rows
+    (64, 64, 0, 3, {"stack": 0}),                               # one workgroup per row
     (203, 203, LN | PH, 9, {"stack": 0, "rows16": 1}),          # the same, 16 waves
     (320, 320, LN | PH, 9, {"stack": 0, "rows16": 1}),          # groups of four rows over several workgroups
     (520, 130, CIFG | LN | PROJ, 30, {"stack": 0, "rows16": 1}),

@@ -39,7 +39,7 @@ def test_variants_every_tensor(orc, flags):
 
 
 @pytest.mark.parametrize("N,rows16", [
-    (200, 1),  # one workgroup per four rows: launched plainly whatever the option says
+    (200, 1),  # one workgroup per row: launched plainly whatever the option says
     (200, 2),  # groups of 16 rows: 4 workgroups per group, 5 groups
     (200, 0),  # groups of 32 rows: 3 groups
     (320, 1),  # groups of four rows
@@ -135,7 +135,7 @@ def test_persistent_path_every_step_and_layer(orc, flags, rows16):
     checked step by step instead: the sequence runs as one-step calls with h and c
     carried in the state buffers, and after every call the h and c of EVERY layer
     are compared with the oracle's traces of that layer at that step.  rows16 = 2:
-    groups of 16 rows, 1: one workgroup per four rows, 0: groups of 32 rows."""
+    groups of 16 rows, 1: one workgroup per row, 0: groups of 32 rows."""
     import torch
 
     print(f"every step and layer: flags={flags} rows16={rows16}", flush=True)
@@ -430,11 +430,16 @@ def test_longest_sequences(orc, T, flags, with_state, rows16):
     the kernels with groups of 16 or 32 rows count up over the launch); one step
     more and the layer runs in two pieces, h and c carried from one to the next (c
     through the caller's state buffer, or through the workspace when there is
-    none).  On one workgroup per four rows (rows16 = 1), and on groups of 16 (2)
+    none).  On one workgroup per row (rows16 = 1), and on groups of 16 (2)
     and of 32 rows (0), of two workgroups, so the words are in use."""
     print(f"T {T} rows16 {rows16}", flush=True)
     layers, x = wl.make_custom([16], 128, 64, flags, 3, T, seed=21)
     run_and_compare(orc, layers, x, f"long{T}", trace=False, with_state=with_state, options={"rows16": rows16})
+
+
+def test_longest_sequence_on_one_workgroup_per_four_rows(orc):
+    layers, x = wl.make_custom([4], 40, 40, wl.LAYER_NORM, 257, (1 << 14) + 1, seed=24)
+    run_and_compare(orc, layers, x, "long_solo", trace=False, rows=[0, 3, 255, 256])
 
 
 @pytest.mark.parametrize("T,with_state", [(1 << 14, True), ((1 << 14) + 1, True), ((1 << 14) + 1, False)])
@@ -475,7 +480,7 @@ def test_rows16_kernel(orc, case, rows16):
 @pytest.mark.parametrize("flags", VARIANTS)
 def test_rows16_variants(orc, flags, rows16):
     """Every variant on the persistent path at a small ragged batch, two layers:
-    in groups of 16 rows (rows16 = 2), one workgroup per four rows (1) and in
+    in groups of 16 rows (rows16 = 2), one workgroup per row (1) and in
     groups of 32 rows (0)."""
     H = 136 if flags & wl.PROJECTION else 200
     _rows16(orc, ([72, H], 200, H, flags, 37, 5, None), rows16)
@@ -503,7 +508,7 @@ def _rows16(orc, case, rows16):
 
 
 @pytest.mark.parametrize("stack,rows16,N", [
-    (0, 1, 200), (2, 1, 200),  # layer after layer on one workgroup per four rows; all layers in one launch
+    (0, 1, 200), (2, 1, 200),  # layer after layer on one workgroup per row; all layers in one launch
     (0, 2, 200), (0, 0, 200),  # groups of 16, of 32 rows
     (0, 1, 320),  # groups of four rows
 ])

@@ -1,6 +1,7 @@
-"""Layers of 129 to 256 cells in one workgroup of 16 waves, per row up to 256 rows and per four rows beyond: widths that end within a wave's block of cells, leave waves without
-cells, or fill all of them; every combination of coupled gates, peephole and layer norm; projections up to the workgroup's
-width; gate values beyond the part of the tables that LDS holds; a second layer, and rows that are not a multiple of four."""
+"""Layers of 129 to 256 cells in one workgroup of 16 waves, per row up to 256 rows and per four rows beyond: widths that end within
+a wave's block of cells, leave waves without cells, or fill all of them; every combination of coupled gates, peephole and layer
+norm; projections up to the workgroup's width; gate values beyond the part of the tables that LDS holds; a second layer, and rows
+that are not a multiple of four."""
 import numpy as np
 import pytest
 
