@@ -81,7 +81,7 @@ def test_both_directions_in_one_launch_of_the_16_row_kernel(orc, proj, variant, 
 @pytest.mark.parametrize("proj", [0, 1])
 @pytest.mark.parametrize("variant", range(8))
 @pytest.mark.parametrize("B", [6, 130])
-def test_both_directions_in_one_launch_of_the_one_workgroup_kernels(orc, B, variant, proj, N):
+def test_both_directions_in_one_launch_of_the_one_workgroup_kernel(orc, B, variant, proj, N):
     """Every instantiation of the kernels without exchange (CIFG, peephole, layer norm, projection) on both directions: a workgroup
     per row (6 rows), a workgroup per four rows, the last of each direction with two (130, beyond 256 rows of both together)."""
     H = N - 7 if proj else N
