@@ -838,8 +838,9 @@ struct RecPlan {
 };
 
 int64_t sync_bytes(int groups);
-// share: launches' worth of groups that are to fit one launch (2: both directions of a bidirectional layer)
-RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1) {
+// share: launches' worth of groups that are to fit one launch (2: both directions of a bidirectional layer); per_row: small
+// layers may take a workgroup per row
+RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1, bool per_row = true) {
   const LayerHost &h = m->host[l];
   const LayerDev &d = m->dev[l];
   const bool proj = h.projection();
@@ -913,7 +914,7 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1) {
     // With a wide projection the tables of some cell formats leave the form per row no room for the terms of all steps (256 cells,
     // 224 outputs, layer norm, 12 steps, 64 rows, us: groups of four rows over several workgroups 57, per row without them 45), or
     // none at all.  (LDS for W x in the launch is enough for a launch without, the pieces of a long sequence among them.)
-    const bool small = row_supported(h.N, h.H, (int)h.flags, B * share);
+    const bool small = per_row && row_supported(h.N, h.H, (int)h.flags, B * share);
     p.row = small && row_lds_bytes(r1, false) <= 160 * 1024;
     // Then groups of four rows over several workgroups are ahead with layer norm alone, else one workgroup per four rows: 256 cells
     // and outputs, 64 rows, 100 steps 363 us against 376, coupled gates 352 against 327, peephole 466 against 440, both 444, 384.
@@ -1440,6 +1441,15 @@ int lstm_int_forward_static(const lstm_int_model *m, const int8_t *x, int32_t T,
 // itself -- no flipped copies of x and y.  A direction alone would leave at least half of the compute units idle there,
 // and a step costs the same whether its neighbours work or not.  Otherwise the two directions run one after the other.
 // (One layer of 512 cells, 64 rows, 100 steps: 1.00 ms one after the other, 0.52 ms side by side.)
+// A cell format may leave one direction no room for a workgroup per row (plan_rec): then neither has one.
+static void plan_pair(const lstm_int_model *f, const lstm_int_model *b, int l, int T, int B, RecPlan &pf, RecPlan &pb) {
+  pf = plan_rec(f, l, T, B, 2);
+  pb = plan_rec(b, l, T, B, 2);
+  if (pf.row == pb.row) return;
+  pf = plan_rec(f, l, T, B, 2, false);
+  pb = plan_rec(b, l, T, B, 2, false);
+}
+
 static bool pair_chosen(const lstm_int_model *f, const lstm_int_model *b, int32_t T, int32_t B) {
   const size_t L = f->host.size();
   if (b->host.size() != L || f->device < 0 || b->device != f->device || T < 1 || B < 1 || T > 1 << 14 || f->path == 1 ||
@@ -1449,7 +1459,8 @@ static bool pair_chosen(const lstm_int_model *f, const lstm_int_model *b, int32_
     const LayerHost &hf = f->host[l], &hb = b->host[l];
     if (hf.N != hb.N || hf.H != hb.H || hf.flags != hb.flags || hf.I != hb.I) return false;
     if ((f->sparse == 2 && f->dev[l].R2s) || (b->sparse == 2 && b->dev[l].R2s)) return false;
-    const RecPlan pf = plan_rec(f, (int)l, T, B, 2), pb = plan_rec(b, (int)l, T, B, 2);
+    RecPlan pf, pb;
+    plan_pair(f, b, (int)l, T, B, pf, pb);
     if (!pf.ok || !pb.ok || !pf.use16 || !pb.use16 || pf.solo != pb.solo || pf.row != pb.row || pf.quad != pb.quad) return false;
     if (!pf.solo && pf.groups + pb.groups > 8 * (32 / pf.ra.GS)) return false;
   }
@@ -1491,7 +1502,8 @@ static int forward_pair(lstm_int_model *const (&m)[2], const int8_t *x, int32_t 
     RecArgs2 pair;
     RowInput input[2];  // W x in the recurrent launch itself
     memset(input, 0, sizeof(input));
-    RecPlan plan[2] = {plan_rec(m[0], l, T, B, 2), plan_rec(m[1], l, T, B, 2)};
+    RecPlan plan[2];
+    plan_pair(m[0], m[1], l, T, B, plan[0], plan[1]);
     const int groups = plan[0].groups + plan[1].groups;
     bool own_input = plan[0].row_own && plan[1].row_own;  // of both or neither
     for (int i = 0; i < 2; ++i) {

@@ -119,3 +119,29 @@ def test_wide_projections_in_every_cell_format(orc, H, flags, m_c, T, own):
     assert model.device_status() == 0 and launches["recurrent"] == 1 and launches["cell"] == 0
     assert launches["input_gemm"] == 1 - own
     assert_equal("y", y, np.asarray(orc.forward(oracle, xq.cpu().numpy())))
+
+
+@pytest.mark.parametrize("B,T", [(5, 7), (5, 12), (70, 20)])
+def test_two_directions_of_unlike_cell_formats(orc, B, T):
+    """A format whose tables leave one direction no room for a workgroup per row: both run in one launch all the same."""
+    import torch
+
+    others = []
+    layers, x = wl.make_custom([48], 256, 256, LN | PROJ, B, T, seed=5, weight_param=0.06)
+    back, _ = wl.make_custom([48], 256, 256, LN | PROJ, B, T, seed=6, weight_param=0.06)
+    xd = calibrate_on_gpu(layers, x)
+    calibrate_on_gpu(back, x)
+    layers[0].c_absmax = 0.9 * 2.0 ** 2
+    for m_c in (2, 3):
+        back[0].c_absmax = 0.9 * 2.0 ** m_c
+        fwd, bwd = binding.prepare(layers), binding.prepare(back)
+        bwd.set_option("reverse", 1)
+        xq = fwd.quantize_input(xd)
+        bwd.profile_begin()
+        y = binding.forward_bidirectional(fwd, bwd, xq).cpu().numpy()
+        others.append(bwd.profile_end()["other"]["launches"])
+        assert fwd.device_status() == 0 and bwd.device_status() == 0
+        xs = xq.cpu().numpy()
+        assert_equal("forward", y[:, :, :256], np.asarray(orc.forward(orc.prepare(layers), xs)))
+        assert_equal("backward", y[:, :, 256:], np.asarray(orc.forward(orc.prepare(back), xs, reverse=True)))
+    assert others[0] == others[1], others  # a direction by itself has its input and its output turned around
