@@ -277,6 +277,15 @@ int lstm_int_forward_bidirectional(const lstm_int_model *fwd, const lstm_int_mod
  *           than one layer after the other (small batches: one-step calls,
  *           sequences at up to about 64 rows); 2 = wherever it can run.
  *           Calls with a trace or with "reverse" run layer after layer.
+ *           (0 turns "row_stack" off too.)
+ *   "row_stack": models of 2 to 6 layers of up to 256 cells and outputs and of one
+ *           variant can run in ONE launch with a workgroup per (layer, batch row),
+ *           up to 256 of them: a layer works on a piece of the sequence, up to 16
+ *           steps, while the layer below works on the next one; in a bidirectional
+ *           call both directions (of up to 3 layers) together.  0 = never, 1
+ *           (default) = where it is expected to be the fastest way, 2 = wherever it
+ *           can run.  Calls with a trace run layer after layer.
+ *   "row_stack_piece": steps of a piece, 1 to 16; 0 (default) = chosen.
  *   "stack_step_ns", "stack_prefetch_kb", "flag_sleep": knobs of the stacked
  *           launch: expected time of one item (for the choice above), KB of a
  *           layer's W requested ahead of each item, pause between polls of the
@@ -386,7 +395,8 @@ int lstm_int_phase_ticks(const lstm_int_model *model, int64_t ticks[16]);
  * Per-kernel device time of the forward calls made while profiling is on,
  * measured with HIP events on the stream the kernels run on.
  * lstm_int_profile_begin resets the counters and makes forward record events
- * (created as the launches need them, any number per call);
+ * (created as the launches need them, any number per call; a launch of the
+ * kernel with a workgroup per row that runs several layers counts once for each);
  * lstm_int_profile_end synchronizes that stream, fills, per kernel class k
  * (LSTM_INT_K_*), launches[k] and total_ms[k], and destroys the events.
  * Profiling adds host work to forward; throughput is measured with it off.

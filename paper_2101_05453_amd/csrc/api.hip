@@ -7,6 +7,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <optional>
 #include <vector>
 
 #include "kernels.h"
@@ -110,7 +111,7 @@ struct Profile {
   bool on = false;
   hipStream_t stream = nullptr;
   std::vector<hipEvent_t> ev;  // pairs (start, stop)
-  std::vector<int> cls;
+  std::vector<int> cls, layers;  // of each pair: kernel class, layers that the launch runs and is counted for
   size_t used = 0;  // pairs in use
   bool failed = false;  // an event could not be created: the times would be incomplete
   void release() {
@@ -118,6 +119,7 @@ struct Profile {
       if (e) (void)hipEventDestroy(e);
     ev.clear();
     cls.clear();
+    layers.clear();
     used = 0;
   }
 };
@@ -137,6 +139,8 @@ struct lstm_int_model {
   int cooperative = 0;  // 1: the persistent kernel is launched cooperatively
   int rows16 = 1;       // 1, 2: batches that fit one launch of the 16-row kernel take it; 1: also the one-workgroup and the four-row kernel
   int sparse = 1;       // 1: layers whose recurrent weights are 2:4 run R h on the sparse MFMA (32-row kernel)
+  int row_stack = 1;    // several small layers in one launch, a workgroup per (layer, row): 0 never, 1 where it is expected to be faster, 2 wherever it can run
+  int row_stack_piece = 0;  // steps that a layer hands on at a time there, 0 = chosen
   int stack = 1;        // stacked launch (one layer per XCD): 0 never, 1 where it is expected to be faster, 2 wherever it can run
   int flag_sleep = 2;   // stacked launch: pause between two polls of the layer below's flag, x 64 clocks
   double stack_step_us = 0;  // expected time of one (step, row tile) item of the stacked launch; 0: stacked_us's own
@@ -234,7 +238,7 @@ StackPlan plan_stack(const lstm_int_model *m, int64_t T, int64_t B) {
   return w;
 }
 
-bool stack_chosen(const lstm_int_model *m, int64_t T, int64_t B);  // below plan_rec, which it asks
+size_t way_bytes(const lstm_int_model *m, int64_t T, int64_t B);  // workspace of a launch of several layers, 0: one after the other
 
 Requant make_requant(const int32_t *M, const int32_t *e, int first, int count, int cols_per_gate,
                      int zp) {
@@ -280,7 +284,7 @@ struct Timed {
   Profile &p;
   hipStream_t s;
   bool active;
-  Timed(Profile &prof, hipStream_t stream, int cls) : p(prof), s(stream), active(false) {
+  Timed(Profile &prof, hipStream_t stream, int cls, int layers = 1) : p(prof), s(stream), active(false) {
     if (!p.on) return;
     // events are created as launches need them (any number of launches per call) and freed by profile_end
     if ((p.used + 1) * 2 > p.ev.size()) {
@@ -293,8 +297,10 @@ struct Timed {
       p.ev.push_back(e0);
       p.ev.push_back(e1);
       p.cls.push_back(0);
+      p.layers.push_back(1);
     }
     active = true;
+    p.layers[p.used] = layers;
     p.cls[p.used] = cls;
     p.stream = s;
     (void)hipEventRecord(p.ev[2 * p.used], s);
@@ -685,8 +691,8 @@ size_t lstm_int_workspace_bytes(const lstm_int_model *m, int32_t T, int32_t B) {
   if (!m || T < 0 || B < 0 || m->host.empty()) return 0;
   if (T == 0 || B == 0) return 256;
   // a call with a trace runs the layers one after the other, so that layout always has to fit
-  const size_t seq = plan_workspace(m, T, B).total;
-  return m->device >= 0 && stack_chosen(m, T, B) ? std::max(seq, plan_stack(m, T, B).total) : seq;
+  const size_t bytes = plan_workspace(m, T, B).total;
+  return m->device >= 0 ? std::max(bytes, way_bytes(m, T, B)) : bytes;
 }
 
 }  // extern "C"
@@ -700,7 +706,7 @@ void plant_misplaced(const lstm_int_model *m, hipStream_t s, uint8_t *sync) {
     launch_fill_i16(s, reinterpret_cast<int16_t *>(sync + 256 * xcd + 12), 1, 1);
 }
 
-// All layers in one launch (stack_kernel.inc.h).  The caller has checked stack_chosen and the workspace size.
+// All layers in one launch (stack_kernel.inc.h).  The caller has checked choose_way and the workspace size.
 int forward_stack(lstm_int_model *m, const int8_t *x, int32_t T, int32_t B, int8_t *y, int8_t *h_state,
                   int16_t *c_state, uint8_t *wsb, hipStream_t s) {
   const StackPlan sp = plan_stack(m, T, B);
@@ -837,10 +843,25 @@ struct RecPlan {
   bool rest32 = false;  // groups of 64 rows: a rest of the batch that fits one launch of groups of 32 runs as those
 };
 
+// The persistent kernels' one-product form of rescale needs shifts in [3, 62].
+bool shifts_ok(const LayerHost &h) {
+  auto ok = [](int e) { return 31 - e >= 3 && 31 - e <= 62; };
+  bool all = ok(h.em) && (!h.projection() || ok(h.ep));
+  for (int g = 4 - h.G; g < 4; ++g) all = all && ok(h.eh[g]) && (!h.layer_norm() || ok(h.eln[g]));
+  for (int j = 4 - h.G; j < 3; ++j) all = all && (!h.peephole() || ok(h.ec[j]));
+  return all;
+}
+
+// For plan_rec: the layer is one of several in one launch (row_kernel.inc.h), the widest of them with `widest` cells or outputs, and
+// a wave has LDS for the W x terms of `term_steps` steps, the workgroup `x_bytes` for inputs
+struct RowStackRoom {
+  int widest, term_steps, x_bytes;
+};
+
 int64_t sync_bytes(int groups);
 // share: launches' worth of groups that are to fit one launch (2: both directions of a bidirectional layer); per_row: small
 // layers may take a workgroup per row
-RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1, bool per_row = true) {
+RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1, bool per_row = true, const RowStackRoom *room = nullptr) {
   const LayerHost &h = m->host[l];
   const LayerDev &d = m->dev[l];
   const bool proj = h.projection();
@@ -877,13 +898,7 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1, bo
   ra.idle_poll_sleep = m->idle_poll_sleep;
   ra.ticks = m->phase_timing ? reinterpret_cast<long long *>(m->status + 16) : nullptr;
   ra.extra_arrivals = m->extra_arrivals;
-  // the kernel's one-product form of rescale needs shifts in [3, 62]; its tables must compress (lut_ok below)
-  auto shift_ok = [](int r) { return r >= 3 && r <= 62; };
-  bool ok = shift_ok(ra.rm) && (!proj || shift_ok(ra.rp));
-  for (int g = 4 - h.G; g < 4; ++g)
-    if (!shift_ok(ra.rh[g]) || (h.layer_norm() && !shift_ok(ra.rln[g]))) ok = false;
-  for (int j = 4 - h.G; j < 3; ++j)
-    if (h.peephole() && !shift_ok(ra.rc[j])) ok = false;
+  const bool ok = shifts_ok(h);  // the tables must compress too (lut_ok below)
   // rec_kernel's tables: the shortest prefixes first (the budget test below uses them)
   auto set_lut = [&](int i, const WideTable &w) {
     int dom = 0, tail = 0;
@@ -915,7 +930,8 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1, bo
     // 224 outputs, layer norm, 12 steps, 64 rows, us: groups of four rows over several workgroups 57, per row without them 45), or
     // none at all.  (LDS for W x in the launch is enough for a launch without, the pieces of a long sequence among them.)
     const bool small = per_row && row_supported(h.N, h.H, (int)h.flags, B * share);
-    p.row = small && row_lds_bytes(r1, false) <= 160 * 1024;
+    p.row = small && (room ? row_stack_lds_bytes(r1, room->widest, room->term_steps, room->x_bytes) : row_lds_bytes(r1, false)) <= 160 * 1024;
+    if (room && !p.row) return p;
     // Then groups of four rows over several workgroups are ahead with layer norm alone, else one workgroup per four rows: 256 cells
     // and outputs, 64 rows, 100 steps 363 us against 376, coupled gates 352 against 327, peephole 466 against 440, both 444, 384.
     const bool spread = small && !p.row && (h.flags & 7) == 4 && quad_supported(h.N, h.H, (int)h.flags, B, share, &g4);
@@ -962,7 +978,7 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1, bo
     ra.R2 = d.R2s;
     ra.sparse = 1;
   }
-  auto lds_need = [&]() { return p.quad ? quad_lds_bytes(ra) : p.row ? row_lds_bytes(ra, p.row_own) : p.solo ? solo_lds_bytes(ra) : p.use16 ? rec16_lds_bytes(ra) : rec_lds_bytes(ra); };
+  auto lds_need = [&]() { return room ? row_stack_lds_bytes(ra, room->widest, room->term_steps, room->x_bytes) : p.quad ? quad_lds_bytes(ra) : p.row ? row_lds_bytes(ra, p.row_own) : p.solo ? solo_lds_bytes(ra) : p.use16 ? rec16_lds_bytes(ra) : rec_lds_bytes(ra); };
   // What LDS is left goes to longer prefixes of the two gate tables, 1 KB at a time in turn: a value
   // beyond the prefix costs the whole group a detour (rec_kernel.inc.h, lookup), and with 24576 entries
   // (|x| < 6 in Q3.12) there is about one per million layer-norm outputs instead of one per thousand.
@@ -1068,26 +1084,214 @@ double stacked_us(const LayerHost &h, int L, int64_t T, int64_t B, double item_u
   return 14.0 + 1.47 * mb + (double)(items + L - 2) * item;
 }
 
-// Whether forward runs T steps of B rows as one stacked launch (a function of the model, its options, T
-// and B only: lstm_int_workspace_bytes and lstm_int_forward must agree): where its expected time is the
-// shorter one.  The formulas are off by 2 to 5 % at the median (12 % with a workgroup of 16 waves per row) and up to 40 % in
-// single calls, but a wrong choice is a close one: over 1034 calls that were not in the fit it costs 0.3 % against the better way
-// of each, and more than 2 % in 30 of them (228 cells, projection to 88, six layers, 21 rows, 57 steps: 741 us one after the
-// other, as chosen, 623 stacked).  Taking the stacked launch as long as it costs no more than 7 % per layer, for the sake of the
-// launches, cost 4 % over the 585 of them with up to 256 cells; with the host waiting for each call it was no better.
-bool stack_chosen(const lstm_int_model *m, int64_t T, int64_t B) {
+// Whether the stacked launch takes T steps of B rows
+bool stack_can_run(const lstm_int_model *m, int64_t T, int64_t B) {
   if (!m->stackable || m->stack == 0 || m->path == 1 || m->reverse) return false;
   int ks = 0;
   const LayerHost &h = m->host[0];
   const int L = (int)m->host.size();
   if (!stack_supported(h.N, h.H, (int)h.flags, m->dev[0].Ipad, L, (int)T, (int)B, &ks) || ks != m->stack_ks) return false;
-  if (kStackFlagsOff + (size_t)L * ((B + 31) / 32) * 128 > kSyncBytes) return false;  // flags behind the statistics words
-  if (m->stack == 2) return true;
+  return kStackFlagsOff + (size_t)L * ((B + 31) / 32) * 128 <= kSyncBytes;  // flags behind the statistics words
+}
+
+InGemmArgs plan_in_gemm(const lstm_int_model *m, int l, int T, int B);
+
+// Layers of up to 256 cells above each other as one launch, a workgroup per (layer, row) (row_kernel.inc.h): of one model, or of the
+// two directions of a bidirectional one, whose layers are independent of each other.
+struct RowStackPlan {
+  bool ok = false;
+  int L = 0, dirs = 0, piece = 0;
+  RowStackRoom room = {0, 0, 0};
+  bool own0 = false;  // W x of the first layer in the launch itself, else by the input GEMM
+  double us = 0;      // expected time
+  size_t xpad = 0, tx[2] = {0, 0}, out[kRowStackLayers], flags = 0, flags_bytes = 0, total = 0;  // workspace; out, by l * dirs + direction
+};
+// Whether layer l has the LDS there, with the shortest tables
+bool row_stack_fits(const lstm_int_model *m, int l, const RowStackRoom &room) {
+  const LayerHost &h = m->host[l];
+  RecArgs a;
+  a.N = h.N; a.H = h.H; a.flags = (int)h.flags;
+  const WideTable *const tables[3] = {&m->wsig3, &m->wtanh3, &m->dev[l].wtanhc};
+  for (int i = 0; i < 3; ++i) {
+    int dom = 0, tail = 0;
+    tables[i]->shortest(&dom, &tail);
+    if (dom == 0) return false;
+    a.lut[i].blob = tables[i]->blob; a.lut[i].sh = tables[i]->sh; a.lut[i].dom = dom; a.lut[i].tail = tail;
+  }
+  return row_stack_lds_bytes(a, room.widest, room.term_steps, room.x_bytes) <= 160 * 1024;
+}
+RowStackPlan plan_row_stack(const lstm_int_model *const *m, int dirs, int64_t T, int64_t B) {
+  RowStackPlan p;
+  const int L = (int)m[0]->host.size();
+  if (L < 2 || L * dirs > kRowStackLayers || T < 1 || B < 1 || T > 1 << 14 || L * dirs * B > 256) return p;
+  const LayerHost &h0 = m[0]->host[0];
+  int widest = 0, deepest = 0;  // deepest: input of a layer above the first
+  for (int i = 0; i < dirs; ++i) {
+    if (m[i]->row_stack == 0 || m[i]->stack == 0 || m[i]->path == 1 || m[i]->rows16 != 1) return p;
+    for (int l = 0; l < L; ++l) {
+      const LayerHost &h = m[i]->host[l];
+      const LayerDev &d = m[i]->dev[l];
+      if (h.N > 256 || h.H > 256 || !d.p2 || !d.p16 || !d.W2f || h.flags != h0.flags || (m[i]->sparse == 2 && d.R2s) || !shifts_ok(h)) return p;
+      for (int g = 4 - h.G; g < 4; ++g)
+        if (31 - h.ex[g] < 3 || 31 - h.ex[g] > 62) return p;
+      widest = std::max(widest, std::max(h.N, h.H));
+      if (l > 0) deepest = std::max(deepest, d.Ipad);
+    }
+  }
+  // Expected time, us, by step, W x of a piece of the sequence, hand-over to the next layer; fitted to 330 calls of 2 to 6 layers of 32 to
+  // 256 cells in all variants, 1 to 100 steps, pieces of 1 to 16 steps, with either input (off by 4 % at the median; the piece that it
+  // picks costs 0.7 % against the best of those timed).
+  const double ln = h0.layer_norm() ? 1 : 0, pr = h0.projection() ? 1 : 0, late_o = h0.layer_norm() && h0.peephole() ? 1 : 0;
+  static const double kCost[3][6] = {{0.60, 0.48, 0.56, 0.13, 1.66, 0.008}, {0.69, 0.67, 0.64, 0.11, 1.86, 0.007}, {1.10, 0.78, 1.00, 0.20, 2.90, 0.010}};
+  const double(&k)[6] = kCost[widest <= 64 ? 0 : widest <= 128 ? 1 : 2];
+  const double step = k[0] + k[1] * ln + k[2] * late_o + k[3] * pr;
+  const double kb = round_up(h0.N, 16) / 256.0, terms = k[4] + k[5] * kb * deepest, terms0 = k[4] + k[5] * kb * m[0]->dev[0].Ipad;
+  const double gemm = 4.6 + m[0]->dev[0].Ipad / 250.0 + 2.3e-6 * T * B * h0.N * dirs + (dirs - 1) * 5.0;  // beyond the launch that clears the words
+  bool refused[2][17] = {};
+  while (!p.ok) {  // the fastest that fits the LDS
+    p.us = 0;
+    for (int own = 0; own < 2; ++own)
+      for (int piece = 1; piece <= std::min<int64_t>(16, T); ++piece) {
+        if (refused[own][piece] || (m[0]->row_stack_piece && piece != std::min<int64_t>(m[0]->row_stack_piece, T))) continue;
+        const double pieces = (double)((T + piece - 1) / piece), t = own ? std::max(terms0, terms) : terms;
+        const double us = 6.0 + 2.0 * (dirs - 1) + T * step + pieces * t + (L - 1) * (piece * step + 3.7 + (T > piece ? step : 0)) + (own ? terms0 : gemm);
+        if (p.us > 0 && us >= p.us) continue;
+        p.us = us;
+        p.piece = piece;
+        p.own0 = own;
+      }
+    if (p.us == 0) return p;
+    p.room = {widest, p.own0 ? p.piece : 2 * p.piece, 16 * (p.own0 ? std::max(deepest, m[0]->dev[0].Ipad) : deepest)};
+    p.ok = true;
+    for (int i = 0; i < dirs && p.ok; ++i)
+      for (int l = 0; l < L && p.ok; ++l) p.ok = row_stack_fits(m[i], l, p.room);
+    if (!p.ok) refused[p.own0][p.piece] = true;
+  }
+  p.L = L;
+  p.dirs = dirs;
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    size_t o = off;
+    off += align256(bytes);
+    return o;
+  };
+  p.xpad = take(((size_t)T * B + 32) * m[0]->dev[0].Ipad);
+  for (int i = 0; i < dirs && !p.own0; ++i) p.tx[i] = take((size_t)T * round_up((int)B, 32) * 4 * m[i]->dev[0].Ncp * 2);
+  for (int l = 0; l < L; ++l)
+    for (int i = 0; i < dirs; ++i) p.out[l * dirs + i] = take(((size_t)T * B + 32) * m[i]->dev[l].Hpad);
+  p.flags_bytes = (size_t)L * dirs * B * kRowFlagWords * 4;
+  p.flags = take(p.flags_bytes);
+  p.total = off;
+  return p;
+}
+
+// How forward runs T steps of B rows: a function of the model, its options, T and B only (lstm_int_workspace_bytes and lstm_int_forward
+// must agree), by the expected times.  The formulas of one layer after the other and of the stacked launch are off by 2 to 5 % at the
+// median (12 % with a workgroup of 16 waves per row) and up to 40 % in single calls, but a wrong choice is a close one: over 1034
+// calls that were not in the fit it costs 0.3 % against the better way of each, and more than 2 % in 30 of them (228 cells,
+// projection to 88, six layers, 21 rows, 57 steps: 741 us one after the other, as chosen, 623 stacked).  Taking the stacked launch as
+// long as it costs no more than 7 % per layer, for the sake of the launches, cost 4 % over the 585 of them with up to 256 cells; with
+// the host waiting for each call it was no better.
+struct Way {
+  bool stacked = false;  // one layer per XCD
+  RowStackPlan rows;     // ok: a workgroup per (layer, row)
+};
+Way choose_way(const lstm_int_model *m, int64_t T, int64_t B) {
+  Way w;
+  w.stacked = stack_can_run(m, T, B);
+  if (w.stacked && m->stack == 2 && m->row_stack != 2) return w;
+  w.rows = plan_row_stack(&m, 1, T, B);
+  if (w.rows.ok && m->row_stack == 2) w.stacked = false;
+  if (!w.stacked && (!w.rows.ok || m->row_stack == 2)) return w;
+  if (m->stack == 2 && w.stacked) {
+    w.rows.ok = false;
+    return w;
+  }
   // no call outgrows the library's own workspace (lstm_int_forward_static) because of this choice
-  if (plan_stack(m, T, B).total > (size_t)LSTM_INT_STATIC_WORKSPACE_BYTES &&
-      plan_workspace(m, T, B).total <= (size_t)LSTM_INT_STATIC_WORKSPACE_BYTES)
-    return false;
-  return stacked_us(h, L, T, B, m->stack_step_us) < sequential_us(h, plan_rec(m, 0, (int)T, (int)B), L, T, B);
+  const size_t limit = (size_t)LSTM_INT_STATIC_WORKSPACE_BYTES;
+  if (plan_workspace(m, T, B).total <= limit) {
+    w.stacked = w.stacked && plan_stack(m, T, B).total <= limit;
+    w.rows.ok = w.rows.ok && w.rows.total <= limit;
+  }
+  if (!w.stacked && !w.rows.ok) return w;
+  const LayerHost &h = m->host[0];
+  const int L = (int)m->host.size();
+  const double seq = sequential_us(h, plan_rec(m, 0, (int)T, (int)B), L, T, B);
+  const double stacked = w.stacked ? stacked_us(h, L, T, B, m->stack_step_us) : seq;
+  w.rows.ok = w.rows.ok && w.rows.us < std::min(seq, stacked);
+  w.stacked = !w.rows.ok && stacked < seq;
+  return w;
+}
+size_t way_bytes(const lstm_int_model *m, const Way &w, int64_t T, int64_t B) {
+  return w.rows.ok ? w.rows.total : w.stacked ? plan_stack(m, T, B).total : 0;
+}
+size_t way_bytes(const lstm_int_model *m, int64_t T, int64_t B) { return way_bytes(m, choose_way(m, T, B), T, B); }
+
+// All layers of one or two models in one launch.  y: [T, B, ldy], direction i at column y_col[i], or NULL: left in the last `out`.
+int forward_row_stack(lstm_int_model *const *m, const RowStackPlan &p, const int8_t *x, int ldx, int32_t T, int32_t B, int8_t *y, int ldy,
+                      const int *y_col, int8_t *const *h_state, int16_t *const *c_state, uint8_t *wsb, hipStream_t s) {
+  const int L = p.L, dirs = p.dirs;
+  int *const flags = reinterpret_cast<int *>(wsb + p.flags);
+  RowStackArgs args;
+  memset(&args, 0, sizeof(args));
+  size_t lds = 0;
+  if (p.own0) {
+    Timed t(m[0]->prof, s, LSTM_INT_K_OTHER);
+    launch_fill_i16(s, reinterpret_cast<int16_t *>(flags), (int64_t)p.flags_bytes / 2, 0);
+  }
+  for (int i = 0; i < dirs; ++i) {
+    size_t h_off = 0, c_off = 0;
+    for (int l = 0; l < L; ++l) {
+      const LayerHost &h = m[i]->host[l];
+      const LayerDev &d = m[i]->dev[l];
+      const int at = l * dirs + i;
+      const RecPlan plan = plan_rec(m[i], l, T, B, L * dirs, true, &p.room);
+      if (!plan.ok || !plan.row) return LSTM_INT_E_DEVICE;
+      RecDirArgs ra;
+      memset(&ra, 0, sizeof(ra));
+      static_cast<RecArgs &>(ra) = plan.ra;
+      lds = std::max(lds, row_stack_lds_bytes(ra, p.room.widest, p.room.term_steps, p.room.x_bytes));
+      RowInput &in = args.in[at];
+      InGemmArgs ga = plan_in_gemm(m[i], l, T, B);
+      ga.A = l == 0 ? x : reinterpret_cast<const int8_t *>(wsb + p.out[at - dirs]);
+      ga.lda = l == 0 ? ldx : m[i]->dev[l - 1].Hpad;
+      ga.cols = l == 0 ? std::min(ldx, d.Ipad) : 0;
+      if (!in_gemm_ws_supported(ga)) return LSTM_INT_E_DEVICE;
+      row_set_input(in, ga);
+      if (l == 0 && !p.own0) {
+        in.x = nullptr;
+        ga.tx2 = reinterpret_cast<int4 *>(wsb + p.tx[i]);
+        ga.has_init = 1;
+        if (i == 0) {
+          ga.init.sync = reinterpret_cast<int4 *>(flags);
+          ga.init.sync_vec = (int64_t)p.flags_bytes / 16;
+        }
+        Timed t(m[i]->prof, s, LSTM_INT_K_INPUT_GEMM);
+        launch_in_gemm_ws(s, ga, m[i]->num_cus);
+      }
+      in.h_src = in.h_dst = h_state[i] ? h_state[i] + h_off : nullptr;
+      in.piece = p.piece;
+      in.term_steps = p.room.term_steps;
+      in.x_bytes = p.room.x_bytes;
+      in.ready = l > 0 ? flags + (size_t)(at - dirs) * B * kRowFlagWords : nullptr;
+      in.done = l + 1 < L ? flags + (size_t)at * B * kRowFlagWords : nullptr;
+      in.spin_limit = m[i]->spin_limit;
+      in.never = m[i]->extra_arrivals ? 1 << 20 : 0;
+      ra.tx2 = l == 0 && !p.own0 ? ga.tx2 : nullptr;
+      ra.out = reinterpret_cast<int8_t *>(wsb + p.out[at]);
+      ra.y = l == L - 1 && y ? y + y_col[i] : nullptr;
+      ra.ldy = ldy;
+      ra.rev = dirs == 2 ? i : 0;
+      ra.c_in = ra.c_out = c_state[i] ? c_state[i] + c_off : nullptr;
+      row_stack_layer(args.rec.d[at], ra);
+      h_off += (size_t)B * h.H;
+      c_off += (size_t)B * h.N;
+    }
+  }
+  Timed t0(m[0]->prof, s, LSTM_INT_K_RECURRENT, L);
+  std::optional<Timed> t1;  // the other direction's model counts its layers too
+  if (dirs == 2) t1.emplace(m[1]->prof, s, LSTM_INT_K_RECURRENT, L);
+  return launch_row_stack(s, args, L * dirs, (int)m[0]->host[0].flags, p.room.widest, lds) == hipSuccess ? LSTM_INT_OK : LSTM_INT_E_DEVICE;
 }
 
 // Synchronization scratch of a launch (plan_workspace's `sync`): barrier counters and placement words, statistics words.
@@ -1144,16 +1348,41 @@ int lstm_int_forward(const lstm_int_model *cm, const int8_t *x, int32_t T, int32
   if (trace && (trace->layer < 0 || trace->layer >= L)) return LSTM_INT_E_INVALID_ARG;
   if ((int64_t)T * B > (int64_t)1 << 30) return LSTM_INT_E_UNSUPPORTED;
   const Workspace ws = plan_workspace(m, T, B);
-  if (workspace_bytes < lstm_int_workspace_bytes(m, T, B) || (reinterpret_cast<uintptr_t>(workspace) & 255))
+  const Way way = choose_way(m, T, B);
+  if (workspace_bytes < std::max(ws.total, way_bytes(m, way, T, B)) || (reinterpret_cast<uintptr_t>(workspace) & 255))
     return LSTM_INT_E_WORKSPACE;
   if (hipSetDevice(m->device) != hipSuccess) return LSTM_INT_E_DEVICE;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   uint8_t *wsb = static_cast<uint8_t *>(workspace);
   // every layer alike, no dump asked for: all layers in one launch, one layer per XCD, where that is faster
-  if (!trace && stack_chosen(m, T, B) && (reinterpret_cast<uintptr_t>(y) & 3) == 0 &&
+  if (!trace && way.stacked && (reinterpret_cast<uintptr_t>(y) & 3) == 0 &&
       (reinterpret_cast<uintptr_t>(h_state) & 3) == 0 && (reinterpret_cast<uintptr_t>(c_state) & 1) == 0) {
     const int rc = forward_stack(m, x, T, B, y, h_state, c_state, wsb, s);
     if (rc != LSTM_INT_E_UNSUPPORTED) return rc;  // the LDS budget did not fit: the layers run one after the other
+  }
+  if (!trace && way.rows.ok && (reinterpret_cast<uintptr_t>(y) & 3) == 0) {
+    const RowStackPlan &rows_plan = way.rows;
+    const int I = m->host[0].I, Ip = m->dev[0].Ipad, H = m->host.back().H;
+    const bool rev = m->reverse != 0;
+    InGemmArgs g0 = plan_in_gemm(m, 0, T, B);
+    g0.A = x; g0.lda = I;
+    const bool in_place = !rev && in_gemm_ws_supported(g0);
+    int8_t *xp = reinterpret_cast<int8_t *>(wsb + rows_plan.xpad);
+    if (!in_place) {
+      Timed t(m->prof, s, LSTM_INT_K_OTHER);
+      if (rev)
+        launch_flip_rows_i8(s, x, I, xp, Ip, T, B, I, 0);
+      else
+        launch_copy_rows_i8(s, x, I, xp, Ip, T * B, I, 0);
+    }
+    const int y_col = 0;
+    const int rc = forward_row_stack(&m, rows_plan, in_place ? x : xp, in_place ? I : Ip, T, B, rev ? nullptr : y, H, &y_col, &h_state, &c_state, wsb, s);
+    if (rc != LSTM_INT_OK) return rc;
+    if (rev) {
+      Timed t(m->prof, s, LSTM_INT_K_OTHER);
+      launch_flip_rows_i8(s, reinterpret_cast<int8_t *>(wsb + rows_plan.out[rows_plan.L - 1]), m->dev.back().Hpad, y, H, T, B, H, 0);
+    }
+    return hipGetLastError() == hipSuccess ? LSTM_INT_OK : LSTM_INT_E_DEVICE;
   }
   int16_t *tx = reinterpret_cast<int16_t *>(wsb + ws.tx);
   int16_t *th = reinterpret_cast<int16_t *>(wsb + ws.th);
@@ -1598,10 +1827,24 @@ static size_t bidi_pair_bytes(const lstm_int_model *f, const lstm_int_model *b, 
   return plan_workspace(f, T, B).total + plan_workspace(b, T, B).total;
 }
 
+// Stacks of small layers: both directions and all layers in one launch
+static bool row_stack_pair_chosen(const lstm_int_model *f, const lstm_int_model *b, int32_t T, int32_t B, RowStackPlan *plan) {
+  const size_t L = f->host.size();
+  if (b->host.size() != L || f->device < 0 || b->device != f->device || f->host[0].I != b->host[0].I) return false;
+  const lstm_int_model *const m[2] = {f, b};
+  *plan = plan_row_stack(m, 2, T, B);
+  if (!plan->ok) return false;
+  if (f->row_stack == 2) return true;
+  // against a launch per layer for both directions: these shapes nearly always have it
+  return plan->us < sequential_us(f->host[0], plan_rec(f, 0, T, B, 2), (int)L, T, B);
+}
+
 size_t lstm_int_bidirectional_workspace_bytes(const lstm_int_model *f, const lstm_int_model *b, int32_t T, int32_t B) {
   if (!f || !b || T < 0 || B < 0 || f->host.empty() || b->host.empty()) return 0;
-  const size_t seq = bidi_sequential_bytes(f, b, T, B);
-  return pair_chosen(f, b, T, B) ? std::max(seq, bidi_pair_bytes(f, b, T, B)) : seq;
+  size_t bytes = bidi_sequential_bytes(f, b, T, B);
+  if (pair_chosen(f, b, T, B)) bytes = std::max(bytes, bidi_pair_bytes(f, b, T, B));
+  RowStackPlan plan;
+  return row_stack_pair_chosen(f, b, T, B, &plan) ? std::max(bytes, plan.total) : bytes;
 }
 
 int lstm_int_forward_bidirectional(const lstm_int_model *f, const lstm_int_model *b, const int8_t *x, int32_t T,
@@ -1620,6 +1863,26 @@ int lstm_int_forward_bidirectional(const lstm_int_model *f, const lstm_int_model
     return LSTM_INT_E_WORKSPACE;
   const int Hf = f->host.back().H, Hb = b->host.back().H;
   hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
+  RowStackPlan rows_plan;
+  if (row_stack_pair_chosen(f, b, T, B, &rows_plan) && workspace_bytes >= rows_plan.total) {
+    if (hipSetDevice(f->device) != hipSuccess) return LSTM_INT_E_DEVICE;
+    lstm_int_model *const m[2] = {const_cast<lstm_int_model *>(f), const_cast<lstm_int_model *>(b)};  // profiling counters only
+    uint8_t *wsb = static_cast<uint8_t *>(workspace);
+    const int I = f->host[0].I, Ip = f->dev[0].Ipad, y_col[2] = {0, Hf};
+    InGemmArgs g0[2] = {plan_in_gemm(m[0], 0, T, B), plan_in_gemm(m[1], 0, T, B)};
+    g0[0].A = g0[1].A = x;
+    g0[0].lda = g0[1].lda = I;
+    const bool in_place = in_gemm_ws_supported(g0[0]) && in_gemm_ws_supported(g0[1]);
+    int8_t *xp = reinterpret_cast<int8_t *>(wsb + rows_plan.xpad);
+    if (!in_place) {  // one copy serves both
+      Timed t(m[0]->prof, s, LSTM_INT_K_OTHER);
+      launch_copy_rows_i8(s, x, I, xp, Ip, T * B, I, 0);
+    }
+    int8_t *const hs[2] = {h_state_fwd, h_state_bwd};
+    int16_t *const cs[2] = {c_state_fwd, c_state_bwd};
+    const int rc = forward_row_stack(m, rows_plan, in_place ? x : xp, in_place ? I : Ip, T, B, y, Hf + Hb, y_col, hs, cs, wsb, s);
+    return rc != LSTM_INT_OK ? rc : hipGetLastError() == hipSuccess ? LSTM_INT_OK : LSTM_INT_E_DEVICE;
+  }
   if ((int64_t)T * B <= (int64_t)1 << 30 && pair_chosen(f, b, T, B) && workspace_bytes >= bidi_pair_bytes(f, b, T, B)) {
     if (hipSetDevice(f->device) != hipSuccess) return LSTM_INT_E_DEVICE;
     lstm_int_model *const m[2] = {const_cast<lstm_int_model *>(f), const_cast<lstm_int_model *>(b)};  // profiling counters only
@@ -1663,6 +1926,16 @@ int lstm_int_set_option(lstm_int_model *m, const char *key, int64_t value) {
   if (!strcmp(key, "stack")) {
     if (value < 0 || value > 2) return LSTM_INT_E_INVALID_ARG;
     m->stack = (int)value;
+    return LSTM_INT_OK;
+  }
+  if (!strcmp(key, "row_stack")) {
+    if (value < 0 || value > 2) return LSTM_INT_E_INVALID_ARG;
+    m->row_stack = (int)value;
+    return LSTM_INT_OK;
+  }
+  if (!strcmp(key, "row_stack_piece")) {
+    if (value < 0 || value > 16) return LSTM_INT_E_INVALID_ARG;
+    m->row_stack_piece = (int)value;
     return LSTM_INT_OK;
   }
   if (!strcmp(key, "stack_prefetch_kb")) {
@@ -1782,7 +2055,7 @@ int lstm_int_profile_end(lstm_int_model *m, int64_t launches[LSTM_INT_K_COUNT],
       rc = LSTM_INT_E_DEVICE;
       break;
     }
-    launches[p.cls[i]] += 1;
+    launches[p.cls[i]] += p.layers[i];
     total_ms[p.cls[i]] += ms;
   }
   p.release();  // no event outlives the measurement

@@ -264,11 +264,56 @@ struct RowInput {  // W x in the launch itself instead of tx2 (x == NULL): then 
   RescaleHi rs[4];
   const int8_t *h_src;  // [B, H] or NULL (the zero point)
   int8_t *h_dst;        // [B, H] or NULL: h of the last step
+  // launches of several layers (RowStackArgs) alone
+  int piece, term_steps;  // steps of a piece of the sequence, at most 16, and steps of terms a wave has room for in LDS
+  int x_bytes;            // LDS for x of a piece: 1 KB for each 64-byte k step of the deepest layer that computes W x
+  const int *ready;       // words of the layer below, or NULL: x is complete
+  int *done;              // [B] words of kRowFlagWords: steps of the row that are in `out`; NULL: nobody reads `out` in this launch
+  int spin_limit, never;  // never: 0; tests: steps that will not come are waited for
 };
 struct RowArgs {
   RecArgs2 rec;
   RowInput in[2];
 };
+// Several layers in one launch, as a wavefront over layers and time: a workgroup per (layer, row).  A layer here is what row_kernel reads of
+// RecDirArgs (of which eight do not fit a kernel's arguments); in[l].x = NULL: W x from tx2.
+struct RowLayer {
+  int T, B, N, H, Hpad, Bp, Ncp, ks16, npadp, ldy, rev, m_c, pre_h;
+  const int4 *R2h;
+  const int32_t *bh4;
+  const int16_t *Lq4;
+  const int32_t *qb4;
+  const int16_t *Pq3;
+  int32_t Mh[4], rh[4];
+  int32_t Mc[3], rc[3];
+  int32_t Mln[4], rln[4];
+  int32_t Mm, rm, zp_m;
+  int32_t Mp, rp, zp_h;
+  LutWide lut[3];
+  const int8_t *Wp2;
+  const int32_t *bp2;
+  const int4 *tx2;
+  const int8_t *h0;
+  int8_t *out, *y;
+  const int16_t *c_in;
+  int16_t *c_out;
+  int *status;
+};
+constexpr int kRowStackLayers = 6;  // what 4 KB of arguments hold
+constexpr int kRowFlagWords = 32;   // a line for each
+struct RowStackArgs {
+  struct {
+    RowLayer d[kRowStackLayers];
+  } rec;
+  RowInput in[kRowStackLayers];
+};
+static_assert(sizeof(RowStackArgs) <= 4096, "kernel arguments");
+void row_stack_layer(RowLayer &to, const RecDirArgs &from);
+// LDS of a launch, for one of its layers; widest: most cells or outputs of a layer
+size_t row_stack_lds_bytes(const RecArgs &a, int widest, int term_steps, int x_bytes);
+// flags: the layers'; lds: the most that one of them needs
+hipError_t launch_row_stack(hipStream_t s, const RowStackArgs &a, int layers, int flags, int widest, size_t lds);
+
 bool row_supported(int N, int H, int flags, int rows);
 // whether W x of T steps of B rows is the faster in the launch itself; kpad: bytes of a weight row
 bool row_takes_input(int N, int H, int kpad, int T, int B);

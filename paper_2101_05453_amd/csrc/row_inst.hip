@@ -21,6 +21,19 @@ static row_fn pick_row(int form, int fl, bool own) {
   return nullptr;
 }
 
+// Several layers in one launch (row_stack_inst_{64,128,256}.hip): T steps of L layers take T + (L - 1) (piece + 1) steps one behind the other
+// instead of L T, and a launch instead of one or two per layer; W x of a piece comes to 2 to 5 us.  Layer after layer (or the
+// stacked launch, where that is ahead) -> this, us:
+//   6 layers of 86 cells, layer norm, 5 rows, 1 step      63 -> 34     3 layers of 128 cells, layer norm, 39 rows, 43 steps   187 -> 117
+//   6 layers of 32 cells, layer norm, 16 rows, 100 steps 575 -> 201    4 layers of 219 cells, peephole, 11 rows, 64 steps      366 -> 179
+//   2 layers of 208 cells, layer norm, 9 rows, 64 steps  230 -> 179    2 layers of 49 cells, 32 rows, 3 steps, two directions   25 -> 22
+row_stack_fn row_stack_pick_64(int fl);
+row_stack_fn row_stack_pick_128(int fl);
+row_stack_fn row_stack_pick_256(int fl);
+static row_stack_fn pick_row_stack(int form, int fl) {
+  return form == 0 ? row_stack_pick_64(fl) : form == 1 ? row_stack_pick_128(fl) : form == 2 ? row_stack_pick_256(fl) : nullptr;
+}
+
 // Up to 256 rows, a compute unit for each: the launch of four rows per workgroup -> this one, us, 100 steps of 64 rows, input 64
 //                 no layer norm    layer norm    and peephole    projection, no layer norm
 //   64 cells          79 ->  62     161 -> 109     223 -> 173          92 ->  75
@@ -34,17 +47,24 @@ bool row_supported(int N, int H, int flags, int rows) {
   return form >= 0 && ((flags & 8) || H == N) && rows <= 256;
 }
 
-size_t row_lds_bytes(const RecArgs &a, bool own) {
-  const int form = row_form(a.N, a.H);
+static size_t lds_bytes(const RecArgs &a, int form, size_t term_bytes) {  // term_bytes: of a wave's W x terms
   if (form < 0) return (size_t)1 << 30;
   const size_t NC = kRowCells[form];
   size_t n = 3 * NC + 16 * 8 + 4 * sizeof(LnRow2) + 64 + 128;
   n = (n + 1023) & ~(size_t)1023;
-  n += (NC / 16) * (size_t)row_terms_bytes((int)NC / 16, a.T, own) + (form == 2 && (a.flags & 4) ? 1024 * 16 : 0);
+  n += (NC / 16) * term_bytes + (form == 2 && (a.flags & 4) ? 1024 * 16 : 0);
   for (int i = 0; i < 3; ++i)
     if (i < 2 || a.lut[2].blob != a.lut[1].blob) n += (size_t)lut_wide_lds_bytes(a.lut[i].dom, a.lut[i].sh, a.lut[i].tail != 0);
   if (form == 2 && (a.flags & 8)) n += (size_t)((a.H + 15) & ~15) * (NC + 16);
   return n;
+}
+
+size_t row_lds_bytes(const RecArgs &a, bool own) {
+  const int form = row_form(a.N, a.H);
+  return form < 0 ? (size_t)1 << 30 : lds_bytes(a, form, row_terms_bytes(kRowCells[form] / 16, a.T, own));
+}
+size_t row_stack_lds_bytes(const RecArgs &a, int widest, int term_steps, int x_bytes) {
+  return lds_bytes(a, row_form(widest, widest), (size_t)term_steps * 128) + x_bytes;
 }
 
 hipError_t row_init() {
@@ -52,6 +72,9 @@ hipError_t row_init() {
     for (int k = 0; k < 32; ++k) {
       hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(pick_row(form, k >> 1, k & 1)),
                                          hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+      if (e != hipSuccess) return e;
+      if (k & 1) continue;
+      e = hipFuncSetAttribute(reinterpret_cast<const void *>(pick_row_stack(form, k >> 1)), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
       if (e != hipSuccess) return e;
     }
   return hipSuccess;
@@ -101,6 +124,40 @@ hipError_t launch_row(hipStream_t s, const RowArgs &a) {
   const int blocks = ((f.N > f.H ? f.N : f.H) + 15) / 16;  // a wave each; four at least, which bring the tables in sooner
   void *params[] = {&args};
   return hipLaunchKernel(reinterpret_cast<const void *>(fn), dim3(f.groups + b.groups), dim3(64 * (blocks < 4 ? 4 : blocks)), params, lds, s);
+}
+
+void row_stack_layer(RowLayer &to, const RecDirArgs &from) {
+  to.T = from.T; to.B = from.B; to.N = from.N; to.H = from.H; to.Hpad = from.Hpad; to.Bp = from.Bp; to.Ncp = from.Ncp;
+  to.ks16 = from.ks16; to.npadp = from.npadp; to.ldy = from.ldy; to.rev = from.rev; to.m_c = from.m_c; to.pre_h = from.pre_h;
+  to.R2h = from.R2h; to.bh4 = from.bh4; to.Lq4 = from.Lq4; to.qb4 = from.qb4; to.Pq3 = from.Pq3;
+  for (int g = 0; g < 4; ++g) {
+    to.Mh[g] = from.Mh[g]; to.rh[g] = from.rh[g];
+    to.Mln[g] = from.Mln[g]; to.rln[g] = from.rln[g];
+  }
+  for (int j = 0; j < 3; ++j) {
+    to.Mc[j] = from.Mc[j]; to.rc[j] = from.rc[j];
+    to.lut[j] = from.lut[j];
+  }
+  to.Mm = from.Mm; to.rm = from.rm; to.zp_m = from.zp_m;
+  to.Mp = from.Mp; to.rp = from.rp; to.zp_h = from.zp_h;
+  to.Wp2 = from.Wp2; to.bp2 = from.bp2; to.tx2 = from.tx2; to.h0 = from.h0; to.out = from.out; to.y = from.y;
+  to.c_in = from.c_in; to.c_out = from.c_out; to.status = from.status;
+}
+
+hipError_t launch_row_stack(hipStream_t s, const RowStackArgs &a, int layers, int flags, int widest, size_t lds) {
+  const int form = row_form(widest, widest);
+  row_stack_fn fn = layers < 1 || layers > kRowStackLayers ? nullptr : pick_row_stack(form, flags & 15);
+  if (!fn || lds > 160 * 1024) return hipErrorInvalidValue;
+  for (int l = 0; l < layers; ++l) {
+    const RowInput &in = a.in[l];
+    if (a.rec.d[l].B != a.rec.d[0].B || in.piece < 1 || in.piece > 16 || in.term_steps < (in.x ? in.piece : 2 * in.piece) || (in.x && in.x_bytes < 1024 * in.kx) || !a.rec.d[l].R2h ||
+        (!in.x && !a.rec.d[l].tx2))
+      return hipErrorInvalidValue;
+  }
+  RowStackArgs args = a;
+  const int blocks = (widest + 15) / 16;
+  void *params[] = {&args};
+  return hipLaunchKernel(reinterpret_cast<const void *>(fn), dim3(layers * a.rec.d[0].B), dim3(64 * (blocks < 4 ? 4 : blocks)), params, lds, s);
 }
 
 }  // namespace lstm_int

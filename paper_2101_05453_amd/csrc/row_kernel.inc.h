@@ -35,11 +35,20 @@ __host__ __device__ constexpr int row_terms_bytes(int waves, int T, bool own) {
   return (own && T > row_ahead(waves) ? T : row_ahead(waves)) * 128;
 }
 
+// Where a wave's W x terms come from
+constexpr int kRowTerms = 0;  // tx2, a ring of the steps on their way
+constexpr int kRowOwn = 1;    // computed here, all steps ahead of the first
+constexpr int kRowStack = 2;  // a launch of several layers: computed here, a piece of the sequence at a time, as soon as the layer
+                              // below has it; or, with tx2, its terms a piece ahead
+
 // The LDS of a launch, from the front (row_lds_bytes mirrors it): h twice, m, sums, statistics, W x terms, tables.
-// FL: bit 0 coupled gates, bit 1 peephole, bit 2 layer norm, bit 3 projection.  OWN: W x is computed here (RowInput).
-template <int WAVES, int KS16, int FL, bool OWN>
-__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVES == 4 ? 2 : WAVES / 4, WAVES == 4 ? 2 : WAVES / 4))) void row_kernel(RowArgs all) {
-  const RecArgs2 &args = all.rec;
+// FL: bit 0 coupled gates, bit 1 peephole, bit 2 layer norm, bit 3 projection.  MODE: kRow...
+// kRowStack: several layers in one launch, a workgroup per (layer, row), those of the layers below first.  Rows never interact, so a
+// layer's workgroup waits for one other alone, that of the same row in the layer below, and for nobody above it: workgroups start
+// in their order, so that whoever is waited for has started or will, however few fit the chip at once.
+template <int WAVES, int KS16, int FL, int MODE>
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVES == 4 ? 2 : WAVES / 4, WAVES == 4 ? 2 : WAVES / 4))) void row_kernel(std::conditional_t<MODE == kRowStack, RowStackArgs, RowArgs> all) {
+  constexpr bool OWN = MODE == kRowOwn, STACK = MODE == kRowStack;
   constexpr bool cifg = FL & 1, ph = FL & 2, ln = FL & 4, proj = FL & 8;
   constexpr int NC = 16 * WAVES;  // cells and outputs of the workgroup at most
   const int waves = (int)(blockDim.x >> 6), NT = (int)blockDim.x;  // as many as the layer has blocks of 16 cells or outputs
@@ -55,9 +64,17 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c16 = lane & 15, q = lane >> 4;
   const int gq = cifg && q == 0 ? 1 : q;  // this lane's gate
-  const int which = (int)blockIdx.x >= args.d[0].groups ? 1 : 0;
-  const RecDirArgs &a = args.d[which];
-  const int row = (int)blockIdx.x - (which ? args.d[0].groups : 0);
+  // the layer of the launch this workgroup works on, and its row (written out: through functions that return references the
+  // kernels of one layer take two registers more, which 16 waves with peephole and layer norm do not have)
+  int which, row = (int)blockIdx.x;
+  if constexpr (STACK) {
+    which = row / all.rec.d[0].B;
+    row -= which * all.rec.d[0].B;
+  } else {
+    which = (int)blockIdx.x >= all.rec.d[0].groups ? 1 : 0;
+    row -= which ? all.rec.d[0].groups : 0;
+  }
+  const auto &a = all.rec.d[which];
   const RowInput &in = all.in[which];
   const int T = a.T, N = a.N, H = a.H, rev = a.rev, ldy = a.ldy;
 
@@ -69,9 +86,14 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
   int *flag = reinterpret_cast<int *>(p);         p += 64;  // 1: every gate's sigma >= 2^12
   v4i *tables = reinterpret_cast<v4i *>(p);       p += 128;  // LEAN: [gates, second lookups][lane group]
   p = lds + (((size_t)(p - lds) + 1023) & ~(size_t)1023);
-  // W x terms: [step % AHEAD][wave][8 pieces of 16 bytes], or, computed here, [step][wave][gate][16 cells]
-  uint8_t *const txL = p + wave * 128;
-  p += WAVES * row_terms_bytes(WAVES, T, OWN);
+  // W x terms: [step % AHEAD][wave][8 pieces of 16 bytes], or, computed here, [step][wave][gate][16 cells]; of several layers
+  // [wave][step of the piece] of either kind, of two pieces by turns with tx2
+  const int piece = STACK ? in.piece : 0;
+  const bool from_tx = STACK && in.x == nullptr;
+  uint8_t *const txL = p + wave * (STACK ? in.term_steps * 128 : 128);
+  p += WAVES * (STACK ? in.term_steps * 128 : row_terms_bytes(WAVES, T, OWN));
+  int8_t *const xT = reinterpret_cast<int8_t *>(p);  // several layers: x of a piece as MFMA operands, [k step][lane][16 bytes]
+  p += STACK ? in.x_bytes : 0;
   double *const lnL = reinterpret_cast<double *>(p) + tid * 2;  // LEAN: layer-norm weight and bias of the lane's gate and cell
   p += ln && LEAN ? 64 * WAVES * 16 : 0;
   const bool share_tanh = a.lut[2].blob == a.lut[1].blob;
@@ -104,51 +126,70 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     }
   }
   const bool real = wave < (a.Ncp >> 4);  // the layer has this block of 16 cells (cells past N are zero weights)
-  // W x of all steps of the row, 16 at a time: the steps are the rows of the MFMA's first operand (step t0 + lane % 16), the second is the
+  // W x of up to 16 steps t0 .. tn - 1 of the row: the steps are the rows of the MFMA's first operand (step t0 + lane % 16), the second is the
   // input GEMM's operand of two tiles of eight cells, gathered; a lane ends with cell c16 in steps 4 q + v.
-  auto input_terms = [&](int t0) {
-    const int t = t0 + c16 < T ? t0 + c16 : T - 1;
-    const int8_t *xr = in.x + ((size_t)(rev ? T - 1 - t : t) * a.B + row) * in.ldx + (q << 4);
-    const int8_t *wr = in.W2f + ((size_t)(wave * 2 + (c16 >> 3)) * 2 * in.kx + (q >> 1)) * 1024 + ((c16 & 7) + 32 * (q & 1)) * 16;
+  constexpr int TERM_STRIDE = STACK ? 128 : WAVES * 128;  // LDS bytes from a step's terms to the next one's
+  auto input_row = [&](int t0, int tn) {
+    const int t = t0 + c16 < tn ? t0 + c16 : tn - 1;
+    return in.x + ((size_t)(rev ? T - 1 - t : t) * a.B + row) * in.ldx + (q << 4);
+  };
+  auto input_weights = [&]() { return in.W2f + ((size_t)(wave * 2 + (c16 >> 3)) * 2 * in.kx + (q >> 1)) * 1024 + ((c16 & 7) + 32 * (q & 1)) * 16; };
+  auto input_terms = [&](int t0, int tn, uint8_t *dst) {
+    const int8_t *xr = STACK ? xT + lane * 16 : input_row(t0, tn);
+    const int8_t *wr = input_weights();
     const int32_t *br = in.bx2 + (wave * 2 + (c16 >> 3)) * 32 + (c16 & 7);
-    v4i acc[4];
+    // With 16 waves the pieces of a sequence are worked out beside the recurrent weights, one gate at a time
+    constexpr int GATES = STACK && LEAN ? 1 : 4, U = STACK && LEAN ? 2 : 4;  // U: k steps whose operands are on their way together
 #pragma unroll
-    for (int g = g_first; g < 4; ++g) {
-      const int32_t b = br[8 * g];
-      acc[g] = v4i{b, b, b, b};
-    }
-    constexpr int U = 4;  // k steps whose operands are on their way together
-    for (int k0 = 0; k0 < in.kx; k0 += U) {
-      v4i xf[U], wf[U][4];
+    for (int g0 = GATES == 4 ? 0 : g_first; g0 < 4; g0 += GATES) {
+      const int g_from = GATES == 4 ? g_first : g0, g_end = g0 + GATES;
+      v4i acc[GATES];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int ks = k0 + u < in.kx ? k0 + u : in.kx - 1;
-        xf[u] = v4i{0, 0, 0, 0};
-        if (ks * 64 + (q << 4) < in.cols && k0 + u < in.kx) xf[u] = *reinterpret_cast<const v4i *>(xr + ks * 64);
-#pragma unroll
-        for (int g = g_first; g < 4; ++g) wf[u][g] = *reinterpret_cast<const v4i *>(wr + (size_t)ks * 2048 + g * 128);
+      for (int g = g_from; g < g_end; ++g) {
+        const int32_t b = br[8 * g];
+        acc[g - g0] = v4i{b, b, b, b};
       }
-      __builtin_amdgcn_sched_barrier(0);
+      for (int k0 = 0; k0 < in.kx; k0 += U) {
+        v4i xf[U], wf[U][GATES];
 #pragma unroll
-      for (int u = 0; u < U; ++u)
+        for (int u = 0; u < U; ++u) {
+          const int ks = k0 + u < in.kx ? k0 + u : in.kx - 1;
+          if (!STACK) {
+            xf[u] = v4i{0, 0, 0, 0};
+            if (ks * 64 + (q << 4) < in.cols && k0 + u < in.kx) xf[u] = *reinterpret_cast<const v4i *>(xr + ks * 64);
+          }
 #pragma unroll
-        for (int g = g_first; g < 4; ++g) acc[g] = __builtin_amdgcn_mfma_i32_16x16x64_i8(xf[u], wf[u][g], acc[g], 0, 0, 0);
-    }
+          for (int g = g_from; g < g_end; ++g) wf[u][g - g0] = *reinterpret_cast<const v4i *>(wr + (size_t)ks * 2048 + g * 128);
+        }
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int g = g_first; g < 4; ++g)
+        for (int u = 0; u < U; ++u) {
+          if (STACK) {
+            xf[u] = *reinterpret_cast<const v4i *>(xr + (k0 + u < in.kx ? k0 + u : in.kx - 1) * 1024);
+            if (k0 + u >= in.kx) xf[u] = v4i{0, 0, 0, 0};
+          }
+#pragma unroll
+          for (int g = g_from; g < g_end; ++g) acc[g - g0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(xf[u], wf[u][g - g0], acc[g - g0], 0, 0, 0);
+        }
+      }
+      if (__builtin_expect(in.pre, 0)) {
+#pragma unroll
+        for (int g = g_from; g < g_end; ++g)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) acc[g - g0][v] = rescale_preshift(acc[g - g0][v], in.rs[g]);
+      }
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        int32_t s = acc[g][v];
-        if (in.pre) {
-          asm volatile("" : "+v"(s));
-          s = rescale_preshift(s, in.rs[g]);
-        }
-        if (t0 + 4 * q + v < T) *reinterpret_cast<int16_t *>(txL + (t0 + 4 * q + v) * WAVES * 128 + g * 32 + c16 * 2) = (int16_t)rescale_sat16_pre<0>(s, in.rs[g]);
+        const int t = t0 + 4 * q + v;  // steps past the last one go to a place nobody reads
+        uint8_t *const to = t < tn ? dst + (OWN ? t : 4 * q + v) * TERM_STRIDE + c16 * 2 : reinterpret_cast<uint8_t *>(flag) - g_from * 32 + 4;
+#pragma unroll
+        for (int g = g_from; g < g_end; ++g) *reinterpret_cast<int16_t *>(to + (t < tn ? g : g_from) * 32) = (int16_t)rescale_sat16_pre<0>(acc[g - g0][v], in.rs[g]);
       }
+    }
   };
   // (with LEAN ahead of the recurrent weights, which take the registers)
   if (OWN && real)
-    for (int t0 = 0; t0 < T; t0 += 16) input_terms(t0);
+    for (int t0 = 0; t0 < T; t0 += 16) input_terms(t0, T, txL);
   v4i Wf[4][KS16];  // [gate]: lane (c16, q) holds bytes 16 q.. of each 64-deep k step of cell c16's row
   v4i Wp[proj && !LEAN ? KS16 : 1];  // W_proj: the same of output 16 wave + c16
   const size_t n = (real ? wave : 0) * 16 + c16;
@@ -247,12 +288,14 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
   // h before step 0; the other half and m start as zeros (bytes past the real ones only meet zero weights)
   for (int i = tid; i < 3 * NC; i += NT) {
     int8_t v = 0;
-    if (i < H) v = !OWN ? a.h0[(size_t)row * a.Hpad + i] : in.h_src ? in.h_src[(size_t)row * H + i] : (int8_t)a.zp_h;
+    if (i < H) v = MODE == kRowTerms ? a.h0[(size_t)row * a.Hpad + i] : in.h_src ? in.h_src[(size_t)row * H + i] : (int8_t)a.zp_h;
     hT[i] = v;
   }
   const int cell = wave * 16 + c16;  // this lane's cell, and its output of the projection
   int32_t creg = (a.c_in && cell < N) ? a.c_in[(size_t)row * N + cell] : 0;
-  const double inv_n = 1.0 / (double)N;
+  double inv_n = 1.0 / (double)N;
+  if (STACK)  // in scalar registers, where it is not spilled: a reload would wait for the stores of the output
+    inv_n = __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(inv_n)), __builtin_amdgcn_readfirstlane(__double2loint(inv_n)));
   const bool pre_ln = ln && (a.rln[0] < 33 || a.rln[1] < 33 || a.rln[2] < 33 || a.rln[3] < 33);
   const bool pre_m = a.rm < 33, pre_p = proj && a.rp < 33;
   const bool pre_h = a.pre_h != 0;
@@ -274,8 +317,18 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     if (lane < 8) dma(tx_src, txL + (t & (AHEAD - 1)) * WAVES * 128);
     tx_src += t + 1 < T ? tx_ahead : 0;
   };
-  const int tx_at = OWN ? gq * 32 + c16 * 2 : ((c16 >> 3) * 4 + (gq >> 1) * 2 + ((c16 >> 2) & 1)) * 16 + ((gq & 1) * 4 + (c16 & 3)) * 2;
-  if (!OWN)
+  const int tx_at = OWN || (STACK && !from_tx) ? gq * 32 + c16 * 2 : ((c16 >> 3) * 4 + (gq >> 1) * 2 + ((c16 >> 2) & 1)) * 16 + ((gq & 1) * 4 + (c16 & 3)) * 2;
+  // several layers: the terms of steps t0 .. tn - 1 (at most 16), eight steps per load of the wave
+  auto piece_request = [&](int t0, int tn, uint8_t *dst) {
+    for (int s = 0; t0 + s < tn; s += 8) {
+      const int t = t0 + s + (lane >> 3), l8 = lane & 7;
+      const int16_t *src = reinterpret_cast<const int16_t *>(a.tx2) + (size_t)(rev ? T - 1 - t : t) * tx_step +
+                           ((size_t)(row >> 5) * (a.Ncp >> 3) + (real ? wave : 0) * 2 + (l8 >> 2)) * 1024 + ((l8 >> 1) & 1) * 512 +
+                           ((row & 31) + 32 * (l8 & 1)) * 8;
+      if (t < tn) dma(src, dst + s * 128);
+    }
+  };
+  if (MODE == kRowTerms)
     for (int s = 0; s < AHEAD && s < T; ++s) tx_request(s);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
@@ -351,7 +404,67 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
   const long long out_step = rev ? -(long long)a.B * a.Hpad : (long long)a.B * a.Hpad, y_step = rev ? -(long long)a.B * ldy : (long long)a.B * ldy;
   const bool writes = q == 0 && cell < H, has_y = a.y != nullptr;
 
+  // several layers: the terms of the step, the first step of the next piece, its half of the terms' LDS
+  const uint8_t *tx_now = txL + tx_at;
+  int next = 0, half = 0;
+  bool gave_up = false;
+  if constexpr (STACK) {
+    if (from_tx) {
+      piece_request(0, piece < T ? piece : T, txL);
+    } else if (in.ready && real) {
+      // while the layer below is on its way: the input weights into the L2
+      const int8_t *wr = input_weights();
+      for (int ks = 0; ks < in.kx; ++ks) {
+        int32_t w[4];
+#pragma unroll
+        for (int g = g_first; g < 4; ++g) w[g] = *reinterpret_cast<const int32_t *>(wr + (size_t)ks * 2048 + g * 128);
+#pragma unroll
+        for (int g = g_first; g < 4; ++g) asm volatile("" ::"v"(w[g]));
+      }
+    }
+  }
+
   for (int t = 0; t < T; ++t) {
+    bool publish = false;
+    if constexpr (STACK) {
+      if (t == next) {
+        publish = t > 0 && in.done;
+        next = t + piece < T ? t + piece : T;
+        if (from_tx) {
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this piece has landed; the next one is asked for
+          if (next < T) piece_request(next, next + piece < T ? next + piece : T, txL + (half ^ 1) * piece * 128);
+        } else {
+          // x of the piece into LDS, a k step by a wave, past the L1 and the L2: another workgroup of the launch may have written it, on
+          // another XCD.  (Every wave for itself, out of the product's loop, came to 1.5 us a piece more with 16 waves.)
+          if (wave < in.kx) {
+            if (in.ready && !gave_up) {
+              const int *const flag = in.ready + row * kRowFlagWords;
+              int budget = in.spin_limit;
+              while (__builtin_amdgcn_readfirstlane(__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) < next + in.never) {
+                __builtin_amdgcn_s_sleep(1);
+                if (--budget < 0) {  // the outputs are not valid; every later wait is skipped
+                  gave_up = true;
+                  if (lane == 0) __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                  break;
+                }
+              }
+            }
+            const int8_t *xr = input_row(t, next);
+            for (int ks = wave; ks < in.kx; ks += waves) {
+              // bytes that may not be read meet zero weights
+              const int8_t *from = ks * 64 + (q << 4) < in.cols ? xr + ks * 64 : xr - (q << 4);
+              __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)from,
+                                               (__attribute__((address_space(3))) void *)(xT + ks * 1024), 16, 0, 16 /* sc1 */);
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+          }
+          lds_barrier();
+          if (real) input_terms(t, next, txL);
+        }
+        tx_now = txL + (from_tx ? half * piece * 128 : 0) + tx_at;
+        half ^= 1;
+      }
+    }
     const int8_t *hcur = hT + (t & 1) * NC;
     int8_t *hnext = hT + ((t + 1) & 1) * NC;
     u64 *const sums = red + (t & 1) * 8;
@@ -359,8 +472,9 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
 #pragma unroll
     for (int ks = 0; ks < KS16; ++ks) hf[ks] = *reinterpret_cast<const v4i *>(hcur + (q << 4) + ks * 64);
     // the terms of this step: the loads of the steps ahead are younger (and stores among them make the wait stricter)
-    if (!OWN) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AHEAD - 1) : "memory");
-    const int32_t tx = *reinterpret_cast<const int16_t *>(txL + (OWN ? t : t & (AHEAD - 1)) * WAVES * 128 + tx_at);
+    if (MODE == kRowTerms) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AHEAD - 1) : "memory");
+    const int32_t tx = *reinterpret_cast<const int16_t *>(STACK ? tx_now : txL + (OWN ? t : t & (AHEAD - 1)) * WAVES * 128 + tx_at);
+    if (STACK) tx_now += 128;
     if (ln && tid < 8) red[((t + 1) & 1) * 8 + tid] = 0;  // read in the step before, added to in the next one
     int32_t acc[4];
 #pragma unroll
@@ -372,13 +486,13 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     }
     // gate sum (Secs. 3.2.4/3.2.5); with a peephole the o gate is finished after c^t
     int32_t s = of_gate(cifg ? 0 : acc[0], acc[1], acc[2], acc[3]) + bh;
-    int32_t v = rescaled16(s, ps, pre_h, [&] { return of_gate(a.rh[0], a.rh[1], a.rh[2], a.rh[3]); }) + (proj && !real ? 0 : tx);
+    int32_t v = rescaled16(s, ps, pre_h, [&] { return of_gate(a.rh[0], a.rh[1], a.rh[2], a.rh[3]); }) + ((proj || STACK) && !real ? 0 : tx);
     if (ph) v += peephole(Pold, creg);
     const int32_t open = v;
     v = clamp_i32(v, glo, 32767);
     if (ln) add_stats(sums + q, v, true);
     asm volatile("" ::"v"(v));  // the term has been read: its place takes the one of a later step
-    if (!OWN) tx_request(t + AHEAD);
+    if (MODE == kRowTerms) tx_request(t + AHEAD);
     // layer norm, sigma / tanh (Secs. 3.2.6, 3.2.1)
     if (ln) v = normalize(sums + q, v, !(ph && q == 3));
     const int32_t act = activation(v, 0, q == 2, [&] { return q == 2 ? offT[1] : offT[0]; });
@@ -430,42 +544,63 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
       }
     }
     if (q == 0) hnext[cell] = hq;
+    if (STACK && publish) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the steps before this one have left
     lds_barrier();  // the next h is complete
+    if (STACK && publish && tid == 0) __hip_atomic_store(in.done + row * kRowFlagWords, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (writes) {
-      out[cell] = hq;
+      if (!STACK)
+        out[cell] = hq;
+      else if (in.done)  // for the layer above, through the L2
+        __hip_atomic_store(out + cell, hq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      else if (!has_y)
+        out[cell] = hq;
       if (has_y) y[cell] = hq;
     }
     out += out_step;
     y += y_step;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing is on its way into LDS when the workgroup gives it back
-  if (OWN && in.h_dst)
+  if (STACK && in.done) {
+    __syncthreads();
+    if (tid == 0) __hip_atomic_store(in.done + row * kRowFlagWords, T, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (MODE != kRowTerms && in.h_dst)
     for (int i = tid; i < H; i += NT) in.h_dst[(size_t)row * H + i] = hT[(T & 1) * NC + i];
   if (a.c_out && q == 0 && cell < N) a.c_out[(size_t)row * N + cell] = (int16_t)creg;
 }
 
 typedef void (*row_fn)(RowArgs);
+typedef void (*row_stack_fn)(RowStackArgs);
+
+template <int WAVES, int KS16, int FL = 0>
+row_stack_fn row_stack_pick_size(int fl) {
+  if constexpr (FL < 15) {
+    return fl == FL ? row_kernel<WAVES, KS16, FL, kRowStack> : row_stack_pick_size<WAVES, KS16, FL + 1>(fl);
+  } else {
+    return row_kernel<WAVES, KS16, 15, kRowStack>;
+  }
+}
 
 // kernel for (flags & 15)
 template <int WAVES, int KS16, bool OWN>
 row_fn row_pick_size(int fl) {
   switch (fl & 15) {
-    case 0: return row_kernel<WAVES, KS16, 0, OWN>;
-    case 1: return row_kernel<WAVES, KS16, 1, OWN>;
-    case 2: return row_kernel<WAVES, KS16, 2, OWN>;
-    case 3: return row_kernel<WAVES, KS16, 3, OWN>;
-    case 4: return row_kernel<WAVES, KS16, 4, OWN>;
-    case 5: return row_kernel<WAVES, KS16, 5, OWN>;
-    case 6: return row_kernel<WAVES, KS16, 6, OWN>;
-    case 7: return row_kernel<WAVES, KS16, 7, OWN>;
-    case 8: return row_kernel<WAVES, KS16, 8, OWN>;
-    case 9: return row_kernel<WAVES, KS16, 9, OWN>;
-    case 10: return row_kernel<WAVES, KS16, 10, OWN>;
-    case 11: return row_kernel<WAVES, KS16, 11, OWN>;
-    case 12: return row_kernel<WAVES, KS16, 12, OWN>;
-    case 13: return row_kernel<WAVES, KS16, 13, OWN>;
-    case 14: return row_kernel<WAVES, KS16, 14, OWN>;
-    default: return row_kernel<WAVES, KS16, 15, OWN>;
+    case 0: return row_kernel<WAVES, KS16, 0, OWN ? kRowOwn : kRowTerms>;
+    case 1: return row_kernel<WAVES, KS16, 1, OWN ? kRowOwn : kRowTerms>;
+    case 2: return row_kernel<WAVES, KS16, 2, OWN ? kRowOwn : kRowTerms>;
+    case 3: return row_kernel<WAVES, KS16, 3, OWN ? kRowOwn : kRowTerms>;
+    case 4: return row_kernel<WAVES, KS16, 4, OWN ? kRowOwn : kRowTerms>;
+    case 5: return row_kernel<WAVES, KS16, 5, OWN ? kRowOwn : kRowTerms>;
+    case 6: return row_kernel<WAVES, KS16, 6, OWN ? kRowOwn : kRowTerms>;
+    case 7: return row_kernel<WAVES, KS16, 7, OWN ? kRowOwn : kRowTerms>;
+    case 8: return row_kernel<WAVES, KS16, 8, OWN ? kRowOwn : kRowTerms>;
+    case 9: return row_kernel<WAVES, KS16, 9, OWN ? kRowOwn : kRowTerms>;
+    case 10: return row_kernel<WAVES, KS16, 10, OWN ? kRowOwn : kRowTerms>;
+    case 11: return row_kernel<WAVES, KS16, 11, OWN ? kRowOwn : kRowTerms>;
+    case 12: return row_kernel<WAVES, KS16, 12, OWN ? kRowOwn : kRowTerms>;
+    case 13: return row_kernel<WAVES, KS16, 13, OWN ? kRowOwn : kRowTerms>;
+    case 14: return row_kernel<WAVES, KS16, 14, OWN ? kRowOwn : kRowTerms>;
+    default: return row_kernel<WAVES, KS16, 15, OWN ? kRowOwn : kRowTerms>;
   }
 }
 
