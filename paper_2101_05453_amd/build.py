@@ -6,7 +6,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblstm_int.so")
 SOURCES = ["prepare.cpp", "kernels.hip", "persistent.hip", "in_gemm.hip", "deep_gemm.hip", "rec_inst_8.hip", "rec_inst_20.hip",
-           "rec_inst_32.hip", "rec_sparse_inst_8.hip", "rec_sparse_inst_20.hip", "rec_sparse_inst_32.hip", "rec16_inst.hip", "rec16_inst_4.hip", "rec16_inst_10.hip", "rec16_inst_16.hip", "solo_inst.hip", "row_inst.hip", "row_inst_64.hip", "row_inst_128.hip", "row_inst_256.hip", "row_stack_inst_64.hip", "row_stack_inst_128.hip", "row_stack_inst_256.hip", "quad_inst.hip", "quad_inst_8.hip", "quad_inst_10.hip", "quad_inst_16.hip", "stack.hip", "stack_inst_8.hip", "stack_inst_20.hip", "stack_inst_32.hip", "calibrate.hip", "ceiling.hip", "gru.hip", "gru_seq.hip", "gru_rows.hip", "sru.hip", "api.hip"]
+           "rec_inst_32.hip", "rec_sparse_inst_8.hip", "rec_sparse_inst_20.hip", "rec_sparse_inst_32.hip", "rec16_inst.hip", "rec16_inst_4.hip", "rec16_inst_10.hip", "rec16_inst_16.hip", "solo_inst.hip", "row_inst.hip", "row_inst_64.hip", "row_inst_128.hip", "row_inst_192.hip", "row_inst_256.hip", "row_stack_inst_64.hip", "row_stack_inst_128.hip", "row_stack_inst_192.hip", "row_stack_inst_256.hip", "quad_inst.hip", "quad_inst_8.hip", "quad_inst_10.hip", "quad_inst_16.hip", "stack.hip", "stack_inst_8.hip", "stack_inst_20.hip", "stack_inst_32.hip", "calibrate.hip", "ceiling.hip", "gru.hip", "gru_seq.hip", "gru_rows.hip", "sru.hip", "api.hip"]
 HOSTMATH_LIB = os.path.join(HERE, "liblstm_int_hostmath.so")
 HOSTMATH_SAN_LIB = os.path.join(HERE, "liblstm_int_hostmath_san.so")
 SANITIZE_FLAGS = ["-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-fno-omit-frame-pointer", "-g"]
@@ -16,10 +16,10 @@ HIP_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contra
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
              "-Wall", "-Wno-unused-function"]
 # in_gemm.hip and the like: MFMA results go to ordinary vector registers, where the requantization reads them without copies
-EXTRA_FLAGS = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] for f in ("in_gemm.hip", "deep_gemm.hip", "rec_inst_8.hip", "rec_inst_20.hip", "rec_inst_32.hip", "rec_sparse_inst_8.hip", "rec_sparse_inst_20.hip", "rec_sparse_inst_32.hip", "rec16_inst_4.hip", "rec16_inst_10.hip", "rec16_inst_16.hip", "solo_inst.hip", "row_inst_64.hip", "row_inst_128.hip", "row_inst_256.hip", "row_stack_inst_64.hip", "row_stack_inst_128.hip", "row_stack_inst_256.hip", "quad_inst_8.hip", "quad_inst_10.hip", "quad_inst_16.hip", "stack_inst_8.hip", "stack_inst_20.hip", "stack_inst_32.hip", "gru_seq.hip", "gru_rows.hip")}
+EXTRA_FLAGS = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] for f in ("in_gemm.hip", "deep_gemm.hip", "rec_inst_8.hip", "rec_inst_20.hip", "rec_inst_32.hip", "rec_sparse_inst_8.hip", "rec_sparse_inst_20.hip", "rec_sparse_inst_32.hip", "rec16_inst_4.hip", "rec16_inst_10.hip", "rec16_inst_16.hip", "solo_inst.hip", "row_inst_64.hip", "row_inst_128.hip", "row_inst_192.hip", "row_inst_256.hip", "row_stack_inst_64.hip", "row_stack_inst_128.hip", "row_stack_inst_192.hip", "row_stack_inst_256.hip", "quad_inst_8.hip", "quad_inst_10.hip", "quad_inst_16.hip", "stack_inst_8.hip", "stack_inst_20.hip", "stack_inst_32.hip", "gru_seq.hip", "gru_rows.hip")}
 # rec_kernel, row_kernel, gru_rows_kernel: what these two passes move out of the step loop, or turn into running pointers of it, ends in spilled registers
 # (eight layers of 2048 cells, 256 rows: 5530 -> 5340 us)
-for _f in ("rec_inst_8.hip", "rec_inst_20.hip", "rec_inst_32.hip", "rec_sparse_inst_8.hip", "rec_sparse_inst_20.hip", "rec_sparse_inst_32.hip", "stack_inst_8.hip", "stack_inst_20.hip", "stack_inst_32.hip", "row_inst_64.hip", "row_inst_128.hip", "row_inst_256.hip", "row_stack_inst_64.hip", "row_stack_inst_128.hip", "row_stack_inst_256.hip", "gru_rows.hip"):
+for _f in ("rec_inst_8.hip", "rec_inst_20.hip", "rec_inst_32.hip", "rec_sparse_inst_8.hip", "rec_sparse_inst_20.hip", "rec_sparse_inst_32.hip", "stack_inst_8.hip", "stack_inst_20.hip", "stack_inst_32.hip", "row_inst_64.hip", "row_inst_128.hip", "row_inst_192.hip", "row_inst_256.hip", "row_stack_inst_64.hip", "row_stack_inst_128.hip", "row_stack_inst_192.hip", "row_stack_inst_256.hip", "gru_rows.hip"):
     EXTRA_FLAGS[_f] = EXTRA_FLAGS[_f] + ["-mllvm", "-disable-lsr", "-mllvm", "-disable-machine-licm"]
 
 

@@ -10,15 +10,29 @@ static int row_form(int N, int H) {
     if (N <= kRowCells[i] && H <= kRowCells[i]) return i;
   return -1;
 }
-// row_inst_{64,128,256}.hip
+// row_inst_{64,128,192,256}.hip, row_stack_inst_{...}.hip
 row_fn row_pick_64(int fl, bool own);
 row_fn row_pick_128(int fl, bool own);
+row_fn row_pick_192(int fl, bool own);
 row_fn row_pick_256(int fl, bool own);
-static row_fn pick_row(int form, int fl, bool own) {
+row_fn row_pick_256_128(int fl, bool own);
+row_stack_fn row_stack_pick_64(int fl);
+row_stack_fn row_stack_pick_128(int fl);
+row_stack_fn row_stack_pick_192(int fl);
+row_stack_fn row_stack_pick_256(int fl);
+row_stack_fn row_stack_pick_256_128(int fl);
+// H: outputs, the depth of R h
+static row_fn pick_row(int form, int H, int fl, bool own) {
   if (form == 0) return row_pick_64(fl, own);
   if (form == 1) return row_pick_128(fl, own);
-  if (form == 2) return row_pick_256(fl, own);
-  return nullptr;
+  if (form != 2) return nullptr;
+  return H <= 128 && (fl & 8) ? row_pick_256_128(fl, own) : H <= 192 ? row_pick_192(fl, own) : row_pick_256(fl, own);
+}
+static row_stack_fn pick_row_stack(int form, int H, int fl) {
+  if (form == 0) return row_stack_pick_64(fl);
+  if (form == 1) return row_stack_pick_128(fl);
+  if (form != 2) return nullptr;
+  return H <= 128 && (fl & 8) ? row_stack_pick_256_128(fl) : H <= 192 ? row_stack_pick_192(fl) : row_stack_pick_256(fl);
 }
 
 // Several layers in one launch (row_stack_inst_{64,128,256}.hip): T steps of L layers take T + (L - 1) (piece + 1) steps one behind the other
@@ -26,14 +40,10 @@ static row_fn pick_row(int form, int fl, bool own) {
 // stacked launch, where that is ahead) -> this, us:
 //   6 layers of 86 cells, layer norm, 5 rows, 1 step      63 -> 34     3 layers of 128 cells, layer norm, 39 rows, 43 steps   187 -> 117
 //   6 layers of 32 cells, layer norm, 16 rows, 100 steps 575 -> 201    4 layers of 219 cells, peephole, 11 rows, 64 steps      366 -> 179
-//   2 layers of 208 cells, layer norm, 9 rows, 64 steps  230 -> 179    2 layers of 49 cells, 32 rows, 3 steps, two directions   25 -> 22
+//   2 layers of 203 cells, 131 outputs, 37 rows, 60 steps 217 -> 140    2 layers of 49 cells, 32 rows, 3 steps, two directions   25 -> 22
 row_stack_fn row_stack_pick_64(int fl);
 row_stack_fn row_stack_pick_128(int fl);
 row_stack_fn row_stack_pick_256(int fl);
-static row_stack_fn pick_row_stack(int form, int fl) {
-  return form == 0 ? row_stack_pick_64(fl) : form == 1 ? row_stack_pick_128(fl) : form == 2 ? row_stack_pick_256(fl) : nullptr;
-}
-
 // Up to 256 rows, a compute unit for each: the launch of four rows per workgroup -> this one, us, 100 steps of 64 rows, input 64
 //                 no layer norm    layer norm    and peephole    projection, no layer norm
 //   64 cells          79 ->  62     161 -> 109     223 -> 173          92 ->  75
@@ -69,14 +79,15 @@ size_t row_stack_lds_bytes(const RecArgs &a, int widest, int term_steps, int x_b
 
 hipError_t row_init() {
   for (int form = 0; form < 3; ++form)
-    for (int k = 0; k < 32; ++k) {
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(pick_row(form, k >> 1, k & 1)),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-      if (e != hipSuccess) return e;
-      if (k & 1) continue;
-      e = hipFuncSetAttribute(reinterpret_cast<const void *>(pick_row_stack(form, k >> 1)), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-      if (e != hipSuccess) return e;
-    }
+    for (int H = form < 2 ? 256 : 128; H <= 256; H += 64)
+      for (int k = 0; k < 32; ++k) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(pick_row(form, H, k >> 1, k & 1)),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        if (e == hipSuccess && !(k & 1))
+          e = hipFuncSetAttribute(reinterpret_cast<const void *>(pick_row_stack(form, H, k >> 1)),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        if (e != hipSuccess) return e;
+      }
   return hipSuccess;
 }
 
@@ -113,10 +124,10 @@ hipError_t launch_row(hipStream_t s, const RowArgs &a) {
   const RecArgs &f = a.rec.d[0], &b = a.rec.d[1];
   const int form = row_form(f.N, f.H);
   const bool own = a.in[0].x != nullptr;
-  row_fn fn = pick_row(form, f.flags & 15, own);
+  row_fn fn = pick_row(form, f.H, f.flags & 15, own);
   if (!fn || !f.R2h || f.rows_pg != 1 || f.groups != f.B ||
       (own && f.T > row_input_steps(kRowCells[form] / 16)) ||
-      (b.groups > 0 && (!b.R2h || row_form(b.N, b.H) != form || f.flags != b.flags || b.rows_pg != 1 || b.groups != b.B || own != (a.in[1].x != nullptr))))
+      (b.groups > 0 && (!b.R2h || row_form(b.N, b.H) != form || f.H != b.H || f.flags != b.flags || b.rows_pg != 1 || b.groups != b.B || own != (a.in[1].x != nullptr))))
     return hipErrorInvalidValue;
   size_t lds = row_lds_bytes(f, own);
   if (b.groups > 0) lds = lds > row_lds_bytes(b, own) ? lds : row_lds_bytes(b, own);
@@ -146,7 +157,9 @@ void row_stack_layer(RowLayer &to, const RecDirArgs &from) {
 
 hipError_t launch_row_stack(hipStream_t s, const RowStackArgs &a, int layers, int flags, int widest, size_t lds) {
   const int form = row_form(widest, widest);
-  row_stack_fn fn = layers < 1 || layers > kRowStackLayers ? nullptr : pick_row_stack(form, flags & 15);
+  int H = 0;
+  for (int l = 0; l < layers && l < kRowStackLayers; ++l) H = H > a.rec.d[l].H ? H : a.rec.d[l].H;
+  row_stack_fn fn = layers < 1 || layers > kRowStackLayers ? nullptr : pick_row_stack(form, H, flags & 15);
   if (!fn || lds > 160 * 1024) return hipErrorInvalidValue;
   for (int l = 0; l < layers; ++l) {
     const RowInput &in = a.in[l];

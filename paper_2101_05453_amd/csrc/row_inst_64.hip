@@ -2,5 +2,5 @@
 #include "row_kernel.inc.h"
 
 namespace lstm_int {
-row_fn row_pick_64(int fl, bool own) { return own ? row_pick_size<4, 1, true>(fl) : row_pick_size<4, 1, false>(fl); }
+row_fn row_pick_64(int fl, bool own) { return own ? row_pick_size<4, 1, kRowOwn, 0>(fl) : row_pick_size<4, 1, kRowTerms, 0>(fl); }
 }  // namespace lstm_int

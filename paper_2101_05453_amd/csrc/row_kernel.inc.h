@@ -42,6 +42,8 @@ constexpr int kRowStack = 2;  // a launch of several layers: computed here, a pi
                               // below has it; or, with tx2, its terms a piece ahead
 
 // The LDS of a launch, from the front (row_lds_bytes mirrors it): h twice, m, sums, statistics, W x terms, tables.
+// KS16: k steps of R h, as the outputs ask for: with 16 waves (129 to 256 cells) two to four (each that is not there saves 16 of 64 products
+// a wave and 16 of its 128 registers: layers of 129 to 192 cells 0.93 of the time with four, up to 128 outputs of wider ones 0.85)
 // FL: bit 0 coupled gates, bit 1 peephole, bit 2 layer norm, bit 3 projection.  MODE: kRow...
 // kRowStack: several layers in one launch, a workgroup per (layer, row), those of the layers below first.  Rows never interact, so a
 // layer's workgroup waits for one other alone, that of the same row in the layer below, and for nobody above it: workgroups start
@@ -51,6 +53,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
   constexpr bool OWN = MODE == kRowOwn, STACK = MODE == kRowStack;
   constexpr bool cifg = FL & 1, ph = FL & 2, ln = FL & 4, proj = FL & 8;
   constexpr int NC = 16 * WAVES;  // cells and outputs of the workgroup at most
+  constexpr int KSP = NC / 64;    // k steps of the projection (KS16: of R h)
   const int waves = (int)(blockDim.x >> 6), NT = (int)blockDim.x;  // as many as the layer has blocks of 16 cells or outputs
   // Statistics to (mean, sigma) form, a chain of 60 dependent instructions: up to two waves a SIMD every wave does it for
   // itself, which costs no more than one wave and saves a barrier; with four it would take the SIMD twice as long
@@ -191,18 +194,18 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
   if (OWN && real)
     for (int t0 = 0; t0 < T; t0 += 16) input_terms(t0, T, txL);
   v4i Wf[4][KS16];  // [gate]: lane (c16, q) holds bytes 16 q.. of each 64-deep k step of cell c16's row
-  v4i Wp[proj && !LEAN ? KS16 : 1];  // W_proj: the same of output 16 wave + c16
+  v4i Wp[proj && !LEAN ? KSP : 1];  // W_proj: the same of output 16 wave + c16
   const size_t n = (real ? wave : 0) * 16 + c16;
   {
     // rec16_kernel's tile j holds, in row 4 q' + g, gate g of cell 4 q' + j
     const int4 *src = a.R2h + (size_t)((real ? wave : 0) * 4 + (c16 & 3)) * a.ks16 * 64 + 4 * (c16 >> 2) + 16 * q;
-    int4 w[4][KS16], wp[KS16];
+    int4 w[4][KS16], wp[KSP];
 #pragma unroll
     for (int g = g_first; g < 4; ++g)
 #pragma unroll
       for (int ks = 0; ks < KS16; ++ks) w[g][ks] = real ? src[(size_t)ks * 64 + g] : int4{0, 0, 0, 0};
     if (proj && LEAN) {  // output rows of npadp >= N bytes each
-      const int rows = (H + 15) & ~15, pieces = KS16 * 4;
+      const int rows = (H + 15) & ~15, pieces = KSP * 4;
       for (int i = tid; i < rows * pieces; i += NT) {
         const int o = i / pieces, k = (i - o * pieces) * 16;
         int4 v = {0, 0, 0, 0};
@@ -213,7 +216,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     if (proj && !LEAN) {
       const int o = wave * 16 + c16;
 #pragma unroll
-      for (int ks = 0; ks < KS16; ++ks) {
+      for (int ks = 0; ks < KSP; ++ks) {
         const int k = ks * 64 + q * 16;
         wp[ks] = int4{0, 0, 0, 0};
         if (o < H && k < a.npadp) wp[ks] = *reinterpret_cast<const int4 *>(a.Wp2 + (size_t)o * a.npadp + k);
@@ -229,7 +232,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
       }
     if (proj && !LEAN)
 #pragma unroll
-      for (int ks = 0; ks < KS16; ++ks) {
+      for (int ks = 0; ks < KSP; ++ks) {
         Wp[ks] = v4i{wp[ks].x, wp[ks].y, wp[ks].z, wp[ks].w};
         asm volatile("" : "+v"(Wp[ks]));
       }
@@ -531,7 +534,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
       if (!LEAN || wave * 16 < H) {
         v4i pacc = v4i{0, 0, 0, 0};
 #pragma unroll
-        for (int ks = 0; ks < KS16; ++ks)
+        for (int ks = 0; ks < KSP; ++ks)
           pacc = __builtin_amdgcn_mfma_i32_16x16x64_i8(*reinterpret_cast<const v4i *>(mT + (q << 4) + ks * 64),
                                                        LEAN ? *reinterpret_cast<const v4i *>(WpL + cell * LS + (q << 4) + ks * 64) : Wp[LEAN ? 0 : ks],
                                                        pacc, 0, 0, 0);
@@ -572,35 +575,13 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
 typedef void (*row_fn)(RowArgs);
 typedef void (*row_stack_fn)(RowStackArgs);
 
-template <int WAVES, int KS16, int FL = 0>
-row_stack_fn row_stack_pick_size(int fl) {
+// kernel for fl of FL to 15
+template <int WAVES, int KS16, int MODE, int FL>
+auto row_pick_size(int fl) -> decltype(&row_kernel<WAVES, KS16, 15, MODE>) {
   if constexpr (FL < 15) {
-    return fl == FL ? row_kernel<WAVES, KS16, FL, kRowStack> : row_stack_pick_size<WAVES, KS16, FL + 1>(fl);
+    return fl == FL ? row_kernel<WAVES, KS16, FL, MODE> : row_pick_size<WAVES, KS16, MODE, FL + 1>(fl);
   } else {
-    return row_kernel<WAVES, KS16, 15, kRowStack>;
-  }
-}
-
-// kernel for (flags & 15)
-template <int WAVES, int KS16, bool OWN>
-row_fn row_pick_size(int fl) {
-  switch (fl & 15) {
-    case 0: return row_kernel<WAVES, KS16, 0, OWN ? kRowOwn : kRowTerms>;
-    case 1: return row_kernel<WAVES, KS16, 1, OWN ? kRowOwn : kRowTerms>;
-    case 2: return row_kernel<WAVES, KS16, 2, OWN ? kRowOwn : kRowTerms>;
-    case 3: return row_kernel<WAVES, KS16, 3, OWN ? kRowOwn : kRowTerms>;
-    case 4: return row_kernel<WAVES, KS16, 4, OWN ? kRowOwn : kRowTerms>;
-    case 5: return row_kernel<WAVES, KS16, 5, OWN ? kRowOwn : kRowTerms>;
-    case 6: return row_kernel<WAVES, KS16, 6, OWN ? kRowOwn : kRowTerms>;
-    case 7: return row_kernel<WAVES, KS16, 7, OWN ? kRowOwn : kRowTerms>;
-    case 8: return row_kernel<WAVES, KS16, 8, OWN ? kRowOwn : kRowTerms>;
-    case 9: return row_kernel<WAVES, KS16, 9, OWN ? kRowOwn : kRowTerms>;
-    case 10: return row_kernel<WAVES, KS16, 10, OWN ? kRowOwn : kRowTerms>;
-    case 11: return row_kernel<WAVES, KS16, 11, OWN ? kRowOwn : kRowTerms>;
-    case 12: return row_kernel<WAVES, KS16, 12, OWN ? kRowOwn : kRowTerms>;
-    case 13: return row_kernel<WAVES, KS16, 13, OWN ? kRowOwn : kRowTerms>;
-    case 14: return row_kernel<WAVES, KS16, 14, OWN ? kRowOwn : kRowTerms>;
-    default: return row_kernel<WAVES, KS16, 15, OWN ? kRowOwn : kRowTerms>;
+    return row_kernel<WAVES, KS16, 15, MODE>;
   }
 }
 

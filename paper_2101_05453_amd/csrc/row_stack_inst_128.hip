@@ -2,5 +2,5 @@
 #include "row_kernel.inc.h"
 
 namespace lstm_int {
-row_stack_fn row_stack_pick_128(int fl) { return row_stack_pick_size<8, 2>(fl); }
+row_stack_fn row_stack_pick_128(int fl) { return row_pick_size<8, 2, kRowStack, 0>(fl); }
 }  // namespace lstm_int
