@@ -270,7 +270,7 @@ bool rec_extents_ok(const RecArgs &ra, const Workspace &ws, int T_all, int t0, b
   // layer output [T_all, B, Hpad]
   if ((size_t)T_all * ra.B * ra.Hpad > ws.out_bytes) return false;
   // m exchange buffer [T][Bp][npadp] in tiles
-  if (has_proj && (size_t)ra.T * Bp * ra.npadp > ws.m2_bytes) return false;
+  if (has_proj && (size_t)ra.T * Bp * ra.npadp > ws.m2_bytes) return false;  // (marked words: plan_rec has seen to their place)
   // counters [groups][64] words and statistics accumulators [groups][4][256] 64-bit words
   if (solo) return true;
   const size_t group_bytes = kStatGroupBytes + (ra.flags & kTaggedState ? (size_t)tagged_group_words(ra.H, ra.rows_pg) * 8 : 0);
@@ -840,6 +840,8 @@ struct RecPlan {
   // 16-row one
   bool solo = false, row = false, quad = false;
   bool row_own = false;  // with row: W x in the launch itself, where its input allows it
+  bool marked = false;   // rec_kernel with m in marked words, at mark_at bytes of the synchronization scratch (0: in the m exchange buffer)
+  int64_t mark_at = 0;
   bool rest32 = false;  // groups of 64 rows: a rest of the batch that fits one launch of groups of 32 runs as those
 };
 
@@ -1008,8 +1010,14 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1, bo
     ra.flags &= ~kFourPredSlots;
     if (lds_need() > 160 * 1024) ra.flags |= kFourPredSlots;
     // one tile of outputs per workgroup, whole pieces of eight of them, and room behind the statistics words of all groups
-    if (rec_tagged(ra) && sync_bytes(p2_groups) + (int64_t)p2_groups * tagged_group_words(h.H, 32) * 8 <= (int64_t)kSyncBytes)
+    const int64_t words_end = sync_bytes(p2_groups) + (int64_t)p2_groups * tagged_group_words(h.H, 32) * 8;
+    // m goes through marked words then: in the m exchange buffer, or, where a short call leaves it too few slots, behind those
+    const bool m_here = proj && T < kMarkSlots;
+    if (rec_tagged(ra) && words_end + (m_here ? (int64_t)kMarkSlots * ra.Bp * ra.npadp : 0) <= (int64_t)kSyncBytes) {
       ra.flags |= kTaggedState;
+      p.marked = proj;
+      if (m_here) p.mark_at = words_end;
+    }
   }
   p.groups = p2_groups;
   p.rest32 = !p.use16 && ra.rows_pg == 64 && ra.ks == 32 && B > p2_groups * 64;
@@ -1451,7 +1459,7 @@ int lstm_int_forward(const lstm_int_model *cm, const int8_t *x, int32_t T, int32
     if (use_p2) {
       ra.tx2 = reinterpret_cast<const int4 *>(tx);
       ra.h0 = h0; ra.out = out;
-      ra.mbuf = reinterpret_cast<int8_t *>(wsb + ws.m2);
+      ra.mbuf = reinterpret_cast<int8_t *>(plan.mark_at ? wsb + ws.sync + plan.mark_at : wsb + ws.m2);
       ra.c_in = c_state ? c_state + c_off : nullptr;
       ra.c_out = c_state ? c_state + c_off : nullptr;
       if (!plan.solo) set_sync(ra, m, wsb + ws.sync);
@@ -1477,7 +1485,7 @@ int lstm_int_forward(const lstm_int_model *cm, const int8_t *x, int32_t T, int32
         // final h on its way to the state buffer: done by the input GEMM's workgroups ahead of their own
         // work, or by a kernel of their own where the general input GEMM runs
         const int g0 = std::min(p2_groups, (B + ra.rows_pg - 1) / ra.rows_pg);
-        const int64_t clear = sync_bytes(plan, g0);
+        const int64_t clear = sync_bytes(plan, g0), mark = plan.marked ? (int64_t)std::min(T, kMarkSlots - 1) * ra.Bp * ra.npadp : 0;
         const bool ws_gemm = in_gemm_ws_supported(ga);
         if (ws_gemm) {
           ga.has_init = 1;
@@ -1485,10 +1493,11 @@ int lstm_int_forward(const lstm_int_model *cm, const int8_t *x, int32_t T, int32
           ga.init.h0 = h0; ga.init.ld_h0 = d.Hpad; ga.init.rows = B; ga.init.cols = h.H; ga.init.zp = h.zp_h;
           ga.init.sync = reinterpret_cast<int4 *>(wsb + ws.sync); ga.init.sync_vec = clear / 16;
           ga.init.c_src = pend.src; ga.init.c_ld_src = pend.ld; ga.init.c_dst = pend.dst; ga.init.c_cols = pend.cols;
+          ga.init.mark = reinterpret_cast<int4 *>(ra.mbuf); ga.init.mark_vec = mark / 16;
         } else {
           Timed t(m->prof, s, LSTM_INT_K_OTHER);
           launch_init_layer(s, h_state ? h_state + h_off : nullptr, h.H, h0, d.Hpad, B, h.H, h.zp_h, wsb + ws.sync,
-                            clear, pend.src, pend.ld, pend.dst, pend.cols);
+                            clear, pend.src, pend.ld, pend.dst, pend.cols, ra.mbuf, mark);
         }
         pend.dst = nullptr;
         Timed t(m->prof, s, LSTM_INT_K_INPUT_GEMM);
@@ -1528,6 +1537,8 @@ int lstm_int_forward(const lstm_int_model *cm, const int8_t *x, int32_t T, int32
           if (!plan.solo && (b0 > 0 || t0 > 0)) {
             Timed t(m->prof, s, LSTM_INT_K_OTHER);
             launch_fill_i16(s, reinterpret_cast<int16_t *>(wsb + ws.sync), sync_bytes(plan, ra.groups) / 2, 0);
+            if (plan.marked && b0 == 0)
+              launch_fill_i16(s, reinterpret_cast<int16_t *>(ra.mbuf), (int64_t)(kMarkSlots - 1) * ra.Bp * ra.npadp / 2, (int16_t)kMarkFree);
           }
           if (!rec_extents_ok(ra, ws, T, t0, proj)) return LSTM_INT_E_WORKSPACE;
           if (!plan.solo) plant_misplaced(m, s, wsb + ws.sync);

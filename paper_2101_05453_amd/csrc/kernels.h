@@ -74,7 +74,7 @@ void launch_fill_rows_i8(hipStream_t s, int8_t *dst, int ld_dst, int rows, int c
 // and, if c_dst is not NULL, c_dst [rows, c_cols] <- c_src [rows, c_ld_src] -- one launch
 void launch_init_layer(hipStream_t s, const int8_t *h_src, int ld_src, int8_t *h0, int ld_h0, int rows, int cols,
                        int zp, void *sync, int64_t sync_bytes, const int8_t *c_src, int c_ld_src, int8_t *c_dst,
-                       int c_cols);
+                       int c_cols, void *mark = nullptr, int64_t mark_bytes = 0);
 void launch_copy_i16(hipStream_t s, const int16_t *src, int16_t *dst, int64_t n);
 void launch_fill_i16(hipStream_t s, int16_t *dst, int64_t n, int value);
 // q[i] = clamp(floor(x[i] / scale + 1/2) + zp, -128, 127), computed in double (Sec. 3.2.4)

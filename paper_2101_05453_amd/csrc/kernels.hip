@@ -645,12 +645,14 @@ __global__ void init_layer_kernel(LayerInit w) {
 
 void launch_init_layer(hipStream_t s, const int8_t *h_src, int ld_src, int8_t *h0, int ld_h0, int rows, int cols,
                        int zp, void *sync, int64_t sync_bytes, const int8_t *c_src, int c_ld_src, int8_t *c_dst,
-                       int c_cols) {
+                       int c_cols, void *mark, int64_t mark_bytes) {
   LayerInit w;
+  w.mark = static_cast<int4 *>(mark); w.mark_vec = mark_bytes / 16;
   w.h_src = h_src; w.ld_src = ld_src; w.h0 = h0; w.ld_h0 = ld_h0; w.rows = rows; w.cols = cols; w.zp = zp;
   w.sync = static_cast<int4 *>(sync); w.sync_vec = sync_bytes / 16;  // a multiple of 16 bytes, 16-byte aligned
   w.c_src = c_src; w.c_ld_src = c_ld_src; w.c_dst = c_dst; w.c_cols = c_cols;
-  const int64_t most = std::max<int64_t>(std::max<int64_t>(w.sync_vec, (int64_t)rows * ld_h0), c_dst ? (int64_t)rows * c_cols : 0);
+  int64_t most = std::max<int64_t>(std::max<int64_t>(w.sync_vec, (int64_t)rows * ld_h0), c_dst ? (int64_t)rows * c_cols : 0);
+  most = std::max<int64_t>(most, w.mark_vec);
   hipLaunchKernelGGL(init_layer_kernel, dim3(grid_for(most)), dim3(256), 0, s, w);
 }
 

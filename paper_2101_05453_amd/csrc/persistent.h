@@ -18,6 +18,10 @@ namespace lstm_int {
 //   tx2[(t*Bp + b) / 32][cell tile][half][lane][8]
 // with lane = b % 32 + 32 * ((cell % 8) / 4), half 0 = gates i,f, half 1 =
 // gates z,o, and the 8 values = [gate in half][cell % 4].
+// rec_kernel with kTaggedState and a projection: mbuf is [4 slots, escape slot][Bp / 32][npadp / 32][32 rows][32 cells], the four slots (as
+// many of them as there are steps) filled with kMarkFree
+constexpr uint32_t kMarkFree = 0x7F807F80u, kMarkEscape = kMarkFree ^ 1;  // four cells at the ends of their range by turns: hardly ever a value
+constexpr int kMarkSlots = 5;
 // What has to be in place before a layer's recurrent kernel starts: the initial h (given, or the zero
 // point), cleared synchronization words, and -- to save a launch -- a pending copy of rows (the previous
 // layer's final h on its way to the caller's state buffer).  Done by its own small kernel, or by the
@@ -33,9 +37,12 @@ struct LayerInit {
   int c_ld_src;
   int8_t *c_dst;
   int c_cols;
+  int4 *mark;           // mark_vec 16-byte words to fill with kMarkFree
+  long long mark_vec;
 };
 __device__ __forceinline__ void layer_init_device(const LayerInit &w, long long gtid, long long gthreads) {
   for (long long i = gtid; i < w.sync_vec; i += gthreads) w.sync[i] = int4{0, 0, 0, 0};
+  for (long long i = gtid; i < w.mark_vec; i += gthreads) w.mark[i] = int4{(int)kMarkFree, (int)kMarkFree, (int)kMarkFree, (int)kMarkFree};
   const long long total = (long long)w.rows * w.ld_h0;
   for (long long i = gtid; i < total; i += gthreads) {
     const long long r = i / w.ld_h0;

@@ -58,6 +58,17 @@ __device__ __forceinline__ bool group_sync(unsigned *counter, unsigned &epoch, i
   return lds_flag[0] != 0;
 }
 
+// Eight loads of 16 bytes per lane at agent scope (past the L1): w[k] = the 16 bytes at base + at[k]
+__device__ __forceinline__ void poll_marked(const int8_t *base, const unsigned (&at)[8], v4i (&w)[8]) {
+  asm volatile("global_load_dwordx4 %0, %8, %16 sc1\n\tglobal_load_dwordx4 %1, %9, %16 sc1\n\t"
+               "global_load_dwordx4 %2, %10, %16 sc1\n\tglobal_load_dwordx4 %3, %11, %16 sc1\n\t"
+               "global_load_dwordx4 %4, %12, %16 sc1\n\tglobal_load_dwordx4 %5, %13, %16 sc1\n\t"
+               "global_load_dwordx4 %6, %14, %16 sc1\n\tglobal_load_dwordx4 %7, %15, %16 sc1\n\ts_waitcnt vmcnt(0)"
+               : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3]), "=&v"(w[4]), "=&v"(w[5]), "=&v"(w[6]), "=&v"(w[7])
+               : "v"(at[0]), "v"(at[1]), "v"(at[2]), "v"(at[3]), "v"(at[4]), "v"(at[5]), "v"(at[6]), "v"(at[7]), "s"(base)
+               : "memory");
+}
+
 // The status word of the second layer of a launch of two (RecArgs2, the kernel's only argument), NULL if there is none.
 // Read from the argument segment where it is needed, at the end of a launch: as a use of the argument it stayed in a pair of
 // scalar registers through the step loop, and the four-row kernel took 3.4 % longer (512 cells, layer norm, 16 rows).
@@ -549,6 +560,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
   };
 
+  // m in marked words (TAG and a projection): who needs m polls the words that hold it, eight cells of a row in 64 bits, in one of four
+  // slots that take turns.  A word that is not written yet holds kMarkFree in its low half; a value that looks like that, or like
+  // kMarkEscape, leaves in the escape slot, and kMarkEscape says so.  What a word holds is the operand of the product, so that
+  // nothing is unpacked, and there is no store to wait for, no counter and no second trip for the data.
+  auto m_word = [&](int t, int lane) -> int8_t * {  // of lane and lane ^ 32: cells 8 wave .. 8 wave + 7 of row lane % 32
+    int8_t *slot = a.mbuf + (size_t)(t & 3) * a.Bp * a.npadp + ((size_t)(row0 >> 5) * (a.npadp >> 5) + member * 2 + (wave >> 2)) * 1024;
+    return slot + (unsigned)((lane & 31) * 32 + (wave & 3) * 8);
+  };
   const int tid0 = tid;
   const bool tails = a.lut[0].tail | a.lut[1].tail | a.lut[2].tail;  // some table's LDS copy ends before its flat part
   // this lane's operand row of W_proj; rows beyond a tile's prow outputs re-read row 0: their results are never stored
@@ -597,6 +616,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (TAG && t > 0) {
       if (flag[0] == 0) return;
       store_output(t - 1, lane);
+      // everyone's h of step t - 1 is here, so everyone has read m of that step: this lane's word of it is marked as not written, for
+      // step t + 3
+      if (proj && t + 3 < a.T && b2 == 0) *reinterpret_cast<uint32_t *>(m_word(t - 1, lane)) = kMarkFree;
     }
     if (RT > 1) load_tx(t);
     TICK(0);
@@ -1038,6 +1060,18 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         if (n0 < Hr)
           *reinterpret_cast<v2i *>(reinterpret_cast<uint8_t *>(xh + (size_t)(t & 1) * Hr * 8) + (unsigned)(col * Hr + n0) * 2) =
               v2i{(int)__builtin_amdgcn_perm(pk, tag, 0x00050004u), (int)__builtin_amdgcn_perm(pk, tag, 0x00070006u)};
+      } else if (TAG) {  // rows beyond the batch too: their words are polled with the others
+        const auto both = __builtin_amdgcn_permlane32_swap(pk, pk, false, false);
+        uint32_t lo = both[0];
+        if (b2 == 0) {
+          int8_t *const to = m_word(t, lane);
+          if (__builtin_expect((lo ^ kMarkFree) < 2, 0)) {
+            *reinterpret_cast<uint32_t *>(to + (size_t)(4 - (t & 3)) * a.Bp * a.npadp) = lo;
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            lo = kMarkEscape;
+          }
+          *reinterpret_cast<v2i *>(to) = v2i{(int)lo, (int)both[1]};
+        }
       } else if (row < a.B && n0 < a.N) {  // cells past N fill padding of the row (and only ever meet zero weights)
         // scalar bases, 32-bit offsets of the lane: pointers of the lane's own would be held through the loop
         int8_t *mb = mdst + (proj ? ((size_t)((row0 >> 5) + rt) * (a.npadp >> 5) + member * 2 + (wave >> 2)) * 1024
@@ -1050,10 +1084,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       }
     }
     TICK(6);
-    if (proj) {
-      if (!group_sync(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, a.sync_sleep, a.poll_sleep, flag)) return;
-    } else if (TAG && (FL & 8)) {
-      if (!ln) __syncthreads();  // every wave is past R h: the h tile may be filled again
+    if (TAG) {
+      if (!ln) __syncthreads();  // every wave is past R h: the h tile may be filled again, with h or with partial sums
     } else {
       if (!group_sync(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, a.sync_sleep, a.poll_sleep, flag)) return;
     }
@@ -1064,13 +1096,52 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       const int ksteps = a.npadp >> 5;     // 32-wide k steps, a multiple of 4, at most 64 (N <= 2048)
       const int per_wave = (ksteps + 7) >> 3;
       const int kfirst = wave * per_wave;  // the last waves may have fewer, or none
+      const int kend = TAG ? 2 * GS : ksteps;  // TAG: k steps that somebody writes
       for (int pt = 0; pt < my_ptiles; ++pt) {
         const int ptile = member + pt * GS;
         const int8_t *wrow = WpL + wp_lane + pt * a.prow * WLS + kfirst * 32;
-        const int kmine = ksteps - kfirst < per_wave ? ksteps - kfirst : per_wave;  // uniform
+        const int kmine = kend - kfirst < per_wave ? kend - kfirst : per_wave;  // uniform
         // A wave with all eight steps (from 1793 cells on all waves but perhaps the last) runs them straight.  Two layers, projection
         // to 640, layer norm, 256 rows, 32 steps, with the tests -> this: 2048 cells 735 -> 713 us, 1984 752 -> 715, 1856 736 -> 707
         v4i mv[8];
+        auto poll_m = [&]() {
+          const int8_t *mrow = a.mbuf + (size_t)(t & 3) * a.Bp * a.npadp + ((size_t)(row0 >> 5) * ksteps + kfirst) * 1024;
+          const unsigned moff = col * 32 + b2 * 16;
+          unsigned at[8];
+#pragma unroll
+          for (int k = 0; k < 8; ++k) at[k] = moff + (k < kmine ? k : 0) * 1024;
+          int budget = a.spin_limit;
+          uint32_t least;
+          for (int i = 0; i < a.sync_sleep; ++i) __builtin_amdgcn_s_sleep(1);
+          for (;;) {
+            poll_marked(mrow, at, mv);
+            least = 0xFFFFFFFFu;
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+#pragma unroll
+              for (int i = 0; i < 4; i += 2) {
+                const uint32_t d = (uint32_t)mv[k][i] ^ kMarkFree;
+                least = least < d ? least : d;
+              }
+            if (a.extra_arrivals) least = 0;  // tests: words that nobody writes
+            if (__builtin_amdgcn_ballot_w64(least == 0) == 0) break;
+            --budget;
+            if ((budget & 15) == 0 && (budget <= 0 || __hip_atomic_load(a.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
+              __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              flag[0] = 0;
+              break;
+            }
+          }
+          if (__builtin_expect(__builtin_amdgcn_ballot_w64(least == 1) != 0, 0)) {
+            const int8_t *esc = mrow + (size_t)(4 - (t & 3)) * a.Bp * a.npadp;
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+#pragma unroll
+              for (int i = 0; i < 4; i += 2)
+                if ((uint32_t)mv[k][i] == kMarkEscape)
+                  mv[k][i] = (int)__hip_atomic_load(reinterpret_cast<const uint32_t *>(esc + at[k] + 4 * i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          }
+        };
         auto load_m = [&](int rt) {
           // rows of the tile beyond the batch were never written; their results are not stored either
           const int8_t *mrow = a.mbuf + (size_t)t * a.Bp * a.npadp + ((size_t)((row0 >> 5) + rt) * ksteps + kfirst) * 1024;
@@ -1088,7 +1159,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         // a row tile that starts beyond the batch (second tile of a ragged last group) has no rows in the exchange buffer
         // at all; the test is uniform over the workgroup, so the barriers below stay matched
         auto has_rows = [&](int rt) { return rt == 0 || (rt < RT && row0 + rt * 32 < a.B); };
-        load_m(0);
+        if (TAG) {
+          if (kmine > 0) poll_m();
+        } else {
+          load_m(0);
+        }
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
           if (!has_rows(rt)) continue;
