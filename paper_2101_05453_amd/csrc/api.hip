@@ -840,7 +840,7 @@ struct RecPlan {
   // 16-row one
   bool solo = false, row = false, quad = false;
   bool row_own = false;  // with row: W x in the launch itself, where its input allows it
-  bool marked = false;   // rec_kernel with m in marked words, at mark_at bytes of the synchronization scratch (0: in the m exchange buffer)
+  bool marked = false;   // rec_kernel, rec16_kernel with m in marked words, at mark_at bytes of the synchronization scratch (0: in the m exchange buffer)
   int64_t mark_at = 0;
   bool rest32 = false;  // groups of 64 rows: a rest of the batch that fits one launch of groups of 32 runs as those
 };
@@ -967,9 +967,14 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1, bo
     r16.Wp2 = d.Wp2; r16.bp2 = d.bp2; r16.ptiles = d.ptiles; r16.prow = 32;
     // the exchange words share the region of the statistics words with all groups of the launch
     r16.flags &= ~kFourPredSlots;
-    if (d.GS > 1 && (int64_t)256 * 64 * 4 + (int64_t)g16 * share * (kStatGroupBytes + tagged_group_words(h.H, 16) * 8) <= (int64_t)kSyncBytes)
-      r16.flags |= kTaggedState;
+    // (m through marked words then, as below)
+    const int64_t words_end = sync_bytes(g16 * share) + (int64_t)g16 * share * tagged_group_words(h.H, 16) * 8;
+    const bool m_here = proj && T < kMarkSlots;
+    const bool tagged = d.GS > 1 && words_end + (m_here ? (int64_t)share * kMarkSlots * ra.Bp * ra.npadp : 0) <= (int64_t)kSyncBytes;
+    if (tagged) r16.flags |= kTaggedState;
     if (rec16_lds_bytes(r16) <= 160 * 1024) {
+      p.marked = tagged && proj;
+      if (p.marked && m_here) p.mark_at = words_end;
       ra = r16;
       p2_groups = g16;
       p.use16 = true;
@@ -1763,6 +1768,8 @@ static int forward_pair(lstm_int_model *const (&m)[2], const int8_t *x, int32_t 
       ga.tx2 = reinterpret_cast<int4 *>(base[i] + ws[i].tx);
       uint8_t *sync = base[0] + ws[0].sync;
       const int64_t clear = i == 0 ? sync_bytes(plan[0], groups) : 0;
+      const int64_t m_row = (int64_t)plan[i].ra.Bp * plan[i].ra.npadp, mark = plan[i].marked ? std::min(T, kMarkSlots - 1) * m_row : 0;
+      int8_t *mbuf = reinterpret_cast<int8_t *>(plan[i].mark_at ? sync + plan[i].mark_at + i * kMarkSlots * m_row : base[i] + ws[i].m2);
       if (own_input) {
         Timed t(m[i]->prof, s, LSTM_INT_K_OTHER);
         if (pend[i].dst) launch_copy_rows_i8(s, pend[i].src, pend[i].ld, pend[i].dst, pend[i].cols, B, pend[i].cols, 0);
@@ -1775,13 +1782,14 @@ static int forward_pair(lstm_int_model *const (&m)[2], const int8_t *x, int32_t 
         ga.init.h0 = h0; ga.init.ld_h0 = d.Hpad; ga.init.rows = B; ga.init.cols = h.H; ga.init.zp = h.zp_h;
         ga.init.sync = reinterpret_cast<int4 *>(sync); ga.init.sync_vec = clear / 16;
         ga.init.c_src = pend[i].src; ga.init.c_ld_src = pend[i].ld; ga.init.c_dst = pend[i].dst; ga.init.c_cols = pend[i].cols;
+        ga.init.mark = reinterpret_cast<int4 *>(mbuf); ga.init.mark_vec = mark / 16;
         Timed t(m[i]->prof, s, LSTM_INT_K_INPUT_GEMM);
         launch_in_gemm_ws(s, ga, m[i]->num_cus);
       } else {
         {
           Timed t(m[i]->prof, s, LSTM_INT_K_OTHER);
           launch_init_layer(s, h_src, h.H, h0, d.Hpad, B, h.H, h.zp_h, sync, clear, pend[i].src, pend[i].ld, pend[i].dst,
-                            pend[i].cols);
+                            pend[i].cols, mbuf, mark);
         }
         Timed t(m[i]->prof, s, LSTM_INT_K_INPUT_GEMM);
         launch_in_gemm(s, ga);
@@ -1790,7 +1798,7 @@ static int forward_pair(lstm_int_model *const (&m)[2], const int8_t *x, int32_t 
       static_cast<RecArgs &>(ra) = plan[i].ra;
       ra.tx2 = ga.tx2;
       ra.h0 = h0; ra.out = out;
-      ra.mbuf = reinterpret_cast<int8_t *>(base[i] + ws[i].m2);
+      ra.mbuf = mbuf;
       ra.c_in = ra.c_out = c_state[i] ? c_state[i] + c_off[i] : nullptr;
       ra.rev = i;
       ra.ldy = Hl[0] + Hl[1];

@@ -18,8 +18,8 @@ namespace lstm_int {
 //   tx2[(t*Bp + b) / 32][cell tile][half][lane][8]
 // with lane = b % 32 + 32 * ((cell % 8) / 4), half 0 = gates i,f, half 1 =
 // gates z,o, and the 8 values = [gate in half][cell % 4].
-// rec_kernel with kTaggedState and a projection: mbuf is [4 slots, escape slot][Bp / 32][npadp / 32][32 rows][32 cells], the four slots (as
-// many of them as there are steps) filled with kMarkFree
+// rec_kernel with kTaggedState and a projection: mbuf is [4 slots, escape slot][Bp / 32][npadp / 32][32 rows][32 cells], rec16_kernel's
+// [4 slots, escape slot][Bp / 16][npadp / 64][16 rows][64 cells], the four slots (as many of them as there are steps) filled with kMarkFree
 constexpr uint32_t kMarkFree = 0x7F807F80u, kMarkEscape = kMarkFree ^ 1;  // four cells at the ends of their range by turns: hardly ever a value
 constexpr int kMarkSlots = 5;
 // What has to be in place before a layer's recurrent kernel starts: the initial h (given, or the zero

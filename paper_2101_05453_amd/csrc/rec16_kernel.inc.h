@@ -13,11 +13,15 @@
 //
 // The hidden state travels as (value, tag) byte pairs, the tag being the step (kTaggedState, quad_kernel.inc.h has more on it):
 // 16 bytes a thread hold eight cells, and who needs them polls them, up to four loads a thread.  Through the layer output, the
-// group's counter and a load of the tile behind it (the way m still goes, 64 KB as pairs for each workgroup with outputs) -> this,
-// 200 steps, us:
+// group's counter and a load of the tile behind it -> this, 200 steps, us:
 //   1024 cells, 128 rows  788 -> 606, layer norm 1127 -> 908       512 cells, 200 rows  653 -> 510, layer norm 971 -> 774
 //   two directions of 512 cells, 100 rows, 100 steps 364 -> 271    512 cells, 256 outputs, layer norm, 200 rows 1382 -> 1158
 //   2048 cells, 640 outputs, 128 rows 1168 -> 999, layer norm 1592 -> 1396, and peephole 1868 -> 1653; 160 outputs, layer norm 1577 -> 1314
+// With a projection m goes in marked words then (below).  It went through the exchange buffer and the group's counter before (every
+// wave's stores acknowledged, one add per workgroup, polls, a load of the tile); 100 steps, us: 2048 cells, 640 outputs, 128 rows 504 ->
+// 451, layer norm 726 -> 667, and peephole 849 -> 788; 160 outputs, layer norm 682 -> 617; 1088 cells, 320 outputs, layer norm, 100
+// rows 659 -> 598; 512 cells, 256 outputs, layer norm, 200 rows 588 -> 544.  A pause ahead of the first poll of m only adds to the step (4 x
+// 64 clocks: 0.1 us), and so do pauses of the workgroups without outputs between their polls of the state, from 8 x 64 clocks on.
 // The counter remains where one workgroup is the group, and where the words of all groups find no room.  Either way is a form of its
 // own (TAG): with both in one kernel, chosen by a test in the step loop, the registers that each keeps for itself spilled (12 to
 // 80 bytes a lane at 2048 cells with layer norm, three times the scalar ones everywhere), and the same calls took 632, 950, 533, 847,
@@ -119,22 +123,27 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   constexpr int TILE_KB = (16 * LS + 1023) / 1024;
   // m or h of a step leaves through LDS, by one wave in stores of 16 bytes a lane, which are acknowledged 0.25 us before those
   // of two bytes a lane from all waves.  Behind a second round of statistics the barrier that takes costs more: 2048 cells
-  // with peephole and layer norm 9.2 -> 9.5 us a step.
-  constexpr bool GATHER = !(ph && ln);
+  // with peephole and layer norm 9.2 -> 9.5 us a step (marked words come in whole pieces of eight cells, and no other barrier follows).
+  constexpr bool GATHER = !(ph && ln) || TAG == 2;
   uint8_t *p = lds;
   int8_t *hT = reinterpret_cast<int8_t *>(p);
   // hidden state of the step on its way out, where the loads past the h tile go, which nobody reads: 16-byte pieces of row r
   // at r * 64, exchanged by r / 4 so that rows in the same banks differ.  With neither layer norm nor a projection two of them by
   // turns: no barrier lies between the barrier behind which wave 1 reads it once more (store_output) and the next hidden state.
   constexpr int mflip = TAG == 1 && !ln ? 1024 : 0;
-  int8_t *const mS0 = reinterpret_cast<int8_t *>(lds) + TILE_KB * 1024;
+  // In marked words (below) wave 0 reads m there while other waves may have their partial sums of the projection already: with layer
+  // norm, whose barriers lie between R h and m, it is where wave 0's own sums go, else where the statistics would be.  Whoever has a
+  // word of the step's hidden state knows that m has been read.
+  constexpr int kPredBytes = 8 * 2 * 64 * 16, kTileBytes = (TILE_KB + 1) * 1024 + mflip;  // one spare chunk for the loads past the tile
+  constexpr int kScratch = TAG == 2 && kTileBytes < kPredBytes ? kPredBytes : kTileBytes;
+  static_assert(sizeof(LnRow2) * items >= 1024);
+  int8_t *const mS0 = reinterpret_cast<int8_t *>(lds) + (TAG != 2 ? TILE_KB * 1024 : ln ? 0 : kScratch + items * 8);
   auto mS_of = [&](int t) { return mS0 + (t & 1) * mflip; };
   auto piece_at = [](int row, int piece) { return row * 64 + ((piece ^ (row >> 2)) << 4); };
   v4i *pred = reinterpret_cast<v4i *>(p);  // projection partials [8 waves][2 halves][64 lanes] reuse the h tile between steps
   {
-    const size_t tile_bytes = (size_t)(TILE_KB + 1) * 1024 + mflip;  // one spare chunk for the loads past the tile
-    const size_t pred_bytes = proj ? 8 * 2 * 64 * 16 : 0;
-    p += tile_bytes > pred_bytes ? tile_bytes : pred_bytes;
+    const int pred_bytes = proj ? kPredBytes : 0;
+    p += kTileBytes > pred_bytes ? kTileBytes : pred_bytes;
   }
   u64 *red = reinterpret_cast<u64 *>(p);                 p += (size_t)items * 8;  // [item] sums
   LnRow2 *lnrow = reinterpret_cast<LnRow2 *>(p);         p += (size_t)items * sizeof(LnRow2);
@@ -374,6 +383,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       }
     }
   };
+  // m in marked words (TAG == 2), as in rec_kernel: 64 bits of eight cells whose low half is kMarkFree are not written yet; four slots
+  // of [row / 16][k step of 64 cells = member][row % 16][64 cells] that take turns, and one for what looks like a mark.
+  auto m_word = [&](int t) -> int8_t * {  // wave 0: the 16 cells of a row that this lane stores
+    return a.mbuf + (size_t)(t & 3) * a.Bp * a.npadp + (((size_t)(row0 >> 4) * (a.npadp >> 6) + member) << 10) + lane * 16;
+  };
   // Tagged state: the layer output of step t, which nobody waits for, behind the polls of the next step
   uint32_t hkeep = 0;
   auto store_output = [&](int t) {
@@ -437,6 +451,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (tagged && t > 0) {
       if (flag[0] == 0) return;
       store_output(t - 1);
+      // everyone's h of step t - 1 is here, so everyone has read m of that step: the words that this lane wrote are marked as not
+      // written, for step t + 3
+      if (TAG == 2 && t + 3 < a.T && wave == 0) *reinterpret_cast<v4i *>(m_word(t - 1)) = v4i{} + (int)kMarkFree;
     }
     // the W x terms of this step were requested one step ahead (they come from HBM)
     const int32_t txw[4] = {txn[0], txn[1], txn[2], txn[3]};
@@ -786,6 +803,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
               for (int i = 0; i < 4; ++i) w[i] = (int)__builtin_amdgcn_perm((uint32_t)piece[2 * k + (i >> 1)], tag, i & 1 ? 0x00070006u : 0x00050004u);
               *reinterpret_cast<v4i *>(dst + 16 * k) = w;
             }
+        } else if (TAG == 2) {  // rows beyond the batch too: their words are polled with the others
+          int8_t *const to = m_word(t);
+          v4i w = piece;
+          if (__builtin_expect(((uint32_t)w[0] ^ kMarkFree) < 2 || ((uint32_t)w[2] ^ kMarkFree) < 2, 0)) {
+            *reinterpret_cast<v4i *>(to + (size_t)(4 - (t & 3)) * a.Bp * a.npadp) = w;
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (((uint32_t)w[0] ^ kMarkFree) < 2) w[0] = (int)kMarkEscape;
+            if (((uint32_t)w[2] ^ kMarkFree) < 2) w[2] = (int)kMarkEscape;
+          }
+          *reinterpret_cast<v4i *>(to) = w;
         } else if (srow < a.B && n < a.N) {
           if (proj) {  // the same exchange buffer
             *reinterpret_cast<v4i *>(a.mbuf + (size_t)t * a.Bp * a.npadp +
@@ -803,35 +830,79 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       }
     }
     TICK(6);
-    if ((proj || !tagged) && !group_sync(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, a.sync_sleep, a.poll_sleep, flag)) return;
+    if (!tagged && !group_sync(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, a.sync_sleep, a.poll_sleep, flag)) return;
     TICK(7);
 
     // ---- projection (Sec. 3.2.8): tile pt of 32 outputs as two 16-wide halves, K = N split over the waves
     if (proj) {
-      const int ksteps = a.npadp >> 6;
+      const int ksteps = TAG == 2 ? GS : a.npadp >> 6;  // marked words: k steps that somebody writes
       const int per_wave = (ksteps + 7) >> 3;
       const RescaleHi pp = prm->p;
       const int32_t zp_h = prm->zp_h;
-      for (int pt = 0; pt < my_ptiles; ++pt) {
-        const int ptile = member + pt * GS;
-        v4i pacc[2] = {v4i{0, 0, 0, 0}, v4i{0, 0, 0, 0}};
-        const int8_t *mbase = a.mbuf + (size_t)t * a.Bp * a.npadp + (((size_t)(row0 >> 4) * ksteps * 16 + r) << 6) + (q << 4);
-        const int8_t *wbase = WpL + ((size_t)pt * 32 + r) * WLS + (q << 4);
-        // all loads of the wave's k steps first (at most 4: N <= 2048); steps past the end re-read the
-        // last one against zero weights
-        int4 mv[4];
+      auto poll_m = [&](int t, v4i (&mv)[4]) {  // the wave's k steps; steps past the end: the last one again
+        const int8_t *base = a.mbuf + (size_t)(t & 3) * a.Bp * a.npadp + (((size_t)(row0 >> 4) * (a.npadp >> 6)) << 10);
+        unsigned at[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           int kk = wave * per_wave + (k < per_wave ? k : per_wave - 1);
           kk = kk < ksteps ? kk : ksteps - 1;
-          mv[k] = *reinterpret_cast<const int4 *>(mbase + (size_t)kk * 1024);
+          at[k] = (unsigned)(kk * 1024 + r * 64 + q * 16);
+        }
+        int budget = a.spin_limit;
+        uint32_t least;
+        for (;;) {
+          poll_pairs(reinterpret_cast<const u64 *>(base), at, mv);
+          least = 0xFFFFFFFFu;
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int i = 0; i < 4; i += 2) {
+              const uint32_t d = (uint32_t)mv[k][i] ^ kMarkFree;
+              least = least < d ? least : d;
+            }
+          if (a.extra_arrivals) least = 0;  // tests: words that nobody writes
+          if (__builtin_amdgcn_ballot_w64(least == 0) == 0) break;
+          --budget;
+          if ((budget & 15) == 0 && (budget <= 0 || __hip_atomic_load(a.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
+            __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            flag[0] = 0;
+            break;
+          }
+        }
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(least == 1) != 0, 0)) {
+          const int8_t *esc = base + (size_t)(4 - (t & 3)) * a.Bp * a.npadp;
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int i = 0; i < 4; i += 2)
+              if ((uint32_t)mv[k][i] == kMarkEscape)
+                mv[k][i] = (int)__hip_atomic_load(reinterpret_cast<const uint32_t *>(esc + at[k] + 4 * i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+      };
+      for (int pt = 0; pt < my_ptiles; ++pt) {
+        const int ptile = member + pt * GS;
+        v4i pacc[2] = {v4i{0, 0, 0, 0}, v4i{0, 0, 0, 0}};
+        const int8_t *mbase = a.mbuf + (size_t)t * a.Bp * a.npadp + (((size_t)(row0 >> 4) * (a.npadp >> 6) * 16 + r) << 6) + (q << 4);
+        const int8_t *wbase = WpL + ((size_t)pt * 32 + r) * WLS + (q << 4);
+        // all loads of the wave's k steps first (at most 4: N <= 2048); steps past the end re-read the
+        // last one against zero weights
+        v4i mv[4];
+        if constexpr (TAG == 2) {
+          poll_m(t, mv);
+        } else {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            int kk = wave * per_wave + (k < per_wave ? k : per_wave - 1);
+            kk = kk < ksteps ? kk : ksteps - 1;
+            mv[k] = *reinterpret_cast<const v4i *>(mbase + (size_t)kk * 1024);
+          }
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           int kk = wave * per_wave + (k < per_wave ? k : per_wave - 1);
           const bool real = k < per_wave && kk < ksteps;
           kk = kk < ksteps ? kk : ksteps - 1;
-          const v4i mf = v4i{mv[k].x, mv[k].y, mv[k].z, mv[k].w};
+          const v4i mf = mv[k];
 #pragma unroll
           for (int ct = 0; ct < 2; ++ct) {
             v4i wf = *reinterpret_cast<const v4i *>(wbase + (size_t)ct * 16 * WLS + kk * 64);

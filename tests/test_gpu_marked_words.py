@@ -1,0 +1,70 @@
+"""m in marked words (the 16-row and the 32-row kernel, tagged state with a projection): fewer steps than slots, slots that come round
+again, workgroups without outputs, rows beyond the batch -- and values of m that look like the marks themselves."""
+import numpy as np
+import pytest
+import torch
+
+import lstm_workloads as wl
+from paper_2101_05453_amd import binding
+from parity_util import assert_equal, calibrate_on_gpu, run_and_compare
+
+pytestmark = pytest.mark.gpu
+LN, PH, PROJ, CIFG = wl.LAYER_NORM, wl.PEEPHOLE, wl.PROJECTION, wl.CIFG
+
+
+@pytest.mark.parametrize("rows16", [0, 2])
+@pytest.mark.parametrize("T", [1, 3, 5, 6, 13])
+@pytest.mark.parametrize("N,H,B,flags", [
+    (200, 152, 37, 0), (600, 296, 19, PH), (600, 200, 40, LN), (1100, 16, 33, LN | PH), (650, 640, 16, CIFG | LN | PH), (136, 24, 50, PH | CIFG),
+])
+def test_slots_in_turn(orc, N, H, B, flags, T, rows16):
+    layers, x = wl.make_custom([24], N, H, flags | PROJ, B, T, seed=N + T, weight_param=0.9 / N ** 0.5)
+    run_and_compare(orc, layers, x, f"m{N}h{H}t{T}", trace=False, options={"rows16": rows16})
+
+
+@pytest.mark.parametrize("T", [3, 12])
+@pytest.mark.parametrize("flags", [0, LN, PH | LN])
+def test_two_directions(orc, flags, T):
+    models, olds, x = [], [], None
+    for seed in (3, 4):
+        layers, xf = wl.make_custom([24], 300, 136, flags | PROJ, 21, T, seed=seed, weight_param=0.06)
+        x = xf if x is None else x
+        calibrate_on_gpu(layers, x)
+        models.append(binding.prepare(layers))
+        olds.append(orc.prepare(layers))
+    models[1].set_option("reverse", 1)
+    for m in models:
+        m.set_option("rows16", 2)
+    xq = models[0].quantize_input(torch.from_numpy(x).cuda())
+    y = binding.forward_bidirectional(models[0], models[1], xq).cpu().numpy()
+    assert all(m.device_status() == 0 for m in models)
+    xh = xq.cpu().numpy()
+    assert_equal("forward", y[:, :, :136], orc.forward(olds[0], xh))
+    assert_equal("backward", y[:, :, 136:], orc.forward(olds[1], np.ascontiguousarray(xh[::-1]))[::-1])
+
+
+@pytest.mark.parametrize("rows16", [0, 2])
+@pytest.mark.parametrize("flags,most", [(0, 0.97), (PH | LN, 0.93)])
+def test_values_that_look_like_marks(orc, flags, most, rows16):
+    """Cells driven to both ends of the range of m by turns, every eighth of them to either side of -127."""
+    N, H, B, T = 200, 136, 37, 9
+    layers, x = wl.make_custom([24], N, H, flags | PROJ, B, T, seed=1, weight_param=0.02)
+    lay, n = layers[0], np.arange(N)
+    for g in (0, 1):  # input and forget gate open
+        lay.b[g][:] = 5.0
+    lay.b[2][:] = np.where(n % 2, 6.0, -6.0)
+    lay.b[3][:] = np.where(n % 8 == 0, 2.5 + 2.0 * n / N, 6.0)
+    if flags & LN:  # the biases alone
+        for g in range(4):
+            lay.Lw[g][:] = 0.05
+    xd = calibrate_on_gpu(layers, x)
+    lay.m_min, lay.m_max = -most, most
+    model, old = binding.prepare(layers), orc.prepare(layers)
+    model.set_option("rows16", rows16)
+    xq = model.quantize_input(xd)
+    y = model.forward(xq)
+    assert model.device_status() == 0
+    want, trace = orc.forward(old, xq.cpu().numpy(), trace_layer=0)
+    words = np.ascontiguousarray(trace["m"][:, :, :N // 8 * 8]).view(np.uint32)[:, :, ::2]
+    assert (words == 0x7F807F80).any() and (words == 0x7F807F81).any()
+    assert_equal("y", y.cpu().numpy(), want)
