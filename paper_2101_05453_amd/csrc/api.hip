@@ -776,6 +776,14 @@ int forward_stack(lstm_int_model *m, const int8_t *x, int32_t T, int32_t B, int8
   sa.h_final = h_state;
   const size_t flags_off = kStackFlagsOff;
   sa.flags = reinterpret_cast<unsigned *>(wsb + sp.sync + flags_off);
+  // a launch of one item per layer: m and the rows between the layers in marked words
+  const bool one = T == 1 && sa.row_tiles == 1;
+  const size_t escape_off = flags_off + 2 * (size_t)L * 128;
+  if (one) {
+    sa.near_end = sa.flags + (size_t)L * 32;
+    sa.m_escape = reinterpret_cast<int8_t *>(wsb + sp.sync + escape_off);
+    if (escape_off + L * sp.mbuf_stride > kSyncBytes) return LSTM_INT_E_UNSUPPORTED;  // (512 KB at most)
+  }
   sa.flag_sleep = m->flag_sleep;
   sa.tick_layer = std::min(L - 1, std::max(0, m->phase_timing - 1));
   {
@@ -819,6 +827,11 @@ int forward_stack(lstm_int_model *m, const int8_t *x, int32_t T, int32_t B, int8
     for (int l = 0; l < L; ++l) si.zp[l] = m->host[l].zp_h;
     si.sync = reinterpret_cast<int4 *>(wsb + sp.sync);
     si.sync_vec = (long long)((flags_off + (size_t)L * sa.row_tiles * 128 + 15) / 16);
+    if (one) {
+      si.sync_vec = (long long)((kStackFlagsOff + 2 * (size_t)L * 128) / 16);
+      si.mark = reinterpret_cast<int4 *>(sa.mbuf_base); si.mark_vec = (long long)(L * sp.mbuf_stride / 16);
+      si.mark_out = reinterpret_cast<uint32_t *>(sa.out_base); si.mark_out_stride = (long long)sp.out_stride;
+    }
     launch_stack_init(s, si);
   }
   plant_misplaced(m, s, wsb + sp.sync);

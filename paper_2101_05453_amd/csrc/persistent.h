@@ -387,6 +387,8 @@ struct StackArgs {
   int8_t *h_final;           // NULL, or the caller's h state: layer l's last h, [B, H], at + l * B * H
   unsigned *flags;           // [L][row_tiles] lines of 32 words, zeroed: steps finished, in word 0 for the whole layer, or, in
                              // a launch of one item per layer, in word w for workgroup w of the layer
+  unsigned *near_end;        // launch of one item per layer: [L] lines of 32 words, zeroed: word 0 = workgroup 0 has its m
+  int8_t *m_escape;          // ... and the escape slots of m (kMarkEscape), of layer l at + l * mbuf_stride; mbuf and out are marked there
   int lutc_lds_bytes;        // LDS bytes of the largest cell-format tanh copy among the layers (0: all share the
                              // gate tanh table's copy); host side of the LDS budget
   int flag_sleep;            // pause between two polls of a flag, x 64 clocks
@@ -401,6 +403,10 @@ struct StackInit {
   int zp[8];            // code of real 0 per layer (h_src == NULL)
   int4 *sync;           // sync_vec 16-byte words to clear
   long long sync_vec;
+  int4 *mark;           // mark_vec 16-byte words to fill with kMarkFree
+  long long mark_vec;
+  uint32_t *mark_out;   // NULL, or [L - 1][rows, ld_h0] bytes, layers mark_out_stride bytes apart: cols of them to be marked, the rest cleared
+  long long mark_out_stride;
 };
 void launch_stack_init(hipStream_t s, const StackInit &w);
 

@@ -70,22 +70,30 @@ hipError_t stack_init() {
 }
 
 // Everything a stack launch needs in place: the initial h of every layer ([B, Hpad], given rows or the
-// layer's zero point, padding bytes 0) and the zeroed synchronization words and flags.
+// layer's zero point, padding bytes 0), the zeroed synchronization words and flags, and the marks of words not stored yet.
 __global__ void stack_init_kernel(StackInit w) {
   const long long gtid = blockIdx.x * (long long)blockDim.x + threadIdx.x, gthreads = (long long)gridDim.x * blockDim.x;
   for (long long i = gtid; i < w.sync_vec; i += gthreads) w.sync[i] = int4{0, 0, 0, 0};
-  const long long per_layer = (long long)w.rows * w.ld_h0, total = per_layer * w.L;
-  for (long long i = gtid; i < total; i += gthreads) {
-    const int l = (int)(i / per_layer);
-    const long long j = i - l * per_layer;
-    const long long r = j / w.ld_h0;
-    const int col = (int)(j - r * w.ld_h0);
-    w.h0[i] = col < w.cols ? (w.h_src ? w.h_src[((long long)l * w.rows + r) * w.cols + col] : (int8_t)w.zp[l]) : (int8_t)0;
+  for (long long i = gtid; i < w.mark_vec; i += gthreads) w.mark[i] = int4{(int)kMarkFree, (int)kMarkFree, (int)kMarkFree, (int)kMarkFree};
+  // words of four cells; 32-bit indices, whose division is a tenth of a 64-bit one
+  const unsigned row_words = (unsigned)w.ld_h0 / 4, rows = (unsigned)w.rows, total = (unsigned)w.L * rows * row_words;
+  for (unsigned i = (unsigned)gtid; i < total; i += (unsigned)gthreads) {
+    const unsigned row = i / row_words, l = row / rows, word = i - row * row_words;
+    const int col = (int)word * 4;
+    uint32_t v = 0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      if (col + c < w.cols) v |= (uint32_t)(uint8_t)(w.h_src ? w.h_src[(size_t)row * w.cols + col + c] : (int8_t)w.zp[l]) << (8 * c);
+    reinterpret_cast<uint32_t *>(w.h0)[i] = v;
+    if (w.mark_out && l + 1 < (unsigned)w.L)
+      w.mark_out[(size_t)l * (w.mark_out_stride / 4) + (i - l * rows * row_words)] = col < w.cols ? kMarkFree : 0u;
   }
 }
 
 void launch_stack_init(hipStream_t s, const StackInit &w) {
-  const long long most = w.sync_vec > (long long)w.rows * w.ld_h0 * w.L ? w.sync_vec : (long long)w.rows * w.ld_h0 * w.L;
+  const long long words = (long long)w.rows * w.ld_h0 / 4 * w.L;  // below 2^31: stack_supported holds the rows below 2^19
+  long long most = w.sync_vec > words ? w.sync_vec : words;
+  if (w.mark_vec > most) most = w.mark_vec;
   long long blocks = (most + 255) / 256;
   if (blocks > 1024) blocks = 1024;
   if (blocks < 1) blocks = 1;

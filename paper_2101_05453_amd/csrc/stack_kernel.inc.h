@@ -14,6 +14,11 @@
 //     was never read before, so no cache on the reading side can hold an older
 //     copy.
 //   * the cell state lives in memory between the items of a row tile.
+// A launch of one item per layer (ONE, the streaming call) hands m and the rows between the layers on in marked words: who needs
+// them polls the words themselves.  8 layers of 2048 cells, 640 outputs, layer norm, 32 rows, one step, us: 111.6 with counters and flags,
+// 105.9 with m in marked words, 103.0 with the rows too, 101.3 with what the first item needs asked for in the order of its use.
+// What is left: 20 us until layer 0 has its weights (10.5 MB through one XCD), then 9 to 10 us a layer: W x 0.8, gate sums 0.6, statistics
+// 1.4, layer norm to the cell 1.5, hidden 0.7, m and the projection 2.3, the rows to the next XCD 1.3 to 3.5.
 // Included by the stack_inst_*.hip translation units.
 #pragma once
 
@@ -148,58 +153,59 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int WLS = a.npadp + 16;
   const int my_ptiles = proj ? (a.ptiles > member ? (a.ptiles - member + GS - 1) / GS : 0) : 0;
 
-  // ---- one-time loads: R slice -> registers; per-cell parameters, tables, W_proj tiles -> LDS
-  v4i Wf[KS];
-  // 1 KB per wave load, all in flight together before the first is pinned to its place
-  auto load_operands = [&](const int4 *src, int n) {
-    int4 w[KS];
+  // ---- one-time loads, in the order in which they are needed: the first item's rows of h -> LDS, the R slice -> registers,
+  // tables and W_proj tiles -> LDS.  Loads return in order, so what is small and has to
+  // go through a register first is asked for ahead of them.
+  constexpr int TILE_KB = (32 * LS + 1023) / 1024;
+  constexpr int NCH = (TILE_KB + WAVES - 1) / WAVES;  // chunks per wave
+  // the tile of 32 rows starting at row0 of a [.., ld] buffer -> LDS; bytes of a row beyond `width`, the
+  // row padding read offset 0 of the tile (they only ever meet zero weights or are
+  // not used); BYPASS = the loads pass the L2 by (rows written by another XCD during this launch)
+  auto tile_to_lds = [&](const int8_t *base, int ld, int width, int row0, auto bypass_tag) {
+    constexpr int AUX = decltype(bypass_tag)::value ? 16 : 0;  // sc1
+    const int8_t *tile = base + (size_t)row0 * ld;
+    asm volatile("" : "+s"(tile));
+    int l = lane;
+    asm volatile("" : "+v"(l));  // the lane's offsets are computed here, not kept
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) w[ks] = src[(size_t)(ks < n ? ks : 0) * 64];
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      Wf[ks] = v4i{w[ks].x, w[ks].y, w[ks].z, w[ks].w};
-      asm volatile("" : "+v"(Wf[ks]));
+    for (int j = 0; j < NCH; ++j) {
+      if (WAVES * (j + 1) > TILE_KB && wave + WAVES * j >= TILE_KB) continue;  // uniform
+      const int o = (wave + WAVES * j) * 1024 + l * 16;
+      const int r = o / LS, c = o - r * LS, last = a.B - 1 - row0;
+      const unsigned off = (r < 32 && c < width) ? (unsigned)((r < last ? r : last) * ld + c) : 0u;
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(tile + off),
+                                       (__attribute__((address_space(3))) void *)(hT + (wave + WAVES * j) * 1024), 16, 0, AUX);
     }
-    __builtin_amdgcn_sched_barrier(0);
   };
-  load_operands(sl.R2 + (size_t)(member * WAVES + wave) * KS * 64 + lane, KS);
-  const int cell_w = wave * 8 + 4 * b2;  // + c, within the workgroup's 64 cells
+  int16_t Lq = 0, Pq = 0;
+  int32_t qb = 0, bh = 0, bx = 0, bp = 0;
   if (tid < 256) {
     const int g = tid >> 6, n = tid & 63;
     const size_t idx = (size_t)g * a.Ncp + member * 64 + n;
-    LdL[tid] = ln ? ln_weight_scaled(sl.Lq4[idx]) : 0.0;
-    bdL[tid] = ln ? ln_bias_scaled(sl.qb4[idx]) : 0.0;
-    PqL[tid] = (ph && g < 3) ? sl.Pq3[idx] : 0;
-    bhL[tid] = sl.bh4[idx];
-    bxL[tid] = sl.bx2[(size_t)member * 256 + tid];  // the workgroup's 8 tiles x 32 rows
-  }
-  if (tid < 4) {
-    prm->h[tid] = rescale_hi_prepare(sl.Mh[tid], sl.rh[tid]);
-    prm->x[tid] = rescale_hi_prepare(sl.Mx[tid], sl.rx[tid]);
-    prm->c[tid] = rescale_hi_prepare(tid < 3 && ph ? sl.Mc[tid] : 0, tid < 3 && ph ? sl.rc[tid] : 33);
-    prm->ln[tid] = rescale_hi_prepare(sl.Mln[tid], ln ? sl.rln[tid] : 33);
-  }
-#pragma unroll
-  for (int i = 0; i < 3; ++i)  // (indexed by the thread these arrays would lie in scratch memory)
-    if (tid == i) {
-      LutLds d;
-      d.dom = i == 2 && share_tanh ? lw[1].dom : lw[i].dom;  // a shared copy has the gate table's prefix
-      d.sh = i == 2 && share_tanh ? lw[1].sh : lw[i].sh;
-      d.offD = (int32_t)(lutD[i] - lds);
-      d.offB = (int32_t)(lutB[i] - lds);
-      d.offT = lutTl[i] ? (int32_t)(lutTl[i] - lds) : 0;
-      d.pad[0] = d.pad[1] = d.pad[2] = 0;
-      lutP[i] = d;
+    if (ln) {
+      Lq = sl.Lq4[idx];
+      qb = sl.qb4[idx];
     }
-  if (tid == 0) {
-    prm->m = rescale_hi_prepare(sl.Mm, sl.rm);
-    prm->p = rescale_hi_prepare(proj ? sl.Mp : 0, proj ? sl.rp : 33);
-    prm->zp_m = sl.zp_m; prm->zp_h = sl.zp_h;
-    prm->inv_n = 1.0 / (double)a.N;
-    prm->m_c = sl.m_c; prm->glo = ln ? -32767 : -32768;
+    if (ph && g < 3) Pq = sl.Pq3[idx];
+    bh = sl.bh4[idx];
+    bx = sl.bx2[(size_t)member * 256 + tid];  // the workgroup's 8 tiles x 32 rows
   }
-  for (int i = tid; i < 32 * LS / 16; i += 64 * WAVES) reinterpret_cast<int4 *>(hT)[i] = int4{0, 0, 0, 0};
+  if (my_ptiles > 0 && tid < 32) bp = sl.bp2[member * 32 + tid];
+  tile_to_lds(h0, a.Hpad, a.Hpad, 0, std::false_type{});
+  v4i Wf[KS];
+  // 1 KB per wave load, all in flight together before the first is pinned to its place
+  auto ask_operands = [&](const int4 *src, int n, auto &w) {
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) w[ks] = *reinterpret_cast<const v4i *>(src + (size_t)(ks < n ? ks : 0) * 64);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto pin_operands = [&](auto &w) {
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(w[ks]));
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  ask_operands(sl.R2 + (size_t)(member * WAVES + wave) * KS * 64 + lane, KS, Wf);
+  
   {
     auto dma = [&](const void *src, const void *dst) {
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
@@ -229,20 +235,53 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       }
       dma(src, WpL + c * 1024);
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   }
-
-  constexpr int TILE_KB = (32 * LS + 1023) / 1024;
-  constexpr int NCH = (TILE_KB + WAVES - 1) / WAVES;  // chunks per wave
-
-  if (my_ptiles > 0 && tid < 32) bpL[tid] = sl.bp2[member * 32 + tid];
+  __builtin_amdgcn_sched_barrier(0);
+  const int cell_w = wave * 8 + 4 * b2;  // + c, within the workgroup's 64 cells
+  if (tid < 256) {
+    LdL[tid] = ln ? ln_weight_scaled(Lq) : 0.0;
+    bdL[tid] = ln ? ln_bias_scaled(qb) : 0.0;
+    PqL[tid] = Pq;
+    bhL[tid] = bh;
+    bxL[tid] = bx;
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i)  // (indexed by the thread these would be loads that return behind the others)
+    if (tid == i) {
+      prm->h[i] = rescale_hi_prepare(sl.Mh[i], sl.rh[i]);
+      prm->x[i] = rescale_hi_prepare(sl.Mx[i], sl.rx[i]);
+      prm->c[i] = rescale_hi_prepare(i < 3 && ph ? sl.Mc[i < 3 ? i : 0] : 0, i < 3 && ph ? sl.rc[i < 3 ? i : 0] : 33);
+      prm->ln[i] = rescale_hi_prepare(sl.Mln[i], ln ? sl.rln[i] : 33);
+    }
+#pragma unroll
+  for (int i = 0; i < 3; ++i)  // (indexed by the thread these arrays would lie in scratch memory)
+    if (tid == i) {
+      LutLds d;
+      d.dom = i == 2 && share_tanh ? lw[1].dom : lw[i].dom;  // a shared copy has the gate table's prefix
+      d.sh = i == 2 && share_tanh ? lw[1].sh : lw[i].sh;
+      d.offD = (int32_t)(lutD[i] - lds);
+      d.offB = (int32_t)(lutB[i] - lds);
+      d.offT = lutTl[i] ? (int32_t)(lutTl[i] - lds) : 0;
+      d.pad[0] = d.pad[1] = d.pad[2] = 0;
+      lutP[i] = d;
+    }
+  if (tid == 0) {
+    prm->m = rescale_hi_prepare(sl.Mm, sl.rm);
+    prm->p = rescale_hi_prepare(proj ? sl.Mp : 0, proj ? sl.rp : 33);
+    prm->zp_m = sl.zp_m; prm->zp_h = sl.zp_h;
+    prm->inv_n = 1.0 / (double)a.N;
+    prm->m_c = sl.m_c; prm->glo = ln ? -32767 : -32768;
+  }
+  if (my_ptiles > 0 && tid < 32) bpL[tid] = bp;
   if (tid < items) red[tid] = 0;
   if (tid < 12) tickL[tid] = 0;
   if (tid == 0) {
     flag[0] = 1;
     flag[1] = 0;
   }
-  __syncthreads();
+  pin_operands(Wf);  // the rows of h came ahead of them
+  if (!ONE) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  lds_barrier();
 
   // optional phase timing (diagnostics): workgroup 0 of one layer, 100 MHz wall clock ticks per phase
   long long tick_last = 0;
@@ -289,23 +328,83 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int n_items = a.T * RTILES;
   const int pre_h = sl.pre_h, pre_x = sl.pre_x;
 
-  // the tile of 32 rows starting at row0 of a [.., ld] buffer -> LDS; bytes of a row beyond `width`, the
-  // row padding read offset 0 of the tile (they only ever meet zero weights or are
-  // not used); BYPASS = the loads pass the L2 by (rows written by another XCD during this launch)
-  auto tile_to_lds = [&](const int8_t *base, int ld, int width, int row0, auto bypass_tag) {
-    constexpr int AUX = decltype(bypass_tag)::value ? 16 : 0;  // sc1
-    const int8_t *tile = base + (size_t)row0 * ld;
-    asm volatile("" : "+s"(tile));
-    int l = lane;
-    asm volatile("" : "+v"(l));  // the lane's offsets are computed here, not kept
+  // ONE: the rows of the layer below are polled themselves.  Its words of four outputs hold kMarkFree until they are stored; a
+  // value that looks like that is believed when all workgroups that store rows have said, in a word each, that theirs are stored.
+  auto poll_input = [&](auto count, int tid) {
+    constexpr int U = decltype(count)::value;
+    const int per_row = 2 * kx;
+    const uint32_t per_piece = (1u << 20) / (uint32_t)per_row + 1;  // c / per_row = c per_piece / 2^20: c < 2048, per_row <= 64
+    const int sayers = proj ? (a.ptiles < GS ? a.ptiles : GS) : GS, lane = tid & 63;
+    unsigned at[U], to[U];
+    v4i w[U];
 #pragma unroll
-    for (int j = 0; j < NCH; ++j) {
-      if (WAVES * (j + 1) > TILE_KB && wave + WAVES * j >= TILE_KB) continue;  // uniform
-      const int o = (wave + WAVES * j) * 1024 + l * 16;
-      const int r = o / LS, c = o - r * LS, last = a.B - 1 - row0;
-      const unsigned off = (r < 32 && c < width) ? (unsigned)((r < last ? r : last) * ld + c) : 0u;
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(tile + off),
-                                       (__attribute__((address_space(3))) void *)(hT + (wave + WAVES * j) * 1024), 16, 0, AUX);
+    for (int k = 0; k < U; ++k) {
+      const int c = k * 512 + tid < 64 * kx ? k * 512 + tid : tid;
+      const int r = (int)((uint32_t)c * per_piece >> 20), pc = c - r * per_row;
+      at[k] = (unsigned)((r < a.B ? r : a.B - 1) * ldx + pc * 16);
+      to[k] = (unsigned)(r * LS + pc * 16);
+    }
+    int budget = a.spin_limit;
+    bool all_said = false;
+    for (;;) {
+      poll_pairs(reinterpret_cast<const u64 *>(xin), at, w);
+      bool open = a.extra_arrivals != 0;  // tests: rows that never come
+#pragma unroll
+      for (int k = 0; k < U; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) open |= (uint32_t)w[k][i] == kMarkFree;
+      if (all_said || __builtin_amdgcn_ballot_w64(open) == 0) break;
+      --budget;
+      if ((budget & 7) == 0) {
+        if (budget <= 0 || __hip_atomic_load(a.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
+          __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          flag[0] = 0;
+          break;
+        }
+        const unsigned said =
+            lane < sayers ? __hip_atomic_load(sa.flags + (layer - 1) * 32 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 1u;
+        all_said = a.extra_arrivals == 0 && __builtin_amdgcn_ballot_w64(said == 0) == 0;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < U; ++k)
+      if (k * 512 + tid < 64 * kx) *reinterpret_cast<v4i *>(hT + to[k]) = w[k];
+  };
+
+  // ONE: this wave's k steps of m in marked words, as in rec_kernel
+  auto poll_m = [&](const int8_t *mrow, unsigned moff, int kmine, v4i (&mv)[8]) {
+    unsigned at[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) at[k] = moff + (k < kmine ? k : 0) * 1024;
+    int budget = a.spin_limit;
+    uint32_t least;
+    for (;;) {
+      poll_marked(mrow, at, mv);
+      least = 0xFFFFFFFFu;
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; i += 2) {
+          const uint32_t d = (uint32_t)mv[k][i] ^ kMarkFree;
+          least = least < d ? least : d;
+        }
+      if (a.extra_arrivals) least = 0;  // tests: words that nobody writes
+      if (__builtin_amdgcn_ballot_w64(least == 0) == 0) break;
+      --budget;
+      if ((budget & 15) == 0 && (budget <= 0 || __hip_atomic_load(a.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
+        __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        flag[0] = 0;
+        break;
+      }
+    }
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(least == 1) != 0, 0)) {
+      const int8_t *esc = sa.m_escape + (size_t)layer * sa.mbuf_stride + (mrow - mbuf);
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; i += 2)
+          if ((uint32_t)mv[k][i] == kMarkEscape)
+            mv[k][i] = (int)__hip_atomic_load(reinterpret_cast<const uint32_t *>(esc + at[k] + 4 * i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   };
 
@@ -333,12 +432,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
 
     // ---- h^{t-1} rows of the tile -> LDS; R h on the MFMA; kept as packed int16 terms
-    {
+    if (!ONE && it > 0) {  // the first item's rows are there
       const int8_t *hp = t == 0 ? h0 : out + (size_t)(t - 1) * a.B * a.Hpad;
       tile_to_lds(hp, a.Hpad, a.Hpad, row0, std::false_type{});
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
     }
-    __syncthreads();
     TICK(0);
     // The first part of this wave's slice of W (one tile of kx fragments of 1 KB, contiguous) is asked for
     // ahead of its use, one word per 128-byte line, so that it is on its way into the L2 while R h runs and
@@ -385,10 +484,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         pack(std::integral_constant<int, 2>{});
     }
     // A launch of one item per layer (one step, one row tile -- the streaming call) has no further use for
-    // R: W takes its place in the registers while the layers below are still at work, and W x below runs
-    // from registers instead of waiting for memory.
+    // R: W takes its place in the registers while the layers below are still at work, and W x below
+    // runs from registers instead of waiting for memory.
     constexpr bool w_resident = ONE;
-    if (w_resident) load_operands(reinterpret_cast<const int4 *>(sl.W2f + ((size_t)(member * WAVES + wave) * kx) * 1024) + lane, kx);
+    if constexpr (w_resident) {  // (beside R, in registers of its own, W spills 12 to 240 bytes a lane: 136 us for the call below instead of 101)
+      ask_operands(reinterpret_cast<const int4 *>(sl.W2f + ((size_t)(member * WAVES + wave) * kx) * 1024) + lane, kx, Wf);
+      pin_operands(Wf);
+    }
     TICK(1);
 
     // ---- W x^t: weights streamed from memory as MFMA operands, DW k steps ahead
@@ -399,14 +501,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int ks = 0; ks < DW && ks < KS; ++ks)
       if (ks < kx && !w_resident) wq[ks] = wload(ks);
-    // The input rows: wait until the layer below has finished step t of this row tile.  ONE: each of its workgroups that
-    // store rows says so itself, in a word of the tile's line that a lane of wave 0 polls, so that its last barrier is not
-    // waited for (8 layers of 2048 cells, 32 rows: 120.6 -> 111.7 us); else the first workgroup does, behind that barrier.
+    // The input rows: wait until the layer below has finished step t of this row tile.  ONE: until one of its workgroups is
+    // at the end of its step; what they hand over is polled itself then.
     if (layer > 0) {
-      const int sayers = !ONE ? 1 : proj ? (a.ptiles < GS ? a.ptiles : GS) : GS;
-      if (wave == 0 && lane < sayers) {
-        const unsigned *f = sa.flags + ((size_t)(layer - 1) * RTILES + rtile) * 32 + lane;
-        const unsigned want = (unsigned)(t + 1 + (ONE ? a.extra_arrivals : 0));
+      if (tid == 0) {
+        const unsigned *f = ONE ? sa.near_end + (layer - 1) * 32 : sa.flags + ((size_t)(layer - 1) * RTILES + rtile) * 32;
+        const unsigned want = (unsigned)(t + 1);
         int budget = a.spin_limit;
         for (;;) {
           const unsigned v = __hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -423,7 +523,17 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     __syncthreads();  // also: every wave has read its h fragments, the tile can be overwritten
     if (flag[0] == 0) return;
     TICK(2);
-    {
+    if (ONE && layer > 0) {
+      const int mine = (64 * kx - wave * 64 + 511) >> 9;  // 16-byte pieces of the tile for a thread of this wave
+      if (mine >= 4)
+        poll_input(std::integral_constant<int, 4>{}, tid);
+      else if (mine == 3)
+        poll_input(std::integral_constant<int, 3>{}, tid);
+      else if (mine == 2)
+        poll_input(std::integral_constant<int, 2>{}, tid);
+      else if (mine == 1)
+        poll_input(std::integral_constant<int, 1>{}, tid);
+    } else {
       const int8_t *xp = xin + (size_t)t * a.B * ldx;
       if (x_bypass)
         tile_to_lds(xp, ldx, kx * 32, row0, std::true_type{});
@@ -434,7 +544,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
       for (int i = 0; i < NPF; ++i) asm volatile("" ::"v"(pf[i]));  // the prefetched words themselves are not used
     }
+    if (ONE) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // tables and W_proj tiles, of waves that polled nothing too
     __syncthreads();
+    if (ONE && flag[0] == 0) return;
     TICK(3);
     v16i acc;
 #pragma unroll
@@ -569,6 +681,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       return *flag != 0;
     };
     TICK(5);
+    if (ONE && !proj && !last_layer && member == 0 && tid == 0)
+      __hip_atomic_store(sa.near_end + layer * 32, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (ln) {
       publish_stats(0, g_first, ph ? 2 : 3);
       if (!collect_stats(0, g_first, ph ? 2 : 3)) return;
@@ -790,7 +904,19 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         const int32_t mq = sat8(rescale_sat16_pre<0>(om, pm) + zp_m);
         pk |= (uint32_t)(mq & 0xFF) << (8 * c);
       }
-      if (row < a.B && n0 < a.N) {
+      if (ONE && proj) {  // marked words as in rec_kernel, rows beyond the batch too
+        const auto both = __builtin_amdgcn_permlane32_swap(pk, pk, false, false);
+        uint32_t lo = both[0];
+        if (b2 == 0) {
+          const unsigned off = (member * 2 + (wave >> 2)) * 1024 + col * 32 + (wave & 3) * 8;
+          if (__builtin_expect((lo ^ kMarkFree) < 2, 0)) {
+            *reinterpret_cast<uint32_t *>(sa.m_escape + (size_t)layer * sa.mbuf_stride + off) = lo;
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            lo = kMarkEscape;
+          }
+          *reinterpret_cast<v2i *>(mbuf + off) = v2i{(int)lo, (int)both[1]};
+        }
+      } else if (row < a.B && n0 < a.N) {
         if (proj) {
           const size_t off = (((size_t)(row >> 5) * (a.npadp >> 5) + (n0 >> 5)) * 32 + (row & 31)) * 32 + (n0 & 31);
           *reinterpret_cast<uint32_t *>(mdst + off) = pk;
@@ -804,7 +930,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       }
     }
     TICK(8);
-    if ((proj || !ONE) && !group_sync(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, a.sync_sleep, a.poll_sleep, flag)) return;
+    if (ONE && proj && !last_layer && member == 0 && tid == 0)
+      __hip_atomic_store(sa.near_end + layer * 32, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (ONE && proj && !ln) __syncthreads();  // every wave is past W x: the partial sums may lie in the tile
+    if (!ONE && !group_sync(counter, epoch, GS + a.extra_arrivals, a.status, a.spin_limit, a.sync_sleep, a.poll_sleep, flag)) return;
     TICK(9);
 
     // ---- projection (Sec. 3.2.8)
@@ -812,7 +941,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       const int ksteps = a.npadp >> 5;     // 32-wide k steps, a multiple of 4, at most 64 (N <= 2048)
       const int per_wave = (ksteps + 7) >> 3;
       const int kfirst = wave * per_wave;  // the last waves may have fewer, or none
-      const int kmine = ksteps - kfirst < per_wave ? ksteps - kfirst : per_wave;  // uniform
+      const int kend = ONE ? 2 * GS : ksteps;  // ONE: k steps that somebody writes
+      const int kmine = kend - kfirst < per_wave ? kend - kfirst : per_wave;  // uniform
       for (int pt = 0; pt < my_ptiles; ++pt) {
         const int ptile = member + pt * GS;
         const int8_t *wrow = WpL + wp_lane + pt * a.prow * WLS + kfirst * 32;
@@ -822,14 +952,17 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         v16i pacc;
 #pragma unroll
         for (int v = 0; v < 16; ++v) pacc[v] = 0;
+        if (ONE && kmine > 0) poll_m(mrow, moff, kmine, mv);
         if (kmine == 8) {  // straight, as in rec_kernel (8 layers of 2048 cells, 32 rows, one step 110.6 -> 107.7 us)
+          if (!ONE)
 #pragma unroll
-          for (int k = 0; k < 8; ++k) mv[k] = *reinterpret_cast<const v4i *>(mrow + moff + k * 1024);
+            for (int k = 0; k < 8; ++k) mv[k] = *reinterpret_cast<const v4i *>(mrow + moff + k * 1024);
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int k = 0; k < 8; ++k)
             pacc = __builtin_amdgcn_mfma_i32_32x32x32_i8(*reinterpret_cast<const v4i *>(wrow + k * 32), mv[k], pacc, 0, 0, 0);
         } else {
+          if (!ONE)
 #pragma unroll
           for (int k = 0; k < 8; ++k)
             if (k < kmine) mv[k] = *reinterpret_cast<const v4i *>(mrow + moff + k * 1024);
@@ -862,11 +995,17 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
           for (int c = 0; c < 2; ++c)
             hq[c] = (uint32_t)(sat8(rescale_sat16_pre(sum[c] + (pt == 0 ? bpL[pl + c] : sl.bp2[ptile * 32 + pl + c]), pp) + zp_h) & 0xFF);
+          const size_t orow0 = (size_t)t * a.B + row0;
+          int8_t *od = out + orow0 * a.Hpad + ptile * a.prow + (unsigned)(col * a.Hpad + pl);
+          // an output past H falls into the padding of the row (and only ever meets zero weights)
+          if (ONE) {  // whole words, which the layer above polls
+            const uint32_t pk = hq[0] | hq[1] << 8;
+            const auto both = __builtin_amdgcn_permlane32_swap(pk, pk, false, false);
+            if (b2 == 0 && row < a.B && p0 < a.H)
+              __hip_atomic_store(reinterpret_cast<uint32_t *>(od), both[0] | both[1] << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          }
           if (row < a.B && p0 < a.H) {
-            const size_t orow0 = (size_t)t * a.B + row0;
-            int8_t *od = out + orow0 * a.Hpad + ptile * a.prow + (unsigned)(col * a.Hpad + pl);
-            // an output past H falls into the padding of the row (and only ever meets zero weights)
-            __hip_atomic_store(reinterpret_cast<uint16_t *>(od), (uint16_t)(hq[0] | hq[1] << 8), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (!ONE) __hip_atomic_store(reinterpret_cast<uint16_t *>(od), (uint16_t)(hq[0] | hq[1] << 8), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (yout) {
               int8_t *yd = yout + orow0 * a.H + ptile * a.prow + (unsigned)(col * a.H + pl);
               yd[0] = (int8_t)hq[0];
@@ -879,7 +1018,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             }
           }
         }
-        // the last tile's partial sums are overwritten behind the group barrier only
+        // the last tile's partial sums are overwritten behind the group barrier only, or not at all
         if (pt + 1 < my_ptiles) __syncthreads();
       }
       TICK(10);

@@ -1,5 +1,6 @@
-"""m in marked words (the 16-row and the 32-row kernel, tagged state with a projection): fewer steps than slots, slots that come round
-again, workgroups without outputs, rows beyond the batch -- and values of m that look like the marks themselves."""
+"""m in marked words (the 16-row and the 32-row kernel, tagged state with a projection; a stacked launch of one item per layer, whose layers
+hand their rows on the same way): fewer steps than slots, slots that come round again, workgroups without outputs, rows beyond the
+batch -- and values that look like the marks themselves."""
 import numpy as np
 import pytest
 import torch
@@ -43,28 +44,59 @@ def test_two_directions(orc, flags, T):
     assert_equal("backward", y[:, :, 136:], orc.forward(olds[1], np.ascontiguousarray(xh[::-1]))[::-1])
 
 
+def _ends_of_the_range(inputs, N, H, flags, B, T, most):
+    """Cells driven to both ends of the range of m by turns, every eighth of them to either side of -127."""
+    layers, x = wl.make_custom(inputs, N, H, flags, B, T, seed=1, weight_param=0.02)
+    n = np.arange(N)
+    for lay in layers:
+        for g in (0, 1):  # input and forget gate open
+            lay.b[g][:] = 5.0
+        lay.b[2][:] = np.where(n % 2, 6.0, -6.0)
+        lay.b[3][:] = np.where(n % 8 == 0, 2.5 + 2.0 * n / N, 6.0)
+        if flags & LN:  # the biases alone
+            for g in range(4):
+                lay.Lw[g][:] = 0.05
+    xd = calibrate_on_gpu(layers, x)
+    for lay in layers:
+        lay.m_min, lay.m_max = -most, most
+        if not flags & PROJ:
+            lay.h_min, lay.h_max = -most, most
+    return layers, xd
+
+
+def _words(m):  # of four cells, the first of eight
+    m = np.ascontiguousarray(m[:, :, :m.shape[2] // 8 * 8])
+    return m.view(np.uint32)[:, :, ::2]
+
+
 @pytest.mark.parametrize("rows16", [0, 2])
 @pytest.mark.parametrize("flags,most", [(0, 0.97), (PH | LN, 0.93)])
 def test_values_that_look_like_marks(orc, flags, most, rows16):
-    """Cells driven to both ends of the range of m by turns, every eighth of them to either side of -127."""
-    N, H, B, T = 200, 136, 37, 9
-    layers, x = wl.make_custom([24], N, H, flags | PROJ, B, T, seed=1, weight_param=0.02)
-    lay, n = layers[0], np.arange(N)
-    for g in (0, 1):  # input and forget gate open
-        lay.b[g][:] = 5.0
-    lay.b[2][:] = np.where(n % 2, 6.0, -6.0)
-    lay.b[3][:] = np.where(n % 8 == 0, 2.5 + 2.0 * n / N, 6.0)
-    if flags & LN:  # the biases alone
-        for g in range(4):
-            lay.Lw[g][:] = 0.05
-    xd = calibrate_on_gpu(layers, x)
-    lay.m_min, lay.m_max = -most, most
+    layers, xd = _ends_of_the_range([24], 200, 136, flags | PROJ, 37, 9, most)
     model, old = binding.prepare(layers), orc.prepare(layers)
     model.set_option("rows16", rows16)
     xq = model.quantize_input(xd)
     y = model.forward(xq)
     assert model.device_status() == 0
     want, trace = orc.forward(old, xq.cpu().numpy(), trace_layer=0)
-    words = np.ascontiguousarray(trace["m"][:, :, :N // 8 * 8]).view(np.uint32)[:, :, ::2]
-    assert (words == 0x7F807F80).any() and (words == 0x7F807F81).any()
+    assert (_words(trace["m"]) == 0x7F807F80).any() and (_words(trace["m"]) == 0x7F807F81).any()
+    assert_equal("y", y.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("flags,most", [(0, 0.9), (PROJ, 0.97), (LN, 0.9), (PH | LN | PROJ, 0.93)])
+@pytest.mark.parametrize("B", [1, 32])
+def test_marks_between_layers_of_a_one_step_stack(orc, B, flags, most):
+    T, L = 7, 3
+    layers, xd = _ends_of_the_range([24] + [136 if flags & PROJ else 200] * (L - 1), 200, 136, flags, B, T, most)
+    model, old = binding.prepare(layers), orc.prepare(layers)
+    model.set_option("stack", 2)
+    model.set_option("row_stack", 0)
+    xq = model.quantize_input(xd)
+    H = layers[0].output_size
+    hs = torch.cat([torch.full((B * H,), model.get_quant(l)["zp_h"], dtype=torch.int8) for l in range(L)]).cuda()
+    cs = torch.zeros(L * B * 200, dtype=torch.int16).cuda()
+    y = torch.cat([model.forward(xq[t:t + 1].contiguous(), h_state=hs, c_state=cs) for t in range(T)])
+    assert model.device_status() == 0
+    want, trace = orc.forward(old, xq.cpu().numpy(), trace_layer=0)
+    assert (_words(trace["m"]) == 0x7F807F80).any()
     assert_equal("y", y.cpu().numpy(), want)
