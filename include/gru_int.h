@@ -136,8 +136,8 @@ int gru_int_forward(const gru_int_model *model, const int8_t *x, int32_t T, int3
 /*
  * Options: "persistent" 1 (default) / 0 = never the one-launch form;
  * "spin_limit" = polls after which a wait inside the persistent kernel gives
- * up; "sync_sleep" = pause before the first poll of the flags (groups of 16 and
- * 32 rows), in units of 64 clocks; "barrier_never_completes" 1 = test hook: every barrier waits for an
+ * up; "sync_sleep" = pause before the first look at the others' state (groups of
+ * 16 rows), in units of 64 clocks; "barrier_never_completes" 1 = test hook: every barrier waits for an
  * arrival that never comes (keep spin_limit small); "reset_status" clears the
  * status word (synchronizes the device).  Results never depend on the tuning
  * options.  Unknown keys or values give LSTM_INT_E_INVALID_ARG.

@@ -423,7 +423,7 @@ struct gru_int_model {
   bool profiling = false;
   std::vector<GruTimed> timed;
   int persistent = 1;   // layers that fit run all their steps in one launch (gru_seq.hip)
-  int spin_limit = 1 << 21, sync_sleep = 8;
+  int spin_limit = 1 << 21, sync_sleep = 4;
   int extra_arrivals = 0;  // test hook (option "barrier_never_completes")
   int *status = nullptr;  // device word: nonzero once a wait inside a persistent kernel gave up (1) or placement failed (2)
   int num_cus = 0;
@@ -461,7 +461,7 @@ GruWs gru_workspace(const gru_int_model *m, int64_t T, int64_t B) {
   w.hop[1] = off; off += align256(max_hop);
   w.h16 = off; off += align256(sum_h16);
   w.sync = off; off += kGruSyncBytes;
-  w.hop_seq = off; off += align256(max_hop * (size_t)T);  // the persistent kernels' exchange buffer: one copy per step
+  w.hop_seq = off; off += align256(max_hop * (size_t)std::max<int64_t>(T, kGruAllSlots));  // the persistent kernels' exchange buffer
   w.total = off;
   return w;
 }
@@ -748,6 +748,7 @@ int gru_int_forward(const gru_int_model *m, const int8_t *x, int32_t T, int32_t 
     }
     da.A = in;  // rows of d.Ip bytes, 16-byte aligned: the caller's, the copy, or the layer below's
     GruSeqArgs sa{};
+    size_t mark_bytes = 0;
     if (seq) {
       sa.B = B; sa.N = N; sa.T = T; sa.Kp = d.Kp;
       sa.GS = d.Kp / 64; sa.rows_pg = rows_pg;
@@ -762,6 +763,7 @@ int gru_int_forward(const gru_int_model *m, const int8_t *x, int32_t T, int32_t 
       sa.y = l == L - 1 ? y : nullptr;
       sa.hx = reinterpret_cast<int8_t *>(ws + w.hop_seq);
       sa.hx_step = hop_bytes(B, d.Kp);
+      mark_bytes = rows_pg == 16 ? sa.hx_step * std::min(T, kGruSlots) : 0;
       for (int g = 0; g < 3; ++g) {
         sa.Mh[g] = q.Mh[g];
         sa.rh[g] = 31 - q.eh[g];
@@ -775,6 +777,8 @@ int gru_int_forward(const gru_int_model *m, const int8_t *x, int32_t T, int32_t 
         ga.has_init = 1;
         ga.init.sync = reinterpret_cast<int4 *>(sa.sync);
         ga.init.sync_vec = (long long)(gru_seq_sync_bytes(sa) / 16);
+        ga.init.mark = reinterpret_cast<int4 *>(sa.hx);
+        ga.init.mark_vec = (long long)(mark_bytes / 16);
       }
     }
     timed_begin(GRU_INT_K_INPUT_GEMM, 1);
@@ -794,7 +798,10 @@ int gru_int_forward(const gru_int_model *m, const int8_t *x, int32_t T, int32_t 
       for (int b0 = 0; b0 < B; b0 += max_groups * rows_pg) {
         sa.batch0 = b0;
         sa.groups = std::min((B - b0 + rows_pg - 1) / rows_pg, max_groups);
-        if (!ws_gemm || b0 > 0) launch_fill_i16(s, reinterpret_cast<int16_t *>(sa.sync), (int64_t)gru_seq_sync_bytes(sa) / 2, 0);
+        if (!ws_gemm && mark_bytes)  // groups of 16 rows: one launch has them all
+          launch_init_layer(s, nullptr, 0, nullptr, 0, 0, 0, 0, sa.sync, (int64_t)gru_seq_sync_bytes(sa), nullptr, 0, nullptr, 0, sa.hx, (int64_t)mark_bytes);
+        else if (!ws_gemm || b0 > 0)
+          launch_fill_i16(s, reinterpret_cast<int16_t *>(sa.sync), (int64_t)gru_seq_sync_bytes(sa) / 2, 0);
         if (launch_gru_seq(s, sa) != hipSuccess) return LSTM_INT_E_DEVICE;
       }
       timed_end();

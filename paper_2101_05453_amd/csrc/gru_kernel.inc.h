@@ -18,6 +18,11 @@ __device__ __forceinline__ void dma16(const void *src, void *dst) {
                                    (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
 }
 
+__device__ __forceinline__ void dma16_agent(const void *src, void *dst) {  // past the L1
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
+                                   (__attribute__((address_space(3))) void *)dst, 16, 0, 16 /* sc1 */);
+}
+
 // All of this wave's vector memory operations are done.  (The builtin, not an asm: the compiler then knows it too, and adds
 // no wait of its own before reads of the LDS that the transfers above filled.)
 __device__ __forceinline__ void wait_vmem() {

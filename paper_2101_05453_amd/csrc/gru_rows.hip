@@ -223,6 +223,66 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   };
   // a piece: bytes 4 q + 2 kh of lane (c16, blk) are this lane's two cells
   auto mine = [&]() { return (blk * 16 + c16) * 16 + 4 * q + 2 * kh; };
+  // Groups of 16 rows: the state travels in marked words, as m does in rec_kernel.  Who needs a piece fetches it until no 64 bits of it
+  // hold kMarkFree, and what looks like a mark leaves through an escape slot.  Slots by turns, an escape slot for the even steps and
+  // one for the odd: who stores step t + 2 has seen step t + 1 of all others, who had step t of everyone before they made that.
+  auto slot_of = [&](int slot) { return hx0 + (size_t)slot * a.hx_step; };
+  auto store_marked = [&](int t) {  // by one wave, from LDS, in whole words
+    v4i w = stage[lane];
+    const unsigned at = member * 1024 + lane * 16;
+    const bool lo = ((uint32_t)w[0] ^ kMarkFree) < 2, hi = ((uint32_t)w[2] ^ kMarkFree) < 2;
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(lo || hi) != 0, 0)) {
+      int8_t *const esc = slot_of(kGruSlots + (t & 1)) + at;
+      if (lo) *reinterpret_cast<int *>(esc) = w[0];
+      if (hi) *reinterpret_cast<int *>(esc + 8) = w[2];
+      wait_vmem();
+      if (lo) w[0] = (int)kMarkEscape;
+      if (hi) w[2] = (int)kMarkEscape;
+    }
+    *reinterpret_cast<v4i *>(slot_of(t & (kGruSlots - 1)) + at) = w;
+  };
+  // By the wave that stores the pieces, when the group's state of step t + 1 is here: then everyone has read this one, whose words
+  // are marked for step t + 4.  (The next piece leaves behind a wait for this store, and step t + 4 is looked for behind that piece.)
+  auto mark_piece = [&](int t) {
+    *reinterpret_cast<v4i *>(slot_of(t & (kGruSlots - 1)) + (unsigned)(member * 1024 + lane * 16)) = v4i{} + (int)kMarkFree;
+  };
+  auto fetch_marked = [&](int t) {  // an eighth of the tile per wave, until every word is there
+    const int8_t *src = slot_of(t & (kGruSlots - 1)) + lane * 16;
+    v4i *const tile = hT + m0 * 64 + lane;
+    int budget = a.spin_limit;
+    uint32_t least;
+    for (;;) {
+#pragma unroll
+      for (int i = 0; i < (KS + 7) / 8; ++i)
+        if (m0 + i < m1) dma16_agent(src + (size_t)(m0 + i) * 1024, hT + (m0 + i) * 64);
+      wait_vmem();
+      least = 0xFFFFFFFFu;
+#pragma unroll
+      for (int i = 0; i < (KS + 7) / 8; ++i)
+        if (m0 + i < m1) {
+          const v4i w = tile[i * 64];
+          const uint32_t d0 = (uint32_t)w[0] ^ kMarkFree, d1 = (uint32_t)w[2] ^ kMarkFree, d = d0 < d1 ? d0 : d1;
+          least = least < d ? least : d;
+        }
+      if (a.never) least = 0;
+      if (__builtin_amdgcn_ballot_w64(least == 0) == 0) break;
+      if (gru_spent(a, budget)) {
+        __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        flag[0] = 0;
+        return;
+      }
+    }
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(least == 1) != 0, 0)) {
+      const int8_t *esc = slot_of(kGruSlots + (t & 1)) + lane * 16;
+      for (int m = m0; m < m1; ++m)
+#pragma unroll
+        for (int k = 0; k < 4; k += 2) {
+          int *const w = reinterpret_cast<int *>(tile + (m - m0) * 64) + k;
+          if ((uint32_t)*w == kMarkEscape)
+            *w = __hip_atomic_load(reinterpret_cast<const int *>(esc + (size_t)m * 1024 + 4 * k), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+  };
   auto store_piece = [&](int t, int rt) {  // by one wave, from LDS: stores of 16 bytes a lane are acknowledged sooner than two-byte ones of all waves
     *reinterpret_cast<v4i *>(hx0 + (size_t)t * a.hx_step + (size_t)(rt * ks_n + member) * 1024 + lane * 16) = stage[rt * 64 + lane];
   };
@@ -286,19 +346,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         wait_vmem();
         __syncthreads();
       } else {
-        *reinterpret_cast<uint16_t *>(hx0 + (size_t)t * a.hx_step + (size_t)member * 1024 + mine()) = (uint16_t)pk;
-        wait_vmem();
-        __syncthreads();
-        if (wave == 0) {
-          raise(0, t + 1);
-          for (int i = 0; i < a.sync_sleep; ++i) __builtin_amdgcn_s_sleep(1);
-          poll(0, t + 1);
-        }
         lds_barrier();
-        fetch(t, 0);
-        wait_vmem();
-        __syncthreads();
+        if (wave == 0) store_marked(t);
+        for (int i = 0; i < a.sync_sleep; ++i) __builtin_amdgcn_s_sleep(1);  // a first look too early costs the arrivals
+        fetch_marked(t);
+        lds_barrier();
         if (flag[0] == 0) return;
+        if (wave == 0 && t > 0 && t + kGruSlots < T) mark_piece(t - 1);
       }
       if (wave == 1) output(t, 0);
     }

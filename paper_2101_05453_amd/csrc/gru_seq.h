@@ -24,8 +24,9 @@ struct GruSeqArgs {
   int32_t zero_state;
   int8_t *h8;                 // [T][B][Kp] for the layer above, or NULL
   int8_t *y;                  // [T][B][N] or NULL
-  int8_t *hx;                 // rows_pg > 4: the exchange buffer [T][row tile of 16][Kp / 64][64 lanes][16 B], every line written
-  size_t hx_step;             //   once and never read before that; bytes of one step
+  int8_t *hx;                 // rows_pg > 4: the exchange buffer, steps or slots of [row tile of 16][Kp / 64][64 lanes][16 B].  32 rows: [T],
+  size_t hx_step;             //   every line written once and never read before that; 16: [kGruAllSlots], as many of the first
+                              //   kGruSlots as there are steps filled with kMarkFree.  hx_step: bytes of one
   int32_t Mh[3], rh[3];       // 3 <= rh <= 62
   LutWide lut[2];             // sigma, tanh
   uint8_t *sync;              // kGruSyncBytes, zero at launch up to gru_seq_sync_bytes
@@ -34,6 +35,8 @@ struct GruSeqArgs {
   int32_t never;              // test hook: every wait is for something that never comes
 };
 
+// gru_rows_kernel, 16 rows: slots that the state of a step passes through by turns, and with the two escape slots (kMarkEscape) behind them
+constexpr int kGruSlots = 4, kGruAllSlots = kGruSlots + 2;
 // scratch: placement words [8][32 words of 8 B], flags [256 workgroups][2 row tiles][64 B], exchange words [256 workgroups][2][64 words]
 constexpr size_t kGruFlagsOff = 2048, kGruWordsOff = kGruFlagsOff + 256 * 128, kGruSyncBytes = kGruWordsOff + 256 * 1024;
 inline size_t gru_seq_sync_bytes(const GruSeqArgs &a) {

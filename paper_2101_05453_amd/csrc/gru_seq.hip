@@ -10,18 +10,24 @@
 //    workgroup scope, polled at agent scope; they meet in the L2 of the group's one XCD, see quad_kernel.inc.h.  Stored at
 //    agent scope, through the L2 to memory: 512 cells, 16 rows, 100 steps 152 -> 267 us.)
 //  * gru_rows_kernel (gru_rows.hip), groups of 16 or 32 rows: eight waves, 16 cells and half of the depth each; a lane
-//    finishes two cells of a row.  A workgroup stores its piece of the state in operand order, waits for the acknowledgement
-//    and raises its flag, a word in a line of its own; one wave polls the flags of all members, then every wave fetches an
-//    eighth of the tile, global -> LDS without a register in between.
-//    Groups of 32 rows are two tiles of 16 by turns, the exchange of one under the product and the cell of the other.
+//    finishes two cells of a row.  Groups of 16 rows hand the state on in marked words: one wave stores the workgroup's piece in
+//    operand order, every wave fetches an eighth of the tile, global -> LDS, until no word of it is marked as not written.  (Until
+//    then a flag raised behind the acknowledgement of the stores, a poll of all flags and the fetch behind it followed each other;
+//    100 steps, us: 512 cells, 256 rows 275 -> 213; 333 cells, 333 rows 367 -> 306; 1024 cells, 128 rows 302 -> 256; 2048 cells, 128 rows 420 ->
+//    374.  A pause of 4 ahead of the first fetch: 0 and 8 are 1 to 4 % slower.)
+//    In groups of 32 rows a workgroup waits for the acknowledgement and raises its flag, a word in a line of its own; one wave
+//    polls the flags of all members, then every wave fetches.
+//    Groups of 32 rows are two tiles of 16 by turns, the exchange of one under the product and the cell of the other:
+//    all that is left of it open is a poll, and marked words cost more than that, asked for before, within or behind the product
+//    (1024 cells, 512 rows 528 -> 554 to 590; two layers of 2048 cells, 256 rows, 64 steps 930 -> 1036 to 1130).
 //    (A flag per wave, polled by the waves that need it, saves both barriers but four times the polling delays the very
 //    stores it waits for: 0.3 to 1.3 us per step slower.  Flags packed into lines: another 1 to 3 us.)
 //
 // What bounds them: the chain of a step, instruction issue of the cell and the exchange (1 us among 2 to 32 workgroups), not
 // the product: 0.65 us of 3.7 at 2048 cells and 64 rows.  Time per step (us), one launch per step, which re-reads the weights
 // from L2 (before; up to 1024 cells 3.6 in one launch) -> these kernels:
-//    512 cells, 16 rows   3.6 -> 1.3     1024 cells, 128 rows  3.7 -> 2.8     2048 cells, 16 rows   8.4 -> 2.4
-//    512 cells, 256 rows  3.7 -> 2.6     1024 cells, 512 rows  10.5 -> 4.3    2048 cells, 256 rows  13.4 -> 5.4
+//    512 cells, 16 rows   3.6 -> 1.3     1024 cells, 128 rows  3.7 -> 2.5     2048 cells, 16 rows   8.4 -> 2.4
+//    512 cells, 256 rows  3.7 -> 2.1     1024 cells, 512 rows  10.5 -> 4.3    2048 cells, 256 rows  13.4 -> 5.4
 //
 // Placement and the waits that end are those of the LSTM's recurrent kernels (rec_kernel.inc.h).
 #include "gru_kernel.inc.h"
@@ -304,7 +310,7 @@ size_t gru_lds_bytes(int ks, int rows, const LutWide (&lut)[2]) {
 }  // namespace
 
 // The fewest rows whose groups fit one launch: the fewer rows a group has, the shorter its step (1024 cells: 2.2 us with 4
-// rows, 2.8 with 16, 4.3 with 32).  32 is the most that keeps the tile of 2048 cells, the terms of two steps and the tables
+// rows, 2.5 with 16, 4.3 with 32).  32 is the most that keeps the tile of 2048 cells, the terms of two steps and the tables
 // in LDS.
 int gru_seq_rows(int N, int B, int *max_groups) {
   if (N < 1 || N > 2048 || B < 1) return 0;

@@ -66,3 +66,35 @@ def test_waits_give_up_and_the_model_recovers(gru, B):  # noqa: F811
     m.set_option("spin_limit", 1 << 21)
     m.set_option("reset_status", 1)
     assert torch.equal(m.forward(xd), want) and m.device_status() == 0
+
+
+@pytest.mark.parametrize("T", [1, 2, 4, 6, 13])
+@pytest.mark.parametrize("N,B", [(130, 520), (600, 110), (130, 2060), (600, 400)])  # 16 rows, 32 rows
+def test_slots_of_the_exchange_in_turn(gru, N, B, T):  # noqa: F811
+    layers, x = wl.make_gru([20, N], N, B, T, seed=N + T, weight_param=0.9 / N ** 0.5, input_param=1.5)
+    rows = sorted({0, 15, 16, 31, 32, B // 2, B - 3, B - 1})
+    run_both_paths(gru, layers, x, f"slots{N}b{B}t{T}", rows=rows)
+
+
+@pytest.mark.parametrize("B", [300, 1030])  # groups of 16 and of 32 rows
+@pytest.mark.parametrize("T", [1, 3, 9])
+def test_states_that_look_like_marks(gru, B, T):  # noqa: F811
+    """Cells at both ends of the range by turns, every eighth of them to either side of -127."""
+    import numpy as np
+    import torch
+    from test_gpu_gru import both, equal, quantize_x
+
+    N = 200
+    layers, x = wl.make_gru([20], N, B, T, seed=3, weight_param=0.01)
+    n = np.arange(N)
+    layers[0].bx[1][:] = -6.0  # the state is the candidate
+    layers[0].bx[2][:] = np.where(n % 8 == 0, -2.2 - 2.2 * n / N, np.where(n % 2, 6.0, -6.0))
+    m, old = both(gru, layers)
+    xq = quantize_x(x, old.get_quant(0))
+    rows = sorted({0, 15, 16, 31, 32, B - 1})
+    y = m.forward(torch.from_numpy(xq).cuda())
+    assert m.device_status() == 0
+    want, trace = old.forward(np.ascontiguousarray(xq[:, rows]), trace_layer=0)
+    words = np.ascontiguousarray(trace["h8"]).view(np.uint32)[:, :, ::2]
+    assert (words == 0x7F807F80).any() and (words == 0x7F807F81).any()
+    equal("y", y.cpu().numpy()[:, rows], want)
