@@ -271,6 +271,7 @@ bool rec_extents_ok(const RecArgs &ra, const Workspace &ws, int T_all, int t0, b
   if ((size_t)T_all * ra.B * ra.Hpad > ws.out_bytes) return false;
   // m exchange buffer [T][Bp][npadp] in tiles
   if (has_proj && (size_t)ra.T * Bp * ra.npadp > ws.m2_bytes) return false;  // (marked words: plan_rec has seen to their place)
+  if ((ra.flags & kMarkedState) && 6 * (size_t)marked_slot_bytes(ra.Bp, ra.GS) > ws.c - ws.th) return false;
   // counters [groups][64] words and statistics accumulators [groups][4][256] 64-bit words
   if (solo) return true;
   const size_t group_bytes = kStatGroupBytes + (ra.flags & kTaggedState ? (size_t)tagged_group_words(ra.H, ra.rows_pg) * 8 : 0);
@@ -855,6 +856,7 @@ struct RecPlan {
   bool row_own = false;  // with row: W x in the launch itself, where its input allows it
   bool marked = false;   // rec_kernel, rec16_kernel with m in marked words, at mark_at bytes of the synchronization scratch (0: in the m exchange buffer)
   int64_t mark_at = 0;
+  bool marked_state = false;  // rec_kernel with h in marked words, in the launch-per-step path's scratch
   bool rest32 = false;  // groups of 64 rows: a rest of the batch that fits one launch of groups of 32 runs as those
 };
 
@@ -1035,6 +1037,11 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1, bo
       ra.flags |= kTaggedState;
       p.marked = proj;
       if (m_here) p.mark_at = words_end;
+    }
+    // the six slots lie where the launch-per-step path has R h and m of a step: 9 bytes and more per row and cell
+    if (rec_marked(ra) && 6 * marked_slot_bytes(ra.Bp, d.GS) <= (int64_t)9 * B * d.GS * 64) {
+      ra.flags |= kMarkedState;
+      p.marked_state = true;
     }
   }
   p.groups = p2_groups;
@@ -1477,13 +1484,14 @@ int lstm_int_forward(const lstm_int_model *cm, const int8_t *x, int32_t T, int32
     if (use_p2) {
       ra.tx2 = reinterpret_cast<const int4 *>(tx);
       ra.h0 = h0; ra.out = out;
-      ra.mbuf = reinterpret_cast<int8_t *>(plan.mark_at ? wsb + ws.sync + plan.mark_at : wsb + ws.m2);
+      ra.mbuf = reinterpret_cast<int8_t *>(plan.marked_state ? wsb + ws.th : plan.mark_at ? wsb + ws.sync + plan.mark_at : wsb + ws.m2);
       ra.c_in = c_state ? c_state + c_off : nullptr;
       ra.c_out = c_state ? c_state + c_off : nullptr;
       if (!plan.solo) set_sync(ra, m, wsb + ws.sync);
     }
     if (use_p2) {
       const int launch_rows = p2_groups * ra.rows_pg;
+      const int64_t mark_slot = plan.marked_state ? marked_slot_bytes(ra.Bp, d.GS) : plan.marked ? (int64_t)ra.Bp * ra.npadp : 0;
       // the kernels write y in words of four cells; rows that are no multiple of four are copied afterwards
       const bool y_after = last && !rev && !proj && (h.N & 3);
       InGemmArgs ga = plan_in_gemm(m, l, T, B);
@@ -1503,7 +1511,7 @@ int lstm_int_forward(const lstm_int_model *cm, const int8_t *x, int32_t T, int32
         // final h on its way to the state buffer: done by the input GEMM's workgroups ahead of their own
         // work, or by a kernel of their own where the general input GEMM runs
         const int g0 = std::min(p2_groups, (B + ra.rows_pg - 1) / ra.rows_pg);
-        const int64_t clear = sync_bytes(plan, g0), mark = plan.marked ? (int64_t)std::min(T, kMarkSlots - 1) * ra.Bp * ra.npadp : 0;
+        const int64_t clear = sync_bytes(plan, g0), mark = std::min(T, kMarkSlots - 1) * mark_slot;
         const bool ws_gemm = in_gemm_ws_supported(ga);
         if (ws_gemm) {
           ga.has_init = 1;
@@ -1555,8 +1563,7 @@ int lstm_int_forward(const lstm_int_model *cm, const int8_t *x, int32_t T, int32
           if (!plan.solo && (b0 > 0 || t0 > 0)) {
             Timed t(m->prof, s, LSTM_INT_K_OTHER);
             launch_fill_i16(s, reinterpret_cast<int16_t *>(wsb + ws.sync), sync_bytes(plan, ra.groups) / 2, 0);
-            if (plan.marked && b0 == 0)
-              launch_fill_i16(s, reinterpret_cast<int16_t *>(ra.mbuf), (int64_t)(kMarkSlots - 1) * ra.Bp * ra.npadp / 2, (int16_t)kMarkFree);
+            if (mark_slot && b0 == 0) launch_fill_i16(s, reinterpret_cast<int16_t *>(ra.mbuf), (kMarkSlots - 1) * mark_slot / 2, (int16_t)kMarkFree);
           }
           if (!rec_extents_ok(ra, ws, T, t0, proj)) return LSTM_INT_E_WORKSPACE;
           if (!plan.solo) plant_misplaced(m, s, wsb + ws.sync);

@@ -142,12 +142,16 @@ constexpr int kFourPredSlots = 256;
 // rec16_kernel, rec_kernel: the hidden state travels as (value, tag) byte pairs, behind the statistics words of the group: two
 // slots of the group's rows (16, 32) of H cells rounded up to 8
 constexpr int kTaggedState = 512;
+// rec_kernel at the longest k without a projection: the hidden state travels in marked words through mbuf, [4 slots by turns, 2 escape
+// slots][Bp / 32][k steps = 2 GS][32 rows][32 cells], as many of the four as there are steps filled with kMarkFree
+constexpr int kMarkedState = 1024;
+inline int64_t marked_slot_bytes(int Bp, int GS) { return (int64_t)Bp * GS * 64; }
 __host__ __device__ inline int tagged_row(int H) { return (H + 7) & ~7; }
 __host__ __device__ inline int tagged_group_words(int H, int rows) { return tagged_row(H) * rows / 2; }  // 64-bit words of a group, both slots
 
 struct RecArgs {
   int T, B, N, H, Hpad;
-  int flags;      // the layer's; rec_kernel: | kFourPredSlots; rec_kernel, rec16_kernel: | kTaggedState
+  int flags;      // the layer's; rec_kernel: | kFourPredSlots, | kMarkedState; rec_kernel, rec16_kernel: | kTaggedState
   int m_c;
   int GS;         // workgroups (compute units) per group = cells / 64
   int groups;     // groups in this launch, each owns rows_pg batch rows
@@ -236,6 +240,8 @@ bool rec_supported(int N, int H, int flags, int B, int *ks, int *rt, int *groups
 size_t rec_lds_bytes(const RecArgs &a);
 // whether rec_kernel can hand the hidden state on in tagged words (kTaggedState), room for them aside
 bool rec_tagged(const RecArgs &a);
+// ... or in marked words (kMarkedState)
+bool rec_marked(const RecArgs &a);
 // Returns hipSuccess or the launch error.
 hipError_t launch_rec(hipStream_t s, const RecArgs &a, bool cooperative);
 // One-time per process: raises the kernels' dynamic LDS limits.

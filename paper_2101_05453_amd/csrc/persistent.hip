@@ -218,6 +218,8 @@ bool rec_tagged(const RecArgs &a) {
   return a.rows_pg == 32 && !a.sparse && a.ks <= 20 && a.GS > 1 && outputs_ok;
 }
 
+bool rec_marked(const RecArgs &a) { return a.rows_pg == 32 && !a.sparse && a.ks == 32 && !(a.flags & 8); }
+
 size_t rec_lds_bytes(const RecArgs &a) {
   const int items = (a.rows_pg / 32) * 128;
   const bool proj = a.flags & 8;
@@ -236,9 +238,9 @@ size_t rec_lds_bytes(const RecArgs &a) {
 }
 
 typedef void (*rec_fn)(RecArgs);
-rec_fn rec_pick_8(int rt, int fl, bool tag);   // rec_inst_8.hip
-rec_fn rec_pick_20(int rt, int fl, bool tag);  // rec_inst_20.hip
-rec_fn rec_pick_32(int rt, int fl, bool tag);  // rec_inst_32.hip
+rec_fn rec_pick_8(int rt, int fl, int tag);   // rec_inst_8.hip
+rec_fn rec_pick_20(int rt, int fl, int tag);  // rec_inst_20.hip
+rec_fn rec_pick_32(int rt, int fl, int tag);  // rec_inst_32.hip
 rec_fn rec_pick_sparse_8(int fl);   // rec_sparse_inst_8.hip
 rec_fn rec_pick_sparse_20(int fl);  // rec_sparse_inst_20.hip
 rec_fn rec_pick_sparse_32(int fl);  // rec_sparse_inst_32.hip
@@ -248,7 +250,7 @@ static rec_fn pick_sparse(int ks, int fl) {
   if (ks == 32) return rec_pick_sparse_32(fl);
   return nullptr;
 }
-static rec_fn pick(int ks, int rt, int fl, bool tag) {
+static rec_fn pick(int ks, int rt, int fl, int tag) {
   if (ks == 8) return rec_pick_8(rt, fl, tag);
   if (ks == 20) return rec_pick_20(rt, fl, tag);
   if (ks == 32) return rec_pick_32(rt, fl, tag);
@@ -257,9 +259,9 @@ static rec_fn pick(int ks, int rt, int fl, bool tag) {
 
 hipError_t rec_init() {
   for (int ks : kKS)
-    for (int form = 0; form < 3; ++form)  // one row tile, two, one with the state in tagged words
+    for (int form = 0; form < 4; ++form)  // one row tile, two, one with the state in tagged words, one in marked words
       for (int fl = 0; fl < 16; ++fl) {
-        rec_fn fn = pick(ks, form == 1 ? 2 : 1, fl, form == 2);
+        rec_fn fn = pick(ks, form == 1 ? 2 : 1, fl, form > 1 ? form - 1 : 0);
         if (!fn) continue;
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
@@ -277,7 +279,7 @@ hipError_t rec_init() {
 hipError_t launch_rec(hipStream_t s, const RecArgs &a, bool cooperative) {
   const int fl = (a.flags & 7) | ((a.flags & 8) ? 0 : 8);  // bit 3: no projection
   if (a.sparse && a.rows_pg != 32) return hipErrorInvalidValue;
-  rec_fn fn = a.sparse ? pick_sparse(a.ks, fl) : pick(a.ks, a.rows_pg / 32, fl, a.flags & kTaggedState);
+  rec_fn fn = a.sparse ? pick_sparse(a.ks, fl) : pick(a.ks, a.rows_pg / 32, fl, a.flags & kMarkedState ? 2 : (a.flags & kTaggedState) != 0);
   if (!fn) return hipErrorInvalidValue;
   const int slots = a.GS * ((a.groups + 7) / 8);
   RecArgs args = a;

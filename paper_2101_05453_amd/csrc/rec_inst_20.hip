@@ -2,5 +2,5 @@
 #include "rec_kernel.inc.h"
 
 namespace lstm_int {
-rec_fn rec_pick_20(int rt, int fl, bool tag) { return rec_pick_ks<20>(rt, fl, tag); }
+rec_fn rec_pick_20(int rt, int fl, int tag) { return rec_pick_ks<20>(rt, fl, tag); }
 }  // namespace lstm_int

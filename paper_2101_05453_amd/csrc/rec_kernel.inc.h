@@ -188,10 +188,11 @@ __device__ __forceinline__ int32_t mirror_tanh_masked(int32_t x, int32_t t) {
 // FL: bit 0 CIFG, bit 1 peephole, bit 2 layer norm, bit 3 "no projection" (compile
 // time, so that the code carries no tests of them); with bit 3 clear the
 // projection is a runtime flag.  SP: the recurrent weights are in the 2:4
-// compressed form (persistent.h) and R h runs on the sparse MFMA.  TAG: the
-// hidden state travels in tagged words (kTaggedState) instead of through the
-// group's counter: a form of its own, as in rec16_kernel.
-template <int KS, int RT, int FL, bool SP = false, bool TAG = false>
+// compressed form (persistent.h) and R h runs on the sparse MFMA.  TAG: how the
+// hidden state travels, 0 through the group's counter, 1 in tagged words
+// (kTaggedState), 2 in marked words (kMarkedState, no projection): forms of
+// their own, as in rec16_kernel.
+template <int KS, int RT, int FL, bool SP = false, int TAG = 0>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void rec_kernel(RecArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   const long long t_start = (long long)wall_clock64();
@@ -251,7 +252,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
   // ---- LDS carve-up (rec_lds_bytes mirrors it): what has a fixed size first, at offsets known to the compiler
   constexpr int LS = KS * 32 + 16;  // h tile row stride
-  static_assert(!TAG || (RT == 1 && !SP && KS <= 20));  // rec_tagged is the host's side of this
+  constexpr bool MARK = TAG == 2;
+  static_assert(TAG != 1 || (RT == 1 && !SP && KS <= 20));  // rec_tagged is the host's side of this
+  static_assert(!MARK || (RT == 1 && (FL & 8) && !SP && KS == 32));  // rec_marked
   uint8_t *p = lds;
   u64 *red = reinterpret_cast<u64 *>(p);                 p += (size_t)items * 8;
   LnRow2 *lnrow = reinterpret_cast<LnRow2 *>(p);         p += (size_t)items * sizeof(LnRow2);
@@ -440,7 +443,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // 320 cells, 1400 rows 345 -> 314.  (Both ways in one kernel, with the counter's pauses for the workgroups without outputs: 539, 641,
   // 756, 574, 594, 458 and 319, and 2 to 5 % on the calls through the counter.)
   const int Hr = FL & 8 ? tagged_row(a.H) : a.H;  // outputs of a projection are whole pieces
-  u64 *accS = a.acc + (size_t)group * (kStatGroupWords + (TAG ? tagged_group_words(a.H, 32) : 0));  // [set][round][S1|S2][item]
+  u64 *accS = a.acc + (size_t)group * (kStatGroupWords + (TAG == 1 ? tagged_group_words(a.H, 32) : 0));  // [set][round][S1|S2][item]
   u64 *const xh = accS + kStatGroupWords;  // [2 slots][32 rows][Hr] (value, tag)
   uint32_t prev1[2] = {0, 0};  // this thread's item, per round: the sums of the statistics words as last read
   u64 prev2[2] = {0, 0};
@@ -499,7 +502,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // as in rec16_kernel
   const unsigned never = a.extra_arrivals ? 0x80u : 0;  // tests: a tag nobody stores in so few steps
   const int row_pieces = Hr >> 3;
-  const uint32_t per_piece = TAG ? 0xFFFFFFFFu / (uint32_t)row_pieces + 1 : 0;  // c / row_pieces = high word of c per_piece, c < 2^12, two pieces or more
+  const uint32_t per_piece = TAG == 1 ? 0xFFFFFFFFu / (uint32_t)row_pieces + 1 : 0;  // c / row_pieces = high word of c per_piece, c < 2^12, two pieces or more
   auto poll_state = [&](auto count, int t, int tid) {
     constexpr int U = decltype(count)::value;
     const uint32_t want = (((unsigned)t + 1) & 0xFF ^ never) * 0x01000100u;
@@ -568,11 +571,78 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     int8_t *slot = a.mbuf + (size_t)(t & 3) * a.Bp * a.npadp + ((size_t)(row0 >> 5) * (a.npadp >> 5) + member * 2 + (wave >> 2)) * 1024;
     return slot + (unsigned)((lane & 31) * 32 + (wave & 3) * 8);
   };
+  // The hidden state in marked words (MARK), half of the bytes of pairs, so that the longest k goes without the counter too.  The h
+  // tile is in the order of the exchange, [k step][32 rows][32 cells], and a wave's eighth of it goes global -> LDS until no word is
+  // marked as not written.  Two escape slots: who stores step t + 2 has seen step t + 1 of all others, who had read step t before
+  // they made that.  1024 cells, 400 rows, 60 steps, layer norm, counter -> this 485 -> 439 us, without it 331 -> 329; 500 rows,
+  // peephole and layer norm 549 -> 535; 700 cells, 300 rows, layer norm 437 -> 391.  Two row tiles, twice the bytes, keep the counter: 1024 cells, 1024 rows, layer norm
+  // 843 -> 981, coupled gates too 728 -> 857 -- a look takes more than 1 us then, workgroups that need a second one come late to the
+  // statistics, and neither a first pause nor looking at a word per writer first made up for that.
+  const size_t hslot = MARK ? (size_t)a.Bp * GS * 64 : 0;
+  constexpr int HCH = KS / WAVES;  // pieces of 1 KB for a wave
+  auto h_word = [&](int slot, int lane) -> int8_t * {  // as m_word
+    return a.mbuf + slot * hslot + (size_t)((row0 >> 5) * 2 * GS + member * 2 + (wave >> 2)) * 1024 + (unsigned)((lane & 31) * 32 + (wave & 3) * 8);
+  };
+  auto fetch_state = [&](int t, int lane) {
+    int8_t *const tile = hT + lane * 16;
+    auto has = [&](int j) { return wave + WAVES * j < 2 * GS; };
+    auto from = [&](int j) { return (unsigned)(((row0 >> 5) * 2 * GS + wave + WAVES * j) * 1024 + lane * 16); };
+    const int8_t *src = a.mbuf + (t & 3) * hslot;
+    asm volatile("" : "+s"(src));
+    int budget = a.spin_limit;
+    uint32_t least;
+    for (int i = 0; i < a.sync_sleep; ++i) __builtin_amdgcn_s_sleep(1);
+    for (;;) {
+#pragma unroll
+      for (int j = 0; j < HCH; ++j)
+        if (has(j))
+          __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + from(j)),
+                                           (__attribute__((address_space(3))) void *)(hT + (wave + WAVES * j) * 1024), 16, 0, 16 /* sc1 */);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      least = 0xFFFFFFFFu;
+#pragma unroll
+      for (int j = 0; j < HCH; ++j)
+        if (has(j)) {
+          const v4i w = *reinterpret_cast<const v4i *>(tile + (wave + WAVES * j) * 1024);
+          const uint32_t d0 = (uint32_t)w[0] ^ kMarkFree, d1 = (uint32_t)w[2] ^ kMarkFree, d = d0 < d1 ? d0 : d1;
+          least = least < d ? least : d;
+        }
+      if (a.extra_arrivals) least = 0;  // tests: words that nobody writes
+      if (__builtin_amdgcn_ballot_w64(least == 0) == 0) break;
+      --budget;
+      if ((budget & 15) == 0 && (budget <= 0 || __hip_atomic_load(a.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
+        __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        flag[0] = 0;
+        return;
+      }
+    }
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(least == 1) != 0, 0)) {
+      const int8_t *esc = a.mbuf + (4 + (t & 1)) * hslot;
+      for (int j = 0; j < HCH; ++j)
+        if (has(j))
+          for (int i = 0; i < 4; i += 2) {
+            int *const w = reinterpret_cast<int *>(tile + (wave + WAVES * j) * 1024) + i;
+            if ((uint32_t)*w == kMarkEscape)
+              *w = __hip_atomic_load(reinterpret_cast<const int *>(esc + from(j) + 4 * i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          }
+    }
+  };
   const int tid0 = tid;
   const bool tails = a.lut[0].tail | a.lut[1].tail | a.lut[2].tail;  // some table's LDS copy ends before its flat part
   // this lane's operand row of W_proj; rows beyond a tile's prow outputs re-read row 0: their results are never stored
   const int wp_lane = (col < a.prow ? col : 0) * WLS + (b2 << 4);
-  if (TAG) {  // h before the first step
+  if (MARK) {  // h before the first step, in the order of the exchange
+#pragma unroll
+    for (int j = 0; j < HCH; ++j) {
+      const int c = wave + WAVES * j, k = c * 32 + (lane & 1) * 16;
+      int row = row0 + (lane >> 1);
+      row = row < a.B ? row : a.B - 1;
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(a.h0 + (k < a.Hpad ? (unsigned)(row * a.Hpad + k) : 0u)),
+                                       (__attribute__((address_space(3))) void *)(hT + c * 1024), 16, 0, 0);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  }
+  if (TAG == 1) {  // h before the first step
 #pragma unroll
     for (int j = 0; j < NCH; ++j)
       if (WAVES * (j + 1) <= TILE_KB || wave + WAVES * j < TILE_KB)
@@ -587,7 +657,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63, col = lane & 31, b2 = lane >> 5, cell_w = wave * 8 + 4 * b2;
     // ---- h^{t-1} rows of the group -> LDS
-    if (TAG) {
+    if (MARK) {
+      if (t > 0) fetch_state(t - 1, lane);
+    } else if (TAG) {
       const int mine = t > 0 ? (4 * Hr - wave * 64 + 511) >> 9 : 0;  // pieces of eight cells for a thread of this wave, 32 rows of Hr / 8
       if (mine >= 5)
         poll_state(std::integral_constant<int, 5>{}, t - 1, tid);
@@ -616,6 +688,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (TAG && t > 0) {
       if (flag[0] == 0) return;
       store_output(t - 1, lane);
+      // everyone's h of step t - 1 is here, so everyone has read h of the step before: this lane's words of that are marked as not
+      // written, for step t + 2
+      if (MARK && t > 1 && t + 3 < a.T && b2 == 0)
+        *reinterpret_cast<uint32_t *>(h_word((t - 2) & 3, lane)) = kMarkFree;
       // everyone's h of step t - 1 is here, so everyone has read m of that step: this lane's word of it is marked as not written, for
       // step t + 3
       if (proj && t + 3 < a.T && b2 == 0) *reinterpret_cast<uint32_t *>(m_word(t - 1, lane)) = kMarkFree;
@@ -655,12 +731,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     } else {
       constexpr int DEPTH = RT == 1 ? 4 : 2;  // h fragments in flight ahead of the MFMAs
       v4i hf[RT][DEPTH];
-      const int8_t *hbase = hT + (size_t)col * LS + (b2 << 4);
+      constexpr int HROW = MARK ? 32 : LS, HSTEP = MARK ? 1024 : 32, HTILE = MARK ? KS * 1024 : 32 * LS;
+      const int8_t *hbase = hT + (size_t)col * HROW + (b2 << 4);
 #pragma unroll
       for (int ks = 0; ks < DEPTH && ks < KS; ++ks)
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
-          hf[rt][ks] = *reinterpret_cast<const v4i *>(hbase + (size_t)rt * 32 * LS + ks * 32);
+          hf[rt][ks] = *reinterpret_cast<const v4i *>(hbase + (size_t)rt * HTILE + ks * HSTEP);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
@@ -668,7 +745,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         for (int rt = 0; rt < RT; ++rt) {
           acc[rt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(Wf[ks], hf[rt][ks % DEPTH], acc[rt], 0, 0, 0);  // acc starts from the folded bias
           if (ks + DEPTH < KS)
-            hf[rt][ks % DEPTH] = *reinterpret_cast<const v4i *>(hbase + (size_t)rt * 32 * LS + (ks + DEPTH) * 32);
+            hf[rt][ks % DEPTH] = *reinterpret_cast<const v4i *>(hbase + (size_t)rt * HTILE + (ks + DEPTH) * HSTEP);
         }
         // keep the LDS reads DEPTH iterations ahead of their MFMAs: without
         // this the instruction scheduler sinks each read next to its use
@@ -1054,7 +1131,19 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         const int32_t mq = sat8(rescale_sat16_pre<0>(om, pm) + zp_m);
         pk |= (uint32_t)(mq & 0xFF) << (8 * c);
       }
-      if (TAG && (FL & 8)) {  // rows beyond the batch and cells up to whole pieces too
+      if (MARK) {  // rows beyond the batch and cells beyond the layer's too
+        hkeep = pk;
+        const auto both = __builtin_amdgcn_permlane32_swap(pk, pk, false, false);
+        uint32_t lo = both[0];
+        if (b2 == 0 && t + 1 < a.T) {  // nobody else reads the last one
+          if (__builtin_expect((lo ^ kMarkFree) < 2, 0)) {
+            *reinterpret_cast<uint32_t *>(h_word(4 + (t & 1), lane)) = lo;
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            lo = kMarkEscape;
+          }
+          *reinterpret_cast<v2i *>(h_word(t & 3, lane)) = v2i{(int)lo, (int)both[1]};
+        }
+      } else if (TAG && (FL & 8)) {  // rows beyond the batch and cells up to whole pieces too
         hkeep = pk;
         const uint32_t tag = ((unsigned)t + 1) & 0xFF;
         if (n0 < Hr)
@@ -1283,13 +1372,22 @@ rec_fn rec_pick_sparse_ks(int fl) {
   return nullptr;
 }
 
-// kernel for (rt, flags & 7) at k depth KS
+// kernel for (rt, flags & 7) at k depth KS; tag as in rec_kernel
 template <int KS>
-rec_fn rec_pick_ks(int rt, int fl, bool tag) {
+rec_fn rec_pick_ks(int rt, int fl, int tag) {
 #define LSTM_REC_CASE(R, F) \
   if (rt == R && fl == F) return rec_kernel<KS, R, F>;
 #define LSTM_REC_TAG(F) \
-  if (rt == 1 && fl == F) return rec_kernel<KS, 1, F, false, true>;
+  if (rt == 1 && fl == F) return rec_kernel<KS, 1, F, false, 1>;
+#define LSTM_REC_MARK(F) \
+  if (rt == 1 && fl == F) return rec_kernel<KS, 1, F, false, 2>;
+  if (tag == 2) {
+    if constexpr (KS == 32) {
+      LSTM_REC_MARK(8) LSTM_REC_MARK(9) LSTM_REC_MARK(10) LSTM_REC_MARK(11)
+      LSTM_REC_MARK(12) LSTM_REC_MARK(13) LSTM_REC_MARK(14) LSTM_REC_MARK(15)
+    }
+    return nullptr;
+  }
   if constexpr (KS <= 20) {
     if (tag) {
       LSTM_REC_TAG(0) LSTM_REC_TAG(1) LSTM_REC_TAG(2) LSTM_REC_TAG(3)
@@ -1309,6 +1407,7 @@ rec_fn rec_pick_ks(int rt, int fl, bool tag) {
   }
   LSTM_REC_CASE(2, 8) LSTM_REC_CASE(2, 9) LSTM_REC_CASE(2, 10) LSTM_REC_CASE(2, 11)
   LSTM_REC_CASE(2, 12) LSTM_REC_CASE(2, 13) LSTM_REC_CASE(2, 14) LSTM_REC_CASE(2, 15)
+#undef LSTM_REC_MARK
 #undef LSTM_REC_TAG
 #undef LSTM_REC_CASE
   return nullptr;

@@ -100,3 +100,49 @@ def test_marks_between_layers_of_a_one_step_stack(orc, B, flags, most):
     want, trace = orc.forward(old, xq.cpu().numpy(), trace_layer=0)
     assert (_words(trace["m"]) == 0x7F807F80).any()
     assert_equal("y", y.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("T", [1, 2, 3, 5, 6, 13])
+@pytest.mark.parametrize("N,B,flags", [
+    (650, 42, LN), (650, 43, LN),  # no room for the slots, and just enough
+    (1024, 97, CIFG), (700, 70, PH | LN), (704, 65, 0), (1024, 500, CIFG | LN), (900, 511, PH | CIFG), (650, 301, PH),
+])
+def test_slots_of_the_state_in_turn(orc, N, B, flags, T):
+    """The 32-row kernel at the longest k without a projection."""
+    layers, x = wl.make_custom([24], N, N, flags, B, T, seed=N + T, weight_param=0.9 / N ** 0.5)
+    rows = sorted({0, 31, 32, B // 2, B - 2, B - 1})
+    run_and_compare(orc, layers, x, f"h{N}b{B}t{T}", trace=False, rows=rows, options={"rows16": 0})
+
+
+@pytest.mark.parametrize("flags", [0, LN])
+@pytest.mark.parametrize("N,B", [(700, 70), (1024, 300)])
+@pytest.mark.parametrize("T", [3, 9])
+def test_states_that_look_like_marks(orc, N, B, flags, T):
+    layers, xd = _ends_of_the_range([24], N, N, flags, B, T, 0.9)
+    model, old = binding.prepare(layers), orc.prepare(layers)
+    model.set_option("rows16", 0)
+    xq = model.quantize_input(xd)
+    y = model.forward(xq)
+    assert model.device_status() == 0
+    rows = [0, 31, 32, 63, B // 2, B - 1]
+    want, trace = orc.forward(old, np.ascontiguousarray(xq.cpu().numpy()[:, rows]), trace_layer=0)
+    assert (_words(trace["m"])[:-1] == 0x7F807F80).any() and (_words(trace["m"])[:-1] == 0x7F807F81).any()
+    assert_equal("y", y.cpu().numpy()[:, rows], want)
+
+
+def test_waits_for_marked_state_give_up():
+    N, B = 700, 70
+    layers, x = wl.make_custom([24], N, N, LN, B, 5, seed=1, weight_param=0.03)
+    calibrate_on_gpu(layers, x)
+    m = binding.prepare(layers)
+    m.set_option("rows16", 0)
+    xq = m.quantize_input(torch.from_numpy(x).cuda())
+    want = m.forward(xq)
+    m.set_option("spin_limit", 64)
+    m.set_option("barrier_never_completes", 1)
+    m.forward(xq)
+    assert m.device_status() == 1
+    m.set_option("barrier_never_completes", 0)
+    m.set_option("spin_limit", 1 << 21)
+    m.set_option("reset_status", 1)
+    assert torch.equal(m.forward(xq), want) and m.device_status() == 0
