@@ -255,6 +255,11 @@ Requant make_requant(const int32_t *M, const int32_t *e, int first, int count, i
   return r;
 }
 
+// Bytes of a group's synchronization words with kTaggedState beyond kStatGroupBytes
+int64_t tagged_group_bytes(const RecArgs &ra) {
+  return (int64_t)tagged_group_words(ra.H, ra.rows_pg) * 8 + (ra.flags & kMemberStats ? (int64_t)(kMemberStatWords - kStatGroupWords) * 8 : 0);
+}
+
 // Whether everything a launch of a persistent recurrent kernel indexes with these arguments lies inside
 // the workspace regions it was given (checked on the host before every launch: an access out of bounds
 // on the device can take the whole GPU down).  T_all = steps of the whole call, t0 = first step of this launch.
@@ -274,7 +279,7 @@ bool rec_extents_ok(const RecArgs &ra, const Workspace &ws, int T_all, int t0, b
   if ((ra.flags & kMarkedState) && 6 * (size_t)marked_slot_bytes(ra.Bp, ra.GS) > ws.c - ws.th) return false;
   // counters [groups][64] words and statistics accumulators [groups][4][256] 64-bit words
   if (solo) return true;
-  const size_t group_bytes = kStatGroupBytes + (ra.flags & kTaggedState ? (size_t)tagged_group_words(ra.H, ra.rows_pg) * 8 : 0);
+  const size_t group_bytes = kStatGroupBytes + (ra.flags & kTaggedState ? (size_t)tagged_group_bytes(ra) : 0);
   if ((size_t)ra.groups * 64 * 4 > (size_t)256 * 64 * 4 || (size_t)ra.groups * group_bytes > (size_t)256 * kStatGroupBytes)
     return false;
   return true;
@@ -982,14 +987,22 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1, bo
     r16.Wp2 = d.Wp2; r16.bp2 = d.bp2; r16.ptiles = d.ptiles; r16.prow = 32;
     // the exchange words share the region of the statistics words with all groups of the launch
     r16.flags &= ~kFourPredSlots;
+    // From 1793 cells on the statistics in words of each member (with the form, 60 steps: 2048 cells 1.04 of the rate, 1500 0.986, 1088 0.98), of
+    // one direction and to 640 outputs (the next depth has no registers for it).
+    if (h.layer_norm() && proj && d.GS > 28 && k16 <= 10 && share == 1) r16.flags |= kMemberStats;
     // (m through marked words then, as below)
-    const int64_t words_end = sync_bytes(g16 * share) + (int64_t)g16 * share * tagged_group_words(h.H, 16) * 8;
+    const int64_t words_end = sync_bytes(g16 * share) + (int64_t)g16 * share * tagged_group_bytes(r16);
     const bool m_here = proj && T < kMarkSlots;
     const bool tagged = d.GS > 1 && words_end + (m_here ? (int64_t)share * kMarkSlots * ra.Bp * ra.npadp : 0) <= (int64_t)kSyncBytes;
-    if (tagged) r16.flags |= kTaggedState;
+    if (tagged)
+      r16.flags |= kTaggedState;
+    else
+      r16.flags &= ~kMemberStats;
     if (rec16_lds_bytes(r16) <= 160 * 1024) {
       p.marked = tagged && proj;
       if (p.marked && m_here) p.mark_at = words_end;
+      // (words of each member, the poll in all waves: 2048 cells, 100 steps, a first pause of 0, 1, 4, 8 and 16 645, 645, 647, 657 and 681 us)
+      if (m->stats_first_sleep < 0 && (r16.flags & kMemberStats)) r16.stats_first_sleep = 1;
       ra = r16;
       p2_groups = g16;
       p.use16 = true;
@@ -1343,7 +1356,7 @@ int64_t sync_bytes(int groups) { return (int64_t)256 * 64 * 4 + (int64_t)groups 
 int64_t sync_bytes(const RecPlan &p, int groups) {
   return p.solo ? 0
          : p.quad ? (int64_t)256 * 64 * 4 + (int64_t)groups * p.ra.GS * kQuadWgBytes
-                  : sync_bytes(groups) + (p.ra.flags & kTaggedState ? (int64_t)groups * tagged_group_words(p.ra.H, p.ra.rows_pg) * 8 : 0);
+                  : sync_bytes(groups) + (p.ra.flags & kTaggedState ? (int64_t)groups * tagged_group_bytes(p.ra) : 0);
 }
 
 // The hoisted W x of layer l (its output goes to ga.tx2, in the tile order of the recurrent kernels).

@@ -149,9 +149,14 @@ inline int64_t marked_slot_bytes(int Bp, int GS) { return (int64_t)Bp * GS * 64;
 __host__ __device__ inline int tagged_row(int H) { return (H + 7) & ~7; }
 __host__ __device__ inline int tagged_group_words(int H, int rows) { return tagged_row(H) * rows / 2; }  // 64-bit words of a group, both slots
 
+// rec16_kernel with kTaggedState and a projection: a statistics word of each member, [2 steps][2 rounds][64 items][32 members]
+constexpr int kMemberStats = 2048;
+constexpr int kMemberStatWords = 2 * 2 * 64 * 32;
+
 struct RecArgs {
   int T, B, N, H, Hpad;
-  int flags;      // the layer's; rec_kernel: | kFourPredSlots, | kMarkedState; rec_kernel, rec16_kernel: | kTaggedState
+  int flags;      // the layer's; rec_kernel: | kFourPredSlots, | kMarkedState; rec_kernel, rec16_kernel: | kTaggedState;
+                  // rec16_kernel: | kMemberStats
   int m_c;
   int GS;         // workgroups (compute units) per group = cells / 64
   int groups;     // groups in this launch, each owns rows_pg batch rows

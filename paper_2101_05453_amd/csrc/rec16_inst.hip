@@ -29,8 +29,8 @@ static rec16_pair_fn pick16_pair(int ks16, int fl, int tag) {
   return nullptr;
 }
 
-// the kernel's TAG
-static int rec16_tag(int flags) { return !(flags & kTaggedState) ? 0 : flags & 8 ? 2 : 1; }
+// the kernel's FORM
+static int rec16_form(int flags) { return !(flags & kTaggedState) ? 0 : !(flags & 8) ? 1 : flags & kMemberStats ? 3 : 2; }
 
 bool rec16_supported(int N, int H, int flags, int B, int *ks16, int *groups) {
   if (N > 2048 || B < 1) return false;
@@ -67,11 +67,13 @@ size_t rec16_lds_bytes(const RecArgs &a) {
 
 hipError_t rec16_init() {
   for (int ks : kKS16)
-    for (int i = 0; i < 24; ++i) {
+    for (int i = 0; i < 32; ++i) {
       const int fl = i & 7, tag = i >> 3;
+      if (tag == 3 && !pick16(ks, fl, tag)) continue;
       hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(pick16(ks, fl, tag)),
                                          hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
       if (e != hipSuccess) return e;
+      if (tag == 3) continue;
       e = hipFuncSetAttribute(reinterpret_cast<const void *>(pick16_pair(ks, fl, tag)), hipFuncAttributeMaxDynamicSharedMemorySize,
                               160 * 1024);
       if (e != hipSuccess) return e;
@@ -80,7 +82,7 @@ hipError_t rec16_init() {
 }
 
 hipError_t launch_rec16(hipStream_t s, const RecArgs &a, bool cooperative) {
-  rec_fn fn = pick16(a.ks16, a.flags & 7, rec16_tag(a.flags));
+  rec_fn fn = pick16(a.ks16, a.flags & 7, rec16_form(a.flags));
   if (!fn || !a.R2h) return hipErrorInvalidValue;
   const int slots = a.GS * ((a.groups + 7) / 8);
   RecArgs args = a;
@@ -94,7 +96,7 @@ hipError_t launch_rec16(hipStream_t s, const RecArgs &a, bool cooperative) {
 
 hipError_t launch_rec16_pair(hipStream_t s, const RecArgs2 &a, bool cooperative) {
   const RecArgs &f = a.d[0], &b = a.d[1];
-  rec16_pair_fn fn = pick16_pair(f.ks16, f.flags & 7, rec16_tag(f.flags));
+  rec16_pair_fn fn = pick16_pair(f.ks16, f.flags & 7, rec16_form(f.flags));
   if (!fn || !f.R2h || !b.R2h || f.GS != b.GS || f.ks16 != b.ks16 || f.flags != b.flags || f.groups + b.groups > 8 * (32 / f.GS))
     return hipErrorInvalidValue;
   const int slots = f.GS * ((f.groups + b.groups + 7) / 8);

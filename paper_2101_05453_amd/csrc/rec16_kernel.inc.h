@@ -23,7 +23,7 @@
 // rows 659 -> 598; 512 cells, 256 outputs, layer norm, 200 rows 588 -> 544.  A pause ahead of the first poll of m only adds to the step (4 x
 // 64 clocks: 0.1 us), and so do pauses of the workgroups without outputs between their polls of the state, from 8 x 64 clocks on.
 // The counter remains where one workgroup is the group, and where the words of all groups find no room.  Either way is a form of its
-// own (TAG): with both in one kernel, chosen by a test in the step loop, the registers that each keeps for itself spilled (12 to
+// own (FORM): with both in one kernel, chosen by a test in the step loop, the registers that each keeps for itself spilled (12 to
 // 80 bytes a lane at 2048 cells with layer norm, three times the scalar ones everywhere), and the same calls took 632, 950, 533, 847,
 // 277, 1253, 1158, 1544, 1792 and 1958 us, the ones through the counter up to 25 % longer than alone.
 //
@@ -59,11 +59,14 @@ __device__ __forceinline__ int rec16_rev(const RecArgs &) { return 0; }
 __device__ __forceinline__ int rec16_rev(const RecDirArgs &a) { return a.rev; }
 
 // PAIR: the launch runs two layers of one shape side by side, each possibly backward in time (RecArgs2).
-// TAG: 0 = the state through the counter; 1, 2 = in tagged words, without and with a projection (rec16_tag).
-template <int KS16, int FL, bool PAIR, int TAG>
+// FORM: 0 = the state through the counter; 1, 2 = in tagged words, without and with a projection; 3 = as 2, and the statistics in a word
+// of each member (rec16_form).  A form of its own for that too: as a test in the step loop it cost the others 1 to 5 %.
+template <int KS16, int FL, bool PAIR, int FORM>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void rec16_kernel(
     std::conditional_t<PAIR, RecArgs2, RecArgs> args) {
   constexpr bool cifg = FL & 1, ph = FL & 2, ln = FL & 4;
+  constexpr int TAG = FORM == 3 ? 2 : FORM;
+  constexpr bool member_words = FORM == 3;
   const long long t_start = (long long)wall_clock64();
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   const int tid = threadIdx.x;
@@ -307,8 +310,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // one set of words: two sets (as in rec_kernel) made this kernel 2-3 % slower, at 8 and at 32 workgroups per group
   constexpr bool tagged = TAG != 0;
   const int Hr = tagged_row(a.H);                    // cells of a row of the exchange
-  u64 *accS = a.acc + (size_t)gl * (kStatGroupWords + (tagged ? tagged_group_words(a.H, 16) : 0));  // [round][S1|S2][item], item < 64
-  u64 *const xh = accS + kStatGroupWords;            // [2 slots][16 rows][Hr] (value, tag)
+  // statistics: [round][S1|S2][item], item < 64, or [step % 2][round][item][member]
+  constexpr int stat_words = member_words ? kMemberStatWords : kStatGroupWords;
+  u64 *accS = a.acc + (size_t)gl * (stat_words + (tagged ? tagged_group_words(a.H, 16) : 0));
+  u64 *const xh = accS + stat_words;                 // [2 slots][16 rows][Hr] (value, tag)
   const unsigned never = a.extra_arrivals ? 0x80u : 0;  // tests: a tag nobody stores in so few steps
   int64_t prevS[2][2] = {{0, 0}, {0, 0}};       // this thread's item, per round: S1, S2
   const double inv_n = 1.0 / (double)a.N;
@@ -524,8 +529,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       gate_sums(std::integral_constant<int, 1>{});
     else
       gate_sums(std::integral_constant<int, 2>{});
-    // statistics over the group's workgroups: as in rec_kernel (words that are never reset, the top
-    // byte counts the adds); item = 16 gate + row
+    // Statistics over the group's workgroups; item = 16 gate + row: as in rec_kernel (words that are never reset, the top byte counts
+    // the adds), or (FORM 3) a word of each member per item, its sum of squares, its sum and a tag of six bits.  A wave polls those of
+    // eight items, two members per lane: no add waits for another at the L2, and nothing has to be subtracted.  128 rows, 640 outputs,
+    // layer norm, 100 steps, adds -> words: 2048 cells 667 -> 640 us, with a peephole 781 -> 762.  In small groups the adds are ahead: 1088 cells,
+    // 320 outputs, 60 steps 347 against 354, 1024 cells without a projection 470 against 484, 512 cells, 256 rows 402 against 420.  (Two slots by
+    // turns: who stores step t + 2 has all words of step t + 1, whose writers had those of step t.)
     auto publish_stats = [&](int round, int g_lo, int g_hi) {
       __syncthreads();
       if (tid < items) {
@@ -535,16 +544,74 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
           red[tid] = 0;  // the next adds to this word come after the next barrier
           const int64_t v1 = ((pk + (1 << 23)) & 0xFFFFFF) - (1 << 23);
           const int64_t v2 = (pk - v1) >> 24;
-          __hip_atomic_fetch_add(&accS[(round * 2 + 0) * 256 + tid], ((u64)1 << 56) + (u64)(v1 + (1 << 22)),
-                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          __hip_atomic_fetch_add(&accS[(round * 2 + 1) * 256 + tid], ((u64)1 << 56) + (u64)v2, __ATOMIC_RELAXED,
-                                 __HIP_MEMORY_SCOPE_AGENT);
+          if (member_words)
+            __hip_atomic_store(&accS[(((t & 1) * 2 + round) * 64 + tid) * 32 + member],
+                               (u64)(v1 + (1 << 21)) | (u64)v2 << 22 | (u64)((t + 1) & 63) << 58, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          else {
+            __hip_atomic_fetch_add(&accS[(round * 2 + 0) * 256 + tid], ((u64)1 << 56) + (u64)(v1 + (1 << 22)),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_fetch_add(&accS[(round * 2 + 1) * 256 + tid], ((u64)1 << 56) + (u64)v2, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+          }
         }
       }
     };
+    auto poll_stats = [&](int round) {
+      int l = lane;
+      asm volatile("" : "+v"(l));
+      const int sub = l & 15, it = l >> 4;  // members 2 sub, 2 sub + 1 of items 8 wave + it and, in the second load, + 4
+      const uint32_t want = (((unsigned)t + 1) << 26) ^ (never << 24);
+      const uint32_t m0 = 2 * sub < GS ? 0xFC000000u : 0, m1 = 2 * sub + 1 < GS ? 0xFC000000u : 0;
+      unsigned at[2];
+      v4i w[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) at[k] = ((((t & 1) * 2 + round) * 64 + wave * 8 + it + 4 * k) * 16 + sub) * 16;
+      int budget = a.spin_limit;
+      for (int i = 0; i < a.stats_first_sleep; ++i) __builtin_amdgcn_s_sleep(1);
+      for (;;) {
+        poll_pairs(accS, at, w);
+        uint32_t off = 0;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) off |= (((uint32_t)w[k][1] ^ want) & m0) | (((uint32_t)w[k][3] ^ want) & m1);
+        if (__builtin_amdgcn_ballot_w64(off != 0) == 0) break;
+        --budget;
+        if ((budget & 15) == 0 && (budget <= 0 || __hip_atomic_load(a.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
+          __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          *flag = 0;
+          break;
+        }
+        for (int i = 0; i < a.stats_sleep; ++i) __builtin_amdgcn_s_sleep(1);
+      }
+      // the sum, and the sum of squares in 20 and 16 bits; words of members that are not there are zero
+      uint32_t s[2][3];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const uint32_t lo0 = (uint32_t)w[k][0], hi0 = (uint32_t)w[k][1], lo1 = (uint32_t)w[k][2], hi1 = (uint32_t)w[k][3];
+        s[k][0] = (lo0 & 0x3FFFFFu) + (lo1 & 0x3FFFFFu);
+        s[k][1] = (__builtin_amdgcn_alignbit(hi0, lo0, 22) & 0xFFFFFu) + (__builtin_amdgcn_alignbit(hi1, lo1, 22) & 0xFFFFFu);
+        s[k][2] = ((hi0 >> 10) & 0xFFFFu) + ((hi1 >> 10) & 0xFFFFu);
+      }
+      auto add_lanes = [&](auto ctrl) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+          for (int i = 0; i < 3; ++i)
+            s[k][i] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s[k][i], decltype(ctrl)::value, 0xF, 0xF, false);
+      };
+      add_lanes(std::integral_constant<int, 0xB1>{});   // lane ^ 1
+      add_lanes(std::integral_constant<int, 0x4E>{});   // lane ^ 2
+      add_lanes(std::integral_constant<int, 0x141>{});  // the other four of eight
+      add_lanes(std::integral_constant<int, 0x140>{});  // the other eight of sixteen
+      const int k = sub >> 3;
+      const uint32_t sum = k ? s[1][0] : s[0][0], lo = k ? s[1][1] : s[0][1], hi = k ? s[1][2] : s[0][2];
+      if ((sub & 7) == 0)
+        lnrow[wave * 8 + it + 4 * k] = ln_row2((int64_t)sum - (int64_t)GS * (1 << 21), (int64_t)lo + ((int64_t)hi << 20), a.N, inv_n);
+    };
     // false: a wait gave up (status word raised), every thread leaves the kernel
     auto collect_stats = [&](int round, int g_lo, int g_hi) -> bool {
-      if (tid < items) {
+      if (member_words) {
+        if ((wave >> 1) >= g_lo && (wave >> 1) <= g_hi) poll_stats(round);
+      } else if (tid < items) {
         const int g = tid >> 4;
         if (g >= g_lo && g <= g_hi) {
           const u64 expect = (u64)(((unsigned)GS * (unsigned)(t + 1)) & 0xFFu);
@@ -987,21 +1054,24 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 typedef void (*rec16_pair_fn)(RecArgs2);
 
 // kernel for (flags & 7) at k depth KS16
-template <int KS16, bool PAIR, int TAG, class Fn>
+template <int KS16, bool PAIR, int FORM, class Fn>
 Fn rec16_pick_tag(int fl) {
   switch (fl & 7) {
-    case 0: return rec16_kernel<KS16, 0, PAIR, TAG>;
-    case 1: return rec16_kernel<KS16, 1, PAIR, TAG>;
-    case 2: return rec16_kernel<KS16, 2, PAIR, TAG>;
-    case 3: return rec16_kernel<KS16, 3, PAIR, TAG>;
-    case 4: return rec16_kernel<KS16, 4, PAIR, TAG>;
-    case 5: return rec16_kernel<KS16, 5, PAIR, TAG>;
-    case 6: return rec16_kernel<KS16, 6, PAIR, TAG>;
-    default: return rec16_kernel<KS16, 7, PAIR, TAG>;
+    case 0: return rec16_kernel<KS16, 0, PAIR, FORM>;
+    case 1: return rec16_kernel<KS16, 1, PAIR, FORM>;
+    case 2: return rec16_kernel<KS16, 2, PAIR, FORM>;
+    case 3: return rec16_kernel<KS16, 3, PAIR, FORM>;
+    case 4: return rec16_kernel<KS16, 4, PAIR, FORM>;
+    case 5: return rec16_kernel<KS16, 5, PAIR, FORM>;
+    case 6: return rec16_kernel<KS16, 6, PAIR, FORM>;
+    default: return rec16_kernel<KS16, 7, PAIR, FORM>;
   }
 }
 template <int KS16, bool PAIR = false, class Fn = rec_fn>
 Fn rec16_pick_ks(int fl, int tag) {
+  if constexpr (KS16 <= 10 && !PAIR)
+    if (tag == 3) return fl == 4 ? rec16_kernel<KS16, 4, PAIR, 3> : fl == 5 ? rec16_kernel<KS16, 5, PAIR, 3> : fl == 6 ? rec16_kernel<KS16, 6, PAIR, 3> : fl == 7 ? rec16_kernel<KS16, 7, PAIR, 3> : nullptr;
+  if (tag == 3) return nullptr;
   if (tag == 0) return rec16_pick_tag<KS16, PAIR, 0, Fn>(fl);
   return tag == 1 ? rec16_pick_tag<KS16, PAIR, 1, Fn>(fl) : rec16_pick_tag<KS16, PAIR, 2, Fn>(fl);
 }

@@ -189,3 +189,15 @@ def test_waits_of_a_one_step_stack_give_up(orc, flags):
     lib_model.set_option("reset_status", 1)
     assert_equal("recovered", lib_model.forward(xd).cpu().numpy(), np.asarray(orc.forward(orc_model, xq)))
     assert lib_model.device_status() == 0
+
+
+@pytest.mark.parametrize("variant", [LN, LN | PH, LN | CIFG, LN | PH | CIFG])
+@pytest.mark.parametrize("N,H,B,T", [
+    (1792, 640, 37, 4),                        # 28 workgroups per group: adds
+    (1793, 640, 37, 4), (1850, 24, 40, 5),     # 29: statistics in words of each member
+    (2048, 640, 128, 3), (1990, 648, 33, 3),   # 32; too many outputs for it
+    (2048, 16, 33, 70),                        # the tags come round
+])
+def test_statistics_of_wide_16_row_groups(orc, N, H, B, T, variant):
+    layers, x = wl.make_custom([24], N, H, variant | PROJ, B, T, seed=N + H + variant, weight_param=0.9 / N ** 0.5)
+    run_and_compare(orc, layers, x, f"s16_{N}_{H}_{variant}", trace=False, rows=[0, 15, 16, 31, B - 1], options={"rows16": 2})
