@@ -284,7 +284,11 @@ int lstm_int_forward_bidirectional(const lstm_int_model *fwd, const lstm_int_mod
  *           steps, while the layer below works on the next one; in a bidirectional
  *           call both directions (of up to 3 layers) together.  0 = never, 1
  *           (default) = where it is expected to be the fastest way, 2 = wherever it
- *           can run.  Calls with a trace run layer after layer.
+ *           can run.  Calls with a trace run layer after layer.  A workgroup there
+ *           waits for the layer below of its row (at most "spin_limit" polls, then
+ *           the device status says so), which has always started before it: the
+ *           launch needs nothing of "cooperative_launch", other calls may run on
+ *           other streams at the same time.
  *   "row_stack_piece": steps of a piece, 1 to 16; 0 (default) = chosen.
  *   "stack_step_ns", "stack_prefetch_kb", "flag_sleep": knobs of the stacked
  *           launch: expected time of one item (for the choice above), KB of a

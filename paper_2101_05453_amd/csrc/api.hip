@@ -1280,6 +1280,7 @@ int forward_row_stack(lstm_int_model *const *m, const RowStackPlan &p, const int
   int *const flags = reinterpret_cast<int *>(wsb + p.flags);
   RowStackArgs args;
   memset(&args, 0, sizeof(args));
+  args.dirs = dirs;
   size_t lds = 0;
   if (p.own0) {
     Timed t(m[0]->prof, s, LSTM_INT_K_OTHER);

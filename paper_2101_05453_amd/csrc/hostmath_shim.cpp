@@ -4,6 +4,7 @@
 #include "calibrate_plan.h"
 #include "lstm_int_math.h"
 #include "model.h"
+#include "row_stack_plan.h"
 #include "sru_plan.h"
 
 using namespace lstm_int;
@@ -13,6 +14,13 @@ extern "C" {
 int32_t hm_rescale(int32_t a, int32_t M, int32_t r) { return rescale(a, M, r); }
 int32_t hm_rescale_hi(int32_t a, int32_t M, int32_t r) { return rescale_hi(a, M, r); }
 int64_t hm_isqrt(int64_t v) { return isqrt_u52(v); }
+
+// place of a workgroup in a launch of several small layers: chain, direction, row, and the layer's arguments for the order of its start
+void hm_row_stack_place(int32_t block, int32_t rows, int32_t dirs, int32_t order, int32_t out[4]) {
+  const RowStackPlace p = row_stack_place(block, rows, dirs);
+  out[0] = p.chain; out[1] = p.dir; out[2] = p.row;
+  out[3] = row_stack_link(order, p.dir, dirs);
+}
 
 // layer norm of one row through ln_row / ln_apply
 void hm_layernorm(const int16_t *q, int32_t n, const int16_t *qL, const int32_t *qb, int32_t M,

@@ -286,7 +286,8 @@ struct RowInput {  // W x in the launch itself instead of tx2 (x == NULL): then 
   int piece, term_steps;  // steps of a piece of the sequence, at most 16, and steps of terms a wave has room for in LDS
   int x_bytes;            // LDS for x of a piece: 1 KB for each 64-byte k step of the deepest layer that computes W x
   const int *ready;       // words of the layer below, or NULL: x is complete
-  int *done;              // [B] words of kRowFlagWords: steps of the row that are in `out`; NULL: nobody reads `out` in this launch
+  int *done;              // [B] words of kRowFlagWords: steps of the row that are in `out`; NULL: nobody reads `out` in this launch.  (Of the
+                          // first layers, directions one behind the other, word 1 too: workgroups of the row that have started.)
   int spin_limit, never;  // never: 0; tests: steps that will not come are waited for
 };
 struct RowArgs {
@@ -324,12 +325,14 @@ struct RowStackArgs {
     RowLayer d[kRowStackLayers];
   } rec;
   RowInput in[kRowStackLayers];
+  int dirs;  // 2: the layers of two directions by turns
 };
 static_assert(sizeof(RowStackArgs) <= 4096, "kernel arguments");
 void row_stack_layer(RowLayer &to, const RecDirArgs &from);
 // LDS of a launch, for one of its layers; widest: most cells or outputs of a layer
 size_t row_stack_lds_bytes(const RecArgs &a, int widest, int term_steps, int x_bytes);
 // flags: the layers'; lds: the most that one of them needs
+// layers: of all directions.  The words behind in[..].done are zero at launch.
 hipError_t launch_row_stack(hipStream_t s, const RowStackArgs &a, int layers, int flags, int widest, size_t lds);
 
 bool row_supported(int N, int H, int flags, int rows);

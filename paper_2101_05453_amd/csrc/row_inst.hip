@@ -160,7 +160,9 @@ hipError_t launch_row_stack(hipStream_t s, const RowStackArgs &a, int layers, in
   int H = 0;
   for (int l = 0; l < layers && l < kRowStackLayers; ++l) H = H > a.rec.d[l].H ? H : a.rec.d[l].H;
   row_stack_fn fn = layers < 1 || layers > kRowStackLayers ? nullptr : pick_row_stack(form, H, flags & 15);
-  if (!fn || lds > 160 * 1024) return hipErrorInvalidValue;
+  if (!fn || lds > 160 * 1024 || a.dirs < 1 || a.dirs > 2 || layers % a.dirs != 0) return hipErrorInvalidValue;
+  for (int i = 0; i < a.dirs; ++i)  // where workgroups that start are counted
+    if (a.in[i].done != a.in[0].done + (size_t)i * a.rec.d[0].B * kRowFlagWords || !a.in[0].done) return hipErrorInvalidValue;
   for (int l = 0; l < layers; ++l) {
     const RowInput &in = a.in[l];
     if (a.rec.d[l].B != a.rec.d[0].B || in.piece < 1 || in.piece > 16 || in.term_steps < (in.x ? in.piece : 2 * in.piece) || (in.x && in.x_bytes < 1024 * in.kx) || !a.rec.d[l].R2h ||

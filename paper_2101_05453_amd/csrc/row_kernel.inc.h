@@ -11,7 +11,8 @@
 // v_permlane32_swap) then give every lane all four gates of its cell, and the cell update runs in the four lanes alike.  With
 // coupled gates, group 0 repeats the f gate.
 //
-// Everything else is as in solo_kernel: h, m and the layer-norm sums pass through LDS, no workgroup waits for another.
+// Everything else is as in solo_kernel: h, m and the layer-norm sums pass through LDS, no workgroup waits for another, but in a launch
+// of several layers (kRowStack) for the layer below.
 //
 // What bounds it: the chain of a step, 64 cells 0.5 us (product 0.1, two table lookups 0.1 each, the arithmetic between them one
 // dependent instruction per 8 clocks), layer norm 0.45 us more; with 16 waves (129 to 256 cells, 1.1 us) the issue of four waves a
@@ -22,6 +23,7 @@
 #pragma once
 
 #include "rec_kernel.inc.h"
+#include "row_stack_plan.h"
 
 namespace lstm_int {
 
@@ -45,9 +47,9 @@ constexpr int kRowStack = 2;  // a launch of several layers: computed here, a pi
 // KS16: k steps of R h, as the outputs ask for: with 16 waves (129 to 256 cells) two to four (each that is not there saves 16 of 64 products
 // a wave and 16 of its 128 registers: layers of 129 to 192 cells 0.93 of the time with four, up to 128 outputs of wider ones 0.85)
 // FL: bit 0 coupled gates, bit 1 peephole, bit 2 layer norm, bit 3 projection.  MODE: kRow...
-// kRowStack: several layers in one launch, a workgroup per (layer, row), those of the layers below first.  Rows never interact, so a
-// layer's workgroup waits for one other alone, that of the same row in the layer below, and for nobody above it: workgroups start
-// in their order, so that whoever is waited for has started or will, however few fit the chip at once.
+// kRowStack: several layers in one launch, a workgroup per (layer, row).  Rows never interact, so a layer's workgroup waits for one
+// other alone, that of the same row in the layer below, and for nobody above it; a row's workgroups take its layers in the order in
+// which they start, from the bottom, so that whoever is waited for has started (row_stack_plan.h).
 template <int WAVES, int KS16, int FL, int MODE>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVES == 4 ? 2 : WAVES / 4, WAVES == 4 ? 2 : WAVES / 4))) void row_kernel(std::conditional_t<MODE == kRowStack, RowStackArgs, RowArgs> all) {
   constexpr bool OWN = MODE == kRowOwn, STACK = MODE == kRowStack;
@@ -71,8 +73,14 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
   // kernels of one layer take two registers more, which 16 waves with peephole and layer norm do not have)
   int which, row = (int)blockIdx.x;
   if constexpr (STACK) {
-    which = row / all.rec.d[0].B;
-    row -= which * all.rec.d[0].B;
+    const RowStackPlace place = row_stack_place((int)blockIdx.x, all.rec.d[0].B, all.dirs);
+    int *const order = reinterpret_cast<int *>(lds + 3 * NC + 16 * 8 + 4 * sizeof(LnRow2)) + 2;  // (behind `flag`, not written again)
+    if (tid == 0)
+      *order = __hip_atomic_fetch_add(all.in[0].done + place.chain * kRowFlagWords + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    // (in scalar registers again: the compiler carries what the branch above has read in vector ones, and the arguments with it)
+    which = __builtin_amdgcn_readfirstlane(row_stack_link(*order, place.dir, all.dirs));
+    row = __builtin_amdgcn_readfirstlane(place.row);
   } else {
     which = (int)blockIdx.x >= all.rec.d[0].groups ? 1 : 0;
     row -= which ? all.rec.d[0].groups : 0;

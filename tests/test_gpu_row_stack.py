@@ -145,6 +145,38 @@ def test_a_wait_that_gives_up(orc):
     assert model.device_status() == 0
 
 
+@pytest.mark.parametrize("cooperative", [0, 1])
+def test_several_streams(orc, cooperative):
+    """Launches of all sizes on eight streams at once: more workgroups than compute units."""
+    import torch
+
+    models, inputs, want = [], [], []
+    for i, (L, N, B, T) in enumerate([(6, 64, 42, 40), (2, 200, 128, 20), (3, 96, 7, 64), (4, 130, 5, 50)]):
+        layers, x = wl.make_custom([48] + [N] * (L - 1), N, N, LN if i % 2 else 0, B, T, seed=i, weight_param=0.9 / N ** 0.5)
+        model, oracle, xq = prepare_both(orc, layers, x)
+        model.set_option("row_stack", 2)
+        model.set_option("cooperative_launch", cooperative)
+        models.append(model)
+        inputs.append(torch.from_numpy(xq).cuda())
+        rows = sorted({0, B - 1})
+        want.append((rows, np.asarray(orc.forward(oracle, np.ascontiguousarray(xq[:, rows])))))
+    streams = [torch.cuda.Stream() for _ in range(8)]
+    spaces = [torch.empty(models[i % 4].workspace_bytes(*inputs[i % 4].shape[:2]), dtype=torch.uint8, device="cuda") for i in range(8)]
+    got = [[] for _ in range(8)]
+    torch.cuda.synchronize()
+    for _ in range(3):
+        for i, s in enumerate(streams):
+            with torch.cuda.stream(s):
+                got[i].append(models[i % 4].forward(inputs[i % 4], workspace=spaces[i]))
+    torch.cuda.synchronize()
+    assert all(m.device_status() == 0 for m in models)
+    for i, ys in enumerate(got):
+        rows, y = want[i % 4]
+        assert_equal("oracle", ys[0].cpu().numpy()[:, rows], y)
+        for other in ys[1:] + got[i % 4]:
+            assert_equal("every call", other.cpu().numpy(), ys[0].cpu().numpy())
+
+
 @pytest.mark.parametrize("I", [64, 1024])
 def test_captured_in_a_hip_graph(orc, I):
     import torch
