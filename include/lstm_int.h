@@ -399,10 +399,12 @@ int lstm_int_phase_ticks(const lstm_int_model *model, int64_t ticks[16]);
  * Per-kernel device time of the forward calls made while profiling is on,
  * measured with HIP events on the stream the kernels run on.
  * lstm_int_profile_begin resets the counters and makes forward record events
- * (created as the launches need them, any number per call; a launch of the
- * kernel with a workgroup per row that runs several layers counts once for each);
+ * (created as the launches need them, any number per call);
  * lstm_int_profile_end synchronizes that stream, fills, per kernel class k
  * (LSTM_INT_K_*), launches[k] and total_ms[k], and destroys the events.
+ * A launch counts once, however many layers it runs ("stack", "row_stack"); one
+ * that runs both directions of a bidirectional call is in the figures of either
+ * model.
  * Profiling adds host work to forward; throughput is measured with it off.
  */
 #define LSTM_INT_K_INPUT_GEMM 0 /* hoisted W x over all T, + rescale        */

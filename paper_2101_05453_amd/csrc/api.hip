@@ -111,7 +111,7 @@ struct Profile {
   bool on = false;
   hipStream_t stream = nullptr;
   std::vector<hipEvent_t> ev;  // pairs (start, stop)
-  std::vector<int> cls, layers;  // of each pair: kernel class, layers that the launch runs and is counted for
+  std::vector<int> cls;
   size_t used = 0;  // pairs in use
   bool failed = false;  // an event could not be created: the times would be incomplete
   void release() {
@@ -119,7 +119,6 @@ struct Profile {
       if (e) (void)hipEventDestroy(e);
     ev.clear();
     cls.clear();
-    layers.clear();
     used = 0;
   }
 };
@@ -290,7 +289,7 @@ struct Timed {
   Profile &p;
   hipStream_t s;
   bool active;
-  Timed(Profile &prof, hipStream_t stream, int cls, int layers = 1) : p(prof), s(stream), active(false) {
+  Timed(Profile &prof, hipStream_t stream, int cls) : p(prof), s(stream), active(false) {
     if (!p.on) return;
     // events are created as launches need them (any number of launches per call) and freed by profile_end
     if ((p.used + 1) * 2 > p.ev.size()) {
@@ -303,10 +302,8 @@ struct Timed {
       p.ev.push_back(e0);
       p.ev.push_back(e1);
       p.cls.push_back(0);
-      p.layers.push_back(1);
     }
     active = true;
-    p.layers[p.used] = layers;
     p.cls[p.used] = cls;
     p.stream = s;
     (void)hipEventRecord(p.ev[2 * p.used], s);
@@ -1335,9 +1332,9 @@ int forward_row_stack(lstm_int_model *const *m, const RowStackPlan &p, const int
       c_off += (size_t)B * h.N;
     }
   }
-  Timed t0(m[0]->prof, s, LSTM_INT_K_RECURRENT, L);
-  std::optional<Timed> t1;  // the other direction's model counts its layers too
-  if (dirs == 2) t1.emplace(m[1]->prof, s, LSTM_INT_K_RECURRENT, L);
+  Timed t0(m[0]->prof, s, LSTM_INT_K_RECURRENT);
+  std::optional<Timed> t1;  // as every launch for two directions, in the profiles of both models
+  if (dirs == 2) t1.emplace(m[1]->prof, s, LSTM_INT_K_RECURRENT);
   return launch_row_stack(s, args, L * dirs, (int)m[0]->host[0].flags, p.room.widest, lds) == hipSuccess ? LSTM_INT_OK : LSTM_INT_E_DEVICE;
 }
 
@@ -2108,7 +2105,7 @@ int lstm_int_profile_end(lstm_int_model *m, int64_t launches[LSTM_INT_K_COUNT],
       rc = LSTM_INT_E_DEVICE;
       break;
     }
-    launches[p.cls[i]] += p.layers[i];
+    launches[p.cls[i]] += 1;
     total_ms[p.cls[i]] += ms;
   }
   p.release();  // no event outlives the measurement

@@ -34,6 +34,23 @@ def prepare_both(orc, layers, x, device=0, scale_x=1.0):
     return lib_model, orc_model, xq
 
 
+def run_counted(model, forward):
+    """forward()'s result, the launches by kernel class, and how the layers of `model`, two or more, ran: "rows" -- one launch, a
+    workgroup per (layer, row), a kernel without phase timers --, "stack" -- one launch, a layer per XCD -- or "layers",
+    one after the other."""
+    import torch
+
+    model.set_option("phase_timing", 1)
+    model.profile_begin()
+    y = forward()
+    torch.cuda.synchronize()
+    n = {k: v["launches"] for k, v in model.profile_end().items()}
+    timed = any(model.phase_ticks())
+    model.set_option("phase_timing", 0)
+    assert model.device_status() == 0 and n["cell"] == 0, n
+    return y, n, "layers" if n["recurrent"] > 1 else "stack" if timed else "rows"
+
+
 def assert_equal(name, got, want):
     got, want = np.asarray(got), np.asarray(want)
     assert got.shape == want.shape and got.dtype == want.dtype, (name, got.shape, want.shape, got.dtype, want.dtype)

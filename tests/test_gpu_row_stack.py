@@ -1,15 +1,27 @@
 """Several layers of up to 256 cells in one launch, a workgroup per (layer, row): every variant in each of the three forms, pieces of the
 sequence of every kind, layers of unlike widths, the first layer's W x from the input matmul and in the launch, carried state, both
-directions, a wait that gives up, and the launch under capture; against the oracle and against layer after layer."""
+directions, a wait that gives up, and the launch under capture; against the oracle and against layer after layer.  That it is this
+launch that ran, the launches and the phase timers show."""
 import numpy as np
 import pytest
 
 import lstm_workloads as wl
 from paper_2101_05453_amd import binding
-from parity_util import assert_equal, prepare_both, run_and_compare
+from parity_util import assert_equal, prepare_both, run_and_compare, run_counted
 
 pytestmark = pytest.mark.gpu
 LN, PH, PROJ, CIFG = wl.LAYER_NORM, wl.PEEPHOLE, wl.PROJECTION, wl.CIFG
+
+
+def compare_rows(orc, layers, x, name, options):
+    """run_and_compare on one launch of all layers."""
+    import torch
+
+    model, y = run_and_compare(orc, layers, x, name, trace=False, options=dict(options, row_stack=2))
+    xd = torch.zeros(x.shape, dtype=torch.int8, device="cuda")
+    _, n, way = run_counted(model, lambda: model.forward(xd))
+    assert way == "rows" and n["recurrent"] == 1 and n["input_gemm"] <= 1, (n, way)
+    return n
 
 
 @pytest.mark.parametrize("flags", range(16))
@@ -17,7 +29,7 @@ LN, PH, PROJ, CIFG = wl.LAYER_NORM, wl.PEEPHOLE, wl.PROJECTION, wl.CIFG
 def test_every_variant(orc, N, flags):
     H = N - 9 if flags & PROJ else N
     layers, x = wl.make_custom([32, H, H], N, H, flags, 3, 21, seed=N + flags, weight_param=0.9 / N ** 0.5)
-    run_and_compare(orc, layers, x, f"rows{N}f{flags}", trace=False, options={"row_stack": 2})
+    compare_rows(orc, layers, x, f"rows{N}f{flags}", {})
 
 
 @pytest.mark.parametrize("T,piece", [(1, 0), (2, 1), (7, 3), (16, 16), (17, 16), (33, 8), (40, 5)])
@@ -28,17 +40,14 @@ def test_pieces(orc, T, piece, I):
     flags = (LN, 0, PH | LN, CIFG | LN | PROJ)[(T + I) % 4]
     N = (64, 100, 203)[T % 3]
     layers, x = wl.make_custom([I, N, N, N], N, N, flags, 5, T, seed=T + I, weight_param=0.9 / N ** 0.5)
-    run_and_compare(orc, layers, x, f"piece{T}.{piece}i{I}", trace=False, options={"row_stack": 2, "row_stack_piece": piece})
+    compare_rows(orc, layers, x, f"piece{T}.{piece}i{I}", {"row_stack_piece": piece})
 
 
-def counted(model, xd, **kw):
-    import torch
-
-    model.profile_begin()
-    y = model.forward(xd, **kw)
-    torch.cuda.synchronize()
-    assert model.device_status() == 0
-    return y.cpu().numpy(), {k: v["launches"] for k, v in model.profile_end().items()}
+@pytest.mark.parametrize("I,T,gemm", [(64, 12, 0), (64, 200, 0), (1024, 12, 1), (1024, 200, 1)])
+def test_the_first_layers_input(orc, I, T, gemm):
+    """W x of the first layer in the launch or by the input matmul."""
+    layers, x = wl.make_custom([I, 256], 256, 256, 0, 30, T, seed=I + T, weight_param=0.05)
+    assert compare_rows(orc, layers, x, f"first{I}.{T}", {})["input_gemm"] == gemm
 
 
 @pytest.mark.parametrize("L,N,B,T,flags,rows", [(6, 96, 42, 12, LN, True), (2, 128, 128, 5, 0, True), (2, 128, 129, 5, 0, False),
@@ -51,12 +60,13 @@ def test_limits(orc, L, N, B, T, flags, rows):
     model, oracle, xq = prepare_both(orc, layers, x)
     xd = torch.from_numpy(xq).cuda()
     model.set_option("row_stack", 2)
-    y, n = counted(model, xd)
-    # the input matmul's launches: of the first layer alone, or of every one that runs by itself
-    assert (n["input_gemm"] + n["recurrent"] <= L + 1) == rows or not rows, n
+    model.set_option("stack_step_ns", 1000000)  # (the launch of a layer per XCD is never the faster way)
+    y, n, way = run_counted(model, lambda: model.forward(xd).cpu().numpy())
+    assert way == ("rows" if rows else "layers") and n["recurrent"] == (1 if rows else L), (n, way)
     model.set_option("row_stack", 0)
     model.set_option("stack", 0)
-    other, _ = counted(model, xd)
+    other, n, way = run_counted(model, lambda: model.forward(xd).cpu().numpy())
+    assert way == "layers" and n["recurrent"] == L, (n, way)
     assert_equal("both ways", y, other)
     at = sorted({0, B // 2, B - 1})
     assert_equal("y", y[:, at], np.asarray(orc.forward(oracle, np.ascontiguousarray(xq[:, at]))))
@@ -79,7 +89,11 @@ def test_carried_state(orc, reverse):
         h = torch.cat([torch.full((B * N,), model.get_quant(l)["zp_h"], dtype=torch.int8, device="cuda") for l in range(3)])
         c = torch.zeros(3 * B * N, dtype=torch.int16, device="cuda")
         cuts = [(0, 9), (9, 10), (10, T)]
-        ys = [model.forward(xd[a:b].contiguous(), h_state=h, c_state=c) for a, b in (cuts[::-1] if reverse else cuts)]
+        ys = []
+        for a, b in cuts[::-1] if reverse else cuts:
+            y, _, ran = run_counted(model, lambda: model.forward(xd[a:b].contiguous(), h_state=h, c_state=c))
+            assert ran == ("rows" if way else "layers")
+            ys.append(y)
         got[way] = [torch.cat(ys[::-1] if reverse else ys).cpu().numpy(), h.cpu().numpy(), c.cpu().numpy()]
     assert model.device_status() == 0
     for name, a, b in zip("yhc", got[2], got[0]):
@@ -108,7 +122,10 @@ def test_two_directions(orc, N, I, B, T, flags):
     for way in (2, 0):
         fwd.set_option("row_stack", way)
         states = [(torch.zeros(3 * B * H, dtype=torch.int8, device="cuda"), torch.zeros(3 * B * N, dtype=torch.int16, device="cuda")) for _ in range(2)]
-        y = binding.forward_bidirectional(fwd, bwd, xd, state_fwd=states[0], state_bwd=states[1])
+        bwd.profile_begin()
+        y, n, ran = run_counted(fwd, lambda: binding.forward_bidirectional(fwd, bwd, xd, state_fwd=states[0], state_bwd=states[1]))
+        # one launch, in the profiles of both models; else one for each layer of either direction or of both
+        assert ran == ("rows" if way else "layers") and bwd.profile_end()["recurrent"]["launches"] == n["recurrent"] == (1 if way else 3), n
         ys.append([y.cpu().numpy()] + [s.cpu().numpy() for p in states for s in p])
     assert fwd.device_status() == 0 and bwd.device_status() == 0
     for a, b in zip(*ys):
@@ -124,7 +141,7 @@ def test_layers_of_unlike_widths(orc):
     a, x = wl.make_custom([48], 200, 200, LN, 4, 20, seed=2, weight_param=0.07)
     b, _ = wl.make_custom([200], 40, 40, LN, 4, 20, seed=3, weight_param=0.1)
     c, _ = wl.make_custom([40], 130, 130, LN, 4, 20, seed=4, weight_param=0.08)
-    run_and_compare(orc, a + b + c, x, "unlike", trace=False, options={"row_stack": 2})
+    compare_rows(orc, a + b + c, x, "unlike", {})
 
 
 def test_a_wait_that_gives_up(orc):
@@ -158,6 +175,7 @@ def test_several_streams(orc, cooperative):
         model.set_option("cooperative_launch", cooperative)
         models.append(model)
         inputs.append(torch.from_numpy(xq).cuda())
+        assert run_counted(model, lambda: model.forward(inputs[-1]))[2] == "rows"
         rows = sorted({0, B - 1})
         want.append((rows, np.asarray(orc.forward(oracle, np.ascontiguousarray(xq[:, rows])))))
     streams = [torch.cuda.Stream() for _ in range(8)]
@@ -188,8 +206,7 @@ def test_captured_in_a_hip_graph(orc, I):
     xd = torch.from_numpy(xq).cuda()
     ws = torch.empty(model.workspace_bytes(30, 6), dtype=torch.uint8, device="cuda")
     y = torch.empty((30, 6, 96), dtype=torch.int8, device="cuda")
-    model.forward(xd, y=y, workspace=ws)
-    torch.cuda.synchronize()
+    assert run_counted(model, lambda: model.forward(xd, y=y, workspace=ws))[2] == "rows"
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
         model.forward(xd, y=y, workspace=ws)

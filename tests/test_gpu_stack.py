@@ -8,7 +8,7 @@ import numpy as np
 import pytest
 
 import lstm_workloads as wl
-from parity_util import assert_equal, prepare_both, run_and_compare
+from parity_util import assert_equal, prepare_both, run_and_compare, run_counted
 
 pytestmark = pytest.mark.gpu
 
@@ -19,15 +19,12 @@ VARIANTS = [0, wl.LAYER_NORM, wl.PEEPHOLE, wl.PROJECTION, wl.CIFG,
 
 
 def _ran_stacked(lib_model, T, B, I0, layers):
-    """One launch of the recurrent class for the whole stack (the launches one after
-    the other need one per layer)."""
+    """One launch of the recurrent class for the whole stack, of the kernel with one layer
+    per XCD (the launches one after the other need one per layer)."""
     import torch
 
-    lib_model.profile_begin()
-    lib_model.forward(torch.zeros((T, B, I0), dtype=torch.int8, device="cuda"))
-    prof = lib_model.profile_end()
-    assert lib_model.device_status() == 0
-    return prof["recurrent"]["launches"] == 1 and prof["input_gemm"]["launches"] == 0 and prof["cell"]["launches"] == 0
+    _, n, way = run_counted(lib_model, lambda: lib_model.forward(torch.zeros((T, B, I0), dtype=torch.int8, device="cuda")))
+    return way == "stack" and n["input_gemm"] == 0
 
 
 @pytest.mark.parametrize("flags", VARIANTS)
@@ -172,8 +169,14 @@ def test_stack_wait_gives_up_and_model_recovers(orc):
 
 def test_stack_falls_back(orc):
     """Layers that differ (or a trace request) run one after the other as before, with
-    the option on."""
+    the option on -- or, as small as these, with a workgroup per (layer, row)."""
+    import torch
+
     layers, x = wl.make_custom([72, 200], 200, 200, wl.LAYER_NORM, 10, 4, seed=9)
     layers2, _ = wl.make_custom([200], 136, 136, wl.LAYER_NORM, 10, 4, seed=10)
     lib_model, _ = run_and_compare(orc, layers + layers2, x, "stack_mixed", trace=True, options={"stack": 2})
     assert not _ran_stacked(lib_model, 4, 10, 72, layers)
+    lib_model.set_option("row_stack", 0)
+    xd = torch.zeros((4, 10, 72), dtype=torch.int8, device="cuda")
+    _, n, way = run_counted(lib_model, lambda: lib_model.forward(xd))
+    assert way == "layers" and n["recurrent"] == 3, (way, n)
