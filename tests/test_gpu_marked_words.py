@@ -146,3 +146,27 @@ def test_waits_for_marked_state_give_up():
     m.set_option("spin_limit", 1 << 21)
     m.set_option("reset_status", 1)
     assert torch.equal(m.forward(xq), want) and m.device_status() == 0
+
+
+LONG = (1 << 14) + 9  # a launch takes 2^14 steps at most: the slots are marked again between two
+
+
+@pytest.mark.parametrize("rows16", [0, 2])
+@pytest.mark.parametrize("flags", [0, LN])
+def test_slots_of_a_second_launch(orc, flags, rows16):
+    layers, x = wl.make_custom([4], 136, 24, flags | PROJ, 35, LONG, seed=3, weight_param=0.08)
+    run_and_compare(orc, layers, x, f"long{flags}", trace=False, rows=[0, 31, 34], options={"rows16": rows16})
+
+
+@pytest.mark.parametrize("flags", [0, LN])
+def test_slots_of_the_state_in_a_second_launch(flags):
+    """The 32-row kernel at the longest k; against one launch per operation and step, which has no slots."""
+    layers, x = wl.make_custom([4], 650, 650, flags, 43, LONG, seed=4, weight_param=0.04)
+    calibrate_on_gpu(layers, np.ascontiguousarray(x[:64]))
+    m = binding.prepare(layers)
+    m.set_option("rows16", 0)
+    xq = m.quantize_input(torch.from_numpy(x).cuda())
+    y = m.forward(xq)
+    assert m.device_status() == 0
+    m.set_option("path", 1)
+    assert torch.equal(m.forward(xq), y)

@@ -201,3 +201,32 @@ def test_waits_of_a_one_step_stack_give_up(orc, flags):
 def test_statistics_of_wide_16_row_groups(orc, N, H, B, T, variant):
     layers, x = wl.make_custom([24], N, H, variant | PROJ, B, T, seed=N + H + variant, weight_param=0.9 / N ** 0.5)
     run_and_compare(orc, layers, x, f"s16_{N}_{H}_{variant}", trace=False, rows=[0, 15, 16, 31, B - 1], options={"rows16": 2})
+
+
+@pytest.mark.parametrize("variant", [LN, LN | PH, LN | CIFG, LN | PH | CIFG])
+@pytest.mark.parametrize("N,H,B", [(1793, 24, 21), (2048, 640, 33)])
+def test_saturated_statistics_of_wide_16_row_groups(orc, N, H, B, variant):
+    """A member's word holds its sum, its sum of squares and the step in 22, 36 and 6 bits: all of its 64 gate sums at either end of
+    their range, where sum and squares come within 64 and within 2^22 of what the fields hold, in a row with members of both signs, in
+    one of one sign (a variance of nearly 0), and beside ordinary members."""
+    import torch
+
+    layers, x = wl.make_custom([16], N, H, variant | PROJ, B, 5, seed=N + variant, weight_param=0.02)
+    lay, member = layers[0], np.arange(N) // 64
+    signs = {0: np.where(member % 2, 1.0, -1.0), 1: np.ones(N), 2: np.where(member < 5, 1.0, -1.0), 3: np.where(member % 3 == 0, 1.0, 0.0)}
+    for g in range(1 if variant & CIFG else 0, 4):
+        s = signs[g][:, None].astype(np.float32)
+        lay.W[g] = np.ascontiguousarray(np.where(s != 0, s * (np.abs(lay.W[g]) + 0.05), lay.W[g] * 0.01).astype(np.float32))
+        if variant & PH and g != 2:  # of the sign of the gate sum, where the state is of the sign of the z gate
+            p = (0, 1, None, 2)[g]
+            lay.P[p] = (np.abs(lay.P[p]) * np.where(signs[2] * signs[g] < 0, -1, 1)).astype(np.float32)
+    x = np.ascontiguousarray((np.abs(x) + 0.3) * np.where(np.arange(B) % 2, 1.0, -1.0)[None, :, None]).astype(np.float32)
+    lib_model, orc_model, xq = prepare_both(orc, layers, x, scale_x=60.0)
+    lib_model.set_option("rows16", 2)
+    y = lib_model.forward(torch.from_numpy(xq).cuda()).cpu().numpy()
+    assert lib_model.device_status() == 0
+    rows = [0, 1, 15, 16, B - 1]
+    want, trace = orc.forward(orc_model, np.ascontiguousarray(xq[:, rows]), trace_layer=0)
+    full = trace["g"][:, :, :, :N // 64 * 64].reshape(5, len(rows), 4, N // 64, 64)
+    assert all((full[:, :, g] == v).all(axis=-1).any() for g in (1, 2, 3) for v in (32767, -32767))
+    assert_equal("y", y[:, rows], np.asarray(want))
