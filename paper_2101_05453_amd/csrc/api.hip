@@ -984,9 +984,11 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1, bo
     r16.Wp2 = d.Wp2; r16.bp2 = d.bp2; r16.ptiles = d.ptiles; r16.prow = 32;
     // the exchange words share the region of the statistics words with all groups of the launch
     r16.flags &= ~kFourPredSlots;
-    // From 1793 cells on the statistics in words of each member (with the form, 60 steps: 2048 cells 1.04 of the rate, 1500 0.986, 1088 0.98), of
-    // one direction and to 640 outputs (the next depth has no registers for it).
-    if (h.layer_norm() && proj && d.GS > 28 && k16 <= 10 && share == 1) r16.flags |= kMemberStats;
+    // Statistics in words of each member in wide groups, of one direction and to 640 outputs (the next depth has no registers for it).
+    // 100 rows, 60 steps, adds -> words, us: layer norm, 640 outputs, 1793 cells 383 -> 385, 1920 382 -> 386, 1921 388.7 -> 388.1, 2048 392
+    // -> 389 (160 outputs 352.2 -> 351.5, 354 -> 352, 355.5 -> 354.7, 360 -> 355); with two rounds a step, peephole, 1793 467 -> 447, 2048 475 ->
+    // 449 (and 1600 452 -> 442, 1408 444 -> 438, where the adds are left).
+    if (h.layer_norm() && proj && d.GS > (h.peephole() ? 28 : 30) && k16 <= 10 && share == 1) r16.flags |= kMemberStats;
     // (m through marked words then, as below)
     const int64_t words_end = sync_bytes(g16 * share) + (int64_t)g16 * share * tagged_group_bytes(r16);
     const bool m_here = proj && T < kMarkSlots;

@@ -194,7 +194,8 @@ def test_waits_of_a_one_step_stack_give_up(orc, flags):
 @pytest.mark.parametrize("variant", [LN, LN | PH, LN | CIFG, LN | PH | CIFG])
 @pytest.mark.parametrize("N,H,B,T", [
     (1792, 640, 37, 4),                        # 28 workgroups per group: adds
-    (1793, 640, 37, 4), (1850, 24, 40, 5),     # 29: statistics in words of each member
+    (1793, 640, 37, 4), (1850, 24, 40, 5),     # 29: with a peephole statistics in words of each member
+    (1920, 40, 33, 3), (1921, 40, 33, 3),      # 30, 31: without one too
     (2048, 640, 128, 3), (1990, 648, 33, 3),   # 32; too many outputs for it
     (2048, 16, 33, 70),                        # the tags come round
 ])
@@ -204,7 +205,7 @@ def test_statistics_of_wide_16_row_groups(orc, N, H, B, T, variant):
 
 
 @pytest.mark.parametrize("variant", [LN, LN | PH, LN | CIFG, LN | PH | CIFG])
-@pytest.mark.parametrize("N,H,B", [(1793, 24, 21), (2048, 640, 33)])
+@pytest.mark.parametrize("N,H,B", [(1921, 24, 21), (2048, 640, 33)])
 def test_saturated_statistics_of_wide_16_row_groups(orc, N, H, B, variant):
     """A member's word holds its sum, its sum of squares and the step in 22, 36 and 6 bits: all of its 64 gate sums at either end of
     their range, where sum and squares come within 64 and within 2^22 of what the fields hold, in a row with members of both signs, in
