@@ -241,7 +241,8 @@ int lstm_int_forward_static(const lstm_int_model *model, const int8_t *x, int32_
  * State buffers as in lstm_int_forward, per direction, each may be NULL; the
  * backward state enters at t = T - 1 and leaves after t = 0.
  * workspace >= lstm_int_bidirectional_workspace_bytes(fwd, bwd, T, B).
- * The two directions run one after the other on hip_stream.
+ * The two directions run on hip_stream, side by side in one launch per layer or
+ * for all layers where their shapes allow it, else one after the other.
  * LSTM_INT_E_INVALID_ARG: widths or input quantization differ, fwd has
  * "reverse" set or bwd has not.
  */
@@ -326,12 +327,18 @@ int lstm_int_forward_bidirectional(const lstm_int_model *fwd, const lstm_int_mod
  *   "poll_sleep", "stats_sleep": pause between two polls of a group barrier /
  *           of the layer-norm statistics words inside the persistent kernel,
  *           in units of 64 clocks (0..1024; defaults 0 and 0).
- *   "stats_first_sleep": pause before the first poll of the statistics words
- *           (default 8).
+ *   "stats_first_sleep": pause before the first poll of the statistics words;
+ *           default 8, but 1 where groups of 16 rows have a word of each
+ *           workgroup (from 1793 cells on with a peephole, from 1921 without), and
+ *           16 in the stacked launch of several items per layer from 16 workgroups
+ *           a layer on.
  *   "sync_sleep": pause before the first poll of the barrier at which all
  *           workgroups of a group arrive together (the first polls would find
- *           the count incomplete and delay the arrivals); -1 (default) = 16 for
- *           groups of 16 workgroups and more, else 4.
+ *           the count incomplete and delay the arrivals), and, in groups of 32
+ *           rows, before the first look at the state or the projection's input
+ *           where those are handed on without a barrier; -1 (default) = 16 for
+ *           groups of 16 workgroups and more (8 in groups of 32 and 64 rows),
+ *           else 4.
  *   "idle_sleep", "idle_poll_sleep": the same for the workgroups that have no
  *           projection tile, behind the projection: pause before their first
  *           poll and between polls (defaults 64 and 12) of the barrier there.

@@ -949,7 +949,8 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1, bo
     // 224 outputs, layer norm, 12 steps, 64 rows, us: groups of four rows over several workgroups 57, per row without them 45), or
     // none at all.  (LDS for W x in the launch is enough for a launch without, the pieces of a long sequence among them.)
     const bool small = per_row && row_supported(h.N, h.H, (int)h.flags, B * share);
-    p.row = small && (room ? row_stack_lds_bytes(r1, room->widest, room->term_steps, room->x_bytes) : row_lds_bytes(r1, false)) <= 160 * 1024;
+    p.row = small && (room ? row_stack_lds_bytes(r1, room->widest, room->term_steps, room->x_bytes)
+                           : row_lds_bytes(r1, false)) <= 160 * 1024;
     if (room && !p.row) return p;
     // Then groups of four rows over several workgroups are ahead with layer norm alone, else one workgroup per four rows: 256 cells
     // and outputs, 64 rows, 100 steps 363 us against 376, coupled gates 352 against 327, peephole 466 against 440, both 444, 384.
@@ -1012,7 +1013,10 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1, bo
     ra.R2 = d.R2s;
     ra.sparse = 1;
   }
-  auto lds_need = [&]() { return room ? row_stack_lds_bytes(ra, room->widest, room->term_steps, room->x_bytes) : p.quad ? quad_lds_bytes(ra) : p.row ? row_lds_bytes(ra, p.row_own) : p.solo ? solo_lds_bytes(ra) : p.use16 ? rec16_lds_bytes(ra) : rec_lds_bytes(ra); };
+  auto lds_need = [&]() {
+    if (room) return row_stack_lds_bytes(ra, room->widest, room->term_steps, room->x_bytes);
+    return p.quad ? quad_lds_bytes(ra) : p.row ? row_lds_bytes(ra, p.row_own) : p.solo ? solo_lds_bytes(ra) : p.use16 ? rec16_lds_bytes(ra) : rec_lds_bytes(ra);
+  };
   // What LDS is left goes to longer prefixes of the two gate tables, 1 KB at a time in turn: a value
   // beyond the prefix costs the whole group a detour (rec_kernel.inc.h, lookup), and with 24576 entries
   // (|x| < 6 in Q3.12) there is about one per million layer-norm outputs instead of one per thousand.
@@ -1050,7 +1054,8 @@ RecPlan plan_rec(const lstm_int_model *m, int l, int T, int B, int share = 1, bo
       p.marked = proj;
       if (m_here) p.mark_at = words_end;
     }
-    // the six slots lie where the launch-per-step path has R h and m of a step: 9 bytes and more per row and cell
+    // the six slots lie where the launch-per-step path has R h and m of a step: 9 bytes and more per row and cell, which is room enough
+    // for 22 to 32 rows, and from 43 on.  (Fewer rows than that run on this kernel with rows16 = 0 alone, and keep the counter.)
     if (rec_marked(ra) && 6 * marked_slot_bytes(ra.Bp, d.GS) <= (int64_t)9 * B * d.GS * 64) {
       ra.flags |= kMarkedState;
       p.marked_state = true;

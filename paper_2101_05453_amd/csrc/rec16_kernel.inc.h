@@ -1069,9 +1069,15 @@ Fn rec16_pick_tag(int fl) {
 }
 template <int KS16, bool PAIR = false, class Fn = rec_fn>
 Fn rec16_pick_ks(int fl, int tag) {
-  if constexpr (KS16 <= 10 && !PAIR)
-    if (tag == 3) return fl == 4 ? rec16_kernel<KS16, 4, PAIR, 3> : fl == 5 ? rec16_kernel<KS16, 5, PAIR, 3> : fl == 6 ? rec16_kernel<KS16, 6, PAIR, 3> : fl == 7 ? rec16_kernel<KS16, 7, PAIR, 3> : nullptr;
-  if (tag == 3) return nullptr;
+  if (tag == 3) {  // layer norm
+    if constexpr (KS16 <= 10 && !PAIR) switch (fl) {
+        case 4: return rec16_kernel<KS16, 4, PAIR, 3>;
+        case 5: return rec16_kernel<KS16, 5, PAIR, 3>;
+        case 6: return rec16_kernel<KS16, 6, PAIR, 3>;
+        case 7: return rec16_kernel<KS16, 7, PAIR, 3>;
+      }
+    return nullptr;
+  }
   if (tag == 0) return rec16_pick_tag<KS16, PAIR, 0, Fn>(fl);
   return tag == 1 ? rec16_pick_tag<KS16, PAIR, 1, Fn>(fl) : rec16_pick_tag<KS16, PAIR, 2, Fn>(fl);
 }

@@ -575,8 +575,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // tile is in the order of the exchange, [k step][32 rows][32 cells], and a wave's eighth of it goes global -> LDS until no word is
   // marked as not written.  Two escape slots: who stores step t + 2 has seen step t + 1 of all others, who had read step t before
   // they made that.  1024 cells, 400 rows, 60 steps, layer norm, counter -> this 485 -> 439 us, without it 331 -> 329; 500 rows,
-  // peephole and layer norm 549 -> 535; 700 cells, 300 rows, layer norm 437 -> 391.  Two row tiles, twice the bytes, keep the counter: 1024 cells, 1024 rows, layer norm
-  // 843 -> 981, coupled gates too 728 -> 857 -- a look takes more than 1 us then, workgroups that need a second one come late to the
+  // peephole and layer norm 549 -> 535; 700 cells, 300 rows, layer norm 437 -> 391.  Two row tiles, twice the bytes, keep the counter: 1024
+  // cells, 1024 rows, layer norm 843 -> 981, coupled gates too 728 -> 857 -- a look takes more than 1 us then, workgroups that need a second one come late to the
   // statistics, and neither a first pause nor looking at a word per writer first made up for that.
   const size_t hslot = MARK ? (size_t)a.Bp * GS * 64 : 0;
   constexpr int HCH = KS / WAVES;  // pieces of 1 KB for a wave

@@ -35,15 +35,13 @@ static row_stack_fn pick_row_stack(int form, int H, int fl) {
   return H <= 128 && (fl & 8) ? row_stack_pick_256_128(fl) : H <= 192 ? row_stack_pick_192(fl) : row_stack_pick_256(fl);
 }
 
-// Several layers in one launch (row_stack_inst_{64,128,256}.hip): T steps of L layers take T + (L - 1) (piece + 1) steps one behind the other
-// instead of L T, and a launch instead of one or two per layer; W x of a piece comes to 2 to 5 us.  Layer after layer (or the
+// Several layers in one launch (row_stack_inst_{64,128,192,256}.hip): T steps of L layers take T + (L - 1) (piece + 1) steps one
+// behind the other instead of L T, and a launch instead of one or two per layer; W x of a piece comes to 2 to 5 us.  Layer after layer (or the
 // stacked launch, where that is ahead) -> this, us:
 //   6 layers of 86 cells, layer norm, 5 rows, 1 step      63 -> 34     3 layers of 128 cells, layer norm, 39 rows, 43 steps   187 -> 117
 //   6 layers of 32 cells, layer norm, 16 rows, 100 steps 575 -> 201    4 layers of 219 cells, peephole, 11 rows, 64 steps      366 -> 179
 //   2 layers of 203 cells, 131 outputs, 37 rows, 60 steps 217 -> 140    2 layers of 49 cells, 32 rows, 3 steps, two directions   25 -> 22
-row_stack_fn row_stack_pick_64(int fl);
-row_stack_fn row_stack_pick_128(int fl);
-row_stack_fn row_stack_pick_256(int fl);
+
 // Up to 256 rows, a compute unit for each: the launch of four rows per workgroup -> this one, us, 100 steps of 64 rows, input 64
 //                 no layer norm    layer norm    and peephole    projection, no layer norm
 //   64 cells          79 ->  62     161 -> 109     223 -> 173          92 ->  75
@@ -127,7 +125,8 @@ hipError_t launch_row(hipStream_t s, const RowArgs &a) {
   row_fn fn = pick_row(form, f.H, f.flags & 15, own);
   if (!fn || !f.R2h || f.rows_pg != 1 || f.groups != f.B ||
       (own && f.T > row_input_steps(kRowCells[form] / 16)) ||
-      (b.groups > 0 && (!b.R2h || row_form(b.N, b.H) != form || f.H != b.H || f.flags != b.flags || b.rows_pg != 1 || b.groups != b.B || own != (a.in[1].x != nullptr))))
+      (b.groups > 0 && (!b.R2h || row_form(b.N, b.H) != form || f.H != b.H || f.flags != b.flags || b.rows_pg != 1 ||
+                        b.groups != b.B || own != (a.in[1].x != nullptr))))
     return hipErrorInvalidValue;
   size_t lds = row_lds_bytes(f, own);
   if (b.groups > 0) lds = lds > row_lds_bytes(b, own) ? lds : row_lds_bytes(b, own);
@@ -165,14 +164,15 @@ hipError_t launch_row_stack(hipStream_t s, const RowStackArgs &a, int layers, in
     if (a.in[i].done != a.in[0].done + (size_t)i * a.rec.d[0].B * kRowFlagWords || !a.in[0].done) return hipErrorInvalidValue;
   for (int l = 0; l < layers; ++l) {
     const RowInput &in = a.in[l];
-    if (a.rec.d[l].B != a.rec.d[0].B || in.piece < 1 || in.piece > 16 || in.term_steps < (in.x ? in.piece : 2 * in.piece) || (in.x && in.x_bytes < 1024 * in.kx) || !a.rec.d[l].R2h ||
-        (!in.x && !a.rec.d[l].tx2))
+    if (a.rec.d[l].B != a.rec.d[0].B || in.piece < 1 || in.piece > 16 || in.term_steps < (in.x ? in.piece : 2 * in.piece) ||
+        (in.x && in.x_bytes < 1024 * in.kx) || !a.rec.d[l].R2h || (!in.x && !a.rec.d[l].tx2))
       return hipErrorInvalidValue;
   }
   RowStackArgs args = a;
   const int blocks = (widest + 15) / 16;
   void *params[] = {&args};
-  return hipLaunchKernel(reinterpret_cast<const void *>(fn), dim3(layers * a.rec.d[0].B), dim3(64 * (blocks < 4 ? 4 : blocks)), params, lds, s);
+  return hipLaunchKernel(reinterpret_cast<const void *>(fn), dim3(layers * a.rec.d[0].B), dim3(64 * (blocks < 4 ? 4 : blocks)), params,
+                         lds, s);
 }
 
 }  // namespace lstm_int

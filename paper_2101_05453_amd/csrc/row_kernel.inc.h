@@ -51,7 +51,8 @@ constexpr int kRowStack = 2;  // a launch of several layers: computed here, a pi
 // other alone, that of the same row in the layer below, and for nobody above it; a row's workgroups take its layers in the order in
 // which they start, from the bottom, so that whoever is waited for has started (row_stack_plan.h).
 template <int WAVES, int KS16, int FL, int MODE>
-__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVES == 4 ? 2 : WAVES / 4, WAVES == 4 ? 2 : WAVES / 4))) void row_kernel(std::conditional_t<MODE == kRowStack, RowStackArgs, RowArgs> all) {
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVES == 4 ? 2 : WAVES / 4, WAVES == 4 ? 2 : WAVES / 4)))
+void row_kernel(std::conditional_t<MODE == kRowStack, RowStackArgs, RowArgs> all) {
   constexpr bool OWN = MODE == kRowOwn, STACK = MODE == kRowStack;
   constexpr bool cifg = FL & 1, ph = FL & 2, ln = FL & 4, proj = FL & 8;
   constexpr int NC = 16 * WAVES;  // cells and outputs of the workgroup at most
@@ -194,7 +195,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
         const int t = t0 + 4 * q + v;  // steps past the last one go to a place nobody reads
         uint8_t *const to = t < tn ? dst + (OWN ? t : 4 * q + v) * TERM_STRIDE + c16 * 2 : reinterpret_cast<uint8_t *>(flag) - g_from * 32 + 4;
 #pragma unroll
-        for (int g = g_from; g < g_end; ++g) *reinterpret_cast<int16_t *>(to + (t < tn ? g : g_from) * 32) = (int16_t)rescale_sat16_pre<0>(acc[g - g0][v], in.rs[g]);
+        for (int g = g_from; g < g_end; ++g)
+          *reinterpret_cast<int16_t *>(to + (t < tn ? g : g_from) * 32) = (int16_t)rescale_sat16_pre<0>(acc[g - g0][v], in.rs[g]);
       }
     }
   };

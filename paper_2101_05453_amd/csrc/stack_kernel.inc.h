@@ -10,15 +10,19 @@
 //   * a layer's output rows are stored with agent-scope stores, which write
 //     through the XCD's L2, and a flag per (layer, row tile) counts the
 //     finished steps; the next layer polls it and reads the rows with loads
-//     that bypass its own L2.  Every such line is written once per launch and
-//     was never read before, so no cache on the reading side can hold an older
-//     copy.
+//     that bypass its own L2 (sc1).  With the flag every such line is written
+//     once per launch and was never read before.  A launch of one item per layer
+//     (ONE, below) reads the lines again and again while they are being
+//     written, so there it is the loads alone, past the reader's L1 and L2,
+//     that keep an older copy from being seen: a plain load of these rows would
+//     find the marks for good.
 //   * the cell state lives in memory between the items of a row tile.
 // A launch of one item per layer (ONE, the streaming call) hands m and the rows between the layers on in marked words: who needs
 // them polls the words themselves.  8 layers of 2048 cells, 640 outputs, layer norm, 32 rows, one step, us: 111.6 with counters and flags,
 // 105.9 with m in marked words, 103.0 with the rows too, 101.3 with what the first item needs asked for in the order of its use.
-// What is left: 20 us until layer 0 has its weights (10.5 MB through one XCD), then 9 to 10 us a layer: W x 0.8, gate sums 0.6, statistics
-// 1.4, layer norm to the cell 1.5, hidden 0.7, m and the projection 2.3, the rows to the next XCD 1.3 to 3.5.
+// What is left, by the timers of each layer's first workgroup: 27 us until layer 0 has its weights (19 the set-up launch, the start and
+// what is loaded ahead of R h, 8 R and W, 10.5 MB through one XCD), 10 its step, then 9.4 a layer: W x 0.8, gate sums 0.6,
+// statistics 1.4, layer norm to the cell 1.5, hidden 0.5, m and the projection 2.3, the rows to the next XCD 2.3.
 // Included by the stack_inst_*.hip translation units.
 #pragma once
 
