@@ -1190,7 +1190,7 @@ RowStackPlan plan_row_stack(const lstm_int_model *const *m, int dirs, int64_t T,
   }
   // Expected time, us, by step, W x of a piece of the sequence, hand-over to the next layer; fitted to 590 calls of 2 to 6 layers of 32 to
   // 256 cells in all variants, 1 to 100 steps, pieces of 1 to 16 steps, with either input (off by 4 % at the median; the piece that it
-  // picks costs 0.7 % against the best of those timed, the choice against the other ways 1 %).
+  // picks costs 0.7 % against the best of those timed, the choice against the other ways 1 %), and 0.5 for the order of the starts.
   const double ln = h0.layer_norm() ? 1 : 0, pr = h0.projection() ? 1 : 0, late_o = h0.layer_norm() && h0.peephole() ? 1 : 0;
   static const double kCost[3][6] = {{0.60, 0.48, 0.56, 0.13, 1.66, 0.008}, {0.69, 0.67, 0.64, 0.11, 1.86, 0.007}, {0.98, 0.77, 0.85, 0.16, 1.60, 0.019}};
   const double(&k)[6] = kCost[widest <= 64 ? 0 : widest <= 128 ? 1 : 2];
@@ -1204,7 +1204,7 @@ RowStackPlan plan_row_stack(const lstm_int_model *const *m, int dirs, int64_t T,
       for (int piece = 1; piece <= std::min<int64_t>(16, T); ++piece) {
         if (refused[own][piece] || (m[0]->row_stack_piece && piece != std::min<int64_t>(m[0]->row_stack_piece, T))) continue;
         const double pieces = (double)((T + piece - 1) / piece), t = own ? std::max(terms0, terms) : terms;
-        const double us = 5.0 + T * step + pieces * t + (L - 1) * (piece * step + 3.7 + (T > piece ? step : 0)) + (own ? terms0 : gemm);
+        const double us = 5.5 + T * step + pieces * t + (L - 1) * (piece * step + 3.7 + (T > piece ? step : 0)) + (own ? terms0 : gemm);
         if (p.us > 0 && us >= p.us) continue;
         p.us = us;
         p.piece = piece;
