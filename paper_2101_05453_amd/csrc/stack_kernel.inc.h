@@ -14,8 +14,8 @@
 //     once per launch and was never read before.  A launch of one item per layer
 //     (ONE, below) reads the lines again and again while they are being
 //     written, so there it is the loads alone, past the reader's L1 and L2,
-//     that keep an older copy from being seen: a plain load of these rows would
-//     find the marks for good.
+//     that keep an older copy from being seen: a plain load of these rows could
+//     go on finding the marks in that L2.
 //   * the cell state lives in memory between the items of a row tile.
 // A launch of one item per layer (ONE, the streaming call) hands m and the rows between the layers on in marked words: who needs
 // them polls the words themselves.  8 layers of 2048 cells, 640 outputs, layer norm, 32 rows, one step, us: 111.6 with counters and flags,
